@@ -12,62 +12,9 @@
 // time, and the merge is a rank computation on both sides followed by one reduction of equal
 // neighbours; the stages and the two arrays are the paper's.
 #pragma once
-#include "common.hpp"
+#include "sort_kernels.hpp"
 
 namespace spg {
-
-// In-place exclusive scan of n int64 counters by one workgroup; v[n] receives the total.
-__global__ __launch_bounds__(1024) void k_scan_i64(int64_t n, long long* __restrict__ v) {
-  __shared__ long long part[1024];
-  const int tid = threadIdx.x;
-  const int64_t per = (n + 1023) / 1024;
-  const int64_t lo = tid * per, hi = lo + per < n ? lo + per : n;
-  long long s = 0;
-  for (int64_t i = lo; i < hi; ++i) s += v[i];
-  part[tid] = s;
-  __syncthreads();
-  for (int dd = 1; dd < 1024; dd <<= 1) {
-    const long long t = tid >= dd ? part[tid - dd] : 0;
-    __syncthreads();
-    part[tid] += t;
-    __syncthreads();
-  }
-  long long run = part[tid] - s;
-  for (int64_t i = lo; i < hi; ++i) { const long long c = v[i]; v[i] = run; run += c; }
-  if (tid == 1023) v[n] = part[1023];
-}
-
-// Exclusive scan of n 32-bit counters in place, in three steps: sums of tiles of kScanTileU32 counters,
-// a scan of those sums (one workgroup: k_scan_u32), and the scan inside every tile on top of its sum.
-constexpr int kScanTileU32 = 4096;   // 256 threads x 16 counters
-__global__ __launch_bounds__(256) void k_scan_tile_sums(int64_t n, const unsigned* __restrict__ v, unsigned* __restrict__ sums) {
-  __shared__ unsigned ws[4];
-  const int64_t base = (int64_t)blockIdx.x * kScanTileU32;
-  unsigned s = 0;
-  for (int t = 0; t < 16; ++t) {
-    const int64_t i = base + (int64_t)t * 256 + threadIdx.x;
-    if (i < n) s += v[i];
-  }
-  s = (unsigned)wave_sum((int)s);
-  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) sums[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
-}
-
-__global__ __launch_bounds__(256) void k_scan_tile_final(int64_t n, unsigned* __restrict__ v, const unsigned* __restrict__ sums) {
-  __shared__ unsigned ws[4];
-  const int64_t base = (int64_t)blockIdx.x * kScanTileU32 + (int64_t)threadIdx.x * 16;   // a thread owns 16 consecutive counters
-  unsigned x[16], s = 0;
-#pragma unroll
-  for (int t = 0; t < 16; ++t) { x[t] = base + t < n ? v[base + t] : 0u; s += x[t]; }
-  const unsigned incl = (unsigned)wave_incl_scan((int)s);
-  if ((threadIdx.x & 63) == 63) ws[threadIdx.x >> 6] = incl;
-  __syncthreads();
-  unsigned run = sums[blockIdx.x] + incl - s;
-  for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) run += ws[w];
-#pragma unroll
-  for (int t = 0; t < 16; ++t) { if (base + t < n) v[base + t] = run; run += x[t]; }
-}
 
 // Row index of every entry of a CSR matrix (a wave per row).
 __global__ __launch_bounds__(256) void k_expand_rows(int64_t rows, const int64_t* __restrict__ rowptr, int32_t* __restrict__ out) {
@@ -113,8 +60,8 @@ __global__ __launch_bounds__(256) void k_outer_insert(int64_t t0, int64_t n, int
                                                       const int32_t* __restrict__ match, const int64_t* __restrict__ a_ptr,
                                                       const int32_t* __restrict__ a_idx, const T* __restrict__ a_val,
                                                       const int64_t* __restrict__ b_ptr, const int32_t* __restrict__ b_idx,
-                                                      const T* __restrict__ b_val, unsigned long long* __restrict__ keys,
-                                                      unsigned* __restrict__ seq, double* __restrict__ vals) {
+                                                      const T* __restrict__ b_val, int col_bits, unsigned long long* __restrict__ keys,
+                                                      double* __restrict__ vals) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) {
     const int64_t t = t0 + x;
@@ -127,8 +74,7 @@ __global__ __launch_bounds__(256) void k_outer_insert(int64_t t0, int64_t n, int
     const int64_t lb = b_ptr[q + 1] - b_ptr[q];
     const int64_t local = t - off[lo];
     const int64_t pa = a_ptr[lo] + local / lb, pb = b_ptr[q] + local % lb;
-    keys[x] = ((unsigned long long)(unsigned)a_idx[pa] << 32) | (unsigned)b_idx[pb];
-    seq[x] = (unsigned)x;
+    keys[x] = ((unsigned long long)(unsigned)a_idx[pa] << col_bits) | (unsigned)b_idx[pb];
     vals[x] = (double)a_val[pa] * (double)b_val[pb];
   }
 }
@@ -140,17 +86,16 @@ __global__ __launch_bounds__(256) void k_outer_heads(int64_t n, const unsigned l
 }
 
 // Adds up equal coordinates of a sorted array: the thread of a run's first component walks the run in
-// order (seq, when given, leads to the value of a component through the sort's permutation).
+// order.
 // pos = exclusive scan of the head flags = where the run's sum goes.
-__global__ __launch_bounds__(256) void k_outer_reduce(int64_t n, const unsigned long long* __restrict__ keys, const unsigned* __restrict__ seq,
-                                                      const double* __restrict__ vals, const unsigned* __restrict__ pos,
+__global__ __launch_bounds__(256) void k_outer_reduce(int64_t n, const unsigned long long* __restrict__ keys, const double* __restrict__ vals, const unsigned* __restrict__ pos,
                                                       unsigned long long* __restrict__ out_keys, double* __restrict__ out_vals) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) {
     const unsigned long long key = keys[x];
     if (x > 0 && keys[x - 1] == key) continue;
-    double s = vals[seq ? seq[x] : x];
-    for (int64_t y = x + 1; y < n && keys[y] == key; ++y) s += vals[seq ? seq[y] : y];
+    double s = vals[x];
+    for (int64_t y = x + 1; y < n && keys[y] == key; ++y) s += vals[y];
     out_keys[pos[x]] = key;
     out_vals[pos[x]] = s;
   }
@@ -182,10 +127,10 @@ __global__ __launch_bounds__(256) void k_outer_merge(int64_t na, const unsigned 
 // Compress stage: columns and values of C from the all array (the row pointer comes from the coordinates' high halves).
 template <typename T>
 __global__ __launch_bounds__(256) void k_outer_emit(int64_t n, const unsigned long long* __restrict__ keys, const double* __restrict__ vals,
-                                                    int32_t* __restrict__ colidx, T* __restrict__ values) {
+                                                    unsigned long long col_mask, int32_t* __restrict__ colidx, T* __restrict__ values) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) {
-    colidx[x] = (int32_t)(unsigned)keys[x];
+    colidx[x] = (int32_t)(keys[x] & col_mask);
     values[x] = (T)vals[x];
   }
 }

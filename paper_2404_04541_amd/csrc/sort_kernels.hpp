@@ -1,0 +1,296 @@
+// Stable least-significant-digit radix sort of (key, payload) pairs and exclusive scans, used by the
+// tensor unfolding, the doubly compressed formats and the outer-product workspace.
+//
+// One pass over a digit of at most 8 bits:
+//   k_sort_hist     entries per digit of every range of consecutive tiles (at most kSortMaxRanges ranges)
+//   k_sort_scan     exclusive scan over the ranges, one workgroup per digit
+//   k_sort_scatter  a workgroup walks its range tile by tile: ranks its entries (ballots inside a wave,
+//                   counters per wave in LDS), puts the tile into digit order in LDS and writes every
+//                   digit's entries as one run
+// Bound: memory.  A pass moves key + payload once in and once out and the keys once more for the counts.
+// Carrying the payload (the value itself) costs at most 8 bytes an entry and pass and saves the gather
+// through a permutation at the end, which costs a 128-byte line per entry.  Tiles of 8192 entries keep the
+// runs of a digit at 32 entries (256 bytes of keys) on average; a wave that scattered its own 64 entries
+// without the exchange in LDS wrote 4-byte pieces to as many lines.
+// 10^7 tensor entries of 33 key bits and double values, kernel time per pass over a digit: scan of all counters
+// 1290 -> 5 us (one workgroup had walked them all), scatter 210 -> 105 us (3.1 TB/s of key and value moved), counts
+// 27 -> 17 us; the gather of the values behind the last pass (211 us) is gone.  Unfolding as a whole 8.0 -> 0.8 ms.
+#pragma once
+#include "common.hpp"
+
+namespace spg {
+
+constexpr int kSortThreads = 512;
+constexpr int kSortItems = 16;
+constexpr int kSortTile = kSortThreads * kSortItems;
+constexpr int kSortBins = 256;
+constexpr int kSortMaxRanges = 1024;
+constexpr int kSortWaves = kSortThreads / kWave;
+
+// Adds the digit counts of this workgroup's LDS histogram copies up and writes them for range r of nr.
+constexpr int kHistCopies = 4;
+__device__ __forceinline__ void sort_hist_out(const unsigned (*cnt)[kSortBins], int nbins, int r, int nr, unsigned* __restrict__ hist) {
+  __syncthreads();
+  for (int d = threadIdx.x; d < nbins; d += kSortThreads) {
+    unsigned s = 0;
+#pragma unroll
+    for (int c = 0; c < kHistCopies; ++c) s += cnt[c][d];
+    hist[(int64_t)d * nr + r] = s;
+  }
+}
+
+// hist[digit * gridDim.x + range] = entries of the range whose digit (bits [shift, shift + bits) of the key) is `digit`
+template <typename K>
+__global__ __launch_bounds__(kSortThreads) void k_sort_hist(int64_t n, int64_t per_range, int shift, int bits, const K* __restrict__ keys,
+                                                            unsigned* __restrict__ hist) {
+  __shared__ unsigned cnt[kHistCopies][kSortBins];
+  for (int d = threadIdx.x; d < kHistCopies * kSortBins; d += kSortThreads) (&cnt[0][0])[d] = 0;
+  __syncthreads();
+  const unsigned mask = (1u << bits) - 1;
+  const int64_t lo = (int64_t)blockIdx.x * per_range, hi = lo + per_range < n ? lo + per_range : n;
+  unsigned* mine = cnt[threadIdx.x & (kHistCopies - 1)];
+  for (int64_t p = lo + threadIdx.x; p < hi; p += kSortThreads * 4) {
+    K k[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) k[u] = p + u * kSortThreads < hi ? keys[p + u * kSortThreads] : K(0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (p + u * kSortThreads < hi) atomicAdd(&mine[(unsigned)(k[u] >> shift) & mask], 1u);
+  }
+  sort_hist_out(cnt, 1 << bits, blockIdx.x, gridDim.x, hist);
+}
+
+// Workgroup d: exclusive scan of hist[d * nr .. (d + 1) * nr) in place, total of the digit to totals[d].
+__global__ __launch_bounds__(256) void k_sort_scan(int nr, unsigned* __restrict__ hist, unsigned* __restrict__ totals) {
+  constexpr int kPer = kSortMaxRanges / 256;
+  __shared__ unsigned ws[4];
+  unsigned* h = hist + (int64_t)blockIdx.x * nr;
+  const int base = threadIdx.x * kPer;
+  unsigned v[kPer], s = 0;
+#pragma unroll
+  for (int t = 0; t < kPer; ++t) { v[t] = base + t < nr ? h[base + t] : 0u; s += v[t]; }
+  const unsigned incl = (unsigned)wave_incl_scan((int)s);
+  if (lane_id() == kWave - 1) ws[threadIdx.x >> 6] = incl;
+  __syncthreads();
+  unsigned run = incl - s;
+  for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) run += ws[w];
+#pragma unroll
+  for (int t = 0; t < kPer; ++t) {
+    if (base + t < nr) h[base + t] = run;
+    run += v[t];
+  }
+  if (threadIdx.x == 255) totals[blockIdx.x] = run;
+}
+
+// Exclusive scan of one value per thread over the first 256 threads of the workgroup; all threads call.
+__device__ __forceinline__ unsigned scan_bins(unsigned v, unsigned* ws) {
+  const unsigned incl = (unsigned)wave_incl_scan((int)v);
+  const int wave = threadIdx.x >> 6;
+  __syncthreads();
+  if (lane_id() == kWave - 1 && wave < kSortBins / kWave) ws[wave] = incl;
+  __syncthreads();
+  unsigned before = 0;
+#pragma unroll
+  for (int w = 0; w < kSortBins / kWave; ++w) before += w < wave ? ws[w] : 0u;
+  return before + incl - v;
+}
+
+// One pass.  P: payload.  col_out (optional): the low bits of the key (key & col_mask), written with the last pass.
+template <typename K, typename P>
+__global__ __launch_bounds__(kSortThreads) void k_sort_scatter(int64_t n, int64_t per_range, int shift, int bits, const K* __restrict__ keys,
+                                                               const P* __restrict__ pay, const unsigned* __restrict__ hist,
+                                                               const unsigned* __restrict__ totals, K* __restrict__ keys_out,
+                                                               P* __restrict__ pay_out, int32_t* __restrict__ col_out, K col_mask) {
+  constexpr size_t kSlot = sizeof(K) > sizeof(P) ? sizeof(K) : sizeof(P);
+  __shared__ __align__(16) unsigned char s_tile[kSortTile * kSlot];   // the tile in digit order: keys, then payloads
+  __shared__ unsigned s_cnt[kSortWaves][kSortBins];   // entries of a digit in every wave, then their prefix over the waves
+  __shared__ unsigned s_to[kSortBins];                // global position of a digit's run minus its position in the tile
+  __shared__ unsigned s_at[kSortBins];                // position of a digit's run in the tile
+  __shared__ unsigned ws[kSortBins / kWave];
+  K* s_key = reinterpret_cast<K*>(s_tile);
+  P* s_pay = reinterpret_cast<P*>(s_tile);
+  const int tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
+  const int nbins = 1 << bits;
+  const unsigned mask = (unsigned)nbins - 1;
+  const unsigned long long below = lane == 0 ? 0ULL : (~0ULL >> (64 - lane));
+  unsigned at_global = 0;   // (thread d < nbins) where the next entry of digit d goes
+  {
+    const unsigned mine = tid < nbins ? totals[tid] : 0u;
+    const unsigned before = scan_bins(mine, ws);
+    if (tid < nbins) at_global = before + hist[(int64_t)tid * gridDim.x + blockIdx.x];
+  }
+  const int64_t lo = (int64_t)blockIdx.x * per_range, hi = lo + per_range < n ? lo + per_range : n;
+  for (int64_t t0 = lo; t0 < hi; t0 += kSortTile) {
+    const int count = (int)(hi - t0 < kSortTile ? hi - t0 : kSortTile);
+    // a wave owns kSortItems * 64 consecutive entries, 64 at a time
+    const int first = wave * (kSortItems * kWave) + lane;
+    K key[kSortItems];
+    P val[kSortItems];
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+      const int e = first + i * kWave;
+      key[i] = e < count ? keys[t0 + e] : K(~K(0));   // (behind the end: the last digit, behind every real entry)
+      val[i] = e < count ? pay[t0 + e] : P(0);
+    }
+    for (int d = tid; d < kSortWaves * kSortBins; d += kSortThreads) (&s_cnt[0][0])[d] = 0;
+    __syncthreads();
+    unsigned short rank[kSortItems];
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+      const unsigned d = (unsigned)(key[i] >> shift) & mask;
+      unsigned long long peers = ~0ULL;
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        if (b < bits) {
+          const unsigned long long m = __ballot((d >> b) & 1u);
+          peers &= ((d >> b) & 1u) ? m : ~m;
+        }
+      }
+      const unsigned before = s_cnt[wave][d];
+      rank[i] = (unsigned short)(before + (unsigned)__popcll(peers & below));
+      wave_sync_lds();
+      if ((peers & below) == 0) s_cnt[wave][d] = before + (unsigned)__popcll(peers);
+      wave_sync_lds();
+    }
+    __syncthreads();
+    unsigned total = 0;
+    if (tid < nbins) {
+#pragma unroll
+      for (int w = 0; w < kSortWaves; ++w) { const unsigned c = s_cnt[w][tid]; s_cnt[w][tid] = total; total += c; }
+    }
+    const unsigned at = scan_bins(total, ws);
+    if (tid < nbins) {
+      s_at[tid] = at;
+      s_to[tid] = at_global - at;
+      at_global += total;
+    }
+    __syncthreads();
+    unsigned short pos[kSortItems];
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+      const unsigned d = (unsigned)(key[i] >> shift) & mask;
+      pos[i] = (unsigned short)(s_at[d] + s_cnt[wave][d] + rank[i]);
+      s_key[pos[i]] = key[i];
+    }
+    __syncthreads();
+    unsigned to[kSortItems];
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+      const int e = i * kSortThreads + tid;
+      if (e < count) {
+        const K k = s_key[e];
+        to[i] = s_to[(unsigned)(k >> shift) & mask] + (unsigned)e;
+        keys_out[to[i]] = k;
+        if (col_out) col_out[to[i]] = (int32_t)(k & col_mask);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) s_pay[pos[i]] = val[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+      const int e = i * kSortThreads + tid;
+      if (e < count) pay_out[to[i]] = s_pay[e];
+    }
+    __syncthreads();
+  }
+}
+
+// ptr[r] = first position of the sorted keys whose high part (key >> shift) is r or more (r = 0 .. rows).  A workgroup takes
+// kPtrRows consecutive values: the stretch of keys they fall into is bisected once, each value then only inside it.
+constexpr int kPtrRows = 2048;
+template <typename K>
+__global__ __launch_bounds__(256) void k_key_ptr(int64_t n, int64_t rows, int shift, const K* __restrict__ keys, int64_t* __restrict__ ptr) {
+  __shared__ int64_t bound[2];
+  const int64_t r0 = (int64_t)blockIdx.x * kPtrRows;
+  auto first_of = [&](int64_t r, int64_t lo, int64_t hi) {
+    while (lo < hi) {
+      const int64_t mid = lo + ((hi - lo) >> 1);
+      if ((int64_t)(keys[mid] >> shift) < r) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+  };
+  if (threadIdx.x < 2) bound[threadIdx.x] = first_of(r0 + threadIdx.x * (int64_t)kPtrRows, 0, n);
+  __syncthreads();
+  const int64_t lo = bound[0], hi = bound[1];
+  for (int64_t r = r0 + threadIdx.x; r < r0 + kPtrRows && r <= rows; r += 256) ptr[r] = first_of(r, lo, hi);
+}
+
+// ---- exclusive scan in place, v[n] = total: sums of tiles, scan of the sums by one workgroup, scan inside the tiles ----
+constexpr int kScanV = 16;
+constexpr int kScanTileN = 256 * kScanV;
+
+template <typename T>
+__device__ __forceinline__ T scan_wave(T v) {   // inclusive, over the wave
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const T o = __shfl_up(v, d, kWave);
+    if (lane_id() >= d) v += o;
+  }
+  return v;
+}
+
+// exclusive over a workgroup of 256 threads, with the total
+template <typename T>
+__device__ __forceinline__ T scan_256(T v, T& total, T* ws) {
+  const T incl = scan_wave(v);
+  const int wave = threadIdx.x >> 6;
+  __syncthreads();
+  if (lane_id() == kWave - 1) ws[wave] = incl;
+  __syncthreads();
+  T before = 0;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) { const T x = ws[w]; if (w < wave) before += x; total += x; }
+  return before + incl - v;
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_scan_sums(int64_t n, const T* __restrict__ v, T* __restrict__ sums) {
+  __shared__ T ws[4];
+  const int64_t base = (int64_t)blockIdx.x * kScanTileN;
+  T s = 0;
+#pragma unroll
+  for (int t = 0; t < kScanV; ++t) {
+    const int64_t i = base + (int64_t)t * 256 + threadIdx.x;
+    if (i < n) s += v[i];
+  }
+  T total;
+  (void)scan_256(s, total, ws);
+  if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_scan_top(int64_t n, T* __restrict__ sums) {
+  __shared__ T ws[4];
+  T carry = 0;
+  for (int64_t b = 0; b < n; b += kScanTileN) {
+    const int64_t base = b + (int64_t)threadIdx.x * kScanV;
+    T x[kScanV], s = 0;
+#pragma unroll
+    for (int t = 0; t < kScanV; ++t) { x[t] = base + t < n ? sums[base + t] : T(0); s += x[t]; }
+    T total;
+    T run = carry + scan_256(s, total, ws);
+#pragma unroll
+    for (int t = 0; t < kScanV; ++t) { if (base + t < n) sums[base + t] = run; run += x[t]; }
+    carry += total;
+  }
+  if (threadIdx.x == 0) sums[n] = carry;
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_scan_tiles(int64_t n, T* __restrict__ v, const T* __restrict__ sums) {
+  __shared__ T ws[4];
+  const int64_t base = (int64_t)blockIdx.x * kScanTileN + (int64_t)threadIdx.x * kScanV;   // a thread owns 16 consecutive values
+  T x[kScanV], s = 0;
+#pragma unroll
+  for (int t = 0; t < kScanV; ++t) { x[t] = base + t < n ? v[base + t] : T(0); s += x[t]; }
+  T total;
+  T run = sums[blockIdx.x] + scan_256(s, total, ws);
+#pragma unroll
+  for (int t = 0; t < kScanV; ++t) { if (base + t < n) v[base + t] = run; run += x[t]; }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) v[n] = sums[gridDim.x];
+}
+
+}  // namespace spg

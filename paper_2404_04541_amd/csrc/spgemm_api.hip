@@ -17,6 +17,7 @@
 #include "hash_kernels.hpp"
 #include "dense_kernels.hpp"
 #include "staged_kernels.hpp"
+#include "sort_kernels.hpp"
 #include "tensor_kernels.hpp"
 #include "outer_kernels.hpp"
 
@@ -707,6 +708,8 @@ int spgemm(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, spgemm_csr
 }
 
 
+}  // extern "C"
+
 // ---- sparse tensor entry points ------------------------------------------------------------
 
 namespace {
@@ -737,26 +740,6 @@ int check_tensor(spgemm_context* h, int mode, int64_t I, int64_t J, int64_t K, i
   return SPGEMM_OK;
 }
 
-// Temporary memory of one unfolding: two key buffers, two index buffers, the tile histograms, one flag.
-struct UnfoldTmp {
-  size_t o_k0, o_k1, o_i0, o_i1, o_h, o_bad, bytes;
-  int64_t ntiles;
-};
-
-UnfoldTmp unfold_tmp_layout(int64_t nnz) {
-  UnfoldTmp t{};
-  t.ntiles = ceil_div(nnz > 0 ? nnz : 1, kSortTile);
-  size_t off = 0;
-  t.o_k0 = off; off = align_up(off + (size_t)nnz * 8);
-  t.o_k1 = off; off = align_up(off + (size_t)nnz * 8);
-  t.o_i0 = off; off = align_up(off + (size_t)nnz * 4);
-  t.o_i1 = off; off = align_up(off + (size_t)nnz * 4);
-  t.o_h = off; off = align_up(off + (size_t)t.ntiles * 256 * 4);
-  t.o_bad = off; off = align_up(off + 4);
-  t.bytes = off;
-  return t;
-}
-
 __global__ void k_clear_int(int* p) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0;
 }
@@ -767,51 +750,102 @@ int bits_of(int64_t n) {   // bits that hold 0 .. n-1
   return b;
 }
 
-// Stable least-significant-digit radix sort of (key, index) pairs, 8 bits a pass, over the low bits_lo bits
-// and the bits_hi bits from bit 32 up.  Returns which of the two buffers holds the result.
-int sort_pairs(spgemm_context* h, int64_t n, int64_t ntiles, int bits_lo, int bits_hi, unsigned long long* const keys[2],
-               unsigned* const idx[2], unsigned* hist) {
+// How a sort of n entries by nbits key bits is cut: passes over digits of `bits` bits, ranges of whole tiles.
+struct SortShape {
+  int passes, bits, ranges;
+  int64_t per_range;
+};
+
+SortShape sort_shape(int64_t n, int nbits) {
+  SortShape sh{};
+  if (nbits < 1) nbits = 1;
+  sh.passes = (nbits + 7) / 8;
+  sh.bits = (nbits + sh.passes - 1) / sh.passes;
+  const int64_t tiles = ceil_div(n > 0 ? n : 1, kSortTile);
+  const int64_t tiles_per = ceil_div(tiles, kSortMaxRanges);
+  sh.ranges = (int)ceil_div(tiles, tiles_per);
+  sh.per_range = tiles_per * kSortTile;
+  return sh;
+}
+
+// Counters of a sort: one per digit value and range, and the digits' totals.
+size_t sort_counter_bytes(int64_t n) { return (size_t)(sort_shape(n, 8).ranges + 1) * kSortBins * 4; }
+
+// Stable radix sort of n (key, payload) pairs.  keys[0] holds the keys; the payloads start in pay_in and end in pay_a (pay_b is
+// the other buffer; pay_in may be the one of the two that the first pass does not write).  first_counted: the first digit's
+// counts are in `counters` already.  Returns which of the two key buffers holds the result.
+template <typename K, typename P>
+int sort_pairs(spgemm_context* h, int64_t n, const SortShape& sh, K* const keys[2], const P* pay_in, P* pay_a, P* pay_b, unsigned* counters,
+               bool first_counted, int32_t* col_out, K col_mask) {
   hipStream_t s = h->stream;
+  unsigned* hist = counters + kSortBins;
   int cur = 0;
-  const unsigned gt = (unsigned)ceil_div(ntiles, kSortWgWaves);
-  for (int part = 0; part < 2; ++part) {
-    const int base = part == 0 ? 0 : 32, nbits = part == 0 ? bits_lo : bits_hi;
-    for (int shift = base; shift < base + nbits; shift += 8) {
-      hipLaunchKernelGGL(k_radix_hist, dim3(gt), dim3(256), 0, s, n, ntiles, shift, keys[cur], hist);
-      hipLaunchKernelGGL(k_scan_u32, dim3(1), dim3(1024), 0, s, ntiles * 256, hist);
-      hipLaunchKernelGGL(k_radix_scatter, dim3(gt), dim3(256), 0, s, n, ntiles, shift, keys[cur], idx[cur], hist, keys[1 - cur], idx[1 - cur]);
-      cur = 1 - cur;
-    }
+  for (int pass = 0; pass < sh.passes; ++pass) {
+    const int shift = pass * sh.bits;
+    const bool last = pass + 1 == sh.passes;
+    P* out = (sh.passes - 1 - pass) % 2 == 0 ? pay_a : pay_b;
+    if (pass > 0 || !first_counted)
+      hipLaunchKernelGGL(k_sort_hist<K>, dim3(sh.ranges), dim3(kSortThreads), 0, s, n, sh.per_range, shift, sh.bits, keys[cur], hist);
+    hipLaunchKernelGGL(k_sort_scan, dim3(1u << sh.bits), dim3(256), 0, s, sh.ranges, hist, counters);
+    hipLaunchKernelGGL((k_sort_scatter<K, P>), dim3(sh.ranges), dim3(kSortThreads), 0, s, n, sh.per_range, shift, sh.bits, keys[cur], pay_in, hist,
+                       counters, keys[1 - cur], out, last ? col_out : (int32_t*)nullptr, col_mask);
+    pay_in = out;
+    cur = 1 - cur;
   }
   return cur;
 }
 
-// Keys, stable radix sort, compress, row pointer; everything it touches is given by the caller.
+// Temporary memory of one unfolding: two key buffers, one value buffer (the output is the other), the sort's counters, one flag.
+struct UnfoldTmp {
+  size_t o_k0, o_k1, o_v, o_h, o_bad, bytes;
+};
+
+UnfoldTmp unfold_tmp_layout(int64_t nnz) {
+  UnfoldTmp t{};
+  size_t off = 0;
+  t.o_k0 = off; off = align_up(off + (size_t)nnz * 8);
+  t.o_k1 = off; off = align_up(off + (size_t)nnz * 8);
+  t.o_v = off; off = align_up(off + (size_t)nnz * 8);
+  t.o_h = off; off = align_up(off + sort_counter_bytes(nnz));
+  t.o_bad = off; off = align_up(off + 4);
+  t.bytes = off;
+  return t;
+}
+
+template <typename K, typename T>
+void unfold_launch(spgemm_context* h, const ModeView& v, int64_t nnz, const T* xval, unsigned char* tmp, const UnfoldTmp& lay, int col_bits,
+                   int row_bits, int64_t* rp, int32_t* col, T* val) {
+  hipStream_t s = h->stream;
+  const int64_t rows = v.A * v.B;
+  K* keys[2] = {reinterpret_cast<K*>(tmp + lay.o_k0), reinterpret_cast<K*>(tmp + lay.o_k1)};
+  unsigned* counters = reinterpret_cast<unsigned*>(tmp + lay.o_h);
+  int cur = 0;
+  if (nnz > 0) {
+    const SortShape sh = sort_shape(nnz, col_bits + row_bits);
+    hipLaunchKernelGGL(k_tensor_keys<K>, dim3(sh.ranges), dim3(kSortThreads), 0, s, nnz, sh.per_range, v.A, v.B, v.C, col_bits, sh.bits, v.xa, v.xb,
+                       v.xc, keys[0], counters + kSortBins, reinterpret_cast<int*>(tmp + lay.o_bad));
+    cur = sort_pairs<K, T>(h, nnz, sh, keys, xval, val, reinterpret_cast<T*>(tmp + lay.o_v), counters, true, col, (K)(((K)1 << col_bits) - 1));
+  }
+  hipLaunchKernelGGL(k_key_ptr<K>, dim3((unsigned)ceil_div(rows + 1, kPtrRows)), dim3(256), 0, s, nnz, rows, col_bits, keys[cur], rp);
+}
+
+// Keys, stable radix sort, row pointer; everything it touches is given by the caller.
 // Ends with one stream synchronisation (the out-of-range flag comes to the host).
 int unfold_run(spgemm_context* h, const ModeView& v, int64_t nnz, const void* xval, int32_t dtype, unsigned char* tmp, const UnfoldTmp& lay,
                int64_t* rp, int32_t* col, void* val) {
   hipStream_t s = h->stream;
-  const int64_t rows = v.A * v.B;
-  unsigned long long* keys[2] = {reinterpret_cast<unsigned long long*>(tmp + lay.o_k0), reinterpret_cast<unsigned long long*>(tmp + lay.o_k1)};
-  unsigned* idx[2] = {reinterpret_cast<unsigned*>(tmp + lay.o_i0), reinterpret_cast<unsigned*>(tmp + lay.o_i1)};
-  unsigned* hist = reinterpret_cast<unsigned*>(tmp + lay.o_h);
   int* bad = reinterpret_cast<int*>(tmp + lay.o_bad);
   int host_bad = 0;
-  const int64_t ntiles = lay.ntiles;
   hipLaunchKernelGGL(k_clear_int, dim3(1), dim3(64), 0, s, bad);
-  int cur = 0;
-  if (nnz > 0) {
-    const unsigned g = grid_for(nnz, 256 * 4, (int64_t)h->num_cus * 32);
-    hipLaunchKernelGGL(k_tensor_keys, dim3(g), dim3(256), 0, s, nnz, v.A, v.B, v.C, v.xa, v.xb, v.xc, keys[0], idx[0], bad);
-    cur = sort_pairs(h, nnz, ntiles, bits_of(v.C), bits_of(rows), keys, idx, hist);
-    if (dtype == SPGEMM_F32)
-      hipLaunchKernelGGL(k_tensor_compress<float>, dim3(g), dim3(256), 0, s, nnz, keys[cur], idx[cur], static_cast<const float*>(xval), col,
-                         static_cast<float*>(val));
-    else
-      hipLaunchKernelGGL(k_tensor_compress<double>, dim3(g), dim3(256), 0, s, nnz, keys[cur], idx[cur], static_cast<const double*>(xval), col,
-                         static_cast<double*>(val));
+  const int col_bits = bits_of(v.C), row_bits = bits_of(v.A * v.B);
+  const bool narrow = col_bits + row_bits <= 32;
+  if (dtype == SPGEMM_F32) {
+    if (narrow) unfold_launch<uint32_t>(h, v, nnz, static_cast<const float*>(xval), tmp, lay, col_bits, row_bits, rp, col, static_cast<float*>(val));
+    else unfold_launch<unsigned long long>(h, v, nnz, static_cast<const float*>(xval), tmp, lay, col_bits, row_bits, rp, col, static_cast<float*>(val));
+  } else {
+    if (narrow) unfold_launch<uint32_t>(h, v, nnz, static_cast<const double*>(xval), tmp, lay, col_bits, row_bits, rp, col, static_cast<double*>(val));
+    else unfold_launch<unsigned long long>(h, v, nnz, static_cast<const double*>(xval), tmp, lay, col_bits, row_bits, rp, col, static_cast<double*>(val));
   }
-  hipLaunchKernelGGL(k_tensor_rowptr, dim3(grid_for(rows + 1, 256, (int64_t)h->num_cus * 32)), dim3(256), 0, s, nnz, rows, keys[cur], rp);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(&host_bad, bad, 4, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -822,12 +856,14 @@ int unfold_run(spgemm_context* h, const ModeView& v, int64_t nnz, const void* xv
 
 // Scratch of the entry point that allocates nothing: one array per device, held until the process ends.
 constexpr int64_t kNoAllocMaxNnz = SPTENSOR_NOALLOC_MAX_NNZ;
-constexpr size_t kNoAllocScratchBytes = (size_t)kNoAllocMaxNnz * 24 + ((size_t)kNoAllocMaxNnz / kSortTile + 1) * 1024 + 8 * 256;
+constexpr size_t kNoAllocScratchBytes = (size_t)kNoAllocMaxNnz * 24 + ((size_t)kNoAllocMaxNnz / kSortTile + 2) * kSortBins * 4 + 8 * 256;
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 constexpr int kMaxDevices = 64;
 unsigned char* g_scratch_ptr[kMaxDevices] = {};   // device address of `scratch` on each device, from hipGetSymbolAddress
 
 }  // namespace
+
+extern "C" {
 
 int sptensor_unfold(spgemm_handle h, int mode, int64_t I, int64_t J, int64_t K, int64_t nnz, const int32_t* xi, const int32_t* xj,
                     const int32_t* xk, const void* xval, int32_t dtype, spgemm_csr* out) {
@@ -1073,21 +1109,20 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
 
 namespace {
 
-__global__ void k_pair_keys(int64_t n, const int32_t* __restrict__ hi, const int32_t* __restrict__ lo, unsigned long long* __restrict__ keys,
-                            unsigned* __restrict__ idx) {
+__global__ void k_pair_keys(int64_t n, int lo_bits, const int32_t* __restrict__ hi, const int32_t* __restrict__ lo,
+                            unsigned long long* __restrict__ keys) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride) {
-    keys[p] = ((unsigned long long)(unsigned)hi[p] << 32) | (unsigned)lo[p];
-    idx[p] = (unsigned)p;
-  }
+  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride)
+    keys[p] = ((unsigned long long)(unsigned)hi[p] << lo_bits) | (unsigned)lo[p];
 }
 
-// In-place exclusive scan of n counters (n may be hundreds of millions); sums: ceil(n / kScanTileU32) + 1 slots of scratch.
-void scan_u32_large(spgemm_context* h, int64_t n, unsigned* v, unsigned* sums) {
-  const int64_t tiles = ceil_div(n > 0 ? n : 1, kScanTileU32);
-  hipLaunchKernelGGL(k_scan_tile_sums, dim3((unsigned)tiles), dim3(256), 0, h->stream, n, v, sums);
-  hipLaunchKernelGGL(k_scan_u32, dim3(1), dim3(1024), 0, h->stream, tiles, sums);
-  hipLaunchKernelGGL(k_scan_tile_final, dim3((unsigned)tiles), dim3(256), 0, h->stream, n, v, sums);
+// In-place exclusive scan of n values, v[n] = their sum; sums: ceil(n / kScanTileN) + 1 slots of scratch.
+template <typename T>
+void scan_values(spgemm_context* h, int64_t n, T* v, T* sums) {
+  const int64_t tiles = ceil_div(n > 0 ? n : 1, kScanTileN);
+  hipLaunchKernelGGL(k_scan_sums<T>, dim3((unsigned)tiles), dim3(256), 0, h->stream, n, v, sums);
+  hipLaunchKernelGGL(k_scan_top<T>, dim3(1), dim3(256), 0, h->stream, tiles, sums);
+  hipLaunchKernelGGL(k_scan_tiles<T>, dim3((unsigned)tiles), dim3(256), 0, h->stream, n, v, sums);
 }
 
 struct DevBufs {   // device buffers released together
@@ -1116,10 +1151,9 @@ int dcs_compress(spgemm_context* h, int64_t n, int64_t nnz, const int64_t* ptr, 
   if (!pos) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the doubly compressed format failed");
   const unsigned g = grid_for(n, 256, (int64_t)h->num_cus * 32);
   hipLaunchKernelGGL(k_dcs_flags, dim3(g), dim3(256), 0, s, n, ptr, pos);
-  hipLaunchKernelGGL(k_clear_int, dim3(1), dim3(64), 0, s, reinterpret_cast<int*>(pos + n));
-  unsigned* sums = bufs.get<unsigned>((size_t)ceil_div(n + 1, kScanTileU32) + 1);
+  unsigned* sums = bufs.get<unsigned>((size_t)ceil_div(n > 0 ? n : 1, kScanTileN) + 1);
   if (!sums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the doubly compressed format failed");
-  scan_u32_large(h, n + 1, pos, sums);
+  scan_values(h, n, pos, sums);
   unsigned total = 0;
   HIP_TRY(h, hipMemcpyAsync(&total, pos + n, 4, hipMemcpyDeviceToHost, s));
   HIP_TRY(h, hipStreamSynchronize(s));
@@ -1145,60 +1179,62 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
   if (na > 0) {
     hipLaunchKernelGGL(k_outer_count, dim3(grid_for(na, 256, (int64_t)h->num_cus * 32)), dim3(256), 0, s, na, A->vec, A->ptr, nb, B->vec, B->ptr,
                        off, match);
-    hipLaunchKernelGGL(k_scan_i64, dim3(1), dim3(1024), 0, s, na, off);
+    long long* sums = bufs.get<long long>((size_t)ceil_div(na, kScanTileN) + 1);
+    if (!sums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the outer product failed");
+    scan_values(h, na, off, sums);
     HIP_TRY(h, hipMemcpyAsync(&total, off + na, 8, hipMemcpyDeviceToHost, s));
     HIP_TRY(h, hipStreamSynchronize(s));
   }
   if (cap <= 0) cap = (int64_t)1 << 24;
   if (cap > ((int64_t)1 << 30)) cap = (int64_t)1 << 30;
   if (cap > total) cap = total > 0 ? total : 1;
-  const int64_t ntiles = ceil_div(cap, kSortTile);
-  // accumulation array: coordinates and insertion numbers twice (the sort's two buffers), values once
+  // accumulation array: coordinates (row above the column's bits) and values, twice (the sort's two buffers)
+  const int col_bits = bits_of(n);
+  const unsigned long long col_mask = (1ULL << col_bits) - 1;
   unsigned long long* keys[2] = {bufs.get<unsigned long long>((size_t)cap), bufs.get<unsigned long long>((size_t)cap)};
-  unsigned* seq[2] = {bufs.get<unsigned>((size_t)cap), bufs.get<unsigned>((size_t)cap)};
-  double* vals = bufs.get<double>((size_t)cap);
-  unsigned* hist = bufs.get<unsigned>((size_t)ntiles * 256);
-  if (!keys[0] || !keys[1] || !seq[0] || !seq[1] || !vals || !hist) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the accumulation array failed");
+  double* vals[2] = {bufs.get<double>((size_t)cap), bufs.get<double>((size_t)cap)};
+  unsigned* counters = bufs.get<unsigned>(sort_counter_bytes(cap) / 4);
+  if (!keys[0] || !keys[1] || !vals[0] || !vals[1] || !counters) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the accumulation array failed");
   const int64_t cap_grid = (int64_t)h->num_cus * 32;
   // all array: sorted, unique coordinates with their sums
   unsigned long long* all_k = nullptr;
   double* all_v = nullptr;
   int64_t all_n = 0;
   // sorted array with repeats -> unique array: head flags, their scan, one walk per run
-  auto reduce = [&](int64_t cnt, const unsigned long long* k, const unsigned* sq, const double* v, unsigned long long** ok, double** ov,
+  auto reduce = [&](int64_t cnt, const unsigned long long* k, const double* v, unsigned long long** ok, double** ov,
                     int64_t* on) -> int {
     unsigned* pos = bufs.get<unsigned>((size_t)cnt + 1);
-    unsigned* sums = bufs.get<unsigned>((size_t)ceil_div(cnt + 1, kScanTileU32) + 1);
+    unsigned* sums = bufs.get<unsigned>((size_t)ceil_div(cnt, kScanTileN) + 1);
     if (!pos || !sums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the merge stage failed");
     hipLaunchKernelGGL(k_outer_heads, dim3(grid_for(cnt, 256, cap_grid)), dim3(256), 0, s, cnt, k, pos);
-    hipLaunchKernelGGL(k_clear_int, dim3(1), dim3(64), 0, s, reinterpret_cast<int*>(pos + cnt));
-    scan_u32_large(h, cnt + 1, pos, sums);
+    scan_values(h, cnt, pos, sums);
     unsigned uniq = 0;
     HIP_TRY(h, hipMemcpyAsync(&uniq, pos + cnt, 4, hipMemcpyDeviceToHost, s));
     HIP_TRY(h, hipStreamSynchronize(s));
     *ok = bufs.get<unsigned long long>((size_t)uniq);
     *ov = bufs.get<double>((size_t)uniq);
     if (!*ok || !*ov) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the all array failed");
-    hipLaunchKernelGGL(k_outer_reduce, dim3(grid_for(cnt, 256, cap_grid)), dim3(256), 0, s, cnt, k, sq, v, pos, *ok, *ov);
+    hipLaunchKernelGGL(k_outer_reduce, dim3(grid_for(cnt, 256, cap_grid)), dim3(256), 0, s, cnt, k, v, pos, *ok, *ov);
     HIP_TRY(h, hipGetLastError());
     *on = uniq;
     bufs.release(pos);
     bufs.release(sums);
     return SPGEMM_OK;
   };
-  const int bits_lo = bits_of(n), bits_hi = bits_of(m);
   for (long long t0 = 0; t0 < total; t0 += cap) {
     const int64_t cnt = total - t0 < cap ? total - t0 : cap;
     // insert
     hipLaunchKernelGGL(k_outer_insert<T>, dim3(grid_for(cnt, 256, cap_grid)), dim3(256), 0, s, (int64_t)t0, cnt, na, off, match, A->ptr, A->idx,
-                       static_cast<const T*>(A->values), B->ptr, B->idx, static_cast<const T*>(B->values), keys[0], seq[0], vals);
+                       static_cast<const T*>(A->values), B->ptr, B->idx, static_cast<const T*>(B->values), col_bits, keys[0], vals[0]);
     // sort
-    const int cur = sort_pairs(h, cnt, ceil_div(cnt, kSortTile), bits_lo, bits_hi, keys, seq, hist);
+    const SortShape sh = sort_shape(cnt, col_bits + bits_of(m));
+    double* const sorted = vals[sh.passes & 1];
+    const int cur = sort_pairs<unsigned long long, double>(h, cnt, sh, keys, vals[0], sorted, vals[1 - (sh.passes & 1)], counters, false, nullptr, 0ULL);
     // merge: equal coordinates of the batch, then the batch into the all array
     unsigned long long* uk = nullptr;
     double* uv = nullptr;
     int64_t un = 0;
-    int rc = reduce(cnt, keys[cur], seq[cur], vals, &uk, &uv, &un);
+    int rc = reduce(cnt, keys[cur], sorted, &uk, &uv, &un);
     if (rc) return rc;
     if (all_n == 0) {
       all_k = uk; all_v = uv; all_n = un;
@@ -1212,7 +1248,7 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
     unsigned long long* nk = nullptr;
     double* nv = nullptr;
     int64_t nn = 0;
-    rc = reduce(all_n + un, mk, nullptr, mv, &nk, &nv, &nn);
+    rc = reduce(all_n + un, mk, mv, &nk, &nv, &nn);
     if (rc) return rc;
     bufs.release(all_k); bufs.release(all_v); bufs.release(uk); bufs.release(uv); bufs.release(mk); bufs.release(mv);
     all_k = nk; all_v = nv; all_n = nn;
@@ -1221,9 +1257,9 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
   int32_t* col = all_n ? bufs.get<int32_t>((size_t)all_n) : nullptr;
   T* val = all_n ? bufs.get<T>((size_t)all_n) : nullptr;
   if (all_n && (!col || !val)) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of C failed");
-  hipLaunchKernelGGL(k_tensor_rowptr, dim3(grid_for(m + 1, 256, cap_grid)), dim3(256), 0, s, all_n, m, all_k ? all_k : keys[0], rp);
+  hipLaunchKernelGGL(k_key_ptr<unsigned long long>, dim3((unsigned)ceil_div(m + 1, kPtrRows)), dim3(256), 0, s, all_n, m, col_bits, all_k ? all_k : keys[0], rp);
   if (all_n)
-    hipLaunchKernelGGL(k_outer_emit<T>, dim3(grid_for(all_n, 256, cap_grid)), dim3(256), 0, s, all_n, all_k, all_v, col, val);
+    hipLaunchKernelGGL(k_outer_emit<T>, dim3(grid_for(all_n, 256, cap_grid)), dim3(256), 0, s, all_n, all_k, all_v, col_mask, col, val);
   HIP_TRY(h, hipGetLastError());
   HIP_TRY(h, hipStreamSynchronize(s));
   bufs.keep(rp); bufs.keep(col); bufs.keep(val);
@@ -1297,32 +1333,33 @@ int spgemm_dcsc_from_csr(spgemm_handle h, const spgemm_csr* M, spgemm_dcs* out) 
   DevBufs bufs(h);
   const int64_t nnz = M->nnz;
   const size_t vsz = M->dtype == SPGEMM_F32 ? 4 : 8;
-  const int64_t ntiles = ceil_div(nnz > 0 ? nnz : 1, kSortTile);
   // compressed sparse columns first: sort the entries by (column, row), stable
   int32_t* rowid = bufs.get<int32_t>((size_t)nnz);
   unsigned long long* keys[2] = {bufs.get<unsigned long long>((size_t)nnz), bufs.get<unsigned long long>((size_t)nnz)};
-  unsigned* seq[2] = {bufs.get<unsigned>((size_t)nnz), bufs.get<unsigned>((size_t)nnz)};
-  unsigned* hist = bufs.get<unsigned>((size_t)ntiles * 256);
+  void* tmp = bufs.get<unsigned char>((size_t)nnz * vsz);
+  unsigned* counters = bufs.get<unsigned>(sort_counter_bytes(nnz) / 4);
   int64_t* colptr = bufs.get<int64_t>((size_t)M->cols + 1);
   int32_t* idx = bufs.get<int32_t>((size_t)nnz);
   void* val = bufs.get<unsigned char>((size_t)nnz * vsz);
-  if (!rowid || !keys[0] || !keys[1] || !seq[0] || !seq[1] || !hist || !colptr || !idx || !val)
+  if (!rowid || !keys[0] || !keys[1] || !tmp || !counters || !colptr || !idx || !val)
     return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the doubly compressed format failed");
   int cur = 0;
   const int64_t cap_grid = (int64_t)h->num_cus * 32;
+  const int row_bits = bits_of(M->rows);
   if (nnz > 0) {
+    const SortShape sh = sort_shape(nnz, row_bits + bits_of(M->cols));
+    const unsigned long long row_mask = (1ULL << row_bits) - 1;
     hipLaunchKernelGGL(k_expand_rows, dim3(grid_for(M->rows, 4, cap_grid)), dim3(256), 0, s, M->rows, M->rowptr, rowid);
-    hipLaunchKernelGGL(k_pair_keys, dim3(grid_for(nnz, 256 * 4, cap_grid)), dim3(256), 0, s, nnz, M->colidx, rowid, keys[0], seq[0]);
-    cur = sort_pairs(h, nnz, ntiles, bits_of(M->rows), bits_of(M->cols), keys, seq, hist);
-    const unsigned g = grid_for(nnz, 256 * 4, cap_grid);
+    hipLaunchKernelGGL(k_pair_keys, dim3(grid_for(nnz, 256 * 4, cap_grid)), dim3(256), 0, s, nnz, row_bits, M->colidx, rowid, keys[0]);
     if (M->dtype == SPGEMM_F32)
-      hipLaunchKernelGGL(k_tensor_compress<float>, dim3(g), dim3(256), 0, s, nnz, keys[cur], seq[cur], static_cast<const float*>(M->values), idx,
-                         static_cast<float*>(val));
+      cur = sort_pairs<unsigned long long, float>(h, nnz, sh, keys, static_cast<const float*>(M->values), static_cast<float*>(val),
+                                                  static_cast<float*>(tmp), counters, false, idx, row_mask);
     else
-      hipLaunchKernelGGL(k_tensor_compress<double>, dim3(g), dim3(256), 0, s, nnz, keys[cur], seq[cur], static_cast<const double*>(M->values), idx,
-                         static_cast<double*>(val));
+      cur = sort_pairs<unsigned long long, double>(h, nnz, sh, keys, static_cast<const double*>(M->values), static_cast<double*>(val),
+                                                   static_cast<double*>(tmp), counters, false, idx, row_mask);
   }
-  hipLaunchKernelGGL(k_tensor_rowptr, dim3(grid_for(M->cols + 1, 256, cap_grid)), dim3(256), 0, s, nnz, M->cols, keys[cur], colptr);
+  hipLaunchKernelGGL(k_key_ptr<unsigned long long>, dim3((unsigned)ceil_div(M->cols + 1, kPtrRows)), dim3(256), 0, s, nnz, M->cols, row_bits, keys[cur],
+                     colptr);
   HIP_TRY(h, hipGetLastError());
   int32_t* vec = nullptr;
   int64_t* ptr = nullptr;
