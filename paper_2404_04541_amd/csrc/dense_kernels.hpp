@@ -42,7 +42,7 @@ constexpr int kDirectMinDefault = 6144; // a block with at least this many entri
 constexpr int kRunTiles = 16;           // tiles handed to a workgroup at a time
 constexpr int kListSlab = 1 << 20;      // list entries, tile and run records that a symbolic workgroup draws at a time
 constexpr int kTileSlab = 2048;
-constexpr int kRunSlab = 256;
+constexpr int kRunSlab = 256;           // (run records: at most; see run_slab)
 constexpr int kDirectBit = 1 << 30;     // in TileRec::cnt
 constexpr int kSearchBit = 1 << 29;     // in TileRec::cnt: a searched tile (ranks by bisection of the column list)
 constexpr int kCountMask = kSearchBit - 1;
@@ -79,6 +79,22 @@ template <typename V>
 __device__ __forceinline__ void stream_store(V* p, V v) { __builtin_nontemporal_store(v, p); }
 template <typename V>
 __device__ __forceinline__ V stream_load(const V* p) { return __builtin_nontemporal_load(p); }
+
+// Run records that a symbolic workgroup draws at a time.  What a workgroup draws and does not use stays in the list as
+// an empty record that the numeric kernel steps over (two barriers, about 2 us), so the slab follows the rows a workgroup
+// gets: an eighth of them, 256 for the large products (where a draw per row cost 2.9 ms).  With 256 always, a product with
+// four dense rows per workgroup stepped over 252 empty records in every workgroup: 850 rows of 2600 products took
+// 753 us in the numeric kernel, and 52 us with slabs that follow the rows.
+__host__ __device__ __forceinline__ unsigned run_slab(int64_t rows, int64_t workgroups) {
+  const int64_t s = rows / (8 * workgroups);
+  return (unsigned)(s < 1 ? 1 : (s > kRunSlab ? kRunSlab : s));
+}
+// List entries that a symbolic workgroup draws at a time: together at most a quarter of the list, so that a short list is not
+// spent on slack.
+__host__ __device__ __forceinline__ unsigned long long list_slab_of(unsigned long long list_cap, int64_t workgroups) {
+  const unsigned long long s = (list_cap / (4ULL * (unsigned long long)workgroups)) & ~3ULL;
+  return s < (unsigned long long)kListSlab ? s : (unsigned long long)kListSlab;
+}
 
 struct TileRec { int b0, b1, cnt, out; };     // blocks [b0, b1), entries (| kDirectBit), offset inside the row of C
 // tiles [first, first + count) of one row; its A entries [a0, a0 + d); list (-1: the row has no list):
@@ -510,11 +526,13 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
   SPG_CLK(clk_begin(&rs->clk);)
   int row = next_dense_row(perm, ctl, &rs->s_row);
   int next_row = -1;   // (thread 0) the row after this one, fetched while this one is in the works
-  // (thread 0) what is left of the slabs drawn from the plan's lists, and what this workgroup used
-  unsigned long long sl_pos = 0, sl_left = 0;
-  // (slabs of the list: together at most a quarter of it, so that a short list is not spent on slack)
-  const unsigned long long list_slab = list_cap / (4ULL * gridDim.x) < (unsigned long long)kListSlab ? (list_cap / (4ULL * gridDim.x)) & ~3ULL : (unsigned long long)kListSlab;
-  unsigned st_pos = 0, st_left = 0, sr_pos = 0, sr_left = 0, used_tiles = 0, used_runs = 0;
+  // (thread 0) what is left of the slabs drawn from the plan's lists, and what this workgroup used.  The first slab of
+  // every workgroup is its own by its number (the cursors start behind these: k_set_caps); when all workgroups drew their
+  // first slab from the shared cursors at the same moment, the compare-and-swaps of 256 of them took 0.2 ms (1071 rows: 366 -> 73 us).
+  const unsigned long long list_slab = list_slab_of(list_cap, gridDim.x);
+  const unsigned rslab = run_slab(row_hi - row_lo, gridDim.x);
+  unsigned long long sl_pos = blockIdx.x * list_slab, sl_left = list_slab;
+  unsigned st_pos = blockIdx.x * (unsigned)kTileSlab, st_left = kTileSlab, sr_pos = blockIdx.x * rslab, sr_left = rslab, used_tiles = 0, used_runs = 0;
   while (row >= 0) {
     unsigned nx = 0;   // (thread 0) the draw for the row after this one: on its way while this row is in the works
     if (tid == 0) nx = atomicAdd(&ctl->work[0], 1u);
@@ -641,9 +659,10 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
           }
           if (room && (unsigned)nr > sr_left) {
             for (unsigned i = 0; i < sr_left; ++i) runs[sr_pos + i].count = 0;   // (slots left behind: empty records)
-            sr_pos = atomicAdd(&ctl->run_cursor, (unsigned)kRunSlab);
-            room = sr_pos + (unsigned)kRunSlab <= run_cap;
-            sr_left = room ? (unsigned)kRunSlab : 0u;
+            const unsigned grab = (unsigned)nr > rslab ? (unsigned)nr : rslab;
+            sr_pos = atomicAdd(&ctl->run_cursor, grab);
+            room = sr_pos + grab <= run_cap;
+            sr_left = room ? grab : 0u;
           }
           if (room) {
             tb = st_pos; st_pos += (unsigned)nt; st_left -= (unsigned)nt;

@@ -257,10 +257,11 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
   if (ip_d / h->direct_min < direct) direct = ip_d / h->direct_min;
   const double entries = ip_d < rows_d * n ? ip_d : rows_d * n;
   const double weight = rows_d * blocks * kRankBlkBytes + (double)kRankEntryBytes * entries;
-  // (+ a slab per workgroup of the symbolic kernel: what a workgroup has drawn and not used)
+  // (+ a slab per workgroup of the symbolic kernel: what a workgroup has drawn and not used; a row whose runs do not fit
+  // what is left of a run slab leaves fewer records behind than it takes, hence twice the runs)
   const double wgs = (double)grid_for((int64_t)rows_d, 1, h->num_cus) + 1.0;
   const double tiles = 2.0 * direct + 2.0 * weight / kTileBudget + 4.0 * rows_d * spans + 16.0 + wgs * kTileSlab;
-  const double runs = (tiles - wgs * kTileSlab) / kRunTiles + rows_d * spans + 16.0 + wgs * kRunSlab;
+  const double runs = 2.0 * ((tiles - wgs * kTileSlab) / kRunTiles + rows_d * spans + 16.0) + wgs * kRunSlab;
   if (tiles > 4.0e9) return fail(h, SPGEMM_UNSUPPORTED, "tile list of the dense workspace would exceed 2^32 records");
   *tile_cap = (unsigned)tiles;
   *run_cap = (unsigned)runs;
@@ -299,8 +300,14 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
   return SPGEMM_OK;
 }
 
-__global__ void k_set_caps(Control* ctl, unsigned tile_cap, unsigned run_cap, unsigned long long list_cap) {
-  if (threadIdx.x == 0) { ctl->tile_cap = tile_cap; ctl->run_cap = run_cap; ctl->list_cap = list_cap; }
+// Capacities of the dense workspace's lists, and their cursors behind the first slab of every workgroup of k_sym_dense.
+__global__ void k_set_caps(Control* ctl, unsigned tile_cap, unsigned run_cap, unsigned long long list_cap, int64_t rows, unsigned workgroups) {
+  if (threadIdx.x == 0) {
+    ctl->tile_cap = tile_cap; ctl->run_cap = run_cap; ctl->list_cap = list_cap;
+    ctl->tile_cursor = workgroups * kTileSlab;
+    ctl->run_cursor = workgroups * run_slab(rows, workgroups);
+    ctl->list_cursor = workgroups * list_slab_of(list_cap, workgroups);
+  }
 }
 
 template <typename T>
@@ -323,7 +330,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   int rc = alloc_dense_lists(h, p, B, host, &tile_cap, &run_cap);
   if (rc) return rc;
   if (rows_dense > 0) {
-    hipLaunchKernelGGL(k_set_caps, dim3(1), dim3(64), 0, s, p->ctl, tile_cap, run_cap, p->col_list_cap);
+    hipLaunchKernelGGL(k_set_caps, dim3(1), dim3(64), 0, s, p->ctl, tile_cap, run_cap, p->col_list_cap, rows_dense, grid_for(rows_dense, 1, h->num_cus));
     if (p->blk_ptr) {
       Timer t(h, SPGEMM_K_BLOCK_PTR);
       const int64_t items = B->rows * (int64_t)p->blk_ptr_cols;

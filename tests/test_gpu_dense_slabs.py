@@ -1,0 +1,27 @@
+"""The plan's list, tile and run slabs of the dense workspace: fewer rows than workgroups, about as many, several slabs per
+workgroup, and rows whose runs do not fit a slab."""
+import numpy as np
+import pytest
+
+from paper_2404_04541_amd import workloads as W
+from helpers import gpu_product, assert_matches_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows,mean,cols,b_mean", [
+    (1, 60, 50_000, 60),           # one workgroup
+    (255, 60, 50_000, 60),
+    (257, 60, 50_000, 60),         # two rows in one workgroup, slab of one record
+    (5000, 50, 9_001, 50),         # two records a slab
+    (3, 1500, 3_000_000, 700),     # three spans, several runs in each: more than a slab of one record
+])
+def test_dense_rows_and_slabs(rows, mean, cols, b_mean):
+    # (lengths near the mean: every row is long enough for the dense workspace)
+    k = 2000
+    A = W.uniform_rows(rows, k, mean, 91, 1, np.float64)
+    B = W.uniform_rows(k, cols, b_mean, 91, 3, np.float64)
+    got = gpu_product(A, B)
+    assert_matches_oracle(A, B, got, what=f"{rows} dense rows")
+    st = got[3]
+    assert st["num_bin_rows"][5] + st["num_bin_rows"][6] == rows and st["dense_runs"] >= rows
