@@ -104,7 +104,7 @@ typedef struct {
   int64_t dense_direct_tiles; /* of those, tiles accumulated by column (one pass) */
   int64_t dense_runs;         /* work items (runs of tiles of one row) */
   int64_t dense_search_tiles; /* of the tiles, whole short rows whose ranks come from bisecting the column list */
-  int64_t plan_bytes;         /* device memory the plan holds (per-row arrays, tile lists, block table, structure list) */
+  int64_t plan_bytes;         /* device memory the plan holds (per-row arrays, tile lists, block table, structure list, order of short rows) */
   int64_t plan_list_bytes;    /* of those, what the structure list (columns or flag words of the dense rows) was given */
   int64_t plan_list_used;     /* ... and what the symbolic phase filled of it */
 } spgemm_stats;
@@ -126,8 +126,9 @@ enum {
   SPGEMM_OPT_DIRECT_MIN = 3,
   /* 1 (default): the plan keeps the column indices of the dense workspace's ranked tiles
    * (up to a third of the free device memory), which saves the numeric phase one pass over
-   * those tiles' products; rows that do not fit fall back to the two-pass route.  0: never.
-   * A value of 4096 or more limits the list to that many bytes. */
+   * those tiles' products; rows that do not fit fall back to the two-pass route.  It also keeps the
+   * order of the products of short rows (up to a quarter of the free memory), which saves the numeric
+   * phase their sort or hash.  0: neither.  A value of 4096 or more limits each of the two to that many bytes. */
   SPGEMM_OPT_COLUMN_LIST = 4,
   /* 1 (default): for an ascending B the plan holds a table of per-row offsets at every 8192nd
    * column (when it fits 1 GiB), which turns the search for a tile's piece of a B row into two

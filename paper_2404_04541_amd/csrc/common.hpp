@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace spg {
 
@@ -36,6 +37,7 @@ struct Control {
   unsigned tiles_used, runs_used;     // records in use (the cursors also count what is left of the workgroups' slabs)
   unsigned direct_tiles;              // how many of the tiles are direct
   unsigned search_tiles;              // how many are searched tiles
+  unsigned recorded;                  // rows with a record for the numeric phase
   unsigned long long list_cursor, list_cap;   // entries used / available in the plan's column list
   int error;                      // nonzero: a device-side input check failed
   int b_sorted;                   // 1 when every B row is strictly ascending
@@ -81,6 +83,20 @@ struct __attribute__((packed, aligned(sizeof(E)))) Run { E v[N]; };
 
 template <typename E, int N>
 __device__ __forceinline__ Run<E, N> load_run(const E* p) { return *reinterpret_cast<const Run<E, N>*>(p); }
+
+// Where the B row of an entry of A begins and how long it is, in one word (the row count leaves these for the kernels of short
+// rows when B's row pointer does not fit the L2 cache; a row of 2^24 - 1 or more entries is in no such row).
+constexpr int kDescLenBits = 24;
+__device__ __forceinline__ unsigned long long make_desc(int64_t start, int64_t len) {
+  const unsigned long long top = (1ULL << kDescLenBits) - 1;
+  return ((unsigned long long)start << kDescLenBits) | ((unsigned long long)len < top ? (unsigned long long)len : top);
+}
+__device__ __forceinline__ Run<int64_t, 2> desc_bounds(unsigned long long v) {
+  Run<int64_t, 2> r;
+  r.v[0] = (int64_t)(v >> kDescLenBits);
+  r.v[1] = r.v[0] + (int64_t)(v & ((1ULL << kDescLenBits) - 1));
+  return r;
+}
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
@@ -198,6 +214,64 @@ __device__ __forceinline__ int classify_numeric(long long ip, int cnt, int force
   if (cnt <= kNumHashSmall) return 2;
   if (cnt <= kNumHashLarge) return 3;
   return staged_ok ? 4 : dense;
+}
+
+// Value of the lane whose number differs in bit D (a power of two): DPP inside a row of 16 lanes, the LDS crossbar beyond.
+template <int D>
+__device__ __forceinline__ unsigned lane_xor(unsigned v) {
+  static_assert(D == 1 || D == 2 || D == 4 || D == 8 || D == 16 || D == 32, "one bit of the lane number");
+  if constexpr (D == 1) return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true);        // quad_perm [1,0,3,2]
+  else if constexpr (D == 2) return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true);   // quad_perm [2,3,0,1]
+  else if constexpr (D == 4) {                                                                                 // row_half_mirror (xor 7), quad_perm [3,2,1,0] (xor 3)
+    const int m = __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true);
+    return (unsigned)__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xf, 0xf, true);
+  } else if constexpr (D == 8) return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, true); // row_ror:8
+  else if constexpr (D == 16) return (unsigned)__builtin_amdgcn_ds_swizzle((int)v, 0x401F);                    // bit mode: and 31, xor 16
+  else return (unsigned)__shfl_xor((int)v, 32, kWave);
+}
+
+// Bitonic sort in registers, ascending: lane gl of a group of N / KPL lanes (16 or 64, aligned) holds elements gl * KPL ..
+// gl * KPL + KPL - 1.  An exchange is a lane move and one median with 0 or ~0 (the minimum or the maximum of the two); the
+// same network through LDS costs two reads and two writes per pair and a round trip per stage.
+template <int N, int KPL, int K, int J>
+__device__ __forceinline__ void lane_sort_stage(unsigned (&key)[KPL], int gl) {
+  if constexpr (J < KPL) {
+#pragma unroll
+    for (int q = 0; q < KPL; ++q) {
+      if ((q & J) == 0) {
+        const unsigned lo = key[q] < key[q | J] ? key[q] : key[q | J], hi = key[q] < key[q | J] ? key[q | J] : key[q];
+        bool up = true;
+        if constexpr (K < KPL) up = (q & K) == 0;
+        else if constexpr (K < N) up = (gl & (K / KPL)) == 0;
+        key[q] = up ? lo : hi;
+        key[q | J] = up ? hi : lo;
+      }
+    }
+  } else {
+    constexpr int D = J / KPL;
+    bool lower = (gl & D) == 0;
+    if constexpr (K < N) lower = lower == ((gl & (K / KPL)) == 0);
+    const unsigned limit = lower ? 0u : ~0u;
+#pragma unroll
+    for (int q = 0; q < KPL; ++q) {
+      const unsigned other = lane_xor<D>(key[q]);
+      const unsigned lo = key[q] < other ? key[q] : other, hi = key[q] < other ? other : key[q];
+      const unsigned m = hi < limit ? hi : limit;
+      key[q] = lo > m ? lo : m;   // (one v_med3_u32)
+    }
+  }
+  if constexpr (J > 1) lane_sort_stage<N, KPL, K, J / 2>(key, gl);
+}
+
+template <int N, int KPL, int K = 2>
+__device__ __forceinline__ void lane_sort(unsigned (&key)[KPL], int gl) {
+  lane_sort_stage<N, KPL, K, K / 2>(key, gl);
+  if constexpr (K < N) lane_sort<N, KPL, K * 2>(key, gl);
+}
+
+// Lanes of `mask` below this one.
+__device__ __forceinline__ int lanes_below(unsigned long long mask) {
+  return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
 }
 
 // Bitonic sort of the first n keys (a power of two, at most NMAX) held in LDS by G cooperating

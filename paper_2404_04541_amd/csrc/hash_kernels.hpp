@@ -8,6 +8,7 @@
 //           and that prefix is copied to the row of C.
 #pragma once
 #include "common.hpp"
+#include "record_kernels.hpp"
 
 namespace spg {
 
@@ -60,7 +61,8 @@ __global__ __launch_bounds__(256) void k_hash(const int* __restrict__ perm, cons
                                                const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
                                                const int32_t* __restrict__ b_col, const T* __restrict__ b_val,
                                                int* __restrict__ cnt, const int64_t* __restrict__ c_rp,
-                                               int32_t* __restrict__ c_col, T* __restrict__ c_val, int64_t n_cols) {
+                                               int32_t* __restrict__ c_col, T* __restrict__ c_val, int64_t n_cols,
+                                               const int* __restrict__ record_of) {
   constexpr int H = 1 << LOGH;
   const bool packable = n_cols <= (int64_t(1) << (31 - LOGH));   // column << LOGH stays below the pad key
   constexpr int kGroups = 256 / GROUP;
@@ -91,6 +93,9 @@ __global__ __launch_bounds__(256) void k_hash(const int* __restrict__ perm, cons
     const unsigned slot = r * ngroups + blockIdx.x * kGroups + g;
     const bool live = slot < nrows;
     const int row = live ? perm[first + slot] : 0;
+    // (wave-uniform) rows whose ranks the symbolic pass has recorded are done elsewhere
+    if constexpr (GROUP == kWave && NUMERIC)
+      if (record_of && live && ip_row[row] <= kSymHashSmall && record_of[row] >= 0) continue;
     for (int t = gl; t < H; t += GROUP) {
       keys[t] = kEmptyKey;
       if (NUMERIC) vals[t] = 0.0;

@@ -49,13 +49,14 @@ __global__ __launch_bounds__(256) void k_validate_b(int64_t rows, int64_t cols, 
 // One workgroup of 1024 threads per 256 consecutive rows of A (a chunk of hub rows holds a large
 // share of all entries, so the chunk gets the widest workgroup): the chunk's A entries are read
 // coalesced, each entry adds the length of its B row to its row's counter in LDS.
+// desc (optional): start and length of every A entry's B row, for the kernels of short rows.
 // Writes ip (saturated to int32), the symbolic bin, zero counts for rows without products.
 constexpr int kCountThreads = 1024;
 __global__ __launch_bounds__(kCountThreads) void k_count_rows(int64_t m, int64_t nnz_a, int64_t b_rows,
                                                     const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                     const int64_t* __restrict__ b_rp, int* __restrict__ ip_out,
                                                     unsigned char* __restrict__ bin_out, int* __restrict__ cnt_out,
-                                                    Control* ctl, int force, int row_block) {
+                                                    Control* ctl, int force, int row_block, unsigned long long* __restrict__ desc) {
   __shared__ long long rp[257];
   __shared__ unsigned long long ipl[256];
   __shared__ unsigned hist[kNumBins];
@@ -97,6 +98,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int64_t m, int64_t
     for (long long p0 = lo + tid; p0 < hi; p0 += kCountThreads * 4) {
       int k[4];
       long long len[4];
+      int64_t start[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const long long p = p0 + u * kCountThreads;
@@ -106,9 +108,11 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int64_t m, int64_t
       for (int u = 0; u < 4; ++u) {
         const long long p = p0 + u * kCountThreads;
         len[u] = 0;
+        start[u] = 0;
         if (p < hi) {
           if (k[u] < 0 || k[u] >= b_rows) { badcol = true; continue; }
           const Run<int64_t, 2> bounds = load_run<int64_t, 2>(b_rp + k[u]);   // (both ends of the row in one load)
+          start[u] = bounds.v[0];
           len[u] = bounds.v[1] - bounds.v[0];
           if (len[u] < 0) { badcol = true; len[u] = 0; }
         }
@@ -116,6 +120,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int64_t m, int64_t
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const long long p = p0 + u * kCountThreads;
+        if (desc && p < hi) desc[p] = make_desc(start[u], len[u]);
         if (len[u] > 0) {
           // row of entry p: last t with rp[t] <= p
           int a = 0, b = nr;

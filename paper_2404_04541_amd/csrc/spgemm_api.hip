@@ -14,6 +14,7 @@
 #include "common.hpp"
 #include "setup_kernels.hpp"
 #include "esc_kernels.hpp"
+#include "record_kernels.hpp"
 #include "hash_kernels.hpp"
 #include "dense_kernels.hpp"
 #include "staged_kernels.hpp"
@@ -56,23 +57,30 @@ struct spgemm_plan_s {
   int64_t m = 0, k = 0, n = 0, nnz_a = 0, nnz_b = 0;
   int dtype = 0;
   void* scratch = nullptr;
-  size_t scratch_bytes = 0, scratch2_bytes = 0, scratch3_bytes = 0;
+  size_t scratch_bytes = 0, scratch2_bytes = 0;
   int* ip = nullptr;
   int* cnt = nullptr;
   int* perm_sym = nullptr;
   int* perm_num = nullptr;
   unsigned char* bin = nullptr;
   long long* partial = nullptr;
+  unsigned long long* desc = nullptr;   // per entry of A: its B row (optional)
   void* scratch2 = nullptr;  // sized after the row classes are known: block offsets of B, tile and run lists
   int* blk_ptr = nullptr;    // rows(B) x blk_ptr_cols offsets, null when not needed or too large
   int blk_ptr_cols = 0;      // column blocks + 1
   TileRec* tiles = nullptr;
   RunRec* runs = nullptr;
-  void* scratch3 = nullptr;  // column list of the ranked tiles (optional: sized from what the device has free)
+  void* scratch3 = nullptr;  // optional, sized from what the device has free: what short rows leave for the numeric phase, then the column list of the ranked tiles
   int32_t* col_list = nullptr;
   unsigned long long col_list_cap = 0;
+  size_t list_bytes = 0, short_bytes = 0;
+  unsigned* esc_words[2] = {nullptr, nullptr};   // sorted words of the rows of symbolic bins 0 and 1
+  unsigned* records = nullptr;   // rows of symbolic bin 2
+  int* record_of = nullptr;      // per row of A: its record, -1 = none (written for the rows of symbolic bin 2)
+  unsigned record_rows = 0;      // rows of the bin that have room for a record
   Control* ctl = nullptr;
   int64_t scan_blocks = 0;
+  int64_t recorded = 0;          // rows that have a record
   bool symbolic_done = false;
   bool numeric_pending = false;   // timed numeric launches not yet folded into stats
   bool numeric_in_flight = false; // numeric kernels were enqueued and the stream has not been waited for since
@@ -212,7 +220,20 @@ inline unsigned grid_for(int64_t items, int64_t per_block, int64_t cap) {
   return (unsigned)g;
 }
 
+// Sorted-list keys can carry their list position when every column, shifted by the list's log2 capacity, stays below the padding key.
+constexpr int64_t kEscPackCols0 = int64_t(1) << 25, kEscPackCols1 = int64_t(1) << 23;
+constexpr size_t kAskFreeAbove = (size_t)64 << 20;   // optional memory below this is taken without asking the device what it has free
+
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
+
+// Whether the row count leaves start and length of every A entry's B row: 8 bytes an entry, written once and read twice, in place
+// of a gather of B's row pointer in each of the two kernels of short rows.  It pays where those gathers miss the L2 cache (4 MB
+// per XCD) and most rows are short.  4.2 M rows of 8 entries times 4.2 M rows of 4, both kernels and the count:
+// 3.50 ms with the gathers, 2.51 ms without; with a cached B the words would cost what they save.
+bool wants_desc(const spgemm_csr* A, const spgemm_csr* B) {
+  if (A->rows == 0 || B->rows * 8 <= ((int64_t)4 << 20) || B->nnz >= (int64_t(1) << 39) || A->nnz >= (int64_t(1) << 39)) return false;
+  return (double)A->nnz / (double)A->rows * ((double)B->nnz / (double)B->rows) <= (double)kEscLargeCap;
+}
 
 // Symbolic phase, first part: count, check, bin.  Ends with the control block on the host
 // (one synchronisation): the second part sizes its lists and launches from the bin populations.
@@ -226,7 +247,7 @@ int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const sp
                        B->rows, B->cols, B->nnz, B->rowptr, B->colidx, p->ctl);
     if (m > 0)
       hipLaunchKernelGGL(k_count_rows, dim3(grid_for(m, 256, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, s, m, A->nnz, B->rows, A->rowptr, A->colidx,
-                         B->rowptr, p->ip, p->bin, p->cnt, p->ctl, h->force, h->row_block);
+                         B->rowptr, p->ip, p->bin, p->cnt, p->ctl, h->force, h->row_block, p->desc);
   }
   {
     Timer t(h, SPGEMM_K_BIN);
@@ -243,8 +264,8 @@ int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const sp
 // Sizes and allocates what the dense kernels need beyond the per-row arrays: the tile and run
 // lists (from an upper bound of the number of tiles) and the table of block offsets of B.
 int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, const Control& host, unsigned* tile_cap,
-                      unsigned* run_cap) {
-  *tile_cap = 0; *run_cap = 0;
+                      unsigned* run_cap, double* list_want) {
+  *tile_cap = 0; *run_cap = 0; *list_want = 0;
   double rows_d = 0, ip_d = 0;
   for (int b = 4; b <= 6; ++b) { rows_d += host.hist[0][b]; ip_d += (double)host.bin_ip[0][b]; }
   if (rows_d == 0) return SPGEMM_OK;
@@ -280,24 +301,66 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
   p->runs = reinterpret_cast<RunRec*>(base + o_runs);
   p->blk_ptr = with_bp ? reinterpret_cast<int*>(base + o_bp) : nullptr;
   // Column list: the dense symbolic kernel leaves the columns of its ranked tiles there, which saves
-  // the numeric kernel one pass over those tiles' products.  At most `entries` are needed; take no
-  // more than a third of what the device has free, and do without if the allocation fails.
-  size_t free_b = 0, total_b = 0;
-  if (h->col_list && hipMemGetInfo(&free_b, &total_b) == hipSuccess) {
-    double want = (entries + 4.0 * rows_d * spans) * 4.0;   // (every row's share is rounded up to 16 bytes)
-    if (want > (double)free_b / 3.0) want = (double)free_b / 3.0;
-    if (h->col_list > 1 && want > (double)h->col_list) want = (double)h->col_list;
-    const size_t bytes = ((size_t)want) & ~(size_t)255;
-    if (bytes >= 4096) {
-      p->scratch3 = dev_alloc(h, bytes);
-      if (p->scratch3) {
-        p->scratch3_bytes = bytes;
-        p->col_list = static_cast<int32_t*>(p->scratch3);
-        p->col_list_cap = bytes / 4;
-      }
-    }
-  }
+  // the numeric kernel one pass over those tiles' products.  (Every row's share is rounded up to 16 bytes.)
+  *list_want = (entries + 4.0 * rows_d * spans) * 4.0;
   return SPGEMM_OK;
+}
+
+// The optional part of a plan, one allocation that the product does without when it fails: the column list of the dense rows
+// (at most a third of the free memory), and what the symbolic kernels of short rows leave for the numeric ones
+// (esc_kernels.hpp, record_kernels.hpp; at most a quarter): sorted words for all rows of a bin or for none, records for as
+// many rows as there is room for.
+void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, const Control& host, double list_want) {
+  if (!h->col_list) return;
+  const int64_t max_cols[2] = {kEscPackCols0, kEscPackCols1};
+  const size_t word_bytes[2] = {kEscSmallCap * 4, kEscLargeCap * 4};
+  size_t words[2], want = 0;
+  for (int b = 0; b < 2; ++b) {
+    words[b] = B->cols <= max_cols[b] ? align_up(host.hist[0][b] * word_bytes[b]) : 0;
+    want += words[b];
+  }
+  const size_t rec_bytes = (size_t)kRecWords * 4, map = align_up((size_t)p->m * 4);
+  const size_t rec_rows = B->cols <= (int64_t(1) << kRecColBits) ? host.hist[0][2] : 0;
+  if (rec_rows) want += map + rec_rows * rec_bytes;
+  const size_t asked = h->col_list > 1 ? (size_t)h->col_list : ~(size_t)0;
+  size_t limit = asked;
+  if ((double)want + list_want > (double)kAskFreeAbove) {
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return;
+    if (free_b / 4 < limit) limit = free_b / 4;
+    if (list_want > (double)free_b / 3.0) list_want = (double)free_b / 3.0;
+  }
+  if (list_want > (double)asked) list_want = (double)asked;
+  size_t list_bytes = ((size_t)list_want) & ~(size_t)255;
+  if (list_bytes < 4096) list_bytes = 0;
+  size_t off = 0, o_words[2] = {0, 0};
+  for (int b = 0; b < 2; ++b) {
+    if (words[b] && off + words[b] <= limit) { o_words[b] = off; off += words[b]; }
+    else words[b] = 0;
+  }
+  size_t rows = 0;
+  const size_t o_map = off;
+  if (rec_rows && off + map + rec_bytes <= limit) {
+    rows = (limit - off - map) / rec_bytes;
+    if (rows > rec_rows) rows = rec_rows;
+    off = align_up(off + map + rows * rec_bytes);
+  }
+  if (off + list_bytes == 0) return;
+  unsigned char* base = static_cast<unsigned char*>(dev_alloc(h, off + list_bytes));
+  if (!base) return;
+  p->scratch3 = base;
+  p->short_bytes = off;
+  p->list_bytes = list_bytes;
+  for (int b = 0; b < 2; ++b) if (words[b]) p->esc_words[b] = reinterpret_cast<unsigned*>(base + o_words[b]);
+  if (rows) {
+    p->record_of = reinterpret_cast<int*>(base + o_map);
+    p->records = reinterpret_cast<unsigned*>(base + o_map + map);
+    p->record_rows = (unsigned)rows;
+  }
+  if (list_bytes) {
+    p->col_list = reinterpret_cast<int32_t*>(base + off);
+    p->col_list_cap = list_bytes / 4;
+  }
 }
 
 // Capacities of the dense workspace's lists, and their cursors behind the first slab of every workgroup of k_sym_dense.
@@ -316,9 +379,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   hipStream_t s = h->stream;
   const int64_t m = p->m;
   const int64_t cap_small = (int64_t)h->num_cus * 32;
-  // sorted-list keys can carry their list position when every column, shifted by the list's log2 capacity, stays below the padding key
-  const int pack32 = B->cols <= (int64_t(1) << 25) ? 1 : 0, pack128 = B->cols <= (int64_t(1) << 23) ? 1 : 0;
-  const size_t lds_hash_small = hash_lds_bytes<64, 10, false>();
+  const int pack32 = B->cols <= kEscPackCols0 ? 1 : 0, pack128 = B->cols <= kEscPackCols1 ? 1 : 0;
   const size_t lds_hash_large = hash_lds_bytes<256, 12, false>();
   const unsigned* hist = host.hist[0];
   const int64_t rows_dense = (int64_t)hist[4] + hist[5] + hist[6];
@@ -327,8 +388,10 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   // become searched tiles of the dense kernel, which costs them one global round trip less)
   const int staged = (h->force == 4 && ceil_div(B->cols, kStWinCols) <= kStMaxWindows) ? staged_cap<T>() : 0;
   unsigned tile_cap = 0, run_cap = 0;
-  int rc = alloc_dense_lists(h, p, B, host, &tile_cap, &run_cap);
+  double list_want = 0;
+  int rc = alloc_dense_lists(h, p, B, host, &tile_cap, &run_cap, &list_want);
   if (rc) return rc;
+  alloc_optional(h, p, B, host, list_want);
   if (rows_dense > 0) {
     hipLaunchKernelGGL(k_set_caps, dim3(1), dim3(64), 0, s, p->ctl, tile_cap, run_cap, p->col_list_cap, rows_dense, grid_for(rows_dense, 1, h->num_cus));
     if (p->blk_ptr) {
@@ -342,25 +405,22 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     {
       Timer t(h, SPGEMM_K_SYM_ESC);
       if (hist[0])
-        hipLaunchKernelGGL((k_esc<16, 32, T, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0, 0,
-                           A->rowptr, A->colidx, (const T*)nullptr, B->rowptr, B->colidx, (const T*)nullptr, p->cnt,
-                           (const int64_t*)nullptr, (int32_t*)nullptr, (T*)nullptr, pack32, B->nnz);
+        hipLaunchKernelGGL((p->desc ? k_esc_sym<16, 32, true> : k_esc_sym<16, 32, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0, A->rowptr, A->colidx,
+                           B->rowptr, p->desc, B->colidx, B->nnz, pack32, p->cnt, p->esc_words[0]);
       if (hist[1])
-        hipLaunchKernelGGL((k_esc<64, 128, T, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0, 1,
-                           A->rowptr, A->colidx, (const T*)nullptr, B->rowptr, B->colidx, (const T*)nullptr, p->cnt,
-                           (const int64_t*)nullptr, (int32_t*)nullptr, (T*)nullptr, pack128, B->nnz);
+        hipLaunchKernelGGL((p->desc ? k_esc_sym<64, 128, true> : k_esc_sym<64, 128, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx,
+                           B->rowptr, p->desc, B->colidx, B->nnz, pack128, p->cnt, p->esc_words[1]);
     }
     {
       Timer t(h, SPGEMM_K_SYM_HASH);
       if (hist[2])
-        hipLaunchKernelGGL((k_hash<64, 10, T, false>), dim3(grid_for(hist[2], 4, cap_small)), dim3(256), lds_hash_small, s,
-                           p->perm_sym, p->ctl, 0, 2, p->ip, A->rowptr, A->colidx, (const T*)nullptr, B->rowptr, B->colidx,
-                           (const T*)nullptr, p->cnt, (const int64_t*)nullptr, (int32_t*)nullptr, (T*)nullptr, B->cols);
+        hipLaunchKernelGGL(k_sym_wave, dim3(grid_for(hist[2], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 2, A->rowptr, A->colidx,
+                           B->rowptr, B->colidx, B->nnz, p->cnt, p->records, p->record_rows, p->record_of);
       if (hist[3])
         hipLaunchKernelGGL((k_hash<256, 12, T, false>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
                            lds_hash_large, s, p->perm_sym, p->ctl, 0, 3, p->ip, A->rowptr, A->colidx,
                            (const T*)nullptr, B->rowptr, B->colidx, (const T*)nullptr, p->cnt, (const int64_t*)nullptr,
-                           (int32_t*)nullptr, (T*)nullptr, B->cols);
+                           (int32_t*)nullptr, (T*)nullptr, B->cols, (const int*)nullptr);
     }
     if (rows_dense > 0) {
       Timer t(h, SPGEMM_K_SYM_DENSE);
@@ -400,8 +460,7 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   const int64_t m = p->m;
   if (m == 0) return SPGEMM_OK;
   const int64_t cap_small = (int64_t)h->num_cus * 32;
-  // sorted-list keys can carry their list position when every column, shifted by the list's log2 capacity, stays below the padding key
-  const int pack32 = B->cols <= (int64_t(1) << 25) ? 1 : 0, pack128 = B->cols <= (int64_t(1) << 23) ? 1 : 0;
+  const int pack32 = B->cols <= kEscPackCols0 ? 1 : 0, pack128 = B->cols <= kEscPackCols1 ? 1 : 0;
   const T* a_val = static_cast<const T*>(A->values);
   const T* b_val = static_cast<const T*>(B->values);
   T* c_val = static_cast<T*>(c_val_v);
@@ -411,23 +470,33 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   hipLaunchKernelGGL(k_reset_numeric_work, dim3(1), dim3(64), 0, s, p->ctl);
   {
     Timer t(h, SPGEMM_K_NUM_ESC);
-    if (hist[0])
-      hipLaunchKernelGGL((k_esc<16, 32, T, true>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 0,
-                         A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, pack32, B->nnz);
-    if (hist[1])
-      hipLaunchKernelGGL((k_esc<64, 128, T, true>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 1,
-                         A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, pack128, B->nnz);
+    // (the words were sorted for the rows of the symbolic bin: they serve when the numeric one holds the same rows)
+    if (hist[0] && p->esc_words[0] && hist[0] == p->stats.sym_bin_rows[0])
+      hipLaunchKernelGGL((p->desc ? k_esc_num<16, 32, T, true> : k_esc_num<16, 32, T, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0, A->rowptr, A->colidx,
+                         a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[0], c_rp, c_col, c_val);
+    else if (hist[0])
+      hipLaunchKernelGGL((k_esc<16, 32, T>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 0,
+                         A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, B->nnz);
+    if (hist[1] && p->esc_words[1] && hist[1] == p->stats.sym_bin_rows[1])
+      hipLaunchKernelGGL((p->desc ? k_esc_num<64, 128, T, true> : k_esc_num<64, 128, T, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx,
+                         a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[1], c_rp, c_col, c_val);
+    else if (hist[1])
+      hipLaunchKernelGGL((k_esc<64, 128, T>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 1,
+                         A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack128, B->nnz);
   }
   {
     Timer t(h, SPGEMM_K_NUM_HASH);
-    if (hist[2])
+    if (p->recorded)   // (rows of the bin with a record, then the ones without)
+      hipLaunchKernelGGL(k_num_recorded<T>, dim3(grid_for(hist[2], 4, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 2, p->ip, p->records, p->record_of,
+                         A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val);
+    if (hist[2] > p->recorded)
       hipLaunchKernelGGL((k_hash<64, 8, T, true>), dim3(grid_for(hist[2], 4, cap_small)), dim3(256), lds_hash_small, s,
                          p->perm_num, p->ctl, 1, 2, p->ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, (int*)nullptr,
-                         c_rp, c_col, c_val, B->cols);
+                         c_rp, c_col, c_val, B->cols, p->recorded ? p->record_of : nullptr);
     if (hist[3])
       hipLaunchKernelGGL((k_hash<256, 11, T, true>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
                          lds_hash_large, s, p->perm_num, p->ctl, 1, 3, p->ip, A->rowptr, A->colidx, a_val, B->rowptr,
-                         B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, B->cols);
+                         B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, B->cols, (const int*)nullptr);
   }
   if (hist[4]) {
     Timer t(h, SPGEMM_K_NUM_STAGED);
@@ -558,7 +627,10 @@ int spgemm_symbolic(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, i
   const size_t o_pn = off; off = align_up(off + (size_t)m * 4);
   const size_t o_bin = off; off = align_up(off + (size_t)m);
   const size_t o_part = off; off = align_up(off + (size_t)(p->scan_blocks + 1) * 8);
+  const size_t plain = off, o_desc = off;
+  if (wants_desc(A, B)) off = align_up(off + (size_t)A->nnz * 8);
   p->scratch = dev_alloc(h, off);
+  if (!p->scratch && off > plain) { off = plain; p->scratch = dev_alloc(h, off); }
   p->scratch_bytes = off;
   if (!p->scratch) {
     delete p;
@@ -572,6 +644,7 @@ int spgemm_symbolic(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, i
   p->perm_num = reinterpret_cast<int*>(base + o_pn);
   p->bin = base + o_bin;
   p->partial = reinterpret_cast<long long*>(base + o_part);
+  if (off > plain) p->desc = reinterpret_cast<unsigned long long*>(base + o_desc);
 
   Control host{};
   rc = run_setup(h, p, A, B, &host);
@@ -599,6 +672,7 @@ int spgemm_symbolic(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, i
     spgemm_plan_destroy(p);
     return fail(h, SPGEMM_INVALID_INPUT, "device-side input check failed (column out of range or rowptr not monotone)");
   }
+  p->recorded = host.recorded;
   p->stats.ip_total = (int64_t)host.ip_total;
   p->stats.nnz_c = host.nnz_c;
   for (int b = 0; b < kNumBins; ++b) {
@@ -612,8 +686,8 @@ int spgemm_symbolic(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, i
   p->stats.dense_direct_tiles = host.direct_tiles;
   p->stats.dense_runs = host.runs_used;
   p->stats.dense_search_tiles = host.search_tiles;
-  p->stats.plan_bytes = (int64_t)(p->scratch_bytes + p->scratch2_bytes + p->scratch3_bytes);
-  p->stats.plan_list_bytes = (int64_t)p->scratch3_bytes;
+  p->stats.plan_bytes = (int64_t)(p->scratch_bytes + p->scratch2_bytes + p->short_bytes + p->list_bytes);
+  p->stats.plan_list_bytes = (int64_t)p->list_bytes;
   p->stats.plan_list_used = (int64_t)((host.list_cursor < host.list_cap ? host.list_cursor : host.list_cap) * 4ULL);
   p->symbolic_done = true;
   *nnz_c = host.nnz_c;
@@ -683,7 +757,7 @@ int spgemm(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, spgemm_csr
     col = static_cast<int32_t*>(dev_alloc(h, (size_t)nnz * 4));
     val = dev_alloc(h, (size_t)nnz * vsz);
     if ((!col || !val) && plan->scratch3 && h->col_list) {
-      // the plan's optional structure list may be what stands in the way: plan again without it
+      // the plan's optional lists may be what stands in the way: plan again without it
       dev_free(h, col); dev_free(h, val);
       spgemm_plan_destroy(plan);
       plan = nullptr;
@@ -1015,7 +1089,7 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
     hipLaunchKernelGGL(k_init_control, dim3(1), dim3(64), 0, h->stream, ctl);
     if (m > 0)
       hipLaunchKernelGGL(k_count_rows, dim3(grid_for(m, 256, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, h->stream, m, A->nnz, B->rows, A->rowptr, A->colidx,
-                         B->rowptr, reinterpret_cast<int*>(tmp + o_ip), tmp + o_bin, reinterpret_cast<int*>(tmp + o_cnt), ctl, 0, 0);
+                         B->rowptr, reinterpret_cast<int*>(tmp + o_ip), tmp + o_bin, reinterpret_cast<int*>(tmp + o_cnt), ctl, 0, 0, (unsigned long long*)nullptr);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && m > 0) e = hipMemcpyAsync(ip_host.data(), tmp + o_ip, (size_t)m * 4, hipMemcpyDeviceToHost, h->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(&host, ctl, sizeof(Control), hipMemcpyDeviceToHost, h->stream);

@@ -1,0 +1,104 @@
+"""What the symbolic pass leaves of short rows for the numeric one: 64 and 65 entries in a row of A, 192 and 193
+columns, quads that end at the end of B's arrays, lists too small for every row, too many columns for a record, new values on
+a kept plan."""
+import numpy as np
+import pytest
+
+from paper_2404_04541_amd import workloads as W
+from helpers import gpu_product, assert_matches_oracle
+
+pytestmark = pytest.mark.gpu
+HASH, COLUMN_LIST = 2, 4
+
+
+def csr(rows, cols, dtype, seed):
+    lens = [len(r) for r in rows]
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    colidx = np.concatenate([np.asarray(r, dtype=np.int32) for r in rows]) if sum(lens) else np.zeros(0, np.int32)
+    return W.CSR(len(rows), cols, rowptr, colidx, W.draw_values(int(sum(lens)), -1.0, 1.0, dtype, seed, 1))
+
+
+def operands(cols, dtype, seed=11):
+    """Rows of 129 to 768 products: B rows of 1 to 13 entries, overlapping or not; the last rows of B end its arrays."""
+    rng = np.random.default_rng(seed)
+    b = [np.sort(rng.choice(min(cols, 400), size=1 + i % 13, replace=False)) for i in range(90)]           # few columns: much merging
+    b += [np.sort(rng.choice(cols, size=1 + i % 13, replace=False)) for i in range(90)]                     # many columns
+    b += [np.sort(rng.choice(cols, size=n, replace=False)) for n in (192, 193, 129, 768, 3, 2, 1, 1)]
+    b += [np.arange(cols - 5, cols)]
+    a = []
+    for n in (20, 33, 63, 64, 65, 90):
+        for lo in (0, 90):
+            a.append(rng.choice(np.arange(lo, lo + 90), size=n, replace=False))
+    a += [[180], [181], [182], [183], [180, 184], [180, 185, 186, 187], [182, 188], [], [182, 188, 188, 182]]
+    a += [rng.choice(np.arange(0, 189), size=30, replace=False) for _ in range(40)]
+    return csr(a, len(b), dtype, seed), csr(b, cols, dtype, seed + 1)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("cols", [1000, 1 << 23, (1 << 23) + 1, 30_000_000])
+@pytest.mark.parametrize("force", [0, HASH])
+def test_recorded_rows(cols, dtype, force):
+    A, B = operands(cols, dtype)
+    assert_matches_oracle(A, B, gpu_product(A, B, force), what=f"cols={cols} force={force}")
+
+
+@pytest.mark.parametrize("limit", [0, 4096, 16384])
+def test_room_for_some_rows(limit):
+    A, B = operands(5000, np.float64)
+    assert_matches_oracle(A, B, gpu_product(A, B, options={COLUMN_LIST: limit}), what=f"list of {limit} bytes")
+
+
+@pytest.mark.parametrize("force", [0, HASH])
+def test_new_values_on_a_kept_plan(force):
+    import torch
+    from paper_2404_04541_amd import binding as sg
+    A, B = operands(5000, np.float64)
+    h = sg.Handle()
+    h.set_option(sg.OPT_FORCE_WORKSPACE, force)
+    dA, dB = sg.to_device(A), sg.to_device(B)
+    rp, _, plan = sg.spgemm_symbolic(h, dA, dB)
+    for seed in (21, 22):
+        A.values[:] = W.draw_values(A.nnz, -1.0, 1.0, np.float64, seed, 1)
+        B.values[:] = W.draw_values(B.nnz, -1.0, 1.0, np.float64, seed, 2)
+        dA, dB = sg.to_device(A), sg.to_device(B)   # (other buffers as well)
+        col, val = sg.spgemm_numeric(h, plan, dA, dB, rp)
+        torch.cuda.synchronize()
+        assert_matches_oracle(A, B, (rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy()), what=f"values {seed}")
+    plan.destroy()
+
+
+def short_operands(b_rows, cols, dtype, sort_b, seed=31):
+    """Rows of 0 to 128 products: one long B row, many short ones, more entries than lanes (most of them with empty B rows),
+    columns hit several times; with more than 2^19 rows of B the row count describes the entries."""
+    rng = np.random.default_rng(seed)
+    used = 400
+    b = []
+    for i in range(used):
+        n = [0, 1, 2, 3, 4, 5, 8, 16, 17, 31, 32, 33, 64, 127, 128][i % 15]
+        pick = rng.choice(min(cols, 300) if i % 2 else cols, size=min(n, 300), replace=False)
+        b.append(np.sort(pick) if sort_b else pick)
+    lens = np.array([len(r) for r in b])
+    a = []
+    for total in list(range(0, 34)) + [63, 64, 65, 100, 127, 128]:
+        for most in (4, 16, 128):
+            row, left = [], total
+            while left > 0:
+                ok = np.flatnonzero((lens <= min(left, most)) & (lens > 0))
+                k = int(rng.choice(ok))
+                row.append(k)
+                left -= int(lens[k])
+            a.append(row)
+            a.append(row[:len(row) // 2] + [0, 15, 30] * 30 + row[len(row) // 2:])   # (empty B rows between)
+    B = csr(b, cols, dtype, seed)
+    gap = max(0, b_rows - used)
+    B = W.CSR(used + gap, cols, np.concatenate([B.rowptr, np.full(gap, B.rowptr[-1])]), B.colidx, B.values)
+    return csr(a, used + gap, dtype, seed + 1), B
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("sort_b", [True, False])
+@pytest.mark.parametrize("b_rows,cols", [(400, 300), (600_000, 300), (400, 1 << 23), (600_000, 1 << 25), (400, (1 << 25) + 1), (600_000, 40_000_000)])
+def test_short_rows(b_rows, cols, dtype, sort_b):
+    A, B = short_operands(b_rows, cols, dtype, sort_b)
+    for options in ({}, {COLUMN_LIST: 0}, {COLUMN_LIST: 20_000}):   # (words for both bins, for none, for one)
+        assert_matches_oracle(A, B, gpu_product(A, B, options=options), what=f"rows={b_rows} cols={cols} {options}")
