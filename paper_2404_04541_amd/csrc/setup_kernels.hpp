@@ -9,15 +9,44 @@ __global__ void k_init_control(Control* ctl) {
   for (int i = threadIdx.x; i < (int)(sizeof(Control) / sizeof(unsigned)); i += blockDim.x) w[i] = 0;
 }
 
-// Checks B: rowptr starts at 0, is non-decreasing, ends at nnz, no row of 2^31 or more
+constexpr int kCountThreads = 1024;
+constexpr int kCountMaxRows = 1024;   // rows of A in a chunk: at most
+
+// Adds one row per lane (bin < 0: none) to the bin populations in LDS, the lanes of a bin together: atomics of 64 lanes on the
+// same counter are executed one after the other.  nnz may be null.
+__device__ __forceinline__ unsigned long long wave_sum64(unsigned long long v) {   // 24-bit pieces: 64 of them stay below 2^31
+  unsigned long long s = (unsigned)__builtin_amdgcn_readlane(wave_incl_scan((int)(v & 0xffffff)), kWave - 1);
+  if (__any((v >> 24) != 0)) {
+    s += (unsigned long long)(unsigned)__builtin_amdgcn_readlane(wave_incl_scan((int)((v >> 24) & 0xffffff)), kWave - 1) << 24;
+    s += (unsigned long long)(unsigned)__builtin_amdgcn_readlane(wave_incl_scan((int)(v >> 48)), kWave - 1) << 48;
+  }
+  return s;
+}
+
+__device__ __forceinline__ void add_to_bins(int bin, unsigned long long ip, unsigned nnz, unsigned* hist, unsigned long long* hip, unsigned long long* hnz) {
+  unsigned long long left = __ballot(bin >= 0);
+  while (left) {
+    const int v = __builtin_amdgcn_readlane(bin, __ffsll((long long)left) - 1);
+    const unsigned long long mine = __ballot(bin == v);
+    const unsigned long long s = wave_sum64(bin == v ? ip : 0ULL);
+    const unsigned long long z = hnz ? wave_sum64(bin == v ? (unsigned long long)nnz : 0ULL) : 0ULL;
+    if (lane_id() == 0) {
+      atomicAdd(&hist[v], (unsigned)__popcll(mine));
+      if (s) atomicAdd(&hip[v], s);
+      if (z) atomicAdd(&hnz[v], z);
+    }
+    left &= ~mine;
+  }
+}
+
+// Checks B (workgroup `part` of `parts`): rowptr starts at 0, is non-decreasing, ends at nnz, no row of 2^31 or more
 // entries; every column inside [0, cols).  Also counts descents (col[p] <= col[p-1]) over
 // the flat column array and descents that straddle a row boundary: every row is strictly
-// ascending exactly when the two counts agree (k_bin_offsets turns them into b_sorted).
-__global__ __launch_bounds__(256) void k_validate_b(int64_t rows, int64_t cols, int64_t nnz,
-                                                    const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                                    Control* ctl) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// ascending exactly when the two counts agree (k_bin_scatter turns them into b_sorted).
+__device__ __forceinline__ void validate_b(int part, int parts, int64_t rows, int64_t cols, int64_t nnz, const int64_t* __restrict__ rp,
+                                           const int32_t* __restrict__ col, Control* ctl, int (*sums)[kCountThreads / kWave]) {
+  const int64_t stride = (int64_t)parts * kCountThreads;
+  const int64_t t0 = (int64_t)part * kCountThreads + threadIdx.x;
   bool bad = false;
   int flat = 0, bnd = 0;
   if (t0 == 0 && (rp[0] != 0 || rp[rows] != nnz)) bad = true;
@@ -34,51 +63,58 @@ __global__ __launch_bounds__(256) void k_validate_b(int64_t rows, int64_t cols, 
   }
   if (bad) ctl->error = 1;
   // one pair of atomics per workgroup: nearly every wave has descents to report (the row boundaries)
-  __shared__ int part[2][4];
   flat = wave_sum(flat);
   bnd = wave_sum(bnd);
-  if (lane_id() == 0) { part[0][threadIdx.x >> 6] = flat; part[1][threadIdx.x >> 6] = bnd; }
+  if (lane_id() == 0) { sums[0][threadIdx.x >> 6] = flat; sums[1][threadIdx.x >> 6] = bnd; }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const int f4 = part[0][0] + part[0][1] + part[0][2] + part[0][3], b4 = part[1][0] + part[1][1] + part[1][2] + part[1][3];
-    if (f4) atomicAdd(&ctl->desc_flat, (unsigned long long)f4);
-    if (b4) atomicAdd(&ctl->desc_bnd, (unsigned long long)b4);
+  if (threadIdx.x < 2) {
+    unsigned long long t = 0;
+    for (int w = 0; w < kCountThreads / kWave; ++w) t += (unsigned long long)sums[threadIdx.x][w];
+    if (t) atomicAdd(threadIdx.x == 0 ? &ctl->desc_flat : &ctl->desc_bnd, t);
   }
 }
 
-// One workgroup of 1024 threads per 256 consecutive rows of A (a chunk of hub rows holds a large
-// share of all entries, so the chunk gets the widest workgroup): the chunk's A entries are read
-// coalesced, each entry adds the length of its B row to its row's counter in LDS.
+// Bound: the gather of B's row pointer (a line per entry of A where it does not fit the L2 cache: 33.5 M entries 0.56 ms, with the
+// descriptions written 0.64), a chain of three loads where there are few rows.
+// The first `parts` workgroups check B.  The others count the products of A's rows: a workgroup takes chunks of `chunk_rows`
+// consecutive rows (a chunk of hub rows holds a large share of all entries, hence the widest workgroup): the chunk's A
+// entries are read coalesced, each entry adds the length of its B row to its row's counter in LDS, the lanes that hold the
+// same row together (27 entries a row: 27 additions to one address, one after the other, otherwise).
 // desc (optional): start and length of every A entry's B row, for the kernels of short rows.
 // Writes ip (saturated to int32), the symbolic bin, zero counts for rows without products.
-constexpr int kCountThreads = 1024;
-__global__ __launch_bounds__(kCountThreads) void k_count_rows(int64_t m, int64_t nnz_a, int64_t b_rows,
+__global__ __launch_bounds__(kCountThreads) void k_count_rows(int parts, int64_t b_cols, int64_t b_nnz, const int32_t* __restrict__ b_col, int64_t m,
+                                                    int chunk_rows, int64_t nnz_a, int64_t b_rows,
                                                     const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                     const int64_t* __restrict__ b_rp, int* __restrict__ ip_out,
                                                     unsigned char* __restrict__ bin_out, int* __restrict__ cnt_out,
                                                     Control* ctl, int force, int row_block, unsigned long long* __restrict__ desc) {
-  __shared__ long long rp[257];
-  __shared__ unsigned long long ipl[256];
+  __shared__ long long rp[kCountMaxRows + 1];
+  __shared__ unsigned long long ipl[kCountMaxRows];
   __shared__ unsigned hist[kNumBins];
   __shared__ unsigned long long hip[kNumBins];
+  __shared__ int sums[2][kCountThreads / kWave];
   __shared__ int bad;
+  if ((int)blockIdx.x < parts) {
+    validate_b(blockIdx.x, parts, b_rows, b_cols, b_nnz, b_rp, b_col, ctl, sums);
+    return;
+  }
   const int tid = threadIdx.x;
   if (tid < kNumBins) { hist[tid] = 0; hip[tid] = 0; }
   // a workgroup takes several chunks and reports its bin populations once (thousands of workgroups adding to
   // the same few counters cost more than the counting)
   __shared__ long long next_chunk;
-  int64_t chunk = blockIdx.x;
-  while (chunk * 256 < m) {
+  int64_t chunk = blockIdx.x - parts;
+  while (chunk * chunk_rows < m) {
     // (the chunk after this one is drawn now and looked at when this one is done: chunks differ by orders of
     // magnitude in their entries, so they are handed out rather than dealt)
     long long drawn = 0;
-    if (tid == 0) drawn = (long long)gridDim.x + atomicAdd(&ctl->work[3], 1u);
-    const int64_t r0 = chunk * 256;
-    const int nr = (int)((m - r0) < 256 ? (m - r0) : 256);
+    if (tid == 0) drawn = (long long)(gridDim.x - parts) + atomicAdd(&ctl->work[3], 1u);
+    const int64_t r0 = chunk * chunk_rows;
+    const int nr = (int)((m - r0) < chunk_rows ? (m - r0) : chunk_rows);
     __syncthreads();   // (the bin counters are initialised; the chunk before has left rp and ipl)
     if (tid == 0) bad = 0;
     for (int t = tid; t <= nr; t += kCountThreads) rp[t] = a_rp[r0 + t];
-    if (tid < 256) ipl[tid] = 0;
+    if (tid < kCountMaxRows) ipl[tid] = 0;
     __syncthreads();
     if (tid < nr && rp[tid + 1] < rp[tid]) bad = 1;
     if (tid == 0) {
@@ -95,7 +131,8 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int64_t m, int64_t
     const long long lo = rp[0], hi = rp[nr];
     bool badcol = false;
     // four entries per thread and round, so that their (dependent) loads overlap
-    for (long long p0 = lo + tid; p0 < hi; p0 += kCountThreads * 4) {
+    for (long long q0 = lo; q0 < hi; q0 += kCountThreads * 4) {   // (all threads together: lanes are combined below)
+      const long long p0 = q0 + tid;
       int k[4];
       long long len[4];
       int64_t start[4];
@@ -120,28 +157,46 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int64_t m, int64_t
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const long long p = p0 + u * kCountThreads;
+        if (q0 + u * kCountThreads >= hi) break;
         if (desc && p < hi) desc[p] = make_desc(start[u], len[u]);
-        if (len[u] > 0) {
-          // row of entry p: last t with rp[t] <= p
-          int a = 0, b = nr;
-          while (b - a > 1) {
-            const int mid = (a + b) >> 1;
-            if (rp[mid] <= p) a = mid; else b = mid;
-          }
-          atomicAdd(&ipl[a], (unsigned long long)len[u]);
+        // row of entry p: last t with rp[t] <= p
+        int a = 0, b = nr;
+        while (b - a > 1) {
+          const int mid = (a + b) >> 1;
+          if (rp[mid] <= p) a = mid; else b = mid;
         }
+        if (__any(len[u] >= (1LL << 27))) {   // (sixteen of these need more than 32 bits)
+          if (len[u] > 0) atomicAdd(&ipl[a], (unsigned long long)len[u]);
+          continue;
+        }
+        // inside a DPP row of 16 lanes the entries of a row are neighbours: the last of them adds what all have
+        const int row = p < hi ? a : -1;
+        unsigned sum = (unsigned)len[u];
+        auto below = [&](auto step) {
+          constexpr int kStep = decltype(step)::value;
+          const int r = __builtin_amdgcn_update_dpp(-2, row, 0x110 + kStep, 0xf, 0xf, false);
+          const unsigned l = (unsigned)__builtin_amdgcn_update_dpp(0, (int)sum, 0x110 + kStep, 0xf, 0xf, false);
+          if (r == row) sum += l;
+        };
+        below(std::integral_constant<int, 1>{});
+        below(std::integral_constant<int, 2>{});
+        below(std::integral_constant<int, 4>{});
+        below(std::integral_constant<int, 8>{});
+        const int next = __builtin_amdgcn_update_dpp(-2, row, 0x101, 0xf, 0xf, false);
+        if (next != row && sum > 0) atomicAdd(&ipl[a], (unsigned long long)sum);
       }
     }
     if (badcol) ctl->error = 1;
     __syncthreads();
-    if (tid < nr) {
-      const unsigned long long mine = ipl[tid];
-      const int bin = classify_symbolic((long long)mine, force);
-      ip_out[r0 + tid] = mine > 0x7fffffffULL ? 0x7fffffff : (int)mine;
-      bin_out[r0 + tid] = (unsigned char)bin;
-      if (bin == kEmptyBin) cnt_out[r0 + tid] = 0;
-      atomicAdd(&hist[bin], 1u);
-      if (mine) atomicAdd(&hip[bin], mine);
+    {
+      const unsigned long long mine = tid < nr ? ipl[tid] : 0ULL;
+      const int bin = tid < nr ? classify_symbolic((long long)mine, force) : -1;
+      if (tid < nr) {
+        ip_out[r0 + tid] = mine > 0x7fffffffULL ? 0x7fffffff : (int)mine;
+        bin_out[r0 + tid] = (unsigned char)bin;
+        if (bin == kEmptyBin) cnt_out[r0 + tid] = 0;
+      }
+      add_to_bins(bin, mine, 0u, hist, hip, nullptr);
     }
     if (tid == 0) next_chunk = drawn;
     __syncthreads();
@@ -159,116 +214,141 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int64_t m, int64_t
   }
 }
 
-// Numeric classes from ip and the symbolic counts.
-__global__ void k_classify_numeric(int64_t m, const int* __restrict__ ip, const int* __restrict__ cnt,
-                                   unsigned char* __restrict__ bin_out, Control* ctl, int force, int staged_cap) {
+// What the kernels below share.  A workgroup takes kScanTile rows, every wave kScanItems times 64 consecutive ones, so that the
+// lists of a bin ascend and neighbouring groups of a kernel work on neighbouring rows.
+constexpr int kScanThreads = 1024;
+constexpr int kScanItems = 4;
+constexpr int kScanTile = kScanThreads * kScanItems;
+constexpr int kScanWaves = kScanThreads / kWave;
+constexpr int kScanDirect = 4096;   // up to this many tiles every workgroup adds up the sums of the tiles before its own
+
+// Puts the rows of the tile into their bins: every wave ballots per bin and ranks its lanes inside the ballot masks (a
+// wavefront-level prefix count); the waves of a workgroup add their counts up in LDS, so that a bin costs one global atomic
+// per workgroup.  bin[u]: of row tile_row(u), -1 = none.  Also the bin offsets, by the first workgroup for
+// the kernels that follow.
+__device__ __forceinline__ int64_t tile_row(int u) {
+  return (int64_t)blockIdx.x * kScanTile + (threadIdx.x >> 6) * (kScanItems * kWave) + u * kWave + lane_id();
+}
+
+struct ScatterLds {
+  unsigned count[kNumBins][kScanWaves], base[kNumBins], offset[kNumBins + 1];
+};
+__device__ __forceinline__ void scatter_bins(const int (&bin)[kScanItems], int* __restrict__ perm, Control* ctl, int phase, ScatterLds* sl) {
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+  if (tid == 0) {
+    unsigned run = 0;
+    for (int b = 0; b < kNumBins; ++b) { sl->offset[b] = run; run += ctl->hist[phase][b]; }
+    sl->offset[kNumBins] = run;
+  }
+  int rank[kScanItems];
+#pragma unroll
+  for (int u = 0; u < kScanItems; ++u) rank[u] = 0;
+  for (int v = 0; v < kNumBins - 1; ++v) {   // bin 7 holds rows with no work: not listed
+    unsigned before = 0;
+#pragma unroll
+    for (int u = 0; u < kScanItems; ++u) {
+      const unsigned long long mask = __ballot(bin[u] == v);
+      if (bin[u] == v) rank[u] = (int)before + lanes_below(mask);
+      before += (unsigned)__popcll(mask);
+    }
+    if (lane == 0) sl->count[v][wave] = before;
+  }
+  __syncthreads();
+  if (tid < kNumBins - 1) {
+    unsigned run = 0;
+    for (int w = 0; w < kScanWaves; ++w) { const unsigned c = sl->count[tid][w]; sl->count[tid][w] = run; run += c; }
+    sl->base[tid] = run ? sl->offset[tid] + atomicAdd(&ctl->cursor[phase][tid], run) : 0u;
+  }
+  if (blockIdx.x == 0 && tid <= kNumBins) ctl->offset[phase][tid] = sl->offset[tid];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kScanItems; ++u)
+    if (bin[u] >= 0 && bin[u] < kNumBins - 1) perm[sl->base[bin[u]] + sl->count[bin[u]][wave] + rank[u]] = (int)tile_row(u);
+}
+
+// The control block to the host's copy (pinned memory), by one workgroup whose writes to it are done.
+__device__ __forceinline__ void control_out(const Control* ctl, Control* host) {
+  __threadfence();
+  __syncthreads();
+  const unsigned* from = reinterpret_cast<const unsigned*>(ctl);
+  unsigned* to = reinterpret_cast<unsigned*>(host);
+  for (int i = threadIdx.x; i < (int)(sizeof(Control) / 4); i += blockDim.x) to[i] = __hip_atomic_load(from + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Symbolic bins: lists of rows.
+__global__ __launch_bounds__(kScanThreads) void k_bin_scatter(int64_t m, const unsigned char* __restrict__ bin_of, int* __restrict__ perm, Control* ctl,
+                                                              Control* host) {
+  __shared__ ScatterLds sl;
+  int bin[kScanItems];
+#pragma unroll
+  for (int u = 0; u < kScanItems; ++u) {
+    const int64_t i = tile_row(u);
+    bin[u] = i < m ? bin_of[i] : -1;
+  }
+  // (an error of the count leaves rows without a bin; the one that is set below does not matter here, whoever sees it)
+  if (ctl->error != 1) scatter_bins(bin, perm, ctl, 0, &sl);
+  if (blockIdx.x == 0) {
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const int sorted = ctl->desc_flat == ctl->desc_bnd ? 1 : 0;
+      ctl->b_sorted = sorted;
+      // the dense workspaces walk whole rows of an unsorted B per tile: 32-bit piece prefixes
+      if (!sorted && ctl->long_b_row && !ctl->error) ctl->error = 2;
+    }
+    control_out(ctl, host);
+  }
+}
+
+// Numeric classes from ip and the symbolic counts, and the sum of the counts of every tile.
+__global__ __launch_bounds__(kScanThreads) void k_classify_numeric(int64_t m, const int* __restrict__ ip, const int* __restrict__ cnt,
+                                   unsigned char* __restrict__ bin_out, long long* __restrict__ partial, Control* ctl, int force, int staged_cap) {
   __shared__ unsigned hist[kNumBins];
   __shared__ unsigned long long hip[kNumBins], hnz[kNumBins];
+  __shared__ unsigned long long total;
   if (threadIdx.x < kNumBins) { hist[threadIdx.x] = 0; hip[threadIdx.x] = 0; hnz[threadIdx.x] = 0; }
+  if (threadIdx.x == 0) total = 0;
   __syncthreads();
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
-    const int bin = classify_numeric(ip[i], cnt[i], force, staged_cap);
-    bin_out[i] = (unsigned char)bin;
-    atomicAdd(&hist[bin], 1u);
-    if (bin != kEmptyBin) {
-      atomicAdd(&hip[bin], (unsigned long long)ip[i]);
-      atomicAdd(&hnz[bin], (unsigned long long)cnt[i]);
+  unsigned long long sum = 0;
+#pragma unroll
+  for (int u = 0; u < kScanItems; ++u) {
+    const int64_t i = (int64_t)blockIdx.x * kScanTile + u * kScanThreads + threadIdx.x;
+    int bin = -1, p = 0, c = 0;
+    if (i < m) {
+      p = ip[i];
+      c = cnt[i];
+      bin = classify_numeric(p, c, force, staged_cap);
+      bin_out[i] = (unsigned char)bin;
+      sum += (unsigned long long)c;
     }
+    add_to_bins(bin, bin == kEmptyBin ? 0ULL : (unsigned long long)p, bin == kEmptyBin ? 0u : (unsigned)c, hist, hip, hnz);
   }
+  const unsigned long long s = wave_sum64(sum);
+  if (lane_id() == 0) atomicAdd(&total, s);
   __syncthreads();
   if (threadIdx.x < kNumBins && hist[threadIdx.x]) {
     atomicAdd(&ctl->hist[1][threadIdx.x], hist[threadIdx.x]);
     atomicAdd(&ctl->bin_ip[1][threadIdx.x], hip[threadIdx.x]);
     atomicAdd(&ctl->bin_nnz[threadIdx.x], hnz[threadIdx.x]);
   }
-}
-
-__global__ void k_bin_offsets(Control* ctl, int phase) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    unsigned s = 0;
-    for (int b = 0; b < kNumBins; ++b) {
-      ctl->offset[phase][b] = s;
-      s += ctl->hist[phase][b];
-      ctl->cursor[phase][b] = 0;
-    }
-    ctl->offset[phase][kNumBins] = s;
-    if (phase == 0) {
-      ctl->b_sorted = (ctl->desc_flat == ctl->desc_bnd) ? 1 : 0;
-      // the dense workspaces walk whole rows of an unsorted B per tile: 32-bit piece prefixes
-      if (!ctl->b_sorted && ctl->long_b_row && !ctl->error) ctl->error = 2;
-    }
-  }
-}
-
-// Scatter row ids into their bins.  Each wave ballots per bin and ranks its lanes inside the
-// ballot mask (a wavefront-level prefix count); the waves of a workgroup add their counts up in
-// LDS, so that a bin costs one global atomic per workgroup of 1024 rows.
-constexpr int kScatterThreads = 1024;
-__global__ __launch_bounds__(kScatterThreads) void k_bin_scatter(int64_t m, const unsigned char* __restrict__ bin, int* __restrict__ perm,
-                                                                 Control* ctl, int phase) {
-  constexpr int kWaves = kScatterThreads / kWave;
-  __shared__ unsigned wcount[kNumBins][kWaves];   // per bin: rows of each wave, then their prefix
-  __shared__ unsigned base[kNumBins];
-  if (ctl->error) return;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int b = i < m ? bin[i] : -1;
-  const int lane = lane_id(), wave = threadIdx.x >> 6;
-  const unsigned long long below = lane == 0 ? 0ULL : (~0ULL >> (64 - lane));
-  int rank = 0;
-  for (int v = 0; v < kNumBins - 1; ++v) {   // bin 7 holds rows with no work: not listed
-    const unsigned long long mask = __ballot(b == v);
-    if (lane == 0) wcount[v][wave] = (unsigned)__popcll(mask);
-    if (b == v) rank = __popcll(mask & below);
-  }
-  __syncthreads();
-  if (threadIdx.x < kNumBins - 1) {
-    const int v = threadIdx.x;
-    unsigned run = 0;
-    for (int w = 0; w < kWaves; ++w) { const unsigned c = wcount[v][w]; wcount[v][w] = run; run += c; }
-    base[v] = run ? atomicAdd(&ctl->cursor[phase][v], run) : 0u;
-  }
-  __syncthreads();
-  if (b >= 0 && b < kNumBins - 1) perm[ctl->offset[phase][b] + base[b] + wcount[b][wave] + rank] = (int)i;
+  if (threadIdx.x == 0) partial[blockIdx.x] = (long long)total;
 }
 
 // ---- exclusive scan of int32 row counts into the int64 row pointer -------------------
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 16;
-constexpr int kScanTile = kScanThreads * kScanItems;
+constexpr int kScanBlockThreads = 256;
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_partials(int64_t m, const int* __restrict__ cnt,
-                                                                long long* __restrict__ partial) {
-  const int64_t base = (int64_t)blockIdx.x * kScanTile;
-  long long s = 0;
-  for (int t = 0; t < kScanItems; ++t) {
-    const int64_t i = base + (int64_t)t * kScanThreads + threadIdx.x;
-    if (i < m) s += cnt[i];
-  }
-  for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, kWave);
-  __shared__ long long ws[kScanThreads / kWave];
-  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    long long t = 0;
-    for (int w = 0; w < kScanThreads / kWave; ++w) t += ws[w];
-    partial[blockIdx.x] = t;
-  }
-}
-
-__global__ __launch_bounds__(kScanThreads) void k_scan_blocks(int64_t nblocks, long long* __restrict__ partial,
+__global__ __launch_bounds__(kScanBlockThreads) void k_scan_blocks(int64_t nblocks, long long* __restrict__ partial,
                                                               int64_t m, int64_t* __restrict__ rowptr, Control* ctl) {
   // single workgroup: exclusive scan of the per-tile sums, in place
-  __shared__ long long tile[kScanThreads];
+  __shared__ long long tile[kScanBlockThreads];
   __shared__ long long carry;
   if (threadIdx.x == 0) carry = 0;
   __syncthreads();
-  for (int64_t b0 = 0; b0 < nblocks; b0 += kScanThreads) {
+  for (int64_t b0 = 0; b0 < nblocks; b0 += kScanBlockThreads) {
     const int64_t i = b0 + threadIdx.x;
     const long long v = i < nblocks ? partial[i] : 0;
     tile[threadIdx.x] = v;
     __syncthreads();
-    for (int d = 1; d < kScanThreads; d <<= 1) {
+    for (int d = 1; d < kScanBlockThreads; d <<= 1) {
       long long t = threadIdx.x >= d ? tile[threadIdx.x - d] : 0;
       __syncthreads();
       tile[threadIdx.x] += t;
@@ -276,7 +356,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_blocks(int64_t nblocks, l
     }
     if (i < nblocks) partial[i] = carry + tile[threadIdx.x] - v;
     __syncthreads();
-    if (threadIdx.x == 0) carry += tile[kScanThreads - 1];
+    if (threadIdx.x == 0) carry += tile[kScanBlockThreads - 1];
     __syncthreads();
   }
   if (threadIdx.x == 0) {
@@ -285,32 +365,66 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_blocks(int64_t nblocks, l
   }
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_final(int64_t m, const int* __restrict__ cnt,
-                                                             const long long* __restrict__ partial,
-                                                             int64_t* __restrict__ rowptr) {
-  // thread t owns kScanItems consecutive rows of the tile
-  __shared__ long long tsum[kScanThreads];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  int v[kScanItems];
-  long long s = 0;
+// Six launches (classes, offsets, lists, three of the scan) took 19 us for 1000 rows and 57 us of colliding LDS atomics for
+// 700 000; the two of now 14 and 25 us, and the control block reaches the host without a copy (two copies of 10 to 15 us each).
+// The row pointer and the lists of the numeric bins.  direct: partial holds the sums of the tiles (at most kScanDirect), of
+// which every workgroup adds up its own share; otherwise their exclusive prefix (k_scan_blocks).
+__global__ __launch_bounds__(kScanThreads) void k_scan_final(int64_t m, int64_t tiles, int direct, const int* __restrict__ cnt, const long long* __restrict__ partial,
+                                                             const unsigned char* __restrict__ bin_of, int* __restrict__ perm,
+                                                             int64_t* __restrict__ rowptr, Control* ctl, Control* host) {
+  __shared__ ScatterLds sl;
+  __shared__ unsigned long long before, all;
+  __shared__ long long waves[kScanWaves];
+  const int tid = threadIdx.x;
+  if (tid == 0) { before = 0; all = 0; }
+  int v[kScanItems], bin[kScanItems];
+  long long excl[kScanItems], s = 0;   // entries of the wave's rows before a row, and of all its rows
 #pragma unroll
-  for (int t = 0; t < kScanItems; ++t) {
-    v[t] = (base + t < m) ? cnt[base + t] : 0;
-    s += v[t];
+  for (int u = 0; u < kScanItems; ++u) {
+    const int64_t i = tile_row(u);
+    v[u] = i < m ? cnt[i] : 0;
+    bin[u] = i < m ? bin_of[i] : -1;
   }
-  tsum[threadIdx.x] = s;
+#pragma unroll
+  for (int u = 0; u < kScanItems; ++u) {
+    int incl = wave_incl_scan(v[u] & 0xffffff);   // (24 bits at a time: 64 of them stay below 2^31)
+    excl[u] = s + incl - (v[u] & 0xffffff);
+    s += __builtin_amdgcn_readlane(incl, kWave - 1);
+    if (__any(v[u] >> 24)) {
+      incl = wave_incl_scan(v[u] >> 24);
+      excl[u] += (long long)(incl - (v[u] >> 24)) << 24;
+      s += (long long)__builtin_amdgcn_readlane(incl, kWave - 1) << 24;
+    }
+  }
   __syncthreads();
-  for (int d = 1; d < kScanThreads; d <<= 1) {
-    long long t = threadIdx.x >= d ? tsum[threadIdx.x - d] : 0;
-    __syncthreads();
-    tsum[threadIdx.x] += t;
-    __syncthreads();
+  if (direct) {
+    unsigned long long b = 0, a = 0;
+    for (int64_t t = tid; t < tiles; t += kScanThreads) {
+      if (t >= (int64_t)blockIdx.x && blockIdx.x != 0) break;   // (the first workgroup wants the total)
+      const unsigned long long x = (unsigned long long)partial[t];
+      if (t < (int64_t)blockIdx.x) b += x;
+      a += x;
+    }
+    b = wave_sum64(b);
+    a = wave_sum64(a);
+    if (lane_id() == 0 && b) atomicAdd(&before, b);
+    if (lane_id() == 0 && a) atomicAdd(&all, a);
+  } else if (tid == 0) {
+    before = (unsigned long long)partial[blockIdx.x];
   }
-  long long run = partial[blockIdx.x] + tsum[threadIdx.x] - s;
+  if (lane_id() == 0) waves[tid >> 6] = s;
+  __syncthreads();
+  long long run = (long long)before;
+  for (int w = 0; w < (tid >> 6); ++w) run += waves[w];
 #pragma unroll
-  for (int t = 0; t < kScanItems; ++t) {
-    if (base + t < m) rowptr[base + t] = run;
-    run += v[t];
+  for (int u = 0; u < kScanItems; ++u) {
+    const int64_t i = tile_row(u);
+    if (i < m) rowptr[i] = run + excl[u];
+  }
+  scatter_bins(bin, perm, ctl, 1, &sl);
+  if (blockIdx.x == 0) {
+    if (direct && tid == 0) { rowptr[m] = (int64_t)all; ctl->nnz_c = (long long)all; }
+    control_out(ctl, host);
   }
 }
 

@@ -7,6 +7,7 @@
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -28,6 +29,47 @@ using namespace spg;
 static_assert(num_dense_lds<double>() <= 160 * 1024 && num_dense_lds<float>() <= 160 * 1024, "numeric dense kernel exceeds LDS");
 static_assert(kSymDenseLds <= 160 * 1024, "symbolic dense kernel exceeds LDS");
 static_assert(staged_lds<double>() <= 160 * 1024 && staged_lds<float>() <= 160 * 1024, "staged kernel exceeds LDS");
+
+// Pinned host memory where the symbolic kernels leave the control block for the host.  Allocating and releasing it costs 50 to
+// 300 us, so a few blocks wait for the next calls; a call holds its own from before its first kernel until its stream has been
+// waited for, whatever handle, stream or thread it comes from.
+namespace {
+
+class PinnedBlocks {
+ public:
+  Control* take() {
+    {
+      std::lock_guard<std::mutex> lock(mutex_);
+      if (n_ > 0) return free_[--n_];
+    }
+    void* p = nullptr;
+    return hipHostMalloc(&p, sizeof(Control), hipHostMallocPortable) == hipSuccess ? static_cast<Control*>(p) : nullptr;
+  }
+  void give(Control* p) {
+    {
+      std::lock_guard<std::mutex> lock(mutex_);
+      if (n_ < kKeep) { free_[n_++] = p; return; }
+    }
+    (void)hipHostFree(p);
+  }
+
+ private:
+  static constexpr int kKeep = 16;
+  std::mutex mutex_;
+  Control* free_[kKeep] = {};
+  int n_ = 0;
+};
+PinnedBlocks g_pinned;
+
+struct PinnedLease {
+  Control* p;
+  PinnedLease() : p(g_pinned.take()) {}
+  ~PinnedLease() { if (p) g_pinned.give(p); }
+  PinnedLease(const PinnedLease&) = delete;
+  PinnedLease& operator=(const PinnedLease&) = delete;
+};
+
+}  // namespace
 
 struct TimedLaunch {
   int cls;
@@ -235,29 +277,35 @@ bool wants_desc(const spgemm_csr* A, const spgemm_csr* B) {
   return (double)A->nnz / (double)A->rows * ((double)B->nnz / (double)B->rows) <= (double)kEscLargeCap;
 }
 
+// Rows of A that a workgroup of the row count takes at a time: fewer where there are too few rows to fill the card, more where
+// rows are short (a chunk of 256 rows of one or two entries leaves most of the 1024 threads idle and costs six barriers).
+// 16384 rows of a power-law graph: 256 rows 57 us, 64 rows 27 us; 4.2 M rows of 2.4 entries: 256 rows 232 us, 1024 rows 128 us.
+int count_chunk(spgemm_context* h, int64_t m, int64_t nnz) {
+  if (m >= (int64_t)kCountMaxRows * 2 * h->num_cus && nnz <= 16 * m) return kCountMaxRows;
+  return m >= (int64_t)256 * 2 * h->num_cus ? 256 : 64;
+}
+
 // Symbolic phase, first part: count, check, bin.  Ends with the control block on the host
 // (one synchronisation): the second part sizes its lists and launches from the bin populations.
-int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const spgemm_csr* B, Control* host) {
+int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const spgemm_csr* B, Control* pinned, Control* host) {
   hipStream_t s = h->stream;
   const int64_t m = p->m;
   {
     Timer t(h, SPGEMM_K_COUNT);
-    hipLaunchKernelGGL(k_init_control, dim3(1), dim3(64), 0, s, p->ctl);
-    hipLaunchKernelGGL(k_validate_b, dim3(grid_for(B->nnz > B->rows ? B->nnz : B->rows, 256 * 8, (int64_t)h->num_cus * 16)), dim3(256), 0, s,
-                       B->rows, B->cols, B->nnz, B->rowptr, B->colidx, p->ctl);
-    if (m > 0)
-      hipLaunchKernelGGL(k_count_rows, dim3(grid_for(m, 256, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, s, m, A->nnz, B->rows, A->rowptr, A->colidx,
-                         B->rowptr, p->ip, p->bin, p->cnt, p->ctl, h->force, h->row_block, p->desc);
+    hipLaunchKernelGGL(k_init_control, dim3(1), dim3(256), 0, s, p->ctl);
+    const unsigned parts = grid_for(B->nnz > B->rows ? B->nnz : B->rows, kCountThreads * 8, (int64_t)h->num_cus * 4);
+    const int chunk = count_chunk(h, m, A->nnz);
+    const unsigned groups = m > 0 ? grid_for(m, chunk, (int64_t)h->num_cus * 8) : 0;
+    hipLaunchKernelGGL(k_count_rows, dim3(parts + groups), dim3(kCountThreads), 0, s, (int)parts, B->cols, B->nnz, B->colidx, m, chunk, A->nnz, B->rows,
+                       A->rowptr, A->colidx, B->rowptr, p->ip, p->bin, p->cnt, p->ctl, h->force, h->row_block, p->desc);
   }
   {
     Timer t(h, SPGEMM_K_BIN);
-    hipLaunchKernelGGL(k_bin_offsets, dim3(1), dim3(64), 0, s, p->ctl, 0);
-    if (m > 0)
-      hipLaunchKernelGGL(k_bin_scatter, dim3((unsigned)ceil_div(m, kScatterThreads)), dim3(kScatterThreads), 0, s, m, p->bin, p->perm_sym, p->ctl, 0);
+    hipLaunchKernelGGL(k_bin_scatter, dim3(grid_for(m, kScanTile, (int64_t)1 << 30)), dim3(kScanThreads), 0, s, m, p->bin, p->perm_sym, p->ctl, pinned);
   }
   HIP_TRY(h, hipGetLastError());
-  HIP_TRY(h, hipMemcpyAsync(host, p->ctl, sizeof(Control), hipMemcpyDeviceToHost, s));
   HIP_TRY(h, hipStreamSynchronize(s));
+  std::memcpy(host, pinned, sizeof(Control));
   return SPGEMM_OK;
 }
 
@@ -375,7 +423,7 @@ __global__ void k_set_caps(Control* ctl, unsigned tile_cap, unsigned run_cap, un
 
 template <typename T>
 int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const spgemm_csr* B, int64_t* c_rowptr,
-                 const Control& host) {
+                 const Control& host, Control* pinned) {
   hipStream_t s = h->stream;
   const int64_t m = p->m;
   const int64_t cap_small = (int64_t)h->num_cus * 32;
@@ -430,19 +478,16 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     }
     {
       Timer t(h, SPGEMM_K_BIN);
-      hipLaunchKernelGGL(k_classify_numeric, dim3(grid_for(m, 256, (int64_t)h->num_cus * 8)), dim3(256), 0, s, m, p->ip, p->cnt,
-                         p->bin, p->ctl, h->force, staged);
-      hipLaunchKernelGGL(k_bin_offsets, dim3(1), dim3(64), 0, s, p->ctl, 1);
-      hipLaunchKernelGGL(k_bin_scatter, dim3((unsigned)ceil_div(m, kScatterThreads)), dim3(kScatterThreads), 0, s, m, p->bin, p->perm_num, p->ctl, 1);
+      hipLaunchKernelGGL(k_classify_numeric, dim3((unsigned)p->scan_blocks), dim3(kScanThreads), 0, s, m, p->ip, p->cnt, p->bin, p->partial, p->ctl,
+                         h->force, staged);
     }
   }
   {
     Timer t(h, SPGEMM_K_SCAN);
-    if (p->scan_blocks > 0)
-      hipLaunchKernelGGL(k_scan_partials, dim3((unsigned)p->scan_blocks), dim3(kScanThreads), 0, s, m, p->cnt, p->partial);
-    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanThreads), 0, s, p->scan_blocks, p->partial, m, c_rowptr, p->ctl);
-    if (p->scan_blocks > 0)
-      hipLaunchKernelGGL(k_scan_final, dim3((unsigned)p->scan_blocks), dim3(kScanThreads), 0, s, m, p->cnt, p->partial, c_rowptr);
+    const int direct = p->scan_blocks <= kScanDirect ? 1 : 0;
+    if (!direct) hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanBlockThreads), 0, s, p->scan_blocks, p->partial, m, c_rowptr, p->ctl);
+    hipLaunchKernelGGL(k_scan_final, dim3(p->scan_blocks > 0 ? (unsigned)p->scan_blocks : 1u), dim3(kScanThreads), 0, s, m, p->scan_blocks, direct, p->cnt,
+                       p->partial, p->bin, p->perm_num, c_rowptr, p->ctl, pinned);
   }
   HIP_TRY(h, hipGetLastError());
   return SPGEMM_OK;
@@ -467,7 +512,7 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   const size_t lds_hash_small = hash_lds_bytes<64, 8, true>();
   const size_t lds_hash_large = hash_lds_bytes<256, 11, true>();
   const int64_t* hist = p->stats.num_bin_rows;
-  hipLaunchKernelGGL(k_reset_numeric_work, dim3(1), dim3(64), 0, s, p->ctl);
+  if (hist[4] + hist[5] + hist[6] > 0) hipLaunchKernelGGL(k_reset_numeric_work, dim3(1), dim3(64), 0, s, p->ctl);
   {
     Timer t(h, SPGEMM_K_NUM_ESC);
     // (the words were sorted for the rows of the symbolic bin: they serve when the numeric one holds the same rows)
@@ -612,6 +657,8 @@ int spgemm_symbolic(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, i
   *plan = nullptr;
   if ((rc = ensure_device(h))) return rc;
   drop_timed(h);   // (timed launches of an earlier plan that nobody asked about)
+  PinnedLease pinned;
+  if (!pinned.p) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of pinned host memory failed");
 
   spgemm_plan_s* p = new (std::nothrow) spgemm_plan_s();
   if (!p) return fail(h, SPGEMM_ALLOC_FAILED, "host allocation failed");
@@ -647,13 +694,13 @@ int spgemm_symbolic(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, i
   if (off > plain) p->desc = reinterpret_cast<unsigned long long*>(base + o_desc);
 
   Control host{};
-  rc = run_setup(h, p, A, B, &host);
+  rc = run_setup(h, p, A, B, pinned.p, &host);
   if (rc == SPGEMM_OK && !host.error)
-    rc = (A->dtype == SPGEMM_F32) ? run_symbolic<float>(h, p, A, B, c_rowptr, host) : run_symbolic<double>(h, p, A, B, c_rowptr, host);
+    rc = (A->dtype == SPGEMM_F32) ? run_symbolic<float>(h, p, A, B, c_rowptr, host, pinned.p) : run_symbolic<double>(h, p, A, B, c_rowptr, host, pinned.p);
   if (rc == SPGEMM_OK && !host.error) {
-    hipError_t e = hipMemcpyAsync(&host, p->ctl, sizeof(Control), hipMemcpyDeviceToHost, h->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    const hipError_t e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) rc = fail(h, SPGEMM_HIP_ERROR, std::string("symbolic phase: ") + hipGetErrorString(e));
+    else std::memcpy(&host, pinned.p, sizeof(Control));
   }
   if (rc != SPGEMM_OK) {
     (void)hipStreamSynchronize(h->stream);
@@ -1087,9 +1134,10 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
     Control* ctl = reinterpret_cast<Control*>(tmp + o_ctl);
     Control host{};
     hipLaunchKernelGGL(k_init_control, dim3(1), dim3(64), 0, h->stream, ctl);
+    const int chunk = count_chunk(h, m, A->nnz);
     if (m > 0)
-      hipLaunchKernelGGL(k_count_rows, dim3(grid_for(m, 256, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, h->stream, m, A->nnz, B->rows, A->rowptr, A->colidx,
-                         B->rowptr, reinterpret_cast<int*>(tmp + o_ip), tmp + o_bin, reinterpret_cast<int*>(tmp + o_cnt), ctl, 0, 0, (unsigned long long*)nullptr);
+      hipLaunchKernelGGL(k_count_rows, dim3(grid_for(m, chunk, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, h->stream, 0, B->cols, B->nnz, B->colidx, m, chunk,
+                         A->nnz, B->rows, A->rowptr, A->colidx, B->rowptr, reinterpret_cast<int*>(tmp + o_ip), tmp + o_bin, reinterpret_cast<int*>(tmp + o_cnt), ctl, 0, 0, (unsigned long long*)nullptr);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && m > 0) e = hipMemcpyAsync(ip_host.data(), tmp + o_ip, (size_t)m * 4, hipMemcpyDeviceToHost, h->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(&host, ctl, sizeof(Control), hipMemcpyDeviceToHost, h->stream);
