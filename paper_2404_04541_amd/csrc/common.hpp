@@ -146,6 +146,20 @@ __device__ __forceinline__ int group_incl_scan(int v) {
   }
 }
 
+template <int GROUP>
+__device__ __forceinline__ int group_max_scan(int v) {   // inclusive, inside aligned groups of 16 or 64 lanes, values >= 0
+  auto mx = [](int a, int b) { return a > b ? a : b; };
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true));
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true));
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true));
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true));
+  if constexpr (GROUP == kWave) {
+    v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));
+    v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
+  }
+  return v;
+}
+
 // Sets `bits` in the flag word *word(w) for every calling lane, combining lanes first.  Lanes that
 // hold consecutive entries of an ascending column list hold runs of equal words, and LDS atomics on
 // one address are executed one lane after the other; so inside each DPP row of 16 lanes a lane ORs

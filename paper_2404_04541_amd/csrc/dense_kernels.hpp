@@ -28,9 +28,6 @@ namespace spg {
 
 constexpr int kDenseThreads = 1024;
 constexpr int kDenseWaves = kDenseThreads / kWave;
-constexpr int kShortLen = 32;           // B-row pieces shorter than this are packed across lanes
-constexpr int kUnroll = 4;              // loads in flight per lane while walking a long piece
-constexpr int kChunk = kWave * kUnroll; // elements of a piece that one wave takes at a time
 constexpr int kSymFlagWords = 32768;    // 2^20 columns per symbolic span (128 KB)
 constexpr int kBlkCols = 8192;          // tile boundaries are multiples of this many columns
 constexpr int kBlkShift = 13;
@@ -106,8 +103,8 @@ struct RunRec { int row; unsigned first; int count, d; long long a0, list; };
 struct RowScratch {
   long long start[kSymPieces];   // first B entry of each A entry's piece
   int plen[kSymPieces];          // piece length
-  int cpre[kSymPieces + 1];      // exclusive prefix of chunk counts (long pieces)
-  int spre[kSymPieces + 1];      // exclusive prefix of lengths (short pieces)
+  int cpre[kSymPieces + 1];      // exclusive prefix of quad counts
+  int more[kSymPieces + 1];      // (room for the staging area of the column decode, which takes this struct's place)
   int red[2 * kDenseWaves];
   int s_row;
   int pad;
@@ -135,9 +132,7 @@ __device__ __forceinline__ void block_excl_scan2(int a, int b, int& ea, int& eb,
   eb = pb + ib - b;
 }
 
-constexpr int kChunkUnroll = 8;
-
-// The non-empty pieces that a pass walks, in LDS: first B entry, exclusive prefix of the chunk counts (np + 1
+// The non-empty pieces that a pass walks, in LDS: first B entry, exclusive prefix of the quad counts (np + 1
 // values), length and (numeric) a_ik of every piece.
 template <typename T>
 struct PieceList {
@@ -154,115 +149,99 @@ __device__ __forceinline__ long long uni64(long long v) {
   return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
-__device__ __forceinline__ int lane_get(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
-__device__ __forceinline__ long long lane_get(long long v, int lane) {
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(unsigned long long)v, lane);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)((unsigned long long)v >> 32), lane);
-  return (long long)(((unsigned long long)hi << 32) | lo);
-}
-__device__ __forceinline__ float lane_get(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
-__device__ __forceinline__ double lane_get(double v, int lane) { return __longlong_as_double(lane_get(__double_as_longlong(v), lane)); }
+// Up to four consecutive elements of a piece.
+template <typename T>
+struct Quad {
+  int n = 0;   // elements that are left in the piece from the quad's first on (0: none)
+  T a{};       // a_ik of the piece
+  Run<int32_t, 4> col{};
+  Run<T, 4> b{};
+};
 
-// Visits every element of the pieces once.  A piece is cut into chunks of 64 elements; the
-// chunks of all pieces are dealt to the waves in contiguous shares; a wave reads a chunk
-// coalesced (one element per lane) with kChunkUnroll chunks in flight.  Everything that
-// describes a chunk is wave-uniform: the descriptors of the pieces that a batch of chunks can
-// touch are fetched from LDS by one lane each and handed out with readlane, so a batch costs
-// one LDS round trip before its loads are issued.  f(column, a, b) is called per element
-// (a, b only meaningful when WITH_VALUES); g(columns, a's, b's) gets a whole batch of
-// kChunkUnroll elements per lane (column -1: no element).
+// Visits every element of the pieces once.  A piece is cut into quads; the quads of all pieces are dealt to the waves in
+// contiguous shares of whole batches of 64, a lane takes a quad: one load of four columns and one of four values.  Which piece a lane's quad belongs to: lane i looks at where the i-th piece behind the one in hand begins and pushes
+// i + 1 to the lane whose quad that is; a running maximum spreads it to the lanes behind.
+// g(quad) is called per lane and batch (a, b only meaningful when WITH_VALUES).
+// What bounds the pass is not traffic but what a wave does between loads: chunks of 64 elements with wave-uniform descriptors
+// took about 35 scalar and 10 vector instructions a chunk and were 70 % full with pieces of 122 entries; quads are 98 % full
+// and take about 45 per 256 elements.  R-MAT scale 19 squared (fp32), numeric kernel 27.9 -> 25.9 ms; scale 14: numeric 218 ->
+// 190 us, symbolic 229 -> 208 us; deduplication sweep (fp64) 1.64 -> 1.59 ms.  With values one batch at a time is best (two in
+// flight 26.5 ms, three 29.7, four 31.8: registers; the next one prefetched 25.9, but 1.69 for the sweep); without them the
+// next batch is prefetched (15.8 ms at scale 19 against 16.5).
 template <bool WITH_VALUES, typename T, class G>
-__device__ __forceinline__ void chunk_pass_batches(int np, int nchunks, const PieceList<T> pl, const int32_t* __restrict__ b_col,
-                                                   const T* __restrict__ b_val, G g) {
+__device__ __forceinline__ void quad_pass(int np, int nq, const PieceList<T> pl, const int32_t* __restrict__ b_col,
+                                          const T* __restrict__ b_val, int64_t b_nnz, G g) {
   const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
   np = uni(np);
-  nchunks = uni(nchunks);
-  const int per = (nchunks + kDenseWaves - 1) / kDenseWaves;
-  int c = wave * per;
-  const int cend = c + per < nchunks ? c + per : nchunks;
+  nq = uni(nq);
+  const int nb = (nq + kWave - 1) >> 6;
+  const int per = (nb + kDenseWaves - 1) / kDenseWaves;
+  int c = wave * per * kWave;
+  const int cend = c + per * kWave < nq ? c + per * kWave : nq;
   if (c >= cend) return;
-  int p;
+  int p;   // last piece whose first quad is <= c: among every sixteenth piece first, then among the sixteen
   {
-    int lo = 0, hi = np;   // last piece whose first chunk is <= c
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (uni(pl.cpre[mid]) <= c) lo = mid; else hi = mid;
-    }
-    p = lo;
+    static_assert(kSegCap <= 16 * kWave && kSymPieces <= 16 * kWave, "64 steps of sixteen pieces");
+    const int i0 = lane * 16;
+    const int hi = __popcll(__ballot(i0 < np && pl.cpre[i0 < np ? i0 : 0] <= c)) - 1;
+    const int i1 = hi * 16 + lane;
+    p = hi * 16 + __popcll(__ballot(lane < 16 && i1 < np && pl.cpre[i1 < np ? i1 : 0] <= c)) - 1;
   }
-  for (; c < cend; c += kChunkUnroll) {
-    // lane i describes piece p + i (a batch of kChunkUnroll chunks touches at most that many pieces)
-    const int pi = p + lane < np ? p + lane : np;
-    const int pj = p + lane < np ? p + lane : np - 1;
-    const int d_first = pl.cpre[pi];
-    const int d_len = pl.len[pj];
-    const long long d_s = pl.s[pj];
-    const T d_av = WITH_VALUES ? pl.av[pj] : T(0);
-    int q = 0;
-    // the piece in hand (wave-uniform; re-read from the lanes only when the piece changes)
-    int q_first = lane_get(d_first, 0), q_next = lane_get(d_first, 1), q_len = lane_get(d_len, 0);
-    const int32_t* pc = b_col + lane_get(d_s, 0);
-    const T* pv = b_val + lane_get(d_s, 0);
-    T q_av = WITH_VALUES ? lane_get(d_av, 0) : T(0);
-    int col[kChunkUnroll];
-    T bv[kChunkUnroll], au[kChunkUnroll];
-#pragma unroll
-    for (int u = 0; u < kChunkUnroll; ++u) {
-      const int cu = c + u;
-      col[u] = -1;
-      bv[u] = T(0);
-      au[u] = T(0);
-      if (cu < cend) {
-        if (cu >= q_next) {   // every piece has at least one chunk: one step suffices
-          ++q;
-          q_first = q_next;
-          q_next = lane_get(d_first, q + 1);
-          q_len = lane_get(d_len, q);
-          pc = b_col + lane_get(d_s, q);
-          pv = b_val + lane_get(d_s, q);
-          if (WITH_VALUES) q_av = lane_get(d_av, q);
-        }
-        const int off = (cu - q_first) * kWave + lane;
-        // (wave-uniform piece start + 32-bit lane offset: scalar base, one vector offset)
-        if (off < q_len) {
-          // (a piece is far shorter than 2^30 elements: the byte offset fits 32 bits, which lets the
-          // load take the scalar base plus one vector offset)
-          const unsigned byte_off = (unsigned)off * (unsigned)sizeof(int32_t);
-          col[u] = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(pc) + byte_off);
-          if (WITH_VALUES) bv[u] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(pv) + (unsigned)off * (unsigned)sizeof(T));
-        }
-        au[u] = q_av;
+  auto fetch = [&](int cu, Quad<T>& o) {
+    const int ahead = p + 1 + lane;
+    const int begins = (ahead < np ? pl.cpre[ahead] : 0x7fffffff) - cu;   // (1 or more: piece p holds quad cu)
+    int m = __builtin_amdgcn_ds_permute(begins < kWave ? begins * 4 : 0, lane + 1);   // (the others push to lane 0, which does not look)
+    m = group_max_scan<kWave>(lane == 0 ? 0 : m);
+    const int piece = p + m;
+    const int q = cu + lane;
+    const int off = (q - pl.cpre[piece]) * 4;
+    const int len = pl.len[piece];
+    const int64_t at = pl.s[piece] + off;
+    if (WITH_VALUES) o.a = pl.av[piece];
+    o.n = q < cend ? len - off : 0;
+    p += __popcll(__ballot(begins <= kWave));
+    if (!__any(o.n > 0 && at + 4 > b_nnz)) {
+      if (o.n > 0) {
+        o.col = load_run<int32_t, 4>(b_col + at);
+        if (WITH_VALUES) o.b = load_run<T, 4>(b_val + at);
       }
+    } else {   // (fewer than four elements behind some lane's position)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (i < o.n) {
+          o.col.v[i] = b_col[at + i];
+          if (WITH_VALUES) o.b.v[i] = b_val[at + i];
+        }
     }
-    p += q;
-    g(col, au, bv);
+  };
+  Quad<T> now;
+  if constexpr (WITH_VALUES) {
+    for (; c < cend; c += kWave) {
+      now = Quad<T>{};
+      fetch(c, now);
+      g(now);
+    }
+  } else {
+    fetch(c, now);
+    while (true) {   // (the next batch is on its way while g works on this one)
+      Quad<T> next;
+      const bool more = c + kWave < cend;
+      if (more) fetch(c + kWave, next);
+      g(now);
+      if (!more) break;
+      now = next;
+      c += kWave;
+    }
   }
 }
 
-// chunk_pass with a functor f(column, a, b) per element.
-template <bool WITH_VALUES, typename T, class F>
-__device__ __forceinline__ void chunk_pass(int np, int nchunks, const PieceList<T> pl, const int32_t* __restrict__ b_col,
-                                           const T* __restrict__ b_val, F f) {
-  chunk_pass_batches<WITH_VALUES, T>(np, nchunks, pl, b_col, b_val,
-                                     [&](const int (&col)[kChunkUnroll], const T (&au)[kChunkUnroll], const T (&bv)[kChunkUnroll]) {
-#pragma unroll
-                                       for (int u = 0; u < kChunkUnroll; ++u)
-                                         if (col[u] >= 0) f(col[u], au[u], bv[u]);
-                                     });
-}
-
-// Walks every pair (A entry p of the row, B entry q of row a_col[p]) and calls
-// f(column).  range(k, s, en) may narrow the piece [s, en) of B row k first.  Up to kSymPieces A
-// entries are described at once (one per thread).  Pieces of kShortLen or more are compacted to the
-// front of the scratch arrays and walked like the numeric kernel's pieces: in chunks of 64 elements,
-// dealt to the 16 waves in contiguous shares, kChunkUnroll chunks of whatever pieces in flight per
-// wave.  The shorter pieces are compacted to the back and walked by all threads as one index space,
-// a thread finding its piece by a search over the prefix of their lengths.
-// Contains barriers: every thread of the workgroup must call it.
-template <class Range, class F, class FB>
+// Walks every pair (A entry p of the row, B entry q of row a_col[p]) and hands the columns to f, a quad per lane at a time.
+// range(k, s, en) may narrow the piece [s, en) of B row k first.  Up to kSymPieces A entries are described at once (one per
+// thread).  Contains barriers: every thread of the workgroup must call it.
+template <class Range, class F>
 __device__ __forceinline__ void stream_columns(int64_t a0, int d, const int32_t* __restrict__ a_col,
-                                               const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col,
-                                               RowScratch* rs, Range range, F f, FB fb) {
+                                               const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col, int64_t b_nnz,
+                                               RowScratch* rs, Range range, F f) {
   const int tid = threadIdx.x, lane = tid & 63;
   static_assert(kSymPieces <= kDenseThreads, "a thread per described entry");
   for (int base = 0; base < d; base += kSymPieces) {
@@ -277,41 +256,24 @@ __device__ __forceinline__ void stream_columns(int64_t a0, int d, const int32_t*
       range(k, s, en);
       len = (int)(en - s);
     }
-    const bool is_long = len >= kShortLen;
-    const int nch = is_long ? (len + kWave - 1) >> 6 : 0;
-    const int sl = is_long ? 0 : len;
     if (Range::kNarrows) {   // (a narrowed walk covers a part of the row: its products are counted for the caller)
       unsigned long long wl = (unsigned long long)len;
 #pragma unroll
       for (int sh = 1; sh < kWave; sh <<= 1) wl += __shfl_xor(wl, sh, kWave);
       if (lane == 0 && wl) atomicAdd(&rs->span_ip, wl);
     }
-    int li, ec, nl, tc, sj, es, nshort, ts;
-    block_excl_scan2(is_long ? 1 : 0, nch, li, ec, nl, tc, rs->red);
-    block_excl_scan2(sl > 0 ? 1 : 0, sl, sj, es, nshort, ts, rs->red);
-    if (is_long) {
-      rs->start[li] = s;
-      rs->plen[li] = len;
-      rs->cpre[li] = ec;
-    } else if (sl > 0) {   // (long pieces fill the start array from the front, short ones from the back)
-      rs->start[kSymPieces - 1 - sj] = s;
-      rs->spre[sj] = es;
+    int at, eq, np, tq;
+    block_excl_scan2(len > 0 ? 1 : 0, (len + 3) >> 2, at, eq, np, tq, rs->red);
+    if (len > 0) {
+      rs->start[at] = s;
+      rs->plen[at] = len;
+      rs->cpre[at] = eq;
     }
-    if (tid == 0) { rs->cpre[nl] = tc; rs->spre[nshort] = ts; }
     __syncthreads();
-    SPG_CLK(clk_mark(&rs->clk, 2); clk_add(&rs->clk, 18, 1); clk_add(&rs->clk, 19, (unsigned long long)tc);)
-    if (tc > 0)
-      chunk_pass_batches<false, int>(nl, tc, PieceList<int>{rs->start, rs->cpre, rs->plen, nullptr}, b_col, static_cast<const int*>(nullptr),
-                                     [&](const int (&c)[kChunkUnroll], const int (&)[kChunkUnroll], const int (&)[kChunkUnroll]) { fb(c); });
+    SPG_CLK(clk_mark(&rs->clk, 2); clk_add(&rs->clk, 18, 1); clk_add(&rs->clk, 19, (unsigned long long)tq);)
+    if (tq > 0)
+      quad_pass<false, int>(np, tq, PieceList<int>{rs->start, rs->cpre, rs->plen, nullptr}, b_col, static_cast<const int*>(nullptr), b_nnz, f);
     SPG_CLK(clk_mark(&rs->clk, 3);)
-    for (int t = tid; t < ts; t += kDenseThreads) {
-      int lo = 0, hi = nshort;   // last short piece whose first element is <= t
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (rs->spre[mid] <= t) lo = mid; else hi = mid;
-      }
-      f(b_col[rs->start[kSymPieces - 1 - lo] + (t - rs->spre[lo])]);
-    }
     __syncthreads();
     SPG_CLK(clk_mark(&rs->clk, 4);)
   }
@@ -511,7 +473,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
                                                              int64_t n_cols, const int* __restrict__ ip, int* __restrict__ cnt,
                                                              TileRec* __restrict__ tiles, RunRec* __restrict__ runs,
                                                              int32_t* __restrict__ col_list, int direct_min, int no_tiles_ip,
-                                                             int search_ratio, const int* __restrict__ bp, int nb1) {
+                                                             int search_ratio, const int* __restrict__ bp, int nb1, int64_t b_nnz) {
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned* flags = reinterpret_cast<unsigned*>(smem);                               // kSymFlagWords
   RowScratch* rs = reinterpret_cast<RowScratch*>(smem + (size_t)kSymFlagWords * 4);
@@ -554,31 +516,28 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
       SPG_CLK(clk_mark(&rs->clk, 1); clk_add(&rs->clk, 17, 1);)
       const int lo = (int)c0;
       const int64_t hi = c1;
-      auto mark = [&](int c) {
-        if (c >= lo && (int64_t)c < hi) atomicOr(&flags[(c - lo) >> 5], 1u << ((c - lo) & 31));
-      };
-      // a batch of columns: the flag words are read first (reads of one address are broadcast), and only bits
-      // that are not set yet go through the atomic (hub columns are set early and hit by most pieces)
-      auto mark_batch = [&](const int (&c)[kChunkUnroll]) {
-        unsigned w[kChunkUnroll];
+      // the flag words are read first (reads of one address are broadcast), and only bits that are not set yet go
+      // through the atomic (hub columns are set early and hit by most pieces)
+      auto mark = [&](const Quad<int>& q) {
+        unsigned w[4];
+        bool ok[4];
 #pragma unroll
-        for (int u = 0; u < kChunkUnroll; ++u) {
-          const bool ok = c[u] >= lo && (int64_t)c[u] < hi;
-          w[u] = flags[ok ? (c[u] - lo) >> 5 : 0];
+        for (int i = 0; i < 4; ++i) {
+          ok[i] = i < q.n && q.col.v[i] >= lo && (int64_t)q.col.v[i] < hi;
+          w[i] = flags[ok[i] ? (q.col.v[i] - lo) >> 5 : 0];
         }
 #pragma unroll
-        for (int u = 0; u < kChunkUnroll; ++u) {
-          const bool ok = c[u] >= lo && (int64_t)c[u] < hi;
-          const unsigned bit = 1u << ((c[u] - lo) & 31);
-          if (ok && !(w[u] & bit)) atomicOr(&flags[(c[u] - lo) >> 5], bit);
+        for (int i = 0; i < 4; ++i) {
+          const unsigned bit = 1u << ((q.col.v[i] - lo) & 31);
+          if (ok[i] && !(w[i] & bit)) atomicOr(&flags[(q.col.v[i] - lo) >> 5], bit);
         }
       };
       if (n_cols > span && sorted && bp)
-        stream_columns(a0, d, a_col, b_rp, b_col, rs, TableRange{bp, nb1, (int)(c0 >> kBlkShift), (int)((c1 + kBlkCols - 1) >> kBlkShift)}, mark, mark_batch);
+        stream_columns(a0, d, a_col, b_rp, b_col, b_nnz, rs, TableRange{bp, nb1, (int)(c0 >> kBlkShift), (int)((c1 + kBlkCols - 1) >> kBlkShift)}, mark);
       else if (n_cols > span && sorted)
-        stream_columns(a0, d, a_col, b_rp, b_col, rs, SearchRange{b_col, lo, hi}, mark, mark_batch);
+        stream_columns(a0, d, a_col, b_rp, b_col, b_nnz, rs, SearchRange{b_col, lo, hi}, mark);
       else
-        stream_columns(a0, d, a_col, b_rp, b_col, rs, NoRange{}, mark, mark_batch);
+        stream_columns(a0, d, a_col, b_rp, b_col, b_nnz, rs, NoRange{}, mark);
       // entries per block and per group: thread t owns kWordsPerThread consecutive flag words
       {
         constexpr int kWordsPerThread = kSymFlagWords / kDenseThreads;
@@ -819,7 +778,7 @@ constexpr size_t kSymDenseLds = (size_t)kSymFlagWords * 4 + sizeof(RowScratch) +
 template <typename T>
 struct NumScratch {
   long long c_s[kSegCap];      // first B entry of every non-empty piece of the tile
-  int c_cpre[kSegCap + 1];     // exclusive prefix of the pieces' chunk counts
+  int c_cpre[kSegCap + 1];     // exclusive prefix of the pieces' quad counts
   int c_len[kSegCap];          // piece length
   T c_av[kSegCap];             // a_ik of the piece
   TileRec rec[kRunTiles];
@@ -848,20 +807,19 @@ __device__ __forceinline__ void piece_range(int k, long long rs, long long re, i
 }
 
 // Compacts the non-empty pieces of the workgroup's threads into c_s / c_cpre / c_len / c_av.
-// Returns their number and the chunk total.  Contains barriers.
+// Returns their number and the quad total.  Contains barriers.
 template <typename T>
-__device__ __forceinline__ void tile_pieces(NumScratch<T>* ns, long long s, int len, T av, int& np, int& nchunks) {
+__device__ __forceinline__ void tile_pieces(NumScratch<T>* ns, long long s, int len, T av, int& np, int& nquads) {
   int idx, cpre;
-  block_excl_scan2(len > 0 ? 1 : 0, (len + kWave - 1) >> 6, idx, cpre, np, nchunks, ns->red);
+  block_excl_scan2(len > 0 ? 1 : 0, (len + 3) >> 2, idx, cpre, np, nquads, ns->red);
   if (len > 0) {
     ns->c_s[idx] = s;
     ns->c_cpre[idx] = cpre;
     ns->c_len[idx] = len;
     ns->c_av[idx] = av;
   }
-  if (threadIdx.x == 0) ns->c_cpre[np] = nchunks;
   __syncthreads();
-  SPG_CLK(clk_add(&ns->clk, 20, (unsigned long long)nchunks); clk_add(&ns->clk, 21, (unsigned long long)np);)
+  SPG_CLK(clk_add(&ns->clk, 20, (unsigned long long)nquads); clk_add(&ns->clk, 21, (unsigned long long)np);)
 }
 
 template <typename T, bool CHECK>
@@ -870,7 +828,7 @@ __device__ __forceinline__ void num_dense_run(const RunRec rr, NumScratch<T>* ns
                                               const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col,
                                               const T* __restrict__ b_val, int64_t n_cols, const int* __restrict__ bp, int nb1,
                                               const int32_t* __restrict__ col_list,
-                                              int64_t out_row, int32_t* __restrict__ c_col, T* __restrict__ c_val,
+                                              int64_t b_nnz, int64_t out_row, int32_t* __restrict__ c_col, T* __restrict__ c_val,
                                               const int (&pre_k)[kRegSegs], const T (&pre_av)[kRegSegs]) {
   const int tid = threadIdx.x;
   // the row's structure in the plan: none, its columns, or its flag words
@@ -996,27 +954,24 @@ __device__ __forceinline__ void num_dense_run(const RunRec rr, NumScratch<T>* ns
       for (int sg = 0; sg < nseg; ++sg) {
         T av = my_av;
         if (nseg > 1) seg_piece(sg, s, len, av);
-        int np, nchunks;
-        tile_pieces(ns, s, len, av, np, nchunks);   // (its barriers also publish cols and the cleared sums)
-        chunk_pass_batches<true, T>(np, nchunks, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val,
-                                    [&](const int (&c)[kChunkUnroll], const T (&a)[kChunkUnroll], const T (&b)[kChunkUnroll]) {
-          // last position whose column is <= c (the column is in the list); four bisections
+        int np, nquads;
+        tile_pieces(ns, s, len, av, np, nquads);   // (its barriers also publish cols and the cleared sums)
+        quad_pass<true, T>(np, nquads, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
+                               [&](const Quad<T>& q) {
+          // last position whose column is <= c (the column is in the list); the four bisections of a quad
           // advance in lockstep so that their LDS reads overlap
+          int lo[4] = {0, 0, 0, 0};
+          for (int step = top; step > 0; step >>= 1) {
 #pragma unroll
-          for (int u0 = 0; u0 < kChunkUnroll; u0 += 4) {
-            int lo[4] = {0, 0, 0, 0};
-            for (int step = top; step > 0; step >>= 1) {
-#pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                const int mid = lo[u] + step;
-                if (mid < count && cols[mid < count ? mid : 0] <= c[u0 + u]) lo[u] = mid;
-              }
+            for (int i = 0; i < 4; ++i) {
+              const int mid = lo[i] + step;
+              if (mid < count && cols[mid < count ? mid : 0] <= q.col.v[i]) lo[i] = mid;
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-              if (c[u0 + u] >= 0)
-                __hip_atomic_fetch_add(&acc[lo[u]], (double)a[u0 + u] * (double)b[u0 + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           }
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (i < q.n)
+              __hip_atomic_fetch_add(&acc[lo[i]], (double)q.a * (double)q.b.v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         });
         if (nseg > 1) __syncthreads();
       }
@@ -1040,15 +995,18 @@ __device__ __forceinline__ void num_dense_run(const RunRec rr, NumScratch<T>* ns
       for (int sg = 0; sg < nseg; ++sg) {
         T av = my_av;
         if (nseg > 1) seg_piece(sg, s, len, av);
-        int np, nchunks;
-        tile_pieces(ns, s, len, av, np, nchunks);
+        int np, nquads;
+        tile_pieces(ns, s, len, av, np, nquads);
         SPG_CLK(clk_mark(&ns->clk, 7);)
-        chunk_pass<true, T>(np, nchunks, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, [&](int c, T a, T b) {
-          if (!CHECK || (c >= t_lo && (int64_t)c < t_hi)) {
-            const int rel = c - t_lo;
-            if (!have_list && !have_words) atomicOr(&flags[rel >> 5], 1u << (rel & 31));
-            __hip_atomic_fetch_add(&acc[rel], (double)a * (double)b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          }
+        quad_pass<true, T>(np, nquads, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
+                               [&](const Quad<T>& q) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (i < q.n && (!CHECK || (q.col.v[i] >= t_lo && (int64_t)q.col.v[i] < t_hi))) {
+                const int rel = q.col.v[i] - t_lo;
+                if (!have_list && !have_words) atomicOr(&flags[rel >> 5], 1u << (rel & 31));
+                __hip_atomic_fetch_add(&acc[rel], (double)q.a * (double)q.b.v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+              }
         });
         if (nseg > 1) __syncthreads();
       }
@@ -1095,7 +1053,7 @@ __device__ __forceinline__ void num_dense_run(const RunRec rr, NumScratch<T>* ns
         }
       };
       if (have_list) fetch_list(0);
-      int np = 0, nchunks = 0;
+      int np = 0, nquads = 0;
       int* stage = reinterpret_cast<int*>(acc);   // columns by rank, in the space of the sums, on their way to C
       if (!have_words)
         for (int w = tid; w < nw; w += kDenseThreads) fc[w] = make_uint2(0u, 0u);
@@ -1103,7 +1061,7 @@ __device__ __forceinline__ void num_dense_run(const RunRec rr, NumScratch<T>* ns
         // the symbolic phase left the tile's columns (ascending) in the plan: flag bits and ranks
         // come from that list, and the list is this tile's run of C's column indices
         for (int r = tid; r < count; r += kDenseThreads) acc[r] = 0.0;
-        if (nseg == 1) tile_pieces(ns, s, len, my_av, np, nchunks); else __syncthreads();
+        if (nseg == 1) tile_pieces(ns, s, len, my_av, np, nquads); else __syncthreads();
         SPG_CLK(clk_mark(&ns->clk, 3); clk_add(&ns->clk, 17, 1);)
         for (int j0 = 0; j0 < count; j0 += kListBatch * kDenseThreads) {
           if (j0 > 0) fetch_list(j0);
@@ -1172,19 +1130,22 @@ __device__ __forceinline__ void num_dense_run(const RunRec rr, NumScratch<T>* ns
         for (int r = tid; r < count; r += kDenseThreads) stream_store(&c_col[out + r], stage[r]);
         __syncthreads();
         for (int r = tid; r < count; r += kDenseThreads) acc[r] = 0.0;
-        if (nseg == 1) tile_pieces(ns, s, len, my_av, np, nchunks); else __syncthreads();
+        if (nseg == 1) tile_pieces(ns, s, len, my_av, np, nquads); else __syncthreads();
         SPG_CLK(clk_mark(&ns->clk, 15); clk_add(&ns->clk, 17, 1);)
       } else {
       // pass 1: which columns of the tile exist in the row
       for (int sg = 0; sg < nseg; ++sg) {
         T av = my_av;
         if (nseg > 1) seg_piece(sg, s, len, av);
-        tile_pieces(ns, s, len, av, np, nchunks);
-        chunk_pass<false, T>(np, nchunks, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, [&](int c, T, T) {
-          if (!CHECK || (c >= t_lo && (int64_t)c < t_hi)) {
-            const int rel = c - t_lo;
-            atomicOr(&fc[rel >> 5].x, 1u << (rel & 31));
-          }
+        tile_pieces(ns, s, len, av, np, nquads);
+        quad_pass<false, T>(np, nquads, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
+                                [&](const Quad<T>& q) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (i < q.n && (!CHECK || (q.col.v[i] >= t_lo && (int64_t)q.col.v[i] < t_hi))) {
+                const int rel = q.col.v[i] - t_lo;
+                atomicOr(&fc[rel >> 5].x, 1u << (rel & 31));
+              }
         });
         if (nseg > 1) __syncthreads();
       }
@@ -1234,17 +1195,25 @@ __device__ __forceinline__ void num_dense_run(const RunRec rr, NumScratch<T>* ns
         if (nseg > 1) {
           T av;
           seg_piece(sg, s, len, av);
-          tile_pieces(ns, s, len, av, np, nchunks);
+          tile_pieces(ns, s, len, av, np, nquads);
         }
-        auto add = [&](int c, T a, T b) {
-          if (!CHECK || (c >= t_lo && (int64_t)c < t_hi)) {
-            const int rel = c - t_lo;
-            const uint2 w = fc[rel >> 5];
-            const int rank = (int)w.y + __popc(w.x & ((1u << (rel & 31)) - 1u));
-            __hip_atomic_fetch_add(&acc[rank], (double)a * (double)b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        quad_pass<true, T>(np, nquads, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
+                               [&](const Quad<T>& q) {
+          // the four flag words of a quad first, so that their reads overlap
+          uint2 w[4];
+          bool ok[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            ok[i] = i < q.n && (!CHECK || (q.col.v[i] >= t_lo && (int64_t)q.col.v[i] < t_hi));
+            w[i] = fc[ok[i] ? (q.col.v[i] - t_lo) >> 5 : 0];
           }
-        };
-        chunk_pass<true, T>(np, nchunks, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, add);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (ok[i]) {
+              const int rank = (int)w[i].y + __popc(w[i].x & ((1u << ((q.col.v[i] - t_lo) & 31)) - 1u));
+              __hip_atomic_fetch_add(&acc[rank], (double)q.a * (double)q.b.v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        });
         if (nseg > 1) __syncthreads();
       }
       __syncthreads();
@@ -1263,7 +1232,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_num_dense(Control* ctl, const
                                                              const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
                                                              const int32_t* __restrict__ b_col, const T* __restrict__ b_val,
                                                              int64_t n_cols, const int* __restrict__ bp, int nb1,
-                                                             const int32_t* __restrict__ col_list,
+                                                             const int32_t* __restrict__ col_list, int64_t b_nnz,
                                                              const int64_t* __restrict__ c_rp,
                                                              int32_t* __restrict__ c_col, T* __restrict__ c_val) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1319,9 +1288,9 @@ __global__ __launch_bounds__(kDenseThreads) void k_num_dense(Control* ctl, const
     __syncthreads();
     SPG_CLK(clk_mark(&ns->clk, 0); clk_add(&ns->clk, 16, 1);)
     if (sorted)
-      num_dense_run<T, false>(rr, ns, tile, true, a_col, a_val, b_rp, b_col, b_val, n_cols, bp, nb1, col_list, out_row, c_col, c_val, pre_k, pre_av);
+      num_dense_run<T, false>(rr, ns, tile, true, a_col, a_val, b_rp, b_col, b_val, n_cols, bp, nb1, col_list, b_nnz, out_row, c_col, c_val, pre_k, pre_av);
     else
-      num_dense_run<T, true>(rr, ns, tile, false, a_col, a_val, b_rp, b_col, b_val, n_cols, bp, nb1, col_list, out_row, c_col, c_val, pre_k, pre_av);
+      num_dense_run<T, true>(rr, ns, tile, false, a_col, a_val, b_rp, b_col, b_val, n_cols, bp, nb1, col_list, b_nnz, out_row, c_col, c_val, pre_k, pre_av);
   }
   SPG_CLK(clk_mark(&ns->clk, 14); clk_flush(&ns->clk, ctl->clk[1]);)
 }

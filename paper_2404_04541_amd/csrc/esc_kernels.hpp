@@ -42,20 +42,6 @@ __device__ __forceinline__ int group_last(int v) {
   else return __shfl(v, GROUP - 1, GROUP);
 }
 
-template <int GROUP>
-__device__ __forceinline__ int group_max_scan(int v) {   // inclusive, values >= 0
-  auto mx = [](int a, int b) { return a > b ? a : b; };
-  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true));
-  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true));
-  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true));
-  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true));
-  if constexpr (GROUP == kWave) {
-    v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));
-    v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
-  }
-  return v;
-}
-
 // Calls quad(lane of the entry inside the group, first product's position in the row, its index in B's arrays, products) for
 // quads of the chunk; all lanes of the wave call together, lanes without a quad with 0 products.
 template <int GROUP, int CAP, class F>

@@ -474,7 +474,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
       Timer t(h, SPGEMM_K_SYM_DENSE);
       hipLaunchKernelGGL(k_sym_dense, dim3(grid_for(rows_dense, 1, h->num_cus)), dim3(kDenseThreads), kSymDenseLds, s, p->perm_sym,
                          p->ctl, A->rowptr, A->colidx, B->rowptr, B->colidx, B->cols, p->ip, p->cnt, p->tiles, p->runs, p->col_list, h->direct_min,
-                         staged, h->search_ratio, p->blk_ptr, p->blk_ptr_cols);
+                         staged, h->search_ratio, p->blk_ptr, p->blk_ptr_cols, B->nnz);
     }
     {
       Timer t(h, SPGEMM_K_BIN);
@@ -553,7 +553,7 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
     Timer t(h, SPGEMM_K_NUM_DENSE);
     hipLaunchKernelGGL(k_num_dense<T>, dim3(grid_for(rows_dense, 1, h->num_cus)), dim3(kDenseThreads), num_dense_lds<T>(), s, p->ctl,
                        p->bin, p->tiles, p->runs, A->colidx, a_val, B->rowptr, B->colidx, b_val, B->cols, p->blk_ptr,
-                       p->blk_ptr_cols, p->col_list, c_rp, c_col, c_val);
+                       p->blk_ptr_cols, p->col_list, B->nnz, c_rp, c_col, c_val);
   }
   HIP_TRY(h, hipGetLastError());
   return SPGEMM_OK;

@@ -17,6 +17,8 @@
 
 namespace spg {
 
+constexpr int kChunkUnroll = 8;   // chunks of 64 elements in flight per wave
+
 constexpr int kStWinCols = 131072;
 constexpr int kStWinShift = 17;
 constexpr int kStWinWords = kStWinCols / 32;
