@@ -16,12 +16,13 @@
 
 namespace spg {
 
-// Row index of every entry of a CSR matrix (a wave per row).
-__global__ __launch_bounds__(256) void k_expand_rows(int64_t rows, const int64_t* __restrict__ rowptr, int32_t* __restrict__ out) {
-  const int64_t stride = (int64_t)gridDim.x * (blockDim.x / kWave);
-  const int lane = threadIdx.x & 63;
-  for (int64_t r = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6); r < rows; r += stride)
-    for (int64_t p = rowptr[r] + lane; p < rowptr[r + 1]; p += kWave) out[p] = (int32_t)r;
+// Sort key of every entry of a CSR matrix, (column << row_bits) | row: 16 lanes a row.
+__global__ __launch_bounds__(256) void k_column_keys(int64_t rows, int row_bits, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+                                                     unsigned long long* __restrict__ keys) {
+  const int64_t stride = (int64_t)gridDim.x * (blockDim.x / 16);
+  const int lane = threadIdx.x & 15;
+  for (int64_t r = (int64_t)blockIdx.x * (blockDim.x / 16) + (threadIdx.x >> 4); r < rows; r += stride)
+    for (int64_t p = rowptr[r] + lane; p < rowptr[r + 1]; p += 16) keys[p] = ((unsigned long long)(unsigned)col[p] << row_bits) | (unsigned long long)r;
 }
 
 // flag[v] = 1 when vector v (a row, or a column) has entries.
@@ -54,84 +55,259 @@ __global__ __launch_bounds__(256) void k_outer_count(int64_t na, const int32_t* 
   }
 }
 
-// Insert stage: products [t0, t0 + n) of the k -> i -> j order fill the accumulation array.
+// Insert stage: products [t0, t0 + n) of the k -> i -> j order fill the accumulation array.  A workgroup takes one range of the
+// sort that follows, kInsertTile products at a time: the columns of A that a tile touches are found once (two bisections of the
+// offsets), a product then only looks among those, in LDS when they are few; the first digit's counts of the range on the way.
+// 16.8 M products over 10^6 columns: 338 us with a bisection of all offsets per product (and 27 for the counts), 169 us now.
+constexpr int kInsertTile = 4096;
+constexpr int kInsertCols = 2048;
 template <typename T>
-__global__ __launch_bounds__(256) void k_outer_insert(int64_t t0, int64_t n, int64_t na, const long long* __restrict__ off,
+__global__ __launch_bounds__(kSortThreads) void k_outer_insert(int64_t t0, int64_t n, int64_t per_range, int bits, int64_t na, const long long* __restrict__ off,
                                                       const int32_t* __restrict__ match, const int64_t* __restrict__ a_ptr,
                                                       const int32_t* __restrict__ a_idx, const T* __restrict__ a_val,
                                                       const int64_t* __restrict__ b_ptr, const int32_t* __restrict__ b_idx,
                                                       const T* __restrict__ b_val, int col_bits, unsigned long long* __restrict__ keys,
-                                                      double* __restrict__ vals) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) {
-    const int64_t t = t0 + x;
-    int64_t lo = 0, hi = na;   // last column whose first product is <= t
-    while (hi - lo > 1) {
-      const int64_t mid = lo + ((hi - lo) >> 1);
-      if (off[mid] <= t) lo = mid; else hi = mid;
+                                                      double* __restrict__ vals, unsigned* __restrict__ hist) {
+  __shared__ unsigned cnt[kHistCopies][kSortBins];
+  __shared__ long long s_off[kInsertCols];
+  __shared__ long long bound[2];
+  for (int d = threadIdx.x; d < kHistCopies * kSortBins; d += kSortThreads) (&cnt[0][0])[d] = 0;
+  unsigned* mine = cnt[threadIdx.x & (kHistCopies - 1)];
+  const unsigned mask = (1u << bits) - 1;
+  const int64_t lo = (int64_t)blockIdx.x * per_range, hi = lo + per_range < n ? lo + per_range : n;
+  for (int64_t x0 = lo; x0 < hi; x0 += kInsertTile) {
+    const int64_t x1 = x0 + kInsertTile < hi ? x0 + kInsertTile : hi;
+    __syncthreads();   // (the counters are cleared; the tile before has left the offsets)
+    if (threadIdx.x < 2) {
+      const int64_t t = t0 + (threadIdx.x == 0 ? x0 : x1 - 1);
+      int64_t l = 0, h = na;   // last column whose first product is <= t
+      while (h - l > 1) {
+        const int64_t mid = l + ((h - l) >> 1);
+        if (off[mid] <= t) l = mid; else h = mid;
+      }
+      bound[threadIdx.x] = l;
     }
-    const int64_t q = match[lo];
-    const int64_t lb = b_ptr[q + 1] - b_ptr[q];
-    const int64_t local = t - off[lo];
-    const int64_t pa = a_ptr[lo] + local / lb, pb = b_ptr[q] + local % lb;
-    keys[x] = ((unsigned long long)(unsigned)a_idx[pa] << col_bits) | (unsigned)b_idx[pb];
-    vals[x] = (double)a_val[pa] * (double)b_val[pb];
-  }
-}
-
-// head[x] = 1 when component x starts a new coordinate in a sorted array.
-__global__ __launch_bounds__(256) void k_outer_heads(int64_t n, const unsigned long long* __restrict__ keys, unsigned* __restrict__ head) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) head[x] = (x == 0 || keys[x] != keys[x - 1]) ? 1u : 0u;
-}
-
-// Adds up equal coordinates of a sorted array: the thread of a run's first component walks the run in
-// order.
-// pos = exclusive scan of the head flags = where the run's sum goes.
-__global__ __launch_bounds__(256) void k_outer_reduce(int64_t n, const unsigned long long* __restrict__ keys, const double* __restrict__ vals, const unsigned* __restrict__ pos,
-                                                      unsigned long long* __restrict__ out_keys, double* __restrict__ out_vals) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) {
-    const unsigned long long key = keys[x];
-    if (x > 0 && keys[x - 1] == key) continue;
-    double s = vals[x];
-    for (int64_t y = x + 1; y < n && keys[y] == key; ++y) s += vals[y];
-    out_keys[pos[x]] = key;
-    out_vals[pos[x]] = s;
-  }
-}
-
-// Merge stage, first half: two sorted arrays of unique coordinates into one sorted array (the all array's
-// component first where both hold a coordinate): a component's place is its own index plus its rank in
-// the other array.
-__global__ __launch_bounds__(256) void k_outer_merge(int64_t na, const unsigned long long* __restrict__ ka, const double* __restrict__ va,
-                                                     int64_t nb, const unsigned long long* __restrict__ kb, const double* __restrict__ vb,
-                                                     unsigned long long* __restrict__ out_keys, double* __restrict__ out_vals) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < na + nb; x += stride) {
-    const bool first = x < na;
-    const int64_t i = first ? x : x - na;
-    const unsigned long long key = first ? ka[i] : kb[i];
-    const unsigned long long* other = first ? kb : ka;
-    int64_t lo = 0, hi = first ? nb : na;
-    while (lo < hi) {   // first: components of b below key; second: components of a up to and including key
-      const int64_t mid = lo + ((hi - lo) >> 1);
-      const bool below = first ? other[mid] < key : other[mid] <= key;
-      if (below) lo = mid + 1; else hi = mid;
+    __syncthreads();
+    const int64_t c0 = bound[0], c1 = bound[1] + 1;
+    const bool cached = c1 - c0 <= kInsertCols;
+    if (cached) {
+      for (int64_t c = c0 + threadIdx.x; c < c1; c += kSortThreads) s_off[c - c0] = off[c];
+      __syncthreads();
     }
-    out_keys[i + lo] = key;
-    out_vals[i + lo] = first ? va[i] : vb[i];
+    for (int64_t x = x0 + threadIdx.x; x < x1; x += kSortThreads) {
+      const int64_t t = t0 + x;
+      int64_t col, first;
+      if (cached) {
+        int l = 0, h = (int)(c1 - c0);
+        while (h - l > 1) {
+          const int mid = (l + h) >> 1;
+          if (s_off[mid] <= t) l = mid; else h = mid;
+        }
+        col = c0 + l;
+        first = s_off[l];
+      } else {
+        int64_t l = c0, h = c1;
+        while (h - l > 1) {
+          const int64_t mid = l + ((h - l) >> 1);
+          if (off[mid] <= t) l = mid; else h = mid;
+        }
+        col = l;
+        first = off[l];
+      }
+      const int64_t q = match[col];
+      const int64_t b0 = b_ptr[q], lb = b_ptr[q + 1] - b0, local = t - first;
+      int64_t i, j;
+      if (local <= 0xffffffffLL && lb <= 0xffffffffLL) { const unsigned d = (unsigned)local / (unsigned)lb; i = d; j = (unsigned)local - d * (unsigned)lb; }
+      else { i = local / lb; j = local % lb; }
+      const int64_t pa = a_ptr[col] + i, pb = b0 + j;
+      const unsigned long long key = ((unsigned long long)(unsigned)a_idx[pa] << col_bits) | (unsigned)b_idx[pb];
+      keys[x] = key;
+      vals[x] = (double)a_val[pa] * (double)b_val[pb];
+      atomicAdd(&mine[(unsigned)key & mask], 1u);
+    }
   }
+  sort_hist_out(cnt, 1 << bits, blockIdx.x, gridDim.x, hist);
 }
 
-// Compress stage: columns and values of C from the all array (the row pointer comes from the coordinates' high halves).
+// Where components go: coordinate and sum of the all array or, with the last stage, the coordinate (the row pointer comes from
+// it), the column and the value of C.
 template <typename T>
-__global__ __launch_bounds__(256) void k_outer_emit(int64_t n, const unsigned long long* __restrict__ keys, const double* __restrict__ vals,
-                                                    unsigned long long col_mask, int32_t* __restrict__ colidx, T* __restrict__ values) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) {
-    colidx[x] = (int32_t)(keys[x] & col_mask);
-    values[x] = (T)vals[x];
+struct OuterOut {
+  unsigned long long* keys;
+  double* vals;     // null with the last stage
+  int32_t* col;     // null before it
+  T* val;
+  unsigned long long col_mask;
+  __device__ __forceinline__ void put(int64_t at, unsigned long long key, double v) const {
+    keys[at] = key;
+    if (vals) vals[at] = v;
+    else { col[at] = (int32_t)(key & col_mask); val[at] = (T)v; }
+  }
+};
+
+// Equal neighbours of a sorted array are added up, in their order, by the thread of the run's first component.  A wave owns
+// kRunItems * 64 consecutive components of a tile; heads are ballots, so no flags go through memory (flags, their scan and the
+// walk took 450 us for 16.8 M components, the two passes here 140).
+constexpr int kRunItems = 16;
+constexpr int kRunTile = 256 * kRunItems;
+__device__ __forceinline__ int run_heads(int64_t n, const unsigned long long* __restrict__ keys, int64_t first, unsigned long long (&key)[kRunItems],
+                                         unsigned long long (&heads)[kRunItems]) {
+  int total = 0;
+#pragma unroll
+  for (int t = 0; t < kRunItems; ++t) {
+    const int64_t x = first + t * kWave + lane_id();
+    key[t] = x < n ? keys[x] : 0ULL;
+    heads[t] = __ballot(x < n && (x == 0 || keys[x - 1] != key[t]));
+    total += __popcll(heads[t]);
+  }
+  return total;
+}
+
+// sums[tile] = runs that begin in the tile
+__global__ __launch_bounds__(256) void k_run_count(int64_t n, const unsigned long long* __restrict__ keys, unsigned* __restrict__ sums) {
+  __shared__ int part[4];
+  const int wave = threadIdx.x >> 6;
+  unsigned long long key[kRunItems], heads[kRunItems];
+  const int mine = run_heads(n, keys, (int64_t)blockIdx.x * kRunTile + wave * (kRunItems * kWave), key, heads);
+  if (lane_id() == 0) part[wave] = mine;
+  __syncthreads();
+  if (threadIdx.x == 0) sums[blockIdx.x] = (unsigned)(part[0] + part[1] + part[2] + part[3]);
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_run_sum(int64_t n, const unsigned long long* __restrict__ keys, const double* __restrict__ vals,
+                                                 const unsigned* __restrict__ sums, OuterOut<T> out) {
+  __shared__ int part[4];
+  const int wave = threadIdx.x >> 6;
+  const int64_t first = (int64_t)blockIdx.x * kRunTile + wave * (kRunItems * kWave);
+  unsigned long long key[kRunItems], heads[kRunItems];
+  const int mine = run_heads(n, keys, first, key, heads);
+  if (lane_id() == 0) part[wave] = mine;
+  __syncthreads();
+  int64_t at = sums[blockIdx.x];
+  for (int w = 0; w < wave; ++w) at += part[w];
+#pragma unroll
+  for (int t = 0; t < kRunItems; ++t) {
+    const int64_t x = first + t * kWave + lane_id();
+    if ((heads[t] >> lane_id()) & 1ULL) {
+      double s = vals[x];
+      for (int64_t y = x + 1; y < n && keys[y] == key[t]; ++y) s += vals[y];
+      out.put(at + lanes_below(heads[t]), key[t], s);
+    }
+    at += __popcll(heads[t]);
+  }
+}
+
+// Merge stage: the sorted batch (b, unique coordinates) into the all array (a, sorted, unique), equal coordinates added.  The
+// merged order (a's component first where both hold a coordinate) is cut into tiles of kMergeTile; a tile's share of either
+// array comes from a bisection along the diagonal, places inside the tile from bisections in LDS.  b's component of a coordinate
+// that a holds too is a repeat: a's component takes its value along.
+// Two sorted arrays of 16.7 M components each: bisection of the other array per component, head flags, their scan and a walk
+// over the runs 1.47 ms, here 0.61 ms.
+constexpr int kMergeTile = 2048;
+
+// split[t] = components of a among the first t * kMergeTile of the merged order
+__global__ __launch_bounds__(256) void k_merge_split(int64_t na, const unsigned long long* __restrict__ ka, int64_t nb, const unsigned long long* __restrict__ kb,
+                                                     int64_t tiles, int64_t* __restrict__ split) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t > tiles) return;
+  const int64_t d = t * kMergeTile < na + nb ? t * kMergeTile : na + nb;
+  int64_t lo = d > nb ? d - nb : 0, hi = d < na ? d : na;
+  while (lo < hi) {   // the smallest i with a[i] > b[d - 1 - i]: a's component goes first on equal coordinates
+    const int64_t i = lo + ((hi - lo) >> 1);
+    if (ka[i] <= kb[d - 1 - i]) lo = i + 1; else hi = i;
+  }
+  split[t] = lo;
+}
+
+struct MergeLds {
+  unsigned long long key[kMergeTile];   // a's components of the tile, then b's
+  int repeats[kMergeTile + 1];          // repeats among b's components before a position
+  int part[4];
+};
+
+// Loads the tile's keys and finds b's repeats: ml->repeats is their exclusive prefix.  Returns their number.
+__device__ __forceinline__ int merge_tile(int64_t na, const unsigned long long* __restrict__ ka, const unsigned long long* __restrict__ kb,
+                                          int64_t a0, int an, int64_t b0, int bn, MergeLds* ml) {
+  constexpr int kPer = kMergeTile / 256;
+  for (int x = threadIdx.x; x < an; x += 256) ml->key[x] = ka[a0 + x];
+  for (int x = threadIdx.x; x < bn; x += 256) ml->key[an + x] = kb[b0 + x];
+  __syncthreads();
+  int flag[kPer], mine = 0;   // a thread owns kPer consecutive components of b
+#pragma unroll
+  for (int t = 0; t < kPer; ++t) {
+    const int j = threadIdx.x * kPer + t;
+    flag[t] = 0;
+    if (j < bn) {
+      const unsigned long long key = ml->key[an + j];
+      int lo = 0, hi = an;   // components of a up to and including key
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (ml->key[mid] <= key) lo = mid + 1; else hi = mid;
+      }
+      flag[t] = lo > 0 ? (ml->key[lo - 1] == key ? 1 : 0) : (a0 > 0 && ka[a0 - 1] == key ? 1 : 0);
+    }
+    mine += flag[t];
+  }
+  const int incl = wave_incl_scan(mine);
+  if (lane_id() == kWave - 1) ml->part[threadIdx.x >> 6] = incl;
+  __syncthreads();
+  int run = incl - mine, total = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) { const int c = ml->part[w]; if (w < (int)(threadIdx.x >> 6)) run += c; total += c; }
+#pragma unroll
+  for (int t = 0; t < kPer; ++t) {
+    const int j = threadIdx.x * kPer + t;
+    if (j <= bn) ml->repeats[j] = run;
+    run += flag[t];
+  }
+  if (threadIdx.x == 0 && bn == kMergeTile) ml->repeats[kMergeTile] = total;
+  __syncthreads();
+  return total;
+}
+
+// sums[tile] = components that stay
+__global__ __launch_bounds__(256) void k_merge_count(int64_t na, const unsigned long long* __restrict__ ka, int64_t nb, const unsigned long long* __restrict__ kb,
+                                                     const int64_t* __restrict__ split, unsigned* __restrict__ sums) {
+  __shared__ MergeLds ml;
+  const int64_t d0 = (int64_t)blockIdx.x * kMergeTile, d1 = d0 + kMergeTile < na + nb ? d0 + kMergeTile : na + nb;
+  const int64_t a0 = split[blockIdx.x], a1 = split[blockIdx.x + 1];
+  const int repeats = merge_tile(na, ka, kb, a0, (int)(a1 - a0), d0 - a0, (int)((d1 - a1) - (d0 - a0)), &ml);
+  if (threadIdx.x == 0) sums[blockIdx.x] = (unsigned)((int)(d1 - d0) - repeats);
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_merge_put(int64_t na, const unsigned long long* __restrict__ ka, const double* __restrict__ va, int64_t nb,
+                                                   const unsigned long long* __restrict__ kb, const double* __restrict__ vb,
+                                                   const int64_t* __restrict__ split, const unsigned* __restrict__ sums, OuterOut<T> out) {
+  __shared__ MergeLds ml;
+  const int64_t d0 = (int64_t)blockIdx.x * kMergeTile, d1 = d0 + kMergeTile < na + nb ? d0 + kMergeTile : na + nb;
+  const int64_t a0 = split[blockIdx.x], a1 = split[blockIdx.x + 1];
+  const int64_t b0 = d0 - a0;
+  const int an = (int)(a1 - a0), bn = (int)((d1 - a1) - b0);
+  (void)merge_tile(na, ka, kb, a0, an, b0, bn, &ml);
+  const int64_t at = sums[blockIdx.x];
+  for (int i = threadIdx.x; i < an; i += 256) {
+    const unsigned long long key = ml.key[i];
+    int lo = 0, hi = bn;   // components of b below key
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (ml.key[an + mid] < key) lo = mid + 1; else hi = mid;
+    }
+    double v = va[a0 + i];
+    const bool both = lo < bn ? ml.key[an + lo] == key : (b0 + bn < nb && kb[b0 + bn] == key);
+    if (both) v += vb[b0 + lo];
+    out.put(at + i + lo - ml.repeats[lo], key, v);
+  }
+  for (int j = threadIdx.x; j < bn; j += 256) {
+    const unsigned long long key = ml.key[an + j];
+    int lo = 0, hi = an;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (ml.key[mid] <= key) lo = mid + 1; else hi = mid;
+    }
+    const bool repeat = lo > 0 ? ml.key[lo - 1] == key : (a0 > 0 && ka[a0 - 1] == key);
+    if (!repeat) out.put(at + lo + j - ml.repeats[j], key, vb[b0 + j]);
   }
 }
 

@@ -880,12 +880,13 @@ int bits_of(int64_t n) {   // bits that hold 0 .. n-1
 
 // How a sort of n entries by nbits key bits is cut: passes over digits of `bits` bits, ranges of whole tiles.
 struct SortShape {
-  int passes, bits, ranges;
+  int passes, bits, ranges, first_bit;   // (bits below first_bit are not sorted by)
   int64_t per_range;
 };
 
-SortShape sort_shape(int64_t n, int nbits) {
+SortShape sort_shape(int64_t n, int nbits, int first_bit = 0) {
   SortShape sh{};
+  sh.first_bit = first_bit;
   if (nbits < 1) nbits = 1;
   sh.passes = (nbits + 7) / 8;
   sh.bits = (nbits + sh.passes - 1) / sh.passes;
@@ -909,7 +910,7 @@ int sort_pairs(spgemm_context* h, int64_t n, const SortShape& sh, K* const keys[
   unsigned* hist = counters + kSortBins;
   int cur = 0;
   for (int pass = 0; pass < sh.passes; ++pass) {
-    const int shift = pass * sh.bits;
+    const int shift = sh.first_bit + pass * sh.bits;
     const bool last = pass + 1 == sh.passes;
     P* out = (sh.passes - 1 - pass) % 2 == 0 ? pay_a : pay_b;
     if (pass > 0 || !first_counted)
@@ -1238,13 +1239,6 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
 
 namespace {
 
-__global__ void k_pair_keys(int64_t n, int lo_bits, const int32_t* __restrict__ hi, const int32_t* __restrict__ lo,
-                            unsigned long long* __restrict__ keys) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride)
-    keys[p] = ((unsigned long long)(unsigned)hi[p] << lo_bits) | (unsigned)lo[p];
-}
-
 // In-place exclusive scan of n values, v[n] = their sum; sums: ceil(n / kScanTileN) + 1 slots of scratch.
 template <typename T>
 void scan_values(spgemm_context* h, int64_t n, T* v, T* sums) {
@@ -1329,66 +1323,72 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
   unsigned long long* all_k = nullptr;
   double* all_v = nullptr;
   int64_t all_n = 0;
-  // sorted array with repeats -> unique array: head flags, their scan, one walk per run
-  auto reduce = [&](int64_t cnt, const unsigned long long* k, const double* v, unsigned long long** ok, double** ov,
-                    int64_t* on) -> int {
-    unsigned* pos = bufs.get<unsigned>((size_t)cnt + 1);
-    unsigned* sums = bufs.get<unsigned>((size_t)ceil_div(cnt, kScanTileN) + 1);
-    if (!pos || !sums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the merge stage failed");
-    hipLaunchKernelGGL(k_outer_heads, dim3(grid_for(cnt, 256, cap_grid)), dim3(256), 0, s, cnt, k, pos);
-    scan_values(h, cnt, pos, sums);
-    unsigned uniq = 0;
-    HIP_TRY(h, hipMemcpyAsync(&uniq, pos + cnt, 4, hipMemcpyDeviceToHost, s));
+  int32_t* col = nullptr;
+  T* val = nullptr;
+  // Room for `uniq` components of the next all array; the last stage writes columns and values of C in place of sums.
+  auto room = [&](unsigned uniq, bool last, OuterOut<T>* out) -> int {
+    *out = OuterOut<T>{bufs.get<unsigned long long>((size_t)uniq), nullptr, nullptr, nullptr, col_mask};
+    if (last) {
+      out->col = col = bufs.get<int32_t>((size_t)uniq);
+      out->val = val = bufs.get<T>((size_t)uniq);
+    } else {
+      out->vals = bufs.get<double>((size_t)uniq);
+    }
+    if (!out->keys || (last ? !out->col || !out->val : !out->vals)) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the all array failed");
+    return SPGEMM_OK;
+  };
+  // Scan of the tiles' counts; their sum comes to the host.
+  auto total_of = [&](int64_t tiles, unsigned* sums, unsigned* uniq) -> int {
+    hipLaunchKernelGGL(k_scan_top<unsigned>, dim3(1), dim3(256), 0, s, tiles, sums);
+    HIP_TRY(h, hipMemcpyAsync(uniq, sums + tiles, 4, hipMemcpyDeviceToHost, s));
     HIP_TRY(h, hipStreamSynchronize(s));
-    *ok = bufs.get<unsigned long long>((size_t)uniq);
-    *ov = bufs.get<double>((size_t)uniq);
-    if (!*ok || !*ov) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the all array failed");
-    hipLaunchKernelGGL(k_outer_reduce, dim3(grid_for(cnt, 256, cap_grid)), dim3(256), 0, s, cnt, k, v, pos, *ok, *ov);
-    HIP_TRY(h, hipGetLastError());
-    *on = uniq;
-    bufs.release(pos);
-    bufs.release(sums);
     return SPGEMM_OK;
   };
   for (long long t0 = 0; t0 < total; t0 += cap) {
     const int64_t cnt = total - t0 < cap ? total - t0 : cap;
+    const bool last = t0 + cap >= total;
     // insert
-    hipLaunchKernelGGL(k_outer_insert<T>, dim3(grid_for(cnt, 256, cap_grid)), dim3(256), 0, s, (int64_t)t0, cnt, na, off, match, A->ptr, A->idx,
-                       static_cast<const T*>(A->values), B->ptr, B->idx, static_cast<const T*>(B->values), col_bits, keys[0], vals[0]);
-    // sort
     const SortShape sh = sort_shape(cnt, col_bits + bits_of(m));
+    hipLaunchKernelGGL(k_outer_insert<T>, dim3(sh.ranges), dim3(kSortThreads), 0, s, (int64_t)t0, cnt, sh.per_range, sh.bits, na, off, match, A->ptr, A->idx,
+                       static_cast<const T*>(A->values), B->ptr, B->idx, static_cast<const T*>(B->values), col_bits, keys[0], vals[0], counters + kSortBins);
+    // sort
     double* const sorted = vals[sh.passes & 1];
-    const int cur = sort_pairs<unsigned long long, double>(h, cnt, sh, keys, vals[0], sorted, vals[1 - (sh.passes & 1)], counters, false, nullptr, 0ULL);
+    const int cur = sort_pairs<unsigned long long, double>(h, cnt, sh, keys, vals[0], sorted, vals[1 - (sh.passes & 1)], counters, true, nullptr, 0ULL);
     // merge: equal coordinates of the batch, then the batch into the all array
-    unsigned long long* uk = nullptr;
-    double* uv = nullptr;
-    int64_t un = 0;
-    int rc = reduce(cnt, keys[cur], sorted, &uk, &uv, &un);
+    const int64_t tiles = ceil_div(cnt, kRunTile);
+    unsigned* sums = bufs.get<unsigned>((size_t)tiles + 1);
+    if (!sums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the merge stage failed");
+    hipLaunchKernelGGL(k_run_count, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sums);
+    unsigned uniq = 0;
+    int rc = total_of(tiles, sums, &uniq);
     if (rc) return rc;
+    OuterOut<T> batch{};
+    if ((rc = room(uniq, last && all_n == 0, &batch))) return rc;
+    hipLaunchKernelGGL(k_run_sum<T>, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sorted, sums, batch);
+    bufs.release(sums);
     if (all_n == 0) {
-      all_k = uk; all_v = uv; all_n = un;
+      all_k = batch.keys; all_v = batch.vals; all_n = uniq;
       continue;
     }
-    if (all_n + un >= 0xffffffffLL) return fail(h, SPGEMM_UNSUPPORTED, "the all array of the outer product would exceed 2^32 - 1 components");
-    unsigned long long* mk = bufs.get<unsigned long long>((size_t)(all_n + un));
-    double* mv = bufs.get<double>((size_t)(all_n + un));
-    if (!mk || !mv) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the merge stage failed");
-    hipLaunchKernelGGL(k_outer_merge, dim3(grid_for(all_n + un, 256, cap_grid)), dim3(256), 0, s, all_n, all_k, all_v, un, uk, uv, mk, mv);
-    unsigned long long* nk = nullptr;
-    double* nv = nullptr;
-    int64_t nn = 0;
-    rc = reduce(all_n + un, mk, mv, &nk, &nv, &nn);
-    if (rc) return rc;
-    bufs.release(all_k); bufs.release(all_v); bufs.release(uk); bufs.release(uv); bufs.release(mk); bufs.release(mv);
-    all_k = nk; all_v = nv; all_n = nn;
+    const int64_t both = all_n + (int64_t)uniq;
+    if (both >= 0xffffffffLL) return fail(h, SPGEMM_UNSUPPORTED, "the all array of the outer product would exceed 2^32 - 1 components");
+    const int64_t mtiles = ceil_div(both, kMergeTile);
+    int64_t* split = bufs.get<int64_t>((size_t)mtiles + 1);
+    unsigned* msums = bufs.get<unsigned>((size_t)mtiles + 1);
+    if (!split || !msums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the merge stage failed");
+    hipLaunchKernelGGL(k_merge_split, dim3((unsigned)ceil_div(mtiles + 1, 256)), dim3(256), 0, s, all_n, all_k, (int64_t)uniq, batch.keys, mtiles, split);
+    hipLaunchKernelGGL(k_merge_count, dim3((unsigned)mtiles), dim3(256), 0, s, all_n, all_k, (int64_t)uniq, batch.keys, split, msums);
+    unsigned merged = 0;
+    if ((rc = total_of(mtiles, msums, &merged))) return rc;
+    OuterOut<T> next{};
+    if ((rc = room(merged, last, &next))) return rc;
+    hipLaunchKernelGGL(k_merge_put<T>, dim3((unsigned)mtiles), dim3(256), 0, s, all_n, all_k, all_v, (int64_t)uniq, batch.keys, batch.vals, split, msums, next);
+    HIP_TRY(h, hipGetLastError());
+    bufs.release(all_k); bufs.release(all_v); bufs.release(batch.keys); bufs.release(batch.vals); bufs.release(split); bufs.release(msums);
+    all_k = next.keys; all_v = next.vals; all_n = merged;
   }
-  // compress
-  int32_t* col = all_n ? bufs.get<int32_t>((size_t)all_n) : nullptr;
-  T* val = all_n ? bufs.get<T>((size_t)all_n) : nullptr;
-  if (all_n && (!col || !val)) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of C failed");
+  // compress: columns and values are there, the row pointer comes from the coordinates
   hipLaunchKernelGGL(k_key_ptr<unsigned long long>, dim3((unsigned)ceil_div(m + 1, kPtrRows)), dim3(256), 0, s, all_n, m, col_bits, all_k ? all_k : keys[0], rp);
-  if (all_n)
-    hipLaunchKernelGGL(k_outer_emit<T>, dim3(grid_for(all_n, 256, cap_grid)), dim3(256), 0, s, all_n, all_k, all_v, col_mask, col, val);
   HIP_TRY(h, hipGetLastError());
   HIP_TRY(h, hipStreamSynchronize(s));
   bufs.keep(rp); bufs.keep(col); bufs.keep(val);
@@ -1462,24 +1462,23 @@ int spgemm_dcsc_from_csr(spgemm_handle h, const spgemm_csr* M, spgemm_dcs* out) 
   DevBufs bufs(h);
   const int64_t nnz = M->nnz;
   const size_t vsz = M->dtype == SPGEMM_F32 ? 4 : 8;
-  // compressed sparse columns first: sort the entries by (column, row), stable
-  int32_t* rowid = bufs.get<int32_t>((size_t)nnz);
+  // compressed sparse columns first: a stable sort by column alone (the entries are in row order; a sort by the row's bits as well
+  // took five passes instead of three for 8 M entries of 10^6 columns)
   unsigned long long* keys[2] = {bufs.get<unsigned long long>((size_t)nnz), bufs.get<unsigned long long>((size_t)nnz)};
   void* tmp = bufs.get<unsigned char>((size_t)nnz * vsz);
   unsigned* counters = bufs.get<unsigned>(sort_counter_bytes(nnz) / 4);
   int64_t* colptr = bufs.get<int64_t>((size_t)M->cols + 1);
   int32_t* idx = bufs.get<int32_t>((size_t)nnz);
   void* val = bufs.get<unsigned char>((size_t)nnz * vsz);
-  if (!rowid || !keys[0] || !keys[1] || !tmp || !counters || !colptr || !idx || !val)
+  if (!keys[0] || !keys[1] || !tmp || !counters || !colptr || !idx || !val)
     return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the doubly compressed format failed");
   int cur = 0;
   const int64_t cap_grid = (int64_t)h->num_cus * 32;
   const int row_bits = bits_of(M->rows);
   if (nnz > 0) {
-    const SortShape sh = sort_shape(nnz, row_bits + bits_of(M->cols));
+    const SortShape sh = sort_shape(nnz, bits_of(M->cols), row_bits);
     const unsigned long long row_mask = (1ULL << row_bits) - 1;
-    hipLaunchKernelGGL(k_expand_rows, dim3(grid_for(M->rows, 4, cap_grid)), dim3(256), 0, s, M->rows, M->rowptr, rowid);
-    hipLaunchKernelGGL(k_pair_keys, dim3(grid_for(nnz, 256 * 4, cap_grid)), dim3(256), 0, s, nnz, row_bits, M->colidx, rowid, keys[0]);
+    hipLaunchKernelGGL(k_column_keys, dim3(grid_for(M->rows, 16, cap_grid)), dim3(256), 0, s, M->rows, row_bits, M->rowptr, M->colidx, keys[0]);
     if (M->dtype == SPGEMM_F32)
       cur = sort_pairs<unsigned long long, float>(h, nnz, sh, keys, static_cast<const float*>(M->values), static_cast<float*>(val),
                                                   static_cast<float*>(tmp), counters, false, idx, row_mask);

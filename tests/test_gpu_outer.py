@@ -85,3 +85,20 @@ def test_outer_route_config1_and_a_rectangular_case_with_several_batches():
     a, b = W.config3(scale=12)                    # power-law: long runs of equal coordinates in a batch
     _, _, C = run_outer(a, b, 1 << 18)
     check_against_oracles(a, b, C, "power law")
+
+
+@pytest.mark.parametrize("rows,n,per_a,per_b,capacity", [
+    (300, 40, 9, 7, 2048),        # tiles of the merge that end between equal coordinates, many batches
+    (300, 40, 9, 7, 2049),
+    (300, 40, 9, 7, 4096),        # a tile of runs exactly, and one more
+    (300, 40, 9, 7, 4097),
+    (2, 3, 60, 3, 97),            # six coordinates, long runs
+    (500, 70_000, 12, 40, 0),     # one batch of several ranges
+    (60, 50_000, 400, 30, 50_000),  # a thousand products per column
+])
+def test_outer_tiles(rows, n, per_a, per_b, capacity):
+    k = 3000 if rows > 400 else 700
+    A = W.uniform_rows(rows, k, per_a, 51, 1, np.float64)
+    B = W.uniform_rows(k, n, min(per_b, n), 51, 3, np.float64)
+    _, _, C = run_outer(A, B, capacity)
+    check_against_oracles(A, B, C, f"{rows} x {n}, capacity {capacity}")
