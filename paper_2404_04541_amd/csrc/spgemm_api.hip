@@ -278,10 +278,11 @@ bool wants_desc(const spgemm_csr* A, const spgemm_csr* B) {
 }
 
 // Rows of A that a workgroup of the row count takes at a time: fewer where there are too few rows to fill the card, more where
-// rows are short (a chunk of 256 rows of one or two entries leaves most of the 1024 threads idle and costs six barriers).
+// rows are short (a chunk of 256 rows of one or two entries leaves most of the 1024 threads idle and costs six barriers; graphs
+// with hub rows have longer rows on average and would wait for the chunk of the hubs: R-MAT scale 19 0.84 ms with 1024 rows).
 // 16384 rows of a power-law graph: 256 rows 57 us, 64 rows 27 us; 4.2 M rows of 2.4 entries: 256 rows 232 us, 1024 rows 128 us.
 int count_chunk(spgemm_context* h, int64_t m, int64_t nnz) {
-  if (m >= (int64_t)kCountMaxRows * 2 * h->num_cus && nnz <= 16 * m) return kCountMaxRows;
+  if (m >= (int64_t)kCountMaxRows * 2 * h->num_cus && nnz <= 8 * m) return kCountMaxRows;
   return m >= (int64_t)256 * 2 * h->num_cus ? 256 : 64;
 }
 

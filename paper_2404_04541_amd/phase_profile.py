@@ -15,7 +15,7 @@ import os
 import numpy as np
 
 SYM = {0: "row fetch", 1: "clear flag list", 2: "piece set-up (A entries, B row bounds, scans)", 3: "stream products (wave 0's share)",
-       4: "short pieces + wait for the slowest wave", 5: "entries per block / group", 6: "tile planning", 7: "allocation round trip",
+       4: "wait for the slowest wave", 5: "entries per block / group", 6: "tile planning", 7: "allocation round trip",
        8: "records, flag words out, column decode", 9: "tail"}
 NUM = {0: "run draw", 1: "run set-up (tile records, A entries)", 2: "wait for the previous tile + piece bounds",
        3: "ranked, columns: clear + piece list", 4: "ranked, columns: list -> flags, ranks, C.colidx", 5: "ranked: product pass",
