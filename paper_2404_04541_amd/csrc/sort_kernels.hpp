@@ -17,14 +17,10 @@
 // 27 -> 17 us; the gather of the values behind the last pass (211 us) is gone.  Unfolding as a whole 8.0 -> 0.8 ms.
 #pragma once
 #include "common.hpp"
+#include "sort_shape.hpp"
 
 namespace spg {
 
-constexpr int kSortThreads = 512;
-constexpr int kSortItems = 16;
-constexpr int kSortTile = kSortThreads * kSortItems;
-constexpr int kSortBins = 256;
-constexpr int kSortMaxRanges = 1024;
 constexpr int kSortWaves = kSortThreads / kWave;
 
 // Adds the digit counts of this workgroup's LDS histogram copies up and writes them for range r of nr.

@@ -879,28 +879,6 @@ int bits_of(int64_t n) {   // bits that hold 0 .. n-1
   return b;
 }
 
-// How a sort of n entries by nbits key bits is cut: passes over digits of `bits` bits, ranges of whole tiles.
-struct SortShape {
-  int passes, bits, ranges, first_bit;   // (bits below first_bit are not sorted by)
-  int64_t per_range;
-};
-
-SortShape sort_shape(int64_t n, int nbits, int first_bit = 0) {
-  SortShape sh{};
-  sh.first_bit = first_bit;
-  if (nbits < 1) nbits = 1;
-  sh.passes = (nbits + 7) / 8;
-  sh.bits = (nbits + sh.passes - 1) / sh.passes;
-  const int64_t tiles = ceil_div(n > 0 ? n : 1, kSortTile);
-  const int64_t tiles_per = ceil_div(tiles, kSortMaxRanges);
-  sh.ranges = (int)ceil_div(tiles, tiles_per);
-  sh.per_range = tiles_per * kSortTile;
-  return sh;
-}
-
-// Counters of a sort: one per digit value and range, and the digits' totals.
-size_t sort_counter_bytes(int64_t n) { return (size_t)(sort_shape(n, 8).ranges + 1) * kSortBins * 4; }
-
 // Stable radix sort of n (key, payload) pairs.  keys[0] holds the keys; the payloads start in pay_in and end in pay_a (pay_b is
 // the other buffer; pay_in may be the one of the two that the first pass does not write).  first_counted: the first digit's
 // counts are in `counters` already.  Returns which of the two key buffers holds the result.
@@ -1317,7 +1295,7 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
   const unsigned long long col_mask = (1ULL << col_bits) - 1;
   unsigned long long* keys[2] = {bufs.get<unsigned long long>((size_t)cap), bufs.get<unsigned long long>((size_t)cap)};
   double* vals[2] = {bufs.get<double>((size_t)cap), bufs.get<double>((size_t)cap)};
-  unsigned* counters = bufs.get<unsigned>(sort_counter_bytes(cap) / 4);
+  unsigned* counters = bufs.get<unsigned>(sort_counter_bytes(cap) / 4);   // (the last batch is shorter and may take more ranges)
   if (!keys[0] || !keys[1] || !vals[0] || !vals[1] || !counters) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the accumulation array failed");
   const int64_t cap_grid = (int64_t)h->num_cus * 32;
   // all array: sorted, unique coordinates with their sums

@@ -102,3 +102,15 @@ def test_outer_tiles(rows, n, per_a, per_b, capacity):
     B = W.uniform_rows(k, n, min(per_b, n), 51, 3, np.float64)
     _, _, C = run_outer(A, B, capacity)
     check_against_oracles(A, B, C, f"{rows} x {n}, capacity {capacity}")
+
+
+def test_a_last_batch_that_is_cut_into_more_ranges_than_a_full_one():
+    """A full batch of 1025 sort tiles goes in 513 ranges, the last one of 514 to 1024 tiles in a range per tile."""
+    tile = 8192
+    A = W.uniform_rows(2000, 2000, 64, 53, 1, np.float64)
+    B = W.uniform_rows(2000, 3000, 128, 53, 3, np.float64)
+    products = int(np.diff(B.rowptr)[A.colidx].sum())
+    last = products % (1025 * tile)
+    assert products // (1025 * tile) == 1 and 513 * tile < last <= 1024 * tile
+    _, _, C = run_outer(A, B, 1025 * tile)
+    check_against_oracles(A, B, C, "long last batch")
