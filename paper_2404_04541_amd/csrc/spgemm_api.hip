@@ -358,18 +358,18 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
 // The optional part of a plan, one allocation that the product does without when it fails: the column list of the dense rows
 // (at most a third of the free memory), and what the symbolic kernels of short rows leave for the numeric ones
 // (esc_kernels.hpp, record_kernels.hpp; at most a quarter): sorted words for all rows of a bin or for none, records for as
-// many rows as there is room for.
-void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, const Control& host, double list_want) {
+// many rows as there is room for.  staged: the numeric phase takes all rows this short through the staged list, which reads neither.
+void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, const Control& host, double list_want, bool staged) {
   if (!h->col_list) return;
   const int64_t max_cols[2] = {kEscPackCols0, kEscPackCols1};
   const size_t word_bytes[2] = {kEscSmallCap * 4, kEscLargeCap * 4};
   size_t words[2], want = 0;
   for (int b = 0; b < 2; ++b) {
-    words[b] = B->cols <= max_cols[b] ? align_up(host.hist[0][b] * word_bytes[b]) : 0;
+    words[b] = !staged && B->cols <= max_cols[b] ? align_up(host.hist[0][b] * word_bytes[b]) : 0;
     want += words[b];
   }
   const size_t rec_bytes = (size_t)kRecWords * 4, map = align_up((size_t)p->m * 4);
-  const size_t rec_rows = B->cols <= (int64_t(1) << kRecColBits) ? host.hist[0][2] : 0;
+  const size_t rec_rows = !staged && B->cols <= (int64_t(1) << kRecColBits) ? host.hist[0][2] : 0;
   if (rec_rows) want += map + rec_rows * rec_bytes;
   const size_t asked = h->col_list > 1 ? (size_t)h->col_list : ~(size_t)0;
   size_t limit = asked;
@@ -440,7 +440,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   double list_want = 0;
   int rc = alloc_dense_lists(h, p, B, host, &tile_cap, &run_cap, &list_want);
   if (rc) return rc;
-  alloc_optional(h, p, B, host, list_want);
+  alloc_optional(h, p, B, host, list_want, staged > 0);
   if (rows_dense > 0) {
     hipLaunchKernelGGL(k_set_caps, dim3(1), dim3(64), 0, s, p->ctl, tile_cap, run_cap, p->col_list_cap, rows_dense, grid_for(rows_dense, 1, h->num_cus));
     if (p->blk_ptr) {
@@ -532,7 +532,9 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   }
   {
     Timer t(h, SPGEMM_K_NUM_HASH);
-    if (p->recorded)   // (rows of the bin with a record, then the ones without)
+    // (rows of the bin with a record, then the ones without; a row that has a record is in this bin: it has more than
+    // kEscLargeCap products, or hashing is forced, and at most kNumHashSmall entries)
+    if (p->recorded)
       hipLaunchKernelGGL(k_num_recorded<T>, dim3(grid_for(hist[2], 4, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 2, p->ip, p->records, p->record_of,
                          A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val);
     if (hist[2] > p->recorded)

@@ -8,7 +8,7 @@ from paper_2404_04541_amd import workloads as W
 from helpers import gpu_product, assert_matches_oracle
 
 pytestmark = pytest.mark.gpu
-HASH, COLUMN_LIST = 2, 4
+HASH, STAGED, COLUMN_LIST = 2, 4, 4
 
 
 def csr(rows, cols, dtype, seed):
@@ -102,3 +102,25 @@ def test_short_rows(b_rows, cols, dtype, sort_b):
     A, B = short_operands(b_rows, cols, dtype, sort_b)
     for options in ({}, {COLUMN_LIST: 0}, {COLUMN_LIST: 20_000}):   # (words for both bins, for none, for one)
         assert_matches_oracle(A, B, gpu_product(A, B, options=options), what=f"rows={b_rows} cols={cols} {options}")
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("force", [0, 1, HASH, 3, STAGED])
+def test_rows_without_a_record_beside_rows_that_could_have_one(dtype, force):
+    """200 rows of 500 products, ten of 10 000 products on 100 columns: short of entries for the hash workspace, too many products
+    for a record and for the staged list."""
+    import torch
+    from paper_2404_04541_amd import binding as sg
+    rng = np.random.default_rng(41)
+    B = csr([np.sort(rng.choice(100, size=50, replace=False)) for _ in range(200)], 100, dtype, 42)
+    A = csr([rng.choice(200, size=10, replace=False) for _ in range(200)] + [np.arange(200) for _ in range(10)], 200, dtype, 43)
+    h = sg.Handle()
+    h.set_option(sg.OPT_FORCE_WORKSPACE, force)
+    dA, dB = sg.to_device(A), sg.to_device(B)
+    rp, nnz, plan = sg.spgemm_symbolic(h, dA, dB)
+    col = torch.full((nnz,), -1, dtype=torch.int32, device="cuda")
+    val = torch.full((nnz,), float("nan"), dtype=dA.values.dtype, device="cuda")
+    sg.spgemm_numeric(h, plan, dA, dB, rp, col, val)
+    torch.cuda.synchronize()
+    plan.destroy()
+    assert_matches_oracle(A, B, (rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy()), what=f"force {force}")
