@@ -141,8 +141,14 @@ def to_device(csr, device="cuda") -> DeviceCSR:
 
 
 class Plan:
-    def __init__(self, handle: "Handle", ptr: int, nnz_c: int):
-        self.handle, self.ptr, self.nnz_c = handle, ptr, nnz_c
+    def __init__(self, handle: "Handle", ptr: C.c_void_p, nnz_c: int):
+        self.handle, self._ptr, self.nnz_c = handle, ptr, nnz_c
+        handle._plans[ptr.value] = ptr
+
+    @property
+    def ptr(self) -> Optional[C.c_void_p]:
+        """None once the plan or its handle is gone."""
+        return self._ptr if self._ptr is not None and self._ptr.value in self.handle._plans else None
 
     def stats(self) -> dict:
         st = StatsStruct()
@@ -157,9 +163,9 @@ class Plan:
                 "plan_bytes": int(st.plan_bytes), "plan_list_bytes": int(st.plan_list_bytes), "plan_list_used": int(st.plan_list_used)}
 
     def destroy(self):
-        if self.ptr:
-            self.handle.lib.spgemm_plan_destroy(self.ptr)
-            self.ptr = None
+        ptr, self._ptr = self._ptr, None
+        if ptr is not None and self.handle._plans.pop(ptr.value, None) is not None:
+            self.handle.lib.spgemm_plan_destroy(ptr)
 
     def __del__(self):
         try:
@@ -169,25 +175,31 @@ class Plan:
 
 
 class Handle:
-    """spgemm_create / spgemm_destroy.  Device memory for scratch and results comes from torch."""
+    """spgemm_create / spgemm_destroy.  Device memory for scratch and results comes from torch.
+
+    The library's plans refer to their handle, so closing a handle destroys its plans first: the garbage collector may
+    finalise the two in either order.  The callbacks refer to the table of live buffers, not to the handle: a handle that
+    nobody refers to is gone at once, with the buffers it still holds."""
 
     def __init__(self, stream: Optional[torch.cuda.Stream] = None, torch_allocator: bool = True):
         self.lib = load_library()
+        self.ptr = None
         self.stream = stream
-        self._live = {}
+        self._live = live = {}
+        self._plans = {}
         self._alloc_struct = None
         if torch_allocator:
             def _alloc(_ctx, nbytes):
                 try:
-                    with torch.cuda.stream(self.stream) if self.stream is not None else _nullctx():
+                    with torch.cuda.stream(stream) if stream is not None else _nullctx():
                         t = torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device="cuda")
                 except Exception:
                     return None
-                self._live[t.data_ptr()] = t
+                live[t.data_ptr()] = t
                 return t.data_ptr()
 
             def _free(_ctx, ptr):
-                self._live.pop(ptr, None)
+                live.pop(ptr, None)
 
             self._cb = (ALLOC_FN(_alloc), FREE_FN(_free))
             self._alloc_struct = AllocatorStruct(self._cb[0], self._cb[1], None)
@@ -211,9 +223,11 @@ class Handle:
         return t[:nbytes].view(dtype)
 
     def close(self):
-        if self.ptr:
-            self.lib.spgemm_destroy(self.ptr)
-            self.ptr = None
+        ptr, self.ptr = self.ptr, None
+        if ptr:
+            while self._plans:
+                self.lib.spgemm_plan_destroy(self._plans.popitem()[1])
+            self.lib.spgemm_destroy(ptr)
 
     def __del__(self):
         try:
