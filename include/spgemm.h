@@ -167,7 +167,8 @@ int spgemm_symbolic(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B,
  *   c_colidx, c_values  device, nnz_c elements each, caller-owned, written
  *                       (may be null when nnz_c == 0).
  * Only enqueues work (no synchronisation).  A plan may be
- * reused for further numeric calls with new values on the same structures.
+ * reused for further numeric calls with new values on the same structures; the entries of a row may then come in
+ * another order than before (of an ascending B's row only where no row of the product is dense).
  * Sums are accumulated in double for both value types and rounded once on output (one exception: the
  * staged coordinate list, taken on request only, stages each float product rounded to float).
  * The plan's scratch is read by the enqueued kernels: spgemm_plan_destroy waits for the stream when a

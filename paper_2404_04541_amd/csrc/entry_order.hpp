@@ -1,0 +1,74 @@
+// The order of the operands' entries.  What short rows leave in the plan (sorted words, records, descriptions) goes by the position
+// of an entry in its row, but a plan holds for operands of the same structure whatever the order of a row's entries.  So the
+// columns of both operands are summed with a weight per position (the weights of any two positions differ), once for a plan that
+// its caller holds and again in every numeric phase on it; where the sum is another one, the kernels that go by the plan's order
+// end at once and k_other_order does their rows without it.
+// Bound: memory, one pass over the columns (of one operand where both are the same array), and the launches.  Numeric phase on a
+// kept plan, 27-point stencil (fp64): 61^3 rows 256 -> 268 us, 128^3 rows 2.19 -> 2.24 ms; in another order 475 us and 4.36 ms
+// (without any plan of the order, 546 us and 4.79 ms).  Summed by extra workgroups of the rows' kernel instead, the code made for
+// its rows was 10 % slower even where nothing was summed.
+#pragma once
+#include "common.hpp"
+
+namespace spg {
+
+__device__ __forceinline__ unsigned order_weight(int64_t p) {   // a bijection of 32 bits
+  unsigned x = (unsigned)p ^ ((unsigned)((unsigned long long)p >> 32) * 0x51ED2705u);
+  x = (x ^ (x >> 16)) * 0x9E3779B1u;
+  return (x ^ (x >> 15)) * 0x85157AF5u;
+}
+
+constexpr int kOrderThreads = 1024;
+constexpr int kOrderQuads = 4;   // loads in flight per thread
+constexpr int kOrderTile = kOrderThreads * kOrderQuads * 4;
+
+__device__ __forceinline__ unsigned long long order_sum_of(int64_t n, const int32_t* __restrict__ col) {
+  unsigned long long s = 0;
+  for (int64_t t0 = (int64_t)blockIdx.x * kOrderTile; t0 < n; t0 += (int64_t)gridDim.x * kOrderTile) {
+    Run<int32_t, 4> c[kOrderQuads];
+    const int64_t p = t0 + threadIdx.x * 4;
+    if (t0 + kOrderTile <= n) {
+#pragma unroll
+      for (int u = 0; u < kOrderQuads; ++u) c[u] = load_run<int32_t, 4>(col + p + u * kOrderThreads * 4);
+    } else {
+#pragma unroll
+      for (int u = 0; u < kOrderQuads; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int64_t q = p + u * kOrderThreads * 4 + i;
+          c[u].v[i] = q < n ? col[q] : 0;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kOrderQuads; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s += (unsigned long long)order_weight(p + u * kOrderThreads * 4 + i) * (unsigned)c[u].v[i];
+  }
+  return s;
+}
+
+// One word for both operands (b_col null: B's columns are A's): their sums' low 56 bits above the number of workgroups that have
+// added theirs, so that a workgroup sends one atomic and the last one knows the whole (three atomics each, to sums and a counter:
+// 11 us for 6 M entries, and 15 us with twice the workgroups; now 8 us).  plan: the word is the plan's, otherwise it is compared with it.
+constexpr int kOrderParts = 128;   // at most
+static_assert(kOrderParts < 256, "the count has eight bits");
+__global__ __launch_bounds__(kOrderThreads) void k_order_sum(int64_t na, const int32_t* __restrict__ a_col, int64_t nb, const int32_t* __restrict__ b_col,
+                                                             Control* ctl, int plan) {
+  __shared__ unsigned long long part[kOrderThreads / kWave];
+  const unsigned long long a = order_sum_of(na, a_col), b = b_col ? order_sum_of(nb, b_col) : a;
+  unsigned long long s = a + b * 0x9E3779B97F4A7C15ULL;
+  for (int d = kWave / 2; d > 0; d >>= 1) s += __shfl_xor(s, d, kWave);
+  if (lane_id() == 0) part[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kOrderThreads / kWave; ++w) s += part[w];
+    const unsigned long long mine = (s << 8) + 1, before = atomicAdd(&ctl->order_now, mine);
+    if ((before & 255) == gridDim.x - 1) {
+      ctl->order_now = 0;   // (for the next time)
+      if (plan) ctl->order = before + mine;
+      else ctl->order_differs = before + mine != ctl->order ? 1 : 0;
+    }
+  }
+}
+
+}  // namespace spg

@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256, GROUP == kWave ? 6 : 5) void k_esc_num(const i
   __shared__ unsigned s_cols[kGroups][CAP];
   __shared__ EscLds<GROUP, CAP> s_lds[kGroups];
   __shared__ double s_av[kGroups][GROUP];
-  if (ctl->error) return;
+  if (ctl->error || ctl->order_differs) return;
   const unsigned first = ctl->offset[0][bin];   // (the bins of rows this short are the same in both phases)
   const unsigned nrows = ctl->offset[0][bin + 1] - first;
   const int g = group_number<GROUP>(), gl = threadIdx.x % GROUP;
@@ -254,16 +254,22 @@ __device__ __forceinline__ int count_before(const int* keys, int nscan, unsigned
   return r;
 }
 
-// GROUP lanes per row (16 or 64), list capacity CAP = 2 * GROUP products.
+// GROUP lanes per row (16 or 64), list capacity CAP = 2 * GROUP products; workgroup wg of wgs.
 // Writes the merged (column, value) run at c_rp[row]; pack != 0: every column shifted left by
 // log2(CAP) stays below the padding key, so a key can carry its list position.
 template <int GROUP, int CAP, typename T>
-__global__ __launch_bounds__(256) void k_esc(const int* __restrict__ perm, const Control* __restrict__ ctl, int phase, int bin,
-                                              const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
-                                              const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
-                                              const int32_t* __restrict__ b_col, const T* __restrict__ b_val,
-                                              const int64_t* __restrict__ c_rp,
-                                              int32_t* __restrict__ c_col, T* __restrict__ c_val, int pack, int64_t b_nnz) {
+struct EscRowsLds {
+  __align__(16) int keys[256 / GROUP][CAP];
+  double vals[256 / GROUP][CAP];
+};
+
+template <int GROUP, int CAP, typename T>
+__device__ __forceinline__ void esc_rows(EscRowsLds<GROUP, CAP, T>* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, const Control* __restrict__ ctl,
+                                         int phase, int bin, const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
+                                         const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
+                                         const int32_t* __restrict__ b_col, const T* __restrict__ b_val,
+                                         const int64_t* __restrict__ c_rp,
+                                         int32_t* __restrict__ c_col, T* __restrict__ c_val, int pack, int64_t b_nnz) {
   static_assert(CAP == 2 * GROUP, "each lane owns two list positions");
   constexpr int kGroups = 256 / GROUP;
   constexpr int kLogCap = CAP == 32 ? 5 : 7;
@@ -271,21 +277,18 @@ __global__ __launch_bounds__(256) void k_esc(const int* __restrict__ perm, const
   const int shift = pack ? kLogCap : 0;   // a numeric key: (column << shift) | position
   const int pmask = pack ? CAP - 1 : 0;
   constexpr int kSpreadMax = 16;   // A entries up to which a wave deals a row's products, not its entries, to its lanes
-  __shared__ __align__(16) int s_keys[kGroups][CAP];
-  __shared__ double s_vals[kGroups][CAP];
-  if (ctl->error) return;
   const unsigned first = ctl->offset[phase][bin];
   const unsigned nrows = ctl->offset[phase][bin + 1] - first;
   const int g = threadIdx.x / GROUP;   // group inside the workgroup
   const int gl = threadIdx.x % GROUP;  // lane inside the group
-  int* keys = s_keys[g];
-  double* vals = s_vals[g];
-  const unsigned ngroups = gridDim.x * kGroups;
+  int* keys = lds->keys[g];
+  double* vals = lds->vals[g];
+  const unsigned ngroups = wgs * kGroups;
   // every wave iterates the same number of times so that the shuffles below always see
   // all 64 lanes; groups past the end of the bin run on an empty row
   const unsigned rounds = (nrows + ngroups - 1) / ngroups;
   for (unsigned r = 0; r < rounds; ++r) {
-    const unsigned slot = r * ngroups + blockIdx.x * kGroups + g;
+    const unsigned slot = r * ngroups + wg * kGroups + g;
     const bool live = slot < nrows;
     const int row = live ? perm[first + slot] : 0;
     const int64_t a0 = live ? a_rp[row] : 0;
@@ -426,6 +429,18 @@ __global__ __launch_bounds__(256) void k_esc(const int* __restrict__ perm, const
     }
     group_sync<GROUP>();
   }
+}
+
+template <int GROUP, int CAP, typename T>
+__global__ __launch_bounds__(256) void k_esc(const int* __restrict__ perm, const Control* __restrict__ ctl, int phase, int bin,
+                                              const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
+                                              const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
+                                              const int32_t* __restrict__ b_col, const T* __restrict__ b_val,
+                                              const int64_t* __restrict__ c_rp,
+                                              int32_t* __restrict__ c_col, T* __restrict__ c_val, int pack, int64_t b_nnz) {
+  __shared__ EscRowsLds<GROUP, CAP, T> lds;
+  if (ctl->error) return;
+  esc_rows<GROUP, CAP, T>(&lds, blockIdx.x, gridDim.x, perm, ctl, phase, bin, a_rp, a_col, a_val, b_rp, b_col, b_val, c_rp, c_col, c_val, pack, b_nnz);
 }
 
 }  // namespace spg

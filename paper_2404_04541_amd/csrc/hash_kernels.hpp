@@ -7,6 +7,7 @@
 //           sorted by column (hash retrieval), and that prefix is copied to the row of C.
 #pragma once
 #include "common.hpp"
+#include "esc_kernels.hpp"
 #include "record_kernels.hpp"
 
 namespace spg {
@@ -91,9 +92,9 @@ __device__ __forceinline__ void sort_shares(int* keys, int n) {
   group_sync<GROUP>();
 }
 
-// GROUP threads per row (64: one wave, several rows per workgroup; 256: the workgroup).
+// GROUP threads per row (64: one wave, several rows per workgroup; 256: the workgroup); workgroup wg of wgs.
 template <int GROUP, int LOGH, typename T, bool NUMERIC>
-__global__ __launch_bounds__(256, GROUP > kWave ? 5 : 8) void k_hash(const int* __restrict__ perm, const Control* __restrict__ ctl, int phase, int bin,
+__device__ __forceinline__ void hash_rows(unsigned char* smem, unsigned wg, unsigned wgs, const int* __restrict__ perm, const Control* __restrict__ ctl, int phase, int bin,
                                                const int* __restrict__ ip_row,
                                                const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
@@ -104,7 +105,6 @@ __global__ __launch_bounds__(256, GROUP > kWave ? 5 : 8) void k_hash(const int* 
   constexpr int H = 1 << LOGH;
   const bool packable = n_cols <= (int64_t(1) << (31 - LOGH));   // column << LOGH stays below the pad key
   constexpr int kGroups = 256 / GROUP;
-  extern __shared__ __align__(16) unsigned char smem[];
   // layout: per group H keys, then (numeric) H doubles; one int counter per group at the end
   double* all_vals = reinterpret_cast<double*>(smem);
   int* all_keys = reinterpret_cast<int*>(smem + (NUMERIC ? (size_t)kGroups * H * sizeof(double) : 0));
@@ -116,7 +116,6 @@ __global__ __launch_bounds__(256, GROUP > kWave ? 5 : 8) void k_hash(const int* 
   HashEntry* all_ent = reinterpret_cast<HashEntry*>(extra);
   double* all_pav = reinterpret_cast<double*>(all_ent + kGroups * GROUP);
   int* part = reinterpret_cast<int*>(all_pav + kGroups * GROUP);
-  if (ctl->error) return;
   const unsigned first = ctl->offset[phase][bin];
   const unsigned nrows = ctl->offset[phase][bin + 1] - first;
   const int g = threadIdx.x / GROUP;
@@ -125,10 +124,10 @@ __global__ __launch_bounds__(256, GROUP > kWave ? 5 : 8) void k_hash(const int* 
   double* vals = NUMERIC ? all_vals + g * H : nullptr;
   HashEntry* ent = all_ent + g * GROUP;
   double* pav = all_pav + g * GROUP;
-  const unsigned ngroups = gridDim.x * kGroups;
+  const unsigned ngroups = wgs * kGroups;
   const unsigned rounds = (nrows + ngroups - 1) / ngroups;
   for (unsigned r = 0; r < rounds; ++r) {
-    const unsigned slot = r * ngroups + blockIdx.x * kGroups + g;
+    const unsigned slot = r * ngroups + wg * kGroups + g;
     const bool live = slot < nrows;
     const int row = live ? perm[first + slot] : 0;
     // (wave-uniform) rows whose ranks the symbolic pass has recorded are done elsewhere
@@ -267,10 +266,57 @@ __global__ __launch_bounds__(256, GROUP > kWave ? 5 : 8) void k_hash(const int* 
   }
 }
 
+template <int GROUP, int LOGH, typename T, bool NUMERIC>
+__global__ __launch_bounds__(256, GROUP > kWave ? 5 : 8) void k_hash(const int* __restrict__ perm, const Control* __restrict__ ctl, int phase, int bin,
+                                               const int* __restrict__ ip_row,
+                                               const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
+                                               const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
+                                               const int32_t* __restrict__ b_col, const T* __restrict__ b_val,
+                                               int* __restrict__ cnt, const int64_t* __restrict__ c_rp,
+                                               int32_t* __restrict__ c_col, T* __restrict__ c_val, int64_t n_cols,
+                                               const int* __restrict__ record_of) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  if (ctl->error) return;
+  hash_rows<GROUP, LOGH, T, NUMERIC>(smem, blockIdx.x, gridDim.x, perm, ctl, phase, bin, ip_row, a_rp, a_col, a_val, b_rp, b_col, b_val, cnt, c_rp, c_col, c_val,
+                                     n_cols, record_of);
+}
+
 template <int GROUP, int LOGH, bool NUMERIC>
 constexpr size_t hash_lds_bytes() {
   return (size_t)(256 / GROUP) * (1u << LOGH) * (sizeof(int) + (NUMERIC ? sizeof(double) : 0)) + (256 / GROUP) * sizeof(int) + 8 +
          16 + (size_t)256 * (sizeof(HashEntry) + 8) + (size_t)(256 / GROUP) * (GROUP / kWave + 1) * 4;
+}
+
+// The rows whose order the plan holds (numeric bins 0, 1 and 2: wgs0, wgs1, wgs2 workgroups), again and without it, when the
+// operands' entries come in another order; ends at once otherwise.
+template <typename T>
+__global__ __launch_bounds__(256) void k_other_order(unsigned wgs0, unsigned wgs1, unsigned wgs2, const int* __restrict__ perm, const Control* __restrict__ ctl,
+                                                     const int* __restrict__ ip_row, const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
+                                                     const T* __restrict__ a_val, const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col,
+                                                     const T* __restrict__ b_val, const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col,
+                                                     T* __restrict__ c_val, int pack0, int pack1, int64_t b_nnz, int64_t n_cols) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  if (ctl->error || !ctl->order_differs) return;
+  unsigned wg = blockIdx.x;
+  if (wg < wgs0) {
+    esc_rows<16, 32, T>(reinterpret_cast<EscRowsLds<16, 32, T>*>(smem), wg, wgs0, perm, ctl, 1, 0, a_rp, a_col, a_val, b_rp, b_col, b_val, c_rp, c_col, c_val, pack0, b_nnz);
+    return;
+  }
+  wg -= wgs0;
+  if (wg < wgs1) {
+    esc_rows<64, 128, T>(reinterpret_cast<EscRowsLds<64, 128, T>*>(smem), wg, wgs1, perm, ctl, 1, 1, a_rp, a_col, a_val, b_rp, b_col, b_val, c_rp, c_col, c_val, pack1, b_nnz);
+    return;
+  }
+  wg -= wgs1;
+  hash_rows<64, 8, T, true>(smem, wg, wgs2, perm, ctl, 1, 2, ip_row, a_rp, a_col, a_val, b_rp, b_col, b_val, (int*)nullptr, c_rp, c_col, c_val, n_cols, (const int*)nullptr);
+}
+
+template <typename T>
+constexpr size_t other_order_lds_bytes() {
+  size_t n = hash_lds_bytes<64, 8, true>();
+  if (n < sizeof(EscRowsLds<16, 32, T>)) n = sizeof(EscRowsLds<16, 32, T>);
+  if (n < sizeof(EscRowsLds<64, 128, T>)) n = sizeof(EscRowsLds<64, 128, T>);
+  return n;
 }
 
 }  // namespace spg

@@ -234,7 +234,7 @@ __global__ __launch_bounds__(256) void k_num_recorded(const int* __restrict__ pe
   __shared__ double s_acc[4][256];   // (a rank is a byte)
   __shared__ QuadEntry s_ent[4][kQuadEntries];
   __shared__ T s_av[4][kQuadEntries];
-  if (ctl->error) return;
+  if (ctl->error || ctl->order_differs) return;
   const unsigned first = ctl->offset[1][bin];
   const unsigned nrows = ctl->offset[1][bin + 1] - first;
   const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();

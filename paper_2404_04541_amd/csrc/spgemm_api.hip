@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "entry_order.hpp"
 #include "setup_kernels.hpp"
 #include "esc_kernels.hpp"
 #include "record_kernels.hpp"
@@ -123,6 +124,7 @@ struct spgemm_plan_s {
   Control* ctl = nullptr;
   int64_t scan_blocks = 0;
   int64_t recorded = 0;          // rows that have a record
+  bool order_kept = false;       // the checksums of the order of the entries were taken
   bool symbolic_done = false;
   bool numeric_pending = false;   // timed numeric launches not yet folded into stats
   bool numeric_in_flight = false; // numeric kernels were enqueued and the stream has not been waited for since
@@ -422,9 +424,18 @@ __global__ void k_set_caps(Control* ctl, unsigned tile_cap, unsigned run_cap, un
   }
 }
 
+// The order of the operands' entries: kept with the plan (plan = 1), or compared with it.
+void sum_order(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const spgemm_csr* B, int plan) {
+  const int64_t most = A->nnz > B->nnz ? A->nnz : B->nnz;
+  const bool one = A->colidx == B->colidx && A->nnz == B->nnz;
+  hipLaunchKernelGGL(k_order_sum, dim3(grid_for(most, kOrderTile, kOrderParts)), dim3(kOrderThreads), 0, h->stream, A->nnz, A->colidx, B->nnz,
+                     one ? (const int32_t*)nullptr : B->colidx, p->ctl, plan);
+}
+
+// plan_leaves: the plan goes to the caller, whose numeric phases may bring the entries in another order.
 template <typename T>
 int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const spgemm_csr* B, int64_t* c_rowptr,
-                 const Control& host, Control* pinned) {
+                 const Control& host, Control* pinned, bool plan_leaves) {
   hipStream_t s = h->stream;
   const int64_t m = p->m;
   const int64_t cap_small = (int64_t)h->num_cus * 32;
@@ -441,6 +452,11 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   int rc = alloc_dense_lists(h, p, B, host, &tile_cap, &run_cap, &list_want);
   if (rc) return rc;
   alloc_optional(h, p, B, host, list_want, staged > 0);
+  p->order_kept = plan_leaves && (p->records || p->esc_words[0] || p->esc_words[1]);
+  if (p->order_kept) {
+    Timer t(h, SPGEMM_K_COUNT);
+    sum_order(h, p, A, B, 1);
+  }
   if (rows_dense > 0) {
     hipLaunchKernelGGL(k_set_caps, dim3(1), dim3(64), 0, s, p->ctl, tile_cap, run_cap, p->col_list_cap, rows_dense, grid_for(rows_dense, 1, h->num_cus));
     if (p->blk_ptr) {
@@ -514,18 +530,24 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   const size_t lds_hash_large = hash_lds_bytes<256, 11, true>();
   const int64_t* hist = p->stats.num_bin_rows;
   if (hist[4] + hist[5] + hist[6] > 0) hipLaunchKernelGGL(k_reset_numeric_work, dim3(1), dim3(64), 0, s, p->ctl);
+  // (the words were sorted for the rows of the symbolic bin: they serve when the numeric one holds the same rows)
+  const bool words0 = hist[0] && p->esc_words[0] && hist[0] == p->stats.sym_bin_rows[0];
+  const bool words1 = hist[1] && p->esc_words[1] && hist[1] == p->stats.sym_bin_rows[1];
+  // On a plan that the caller holds: are the entries in the order of the plan?  If not, the kernels that need it end at once, and
+  // k_other_order behind them, which ends at once otherwise (4 us), does their rows.
+  const bool check = p->order_kept && (words0 || words1 || p->recorded);
   {
     Timer t(h, SPGEMM_K_NUM_ESC);
-    // (the words were sorted for the rows of the symbolic bin: they serve when the numeric one holds the same rows)
-    if (hist[0] && p->esc_words[0] && hist[0] == p->stats.sym_bin_rows[0])
-      hipLaunchKernelGGL((p->desc ? k_esc_num<16, 32, T, true> : k_esc_num<16, 32, T, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0, A->rowptr, A->colidx,
-                         a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[0], c_rp, c_col, c_val);
+    if (check) sum_order(h, p, A, B, 0);
+    if (words0)
+      hipLaunchKernelGGL((p->desc ? k_esc_num<16, 32, T, true> : k_esc_num<16, 32, T, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0,
+                         A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[0], c_rp, c_col, c_val);
     else if (hist[0])
       hipLaunchKernelGGL((k_esc<16, 32, T>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 0,
                          A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, B->nnz);
-    if (hist[1] && p->esc_words[1] && hist[1] == p->stats.sym_bin_rows[1])
-      hipLaunchKernelGGL((p->desc ? k_esc_num<64, 128, T, true> : k_esc_num<64, 128, T, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx,
-                         a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[1], c_rp, c_col, c_val);
+    if (words1)
+      hipLaunchKernelGGL((p->desc ? k_esc_num<64, 128, T, true> : k_esc_num<64, 128, T, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1,
+                         A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[1], c_rp, c_col, c_val);
     else if (hist[1])
       hipLaunchKernelGGL((k_esc<64, 128, T>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 1,
                          A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack128, B->nnz);
@@ -541,6 +563,11 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
       hipLaunchKernelGGL((k_hash<64, 8, T, true>), dim3(grid_for(hist[2], 4, cap_small)), dim3(256), lds_hash_small, s,
                          p->perm_num, p->ctl, 1, 2, p->ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, (int*)nullptr,
                          c_rp, c_col, c_val, B->cols, p->recorded ? p->record_of : nullptr);
+    if (check) {
+      const unsigned w0 = words0 ? grid_for(hist[0], 16, cap_small) : 0, w1 = words1 ? grid_for(hist[1], 4, cap_small) : 0, w2 = p->recorded ? grid_for(hist[2], 4, cap_small) : 0;
+      hipLaunchKernelGGL(k_other_order<T>, dim3(w0 + w1 + w2), dim3(256), other_order_lds_bytes<T>(), s, w0, w1, w2, p->perm_num, p->ctl, p->ip, A->rowptr,
+                         A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, pack128, B->nnz, B->cols);
+    }
     if (hist[3])
       hipLaunchKernelGGL((k_hash<256, 11, T, true>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
                          lds_hash_large, s, p->perm_num, p->ctl, 1, 3, p->ip, A->rowptr, A->colidx, a_val, B->rowptr,
@@ -559,6 +586,101 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
                        p->blk_ptr_cols, p->col_list, B->nnz, c_rp, c_col, c_val);
   }
   HIP_TRY(h, hipGetLastError());
+  return SPGEMM_OK;
+}
+
+// plan_leaves: see run_symbolic.
+int symbolic(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B, int64_t* c_rowptr, int64_t* nnz_c, spgemm_plan* plan, bool plan_leaves) {
+  if (!h) return SPGEMM_INVALID_ARG;
+  int rc = check_pair(h, A, B);
+  if (rc) return rc;
+  if (!c_rowptr || !nnz_c || !plan) return fail(h, SPGEMM_INVALID_ARG, "c_rowptr, nnz_c and plan must not be null");
+  *plan = nullptr;
+  if ((rc = ensure_device(h))) return rc;
+  drop_timed(h);   // (timed launches of an earlier plan that nobody asked about)
+  PinnedLease pinned;
+  if (!pinned.p) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of pinned host memory failed");
+
+  spgemm_plan_s* p = new (std::nothrow) spgemm_plan_s();
+  if (!p) return fail(h, SPGEMM_ALLOC_FAILED, "host allocation failed");
+  p->h = h;
+  p->m = A->rows; p->k = A->cols; p->n = B->cols; p->nnz_a = A->nnz; p->nnz_b = B->nnz; p->dtype = A->dtype;
+  const int64_t m = p->m;
+  p->scan_blocks = m > 0 ? ceil_div(m, kScanTile) : 0;
+  size_t off = 0;
+  const size_t o_ctl = off; off = align_up(off + sizeof(Control));
+  const size_t o_ip = off; off = align_up(off + (size_t)m * 4);
+  const size_t o_cnt = off; off = align_up(off + (size_t)m * 4);
+  const size_t o_ps = off; off = align_up(off + (size_t)m * 4);
+  const size_t o_pn = off; off = align_up(off + (size_t)m * 4);
+  const size_t o_bin = off; off = align_up(off + (size_t)m);
+  const size_t o_part = off; off = align_up(off + (size_t)(p->scan_blocks + 1) * 8);
+  const size_t plain = off, o_desc = off;
+  if (wants_desc(A, B)) off = align_up(off + (size_t)A->nnz * 8);
+  p->scratch = dev_alloc(h, off);
+  if (!p->scratch && off > plain) { off = plain; p->scratch = dev_alloc(h, off); }
+  p->scratch_bytes = off;
+  if (!p->scratch) {
+    delete p;
+    return fail(h, SPGEMM_ALLOC_FAILED, "device allocation of plan scratch failed");
+  }
+  unsigned char* base = static_cast<unsigned char*>(p->scratch);
+  p->ctl = reinterpret_cast<Control*>(base + o_ctl);
+  p->ip = reinterpret_cast<int*>(base + o_ip);
+  p->cnt = reinterpret_cast<int*>(base + o_cnt);
+  p->perm_sym = reinterpret_cast<int*>(base + o_ps);
+  p->perm_num = reinterpret_cast<int*>(base + o_pn);
+  p->bin = base + o_bin;
+  p->partial = reinterpret_cast<long long*>(base + o_part);
+  if (off > plain) p->desc = reinterpret_cast<unsigned long long*>(base + o_desc);
+
+  Control host{};
+  rc = run_setup(h, p, A, B, pinned.p, &host);
+  if (rc == SPGEMM_OK && !host.error)
+    rc = (A->dtype == SPGEMM_F32) ? run_symbolic<float>(h, p, A, B, c_rowptr, host, pinned.p, plan_leaves)
+                                 : run_symbolic<double>(h, p, A, B, c_rowptr, host, pinned.p, plan_leaves);
+  if (rc == SPGEMM_OK && !host.error) {
+    const hipError_t e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) rc = fail(h, SPGEMM_HIP_ERROR, std::string("symbolic phase: ") + hipGetErrorString(e));
+    else std::memcpy(&host, pinned.p, sizeof(Control));
+  }
+  if (rc != SPGEMM_OK) {
+    (void)hipStreamSynchronize(h->stream);
+    drop_timed(h);
+    spgemm_plan_destroy(p);
+    return rc;
+  }
+  std::memset(&p->stats, 0, sizeof(p->stats));
+  collect_times(h, &p->stats);
+  if (host.error == 2 || host.error == 3) {
+    spgemm_plan_destroy(p);
+    return host.error == 2 ? fail(h, SPGEMM_UNSUPPORTED, "unsorted B with a row of 2^21 or more entries")
+                           : fail(h, SPGEMM_HIP_ERROR, "internal: tile list overflow in the dense symbolic kernel");
+  }
+  if (host.error) {
+    spgemm_plan_destroy(p);
+    return fail(h, SPGEMM_INVALID_INPUT, "device-side input check failed (column out of range or rowptr not monotone)");
+  }
+  p->recorded = host.recorded;
+  p->stats.ip_total = (int64_t)host.ip_total;
+  p->stats.nnz_c = host.nnz_c;
+  for (int b = 0; b < kNumBins; ++b) {
+    p->stats.sym_bin_rows[b] = host.hist[0][b];
+    p->stats.num_bin_rows[b] = host.hist[1][b];
+    p->stats.sym_bin_ip[b] = (int64_t)host.bin_ip[0][b];
+    p->stats.num_bin_ip[b] = (int64_t)host.bin_ip[1][b];
+    p->stats.num_bin_nnz[b] = (int64_t)host.bin_nnz[b];
+  }
+  p->stats.dense_tiles = host.tiles_used;
+  p->stats.dense_direct_tiles = host.direct_tiles;
+  p->stats.dense_runs = host.runs_used;
+  p->stats.dense_search_tiles = host.search_tiles;
+  p->stats.plan_bytes = (int64_t)(p->scratch_bytes + p->scratch2_bytes + p->short_bytes + p->list_bytes);
+  p->stats.plan_list_bytes = (int64_t)p->list_bytes;
+  p->stats.plan_list_used = (int64_t)((host.list_cursor < host.list_cap ? host.list_cursor : host.list_cap) * 4ULL);
+  p->symbolic_done = true;
+  *nnz_c = host.nnz_c;
+  *plan = p;
   return SPGEMM_OK;
 }
 
@@ -653,96 +775,7 @@ int spgemm_get_stats(spgemm_plan p, spgemm_stats* out) {
 
 int spgemm_symbolic(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, int64_t* c_rowptr, int64_t* nnz_c,
                     spgemm_plan* plan) {
-  if (!h) return SPGEMM_INVALID_ARG;
-  int rc = check_pair(h, A, B);
-  if (rc) return rc;
-  if (!c_rowptr || !nnz_c || !plan) return fail(h, SPGEMM_INVALID_ARG, "c_rowptr, nnz_c and plan must not be null");
-  *plan = nullptr;
-  if ((rc = ensure_device(h))) return rc;
-  drop_timed(h);   // (timed launches of an earlier plan that nobody asked about)
-  PinnedLease pinned;
-  if (!pinned.p) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of pinned host memory failed");
-
-  spgemm_plan_s* p = new (std::nothrow) spgemm_plan_s();
-  if (!p) return fail(h, SPGEMM_ALLOC_FAILED, "host allocation failed");
-  p->h = h;
-  p->m = A->rows; p->k = A->cols; p->n = B->cols; p->nnz_a = A->nnz; p->nnz_b = B->nnz; p->dtype = A->dtype;
-  const int64_t m = p->m;
-  p->scan_blocks = m > 0 ? ceil_div(m, kScanTile) : 0;
-  size_t off = 0;
-  const size_t o_ctl = off; off = align_up(off + sizeof(Control));
-  const size_t o_ip = off; off = align_up(off + (size_t)m * 4);
-  const size_t o_cnt = off; off = align_up(off + (size_t)m * 4);
-  const size_t o_ps = off; off = align_up(off + (size_t)m * 4);
-  const size_t o_pn = off; off = align_up(off + (size_t)m * 4);
-  const size_t o_bin = off; off = align_up(off + (size_t)m);
-  const size_t o_part = off; off = align_up(off + (size_t)(p->scan_blocks + 1) * 8);
-  const size_t plain = off, o_desc = off;
-  if (wants_desc(A, B)) off = align_up(off + (size_t)A->nnz * 8);
-  p->scratch = dev_alloc(h, off);
-  if (!p->scratch && off > plain) { off = plain; p->scratch = dev_alloc(h, off); }
-  p->scratch_bytes = off;
-  if (!p->scratch) {
-    delete p;
-    return fail(h, SPGEMM_ALLOC_FAILED, "device allocation of plan scratch failed");
-  }
-  unsigned char* base = static_cast<unsigned char*>(p->scratch);
-  p->ctl = reinterpret_cast<Control*>(base + o_ctl);
-  p->ip = reinterpret_cast<int*>(base + o_ip);
-  p->cnt = reinterpret_cast<int*>(base + o_cnt);
-  p->perm_sym = reinterpret_cast<int*>(base + o_ps);
-  p->perm_num = reinterpret_cast<int*>(base + o_pn);
-  p->bin = base + o_bin;
-  p->partial = reinterpret_cast<long long*>(base + o_part);
-  if (off > plain) p->desc = reinterpret_cast<unsigned long long*>(base + o_desc);
-
-  Control host{};
-  rc = run_setup(h, p, A, B, pinned.p, &host);
-  if (rc == SPGEMM_OK && !host.error)
-    rc = (A->dtype == SPGEMM_F32) ? run_symbolic<float>(h, p, A, B, c_rowptr, host, pinned.p) : run_symbolic<double>(h, p, A, B, c_rowptr, host, pinned.p);
-  if (rc == SPGEMM_OK && !host.error) {
-    const hipError_t e = hipStreamSynchronize(h->stream);
-    if (e != hipSuccess) rc = fail(h, SPGEMM_HIP_ERROR, std::string("symbolic phase: ") + hipGetErrorString(e));
-    else std::memcpy(&host, pinned.p, sizeof(Control));
-  }
-  if (rc != SPGEMM_OK) {
-    (void)hipStreamSynchronize(h->stream);
-    drop_timed(h);
-    spgemm_plan_destroy(p);
-    return rc;
-  }
-  std::memset(&p->stats, 0, sizeof(p->stats));
-  collect_times(h, &p->stats);
-  if (host.error == 2 || host.error == 3) {
-    spgemm_plan_destroy(p);
-    return host.error == 2 ? fail(h, SPGEMM_UNSUPPORTED, "unsorted B with a row of 2^21 or more entries")
-                           : fail(h, SPGEMM_HIP_ERROR, "internal: tile list overflow in the dense symbolic kernel");
-  }
-  if (host.error) {
-    spgemm_plan_destroy(p);
-    return fail(h, SPGEMM_INVALID_INPUT, "device-side input check failed (column out of range or rowptr not monotone)");
-  }
-  p->recorded = host.recorded;
-  p->stats.ip_total = (int64_t)host.ip_total;
-  p->stats.nnz_c = host.nnz_c;
-  for (int b = 0; b < kNumBins; ++b) {
-    p->stats.sym_bin_rows[b] = host.hist[0][b];
-    p->stats.num_bin_rows[b] = host.hist[1][b];
-    p->stats.sym_bin_ip[b] = (int64_t)host.bin_ip[0][b];
-    p->stats.num_bin_ip[b] = (int64_t)host.bin_ip[1][b];
-    p->stats.num_bin_nnz[b] = (int64_t)host.bin_nnz[b];
-  }
-  p->stats.dense_tiles = host.tiles_used;
-  p->stats.dense_direct_tiles = host.direct_tiles;
-  p->stats.dense_runs = host.runs_used;
-  p->stats.dense_search_tiles = host.search_tiles;
-  p->stats.plan_bytes = (int64_t)(p->scratch_bytes + p->scratch2_bytes + p->short_bytes + p->list_bytes);
-  p->stats.plan_list_bytes = (int64_t)p->list_bytes;
-  p->stats.plan_list_used = (int64_t)((host.list_cursor < host.list_cap ? host.list_cursor : host.list_cap) * 4ULL);
-  p->symbolic_done = true;
-  *nnz_c = host.nnz_c;
-  *plan = p;
-  return SPGEMM_OK;
+  return symbolic(h, A, B, c_rowptr, nnz_c, plan, true);
 }
 
 int spgemm_numeric(spgemm_handle h, spgemm_plan p, const spgemm_csr* A, const spgemm_csr* B, const int64_t* c_rowptr,
@@ -795,7 +828,7 @@ int spgemm(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, spgemm_csr
   if (!rp) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of C.rowptr failed");
   spgemm_plan plan = nullptr;
   int64_t nnz = 0;
-  rc = spgemm_symbolic(h, A, B, rp, &nnz, &plan);
+  rc = symbolic(h, A, B, rp, &nnz, &plan, false);
   if (rc != SPGEMM_OK) {
     dev_free(h, rp);
     return rc;
@@ -813,7 +846,7 @@ int spgemm(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, spgemm_csr
       plan = nullptr;
       const int64_t keep = h->col_list;
       h->col_list = 0;
-      rc = spgemm_symbolic(h, A, B, rp, &nnz, &plan);
+      rc = symbolic(h, A, B, rp, &nnz, &plan, false);
       h->col_list = keep;
       if (rc != SPGEMM_OK) { dev_free(h, rp); return rc; }
       col = static_cast<int32_t*>(dev_alloc(h, (size_t)nnz * 4));
@@ -1164,7 +1197,7 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
     const spgemm_csr a = block_of_a(t);
     blk[(size_t)t].rp = static_cast<int64_t*>(dev_alloc(h, (size_t)(a.rows + 1) * 8));
     if (!blk[(size_t)t].rp) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of a block's row pointer failed");
-    const int r = spgemm_symbolic(&h2, &a, B, blk[(size_t)t].rp, &blk[(size_t)t].nnz, &blk[(size_t)t].plan);
+    const int r = symbolic(&h2, &a, B, blk[(size_t)t].rp, &blk[(size_t)t].nnz, &blk[(size_t)t].plan, false);
     if (r != SPGEMM_OK) h->err = h2.err;
     return r;
   };

@@ -124,3 +124,71 @@ def test_rows_without_a_record_beside_rows_that_could_have_one(dtype, force):
     torch.cuda.synchronize()
     plan.destroy()
     assert_matches_oracle(A, B, (rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy()), what=f"force {force}")
+
+
+def reordered(M, rng):
+    """The same entries, those of every row in another order (and in other buffers)."""
+    at = np.concatenate([lo + rng.permutation(hi - lo) for lo, hi in zip(M.rowptr[:-1], M.rowptr[1:])] + [np.zeros(0, np.int64)])
+    return W.CSR(M.rows, M.cols, M.rowptr.copy(), M.colidx[at], M.values[at])
+
+
+def numeric_on_a_plan(plan_of, calls, what, force=0, offset=0):
+    """One plan for the operands plan_of, the numeric phase for each of calls in turn, every result compared."""
+    import torch
+    from paper_2404_04541_amd import binding as sg
+
+    def device(M):   # offset: B's and A's columns and values do not start where their buffers do
+        d = sg.to_device(M)
+        for name in ("colidx", "values"):
+            t = getattr(d, name)
+            setattr(d, name, torch.cat([t.new_zeros(offset), t])[offset:])
+        return d
+    h = sg.Handle()
+    h.set_option(sg.OPT_FORCE_WORKSPACE, force)
+    A, B = plan_of
+    dA = device(A)
+    dB = dA if B is A else device(B)
+    rp, nnz, plan = sg.spgemm_symbolic(h, dA, dB)
+    for n, (A, B) in enumerate(calls):
+        dA = device(A)
+        dB = dA if B is A else device(B)
+        col = torch.full((nnz,), -1, dtype=torch.int32, device="cuda")
+        val = torch.full((nnz,), float("nan"), dtype=dA.values.dtype, device="cuda")
+        sg.spgemm_numeric(h, plan, dA, dB, rp, col, val)
+        torch.cuda.synchronize()
+        assert_matches_oracle(A, B, (rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy()), what=f"{what}, call {n}")
+    plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("kind", ["recorded", "short", "described", "dense too"])
+def test_entries_in_another_order_on_a_kept_plan(kind, dtype, offset):
+    """The structure is the same whatever the order of a row's entries: a matrix that is assembled again may come in another one."""
+    rng = np.random.default_rng(51)
+    if kind == "recorded":
+        A, B = operands(5000, dtype)
+    elif kind == "dense too":   # (every class of rows; an ascending B has to stay so where rows are dense, so this one is not)
+        A, B = W.random_csr(600, 500, 40, 52, dtype=dtype), W.random_csr(500, 4000, 30, 53, dtype=dtype, sort_rows=False)
+    else:
+        A, B = short_operands(400 if kind == "short" else 600_000, 3000, dtype, True)
+    A2, B2 = reordered(A, rng), reordered(B, rng)
+    numeric_on_a_plan((A, B), [(A2, B), (A, B2), (A, B), (A2, B2), (A, B)], kind, offset=offset)
+
+
+def test_two_entries_exchanged_on_a_kept_plan():
+    """The smallest change of order, at the first and last entries of the arrays; then an operand that is both A and B."""
+    A, B = operands(5000, np.float64)
+    calls = []
+    for M, at in ((A, 0), (A, A.nnz - 2), (B, 1), (B, B.nnz - 2)):
+        N = W.CSR(M.rows, M.cols, M.rowptr, M.colidx.copy(), M.values.copy())
+        for v in (N.colidx, N.values):
+            v[[at, at + 1]] = v[[at + 1, at]]
+        row = int(np.searchsorted(M.rowptr, at, side="right")) - 1
+        assert at + 1 < M.rowptr[row + 1], "the two entries are of one row"
+        calls += [(N, B) if M is A else (A, N), (A, B)]
+    numeric_on_a_plan((A, B), calls, "two entries")
+    S = W.random_csr(700, 700, 15, 54)
+    S2 = reordered(S, np.random.default_rng(55))
+    T = W.CSR(S.rows, S.cols, S.rowptr, S.colidx.copy(), S.values.copy())
+    numeric_on_a_plan((S, S), [(S, S), (S2, S), (S, T), (S2, S2), (T, S)], "A times A")
