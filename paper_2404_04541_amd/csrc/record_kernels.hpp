@@ -244,7 +244,8 @@ __global__ __launch_bounds__(256) void k_num_recorded(const int* __restrict__ pe
   auto record = [&](int row) { return row >= 0 && ip_row[row] <= kSymHashSmall ? record_of[row] : -1; };
   auto range = [&](int row, int64_t& lo, int& n) {
     lo = 0; n = 0;
-    if (row >= 0) { const Run<int64_t, 2> v = load_run<int64_t, 2>(c_rp + row); lo = v.v[0]; n = (int)(v.v[1] - v.v[0]); }
+    // (a recorded row has no more entries than that, whatever room the row pointer leaves behind them)
+    if (row >= 0) { const Run<int64_t, 2> v = load_run<int64_t, 2>(c_rp + row); lo = v.v[0]; n = v.v[1] - v.v[0] < kNumHashSmall ? (int)(v.v[1] - v.v[0]) : kNumHashSmall; }
   };
   auto value = [&](int64_t a, int n) { return lane < n ? a_val[a + lane] : T(0); };
   RowChain<kWave> ch{perm + first, a_rp, a_col, b_rp, nullptr, nrows, gridDim.x * 4};

@@ -192,3 +192,26 @@ def test_two_entries_exchanged_on_a_kept_plan():
     S2 = reordered(S, np.random.default_rng(55))
     T = W.CSR(S.rows, S.cols, S.rowptr, S.colidx.copy(), S.values.copy())
     numeric_on_a_plan((S, S), [(S, S), (S2, S), (S, T), (S2, S2), (T, S)], "A times A")
+
+
+def test_a_row_pointer_that_leaves_room_behind_the_rows():
+    """Recorded rows only, 300 places between the end of one and the start of the next: the rows themselves are the same."""
+    import torch
+    from paper_2404_04541_amd import binding as sg
+    rng = np.random.default_rng(61)
+    B = csr([np.sort(rng.choice(150, size=20, replace=False)) for _ in range(60)], 150, np.float64, 62)
+    A = csr([rng.choice(60, size=10, replace=False) for _ in range(500)], 60, np.float64, 63)
+    h = sg.Handle()
+    dA, dB = sg.to_device(A), sg.to_device(B)
+    rp, nnz, plan = sg.spgemm_symbolic(h, dA, dB)
+    gap = 300
+    wide = rp + gap * torch.arange(A.rows + 1, device="cuda")
+    total = int(wide[-1])
+    col = torch.full((total,), -1, dtype=torch.int32, device="cuda")
+    val = torch.full((total,), float("nan"), dtype=torch.float64, device="cuda")
+    sg.spgemm_numeric(h, plan, dA, dB, wide, col, val)
+    torch.cuda.synchronize()
+    assert plan.stats()["num_bin_rows"][2] == A.rows
+    plan.destroy()
+    keep = torch.arange(nnz, device="cuda") + gap * (torch.searchsorted(rp, torch.arange(nnz, device="cuda"), right=True) - 1)
+    assert_matches_oracle(A, B, (rp.cpu().numpy(), col[keep].cpu().numpy(), val[keep].cpu().numpy()), what="gaps")
