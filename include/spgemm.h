@@ -127,8 +127,9 @@ enum {
   /* 1 (default): the plan keeps the column indices of the dense workspace's ranked tiles
    * (up to a third of the free device memory), which saves the numeric phase one pass over
    * those tiles' products; rows that do not fit fall back to the two-pass route.  It also keeps the
-   * order of the products of short rows (up to a quarter of the free memory), which saves the numeric
-   * phase their sort or hash.  0: neither.  A value of 4096 or more limits each of the two to that many bytes. */
+   * order of the products of short rows (up to a quarter of the free memory; above 64 MB only as far as the
+   * largest C that the product can have still fits beside it), which saves the numeric phase their sort or
+   * hash.  0: neither.  A value of 4096 or more limits each of the two to that many bytes. */
   SPGEMM_OPT_COLUMN_LIST = 4,
   /* 1 (default): for an ascending B the plan holds a table of per-row offsets at every 8192nd
    * column (when it fits 1 GiB), which turns the search for a tile's piece of a B row into two

@@ -14,6 +14,7 @@
 
 #include "common.hpp"
 #include "entry_order.hpp"
+#include "plan_room.hpp"
 #include "setup_kernels.hpp"
 #include "esc_kernels.hpp"
 #include "record_kernels.hpp"
@@ -357,11 +358,11 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
   return SPGEMM_OK;
 }
 
-// The optional part of a plan, one allocation that the product does without when it fails: the column list of the dense rows
-// (at most a third of the free memory), and what the symbolic kernels of short rows leave for the numeric ones
-// (esc_kernels.hpp, record_kernels.hpp; at most a quarter): sorted words for all rows of a bin or for none, records for as
-// many rows as there is room for.  staged: the numeric phase takes all rows this short through the staged list, which reads neither.
-void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, const Control& host, double list_want, bool staged) {
+// The optional part of a plan, one allocation that the product does without when it fails: the column list of the dense rows, and
+// what the symbolic kernels of short rows leave for the numeric ones (esc_kernels.hpp, record_kernels.hpp): sorted words for
+// all rows of a bin or for none, records for as many rows as there is room for.  When it is refused, the list is asked for alone.
+// value_bytes: of an entry of C.  staged: the numeric phase takes all rows this short through the staged list, which reads neither.
+void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, const Control& host, double list_want, size_t value_bytes, bool staged) {
   if (!h->col_list) return;
   const int64_t max_cols[2] = {kEscPackCols0, kEscPackCols1};
   const size_t word_bytes[2] = {kEscSmallCap * 4, kEscLargeCap * 4};
@@ -373,15 +374,21 @@ void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, co
   const size_t rec_bytes = (size_t)kRecWords * 4, map = align_up((size_t)p->m * 4);
   const size_t rec_rows = !staged && B->cols <= (int64_t(1) << kRecColBits) ? host.hist[0][2] : 0;
   if (rec_rows) want += map + rec_rows * rec_bytes;
-  const size_t asked = h->col_list > 1 ? (size_t)h->col_list : ~(size_t)0;
-  size_t limit = asked;
+  const double asked = h->col_list > 1 ? (double)h->col_list : 1.0e30;
+  size_t limit = asked < (double)want ? (size_t)asked : want;
   if ((double)want + list_want > (double)kAskFreeAbove) {
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return;
-    if (free_b / 4 < limit) limit = free_b / 4;
-    if (list_want > (double)free_b / 3.0) list_want = (double)free_b / 3.0;
+    double entries = 0;   // of C, at most
+    for (int b = 0; b < kNumBins; ++b) {
+      const double ip = (double)host.bin_ip[0][b], full = (double)host.hist[0][b] * (double)B->cols;
+      entries += ip < full ? ip : full;
+    }
+    const PlanRoom room = plan_room((double)free_b, list_want, (double)want, entries * (double)(4 + value_bytes), asked);
+    limit = (size_t)room.shorts;
+    list_want = room.list;
   }
-  if (list_want > (double)asked) list_want = (double)asked;
+  if (list_want > asked) list_want = asked;
   size_t list_bytes = ((size_t)list_want) & ~(size_t)255;
   if (list_bytes < 4096) list_bytes = 0;
   size_t off = 0, o_words[2] = {0, 0};
@@ -398,6 +405,10 @@ void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, co
   }
   if (off + list_bytes == 0) return;
   unsigned char* base = static_cast<unsigned char*>(dev_alloc(h, off + list_bytes));
+  if (!base && off && list_bytes) {
+    off = 0; rows = 0; words[0] = words[1] = 0;
+    base = static_cast<unsigned char*>(dev_alloc(h, list_bytes));
+  }
   if (!base) return;
   p->scratch3 = base;
   p->short_bytes = off;
@@ -451,7 +462,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   double list_want = 0;
   int rc = alloc_dense_lists(h, p, B, host, &tile_cap, &run_cap, &list_want);
   if (rc) return rc;
-  alloc_optional(h, p, B, host, list_want, staged > 0);
+  alloc_optional(h, p, B, host, list_want, sizeof(T), staged > 0);
   p->order_kept = plan_leaves && (p->records || p->esc_words[0] || p->esc_words[1]);
   if (p->order_kept) {
     Timer t(h, SPGEMM_K_COUNT);
