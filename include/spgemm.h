@@ -127,7 +127,7 @@ enum {
   /* 1 (default): the plan keeps the column indices of the dense workspace's ranked tiles
    * (up to a third of the free device memory), which saves the numeric phase one pass over
    * those tiles' products; rows that do not fit fall back to the two-pass route.  It also keeps the
-   * order of the products of short rows (up to a quarter of the free memory; above 64 MB only as far as the
+   * order of the products of short rows and where the rows of B are (up to a quarter of the free memory; above 64 MB only as far as the
    * largest C that the product can have still fits beside it), which saves the numeric phase their sort or
    * hash.  0: neither.  A value of 4096 or more limits each of the two to that many bytes. */
   SPGEMM_OPT_COLUMN_LIST = 4,

@@ -108,7 +108,8 @@ struct spgemm_plan_s {
   int* perm_num = nullptr;
   unsigned char* bin = nullptr;
   long long* partial = nullptr;
-  unsigned long long* desc = nullptr;   // per entry of A: its B row (optional)
+  unsigned long long* desc = nullptr;   // per entry of A: its B row (optional, an allocation of its own: given back when the rest needs the room)
+  size_t desc_bytes = 0;
   void* scratch2 = nullptr;  // sized after the row classes are known: block offsets of B, tile and run lists
   int* blk_ptr = nullptr;    // rows(B) x blk_ptr_cols offsets, null when not needed or too large
   int blk_ptr_cols = 0;      // column blocks + 1
@@ -275,9 +276,17 @@ size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 // of a gather of B's row pointer in each of the two kernels of short rows.  It pays where those gathers miss the L2 cache (4 MB
 // per XCD) and most rows are short.  4.2 M rows of 8 entries times 4.2 M rows of 4, both kernels and the count:
 // 3.50 ms with the gathers, 2.51 ms without; with a cached B the words would cost what they save.
-bool wants_desc(const spgemm_csr* A, const spgemm_csr* B) {
+// (Part of a plan's optional memory.  A block of rows of a larger matrix goes without: its positions are those of the whole.)
+bool wants_desc(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B) {
+  if (!h->col_list || h->row_block || (h->col_list > 1 && A->nnz > h->col_list / 8)) return false;
   if (A->rows == 0 || B->rows * 8 <= ((int64_t)4 << 20) || B->nnz >= (int64_t(1) << 39) || A->nnz >= (int64_t(1) << 39)) return false;
   return (double)A->nnz / (double)A->rows * ((double)B->nnz / (double)B->rows) <= (double)kEscLargeCap;
+}
+
+void drop_desc(spgemm_context* h, spgemm_plan_s* p) {   // (no kernel that uses it is on its way)
+  dev_free(h, p->desc);
+  p->desc = nullptr;
+  p->desc_bytes = 0;
 }
 
 // Rows of A that a workgroup of the row count takes at a time: fewer where there are too few rows to fill the card, more where
@@ -361,6 +370,7 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
 // The optional part of a plan, one allocation that the product does without when it fails: the column list of the dense rows, and
 // what the symbolic kernels of short rows leave for the numeric ones (esc_kernels.hpp, record_kernels.hpp): sorted words for
 // all rows of a bin or for none, records for as many rows as there is room for.  When it is refused, the list is asked for alone.
+// The descriptions of A's entries, which the row count has left, go when there is no room for them.
 // value_bytes: of an entry of C.  staged: the numeric phase takes all rows this short through the staged list, which reads neither.
 void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, const Control& host, double list_want, size_t value_bytes, bool staged) {
   if (!h->col_list) return;
@@ -375,8 +385,8 @@ void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, co
   const size_t rec_rows = !staged && B->cols <= (int64_t(1) << kRecColBits) ? host.hist[0][2] : 0;
   if (rec_rows) want += map + rec_rows * rec_bytes;
   const double asked = h->col_list > 1 ? (double)h->col_list : 1.0e30;
-  size_t limit = asked < (double)want ? (size_t)asked : want;
-  if ((double)want + list_want > (double)kAskFreeAbove) {
+  size_t limit = asked - (double)p->desc_bytes < (double)want ? (size_t)(asked - (double)p->desc_bytes) : want;
+  if ((double)(want + p->desc_bytes) + list_want > (double)kAskFreeAbove) {
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return;
     double entries = 0;   // of C, at most
@@ -384,7 +394,8 @@ void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, co
       const double ip = (double)host.bin_ip[0][b], full = (double)host.hist[0][b] * (double)B->cols;
       entries += ip < full ? ip : full;
     }
-    const PlanRoom room = plan_room((double)free_b, list_want, (double)want, entries * (double)(4 + value_bytes), asked);
+    const PlanRoom room = plan_room((double)free_b, list_want, (double)want, (double)p->desc_bytes, entries * (double)(4 + value_bytes), asked);
+    if (!room.desc) drop_desc(h, p);
     limit = (size_t)room.shorts;
     list_want = room.list;
   }
@@ -460,7 +471,12 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   const int staged = (h->force == 4 && ceil_div(B->cols, kStWinCols) <= kStMaxWindows) ? staged_cap<T>() : 0;
   unsigned tile_cap = 0, run_cap = 0;
   double list_want = 0;
+  if (hist[0] + hist[1] == 0) drop_desc(h, p);   // (nobody reads it)
   int rc = alloc_dense_lists(h, p, B, host, &tile_cap, &run_cap, &list_want);
+  if (rc == SPGEMM_ALLOC_FAILED && p->desc) {
+    drop_desc(h, p);
+    rc = alloc_dense_lists(h, p, B, host, &tile_cap, &run_cap, &list_want);
+  }
   if (rc) return rc;
   alloc_optional(h, p, B, host, list_want, sizeof(T), staged > 0);
   p->order_kept = plan_leaves && (p->records || p->esc_words[0] || p->esc_words[1]);
@@ -626,14 +642,15 @@ int symbolic(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B, int64_
   const size_t o_pn = off; off = align_up(off + (size_t)m * 4);
   const size_t o_bin = off; off = align_up(off + (size_t)m);
   const size_t o_part = off; off = align_up(off + (size_t)(p->scan_blocks + 1) * 8);
-  const size_t plain = off, o_desc = off;
-  if (wants_desc(A, B)) off = align_up(off + (size_t)A->nnz * 8);
   p->scratch = dev_alloc(h, off);
-  if (!p->scratch && off > plain) { off = plain; p->scratch = dev_alloc(h, off); }
   p->scratch_bytes = off;
   if (!p->scratch) {
     delete p;
     return fail(h, SPGEMM_ALLOC_FAILED, "device allocation of plan scratch failed");
+  }
+  if (wants_desc(h, A, B)) {
+    p->desc = static_cast<unsigned long long*>(dev_alloc(h, (size_t)A->nnz * 8));
+    p->desc_bytes = p->desc ? (size_t)A->nnz * 8 : 0;
   }
   unsigned char* base = static_cast<unsigned char*>(p->scratch);
   p->ctl = reinterpret_cast<Control*>(base + o_ctl);
@@ -643,7 +660,6 @@ int symbolic(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B, int64_
   p->perm_num = reinterpret_cast<int*>(base + o_pn);
   p->bin = base + o_bin;
   p->partial = reinterpret_cast<long long*>(base + o_part);
-  if (off > plain) p->desc = reinterpret_cast<unsigned long long*>(base + o_desc);
 
   Control host{};
   rc = run_setup(h, p, A, B, pinned.p, &host);
@@ -686,7 +702,7 @@ int symbolic(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B, int64_
   p->stats.dense_direct_tiles = host.direct_tiles;
   p->stats.dense_runs = host.runs_used;
   p->stats.dense_search_tiles = host.search_tiles;
-  p->stats.plan_bytes = (int64_t)(p->scratch_bytes + p->scratch2_bytes + p->short_bytes + p->list_bytes);
+  p->stats.plan_bytes = (int64_t)(p->scratch_bytes + p->scratch2_bytes + p->desc_bytes + p->short_bytes + p->list_bytes);
   p->stats.plan_list_bytes = (int64_t)p->list_bytes;
   p->stats.plan_list_used = (int64_t)((host.list_cursor < host.list_cap ? host.list_cursor : host.list_cap) * 4ULL);
   p->symbolic_done = true;
@@ -765,6 +781,7 @@ int spgemm_plan_destroy(spgemm_plan p) {
   dev_free(p->h, p->scratch);
   dev_free(p->h, p->scratch2);
   dev_free(p->h, p->scratch3);
+  dev_free(p->h, p->desc);
   delete p;
   return SPGEMM_OK;
 }
@@ -850,8 +867,8 @@ int spgemm(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, spgemm_csr
   if (nnz > 0) {
     col = static_cast<int32_t*>(dev_alloc(h, (size_t)nnz * 4));
     val = dev_alloc(h, (size_t)nnz * vsz);
-    if ((!col || !val) && plan->scratch3 && h->col_list) {
-      // the plan's optional lists may be what stands in the way: plan again without it
+    if ((!col || !val) && (plan->scratch3 || plan->desc)) {
+      // the plan's optional memory may be what stands in the way: plan again without it
       dev_free(h, col); dev_free(h, val);
       spgemm_plan_destroy(plan);
       plan = nullptr;

@@ -40,6 +40,34 @@ class Memory:
     def close(self):
         assert not self.live and self.lib.spgemm_destroy(self.h) == 0
 
+    def product(self, A, B, column_list=1, blocks=0):
+        """spgemm, or spgemm_pipelined in so many blocks; compared with the oracle.  -> the call's status."""
+        import torch
+        sg, lib = self.sg, self.lib
+        assert lib.spgemm_set_option(self.h, sg.OPT_COLUMN_LIST, column_list) == 0
+        dA, dB = sg.to_device(A), sg.to_device(B)
+        sa, sb = dA.struct(), dB.struct()
+        parts = (sg.CsrStruct * max(blocks, 1))()
+        first = (C.c_int64 * (blocks + 1))()
+        if blocks:
+            rc = lib.spgemm_pipelined(self.h, C.byref(sa), C.byref(sb), blocks, parts, first)
+        else:
+            rc = lib.spgemm(self.h, C.byref(sa), C.byref(sb), C.byref(parts[0]))
+        torch.cuda.synchronize()
+        if rc != 0:
+            return rc
+        rp, col, val = [np.zeros(1, np.int64)], [], []
+        for c in parts:
+            get = lambda ptr, n, t: self.live[ptr][:n * t.itemsize].view(t) if n else torch.empty(0, dtype=t, device="cuda")  # noqa: E731
+            rp.append(get(c.rowptr, c.rows + 1, torch.int64).cpu().numpy()[1:] + rp[-1][-1])
+            col.append(get(c.colidx, c.nnz, torch.int32).cpu().numpy())
+            val.append(get(c.values, c.nnz, dA.values.dtype).cpu().numpy())
+            for ptr in (c.rowptr, c.colidx, c.values):
+                if ptr:
+                    lib.spgemm_free_device(self.h, ptr)
+        assert_matches_oracle(A, B, (np.concatenate(rp), np.concatenate(col), np.concatenate(val)))
+        return 0
+
     def phases(self, A, B):
         """Both phases by themselves -> stats, and what was asked for by the symbolic one."""
         import torch
@@ -72,3 +100,61 @@ def test_the_structure_list_is_kept_when_the_rest_is_refused():
     m.close()
     assert less.plan_list_bytes == st.plan_list_bytes and less.plan_list_used > 0
     assert less.plan_bytes == st.plan_bytes - (whole - st.plan_list_bytes)
+
+
+def described(rows=200_000):
+    """B's row pointer is larger than an L2 slice and rows are short: the row count describes the entries of A (8 bytes each)."""
+    A = W.uniform_rows(rows, 600_000, 8, 71, 1)
+    return A, W.uniform_rows(600_000, 5000, 4, 72, 3)
+
+
+def test_descriptions_are_part_of_the_optional_memory():
+    from paper_2404_04541_amd import binding as sg
+    A, B = described()
+    desc = A.nnz * 8
+    for column_list, want in ((1, True), (0, False), (4096, False), (desc - 1, False), (desc, True)):
+        m = Memory(sg)
+        assert m.product(A, B, column_list) == 0
+        assert (desc in m.asked) == want, column_list
+        m.close()
+    m = Memory(sg)
+    assert m.product(A, B, blocks=3) == 0
+    assert max(m.asked) < desc or desc not in m.asked   # (a block's positions are those of the whole matrix)
+    m.close()
+    m = Memory(sg, lambda n, used: n == desc)
+    assert m.product(A, B) == 0
+    m.close()
+
+
+def test_c_is_asked_for_again_without_any_optional_memory():
+    from paper_2404_04541_amd import binding as sg
+    A, B = described()
+    m = Memory(sg)
+    assert m.product(A, B, 0) == 0
+    least = m.most   # what the product cannot do without
+    m.close()
+    m = Memory(sg)
+    assert m.product(A, B) == 0 and m.most > least
+    m.close()
+    m = Memory(sg, lambda n, used: used + n > least)
+    assert m.product(A, B) == 0 and A.nnz * 8 in m.asked
+    m.close()
+
+
+def test_the_plan_gives_the_descriptions_back_when_its_lists_find_no_room():
+    from paper_2404_04541_amd import binding as sg
+    A, B = described(20_000)
+    long_rows = W.uniform_rows(50, 600_000, 2000, 73, 1)   # (dense: 8000 products)
+    A = W.CSR(A.rows + 50, A.cols, np.concatenate([A.rowptr, A.rowptr[-1] + long_rows.rowptr[1:]]),
+              np.concatenate([A.colidx, long_rows.colidx]), np.concatenate([A.values, long_rows.values]))
+    m = Memory(sg)
+    m.phases(A, B)
+    asked = m.asked
+    m.close()
+    desc = A.nnz * 8
+    lists = asked[asked.index(desc) + 1]   # tile and run lists, the block table: the plan cannot do without
+    before = sum(asked[:asked.index(desc)])
+    m = Memory(sg, lambda n, used: used + n > before + max(desc, lists))
+    m.phases(A, B)
+    assert lists in m.asked and m.asked.count(lists) == 2
+    m.close()
