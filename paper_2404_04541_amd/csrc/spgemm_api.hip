@@ -1221,18 +1221,40 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
     a.rowptr = A->rowptr + block_rows[t];
     return a;
   };
-  auto symbolic_of = [&](int t) -> int {
-    const spgemm_csr a = block_of_a(t);
-    blk[(size_t)t].rp = static_cast<int64_t*>(dev_alloc(h, (size_t)(a.rows + 1) * 8));
-    if (!blk[(size_t)t].rp) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of a block's row pointer failed");
-    const int r = symbolic(&h2, &a, B, blk[(size_t)t].rp, &blk[(size_t)t].nnz, &blk[(size_t)t].plan, false);
-    if (r != SPGEMM_OK) h->err = h2.err;
-    return r;
-  };
   auto release_plan = [&](int t) {
     Block& b = blk[(size_t)t];
     if (b.done) { (void)hipEventSynchronize(b.done); (void)hipEventDestroy(b.done); b.done = nullptr; }
     if (b.plan) { spgemm_plan_destroy(b.plan); b.plan = nullptr; }
+  };
+  auto symbolic_once = [&](int t) -> int {
+    Block& b = blk[(size_t)t];
+    const spgemm_csr a = block_of_a(t);
+    if (!b.rp) b.rp = static_cast<int64_t*>(dev_alloc(h, (size_t)(a.rows + 1) * 8));
+    if (!b.rp) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of a block's row pointer failed");
+    const int r = symbolic(&h2, &a, B, b.rp, &b.nnz, &b.plan, false);
+    if (r != SPGEMM_OK) h->err = h2.err;
+    return r;
+  };
+  // (when memory is short: once more with the plans before it gone, their numeric phases waited for, and without optional memory)
+  auto symbolic_short = [&](int t) -> int {
+    for (int before = t - 2 > 0 ? t - 2 : 0; before <= t; ++before) release_plan(before);
+    h2.col_list = 0;
+    const int r = symbolic_once(t);
+    h2.col_list = h->col_list;
+    return r;
+  };
+  auto symbolic_of = [&](int t) -> int {
+    const int r = symbolic_once(t);
+    return r == SPGEMM_ALLOC_FAILED ? symbolic_short(t) : r;
+  };
+  auto alloc_c = [&](int t) -> bool {
+    Block& b = blk[(size_t)t];
+    b.col = static_cast<int32_t*>(dev_alloc(h, (size_t)b.nnz * 4));
+    b.val = b.col ? dev_alloc(h, (size_t)b.nnz * vsz) : nullptr;
+    if (b.val) return true;
+    dev_free(h, b.col);
+    b.col = nullptr;
+    return false;
   };
   rc = symbolic_of(0);
   for (int t = 0; t < nblocks && rc == SPGEMM_OK; ++t) {
@@ -1240,9 +1262,11 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
     const spgemm_csr a = block_of_a(t);
     // numeric of block t on the handle's stream (enqueued only) ...
     if (b.nnz > 0) {
-      b.col = static_cast<int32_t*>(dev_alloc(h, (size_t)b.nnz * 4));
-      b.val = dev_alloc(h, (size_t)b.nnz * vsz);
-      if (!b.col || !b.val) { rc = fail(h, SPGEMM_ALLOC_FAILED, "allocation of a block of C failed"); break; }
+      if (!alloc_c(t)) {
+        rc = symbolic_short(t);
+        if (rc == SPGEMM_OK && !alloc_c(t)) rc = fail(h, SPGEMM_ALLOC_FAILED, "allocation of a block of C failed");
+        if (rc != SPGEMM_OK) break;
+      }
       rc = A->dtype == SPGEMM_F32 ? run_numeric<float>(h, b.plan, &a, B, b.rp, b.col, b.val) : run_numeric<double>(h, b.plan, &a, B, b.rp, b.col, b.val);
       if (rc != SPGEMM_OK) break;
     }

@@ -158,3 +158,22 @@ def test_the_plan_gives_the_descriptions_back_when_its_lists_find_no_room():
     m.phases(A, B)
     assert lists in m.asked and m.asked.count(lists) == 2
     m.close()
+
+
+@pytest.mark.parametrize("case", ["graph", "short rows"])
+def test_row_blocks_go_on_without_the_optional_memory(case):
+    from paper_2404_04541_amd import binding as sg
+    A, B = W.config3(scale=13) if case == "graph" else (W.uniform_rows(30_000, 4000, 20, 74, 1), W.uniform_rows(4000, 3000, 20, 75, 3))
+    m = Memory(sg)
+    assert m.product(A, B, 0, blocks=4) == 0
+    least = m.most
+    m.close()
+    m = Memory(sg)
+    assert m.product(A, B, blocks=4) == 0 and m.most > least
+    m.close()
+    m = Memory(sg, lambda n, used: used + n > least)
+    assert m.product(A, B, blocks=4) == 0
+    m.close()
+    m = Memory(sg, lambda n, used: used + n > least // 2)
+    assert m.product(A, B, blocks=4) == -5   # (too little even so: an error, and nothing is left behind)
+    m.close()
