@@ -363,7 +363,11 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
   p->blk_ptr = with_bp ? reinterpret_cast<int*>(base + o_bp) : nullptr;
   // Column list: the dense symbolic kernel leaves the columns of its ranked tiles there, which saves
   // the numeric kernel one pass over those tiles' products.  (Every row's share is rounded up to 16 bytes.)
-  *list_want = (entries + 4.0 * rows_d * spans) * 4.0;
+  // On top of it the first slab of every workgroup of the symbolic kernel (a quarter of the list, at most kListSlab entries each:
+  // list_slab_of): a workgroup whose rows are longer than the slab leaves it unused, and without room for that a quarter of the
+  // rows of a product with few repeated columns lost their place in the list (300 rows of 3000 entries: 225 of them listed).
+  const double entries_want = entries + 4.0 * rows_d * spans, slabs = wgs * kListSlab;
+  *list_want = (entries_want + (entries_want / 3.0 < slabs ? entries_want / 3.0 : slabs)) * 4.0;
   return SPGEMM_OK;
 }
 

@@ -25,3 +25,14 @@ def test_dense_rows_and_slabs(rows, mean, cols, b_mean):
     assert_matches_oracle(A, B, got, what=f"{rows} dense rows")
     st = got[3]
     assert st["num_bin_rows"][5] + st["num_bin_rows"][6] == rows and st["dense_runs"] >= rows
+
+
+@pytest.mark.parametrize("rows", [2, 40, 300])
+def test_every_long_row_finds_room_in_the_list(rows):
+    """Rows of about 3000 entries over a million columns with hardly a column twice: each becomes one searched tile, which needs
+    its columns in the list."""
+    A = W.uniform_rows(rows, 3000, 6, 93, 1, np.float32)
+    B = W.uniform_rows(3000, 1_000_000, 500, 93, 3, np.float32)
+    got = gpu_product(A, B)
+    assert_matches_oracle(A, B, got, what=f"{rows} rows")
+    assert got[3]["dense_search_tiles"] == rows
