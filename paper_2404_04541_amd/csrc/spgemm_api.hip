@@ -367,7 +367,7 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
   // list_slab_of): a workgroup whose rows are longer than the slab leaves it unused, and without room for that a quarter of the
   // rows of a product with few repeated columns lost their place in the list (300 rows of 3000 entries: 225 of them listed).
   const double entries_want = entries + 4.0 * rows_d * spans, slabs = wgs * kListSlab;
-  *list_want = (entries_want + (entries_want / 3.0 < slabs ? entries_want / 3.0 : slabs)) * 4.0;
+  *list_want = (entries_want + (entries_want / 3.0 < slabs ? entries_want / 3.0 : slabs) + 64.0) * 4.0;   // (+ 64: it is cut to whole 256 bytes)
   return SPGEMM_OK;
 }
 

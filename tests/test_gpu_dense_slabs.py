@@ -27,7 +27,7 @@ def test_dense_rows_and_slabs(rows, mean, cols, b_mean):
     assert st["num_bin_rows"][5] + st["num_bin_rows"][6] == rows and st["dense_runs"] >= rows
 
 
-@pytest.mark.parametrize("rows", [2, 40, 300])
+@pytest.mark.parametrize("rows", [1, 2, 40, 300])
 def test_every_long_row_finds_room_in_the_list(rows):
     """Rows of about 3000 entries over a million columns with hardly a column twice: each becomes one searched tile, which needs
     its columns in the list."""
