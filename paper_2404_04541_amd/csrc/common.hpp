@@ -38,7 +38,8 @@ struct Control {
   unsigned direct_tiles;              // how many of the tiles are direct
   unsigned search_tiles;              // how many are searched tiles
   unsigned recorded;                  // rows with a record for the numeric phase
-  unsigned long long list_cursor, list_cap;   // entries used / available in the plan's column list
+  unsigned long long list_cursor, list_cap;   // entries given out (with what is left of the workgroups' slabs) / available in the plan's column list
+  unsigned long long list_used;               // entries that rows have taken
   int error;                      // nonzero: a device-side input check failed
   int b_sorted;                   // 1 when every B row is strictly ascending
   int long_b_row;                 // 1 when some B row has 2^21 or more entries

@@ -341,6 +341,7 @@ struct TilePlan {
   long long list_base;    // position of the span's first entry (or first flag word) in the plan's list, -1 = none
   int list_words;         // > 0: the span's structure goes to the list as that many flag words instead of columns
   int grp[kSpanGroups];   // entries per group of kGrpWords flag words
+  unsigned long long list_used;   // list entries that this workgroup's rows have taken
 };
 
 // index of the lowest set bit at or above position b in the 128-bit mask (hi:lo); 128 when none
@@ -486,6 +487,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
   const unsigned tile_cap = ctl->tile_cap, run_cap = ctl->run_cap;
   const unsigned long long list_cap = ctl->list_cap;
   SPG_CLK(clk_begin(&rs->clk);)
+  if (tid == 0) tp->list_used = 0;
   int row = next_dense_row(perm, ctl, &rs->s_row);
   int next_row = -1;   // (thread 0) the row after this one, fetched while this one is in the works
   // (thread 0) what is left of the slabs drawn from the plan's lists, and what this workgroup used.  The first slab of
@@ -628,6 +630,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
             rb = sr_pos; sr_pos += (unsigned)nr; sr_left -= (unsigned)nr;
           }
         }
+        if (listed) tp->list_used += need;
         tp->list_base = listed ? (long long)at : -1;
         tp->list_words = listed && as_words ? fwords : 0;
         tp->tile_base = tb;
@@ -766,6 +769,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
     for (unsigned i = 0; i < sr_left; ++i) runs[sr_pos + i].count = 0;
     if (used_tiles) atomicAdd(&ctl->tiles_used, used_tiles);
     if (used_runs) atomicAdd(&ctl->runs_used, used_runs);
+    if (tp->list_used) atomicAdd(&ctl->list_used, tp->list_used);
   }
   SPG_CLK(clk_mark(&rs->clk, 9); clk_flush(&rs->clk, ctl->clk[0]);)
 }

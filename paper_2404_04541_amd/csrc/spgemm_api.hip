@@ -708,7 +708,7 @@ int symbolic(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B, int64_
   p->stats.dense_search_tiles = host.search_tiles;
   p->stats.plan_bytes = (int64_t)(p->scratch_bytes + p->scratch2_bytes + p->desc_bytes + p->short_bytes + p->list_bytes);
   p->stats.plan_list_bytes = (int64_t)p->list_bytes;
-  p->stats.plan_list_used = (int64_t)((host.list_cursor < host.list_cap ? host.list_cursor : host.list_cap) * 4ULL);
+  p->stats.plan_list_used = (int64_t)(host.list_used * 4ULL);
   p->symbolic_done = true;
   *nnz_c = host.nnz_c;
   *plan = p;

@@ -36,3 +36,17 @@ def test_every_long_row_finds_room_in_the_list(rows):
     got = gpu_product(A, B)
     assert_matches_oracle(A, B, got, what=f"{rows} rows")
     assert got[3]["dense_search_tiles"] == rows
+
+
+@pytest.mark.parametrize("rows", [1, 40, 300])
+def test_list_bytes_used_are_those_of_the_rows(rows):
+    """Rows of about 3000 entries over a million columns keep their columns, four bytes each in groups of four; a list of 4 KB
+    has room for none of them."""
+    A = W.uniform_rows(rows, 3000, 6, 93, 1, np.float32)
+    B = W.uniform_rows(3000, 1_000_000, 500, 93, 3, np.float32)
+    got = gpu_product(A, B)
+    assert_matches_oracle(A, B, got, what=f"{rows} rows")
+    assert got[3]["plan_list_used"] == int(((np.diff(got[0]) + 3) // 4 * 4).sum()) * 4 <= got[3]["plan_list_bytes"]
+    got = gpu_product(A, B, options={4: 4096})   # (SPGEMM_OPT_COLUMN_LIST)
+    assert_matches_oracle(A, B, got, what=f"{rows} rows, no room")
+    assert got[3]["plan_list_used"] == 0 and got[3]["plan_list_bytes"] == 4096
