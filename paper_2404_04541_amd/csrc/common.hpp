@@ -37,6 +37,7 @@ struct Control {
   unsigned tiles_used, runs_used;     // records in use (the cursors also count what is left of the workgroups' slabs)
   unsigned direct_tiles;              // how many of the tiles are direct
   unsigned search_tiles;              // how many are searched tiles
+  int chunk_rows;                     // rows of A that a workgroup of the row count takes at a time
   unsigned recorded;                  // rows with a record for the numeric phase
   unsigned long long list_cursor, list_cap;   // entries given out (with what is left of the workgroups' slabs) / available in the plan's column list
   unsigned long long list_used;               // entries that rows have taken

@@ -4,13 +4,39 @@
 
 namespace spg {
 
-__global__ void k_init_control(Control* ctl) {
-  unsigned* w = reinterpret_cast<unsigned*>(ctl);
-  for (int i = threadIdx.x; i < (int)(sizeof(Control) / sizeof(unsigned)); i += blockDim.x) w[i] = 0;
-}
-
 constexpr int kCountThreads = 1024;
 constexpr int kCountMaxRows = 1024;   // rows of A in a chunk: at most
+
+// Clears the control block and says how many rows of A a workgroup of the row count takes at a time: chunk, or kCountMaxRows where
+// there are enough rows for all workgroups, rows are short (a chunk of 256 rows of a few entries leaves most of the 1024 threads idle
+// and costs six barriers) and no stretch of them is much heavier than what a workgroup gets anyway (two are resident on each of `cus`
+// compute units; one that holds the hub rows of a graph keeps the whole count waiting).
+// us with chunks of 256 | 1024 rows: 4.2 M rows of 2 entries 329 | 241, of 16 entries 1368 | 1322, of 27 entries 2131 | 2200; 2 M rows of 2
+// entries 121 | 67, of 16 entries 253 | 240, of 27 entries 385 | 383; R-MAT of 2^20 vertices, 4 edges each 248 | 398, of 2^21, 7 edges
+// each 637 | 1061.
+__global__ __launch_bounds__(kCountThreads) void k_init_control(Control* ctl, int64_t m, const int64_t* __restrict__ a_rp, int chunk, int cus) {
+  __shared__ unsigned long long heaviest;
+  unsigned* w = reinterpret_cast<unsigned*>(ctl);
+  for (int i = threadIdx.x; i < (int)(sizeof(Control) / sizeof(unsigned)); i += blockDim.x) w[i] = 0;
+  if (threadIdx.x == 0) heaviest = 0;
+  __syncthreads();
+  if (m >= (int64_t)kCountMaxRows * 2 * cus) {
+    const int64_t nnz = a_rp[m] - a_rp[0];
+    // (looked at are as many stretches of whole chunks as workgroups are resident, or up to twice as many: every chunk took 14 us more)
+    const int64_t stretch = m / ((int64_t)kCountMaxRows * 2 * cus) * kCountMaxRows;
+    unsigned long long most = 0;
+    for (int64_t r = threadIdx.x * stretch; r < m; r += kCountThreads * stretch) {
+      const unsigned long long n = (unsigned long long)(a_rp[r + stretch < m ? r + stretch : m] - a_rp[r]);
+      most = n > most ? n : most;
+    }
+    for (int d = kWave / 2; d > 0; d >>= 1) { const unsigned long long o = __shfl_xor(most, d, kWave); most = o > most ? o : most; }
+    if (lane_id() == 0) atomicMax(&heaviest, most);
+    __syncthreads();
+    // (a row pointer that descends gives a huge one)
+    if (nnz <= 16 * m && heaviest <= (unsigned long long)nnz / (unsigned)cus) chunk = kCountMaxRows;
+  }
+  if (threadIdx.x == 0) ctl->chunk_rows = chunk;
+}
 
 // Adds one row per lane (bin < 0: none) to the bin populations in LDS, the lanes of a bin together: atomics of 64 lanes on the
 // same counter are executed one after the other.  nnz may be null.
@@ -83,7 +109,7 @@ __device__ __forceinline__ void validate_b(int part, int parts, int64_t rows, in
 // desc (optional): start and length of every A entry's B row, for the kernels of short rows.
 // Writes ip (saturated to int32), the symbolic bin, zero counts for rows without products.
 __global__ __launch_bounds__(kCountThreads) void k_count_rows(int parts, int64_t b_cols, int64_t b_nnz, const int32_t* __restrict__ b_col, int64_t m,
-                                                    int chunk_rows, int64_t nnz_a, int64_t b_rows,
+                                                    int64_t nnz_a, int64_t b_rows,
                                                     const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                     const int64_t* __restrict__ b_rp, int* __restrict__ ip_out,
                                                     unsigned char* __restrict__ bin_out, int* __restrict__ cnt_out,
@@ -99,6 +125,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int parts, int64_t
     return;
   }
   const int tid = threadIdx.x;
+  const int chunk_rows = ctl->chunk_rows;
   if (tid < kNumBins) { hist[tid] = 0; hip[tid] = 0; }
   // a workgroup takes several chunks and reports its bin populations once (thousands of workgroups adding to
   // the same few counters cost more than the counting)

@@ -289,14 +289,9 @@ void drop_desc(spgemm_context* h, spgemm_plan_s* p) {   // (no kernel that uses 
   p->desc_bytes = 0;
 }
 
-// Rows of A that a workgroup of the row count takes at a time: fewer where there are too few rows to fill the card, more where
-// rows are short (a chunk of 256 rows of one or two entries leaves most of the 1024 threads idle and costs six barriers; graphs
-// with hub rows have longer rows on average and would wait for the chunk of the hubs: R-MAT scale 19 0.84 ms with 1024 rows).
-// 16384 rows of a power-law graph: 256 rows 57 us, 64 rows 27 us; 4.2 M rows of 2.4 entries: 256 rows 232 us, 1024 rows 128 us.
-int count_chunk(spgemm_context* h, int64_t m, int64_t nnz) {
-  if (m >= (int64_t)kCountMaxRows * 2 * h->num_cus && nnz <= 8 * m) return kCountMaxRows;
-  return m >= (int64_t)256 * 2 * h->num_cus ? 256 : 64;
-}
+// Rows of A that a workgroup of the row count takes at a time, where they are not so many that k_init_control may take more: fewer
+// where there are too few rows to fill the card.  16384 rows of a power-law graph: 256 rows 57 us, 64 rows 27 us.
+int count_chunk(spgemm_context* h, int64_t m) { return m >= (int64_t)256 * 2 * h->num_cus ? 256 : 64; }
 
 // Symbolic phase, first part: count, check, bin.  Ends with the control block on the host
 // (one synchronisation): the second part sizes its lists and launches from the bin populations.
@@ -305,11 +300,11 @@ int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const sp
   const int64_t m = p->m;
   {
     Timer t(h, SPGEMM_K_COUNT);
-    hipLaunchKernelGGL(k_init_control, dim3(1), dim3(256), 0, s, p->ctl);
+    const int chunk = count_chunk(h, m);
+    hipLaunchKernelGGL(k_init_control, dim3(1), dim3(kCountThreads), 0, s, p->ctl, m, A->rowptr, chunk, h->num_cus);
     const unsigned parts = grid_for(B->nnz > B->rows ? B->nnz : B->rows, kCountThreads * 8, (int64_t)h->num_cus * 4);
-    const int chunk = count_chunk(h, m, A->nnz);
     const unsigned groups = m > 0 ? grid_for(m, chunk, (int64_t)h->num_cus * 8) : 0;
-    hipLaunchKernelGGL(k_count_rows, dim3(parts + groups), dim3(kCountThreads), 0, s, (int)parts, B->cols, B->nnz, B->colidx, m, chunk, A->nnz, B->rows,
+    hipLaunchKernelGGL(k_count_rows, dim3(parts + groups), dim3(kCountThreads), 0, s, (int)parts, B->cols, B->nnz, B->colidx, m, A->nnz, B->rows,
                        A->rowptr, A->colidx, B->rowptr, p->ip, p->bin, p->cnt, p->ctl, h->force, h->row_block, p->desc);
   }
   {
@@ -1180,10 +1175,10 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
     if (!tmp) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the row-block planning failed");
     Control* ctl = reinterpret_cast<Control*>(tmp + o_ctl);
     Control host{};
-    hipLaunchKernelGGL(k_init_control, dim3(1), dim3(64), 0, h->stream, ctl);
-    const int chunk = count_chunk(h, m, A->nnz);
+    const int chunk = count_chunk(h, m);
+    hipLaunchKernelGGL(k_init_control, dim3(1), dim3(kCountThreads), 0, h->stream, ctl, m, A->rowptr, chunk, h->num_cus);
     if (m > 0)
-      hipLaunchKernelGGL(k_count_rows, dim3(grid_for(m, chunk, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, h->stream, 0, B->cols, B->nnz, B->colidx, m, chunk,
+      hipLaunchKernelGGL(k_count_rows, dim3(grid_for(m, chunk, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, h->stream, 0, B->cols, B->nnz, B->colidx, m,
                          A->nnz, B->rows, A->rowptr, A->colidx, B->rowptr, reinterpret_cast<int*>(tmp + o_ip), tmp + o_bin, reinterpret_cast<int*>(tmp + o_cnt), ctl, 0, 0, (unsigned long long*)nullptr);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && m > 0) e = hipMemcpyAsync(ip_host.data(), tmp + o_ip, (size_t)m * 4, hipMemcpyDeviceToHost, h->stream);
