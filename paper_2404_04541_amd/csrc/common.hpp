@@ -49,7 +49,6 @@ struct Control {
   unsigned long long bin_ip[2][kNumBins];   // intermediate products per bin
   unsigned long long bin_nnz[kNumBins];     // output entries per numeric bin
   long long nnz_c;
-  long long scan_blocks;
   unsigned long long order, order_now;   // the order of the entries (k_order_sum): the plan's, and the one being added up
   int order_differs;              // 1: the entries of the numeric phase's operands come in another order than the plan's
 #ifdef SPG_PHASE_CLOCKS

@@ -104,7 +104,7 @@ struct RowScratch {
   long long start[kSymPieces];   // first B entry of each A entry's piece
   int plen[kSymPieces];          // piece length
   int cpre[kSymPieces + 1];      // exclusive prefix of quad counts
-  int more[kSymPieces + 1];      // (room for the staging area of the column decode, which takes this struct's place)
+  int more[kSymPieces + 1];      // (the column decode stages kListStage entries per wave from `start` to here)
   int red[2 * kDenseWaves];
   int s_row;
   int pad;

@@ -3,14 +3,14 @@
 // in section 7.3).  Loop order k -> i -> j over A in doubly compressed sparse columns and B in
 // doubly compressed sparse rows; consecutive products land on unrelated coordinates (i, j), so
 // they pass through a workspace of whole components:
-//   insert   a batch of products (i << 32 | j, a_ik * b_kj) fills the accumulation array
-//   sort     the accumulation array goes into result order (stable radix sort by coordinate)
-//   merge    equal coordinates are added up; the sorted batch is merged into the all array
-//            (sorted, unique), again adding equal coordinates
-//   compress the all array becomes the row pointer / column / value arrays of C
-// On the GPU a batch is inserted by one launch (a thread per product), not by one append at a
-// time, and the merge is a rank computation on both sides followed by one reduction of equal
-// neighbours; the stages and the two arrays are the paper's.
+//   insert   a batch of products fills the accumulation array: coordinate (i above the bits of j, one 64-bit key) and a_ik * b_kj
+//   sort     the accumulation array goes into result order (stable radix sort by coordinate, values along)
+//   merge    equal coordinates of the batch are added up (the first component of a run walks it, in order), and the sorted batch
+//            is merged into the all array (sorted, unique), where the all array's component takes the batch's along
+//   compress the last of these stages writes columns and values of C, the row pointer comes from the coordinates
+// On the GPU a batch is inserted by one launch, a workgroup taking a range of the sort and finding the columns of A of a tile of
+// products once, and the merge is cut into tiles along the diagonals of the two arrays; the stages and the two arrays are the
+// paper's.
 #pragma once
 #include "sort_kernels.hpp"
 

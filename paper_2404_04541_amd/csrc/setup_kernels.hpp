@@ -38,8 +38,6 @@ __global__ __launch_bounds__(kCountThreads) void k_init_control(Control* ctl, in
   if (threadIdx.x == 0) ctl->chunk_rows = chunk;
 }
 
-// Adds one row per lane (bin < 0: none) to the bin populations in LDS, the lanes of a bin together: atomics of 64 lanes on the
-// same counter are executed one after the other.  nnz may be null.
 __device__ __forceinline__ unsigned long long wave_sum64(unsigned long long v) {   // 24-bit pieces: 64 of them stay below 2^31
   unsigned long long s = (unsigned)__builtin_amdgcn_readlane(wave_incl_scan((int)(v & 0xffffff)), kWave - 1);
   if (__any((v >> 24) != 0)) {
@@ -49,6 +47,8 @@ __device__ __forceinline__ unsigned long long wave_sum64(unsigned long long v) {
   return s;
 }
 
+// Adds one row per lane (bin < 0: none) to the bin populations in LDS, the lanes of a bin together: atomics of 64 lanes on the
+// same counter are executed one after the other.  hnz may be null.
 __device__ __forceinline__ void add_to_bins(int bin, unsigned long long ip, unsigned nnz, unsigned* hist, unsigned long long* hip, unsigned long long* hnz) {
   unsigned long long left = __ballot(bin >= 0);
   while (left) {

@@ -1383,7 +1383,6 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
   double* vals[2] = {bufs.get<double>((size_t)cap), bufs.get<double>((size_t)cap)};
   unsigned* counters = bufs.get<unsigned>(sort_counter_bytes(cap) / 4);   // (the last batch is shorter and may take more ranges)
   if (!keys[0] || !keys[1] || !vals[0] || !vals[1] || !counters) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the accumulation array failed");
-  const int64_t cap_grid = (int64_t)h->num_cus * 32;
   // all array: sorted, unique coordinates with their sums
   unsigned long long* all_k = nullptr;
   double* all_v = nullptr;

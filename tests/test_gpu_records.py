@@ -215,3 +215,36 @@ def test_a_row_pointer_that_leaves_room_behind_the_rows():
     plan.destroy()
     keep = torch.arange(nnz, device="cuda") + gap * (torch.searchsorted(rp, torch.arange(nnz, device="cuda"), right=True) - 1)
     assert_matches_oracle(A, B, (rp.cpu().numpy(), col[keep].cpu().numpy(), val[keep].cpu().numpy()), what="gaps")
+
+
+def test_numeric_phase_under_capture_on_a_kept_plan():
+    """The numeric phase only enqueues kernels: a captured one follows the operands' buffers, values and order, in every replay."""
+    import torch
+    from paper_2404_04541_amd import binding as sg
+    A, B = operands(5000, np.float64)
+    rng = np.random.default_rng(71)
+    stream = torch.cuda.Stream()
+    h = sg.Handle(stream=stream)
+    with torch.cuda.stream(stream):
+        dA, dB = sg.to_device(A), sg.to_device(B)
+        rp, nnz, plan = sg.spgemm_symbolic(h, dA, dB)
+        col = torch.empty(nnz, dtype=torch.int32, device="cuda")
+        val = torch.empty(nnz, dtype=torch.float64, device="cuda")
+        sg.spgemm_numeric(h, plan, dA, dB, rp, col, val)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            sg.spgemm_numeric(h, plan, dA, dB, rp, col, val)
+    for n, (X, Y) in enumerate([(A, B), (reordered(A, rng), B), (A, B), (A, reordered(B, rng)), (A, B)]):
+        X = W.CSR(X.rows, X.cols, X.rowptr, X.colidx, X.values * (n + 1))
+        for d, m in ((dA, X), (dB, Y)):
+            d.colidx.copy_(torch.from_numpy(m.colidx))
+            d.values.copy_(torch.from_numpy(m.values))
+        col.fill_(-1)
+        val.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_matches_oracle(X, Y, (rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy()), what=f"replay {n}")
+        sg.spgemm(sg.Handle(), dA, dB)   # (other work between the replays)
+    plan.destroy()
