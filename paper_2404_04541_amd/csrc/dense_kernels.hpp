@@ -167,7 +167,8 @@ struct Quad {
 // and take about 45 per 256 elements.  R-MAT scale 19 squared (fp32), numeric kernel 27.9 -> 25.9 ms; scale 14: numeric 218 ->
 // 190 us, symbolic 229 -> 208 us; deduplication sweep (fp64) 1.64 -> 1.59 ms.  With values one batch at a time is best (two in
 // flight 26.5 ms, three 29.7, four 31.8: registers; the next one prefetched 25.9, but 1.69 for the sweep); without them the
-// next batch is prefetched (15.8 ms at scale 19 against 16.5).
+// next batch is prefetched (15.8 ms at scale 19 against 16.5).  At scale 20 the symbolic kernel lost a little against the chunks
+// (42.2 -> 43.7 ms), the numeric one gained 6 ms.
 template <bool WITH_VALUES, typename T, class G>
 __device__ __forceinline__ void quad_pass(int np, int nq, const PieceList<T> pl, const int32_t* __restrict__ b_col,
                                           const T* __restrict__ b_val, int64_t b_nnz, G g) {
