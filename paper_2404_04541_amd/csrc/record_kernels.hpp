@@ -11,8 +11,10 @@
 //   searched or sorted again.  Rows without a record take the hash workspace.
 // The record costs one byte per product and four per entry, written and read once; finding the ranks again costs a
 // compare-and-swap loop per product (the slowest of 64 lanes decides) and a sort per row.
-// Bounds: the symbolic kernel issues about 600 vector instructions per row (insertion 300, sort and ranks 160), the numeric one
-// waits for LDS (27 cycles per wave instruction of additions at random places, 12 of them in a row of 729 products).
+// Bounds: the symbolic kernel issues about 600 vector instructions per row (insertion 300, sort and ranks 160; vector units 0.6, LDS
+// 0.66 of the cycles on the stencil below); the numeric one is bound by memory: 9.9 GB between L2 and memory in 2.2 ms, 4.5 TB/s of
+// the 4.7 that a large copy reaches (records 3.2, C 3.1, A 0.7 GB, the rest B's values, which every die fetches for itself), with LDS
+// active for half of the cycles.
 // 27-point stencil of 128^3 rows, fp64 (729 products and 125 entries per row): hash workspace 2.39 + 4.80 ms, here 3.13 + 2.22 ms;
 // of 61^3 rows, numeric phase on a kept plan: 480 -> 255 us.
 #pragma once
