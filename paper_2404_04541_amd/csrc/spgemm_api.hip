@@ -371,17 +371,22 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
 // all rows of a bin or for none, records for as many rows as there is room for.  When it is refused, the list is asked for alone.
 // The descriptions of A's entries, which the row count has left, go when there is no room for them.
 // value_bytes: of an entry of C.  staged: the numeric phase takes all rows this short through the staged list, which reads neither.
-void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, const Control& host, double list_want, size_t value_bytes, bool staged) {
+// plan_leaves: the numeric phases on the plan look at the order of the entries first, which pays for sorted words alone from a million
+// products on (numeric phase with words and check | without either, us: 0.1 M products 12 | 7, 0.75 M 14.6 | 10, 3 M 27 | 39).
+constexpr unsigned long long kWordsWithCheck = 1ULL << 20;
+void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, const Control& host, double list_want, size_t value_bytes, bool staged,
+                    bool plan_leaves) {
   if (!h->col_list) return;
   const int64_t max_cols[2] = {kEscPackCols0, kEscPackCols1};
   const size_t word_bytes[2] = {kEscSmallCap * 4, kEscLargeCap * 4};
+  const size_t rec_rows = !staged && B->cols <= (int64_t(1) << kRecColBits) ? host.hist[0][2] : 0;
+  const bool with_words = !staged && (!plan_leaves || rec_rows || host.bin_ip[0][0] + host.bin_ip[0][1] >= kWordsWithCheck);
   size_t words[2], want = 0;
   for (int b = 0; b < 2; ++b) {
-    words[b] = !staged && B->cols <= max_cols[b] ? align_up(host.hist[0][b] * word_bytes[b]) : 0;
+    words[b] = with_words && B->cols <= max_cols[b] ? align_up(host.hist[0][b] * word_bytes[b]) : 0;
     want += words[b];
   }
   const size_t rec_bytes = (size_t)kRecWords * 4, map = align_up((size_t)p->m * 4);
-  const size_t rec_rows = !staged && B->cols <= (int64_t(1) << kRecColBits) ? host.hist[0][2] : 0;
   if (rec_rows) want += map + rec_rows * rec_bytes;
   const double asked = h->col_list > 1 ? (double)h->col_list : 1.0e30;
   size_t limit = asked - (double)p->desc_bytes < (double)want ? (size_t)(asked - (double)p->desc_bytes) : want;
@@ -445,12 +450,13 @@ __global__ void k_set_caps(Control* ctl, unsigned tile_cap, unsigned run_cap, un
   }
 }
 
+bool same_columns(const spgemm_csr* A, const spgemm_csr* B) { return A->colidx == B->colidx && A->nnz == B->nnz; }
+
 // The order of the operands' entries: kept with the plan (plan = 1), or compared with it.
 void sum_order(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const spgemm_csr* B, int plan) {
   const int64_t most = A->nnz > B->nnz ? A->nnz : B->nnz;
-  const bool one = A->colidx == B->colidx && A->nnz == B->nnz;
   hipLaunchKernelGGL(k_order_sum, dim3(grid_for(most, kOrderTile, kOrderParts)), dim3(kOrderThreads), 0, h->stream, A->nnz, A->colidx, B->nnz,
-                     one ? (const int32_t*)nullptr : B->colidx, p->ctl, plan);
+                     same_columns(A, B) ? (const int32_t*)nullptr : B->colidx, p->ctl, plan);
 }
 
 // plan_leaves: the plan goes to the caller, whose numeric phases may bring the entries in another order.
@@ -477,7 +483,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     rc = alloc_dense_lists(h, p, B, host, &tile_cap, &run_cap, &list_want);
   }
   if (rc) return rc;
-  alloc_optional(h, p, B, host, list_want, sizeof(T), staged > 0);
+  alloc_optional(h, p, B, host, list_want, sizeof(T), staged > 0, plan_leaves);
   p->order_kept = plan_leaves && (p->records || p->esc_words[0] || p->esc_words[1]);
   if (p->order_kept) {
     Timer t(h, SPGEMM_K_COUNT);
@@ -562,9 +568,10 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   // On a plan that the caller holds: are the entries in the order of the plan?  If not, the kernels that need it end at once, and
   // k_other_order behind them, which ends at once otherwise (4 us), does their rows.
   const bool check = p->order_kept && (words0 || words1 || p->recorded);
+  const bool same = same_columns(A, B), alone = A->nnz + (same ? 0 : B->nnz) <= kOrderAlone;
   {
     Timer t(h, SPGEMM_K_NUM_ESC);
-    if (check) sum_order(h, p, A, B, 0);
+    if (check && !alone) sum_order(h, p, A, B, 0);
     if (words0)
       hipLaunchKernelGGL((p->desc ? k_esc_num<16, 32, T, true> : k_esc_num<16, 32, T, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0,
                          A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[0], c_rp, c_col, c_val);
@@ -592,7 +599,7 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
     if (check) {
       const unsigned w0 = words0 ? grid_for(hist[0], 16, cap_small) : 0, w1 = words1 ? grid_for(hist[1], 4, cap_small) : 0, w2 = p->recorded ? grid_for(hist[2], 4, cap_small) : 0;
       hipLaunchKernelGGL(k_other_order<T>, dim3(w0 + w1 + w2), dim3(256), other_order_lds_bytes<T>(), s, w0, w1, w2, p->perm_num, p->ctl, p->ip, A->rowptr,
-                         A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, pack128, B->nnz, B->cols);
+                         A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, pack128, A->nnz, B->nnz, B->cols, alone ? 1 : 0, same ? 1 : 0);
     }
     if (hist[3])
       hipLaunchKernelGGL((k_hash<256, 11, T, true>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),

@@ -132,6 +132,12 @@ def reordered(M, rng):
     return W.CSR(M.rows, M.cols, M.rowptr.copy(), M.colidx[at], M.values[at])
 
 
+def repeated(M, times):
+    """The rows of M so many times over."""
+    rowptr = np.concatenate([[0], np.cumsum(np.tile(np.diff(M.rowptr), times))]).astype(np.int64)
+    return W.CSR(M.rows * times, M.cols, rowptr, np.tile(M.colidx, times), W.draw_values(M.nnz * times, -1.0, 1.0, M.values.dtype, 3, 1))
+
+
 def numeric_on_a_plan(plan_of, calls, what, force=0, offset=0):
     """One plan for the operands plan_of, the numeric phase for each of calls in turn, every result compared."""
     import torch
@@ -162,7 +168,7 @@ def numeric_on_a_plan(plan_of, calls, what, force=0, offset=0):
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 @pytest.mark.parametrize("offset", [0, 1])
-@pytest.mark.parametrize("kind", ["recorded", "short", "described", "dense too"])
+@pytest.mark.parametrize("kind", ["recorded", "small", "short", "described", "dense too"])
 def test_entries_in_another_order_on_a_kept_plan(kind, dtype, offset):
     """The structure is the same whatever the order of a row's entries: a matrix that is assembled again may come in another one."""
     rng = np.random.default_rng(51)
@@ -171,7 +177,10 @@ def test_entries_in_another_order_on_a_kept_plan(kind, dtype, offset):
     elif kind == "dense too":   # (every class of rows; an ascending B has to stay so where rows are dense, so this one is not)
         A, B = W.random_csr(600, 500, 40, 52, dtype=dtype), W.random_csr(500, 4000, 30, 53, dtype=dtype, sort_rows=False)
     else:
-        A, B = short_operands(400 if kind == "short" else 600_000, 3000, dtype, True)
+        A, B = short_operands(600_000 if kind == "described" else 400, 3000, dtype, True)
+        if kind != "small":   # (a plan that its caller holds has sorted words for short rows of a million products and more)
+            A = repeated(A, 180)
+            assert int(np.diff(B.rowptr)[A.colidx].sum()) > 1 << 20
     A2, B2 = reordered(A, rng), reordered(B, rng)
     numeric_on_a_plan((A, B), [(A2, B), (A, B2), (A, B), (A2, B2), (A, B)], kind, offset=offset)
 
@@ -248,3 +257,28 @@ def test_numeric_phase_under_capture_on_a_kept_plan():
         assert_matches_oracle(X, Y, (rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy()), what=f"replay {n}")
         sg.spgemm(sg.Handle(), dA, dB)   # (other work between the replays)
     plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("sort_b", [True, False])
+@pytest.mark.parametrize("b_rows,cols", [(400, 300), (600_000, 300), (400, 1 << 23), (600_000, 1 << 25), (400, (1 << 25) + 1), (600_000, 40_000_000)])
+def test_short_rows_in_one_call(b_rows, cols, dtype, sort_b):
+    """As test_short_rows; the plan of a single call has sorted words however few products there are."""
+    A, B = short_operands(b_rows, cols, dtype, sort_b)
+    for options in ({}, {COLUMN_LIST: 20_000}):
+        assert_matches_oracle(A, B, gpu_product(A, B, via="single", options=options), what=f"rows={b_rows} cols={cols} {options}")
+
+
+@pytest.mark.parametrize("entries", [16_383, 16_384, 16_385])
+def test_order_of_few_entries(entries):
+    """Up to 16 384 entries of both operands the kernel that would do the rows again looks at the order by itself."""
+    rng = np.random.default_rng(entries)
+    B = csr([np.sort(rng.choice(3000, size=20, replace=False)) for _ in range(300)], 3000, np.float64, 81)
+    lens = np.full(800, (entries - B.nnz) // 800)
+    lens[:(entries - B.nnz) % 800] += 1
+    A = csr([rng.choice(300, size=n, replace=False) for n in lens], 300, np.float64, 82)
+    assert A.nnz + B.nnz == entries
+    last = W.CSR(A.rows, A.cols, A.rowptr, A.colidx.copy(), A.values.copy())
+    for v in (last.colidx, last.values):
+        v[[-1, -2]] = v[[-2, -1]]
+    numeric_on_a_plan((A, B), [(A, B), (last, B), (A, reordered(B, rng)), (A, B)], f"{entries} entries")
