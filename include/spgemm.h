@@ -126,10 +126,12 @@ enum {
   SPGEMM_OPT_DIRECT_MIN = 3,
   /* 1 (default): the plan keeps the column indices of the dense workspace's ranked tiles
    * (up to a third of the free device memory), which saves the numeric phase one pass over
-   * those tiles' products; rows that do not fit fall back to the two-pass route.  It also keeps the
-   * order of the products of short rows and where the rows of B are (up to a quarter of the free memory; above 64 MB only as far as the
-   * largest C that the product can have still fits beside it), which saves the numeric phase their sort or
-   * hash.  0: neither.  A value of 4096 or more limits each of the two to that many bytes. */
+   * those tiles' products; rows that do not fit fall back to the two-pass route.  For short rows it
+   * keeps where their rows of B are and the order of their products (up to a quarter of the free
+   * memory together; above 64 MB only as far as the largest C that the product can have still fits
+   * beside it), which saves the numeric phase their sort or hash.  0: none of it (also for a caller
+   * who only wants the sizes: the symbolic phase alone is faster without).  A value of 4096 or more
+   * limits the list, and what short rows have, to that many bytes each. */
   SPGEMM_OPT_COLUMN_LIST = 4,
   /* 1 (default): for an ascending B the plan holds a table of per-row offsets at every 8192nd
    * column (when it fits 1 GiB), which turns the search for a tile's piece of a B row into two
