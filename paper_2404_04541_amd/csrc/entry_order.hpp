@@ -5,8 +5,7 @@
 // end at once and k_other_order does their rows without it.
 // Bound: memory, one pass over the columns (of one operand where both are the same array), and the launches.  Numeric phase on a
 // kept plan, 27-point stencil (fp64): 61^3 rows 256 -> 268 us, 128^3 rows 2.19 -> 2.24 ms; in another order 475 us and 4.36 ms
-// (without any plan of the order, 546 us and 4.79 ms).  Summed by extra workgroups of the rows' kernel instead, the code made for
-// its rows was 10 % slower even where nothing was summed.
+// (without any plan of the order, 546 us and 4.79 ms).
 #pragma once
 #include "common.hpp"
 
@@ -60,39 +59,45 @@ __device__ __forceinline__ unsigned long long order_share(int64_t na, const int3
   return s;   // (of the wave)
 }
 
-// Up to this many entries (of both operands) every workgroup of k_other_order sums by itself whether it has anything to do, which
-// saves the launch of k_order_sum.  Numeric phase, us with the launch | without: 4 096 entries 17.4 | 13.9, 10 600 entries 19.3 | 15.9,
-// 39 300 entries 18.3 | 21.4.
-constexpr int64_t kOrderAlone = 16384;
-__device__ __forceinline__ bool order_differs_alone(int64_t na, const int32_t* __restrict__ a_col, int64_t nb, const int32_t* __restrict__ b_col, const Control* ctl) {
-  __shared__ unsigned long long part[256 / kWave];
-  const unsigned long long s = order_share<256>(na, a_col, nb, b_col, 0, 1);
-  if (lane_id() == 0) part[threadIdx.x >> 6] = s;
-  __syncthreads();
-  const unsigned long long all = part[0] + part[1] + part[2] + part[3];
-  return all << 8 != (ctl->order & ~255ULL);
-}
-
 // One word for both operands: their sums' low 56 bits above the number of workgroups that have
 // added theirs, so that a workgroup sends one atomic and the last one knows the whole (three atomics each, to sums and a counter:
-// 11 us for 6 M entries, and 15 us with twice the workgroups; now 8 us).  plan: the word is the plan's, otherwise it is compared with it.
+// 11 us for 6 M entries, and 15 us with twice the workgroups; now 8 us).  s: a wave's share, from every wave of the workgroup.  plan:
+// the word is the plan's, otherwise it is compared with it, and *differs says how that came out.
 constexpr int kOrderParts = 128;   // at most
 static_assert(kOrderParts < 256, "the count has eight bits");
-__global__ __launch_bounds__(kOrderThreads) void k_order_sum(int64_t na, const int32_t* __restrict__ a_col, int64_t nb, const int32_t* __restrict__ b_col,
-                                                             Control* ctl, int plan) {
-  __shared__ unsigned long long part[kOrderThreads / kWave];
-  unsigned long long s = order_share<kOrderThreads>(na, a_col, nb, b_col, blockIdx.x, gridDim.x);
+template <int THREADS>
+__device__ __forceinline__ void order_add(unsigned long long s, int parts, Control* ctl, int plan, int* differs) {
+  __shared__ unsigned long long part[THREADS / kWave];
   if (lane_id() == 0) part[threadIdx.x >> 6] = s;
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < kOrderThreads / kWave; ++w) s += part[w];
+    for (int w = 1; w < THREADS / kWave; ++w) s += part[w];
     const unsigned long long mine = (s << 8) + 1, before = atomicAdd(&ctl->order_now, mine);
-    if ((before & 255) == gridDim.x - 1) {
+    if ((before & 255) == (unsigned long long)(parts - 1)) {
       ctl->order_now = 0;   // (for the next time)
-      if (plan) ctl->order = before + mine;
-      else ctl->order_differs = before + mine != ctl->order ? 1 : 0;
+      const unsigned long long all = (before + mine) & ~255ULL;
+      if (plan) ctl->order = all;
+      else *differs = all != ctl->order ? 1 : 0;
     }
   }
 }
+
+__global__ __launch_bounds__(kOrderThreads) void k_order_sum(int64_t na, const int32_t* __restrict__ a_col, int64_t nb, const int32_t* __restrict__ b_col,
+                                                             Control* ctl, int plan) {
+  order_add<kOrderThreads>(order_share<kOrderThreads>(na, a_col, nb, b_col, blockIdx.x, gridDim.x), gridDim.x, ctl, plan, &ctl->order_differs);
+}
+
+// What the numeric kernel of recorded rows needs to look at the order with `parts` workgroups of its own (it does its rows meanwhile:
+// whatever the order, they stay in bounds, for what they index comes from the plan and from row lengths).
+struct OrderOperands {
+  int parts;
+  int64_t na, nb;
+  const int32_t *a_col, *b_col;   // b_col null: as a_col
+};
+// Up to this many entries that saves the launch of k_order_sum; beyond, the rows' kernel loses more (its code with the sum in it takes
+// a tenth longer for the rows).  Numeric phase of stencils, us with the launch | inside | without any check: 10 600 entries 19.0 | 13.6 | 11.6,
+// 0.10 M 21.6 | 16.1 | 13.5, 0.83 M 47.9 | 44.7 | 39.1, 1.6 M 71.7 | 71.3 | 63.1, 2.9 M 144 | 148 | 133.
+constexpr int64_t kOrderInside = 1 << 20;
+constexpr int kOrderInsideTile = 256 * kOrderQuads * 4;
 
 }  // namespace spg

@@ -289,16 +289,16 @@ constexpr size_t hash_lds_bytes() {
 }
 
 // The rows whose order the plan holds (numeric bins 0, 1 and 2: wgs0, wgs1, wgs2 workgroups), again and without it, when the
-// operands' entries come in another order; ends at once otherwise.  alone: it finds that out by itself (b_same: B's columns are A's).
+// operands' entries come in another order; ends at once otherwise.  later: order_later
+// says whether they do, otherwise order_differs.
 template <typename T>
 __global__ __launch_bounds__(256) void k_other_order(unsigned wgs0, unsigned wgs1, unsigned wgs2, const int* __restrict__ perm, const Control* __restrict__ ctl,
                                                      const int* __restrict__ ip_row, const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                      const T* __restrict__ a_val, const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col,
                                                      const T* __restrict__ b_val, const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col,
-                                                     T* __restrict__ c_val, int pack0, int pack1, int64_t a_nnz, int64_t b_nnz, int64_t n_cols, int alone, int b_same) {
+                                                     T* __restrict__ c_val, int pack0, int pack1, int64_t b_nnz, int64_t n_cols, int later) {
   extern __shared__ __align__(16) unsigned char smem[];
-  if (ctl->error) return;
-  if (!(alone ? order_differs_alone(a_nnz, a_col, b_nnz, b_same ? (const int32_t*)nullptr : b_col, ctl) : ctl->order_differs != 0)) return;
+  if (ctl->error || !(later ? ctl->order_later : ctl->order_differs)) return;
   unsigned wg = blockIdx.x;
   if (wg < wgs0) {
     esc_rows<16, 32, T>(reinterpret_cast<EscRowsLds<16, 32, T>*>(smem), wg, wgs0, perm, ctl, 1, 0, a_rp, a_col, a_val, b_rp, b_col, b_val, c_rp, c_col, c_val, pack0, b_nnz);

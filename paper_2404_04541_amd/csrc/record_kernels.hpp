@@ -19,6 +19,7 @@
 // of 61^3 rows, numeric phase on a kept plan: 480 -> 255 us.
 #pragma once
 #include "common.hpp"
+#include "entry_order.hpp"
 #include "row_chain.hpp"
 
 namespace spg {
@@ -227,16 +228,26 @@ __global__ __launch_bounds__(256) void k_sym_wave(const int* __restrict__ perm, 
 }
 
 // Numeric pass over the recorded rows of a bin, a wave per row; rows without a record are left to the hash workspace.
-template <typename T>
-__global__ __launch_bounds__(256) void k_num_recorded(const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const int* __restrict__ ip_row,
+// SUM: the first order.parts workgroups look at the order of the entries (order_later) while the others do the rows.
+template <typename T, bool SUM>
+__global__ __launch_bounds__(256) void k_num_recorded(const int* __restrict__ perm, std::conditional_t<SUM, Control, const Control>* __restrict__ ctl, int bin, const int* __restrict__ ip_row,
                                                       const unsigned* __restrict__ records, const int* __restrict__ record_of,
                                                       const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const T* __restrict__ a_val,
                                                       const int64_t* __restrict__ b_rp, const T* __restrict__ b_val, int64_t b_nnz,
-                                                      const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val) {
+                                                      const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val, const OrderOperands order) {
   __shared__ double s_acc[4][256];   // (a rank is a byte)
   __shared__ QuadEntry s_ent[4][kQuadEntries];
   __shared__ T s_av[4][kQuadEntries];
-  if (ctl->error || ctl->order_differs) return;
+  if (ctl->error || (!SUM && ctl->order_differs)) return;
+  unsigned wg = blockIdx.x, wgs = gridDim.x;
+  if constexpr (SUM) {
+    if ((int)wg < order.parts) {
+      order_add<256>(order_share<256>(order.na, order.a_col, order.nb, order.b_col, wg, order.parts), order.parts, ctl, 0, &ctl->order_later);
+      return;
+    }
+    wg -= order.parts;
+    wgs -= order.parts;
+  }
   const unsigned first = ctl->offset[1][bin];
   const unsigned nrows = ctl->offset[1][bin + 1] - first;
   const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
@@ -250,8 +261,8 @@ __global__ __launch_bounds__(256) void k_num_recorded(const int* __restrict__ pe
     if (row >= 0) { const Run<int64_t, 2> v = load_run<int64_t, 2>(c_rp + row); lo = v.v[0]; n = v.v[1] - v.v[0] < kNumHashSmall ? (int)(v.v[1] - v.v[0]) : kNumHashSmall; }
   };
   auto value = [&](int64_t a, int n) { return lane < n ? a_val[a + lane] : T(0); };
-  RowChain<kWave> ch{perm + first, a_rp, a_col, b_rp, nullptr, nrows, gridDim.x * 4};
-  unsigned row_at = blockIdx.x * 4 + g;
+  RowChain<kWave> ch{perm + first, a_rp, a_col, b_rp, nullptr, nrows, wgs * 4};
+  unsigned row_at = wg * 4 + g;
   ch.start(row_at);
   int at0 = record(ch.row), at1 = record(ch.row1), at2 = record(ch.row2);
   int64_t out0, out1, out2;
@@ -260,7 +271,7 @@ __global__ __launch_bounds__(256) void k_num_recorded(const int* __restrict__ pe
   range(ch.row1, out1, n1);
   range(ch.row2, out2, n2);
   T av0 = value(ch.a0, ch.d), av1 = value(ch.a01, ch.d1);
-  for (; row_at < nrows; row_at += gridDim.x * 4) {
+  for (; row_at < nrows; row_at += wgs * 4) {
     const RowChain<kWave>::Ahead nx = ch.fetch();
     int64_t out3;
     int n3;

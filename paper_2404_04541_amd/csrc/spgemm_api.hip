@@ -568,10 +568,13 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   // On a plan that the caller holds: are the entries in the order of the plan?  If not, the kernels that need it end at once, and
   // k_other_order behind them, which ends at once otherwise (4 us), does their rows.
   const bool check = p->order_kept && (words0 || words1 || p->recorded);
-  const bool same = same_columns(A, B), alone = A->nnz + (same ? 0 : B->nnz) <= kOrderAlone;
+  // (the kernel of recorded rows looks at the order beside its rows where the entries are few: the kernels that need the plan's
+  // order then do their rows whatever it is)
+  const bool same = same_columns(A, B);
+  const bool inside = check && p->recorded && A->nnz + (same ? 0 : B->nnz) <= kOrderInside;
   {
     Timer t(h, SPGEMM_K_NUM_ESC);
-    if (check && !alone) sum_order(h, p, A, B, 0);
+    if (check && !inside) sum_order(h, p, A, B, 0);
     if (words0)
       hipLaunchKernelGGL((p->desc ? k_esc_num<16, 32, T, true> : k_esc_num<16, 32, T, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0,
                          A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[0], c_rp, c_col, c_val);
@@ -589,9 +592,18 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
     Timer t(h, SPGEMM_K_NUM_HASH);
     // (rows of the bin with a record, then the ones without; a row that has a record is in this bin: it has more than
     // kEscLargeCap products, or hashing is forced, and at most kNumHashSmall entries)
-    if (p->recorded)
-      hipLaunchKernelGGL(k_num_recorded<T>, dim3(grid_for(hist[2], 4, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 2, p->ip, p->records, p->record_of,
-                         A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val);
+    if (p->recorded) {
+      const unsigned grid = grid_for(hist[2], 4, cap_small);
+      if (inside) {
+        const int64_t most = A->nnz > B->nnz ? A->nnz : B->nnz;
+        const OrderOperands order{(int)grid_for(most, kOrderInsideTile, kOrderParts), A->nnz, B->nnz, A->colidx, same ? nullptr : B->colidx};
+        hipLaunchKernelGGL((k_num_recorded<T, true>), dim3(grid + order.parts), dim3(256), 0, s, p->perm_num, p->ctl, 2, p->ip, p->records, p->record_of,
+                           A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val, order);
+      } else {
+        hipLaunchKernelGGL((k_num_recorded<T, false>), dim3(grid), dim3(256), 0, s, p->perm_num, p->ctl, 2, p->ip, p->records, p->record_of,
+                           A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val, OrderOperands{});
+      }
+    }
     if (hist[2] > p->recorded)
       hipLaunchKernelGGL((k_hash<64, 8, T, true>), dim3(grid_for(hist[2], 4, cap_small)), dim3(256), lds_hash_small, s,
                          p->perm_num, p->ctl, 1, 2, p->ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, (int*)nullptr,
@@ -599,7 +611,7 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
     if (check) {
       const unsigned w0 = words0 ? grid_for(hist[0], 16, cap_small) : 0, w1 = words1 ? grid_for(hist[1], 4, cap_small) : 0, w2 = p->recorded ? grid_for(hist[2], 4, cap_small) : 0;
       hipLaunchKernelGGL(k_other_order<T>, dim3(w0 + w1 + w2), dim3(256), other_order_lds_bytes<T>(), s, w0, w1, w2, p->perm_num, p->ctl, p->ip, A->rowptr,
-                         A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, pack128, A->nnz, B->nnz, B->cols, alone ? 1 : 0, same ? 1 : 0);
+                         A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, pack128, B->nnz, B->cols, inside ? 1 : 0);
     }
     if (hist[3])
       hipLaunchKernelGGL((k_hash<256, 11, T, true>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),

@@ -269,14 +269,18 @@ def test_short_rows_in_one_call(b_rows, cols, dtype, sort_b):
         assert_matches_oracle(A, B, gpu_product(A, B, via="single", options=options), what=f"rows={b_rows} cols={cols} {options}")
 
 
-@pytest.mark.parametrize("entries", [16_383, 16_384, 16_385])
-def test_order_of_few_entries(entries):
-    """Up to 16 384 entries of both operands the kernel that would do the rows again looks at the order by itself."""
+@pytest.mark.parametrize("entries", [10_000, (1 << 20) - 1, 1 << 20, (1 << 20) + 1])
+def test_order_beside_the_rows_and_before_them(entries):
+    """Up to 2^20 entries of both operands the kernel of recorded rows looks at their order beside its rows."""
     rng = np.random.default_rng(entries)
     B = csr([np.sort(rng.choice(3000, size=20, replace=False)) for _ in range(300)], 3000, np.float64, 81)
-    lens = np.full(800, (entries - B.nnz) // 800)
-    lens[:(entries - B.nnz) % 800] += 1
-    A = csr([rng.choice(300, size=n, replace=False) for n in lens], 300, np.float64, 82)
+    rows = max(1, (entries - B.nnz) // 20)
+    lens = np.full(rows, (entries - B.nnz) // rows)
+    lens[:(entries - B.nnz) % rows] += 1
+    starts = rng.integers(0, 300, size=rows)
+    colidx = (np.repeat(starts, lens) + 7 * (np.arange(lens.sum()) - np.repeat(np.cumsum(lens) - lens, lens))) % 300   # (distinct in a row)
+    A = W.CSR(rows, 300, np.concatenate([[0], np.cumsum(lens)]).astype(np.int64), colidx.astype(np.int32),
+              W.draw_values(int(lens.sum()), -1.0, 1.0, np.float64, 82, 1))
     assert A.nnz + B.nnz == entries
     last = W.CSR(A.rows, A.cols, A.rowptr, A.colidx.copy(), A.values.copy())
     for v in (last.colidx, last.values):
