@@ -103,7 +103,7 @@ typedef struct {
   int64_t dense_tiles;        /* column tiles planned for the dense numeric kernel */
   int64_t dense_direct_tiles; /* of those, tiles accumulated by column (one pass) */
   int64_t dense_runs;         /* work items (runs of tiles of one row) */
-  int64_t dense_search_tiles; /* of the tiles, whole short rows whose ranks come from bisecting the column list */
+  int64_t dense_search_tiles; /* rows whose tiles hold the whole short row and find ranks by bisecting the column list */
   int64_t plan_bytes;         /* device memory the plan holds (per-row arrays, tile lists, block table, structure list, order of short rows) */
   int64_t plan_list_bytes;    /* of those, what the structure list (columns or flag words of the dense rows) was given */
   int64_t plan_list_used;     /* ... and what the symbolic phase filled of it */
@@ -138,8 +138,9 @@ enum {
    * loads.  0: never build it; pieces are found by bisection. */
   SPGEMM_OPT_BLOCK_TABLE = 5,
   /* A short dense row (at most 11264 entries, columns in the plan's list) whose products per entry do
-   * not exceed this value is accumulated in one "searched" tile: a product finds its sum by bisection of
-   * the row's column list, whatever the width of the row.  0: never.  Default 4. */
+   * not exceed this value is accumulated in one "searched" tile, or two, where that saves more than half of
+   * its tiles: a product finds its sum by bisection of the row's column list, whatever the width of the row.
+   * 0: never.  Default 4. */
   SPGEMM_OPT_SEARCH_RATIO = 6
 };
 

@@ -51,6 +51,7 @@ struct Control {
   long long nnz_c;
   unsigned long long order, order_now;   // the order of the entries (k_order_sum): the plan's, and the one being added up
   int order_later;                // as order_differs, found out beside the recorded rows
+  int unlisted;                   // 1: the structure of some row of the dense classes has no place in the plan's list
   int order_differs;              // 1: the entries of the numeric phase's operands come in another order than the plan's
 #ifdef SPG_PHASE_CLOCKS
   unsigned long long clk[2][32];   // [0] dense symbolic, [1] dense numeric: shader clocks per phase, summed over workgroups

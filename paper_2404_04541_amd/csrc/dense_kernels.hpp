@@ -1,14 +1,21 @@
 // Dense LDS workspaces for long rows (Gustavson's flag list / coordinate list of the
-// paper's section 4.4, and the dense first-order workspace of section 7.2), one workgroup
-// of 1024 threads per row.
+// paper's section 4.4, and the dense first-order workspace of section 7.2): the symbolic
+// kernel and what it shares with the numeric one (tile_kernels.hpp).
 //
-// Symbolic (k_sym_dense): a flag list with one bit per column (2^20 columns per span in
+// Symbolic (k_sym_dense), a workgroup per row: a flag list with one bit per column (up to 2^20 columns per span in
 //   128 KB of LDS); products set bits, the row's size is the population count.  From the
 //   finished flag list the kernel also plans the row's numeric work: the column space is cut
 //   at multiples of kBlkCols columns into tiles, each small enough for the numeric workspace,
 //   and the row's column structure goes to the plan (decoded columns, or the flag words of
 //   direct blocks), so that the numeric phase need not find it again.
-// Numeric (k_num_dense), one tile at a time, one pass over the tile's products:
+//   The flag list takes the LDS that the matrix's width needs: a workgroup of 16 waves where that is more than 64 KB, of 8
+//   waves otherwise, two or three of them on a compute unit (sym_dense_workgroups).  What a row costs beside its products
+//   (clearing and counting the flags, the round trips for its entries and its shares of the lists, decoding) was more than
+//   half of the kernel when one workgroup had the compute unit to itself.  The flags are counted with a lane on every fourth
+//   word, a block per wave (32 consecutive words per thread collided on the banks: 21 % of the kernel at scale 14).
+//   R-MAT squared, fp32, ms with one workgroup of 16 waves | now: scale 14 0.210 | 0.155, scale 17 2.75 | 1.30, scale 19
+//   15.8 | 12.0; deduplication sweep, 10000 columns, 1.13 | 0.74.
+// Numeric (k_num_tiles), one tile at a time, one pass over the tile's products:
 //   direct tile (one block of kBlkCols columns in which the row is dense): sums live in a
 //     dense array indexed by column; the flags say which exist; flags and sums are compressed
 //     at the end ("boolean indexing" in the paper's words).
@@ -17,7 +24,7 @@
 //     column j - LDS holds only columns that exist in C and the finished tile is already in
 //     ascending column order.  Flags and ranks come from the plan's column list; without one,
 //     a first pass over the products rebuilds them.
-//   searched tile (a whole short row): the row's columns sit in LDS and a product finds its
+//   searched tile (a short row, or half of one): the row's columns sit in LDS and a product finds its
 //     rank by bisection, so the tile's width does not matter.
 //   The piece of B row k that falls into a tile is found with two loads from a table of
 //   per-row block offsets (ascending B rows), so a pass touches only its own products.
@@ -26,13 +33,11 @@
 
 namespace spg {
 
-constexpr int kDenseThreads = 1024;
-constexpr int kDenseWaves = kDenseThreads / kWave;
 constexpr int kSymFlagWords = 32768;    // 2^20 columns per symbolic span (128 KB)
 constexpr int kBlkCols = 8192;          // tile boundaries are multiples of this many columns
 constexpr int kBlkShift = 13;
 constexpr int kSpanBlocks = kSymFlagWords * 32 / kBlkCols;   // 128 blocks per symbolic span
-constexpr int kTileBudget = 135 * 1024; // LDS bytes of one numeric tile (flags + ranks + sums)
+constexpr int kTileBudget = 66 * 1024; // LDS bytes of one numeric tile (flags + ranks + sums)
 constexpr int kRankBlkBytes = kBlkCols / 32 * 8;   // flag word + rank per 32 columns of a ranked tile
 constexpr int kRankEntryBytes = 8;                // sum per entry of a ranked tile (its column goes straight to C)
 constexpr int kDirectMinDefault = 6144; // a block with at least this many entries becomes a direct tile
@@ -43,17 +48,14 @@ constexpr int kRunSlab = 256;           // (run records: at most; see run_slab)
 constexpr int kDirectBit = 1 << 30;     // in TileRec::cnt
 constexpr int kSearchBit = 1 << 29;     // in TileRec::cnt: a searched tile (ranks by bisection of the column list)
 constexpr int kCountMask = kSearchBit - 1;
-constexpr int kSearchCap = 11264;       // entries of a searched tile (column 4 B + sum 8 B each)
-constexpr int kSegCap = 1024;           // A entries described in LDS at a time (numeric)
+constexpr int kSearchCap = 5632;      // entries of a searched tile (column 4 B + sum 8 B each)
+constexpr int kSearchRow = 2 * kSearchCap;   // entries of a row that becomes searched tiles: one, or two
 constexpr int kBlkWords = kBlkCols / 32;
-constexpr int kSymPieces = 1024;         // A entries that the symbolic kernel describes in LDS at a time
-constexpr int kListStage = kSymPieces * 5 / kDenseWaves;   // entries that a wave gathers in LDS (the piece walker's, free by then) before writing them to the column list
-constexpr int kListBatch = 4;           // column-list loads in flight per thread
+constexpr int kListStage = 5 * kWave;   // entries that a wave gathers in LDS (the piece walker's, free by then) before writing them to the column list
 // every tile kind must fit the tile area of the numeric kernel
 static_assert((long long)kSearchCap * 12 <= kTileBudget, "searched tile: 4 B column + 8 B sum per entry");
-static_assert((long long)kBlkCols * 12 + kBlkCols / 8 <= kTileBudget, "direct tile: sums, columns by rank, flag words");
+static_assert((long long)kBlkCols * 8 + kBlkCols / 8 <= kTileBudget, "direct tile: sums, flag words");
 static_assert(kRankBlkBytes + 8LL * kBlkCols <= kTileBudget, "ranked tile: one block must fit even when it is full");
-constexpr int kRegSegs = 2;             // segments of A entries that the numeric kernel keeps in registers
 constexpr long long kListBias = 1LL << 40;   // RunRec::list holds position + bias (so that -1 can mean "none")
 constexpr long long kListFlagWords = 1LL << 60;   // RunRec::list: the row's structure is kept as flag words, not as columns
 constexpr int kFlagWordsNum = 1, kFlagWordsDen = 1;   // flag words are kept when words * Num <= entries * Den (measured: best near one entry per word)
@@ -66,6 +68,8 @@ __host__ __device__ __forceinline__ int span_flag_words(int64_t n_cols, int64_t 
   const int64_t left = n_cols - c0, span = (int64_t)kSymFlagWords * 32;
   return (int)(((left < span ? left : span) + 31) >> 5);
 }
+// Flag words that the symbolic kernel keeps in LDS: those of a span, in whole blocks.
+__host__ __device__ __forceinline__ int sym_flag_words(int64_t n_cols) { return (span_flag_words(n_cols, 0) + kBlkWords - 1) / kBlkWords * kBlkWords; }
 __host__ __device__ __forceinline__ int span_rank_slots(int words) { return (((words + kGrpWords - 1) / kGrpWords) + 3) & ~3; }
 
 // Stores and loads of data that passes through the numeric kernel once (the result, the plan's
@@ -100,12 +104,14 @@ struct TileRec { int b0, b1, cnt, out; };     // blocks [b0, b1), entries (| kDi
 struct RunRec { int row; unsigned first; int count, d; long long a0, list; };
 
 // Per-workgroup bookkeeping of the piece walker below.
+template <int WAVES>
 struct RowScratch {
-  long long start[kSymPieces];   // first B entry of each A entry's piece
-  int plen[kSymPieces];          // piece length
-  int cpre[kSymPieces + 1];      // exclusive prefix of quad counts
-  int more[kSymPieces + 1];      // (the column decode stages kListStage entries per wave from `start` to here)
-  int red[2 * kDenseWaves];
+  static constexpr int kPieces = WAVES * kWave;   // A entries described in LDS at a time: one per thread
+  long long start[kPieces];   // first B entry of each A entry's piece
+  int plen[kPieces];          // piece length
+  int cpre[kPieces + 1];      // exclusive prefix of quad counts
+  int more[kPieces + 1];      // (the column decode stages kListStage entries per wave from `start` to here)
+  int red[2 * WAVES];
   int s_row;
   int pad;
   unsigned long long span_ip;       // products streamed since the owner last cleared it
@@ -115,17 +121,18 @@ struct RowScratch {
 // Exclusive scans of two ints over the workgroup, with totals.  Contains barriers.
 // The 16 wave totals are scanned by every wave itself: lane w reads the total of wave w, a DPP row
 // scan adds them up, and the wave takes its own prefix and the grand total with readlane.
+template <int WAVES>
 __device__ __forceinline__ void block_excl_scan2(int a, int b, int& ea, int& eb, int& ta, int& tb, int* red) {
-  static_assert(kDenseWaves == 16, "one DPP row of wave totals");
+  static_assert(WAVES == 4 || WAVES == 8 || WAVES == 16, "one DPP row of wave totals, or the first lanes of one");
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ia = wave_incl_scan(a), ib = wave_incl_scan(b);
   __syncthreads();
-  if (lane_id() == kWave - 1) { red[wave] = ia; red[kDenseWaves + wave] = ib; }
+  if (lane_id() == kWave - 1) { red[wave] = ia; red[WAVES + wave] = ib; }
   __syncthreads();
-  const int l = lane_id() & (kDenseWaves - 1);
-  const int sa = group_incl_scan<16>(red[l]), sb = group_incl_scan<16>(red[kDenseWaves + l]);
-  ta = __builtin_amdgcn_readlane(sa, kDenseWaves - 1);
-  tb = __builtin_amdgcn_readlane(sb, kDenseWaves - 1);
+  const int l = lane_id() & (WAVES - 1);   // (the lanes behind WAVES repeat the totals: only the first ones are looked at)
+  const int sa = group_incl_scan<16>(red[l]), sb = group_incl_scan<16>(red[WAVES + l]);
+  ta = __builtin_amdgcn_readlane(sa, WAVES - 1);
+  tb = __builtin_amdgcn_readlane(sb, WAVES - 1);
   const int pa = wave ? __builtin_amdgcn_readlane(sa, wave - 1) : 0;
   const int pb = wave ? __builtin_amdgcn_readlane(sb, wave - 1) : 0;
   ea = pa + ia - a;
@@ -169,20 +176,20 @@ struct Quad {
 // flight 26.5 ms, three 29.7, four 31.8: registers; the next one prefetched 25.9, but 1.69 for the sweep); without them the
 // next batch is prefetched (15.8 ms at scale 19 against 16.5).  At scale 20 the symbolic kernel lost a little against the chunks
 // (42.2 -> 43.7 ms), the numeric one gained 6 ms.
-template <bool WITH_VALUES, typename T, class G>
+template <int WAVES, bool WITH_VALUES, typename T, class G>
 __device__ __forceinline__ void quad_pass(int np, int nq, const PieceList<T> pl, const int32_t* __restrict__ b_col,
                                           const T* __restrict__ b_val, int64_t b_nnz, G g) {
   const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
   np = uni(np);
   nq = uni(nq);
   const int nb = (nq + kWave - 1) >> 6;
-  const int per = (nb + kDenseWaves - 1) / kDenseWaves;
+  const int per = (nb + WAVES - 1) / WAVES;
   int c = wave * per * kWave;
   const int cend = c + per * kWave < nq ? c + per * kWave : nq;
   if (c >= cend) return;
   int p;   // last piece whose first quad is <= c: among every sixteenth piece first, then among the sixteen
   {
-    static_assert(kSegCap <= 16 * kWave && kSymPieces <= 16 * kWave, "64 steps of sixteen pieces");
+    static_assert(WAVES <= 16, "64 steps of sixteen pieces");
     const int i0 = lane * 16;
     const int hi = __popcll(__ballot(i0 < np && pl.cpre[i0 < np ? i0 : 0] <= c)) - 1;
     const int i1 = hi * 16 + lane;
@@ -237,19 +244,19 @@ __device__ __forceinline__ void quad_pass(int np, int nq, const PieceList<T> pl,
 }
 
 // Walks every pair (A entry p of the row, B entry q of row a_col[p]) and hands the columns to f, a quad per lane at a time.
-// range(k, s, en) may narrow the piece [s, en) of B row k first.  Up to kSymPieces A entries are described at once (one per
-// thread).  Contains barriers: every thread of the workgroup must call it.
-template <class Range, class F>
+// range(k, s, en) may narrow the piece [s, en) of B row k first.  As many A entries as the workgroup has threads are described
+// at once.  Contains barriers: every thread of the workgroup must call it.
+template <int WAVES, class Range, class F>
 __device__ __forceinline__ void stream_columns(int64_t a0, int d, const int32_t* __restrict__ a_col,
                                                const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col, int64_t b_nnz,
-                                               RowScratch* rs, Range range, F f) {
+                                               RowScratch<WAVES>* rs, Range range, F f) {
   const int tid = threadIdx.x, lane = tid & 63;
-  static_assert(kSymPieces <= kDenseThreads, "a thread per described entry");
-  for (int base = 0; base < d; base += kSymPieces) {
+  constexpr int kPieces = RowScratch<WAVES>::kPieces;
+  for (int base = 0; base < d; base += kPieces) {
     const int e = base + tid;
     int64_t s = 0;
     int len = 0;
-    if (e < d && tid < kSymPieces) {
+    if (e < d) {
       const int k = a_col[a0 + e];
       const Run<int64_t, 2> bounds = load_run<int64_t, 2>(b_rp + k);
       s = bounds.v[0];
@@ -264,7 +271,7 @@ __device__ __forceinline__ void stream_columns(int64_t a0, int d, const int32_t*
       if (lane == 0 && wl) atomicAdd(&rs->span_ip, wl);
     }
     int at, eq, np, tq;
-    block_excl_scan2(len > 0 ? 1 : 0, (len + 3) >> 2, at, eq, np, tq, rs->red);
+    block_excl_scan2<WAVES>(len > 0 ? 1 : 0, (len + 3) >> 2, at, eq, np, tq, rs->red);
     if (len > 0) {
       rs->start[at] = s;
       rs->plen[at] = len;
@@ -273,7 +280,7 @@ __device__ __forceinline__ void stream_columns(int64_t a0, int d, const int32_t*
     __syncthreads();
     SPG_CLK(clk_mark(&rs->clk, 2); clk_add(&rs->clk, 18, 1); clk_add(&rs->clk, 19, (unsigned long long)tq);)
     if (tq > 0)
-      quad_pass<false, int>(np, tq, PieceList<int>{rs->start, rs->cpre, rs->plen, nullptr}, b_col, static_cast<const int*>(nullptr), b_nnz, f);
+      quad_pass<WAVES, false, int>(np, tq, PieceList<int>{rs->start, rs->cpre, rs->plen, nullptr}, b_col, static_cast<const int*>(nullptr), b_nnz, f);
     SPG_CLK(clk_mark(&rs->clk, 3);)
     __syncthreads();
     SPG_CLK(clk_mark(&rs->clk, 4);)
@@ -329,7 +336,8 @@ struct SearchRange {   // binary search in an ascending row
 };
 
 // LDS of the tile planner.
-struct TilePlan {
+struct __align__(16) TilePlan {
+  int grp[kSpanGroups];   // entries per group of kGrpWords flag words
   int blk_cnt[kSpanBlocks];
   int cum[kSpanBlocks + 1];
   int nxt[kSpanBlocks];
@@ -341,7 +349,6 @@ struct TilePlan {
   int span_out0;          // row_out when the span began
   long long list_base;    // position of the span's first entry (or first flag word) in the plan's list, -1 = none
   int list_words;         // > 0: the span's structure goes to the list as that many flag words instead of columns
-  int grp[kSpanGroups];   // entries per group of kGrpWords flag words
   unsigned long long list_used;   // list entries that this workgroup's rows have taken
 };
 
@@ -469,17 +476,20 @@ __device__ __forceinline__ int next_dense_row(const int* __restrict__ perm, Cont
   return *s_row;
 }
 
-__global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restrict__ perm, Control* ctl,
+template <int WAVES>
+__global__ __launch_bounds__(WAVES * kWave, WAVES == 8 ? 6 : 4) void k_sym_dense(const int* __restrict__ perm, Control* ctl,
                                                              const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                              const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col,
                                                              int64_t n_cols, const int* __restrict__ ip, int* __restrict__ cnt,
                                                              TileRec* __restrict__ tiles, RunRec* __restrict__ runs,
                                                              int32_t* __restrict__ col_list, int direct_min, int no_tiles_ip,
                                                              int search_ratio, const int* __restrict__ bp, int nb1, int64_t b_nnz) {
+  constexpr int kThreads = WAVES * kWave;
   extern __shared__ __align__(16) unsigned char smem[];
-  unsigned* flags = reinterpret_cast<unsigned*>(smem);                               // kSymFlagWords
-  RowScratch* rs = reinterpret_cast<RowScratch*>(smem + (size_t)kSymFlagWords * 4);
-  TilePlan* tp = reinterpret_cast<TilePlan*>(smem + (size_t)kSymFlagWords * 4 + sizeof(RowScratch));
+  const int flag_words = sym_flag_words(n_cols);
+  unsigned* flags = reinterpret_cast<unsigned*>(smem);                               // flag_words
+  RowScratch<WAVES>* rs = reinterpret_cast<RowScratch<WAVES>*>(smem + (size_t)flag_words * 4);
+  TilePlan* tp = reinterpret_cast<TilePlan*>(smem + (size_t)flag_words * 4 + sizeof(RowScratch<WAVES>));
   if (ctl->error) return;
   const bool sorted = ctl->b_sorted != 0;
   const int64_t span = (int64_t)kSymFlagWords * 32;
@@ -511,9 +521,8 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
       const int nb = (int)((c1 - c0 + kBlkCols - 1) >> kBlkShift);
       {
         uint4* f4 = reinterpret_cast<uint4*>(flags);
-        for (int w = tid; w < kSymFlagWords / 4; w += kDenseThreads) f4[w] = make_uint4(0, 0, 0, 0);
+        for (int w = tid; w < flag_words / 4; w += kThreads) f4[w] = make_uint4(0, 0, 0, 0);
       }
-      if (tid < kSpanBlocks) tp->blk_cnt[tid] = 0;
       if (tid == 0) { tp->span_out0 = tp->row_out; tp->list_base = -1; rs->span_ip = 0; }
       __syncthreads();
       SPG_CLK(clk_mark(&rs->clk, 1); clk_add(&rs->clk, 17, 1);)
@@ -541,25 +550,20 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
         stream_columns(a0, d, a_col, b_rp, b_col, b_nnz, rs, SearchRange{b_col, lo, hi}, mark);
       else
         stream_columns(a0, d, a_col, b_rp, b_col, b_nnz, rs, NoRange{}, mark);
-      // entries per block and per group: thread t owns kWordsPerThread consecutive flag words
+      // entries per block and per group: a wave takes a block, a lane four words of it, a group is a row of 16 lanes
       {
-        constexpr int kWordsPerThread = kSymFlagWords / kDenseThreads;
-        static_assert(kWordsPerThread % 4 == 0 && kGrpWords % kWordsPerThread == 0 && kBlkWords % kWordsPerThread == 0, "whole threads per group and block");
-        constexpr int kThreadsPerGroup = kGrpWords / kWordsPerThread, kThreadsPerBlock = kBlkWords / kWordsPerThread;
-        static_assert(kThreadsPerBlock <= kWave, "a block's threads sit in one wave");
-        const uint4* f4 = reinterpret_cast<const uint4*>(flags) + tid * (kWordsPerThread / 4);
-        int local = 0;
-#pragma unroll
-        for (int q = 0; q < kWordsPerThread / 4; ++q) {
-          const uint4 v = f4[q];
-          local += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+        static_assert(kBlkWords == 4 * kWave && kGrpWords == 64, "four words per lane, sixteen lanes per group");
+        const int lane = tid & 63;
+        for (int blk = uni(tid >> 6); blk < nb; blk += WAVES) {
+          const uint4 v = reinterpret_cast<const uint4*>(flags)[blk * kWave + lane];
+          const int incl = wave_incl_scan(__popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w));
+          const int t0 = __builtin_amdgcn_readlane(incl, 15), t1 = __builtin_amdgcn_readlane(incl, 31);
+          const int t2 = __builtin_amdgcn_readlane(incl, 47), t3 = __builtin_amdgcn_readlane(incl, 63);
+          if (lane == 0) {
+            *reinterpret_cast<int4*>(&tp->grp[blk * 4]) = make_int4(t0, t1 - t0, t2 - t1, t3 - t2);
+            tp->blk_cnt[blk] = t3;
+          }
         }
-#pragma unroll
-        for (int sh = 1; sh < kThreadsPerGroup; sh <<= 1) local += __shfl_xor(local, sh, kWave);
-        if (tid % kThreadsPerGroup == 0) tp->grp[tid / kThreadsPerGroup] = local;
-#pragma unroll
-        for (int sh = kThreadsPerGroup; sh < kThreadsPerBlock; sh <<= 1) local += __shfl_xor(local, sh, kWave);
-        if (tid % kThreadsPerBlock == 0) tp->blk_cnt[tid / kThreadsPerBlock] = local;
       }
       __syncthreads();
       SPG_CLK(clk_mark(&rs->clk, 5);)
@@ -576,8 +580,9 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
         // Everything this span needs from the plan's shared lists, and the next row, in one round trip:
         // room for the entries in the column list (without it the numeric kernel rebuilds the flags
         // itself), tile and run records.  A span that got room in the list and has at
-        // most kSearchCap entries and at most search_ratio products per entry becomes one searched tile
-        // (the records planned above stay unused).
+        // most kSearchRow entries and at most search_ratio products per entry becomes one searched tile, or two, where that is
+        // less than half of the tiles planned above (whose records then stay unused): a bisection costs three times the
+        // look-up in a ranked tile (R-MAT scale 17, searched wherever a tile was saved: row blocks 7.27 ms, now 6.83).
         const int total = tp->cum[kSpanBlocks];
         const int nt = tp->ntiles;
         const int nr = (nt + kRunTiles - 1) / kRunTiles;
@@ -589,7 +594,15 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
         const long long span_products = (n_cols > span && sorted) ? (long long)rs->span_ip : (long long)ip[row];
         // (a searched tile takes every product of its pieces: with unordered B rows the pieces are whole rows,
         // so the tile must be the whole row)
-        const bool search_row = (sorted || n_cols <= span) && total <= kSearchCap && nt > 1 && span_products <= (long long)search_ratio * total;
+        bool search_row = (sorted || n_cols <= span) && total <= kSearchRow && nt > (total <= kSearchCap ? 2 : 4) && span_products <= (long long)search_ratio * total;
+        int cut = nb;   // where the second searched tile begins
+        if (search_row && total > kSearchCap) {
+          int e = 0;   // as many blocks as one tile holds
+          for (int step = kSpanBlocks / 2; step > 0; step >>= 1)
+            if (e + step < nb && tp->cum[e + step] <= kSearchCap) e += step;
+          search_row = sorted && total - tp->cum[e] <= kSearchCap;
+          cut = e;
+        }
         const int fwords = (words + 3) & ~3;
         const bool as_words = !search_row && (long long)fwords * kFlagWordsNum <= (long long)kFlagWordsDen * total;
         const unsigned long long need = as_words ? (unsigned long long)(span_rank_slots(words) + fwords)
@@ -632,6 +645,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
           }
         }
         if (listed) tp->list_used += need;
+        else if (total > 0 && !count_only) ctl->unlisted = 1;
         tp->list_base = listed ? (long long)at : -1;
         tp->list_words = listed && as_words ? fwords : 0;
         tp->tile_base = tb;
@@ -645,8 +659,10 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
         } else if (listed && search_row) {
           // (a searched tile pays a bisection per product: only for rows with little deduplication, and
           // only where it saves tiles - a row that is one ranked or direct tile anyway stays that)
-          tp->rec[0] = TileRec{block0, block0 + nb, total | kSearchBit, tp->span_out0};
-          tp->ntiles = 1;
+          const int c0 = cut < nb ? tp->cum[cut] : total;
+          tp->rec[0] = TileRec{block0, block0 + cut, c0 | kSearchBit, tp->span_out0};
+          if (cut < nb) tp->rec[1] = TileRec{block0 + cut, block0 + nb, (total - c0) | kSearchBit, tp->span_out0 + c0};
+          tp->ntiles = cut < nb ? 2 : 1;
           atomicAdd(&ctl->search_tiles, 1u);
         } else if (tp->ndirect > 0) {
           atomicAdd(&ctl->direct_tiles, (unsigned)tp->ndirect);
@@ -670,24 +686,24 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
       }
       if (lb >= 0 && tp->list_words) {
         // the flag list leaves as it is (one coalesced copy), behind the rank of every group's first entry
-        static_assert(kGrpWords * 4 == kBlkWords && kSpanGroups <= kDenseThreads, "four groups per block, a thread per group");
+        static_assert(kGrpWords * 4 == kBlkWords, "four groups per block");
         const int nslots = span_rank_slots(words);
-        if (tid < nslots) {
-          int r = tp->span_out0 + tp->cum[(tid >> 2) < kSpanBlocks ? (tid >> 2) : kSpanBlocks];
-          for (int g = tid & ~3; g < tid; ++g) r += tp->grp[g];
-          col_list[lb + tid] = r;
+        for (int t = tid; t < nslots; t += kThreads) {
+          int r = tp->span_out0 + tp->cum[(t >> 2) < kSpanBlocks ? (t >> 2) : kSpanBlocks];
+          for (int g = t & ~3; g < t; ++g) r += tp->grp[g];
+          col_list[lb + t] = r;
         }
         const uint4* f4 = reinterpret_cast<const uint4*>(flags);
         uint4* o4 = reinterpret_cast<uint4*>(col_list + lb + nslots);
         const int n4 = tp->list_words >> 2;
-        for (int w = tid; w < n4; w += kDenseThreads) o4[w] = f4[w];
+        for (int w = tid; w < n4; w += kThreads) o4[w] = f4[w];
       } else if (lb >= 0) {
         // The list position of a block's first entry is its entry prefix.  Sparse blocks: the columns are decoded, a round
         // with few entries is gathered in LDS first and leaves as one coalesced run.
         // Direct blocks: the numeric kernel wants the flag words themselves (their 256 words fit
         // in the space of the block's entries).
         const int wave = tid >> 6, lane = tid & 63;
-        const bool searched = nt == 1 && (tp->rec[0].cnt & kSearchBit) != 0;
+        const bool searched = (tp->rec[0].cnt & kSearchBit) != 0;
         int* wst = reinterpret_cast<int*>(rs) + wave * kListStage;   // the piece walker's scratch is free now
         // (blocks are handed out one at a time: their entry counts differ by orders of magnitude,
         // so a fixed share per wave would leave most waves waiting for the one with the dense blocks)
@@ -775,532 +791,9 @@ __global__ __launch_bounds__(kDenseThreads) void k_sym_dense(const int* __restri
   SPG_CLK(clk_mark(&rs->clk, 9); clk_flush(&rs->clk, ctl->clk[0]);)
 }
 
-constexpr size_t kSymDenseLds = (size_t)kSymFlagWords * 4 + sizeof(RowScratch) + sizeof(TilePlan);
-
-// ---- numeric --------------------------------------------------------------------------
-
-// LDS behind the tile area of the numeric kernel.
-template <typename T>
-struct NumScratch {
-  long long c_s[kSegCap];      // first B entry of every non-empty piece of the tile
-  int c_cpre[kSegCap + 1];     // exclusive prefix of the pieces' quad counts
-  int c_len[kSegCap];          // piece length
-  T c_av[kSegCap];             // a_ik of the piece
-  TileRec rec[kRunTiles];
-  RunRec rr;                   // the run in the works
-  int red[2 * kDenseWaves];
-  int s_run;
-  int pad;
-  SPG_CLK(ClkLds clk;)
-};
-
-// The piece [s, s + len) of B row k that falls into the tile (blocks [b0, b1), columns [t_lo, t_hi)).
-__device__ __forceinline__ void piece_range(int k, long long rs, long long re, int b0, int b1, int t_lo, int64_t t_hi, bool sorted,
-                                            const int* __restrict__ bp, int nb1, const int32_t* __restrict__ b_col,
-                                            long long& s, int& len) {
-  if (sorted && bp) {
-    const int* row = bp + (int64_t)k * nb1;
-    const int o0 = row[b0], o1 = row[b1];
-    s = rs + o0;
-    len = o1 - o0;
-  } else {
-    int64_t st = rs, en = re;
-    if (sorted) SearchRange{b_col, t_lo, t_hi}(k, st, en);
-    s = st;
-    len = (int)(en - st);
-  }
-}
-
-// Compacts the non-empty pieces of the workgroup's threads into c_s / c_cpre / c_len / c_av.
-// Returns their number and the quad total.  Contains barriers.
-template <typename T>
-__device__ __forceinline__ void tile_pieces(NumScratch<T>* ns, long long s, int len, T av, int& np, int& nquads) {
-  int idx, cpre;
-  block_excl_scan2(len > 0 ? 1 : 0, (len + 3) >> 2, idx, cpre, np, nquads, ns->red);
-  if (len > 0) {
-    ns->c_s[idx] = s;
-    ns->c_cpre[idx] = cpre;
-    ns->c_len[idx] = len;
-    ns->c_av[idx] = av;
-  }
-  __syncthreads();
-  SPG_CLK(clk_add(&ns->clk, 20, (unsigned long long)nquads); clk_add(&ns->clk, 21, (unsigned long long)np);)
-}
-
-template <typename T, bool CHECK>
-__device__ __forceinline__ void num_dense_run(const RunRec rr, NumScratch<T>* ns, unsigned char* tile, bool sorted,
-                                              const int32_t* __restrict__ a_col, const T* __restrict__ a_val,
-                                              const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col,
-                                              const T* __restrict__ b_val, int64_t n_cols, const int* __restrict__ bp, int nb1,
-                                              const int32_t* __restrict__ col_list,
-                                              int64_t b_nnz, int64_t out_row, int32_t* __restrict__ c_col, T* __restrict__ c_val,
-                                              const int (&pre_k)[kRegSegs], const T (&pre_av)[kRegSegs]) {
-  const int tid = threadIdx.x;
-  // the row's structure in the plan: none, its columns, or its flag words
-  const bool have_words = rr.list >= 0 && (rr.list & kListFlagWords) != 0;
-  const bool have_list = rr.list >= 0 && !have_words;
-  const long long list_at = (rr.list & (kListFlagWords - 1)) - kListBias;   // entry 0 of the row, or the span's kept structure
-  const int64_t a0 = rr.a0;
-  const int d = rr.d;
-  const int nseg = (d + kSegCap - 1) / kSegCap;
-  // with few segments, thread e keeps its A entry of every segment in registers for the whole
-  // run, together with the block offsets of the coming tile inside the entry's B row (fetched
-  // while the current tile is in the works)
-  const bool use_table = sorted && bp != nullptr;
-  const bool cached = nseg == 1 || (use_table && nseg <= kRegSegs);
-  int ck[kRegSegs], pf0[kRegSegs], pf1[kRegSegs];
-  long long crs[kRegSegs];
-  T cav[kRegSegs];
-  long long my_re = 0;
-#pragma unroll
-  for (int g = 0; g < kRegSegs; ++g) {
-    ck[g] = 0; pf0[g] = 0; pf1[g] = 0; crs[g] = 0; cav[g] = T(0);
-    const int e = g * kSegCap + tid;
-    if (cached && e < d) {
-      ck[g] = pre_k[g];     // (fetched by the caller together with the run's tile records)
-      cav[g] = pre_av[g];
-      crs[g] = b_rp[ck[g]];
-      if (!use_table) my_re = b_rp[ck[g] + 1];
-      if (use_table) {
-        const TileRec nx = ns->rec[0];
-        const int* row = bp + (int64_t)ck[g] * nb1;
-        pf0[g] = row[nx.b0];
-        pf1[g] = row[nx.b1];
-      }
-    }
-  }
-  SPG_CLK(clk_mark(&ns->clk, 1);)
-  for (int t = 0; t < rr.count; ++t) {
-    const TileRec tr = ns->rec[t];
-    const bool direct = (tr.cnt & kDirectBit) != 0;
-    const bool searched = (tr.cnt & kSearchBit) != 0;
-    const int count = tr.cnt & kCountMask;
-    const int t_lo = tr.b0 << kBlkShift;
-    int64_t t_hi = (int64_t)tr.b1 << kBlkShift;
-    if (t_hi > n_cols) t_hi = n_cols;
-    const int64_t out = out_row + tr.out;
-    // kept flag words of the tile's span: group ranks first, then the words (indexed here by absolute word)
-    const int64_t span_c0 = (int64_t)(tr.b0 / kSpanBlocks) * kSpanBlocks * kBlkCols;
-    const int32_t* kept_ranks = col_list + list_at;
-    const int32_t* kept_words = col_list + list_at + span_rank_slots(span_flag_words(n_cols, span_c0)) - (span_c0 >> 5);
-    // this thread's pieces of the tile, one per cached segment
-    int off_c[kRegSegs], len_c[kRegSegs];
-#pragma unroll
-    for (int g = 0; g < kRegSegs; ++g) {
-      off_c[g] = 0; len_c[g] = 0;
-      const int e = g * kSegCap + tid;
-      if (cached && e < d) {
-        if (use_table) {
-          off_c[g] = pf0[g];
-          len_c[g] = pf1[g] - pf0[g];
-          if (t + 1 < rr.count) {
-            const TileRec nx = ns->rec[t + 1];
-            const int* row = bp + (int64_t)ck[g] * nb1;
-            pf0[g] = nx.b0 == tr.b1 ? pf1[g] : row[nx.b0];
-            pf1[g] = row[nx.b1];
-          }
-        } else {   // one segment, no table
-          long long ps;
-          piece_range(ck[g], crs[g], my_re, tr.b0, tr.b1, t_lo, t_hi, sorted, bp, nb1, b_col, ps, len_c[g]);
-          off_c[g] = (int)(ps - crs[g]);
-        }
-      }
-    }
-    // piece of segment sg for this thread
-    auto seg_piece = [&](int sg, long long& ps, int& plen, T& pav) {
-      if (cached) {
-        static_assert(kRegSegs == 2, "the selects below cover two segments");
-        const int o = sg == 0 ? off_c[0] : off_c[1];
-        plen = sg == 0 ? len_c[0] : len_c[1];
-        ps = (sg == 0 ? crs[0] : crs[1]) + o;
-        pav = sg == 0 ? cav[0] : cav[1];
-        return;
-      }
-      ps = 0; plen = 0; pav = T(0);
-      const int e = sg * kSegCap + tid;
-      if (e < d && e < (sg + 1) * kSegCap) {
-        const int k = a_col[a0 + e];
-        pav = a_val[a0 + e];
-        piece_range(k, b_rp[k], b_rp[k + 1], tr.b0, tr.b1, t_lo, t_hi, sorted, bp, nb1, b_col, ps, plen);
-      }
-    };
-    long long s = 0;
-    int len = 0;
-    T my_av = T(0);
-    if (nseg == 1) seg_piece(0, s, len, my_av);
-    __syncthreads();   // the previous tile's output has left the tile area
-    SPG_CLK(clk_mark(&ns->clk, 2); clk_add(&ns->clk, 22, (unsigned long long)count);)
-    if (searched) {
-      // the tile's columns (from the plan's list) and their sums, by rank; a product finds the rank of
-      // its column by bisection, so the tile may be as wide as the matrix
-      int* cols = reinterpret_cast<int*>(tile);
-      double* acc = reinterpret_cast<double*>(tile + (((size_t)count * 4 + 7) & ~(size_t)7));
-      const int32_t* lst = col_list + list_at + tr.out;
-      for (int j0 = 0; j0 < count; j0 += kListBatch * kDenseThreads) {
-        int lc[kListBatch];
-#pragma unroll
-        for (int i = 0; i < kListBatch; ++i) {
-          const int j = j0 + i * kDenseThreads + tid;
-          lc[i] = j < count ? stream_load(&lst[j]) : -1;
-        }
-#pragma unroll
-        for (int i = 0; i < kListBatch; ++i) {
-          const int j = j0 + i * kDenseThreads + tid;
-          if (j < count) {
-            cols[j] = lc[i];
-            acc[j] = 0.0;
-            stream_store(&c_col[out + j], lc[i]);
-          }
-        }
-      }
-      SPG_CLK(clk_mark(&ns->clk, 10); clk_add(&ns->clk, 19, 1);)
-      int top = 1;   // largest power of two below count
-      while (top * 2 < count) top *= 2;
-      for (int sg = 0; sg < nseg; ++sg) {
-        T av = my_av;
-        if (nseg > 1) seg_piece(sg, s, len, av);
-        int np, nquads;
-        tile_pieces(ns, s, len, av, np, nquads);   // (its barriers also publish cols and the cleared sums)
-        quad_pass<true, T>(np, nquads, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
-                               [&](const Quad<T>& q) {
-          // last position whose column is <= c (the column is in the list); the four bisections of a quad
-          // advance in lockstep so that their LDS reads overlap
-          int lo[4] = {0, 0, 0, 0};
-          for (int step = top; step > 0; step >>= 1) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int mid = lo[i] + step;
-              if (mid < count && cols[mid < count ? mid : 0] <= q.col.v[i]) lo[i] = mid;
-            }
-          }
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (i < q.n)
-              __hip_atomic_fetch_add(&acc[lo[i]], (double)q.a * (double)q.b.v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        });
-        if (nseg > 1) __syncthreads();
-      }
-      __syncthreads();
-      SPG_CLK(clk_mark(&ns->clk, 11);)
-      for (int r = tid; r < count; r += kDenseThreads) stream_store(&c_val[out + r], (T)acc[r]);
-      SPG_CLK(clk_mark(&ns->clk, 12);)
-    } else if (direct) {
-      double* acc = reinterpret_cast<double*>(tile);                      // kBlkCols sums, indexed by column
-      int* stage = reinterpret_cast<int*>(tile + (size_t)kBlkCols * 8);   // kBlkCols columns, by rank
-      unsigned* flags = reinterpret_cast<unsigned*>(tile + (size_t)kBlkCols * 12);   // kBlkCols / 32
-      {
-        double2* a2 = reinterpret_cast<double2*>(acc);
-        for (int r = tid; r < kBlkCols / 2; r += kDenseThreads) a2[r] = make_double2(0.0, 0.0);
-      }
-      // which columns exist: the flag words are in the plan's list, or are rebuilt by the pass
-      if (tid < kBlkCols / 32)   // (the last block of the matrix may be cut short: no flag words are kept behind its end)
-        flags[tid] = have_words ? (tid < (int)((t_hi - t_lo + 31) >> 5) ? (unsigned)kept_words[(long long)tr.b0 * kBlkWords + tid] : 0u)
-                                : (have_list ? (unsigned)col_list[list_at + tr.out + tid] : 0u);
-      SPG_CLK(clk_add(&ns->clk, 18, 1);)
-      for (int sg = 0; sg < nseg; ++sg) {
-        T av = my_av;
-        if (nseg > 1) seg_piece(sg, s, len, av);
-        int np, nquads;
-        tile_pieces(ns, s, len, av, np, nquads);
-        SPG_CLK(clk_mark(&ns->clk, 7);)
-        quad_pass<true, T>(np, nquads, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
-                               [&](const Quad<T>& q) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (i < q.n && (!CHECK || (q.col.v[i] >= t_lo && (int64_t)q.col.v[i] < t_hi))) {
-                const int rel = q.col.v[i] - t_lo;
-                if (!have_list && !have_words) atomicOr(&flags[rel >> 5], 1u << (rel & 31));
-                __hip_atomic_fetch_add(&acc[rel], (double)q.a * (double)q.b.v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-              }
-        });
-        if (nseg > 1) __syncthreads();
-      }
-      __syncthreads();
-      SPG_CLK(clk_mark(&ns->clk, 8);)
-      // compress: thread t owns columns [8 t, 8 t + 8)
-      const unsigned byte = (flags[tid >> 2] >> ((tid & 3) * 8)) & 255u;
-      double v[8];
-      {
-        const double2* a2 = reinterpret_cast<const double2*>(acc) + tid * 4;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { const double2 x = a2[i]; v[2 * i] = x.x; v[2 * i + 1] = x.y; }
-      }
-      int base, dummy_e, tot, dummy_t;
-      block_excl_scan2(__popc(byte), 0, base, dummy_e, tot, dummy_t, ns->red);   // barriers: every sum has been read
-      (void)tot;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        if (byte & (1u << i)) {
-          acc[base] = v[i];
-          stage[base] = t_lo + tid * 8 + i;
-          ++base;
-        }
-      }
-      __syncthreads();
-      for (int r = tid; r < count; r += kDenseThreads) {
-        stream_store(&c_val[out + r], (T)acc[r]);
-        stream_store(&c_col[out + r], stage[r]);
-      }
-      SPG_CLK(clk_mark(&ns->clk, 9);)
-    } else {
-      const int nw = (tr.b1 - tr.b0) * (kBlkCols / 32);                   // 32-bit flag words
-      uint2* fc = reinterpret_cast<uint2*>(tile);                         // per word: .x flag bits, .y rank of its first column
-      double* acc = reinterpret_cast<double*>(tile + (size_t)nw * 8);     // count sums, by rank
-      // with a column list: the first batch of its entries is on its way while the workspace is set up
-      const int32_t* lst = col_list + (have_list ? list_at + tr.out : 0);
-      int lc[kListBatch], lp[kListBatch];   // kListBatch loads in flight per thread
-      auto fetch_list = [&](int j0) {
-#pragma unroll
-        for (int i = 0; i < kListBatch; ++i) {
-          const int j = j0 + i * kDenseThreads + tid;
-          lc[i] = j < count ? stream_load(&lst[j]) : -1;
-          lp[i] = ((tid & 63) == 0 && j > 0 && j < count) ? lst[j - 1] : -1;   // left neighbour of the wave's first entry
-        }
-      };
-      if (have_list) fetch_list(0);
-      int np = 0, nquads = 0;
-      int* stage = reinterpret_cast<int*>(acc);   // columns by rank, in the space of the sums, on their way to C
-      if (!have_words)
-        for (int w = tid; w < nw; w += kDenseThreads) fc[w] = make_uint2(0u, 0u);
-      if (have_list) {
-        // the symbolic phase left the tile's columns (ascending) in the plan: flag bits and ranks
-        // come from that list, and the list is this tile's run of C's column indices
-        for (int r = tid; r < count; r += kDenseThreads) acc[r] = 0.0;
-        if (nseg == 1) tile_pieces(ns, s, len, my_av, np, nquads); else __syncthreads();
-        SPG_CLK(clk_mark(&ns->clk, 3); clk_add(&ns->clk, 17, 1);)
-        for (int j0 = 0; j0 < count; j0 += kListBatch * kDenseThreads) {
-          if (j0 > 0) fetch_list(j0);
-#pragma unroll
-          for (int i = 0; i < kListBatch; ++i) {
-            const int j = j0 + i * kDenseThreads + tid;
-            const int c = lc[i];
-            int prev = __shfl_up(c, 1, kWave);
-            if ((tid & 63) == 0) prev = lp[i];
-            if (c >= 0) {
-              const int rel = c - t_lo;
-              flags_or_combined(rel >> 5, 1u << (rel & 31), [&](int w) { return &fc[w].x; });
-              if (prev < 0 || ((prev - t_lo) >> 5) != (rel >> 5)) fc[rel >> 5].y = (unsigned)j;
-              stream_store(&c_col[out + j], c);
-            }
-          }
-        }
-        __syncthreads();
-        SPG_CLK(clk_mark(&ns->clk, 4);)
-      } else if (have_words) {
-        // the symbolic phase left the span's flag words in the plan, with the rank of the first entry of
-        // every group of kGrpWords words: groups are dealt to the waves in turn (entries thin out with the
-        // column, so neighbouring groups cost about the same), a lane takes a word, ranks follow from one
-        // scan over the wave, and the columns are decoded ("boolean indexing") by rank into LDS
-        const int wave = tid >> 6, lane = tid & 63;
-        const int ngrp = nw / kGrpWords;
-        const int nw_kept = (int)((t_hi - t_lo + 31) >> 5);   // (the last block of the matrix may be cut short)
-        const int32_t* tw = kept_words + (long long)tr.b0 * kBlkWords;
-        const int32_t* tr_ranks = kept_ranks + (int)((t_lo - span_c0) >> 5) / kGrpWords;
-        constexpr int kGrpBatch = 4;
-        int wd[kGrpBatch], rk[kGrpBatch];
-        auto fetch_groups = [&](int g0) {
-#pragma unroll
-          for (int i = 0; i < kGrpBatch; ++i) {
-            const int g = g0 + i * kDenseWaves;
-            const int w = g * kGrpWords + lane;
-            wd[i] = (g < ngrp && w < nw_kept) ? stream_load(&tw[w]) : 0;
-            rk[i] = g < ngrp ? tr_ranks[g] : 0;
-          }
-        };
-        fetch_groups(wave);
-        for (int g0 = wave; g0 < ngrp; g0 += kDenseWaves * kGrpBatch) {
-          int cw[kGrpBatch], cr[kGrpBatch];
-#pragma unroll
-          for (int i = 0; i < kGrpBatch; ++i) { cw[i] = wd[i]; cr[i] = rk[i]; }
-          if (g0 + kDenseWaves * kGrpBatch < ngrp) fetch_groups(g0 + kDenseWaves * kGrpBatch);   // the next batch, while this one is decoded
-#pragma unroll
-          for (int i = 0; i < kGrpBatch; ++i) {
-            const int g = g0 + i * kDenseWaves;
-            if (g < ngrp) {
-              const int w = g * kGrpWords + lane;
-              unsigned bits = (unsigned)cw[i];
-              const int c = __popc(bits);
-              int excl = cr[i] - tr.out + wave_incl_scan(c) - c;   // rank inside the tile
-              fc[w] = make_uint2(bits, (unsigned)excl);
-              const int cbase = t_lo + w * 32;
-              while (bits) {
-                const int b = __ffs((int)bits) - 1;
-                bits &= bits - 1;
-                stage[excl++] = cbase + b;
-              }
-            }
-          }
-        }
-        __syncthreads();
-        for (int r = tid; r < count; r += kDenseThreads) stream_store(&c_col[out + r], stage[r]);
-        __syncthreads();
-        for (int r = tid; r < count; r += kDenseThreads) acc[r] = 0.0;
-        if (nseg == 1) tile_pieces(ns, s, len, my_av, np, nquads); else __syncthreads();
-        SPG_CLK(clk_mark(&ns->clk, 15); clk_add(&ns->clk, 17, 1);)
-      } else {
-      // pass 1: which columns of the tile exist in the row
-      for (int sg = 0; sg < nseg; ++sg) {
-        T av = my_av;
-        if (nseg > 1) seg_piece(sg, s, len, av);
-        tile_pieces(ns, s, len, av, np, nquads);
-        quad_pass<false, T>(np, nquads, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
-                                [&](const Quad<T>& q) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (i < q.n && (!CHECK || (q.col.v[i] >= t_lo && (int64_t)q.col.v[i] < t_hi))) {
-                const int rel = q.col.v[i] - t_lo;
-                atomicOr(&fc[rel >> 5].x, 1u << (rel & 31));
-              }
-        });
-        if (nseg > 1) __syncthreads();
-      }
-      // exclusive prefix of the flag-word populations: every wave owns a contiguous share of
-      // the words and walks it 64 words at a time (lane = word, so LDS reads do not collide);
-      // the columns are decoded from the flag words into the space of the sums, by rank, and
-      // leave from there as one coalesced run of C's column indices
-      const int wave = tid >> 6, lane = tid & 63;
-      const int wper = ((nw + kDenseThreads - 1) / kDenseThreads) * kWave;
-      const int wbase = wave * wper;
-      __syncthreads();
-      int mine = 0;
-      for (int i = lane; i < wper; i += kWave) {
-        const int w = wbase + i;
-        if (w < nw) mine += __popc(fc[w].x);
-      }
-      mine = wave_sum(mine);
-      if (lane == 0) ns->red[wave] = mine;
-      __syncthreads();
-      int running = 0;
-#pragma unroll
-      for (int w = 0; w < kDenseWaves; ++w) running += w < wave ? ns->red[w] : 0;
-      for (int i0 = 0; i0 < wper; i0 += kWave) {
-        const int w = wbase + i0 + lane;
-        unsigned bits = w < nw ? fc[w].x : 0u;
-        const int c = __popc(bits);
-        const int incl = wave_incl_scan(c);
-        int excl = running + incl - c;
-        running += __builtin_amdgcn_readlane(incl, kWave - 1);
-        if (w < nw) fc[w].y = (unsigned)excl;
-        const int cbase = t_lo + w * 32;
-        while (bits) {
-          const int b = __ffs((int)bits) - 1;
-          bits &= bits - 1;
-          stage[excl++] = cbase + b;
-        }
-      }
-      __syncthreads();
-      for (int r = tid; r < count; r += kDenseThreads) stream_store(&c_col[out + r], stage[r]);
-      __syncthreads();
-      for (int r = tid; r < count; r += kDenseThreads) acc[r] = 0.0;
-      __syncthreads();
-      SPG_CLK(clk_mark(&ns->clk, 13);)
-      }
-      // pass 2: accumulate a_ik * b_kj at the rank of column j
-      for (int sg = 0; sg < nseg; ++sg) {
-        if (nseg > 1) {
-          T av;
-          seg_piece(sg, s, len, av);
-          tile_pieces(ns, s, len, av, np, nquads);
-        }
-        quad_pass<true, T>(np, nquads, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
-                               [&](const Quad<T>& q) {
-          // the four flag words of a quad first, so that their reads overlap
-          uint2 w[4];
-          bool ok[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            ok[i] = i < q.n && (!CHECK || (q.col.v[i] >= t_lo && (int64_t)q.col.v[i] < t_hi));
-            w[i] = fc[ok[i] ? (q.col.v[i] - t_lo) >> 5 : 0];
-          }
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (ok[i]) {
-              const int rank = (int)w[i].y + __popc(w[i].x & ((1u << ((q.col.v[i] - t_lo) & 31)) - 1u));
-              __hip_atomic_fetch_add(&acc[rank], (double)q.a * (double)q.b.v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-        });
-        if (nseg > 1) __syncthreads();
-      }
-      __syncthreads();
-      SPG_CLK(clk_mark(&ns->clk, 5);)
-      // compress: sums and columns are already in ascending column order
-      for (int r = tid; r < count; r += kDenseThreads) stream_store(&c_val[out + r], (T)acc[r]);
-      SPG_CLK(clk_mark(&ns->clk, 6);)
-    }
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kDenseThreads) void k_num_dense(Control* ctl, const unsigned char* __restrict__ numbin,
-                                                             const TileRec* __restrict__ tiles, const RunRec* __restrict__ runs,
-                                                             const int32_t* __restrict__ a_col,
-                                                             const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
-                                                             const int32_t* __restrict__ b_col, const T* __restrict__ b_val,
-                                                             int64_t n_cols, const int* __restrict__ bp, int nb1,
-                                                             const int32_t* __restrict__ col_list, int64_t b_nnz,
-                                                             const int64_t* __restrict__ c_rp,
-                                                             int32_t* __restrict__ c_col, T* __restrict__ c_val) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  unsigned char* tile = smem;                                                         // kTileBudget bytes
-  NumScratch<T>* ns = reinterpret_cast<NumScratch<T>*>(smem + kTileBudget);
-  if (ctl->error) return;
-  const bool sorted = ctl->b_sorted != 0;
-  const int tid = threadIdx.x;
-  const unsigned nruns = ctl->run_cursor;
-  // Thread 0 draws runs ahead of their use: the counter value for the run after next and the record
-  // of the next run are on their way while the current run is in the works.
-  unsigned drawn = 0;
-  RunRec coming{};
-  bool have_coming = false;
-  SPG_CLK(clk_begin(&ns->clk);)
-  if (tid == 0) {
-    const unsigned first = atomicAdd(&ctl->work[1], 1u);
-    drawn = atomicAdd(&ctl->work[1], 1u);
-    have_coming = first < nruns;
-    if (have_coming) coming = runs[first];
-  }
-  while (true) {
-    __syncthreads();
-    if (tid == 0) {
-      ns->s_run = have_coming ? 1 : -1;
-      if (have_coming) ns->rr = coming;
-      have_coming = drawn < nruns;
-      if (have_coming) {
-        coming = runs[drawn];
-        drawn = atomicAdd(&ctl->work[1], 1u);
-      }
-    }
-    __syncthreads();
-    if (ns->s_run < 0) break;
-    const RunRec rr = ns->rr;
-    if (rr.count == 0) continue;   // a record that its row did not need
-    // one round trip: the row's class and position in C, the run's tile records, its A entries
-    const int cls = numbin[rr.row];
-    const int64_t out_row = c_rp[rr.row];
-    if (tid < rr.count) ns->rec[tid] = tiles[rr.first + tid];
-    int pre_k[kRegSegs];
-    T pre_av[kRegSegs];
-#pragma unroll
-    for (int g = 0; g < kRegSegs; ++g) {
-      pre_k[g] = 0; pre_av[g] = T(0);
-      const int e = g * kSegCap + tid;
-      if (e < rr.d && rr.d <= kRegSegs * kSegCap) {
-        pre_k[g] = a_col[rr.a0 + e];
-        pre_av[g] = a_val[rr.a0 + e];
-      }
-    }
-    if (cls < 5 || cls > 6) continue;   // the row's numeric class is not this kernel's
-    __syncthreads();
-    SPG_CLK(clk_mark(&ns->clk, 0); clk_add(&ns->clk, 16, 1);)
-    if (sorted)
-      num_dense_run<T, false>(rr, ns, tile, true, a_col, a_val, b_rp, b_col, b_val, n_cols, bp, nb1, col_list, b_nnz, out_row, c_col, c_val, pre_k, pre_av);
-    else
-      num_dense_run<T, true>(rr, ns, tile, false, a_col, a_val, b_rp, b_col, b_val, n_cols, bp, nb1, col_list, b_nnz, out_row, c_col, c_val, pre_k, pre_av);
-  }
-  SPG_CLK(clk_mark(&ns->clk, 14); clk_flush(&ns->clk, ctl->clk[1]);)
-}
-
-template <typename T>
-constexpr size_t num_dense_lds() { return (size_t)kTileBudget + sizeof(NumScratch<T>); }
+template <int WAVES>
+constexpr size_t sym_dense_lds(int64_t flag_words) { return (size_t)flag_words * 4 + sizeof(RowScratch<WAVES>) + sizeof(TilePlan); }
+// Half a span of flag words (64 KB): up to that many columns two workgroups of 8 waves share a compute unit.
+constexpr int64_t kSymNarrowCols = (int64_t)kSymFlagWords * 16;
 
 }  // namespace spg

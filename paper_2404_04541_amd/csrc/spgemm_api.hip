@@ -20,6 +20,7 @@
 #include "record_kernels.hpp"
 #include "hash_kernels.hpp"
 #include "dense_kernels.hpp"
+#include "tile_kernels.hpp"
 #include "staged_kernels.hpp"
 #include "sort_kernels.hpp"
 #include "tensor_kernels.hpp"
@@ -28,8 +29,9 @@
 using namespace spg;
 
 // a workgroup of the big kernels owns the whole LDS of a compute unit (160 KB)
-static_assert(num_dense_lds<double>() <= 160 * 1024 && num_dense_lds<float>() <= 160 * 1024, "numeric dense kernel exceeds LDS");
-static_assert(kSymDenseLds <= 160 * 1024, "symbolic dense kernel exceeds LDS");
+static_assert(num_tiles_lds<double, true>() <= 160 * 1024 && num_tiles_lds<float, true>() <= 160 * 1024, "numeric dense kernel exceeds LDS");
+static_assert(sym_dense_lds<16>(kSymFlagWords) <= 160 * 1024, "symbolic dense kernel exceeds LDS");
+static_assert(sym_dense_lds<8>(kSymNarrowCols / 32) <= 80 * 1024 && num_tiles_lds<double, false>() <= 80 * 1024 && num_tiles_lds<float, false>() <= 80 * 1024, "two workgroups on a compute unit");
 static_assert(staged_lds<double>() <= 160 * 1024 && staged_lds<float>() <= 160 * 1024, "staged kernel exceeds LDS");
 
 // Pinned host memory where the symbolic kernels leave the control block for the host.  Allocating and releasing it costs 50 to
@@ -126,6 +128,7 @@ struct spgemm_plan_s {
   Control* ctl = nullptr;
   int64_t scan_blocks = 0;
   int64_t recorded = 0;          // rows that have a record
+  bool all_listed = false;       // every row of the dense classes has its structure in the column list
   bool order_kept = false;       // the checksums of the order of the entries were taken
   bool symbolic_done = false;
   bool numeric_pending = false;   // timed numeric launches not yet folded into stats
@@ -197,9 +200,12 @@ int ensure_device(spgemm_context* h) {
   if (prop.warpSize != kWave) return fail(h, SPGEMM_UNSUPPORTED, "device is not wave64");
   h->num_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
   int rc;
-  if ((rc = allow_lds(h, k_sym_dense, kSymDenseLds))) return rc;
-  if ((rc = allow_lds(h, k_num_dense<float>, num_dense_lds<float>()))) return rc;
-  if ((rc = allow_lds(h, k_num_dense<double>, num_dense_lds<double>()))) return rc;
+  if ((rc = allow_lds(h, k_sym_dense<16>, sym_dense_lds<16>(kSymFlagWords)))) return rc;
+  if ((rc = allow_lds(h, k_sym_dense<8>, sym_dense_lds<8>(kSymNarrowCols / 32)))) return rc;
+  if ((rc = allow_lds(h, k_num_tiles<float, false>, num_tiles_lds<float, false>()))) return rc;
+  if ((rc = allow_lds(h, k_num_tiles<double, false>, num_tiles_lds<double, false>()))) return rc;
+  if ((rc = allow_lds(h, k_num_tiles<float, true>, num_tiles_lds<float, true>()))) return rc;
+  if ((rc = allow_lds(h, k_num_tiles<double, true>, num_tiles_lds<double, true>()))) return rc;
   if ((rc = allow_lds(h, k_num_staged<float>, staged_lds<float>()))) return rc;
   if ((rc = allow_lds(h, k_num_staged<double>, staged_lds<double>()))) return rc;
   h->device_ready = true;
@@ -317,6 +323,16 @@ int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const sp
   return SPGEMM_OK;
 }
 
+// Workgroups of the dense symbolic kernel: those that are resident (registers for 24 waves on a compute unit, 160 KB of LDS).
+unsigned sym_dense_workgroups(spgemm_context* h, int64_t rows, int64_t cols) {
+  int64_t per_cu = 1;
+  if (cols <= kSymNarrowCols) {
+    per_cu = (int64_t)(160 * 1024 / sym_dense_lds<8>(sym_flag_words(cols)));
+    per_cu = per_cu < 3 ? per_cu : 3;
+  }
+  return grid_for(rows, 1, (int64_t)h->num_cus * per_cu);
+}
+
 // Sizes and allocates what the dense kernels need beyond the per-row arrays: the tile and run
 // lists (from an upper bound of the number of tiles) and the table of block offsets of B.
 int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, const Control& host, unsigned* tile_cap,
@@ -336,7 +352,7 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
   const double weight = rows_d * blocks * kRankBlkBytes + (double)kRankEntryBytes * entries;
   // (+ a slab per workgroup of the symbolic kernel: what a workgroup has drawn and not used; a row whose runs do not fit
   // what is left of a run slab leaves fewer records behind than it takes, hence twice the runs)
-  const double wgs = (double)grid_for((int64_t)rows_d, 1, h->num_cus) + 1.0;
+  const double wgs = (double)sym_dense_workgroups(h, (int64_t)rows_d, B->cols) + 1.0;
   const double tiles = 2.0 * direct + 2.0 * weight / kTileBudget + 4.0 * rows_d * spans + 16.0 + wgs * kTileSlab;
   const double runs = 2.0 * ((tiles - wgs * kTileSlab) / kRunTiles + rows_d * spans + 16.0) + wgs * kRunSlab;
   if (tiles > 4.0e9) return fail(h, SPGEMM_UNSUPPORTED, "tile list of the dense workspace would exceed 2^32 records");
@@ -490,7 +506,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     sum_order(h, p, A, B, 1);
   }
   if (rows_dense > 0) {
-    hipLaunchKernelGGL(k_set_caps, dim3(1), dim3(64), 0, s, p->ctl, tile_cap, run_cap, p->col_list_cap, rows_dense, grid_for(rows_dense, 1, h->num_cus));
+    hipLaunchKernelGGL(k_set_caps, dim3(1), dim3(64), 0, s, p->ctl, tile_cap, run_cap, p->col_list_cap, rows_dense, sym_dense_workgroups(h, rows_dense, B->cols));
     if (p->blk_ptr) {
       Timer t(h, SPGEMM_K_BLOCK_PTR);
       const int64_t items = B->rows * (int64_t)p->blk_ptr_cols;
@@ -521,8 +537,9 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     }
     if (rows_dense > 0) {
       Timer t(h, SPGEMM_K_SYM_DENSE);
-      hipLaunchKernelGGL(k_sym_dense, dim3(grid_for(rows_dense, 1, h->num_cus)), dim3(kDenseThreads), kSymDenseLds, s, p->perm_sym,
-                         p->ctl, A->rowptr, A->colidx, B->rowptr, B->colidx, B->cols, p->ip, p->cnt, p->tiles, p->runs, p->col_list, h->direct_min,
+      const bool narrow = B->cols <= kSymNarrowCols;
+      hipLaunchKernelGGL((narrow ? k_sym_dense<8> : k_sym_dense<16>), dim3(sym_dense_workgroups(h, rows_dense, B->cols)), dim3(narrow ? 512 : 1024),
+                         narrow ? sym_dense_lds<8>(sym_flag_words(B->cols)) : sym_dense_lds<16>(sym_flag_words(B->cols)), s, p->perm_sym, p->ctl, A->rowptr, A->colidx, B->rowptr, B->colidx, B->cols, p->ip, p->cnt, p->tiles, p->runs, p->col_list, h->direct_min,
                          staged, h->search_ratio, p->blk_ptr, p->blk_ptr_cols, B->nnz);
     }
     {
@@ -620,15 +637,16 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   }
   if (hist[4]) {
     Timer t(h, SPGEMM_K_NUM_STAGED);
-    hipLaunchKernelGGL(k_num_staged<T>, dim3(grid_for(hist[4], 1, h->num_cus)), dim3(kDenseThreads), staged_lds<T>(), s, p->perm_num,
+    hipLaunchKernelGGL(k_num_staged<T>, dim3(grid_for(hist[4], 1, h->num_cus)), dim3(kStThreads), staged_lds<T>(), s, p->perm_num,
                        p->ctl, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, B->cols, c_rp, c_col, c_val);
   }
   const int64_t rows_dense = hist[5] + hist[6];
   if (rows_dense > 0) {
     Timer t(h, SPGEMM_K_NUM_DENSE);
-    hipLaunchKernelGGL(k_num_dense<T>, dim3(grid_for(rows_dense, 1, h->num_cus)), dim3(kDenseThreads), num_dense_lds<T>(), s, p->ctl,
-                       p->bin, p->tiles, p->runs, A->colidx, a_val, B->rowptr, B->colidx, b_val, B->cols, p->blk_ptr,
-                       p->blk_ptr_cols, p->col_list, B->nnz, c_rp, c_col, c_val);
+    const bool plain = p->blk_ptr && p->all_listed && B->nnz < kTileMaxNnz;   // (the table is built for ascending rows only)
+    hipLaunchKernelGGL((plain ? k_num_tiles<T, false> : k_num_tiles<T, true>), dim3(grid_for(rows_dense, 1, (int64_t)h->num_cus * 2)), dim3(kTileThreads),
+                       (plain ? num_tiles_lds<T, false>() : num_tiles_lds<T, true>()), s, p->ctl, p->bin, p->tiles, p->runs, A->colidx, a_val, B->rowptr,
+                       B->colidx, b_val, B->cols, p->blk_ptr, p->blk_ptr_cols, p->col_list, B->nnz, c_rp, c_col, c_val);
   }
   HIP_TRY(h, hipGetLastError());
   return SPGEMM_OK;
@@ -707,6 +725,7 @@ int symbolic(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B, int64_
     return fail(h, SPGEMM_INVALID_INPUT, "device-side input check failed (column out of range or rowptr not monotone)");
   }
   p->recorded = host.recorded;
+  p->all_listed = !host.unlisted;
   p->stats.ip_total = (int64_t)host.ip_total;
   p->stats.nnz_c = host.nnz_c;
   for (int b = 0; b < kNumBins; ++b) {

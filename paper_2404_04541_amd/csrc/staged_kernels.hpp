@@ -19,6 +19,8 @@ namespace spg {
 
 constexpr int kChunkUnroll = 8;   // chunks of 64 elements in flight per wave
 
+constexpr int kStThreads = 1024;
+constexpr int kStWaves = kStThreads / kWave;
 constexpr int kStWinCols = 131072;
 constexpr int kStWinShift = 17;
 constexpr int kStWinWords = kStWinCols / 32;
@@ -29,17 +31,17 @@ constexpr int staged_cap() { return sizeof(T) == 4 ? 6144 : 5120; }
 
 // Pieces of the segment being staged (aliases the window area).
 struct StagePieces {
-  long long s[kDenseThreads];     // first B entry of the piece
-  int cpre[kDenseThreads + 1];    // exclusive prefix of chunk counts
-  int epre[kDenseThreads];        // exclusive prefix of lengths
-  int len[kDenseThreads];
+  long long s[kStThreads];     // first B entry of the piece
+  int cpre[kStThreads + 1];    // exclusive prefix of chunk counts
+  int epre[kStThreads];        // exclusive prefix of lengths
+  int len[kStThreads];
 };
 
 template <typename T>
 constexpr size_t staged_lds() {
   const size_t list = (size_t)staged_cap<T>() * (4 + sizeof(T));
   const size_t window = (size_t)kStWinWords * 8 + (size_t)staged_cap<T>() * 12;
-  return list + (window > sizeof(StagePieces) + kDenseThreads * sizeof(T) ? window : sizeof(StagePieces) + kDenseThreads * sizeof(T)) + 256;
+  return list + (window > sizeof(StagePieces) + kStThreads * sizeof(T) ? window : sizeof(StagePieces) + kStThreads * sizeof(T)) + 256;
 }
 
 // Exclusive scans of three ints over the workgroup, with totals.  Contains barriers.
@@ -47,13 +49,13 @@ __device__ __forceinline__ void block_excl_scan3(int a, int b, int c, int& ea, i
   const int wave = threadIdx.x >> 6;
   const int ia = wave_incl_scan(a), ib = wave_incl_scan(b), ic = wave_incl_scan(c);
   __syncthreads();
-  if (lane_id() == kWave - 1) { red[wave] = ia; red[kDenseWaves + wave] = ib; red[2 * kDenseWaves + wave] = ic; }
+  if (lane_id() == kWave - 1) { red[wave] = ia; red[kStWaves + wave] = ib; red[2 * kStWaves + wave] = ic; }
   __syncthreads();
   int pa = 0, pb = 0, pc = 0;
   ta = 0; tb = 0; tc = 0;
 #pragma unroll
-  for (int w = 0; w < kDenseWaves; ++w) {
-    const int va = red[w], vb = red[kDenseWaves + w], vc = red[2 * kDenseWaves + w];
+  for (int w = 0; w < kStWaves; ++w) {
+    const int va = red[w], vb = red[kStWaves + w], vc = red[2 * kStWaves + w];
     if (w < wave) { pa += va; pb += vb; pc += vc; }
     ta += va; tb += vb; tc += vc;
   }
@@ -63,7 +65,7 @@ __device__ __forceinline__ void block_excl_scan3(int a, int b, int c, int& ea, i
 }
 
 template <typename T>
-__global__ __launch_bounds__(kDenseThreads) void k_num_staged(const int* __restrict__ perm, Control* ctl,
+__global__ __launch_bounds__(kStThreads) void k_num_staged(const int* __restrict__ perm, Control* ctl,
                                                               const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                               const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
                                                               const int32_t* __restrict__ b_col, const T* __restrict__ b_val,
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_num_staged(const int* __restr
     // ---- insert: stage every product of the row
     int total = 0;
     unsigned m0 = 0, m1 = 0;   // windows that this thread's products fall into
-    for (int base = 0; base < d; base += kDenseThreads) {
+    for (int base = 0; base < d; base += kStThreads) {
       const int e = base + tid;
       long long s = 0;
       int len = 0;
@@ -132,7 +134,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_num_staged(const int* __restr
       np = uni(np);
       nchunks = uni(nchunks);
       // chunks of 64 elements are dealt to the waves in contiguous shares
-      const int per = (nchunks + kDenseWaves - 1) / kDenseWaves;
+      const int per = (nchunks + kStWaves - 1) / kStWaves;
       int c = wave * per;
       const int cend = c + per < nchunks ? c + per : nchunks;
       if (c < cend) {
@@ -204,9 +206,9 @@ __global__ __launch_bounds__(kDenseThreads) void k_num_staged(const int* __restr
       wmask &= wmask - 1;
       (void)nwin;
       const int w_lo = w << kStWinShift;
-      for (int i = tid; i < kStWinWords; i += kDenseThreads) fc[i] = make_uint2(0u, 0u);
+      for (int i = tid; i < kStWinWords; i += kStThreads) fc[i] = make_uint2(0u, 0u);
       __syncthreads();
-      for (int j = tid; j < total; j += kDenseThreads) {
+      for (int j = tid; j < total; j += kStThreads) {
         const int c = st_col[j];
         if ((c >> kStWinShift) == w) {
           const int rel = c - w_lo;
@@ -215,7 +217,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_num_staged(const int* __restr
       }
       __syncthreads();
       // exclusive prefix of the flag-word populations: wave v owns words [256 v, 256 v + 256)
-      constexpr int kPerWave = kStWinWords / kDenseWaves;
+      constexpr int kPerWave = kStWinWords / kStWaves;
       const int wbase = wave * kPerWave;
       int mine = 0;
 #pragma unroll
@@ -225,7 +227,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_num_staged(const int* __restr
       __syncthreads();
       int running = 0, count = 0;
 #pragma unroll
-      for (int v = 0; v < kDenseWaves; ++v) { const int r = red[v]; running += v < wave ? r : 0; count += r; }
+      for (int v = 0; v < kStWaves; ++v) { const int r = red[v]; running += v < wave ? r : 0; count += r; }
 #pragma unroll
       for (int i = 0; i < kPerWave; i += kWave) {
         const int wi = wbase + i + lane;
@@ -242,9 +244,9 @@ __global__ __launch_bounds__(kDenseThreads) void k_num_staged(const int* __restr
           stage[excl++] = cbase + b;
         }
       }
-      for (int r = tid; r < count; r += kDenseThreads) acc[r] = 0.0;
+      for (int r = tid; r < count; r += kStThreads) acc[r] = 0.0;
       __syncthreads();
-      for (int j = tid; j < total; j += kDenseThreads) {
+      for (int j = tid; j < total; j += kStThreads) {
         const int c = st_col[j];
         if ((c >> kStWinShift) == w) {
           const int rel = c - w_lo;
@@ -254,7 +256,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_num_staged(const int* __restr
         }
       }
       __syncthreads();
-      for (int r = tid; r < count; r += kDenseThreads) {
+      for (int r = tid; r < count; r += kStThreads) {
         c_val[out + r] = (T)acc[r];
         c_col[out + r] = stage[r];
       }
