@@ -17,6 +17,7 @@
 #include "plan_room.hpp"
 #include "setup_kernels.hpp"
 #include "esc_kernels.hpp"
+#include "flag_kernels.hpp"
 #include "record_kernels.hpp"
 #include "hash_kernels.hpp"
 #include "dense_kernels.hpp"
@@ -128,6 +129,7 @@ struct spgemm_plan_s {
   Control* ctl = nullptr;
   int64_t scan_blocks = 0;
   int64_t recorded = 0;          // rows that have a record
+  bool flag_rows = false;        // classes 0 and 1 take the flag-list workspace
   bool all_listed = false;       // every row of the dense classes has its structure in the column list
   bool order_kept = false;       // the checksums of the order of the entries were taken
   bool symbolic_done = false;
@@ -274,17 +276,27 @@ inline unsigned grid_for(int64_t items, int64_t per_block, int64_t cap) {
 
 // Sorted-list keys can carry their list position when every column, shifted by the list's log2 capacity, stays below the padding key.
 constexpr int64_t kEscPackCols0 = int64_t(1) << 25, kEscPackCols1 = int64_t(1) << 23;
+// The numeric phase marks the columns again: where B is larger than a die's L2 cache that is a second line of memory per A entry,
+// which pays when the entry brings eight products or more.  10^6 rows (fp64, us sorted list | flags, 4000 columns): 8 entries times
+// rows of 4, B of 10^4 rows 576 | 515, 10^5 589 | 552, 5 10^5 739 | 819, 2 10^6 737 | 1032; 8 times 12: 1230 | 848, 1273 | 929, 1324 |
+// 1152, 1465 | 1390; 3 times 16: 894 | 502, 927 | 525, 971 | 600, 1202 | 728.
+constexpr int64_t kFlagMaxNnz = int64_t(1) << 20;
 constexpr size_t kAskFreeAbove = (size_t)64 << 20;   // optional memory below this is taken without asking the device what it has free
 
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
+
+// Whether the rows of classes 0 and 1 take the flag-list workspace (flag_kernels.hpp) instead of the sorted list.
+bool flag_rows_ok(spgemm_context* h, const spgemm_csr* B) {
+  return h->force != 1 && B->cols <= kFlagMaxCols && (B->nnz <= kFlagMaxNnz || B->nnz >= 8 * B->rows);
+}
 
 // Whether the row count leaves start and length of every A entry's B row: 8 bytes an entry, written once and read twice, in place
 // of a gather of B's row pointer in each of the two kernels of short rows.  It pays where those gathers miss the L2 cache (4 MB
 // per XCD) and most rows are short.  4.2 M rows of 8 entries times 4.2 M rows of 4, both kernels and the count:
 // 3.50 ms with the gathers, 2.51 ms without; with a cached B the words would cost what they save.
 // (Part of a plan's optional memory.  A block of rows of a larger matrix goes without: its positions are those of the whole.)
-bool wants_desc(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B) {
-  if (!h->col_list || h->row_block || (h->col_list > 1 && A->nnz > h->col_list / 8)) return false;
+bool wants_desc(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B) {   // (never with flag_rows_ok)
+  if (flag_rows_ok(h, B) || !h->col_list || h->row_block || (h->col_list > 1 && A->nnz > h->col_list / 8)) return false;
   if (A->rows == 0 || B->rows * 8 <= ((int64_t)4 << 20) || B->nnz >= (int64_t(1) << 39) || A->nnz >= (int64_t(1) << 39)) return false;
   return (double)A->nnz / (double)A->rows * ((double)B->nnz / (double)B->rows) <= (double)kEscLargeCap;
 }
@@ -396,7 +408,7 @@ void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, co
   const int64_t max_cols[2] = {kEscPackCols0, kEscPackCols1};
   const size_t word_bytes[2] = {kEscSmallCap * 4, kEscLargeCap * 4};
   const size_t rec_rows = !staged && B->cols <= (int64_t(1) << kRecColBits) ? host.hist[0][2] : 0;
-  const bool with_words = !staged && (!plan_leaves || rec_rows || host.bin_ip[0][0] + host.bin_ip[0][1] >= kWordsWithCheck);
+  const bool with_words = !staged && !p->flag_rows && (!plan_leaves || rec_rows || host.bin_ip[0][0] + host.bin_ip[0][1] >= kWordsWithCheck);
   size_t words[2], want = 0;
   for (int b = 0; b < 2; ++b) {
     words[b] = with_words && B->cols <= max_cols[b] ? align_up(host.hist[0][b] * word_bytes[b]) : 0;
@@ -475,6 +487,16 @@ void sum_order(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const s
                      same_columns(A, B) ? (const int32_t*)nullptr : B->colidx, p->ctl, plan);
 }
 
+// launch(words of flags per lane, as a type)
+template <class F>
+void with_flag_words(int64_t cols, F launch) {
+  switch (flag_words_per_lane(cols)) {
+    case 4: launch(std::integral_constant<int, 4>{}); break;
+    case 8: launch(std::integral_constant<int, 8>{}); break;
+    default: launch(std::integral_constant<int, 16>{});
+  }
+}
+
 // plan_leaves: the plan goes to the caller, whose numeric phases may bring the entries in another order.
 template <typename T>
 int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const spgemm_csr* B, int64_t* c_rowptr,
@@ -517,10 +539,20 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   if (m > 0) {
     {
       Timer t(h, SPGEMM_K_SYM_ESC);
-      if (hist[0])
+      if (p->flag_rows) {
+        auto rows = [&](auto wpl) {
+          constexpr int W = decltype(wpl)::value;
+          if (hist[0])
+            hipLaunchKernelGGL((k_flag_sym<32, W>), dim3(grid_for(hist[0], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0, A->rowptr, A->colidx, B->rowptr, B->colidx, B->nnz, p->cnt);
+          if (hist[1])
+            hipLaunchKernelGGL((k_flag_sym<128, W>), dim3(grid_for(hist[1], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx, B->rowptr, B->colidx, B->nnz, p->cnt);
+        };
+        with_flag_words(B->cols, rows);
+      }
+      if (hist[0] && !p->flag_rows)
         hipLaunchKernelGGL((p->desc ? k_esc_sym<16, 32, true> : k_esc_sym<16, 32, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0, A->rowptr, A->colidx,
                            B->rowptr, p->desc, B->colidx, B->nnz, pack32, p->cnt, p->esc_words[0]);
-      if (hist[1])
+      if (hist[1] && !p->flag_rows)
         hipLaunchKernelGGL((p->desc ? k_esc_sym<64, 128, true> : k_esc_sym<64, 128, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx,
                            B->rowptr, p->desc, B->colidx, B->nnz, pack128, p->cnt, p->esc_words[1]);
     }
@@ -592,13 +624,25 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   {
     Timer t(h, SPGEMM_K_NUM_ESC);
     if (check && !inside) sum_order(h, p, A, B, 0);
-    if (words0)
+    if (p->flag_rows) {
+      auto rows = [&](auto wpl) {
+        constexpr int W = decltype(wpl)::value;
+        if (hist[0])
+          hipLaunchKernelGGL((k_flag_num<32, W, T>), dim3(grid_for(hist[0], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 0, A->rowptr, A->colidx, a_val,
+                             B->rowptr, B->colidx, b_val, B->nnz, c_rp, c_col, c_val);
+        if (hist[1])
+          hipLaunchKernelGGL((k_flag_num<128, W, T>), dim3(grid_for(hist[1], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, A->rowptr, A->colidx, a_val,
+                             B->rowptr, B->colidx, b_val, B->nnz, c_rp, c_col, c_val);
+      };
+      with_flag_words(B->cols, rows);
+    } else if (words0)
       hipLaunchKernelGGL((p->desc ? k_esc_num<16, 32, T, true> : k_esc_num<16, 32, T, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0,
                          A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[0], c_rp, c_col, c_val);
     else if (hist[0])
       hipLaunchKernelGGL((k_esc<16, 32, T>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 0,
                          A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, B->nnz);
-    if (words1)
+    if (p->flag_rows) {
+    } else if (words1)
       hipLaunchKernelGGL((p->desc ? k_esc_num<64, 128, T, true> : k_esc_num<64, 128, T, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1,
                          A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[1], c_rp, c_col, c_val);
     else if (hist[1])
@@ -669,6 +713,7 @@ int symbolic(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B, int64_
   p->h = h;
   p->m = A->rows; p->k = A->cols; p->n = B->cols; p->nnz_a = A->nnz; p->nnz_b = B->nnz; p->dtype = A->dtype;
   const int64_t m = p->m;
+  p->flag_rows = flag_rows_ok(h, B);
   p->scan_blocks = m > 0 ? ceil_div(m, kScanTile) : 0;
   size_t off = 0;
   const size_t o_ctl = off; off = align_up(off + sizeof(Control));
