@@ -8,13 +8,15 @@
 //   at multiples of kBlkCols columns into tiles, each small enough for the numeric workspace,
 //   and the row's column structure goes to the plan (decoded columns, or the flag words of
 //   direct blocks), so that the numeric phase need not find it again.
-//   The flag list takes the LDS that the matrix's width needs: a workgroup of 16 waves where that is more than 64 KB, of 8
-//   waves otherwise, two or three of them on a compute unit (sym_dense_workgroups).  What a row costs beside its products
-//   (clearing and counting the flags, the round trips for its entries and its shares of the lists, decoding) was more than
-//   half of the kernel when one workgroup had the compute unit to itself.  The flags are counted with a lane on every fourth
-//   word, a block per wave (32 consecutive words per thread collided on the banks: 21 % of the kernel at scale 14).
-//   R-MAT squared, fp32, ms with one workgroup of 16 waves | now: scale 14 0.210 | 0.155, scale 17 2.75 | 1.30, scale 19
-//   15.8 | 12.0; deduplication sweep, 10000 columns, 1.13 | 0.74.
+//   The flag list takes the LDS that the matrix's width needs (sym_dense_shape): up to 2^18 columns two workgroups of 16 waves
+//   share a compute unit, up to 2^19 two of 8 waves, beyond that one of 16 waves has it to itself.  What a row costs beside its
+//   products (clearing and counting the flags, the round trips for its entries and its shares of the lists, decoding) was more
+//   than half of the kernel with one workgroup.  The flags are counted with a lane on every fourth word, a block per wave (32
+//   consecutive words per thread collided on the banks: 21 % of the kernel at scale 14).
+//   R-MAT squared, fp32, us with one workgroup | two or three of 8 waves | two of 16 waves: scale 14 210 | 155 | 145, scale 17
+//   2750 | 1300 | -, four row blocks of it - | 2210 | 1750, scale 19 15.8 | 12.0 ms | -; the heaviest rows are what 8 waves take too
+//   long for (1500 rows of a block of scale 15: 73 us a block with 16 waves, 123 with 8).  Deduplication sweep, 10000 columns: 1134 |
+//   695 (four of 8 waves) | 760.
 // Numeric (k_num_tiles), one tile at a time, one pass over the tile's products:
 //   direct tile (one block of kBlkCols columns in which the row is dense): sums live in a
 //     dense array indexed by column; the flags say which exist; flags and sums are compressed
@@ -350,6 +352,9 @@ struct __align__(16) TilePlan {
   long long list_base;    // position of the span's first entry (or first flag word) in the plan's list, -1 = none
   int list_words;         // > 0: the span's structure goes to the list as that many flag words instead of columns
   unsigned long long list_used;   // list entries that this workgroup's rows have taken
+  unsigned long long sl_pos, sl_left;   // what is left of the slabs drawn from the plan's lists: list entries,
+  unsigned st_pos, st_left, sr_pos, sr_left;   // tile records, run records
+  unsigned used_tiles, used_runs;
 };
 
 // index of the lowest set bit at or above position b in the 128-bit mask (hi:lo); 128 when none
@@ -477,13 +482,13 @@ __device__ __forceinline__ int next_dense_row(const int* __restrict__ perm, Cont
 }
 
 template <int WAVES>
-__global__ __launch_bounds__(WAVES * kWave, WAVES == 8 ? 6 : 4) void k_sym_dense(const int* __restrict__ perm, Control* ctl,
+__global__ __launch_bounds__(WAVES * kWave, WAVES == 8 ? 4 : 8) void k_sym_dense(const int* __restrict__ perm, Control* ctl,
                                                              const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                              const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col,
                                                              int64_t n_cols, const int* __restrict__ ip, int* __restrict__ cnt,
                                                              TileRec* __restrict__ tiles, RunRec* __restrict__ runs,
                                                              int32_t* __restrict__ col_list, int direct_min, int no_tiles_ip,
-                                                             int search_ratio, const int* __restrict__ bp, int nb1, int64_t b_nnz) {
+                                                             int search_ratio, const int* __restrict__ bp, int nb1, int64_t b_nnz, int run_tiles) {
   constexpr int kThreads = WAVES * kWave;
   extern __shared__ __align__(16) unsigned char smem[];
   const int flag_words = sym_flag_words(n_cols);
@@ -501,13 +506,17 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 ? 6 : 4) void k_sym_dense
   if (tid == 0) tp->list_used = 0;
   int row = next_dense_row(perm, ctl, &rs->s_row);
   int next_row = -1;   // (thread 0) the row after this one, fetched while this one is in the works
-  // (thread 0) what is left of the slabs drawn from the plan's lists, and what this workgroup used.  The first slab of
+  // Thread 0's slabs of the plan's lists are in LDS (its registers would be everybody's).  The first slab of
   // every workgroup is its own by its number (the cursors start behind these: k_set_caps); when all workgroups drew their
   // first slab from the shared cursors at the same moment, the compare-and-swaps of 256 of them took 0.2 ms (1071 rows: 366 -> 73 us).
   const unsigned long long list_slab = list_slab_of(list_cap, gridDim.x);
   const unsigned rslab = run_slab(row_hi - row_lo, gridDim.x);
-  unsigned long long sl_pos = blockIdx.x * list_slab, sl_left = list_slab;
-  unsigned st_pos = blockIdx.x * (unsigned)kTileSlab, st_left = kTileSlab, sr_pos = blockIdx.x * rslab, sr_left = rslab, used_tiles = 0, used_runs = 0;
+  if (tid == 0) {
+    tp->sl_pos = blockIdx.x * list_slab; tp->sl_left = list_slab;
+    tp->st_pos = blockIdx.x * (unsigned)kTileSlab; tp->st_left = kTileSlab;
+    tp->sr_pos = blockIdx.x * rslab; tp->sr_left = rslab;
+    tp->used_tiles = 0; tp->used_runs = 0;
+  }
   while (row >= 0) {
     unsigned nx = 0;   // (thread 0) the draw for the row after this one: on its way while this row is in the works
     if (tid == 0) nx = atomicAdd(&ctl->work[0], 1u);
@@ -585,7 +594,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 ? 6 : 4) void k_sym_dense
         // look-up in a ranked tile (R-MAT scale 17, searched wherever a tile was saved: row blocks 7.27 ms, now 6.83).
         const int total = tp->cum[kSpanBlocks];
         const int nt = tp->ntiles;
-        const int nr = (nt + kRunTiles - 1) / kRunTiles;
+        const int nr = (nt + run_tiles - 1) / run_tiles;
         const bool want_list = !count_only && total > 0 && list_cap > 0;
         // a short row with little deduplication becomes one searched tile and needs its columns; every
         // other row keeps its flag words as they are (no decoding here, and far less memory for rows
@@ -613,13 +622,13 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 ? 6 : 4) void k_sym_dense
         unsigned tb = 0, rb = 0;
         bool listed = false;
         if (want_list) {
-          if (need <= sl_left) {
-            at = sl_pos; sl_pos += need; sl_left -= need; listed = true;
+          if (need <= tp->sl_left) {
+            at = tp->sl_pos; tp->sl_pos += need; tp->sl_left -= need; listed = true;
           } else {   // (what is left of the old slab stays unused)
             const unsigned long long grab = need > list_slab ? need : list_slab;
             unsigned long long base;
             if (reserve_below(&ctl->list_cursor, grab, list_cap, base)) {
-              at = base; sl_pos = base + need; sl_left = grab - need; listed = true;
+              at = base; tp->sl_pos = base + need; tp->sl_left = grab - need; listed = true;
             } else if (grab != need && reserve_below(&ctl->list_cursor, need, list_cap, base)) {
               at = base; listed = true;   // (no room for a slab, but for the row alone)
             }
@@ -627,21 +636,21 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 ? 6 : 4) void k_sym_dense
         }
         bool room = true;
         if (nt > 0) {
-          if ((unsigned)nt > st_left) {
-            st_pos = atomicAdd(&ctl->tile_cursor, (unsigned)kTileSlab);
-            room = st_pos + (unsigned)kTileSlab <= tile_cap;
-            st_left = room ? (unsigned)kTileSlab : 0u;
+          if ((unsigned)nt > tp->st_left) {
+            tp->st_pos = atomicAdd(&ctl->tile_cursor, (unsigned)kTileSlab);
+            room = tp->st_pos + (unsigned)kTileSlab <= tile_cap;
+            tp->st_left = room ? (unsigned)kTileSlab : 0u;
           }
-          if (room && (unsigned)nr > sr_left) {
-            for (unsigned i = 0; i < sr_left; ++i) runs[sr_pos + i].count = 0;   // (slots left behind: empty records)
+          if (room && (unsigned)nr > tp->sr_left) {
+            for (unsigned i = 0; i < tp->sr_left; ++i) runs[tp->sr_pos + i].count = 0;   // (slots left behind: empty records)
             const unsigned grab = (unsigned)nr > rslab ? (unsigned)nr : rslab;
-            sr_pos = atomicAdd(&ctl->run_cursor, grab);
-            room = sr_pos + grab <= run_cap;
-            sr_left = room ? grab : 0u;
+            tp->sr_pos = atomicAdd(&ctl->run_cursor, grab);
+            room = tp->sr_pos + grab <= run_cap;
+            tp->sr_left = room ? grab : 0u;
           }
           if (room) {
-            tb = st_pos; st_pos += (unsigned)nt; st_left -= (unsigned)nt;
-            rb = sr_pos; sr_pos += (unsigned)nr; sr_left -= (unsigned)nr;
+            tb = tp->st_pos; tp->st_pos += (unsigned)nt; tp->st_left -= (unsigned)nt;
+            rb = tp->sr_pos; tp->sr_pos += (unsigned)nr; tp->sr_left -= (unsigned)nr;
           }
         }
         if (listed) tp->list_used += need;
@@ -667,8 +676,8 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 ? 6 : 4) void k_sym_dense
         } else if (tp->ndirect > 0) {
           atomicAdd(&ctl->direct_tiles, (unsigned)tp->ndirect);
         }
-        used_tiles += (unsigned)tp->ntiles;
-        used_runs += (unsigned)tp->nruns;
+        tp->used_tiles += (unsigned)tp->ntiles;
+        tp->used_runs += (unsigned)tp->nruns;
         if (last_span) next_row = nx < row_hi - row_lo ? perm[row_hi - 1 - nx] : -1;
       }
       __syncthreads();
@@ -678,10 +687,10 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 ? 6 : 4) void k_sym_dense
       if (nt > 0 || tp->nruns > 0) {
         if (tid < nt) tiles[tp->tile_base + tid] = tp->rec[tid];
         if (tid < tp->nruns) {   // (runs behind the tiles in use stay empty: count 0)
-          const int left = nt - tid * kRunTiles;
+          const int left = nt - tid * run_tiles;
           // (flag words: the position of the word of column 0, which may lie before the span's words)
           const long long lpos = lb < 0 ? -1LL : (tp->list_words ? (lb + kListBias) | kListFlagWords : lb - tp->span_out0 + kListBias);
-          runs[tp->run_base + tid] = RunRec{row, tp->tile_base + (unsigned)(tid * kRunTiles), left < 0 ? 0 : (left < kRunTiles ? left : kRunTiles), d, a0, lpos};
+          runs[tp->run_base + tid] = RunRec{row, tp->tile_base + (unsigned)(tid * run_tiles), left < 0 ? 0 : (left < run_tiles ? left : run_tiles), d, a0, lpos};
         }
       }
       if (lb >= 0 && tp->list_words) {
@@ -783,9 +792,9 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 ? 6 : 4) void k_sym_dense
     row = rs->s_row;
   }
   if (tid == 0) {
-    for (unsigned i = 0; i < sr_left; ++i) runs[sr_pos + i].count = 0;
-    if (used_tiles) atomicAdd(&ctl->tiles_used, used_tiles);
-    if (used_runs) atomicAdd(&ctl->runs_used, used_runs);
+    for (unsigned i = 0; i < tp->sr_left; ++i) runs[tp->sr_pos + i].count = 0;
+    if (tp->used_tiles) atomicAdd(&ctl->tiles_used, tp->used_tiles);
+    if (tp->used_runs) atomicAdd(&ctl->runs_used, tp->used_runs);
     if (tp->list_used) atomicAdd(&ctl->list_used, tp->list_used);
   }
   SPG_CLK(clk_mark(&rs->clk, 9); clk_flush(&rs->clk, ctl->clk[0]);)
@@ -795,5 +804,6 @@ template <int WAVES>
 constexpr size_t sym_dense_lds(int64_t flag_words) { return (size_t)flag_words * 4 + sizeof(RowScratch<WAVES>) + sizeof(TilePlan); }
 // Half a span of flag words (64 KB): up to that many columns two workgroups of 8 waves share a compute unit.
 constexpr int64_t kSymNarrowCols = (int64_t)kSymFlagWords * 16;
+constexpr int64_t kSymShortCols = (int64_t)kSymFlagWords * 8;
 
 }  // namespace spg

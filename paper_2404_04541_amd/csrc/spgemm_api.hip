@@ -32,7 +32,7 @@ using namespace spg;
 // a workgroup of the big kernels owns the whole LDS of a compute unit (160 KB)
 static_assert(num_tiles_lds<double, true>() <= 160 * 1024 && num_tiles_lds<float, true>() <= 160 * 1024, "numeric dense kernel exceeds LDS");
 static_assert(sym_dense_lds<16>(kSymFlagWords) <= 160 * 1024, "symbolic dense kernel exceeds LDS");
-static_assert(sym_dense_lds<8>(kSymNarrowCols / 32) <= 80 * 1024 && num_tiles_lds<double, false>() <= 80 * 1024 && num_tiles_lds<float, false>() <= 80 * 1024, "two workgroups on a compute unit");
+static_assert(sym_dense_lds<8>(kSymNarrowCols / 32) <= 80 * 1024 && sym_dense_lds<16>(kSymShortCols / 32) <= 80 * 1024 && num_tiles_lds<double, false>() <= 80 * 1024 && num_tiles_lds<float, false>() <= 80 * 1024, "two workgroups on a compute unit");
 static_assert(staged_lds<double>() <= 160 * 1024 && staged_lds<float>() <= 160 * 1024, "staged kernel exceeds LDS");
 
 // Pinned host memory where the symbolic kernels leave the control block for the host.  Allocating and releasing it costs 50 to
@@ -335,15 +335,21 @@ int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const sp
   return SPGEMM_OK;
 }
 
-// Workgroups of the dense symbolic kernel: those that are resident (registers for 24 waves on a compute unit, 160 KB of LDS).
-unsigned sym_dense_workgroups(spgemm_context* h, int64_t rows, int64_t cols) {
-  int64_t per_cu = 1;
-  if (cols <= kSymNarrowCols) {
-    per_cu = (int64_t)(160 * 1024 / sym_dense_lds<8>(sym_flag_words(cols)));
-    per_cu = per_cu < 3 ? per_cu : 3;
-  }
-  return grid_for(rows, 1, (int64_t)h->num_cus * per_cu);
+// The dense symbolic kernel's workgroups: waves of one, and how many are resident on the card.
+struct SymDense { int waves; size_t lds; unsigned groups; };
+SymDense sym_dense_shape(spgemm_context* h, int64_t rows, int64_t cols) {
+  const int64_t words = sym_flag_words(cols);
+  const int waves = cols <= kSymShortCols || cols > kSymNarrowCols ? 16 : 8;
+  const size_t lds = waves == 16 ? sym_dense_lds<16>(words) : sym_dense_lds<8>(words);
+  int64_t per_cu = (int64_t)(160 * 1024 / lds);
+  per_cu = per_cu < 32 / waves ? per_cu : 32 / waves;
+  return SymDense{waves, lds, grid_for(rows, 1, (int64_t)h->num_cus * per_cu)};
 }
+
+// Tiles of a row that a workgroup of the numeric kernel takes together: they share the set-up of the row's entries, but where
+// rows are few the heavy ones should not be one workgroup's work (about 200 rows a block, us for seven blocks of scale 15: 675 | 486 by
+// tile; 5266 rows of scale 14: 153 together, 161 by tile).
+int run_tiles_of(spgemm_context* h, int64_t rows) { return rows <= (int64_t)h->num_cus * 8 ? 1 : kRunTiles; }
 
 // Sizes and allocates what the dense kernels need beyond the per-row arrays: the tile and run
 // lists (from an upper bound of the number of tiles) and the table of block offsets of B.
@@ -364,9 +370,9 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
   const double weight = rows_d * blocks * kRankBlkBytes + (double)kRankEntryBytes * entries;
   // (+ a slab per workgroup of the symbolic kernel: what a workgroup has drawn and not used; a row whose runs do not fit
   // what is left of a run slab leaves fewer records behind than it takes, hence twice the runs)
-  const double wgs = (double)sym_dense_workgroups(h, (int64_t)rows_d, B->cols) + 1.0;
+  const double wgs = (double)sym_dense_shape(h, (int64_t)rows_d, B->cols).groups + 1.0;
   const double tiles = 2.0 * direct + 2.0 * weight / kTileBudget + 4.0 * rows_d * spans + 16.0 + wgs * kTileSlab;
-  const double runs = 2.0 * ((tiles - wgs * kTileSlab) / kRunTiles + rows_d * spans + 16.0) + wgs * kRunSlab;
+  const double runs = 2.0 * ((tiles - wgs * kTileSlab) / run_tiles_of(h, (int64_t)rows_d) + rows_d * spans + 16.0) + wgs * kRunSlab;
   if (tiles > 4.0e9) return fail(h, SPGEMM_UNSUPPORTED, "tile list of the dense workspace would exceed 2^32 records");
   *tile_cap = (unsigned)tiles;
   *run_cap = (unsigned)runs;
@@ -528,7 +534,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     sum_order(h, p, A, B, 1);
   }
   if (rows_dense > 0) {
-    hipLaunchKernelGGL(k_set_caps, dim3(1), dim3(64), 0, s, p->ctl, tile_cap, run_cap, p->col_list_cap, rows_dense, sym_dense_workgroups(h, rows_dense, B->cols));
+    hipLaunchKernelGGL(k_set_caps, dim3(1), dim3(64), 0, s, p->ctl, tile_cap, run_cap, p->col_list_cap, rows_dense, sym_dense_shape(h, rows_dense, B->cols).groups);
     if (p->blk_ptr) {
       Timer t(h, SPGEMM_K_BLOCK_PTR);
       const int64_t items = B->rows * (int64_t)p->blk_ptr_cols;
@@ -569,10 +575,9 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     }
     if (rows_dense > 0) {
       Timer t(h, SPGEMM_K_SYM_DENSE);
-      const bool narrow = B->cols <= kSymNarrowCols;
-      hipLaunchKernelGGL((narrow ? k_sym_dense<8> : k_sym_dense<16>), dim3(sym_dense_workgroups(h, rows_dense, B->cols)), dim3(narrow ? 512 : 1024),
-                         narrow ? sym_dense_lds<8>(sym_flag_words(B->cols)) : sym_dense_lds<16>(sym_flag_words(B->cols)), s, p->perm_sym, p->ctl, A->rowptr, A->colidx, B->rowptr, B->colidx, B->cols, p->ip, p->cnt, p->tiles, p->runs, p->col_list, h->direct_min,
-                         staged, h->search_ratio, p->blk_ptr, p->blk_ptr_cols, B->nnz);
+      const SymDense d = sym_dense_shape(h, rows_dense, B->cols);
+      hipLaunchKernelGGL((d.waves == 16 ? k_sym_dense<16> : k_sym_dense<8>), dim3(d.groups), dim3(d.waves * kWave), d.lds, s, p->perm_sym, p->ctl, A->rowptr, A->colidx, B->rowptr, B->colidx, B->cols, p->ip, p->cnt, p->tiles, p->runs, p->col_list, h->direct_min,
+                         staged, h->search_ratio, p->blk_ptr, p->blk_ptr_cols, B->nnz, run_tiles_of(h, rows_dense));
     }
     {
       Timer t(h, SPGEMM_K_BIN);
@@ -688,7 +693,7 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   if (rows_dense > 0) {
     Timer t(h, SPGEMM_K_NUM_DENSE);
     const bool plain = p->blk_ptr && p->all_listed && B->nnz < kTileMaxNnz;   // (the table is built for ascending rows only)
-    hipLaunchKernelGGL((plain ? k_num_tiles<T, false> : k_num_tiles<T, true>), dim3(grid_for(rows_dense, 1, (int64_t)h->num_cus * 2)), dim3(kTileThreads),
+    hipLaunchKernelGGL((plain ? k_num_tiles<T, false> : k_num_tiles<T, true>), dim3(grid_for(p->stats.dense_runs, 1, (int64_t)h->num_cus * 2)), dim3(kTileThreads),
                        (plain ? num_tiles_lds<T, false>() : num_tiles_lds<T, true>()), s, p->ctl, p->bin, p->tiles, p->runs, A->colidx, a_val, B->rowptr,
                        B->colidx, b_val, B->cols, p->blk_ptr, p->blk_ptr_cols, p->col_list, B->nnz, c_rp, c_col, c_val);
   }
