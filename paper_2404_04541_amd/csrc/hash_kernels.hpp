@@ -102,7 +102,7 @@ __device__ __forceinline__ void hash_rows(unsigned char* smem, unsigned wg, unsi
                                                const int32_t* __restrict__ b_col, const T* __restrict__ b_val,
                                                int* __restrict__ cnt, const int64_t* __restrict__ c_rp,
                                                int32_t* __restrict__ c_col, T* __restrict__ c_val, int64_t n_cols,
-                                               const int* __restrict__ record_of) {
+                                               const int* __restrict__ record_of, int most_ip) {
   constexpr int H = 1 << LOGH;
   const bool packable = n_cols <= (int64_t(1) << (31 - LOGH));   // column << LOGH stays below the pad key
   constexpr int kGroups = 256 / GROUP;
@@ -134,6 +134,9 @@ __device__ __forceinline__ void hash_rows(unsigned char* smem, unsigned wg, unsi
     // (wave-uniform) rows whose ranks the symbolic pass has recorded are done elsewhere
     if constexpr (GROUP == kWave && NUMERIC)
       if (record_of && live && ip_row[row] <= kSymHashSmall && record_of[row] >= 0) continue;
+    // (the same for the workgroup) rows of more products are done by their tiles
+    if constexpr (GROUP > kWave && NUMERIC)
+      if (ip_row[row] > most_ip) continue;
     for (int t = gl; t < H; t += GROUP) {
       keys[t] = kEmptyKey;
       if (NUMERIC) vals[t] = 0.0;
@@ -275,11 +278,11 @@ __global__ __launch_bounds__(256, GROUP > kWave ? 5 : 8) void k_hash(const int* 
                                                const int32_t* __restrict__ b_col, const T* __restrict__ b_val,
                                                int* __restrict__ cnt, const int64_t* __restrict__ c_rp,
                                                int32_t* __restrict__ c_col, T* __restrict__ c_val, int64_t n_cols,
-                                               const int* __restrict__ record_of) {
+                                               const int* __restrict__ record_of, int most_ip) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (ctl->error) return;
   hash_rows<GROUP, LOGH, T, NUMERIC>(smem, blockIdx.x, gridDim.x, perm, ctl, phase, bin, ip_row, a_rp, a_col, a_val, b_rp, b_col, b_val, cnt, c_rp, c_col, c_val,
-                                     n_cols, record_of);
+                                     n_cols, record_of, most_ip);
 }
 
 template <int GROUP, int LOGH, bool NUMERIC>
@@ -310,7 +313,7 @@ __global__ __launch_bounds__(256) void k_other_order(unsigned wgs0, unsigned wgs
     return;
   }
   wg -= wgs1;
-  hash_rows<64, 8, T, true>(smem, wg, wgs2, perm, ctl, 1, 2, ip_row, a_rp, a_col, a_val, b_rp, b_col, b_val, (int*)nullptr, c_rp, c_col, c_val, n_cols, (const int*)nullptr);
+  hash_rows<64, 8, T, true>(smem, wg, wgs2, perm, ctl, 1, 2, ip_row, a_rp, a_col, a_val, b_rp, b_col, b_val, (int*)nullptr, c_rp, c_col, c_val, n_cols, (const int*)nullptr, 0);
 }
 
 template <typename T>

@@ -129,6 +129,7 @@ struct spgemm_plan_s {
   Control* ctl = nullptr;
   int64_t scan_blocks = 0;
   int64_t recorded = 0;          // rows that have a record
+  int force = 0;                 // SPGEMM_OPT_FORCE_WORKSPACE of the symbolic phase
   bool flag_rows = false;        // classes 0 and 1 take the flag-list workspace
   bool all_listed = false;       // every row of the dense classes has its structure in the column list
   bool order_kept = false;       // the checksums of the order of the entries were taken
@@ -571,7 +572,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
         hipLaunchKernelGGL((k_hash<256, 12, T, false>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
                            lds_hash_large, s, p->perm_sym, p->ctl, 0, 3, p->ip, A->rowptr, A->colidx,
                            (const T*)nullptr, B->rowptr, B->colidx, (const T*)nullptr, p->cnt, (const int64_t*)nullptr,
-                           (int32_t*)nullptr, (T*)nullptr, B->cols, (const int*)nullptr);
+                           (int32_t*)nullptr, (T*)nullptr, B->cols, (const int*)nullptr, 0);
     }
     if (rows_dense > 0) {
       Timer t(h, SPGEMM_K_SYM_DENSE);
@@ -615,7 +616,9 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   const size_t lds_hash_small = hash_lds_bytes<64, 8, true>();
   const size_t lds_hash_large = hash_lds_bytes<256, 11, true>();
   const int64_t* hist = p->stats.num_bin_rows;
-  if (hist[4] + hist[5] + hist[6] > 0) hipLaunchKernelGGL(k_reset_numeric_work, dim3(1), dim3(64), 0, s, p->ctl);
+  // (rows of class 3 with more products than the symbolic hash takes have tiles: those do them, unless hashing is asked for)
+  const bool tiles3 = p->force != 2;
+  if (hist[4] + hist[5] + hist[6] + (tiles3 ? hist[3] : 0) > 0) hipLaunchKernelGGL(k_reset_numeric_work, dim3(1), dim3(64), 0, s, p->ctl);
   // (the words were sorted for the rows of the symbolic bin: they serve when the numeric one holds the same rows)
   const bool words0 = hist[0] && p->esc_words[0] && hist[0] == p->stats.sym_bin_rows[0];
   const bool words1 = hist[1] && p->esc_words[1] && hist[1] == p->stats.sym_bin_rows[1];
@@ -673,24 +676,30 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
     if (hist[2] > p->recorded)
       hipLaunchKernelGGL((k_hash<64, 8, T, true>), dim3(grid_for(hist[2], 4, cap_small)), dim3(256), lds_hash_small, s,
                          p->perm_num, p->ctl, 1, 2, p->ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, (int*)nullptr,
-                         c_rp, c_col, c_val, B->cols, p->recorded ? p->record_of : nullptr);
+                         c_rp, c_col, c_val, B->cols, p->recorded ? p->record_of : nullptr, 0);
     if (check) {
       const unsigned w0 = words0 ? grid_for(hist[0], 16, cap_small) : 0, w1 = words1 ? grid_for(hist[1], 4, cap_small) : 0, w2 = p->recorded ? grid_for(hist[2], 4, cap_small) : 0;
       hipLaunchKernelGGL(k_other_order<T>, dim3(w0 + w1 + w2), dim3(256), other_order_lds_bytes<T>(), s, w0, w1, w2, p->perm_num, p->ctl, p->ip, A->rowptr,
                          A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, pack128, B->nnz, B->cols, inside ? 1 : 0);
     }
-    if (hist[3])
-      hipLaunchKernelGGL((k_hash<256, 11, T, true>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
-                         lds_hash_large, s, p->perm_num, p->ctl, 1, 3, p->ip, A->rowptr, A->colidx, a_val, B->rowptr,
-                         B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, B->cols, (const int*)nullptr);
+    // (rows of class 3 that have tiles, the others)
+    if (hist[3] && (!tiles3 || p->stats.sym_bin_rows[2] + p->stats.sym_bin_rows[3] > 0)) {
+      const int most_ip = tiles3 ? kSymHashLarge : 0x7fffffff;
+      if (tiles3 && B->cols <= kRowTileMaxCols)
+        hipLaunchKernelGGL(k_row_tiles<T>, dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(kRowTileWaves * kWave), row_tile_lds<T>(B->cols), s,
+                           p->perm_num, p->ctl, p->ip, most_ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, B->nnz, B->cols, c_rp, c_col, c_val);
+      else
+        hipLaunchKernelGGL((k_hash<256, 11, T, true>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
+                           lds_hash_large, s, p->perm_num, p->ctl, 1, 3, p->ip, A->rowptr, A->colidx, a_val, B->rowptr,
+                           B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, B->cols, (const int*)nullptr, most_ip);
+    }
   }
   if (hist[4]) {
     Timer t(h, SPGEMM_K_NUM_STAGED);
     hipLaunchKernelGGL(k_num_staged<T>, dim3(grid_for(hist[4], 1, h->num_cus)), dim3(kStThreads), staged_lds<T>(), s, p->perm_num,
                        p->ctl, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, B->cols, c_rp, c_col, c_val);
   }
-  const int64_t rows_dense = hist[5] + hist[6];
-  if (rows_dense > 0) {
+  if (hist[5] + hist[6] > 0 || (tiles3 && hist[3] > 0 && p->stats.dense_runs > 0)) {
     Timer t(h, SPGEMM_K_NUM_DENSE);
     const bool plain = p->blk_ptr && p->all_listed && B->nnz < kTileMaxNnz;   // (the table is built for ascending rows only)
     hipLaunchKernelGGL((plain ? k_num_tiles<T, false> : k_num_tiles<T, true>), dim3(grid_for(p->stats.dense_runs, 1, (int64_t)h->num_cus * 2)), dim3(kTileThreads),
@@ -718,6 +727,7 @@ int symbolic(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B, int64_
   p->h = h;
   p->m = A->rows; p->k = A->cols; p->n = B->cols; p->nnz_a = A->nnz; p->nnz_b = B->nnz; p->dtype = A->dtype;
   const int64_t m = p->m;
+  p->force = h->force;
   p->flag_rows = flag_rows_ok(h, B);
   p->scan_blocks = m > 0 ? ceil_div(m, kScanTile) : 0;
   size_t off = 0;

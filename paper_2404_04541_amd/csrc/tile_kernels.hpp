@@ -23,16 +23,16 @@ constexpr int kTileThreads = 1024;
 constexpr int kTileWaves = kTileThreads / kWave;
 constexpr int64_t kTileMaxNnz = int64_t(1) << 30;   // plain: a piece's start shares 32 bits with two others
 
-template <typename T, bool GENERAL>
+template <typename T, bool GENERAL, int WAVES = kTileWaves>
 struct TileScratch {
   using Start = std::conditional_t<GENERAL, unsigned long long, unsigned>;
-  static constexpr int kPieces = GENERAL ? 512 : 768;   // pieces of B rows described at a time
+  static constexpr int kPieces = WAVES < kTileWaves ? WAVES * kWave : (GENERAL ? 512 : 768);   // pieces of B rows described at a time
   Start s[kPieces];               // a piece's first B entry, shifted left by two; entries missing in its last quad below
   int cpre[kPieces + 1];          // exclusive prefix of the pieces' quad counts
   T av[kPieces];                  // a_ik of the piece
   TileRec rec[kRunTiles];
   RunRec rr;                      // the run in the works
-  int red[2 * kTileWaves];
+  int red[2 * WAVES];
   int s_run;
   int split;                      // quads before the pieces of the second round
   SPG_CLK(ClkLds clk;)
@@ -82,19 +82,19 @@ __device__ __forceinline__ void direct_out(const double* acc, const unsigned* fl
 
 // Visits every product of np pieces (nq quads) once, g(quad) per lane: as quad_pass, with the pieces' values and without their
 // lengths (a piece's last quad says how many of its entries are missing).
-template <bool WITH_VALUES, typename T, bool GENERAL, class G>
-__device__ __forceinline__ void tile_pass(int np, int nq, const TileScratch<T, GENERAL>* ts, const int32_t* __restrict__ b_col,
+template <int WAVES, bool WITH_VALUES, typename T, bool GENERAL, class G>
+__device__ __forceinline__ void tile_pass(int np, int nq, const TileScratch<T, GENERAL, WAVES>* ts, const int32_t* __restrict__ b_col,
                                           const T* __restrict__ b_val, int64_t b_nnz, G g) {
   using Start = typename TileScratch<T, GENERAL>::Start;
   const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int nb = (nq + kWave - 1) >> 6;
-  const int per = (nb + kTileWaves - 1) / kTileWaves;
+  const int per = (nb + WAVES - 1) / WAVES;
   int c = wave * per * kWave;
   const int cend = c + per * kWave < nq ? c + per * kWave : nq;
   if (c >= cend) return;
   int p;   // last piece whose first quad is <= c: among every sixteenth piece first, then among the sixteen
   {
-    static_assert(TileScratch<T, GENERAL>::kPieces <= 16 * kWave, "64 steps of sixteen pieces");
+    static_assert(TileScratch<T, GENERAL, WAVES>::kPieces <= 16 * kWave, "64 steps of sixteen pieces");
     const int i0 = lane * 16;
     const int hi = __popcll(__ballot(i0 < np && ts->cpre[i0 < np ? i0 : 0] <= c)) - 1;
     const int i1 = hi * 16 + lane;
@@ -131,22 +131,23 @@ __device__ __forceinline__ void tile_pass(int np, int nq, const TileScratch<T, G
   }
 }
 
-// The tiles of one run; k, av: this thread's A entry, in rows of at most kTileThreads of them.
-template <typename T, bool GENERAL>
-__device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL>* ts, unsigned char* tile, bool sorted, const int32_t* __restrict__ a_col,
+// The tiles of one run; k, av: this thread's A entry, in rows of at most kThreads of them.
+template <int WAVES, typename T, bool GENERAL>
+__device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL, WAVES>* ts, unsigned char* tile, bool sorted, const int32_t* __restrict__ a_col,
                                          const T* __restrict__ a_val, const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col,
                                          const T* __restrict__ b_val, int64_t n_cols, const int* __restrict__ bp, int nb1,
                                          const int32_t* __restrict__ col_list, int64_t b_nnz, int64_t out_row, int32_t* __restrict__ c_col,
                                          T* __restrict__ c_val, int k, T av) {
-  using Start = typename TileScratch<T, GENERAL>::Start;
-  constexpr int kPieces = TileScratch<T, GENERAL>::kPieces;
+  using Start = typename TileScratch<T, GENERAL, WAVES>::Start;
+  constexpr int kPieces = TileScratch<T, GENERAL, WAVES>::kPieces;
+  constexpr int kThreads = WAVES * kWave;
   const int tid = threadIdx.x;
   // the row's structure in the plan: its columns, its flag words, or (general) none
   const bool have = !GENERAL || rr.list >= 0;
   const bool have_words = have && (rr.list & kListFlagWords) != 0;
   const long long list_at = (rr.list & (kListFlagWords - 1)) - kListBias;   // entry 0 of the row, or the span's kept structure
-  const int nseg = (rr.d + kTileThreads - 1) / kTileThreads;
-  // this thread's A entry (rows of at most kTileThreads entries keep it for the whole run) and the place of the coming tile in
+  const int nseg = (rr.d + kThreads - 1) / kThreads;
+  // this thread's A entry (rows of at most kThreads entries keep it for the whole run) and the place of the coming tile in
   // its B row
   unsigned crs = 0;
   int pf0 = 0, pf1 = 0;
@@ -188,7 +189,7 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
     auto products = [&](auto with_values, auto acc) {
       for (int sg = 0; sg < nseg; ++sg) {
         if (nseg > 1) {
-          const int e = sg * kTileThreads + tid;
+          const int e = sg * kThreads + tid;
           len = 0;
           if (e < rr.d) {
             const int ke = a_col[rr.a0 + e];
@@ -206,12 +207,12 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
           }
         }
         int idx, cpre, np, nq;
-        block_excl_scan2<kTileWaves>(len > 0 ? 1 : 0, (len + 3) >> 2, idx, cpre, np, nq, ts->red);
+        block_excl_scan2<WAVES>(len > 0 ? 1 : 0, (len + 3) >> 2, idx, cpre, np, nq, ts->red);
         np = uni(np);
         nq = uni(nq);
         SPG_CLK(clk_add(&ts->clk, 20, (unsigned long long)nq); clk_add(&ts->clk, 21, (unsigned long long)np);)
         for (int i0 = 0; i0 < np; i0 += kPieces) {   // (more pieces than are described at a time: the first of them, then the others)
-          static_assert(2 * kPieces >= kTileThreads, "two rounds");
+          static_assert(2 * kPieces >= kThreads, "two rounds");
           const int i1 = np < i0 + kPieces ? np : i0 + kPieces;
           const int q0 = i0 ? uni(ts->split) : 0;
           if (len > 0) {
@@ -225,7 +226,7 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
           if (tid == 0 && i1 == np) ts->cpre[i1 - i0] = nq - q0;
           __syncthreads();
           const int q1 = i1 == np ? nq : uni(ts->split);
-          tile_pass<decltype(with_values)::value, T, GENERAL>(i1 - i0, q1 - q0, ts, b_col, b_val, b_nnz, acc);
+          tile_pass<WAVES, decltype(with_values)::value, T, GENERAL>(i1 - i0, q1 - q0, ts, b_col, b_val, b_nnz, acc);
           __syncthreads();
         }
       }
@@ -240,7 +241,7 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
       int* cols = reinterpret_cast<int*>(tile);
       double* acc = reinterpret_cast<double*>(tile + (((size_t)count * 4 + 7) & ~(size_t)7));
       const int32_t* lst = col_list + list_at + tr.out;
-      for (int j = tid; j < count; j += kTileThreads) {
+      for (int j = tid; j < count; j += kThreads) {
         const int c = stream_load(&lst[j]);
         cols[j] = c;
         acc[j] = 0.0;
@@ -266,14 +267,14 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
             __hip_atomic_fetch_add(&acc[lo[i]], (double)q.a * (double)q.b.v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       });
       SPG_CLK(clk_mark(&ts->clk, 11);)
-      for (int r = tid; r < count; r += kTileThreads) stream_store(&c_val[out + r], (T)acc[r]);
+      for (int r = tid; r < count; r += kThreads) stream_store(&c_val[out + r], (T)acc[r]);
       SPG_CLK(clk_mark(&ts->clk, 12);)
     } else if (direct) {
       double* acc = reinterpret_cast<double*>(tile);                      // kBlkCols sums, indexed by column
       unsigned* flags = reinterpret_cast<unsigned*>(tile + (size_t)kBlkCols * 8);   // kBlkCols / 32
       {
         double2* a2 = reinterpret_cast<double2*>(acc);
-        for (int r = tid; r < kBlkCols / 2; r += kTileThreads) a2[r] = make_double2(0.0, 0.0);
+        for (int r = tid; r < kBlkCols / 2; r += kThreads) a2[r] = make_double2(0.0, 0.0);
       }
       if (tid < kBlkWords) {   // (the last block of the matrix may be cut short: no flag words are kept behind its end)
         const int64_t span_c0 = (int64_t)(tr.b0 / kSpanBlocks) * kSpanBlocks * kBlkCols;
@@ -292,7 +293,7 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
           }
       });
       SPG_CLK(clk_mark(&ts->clk, 8);)
-      direct_out<kTileWaves>(acc, flags, t_lo, out, c_col, c_val);
+      direct_out<WAVES>(acc, flags, t_lo, out, c_col, c_val);
       SPG_CLK(clk_mark(&ts->clk, 9);)
     } else {
       const int nw = (tr.b1 - tr.b0) * kBlkWords;                         // 32-bit flag words
@@ -312,18 +313,18 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
         const int ngrp = nw / kGrpWords;
         const int nw_kept = (int)((t_hi - t_lo + 31) >> 5);   // (the last block of the matrix may be cut short)
         constexpr int kGrpBatch = 4;
-        for (int g0 = wave; g0 < ngrp; g0 += kTileWaves * kGrpBatch) {
+        for (int g0 = wave; g0 < ngrp; g0 += WAVES * kGrpBatch) {
           int wd[kGrpBatch], rk[kGrpBatch];
 #pragma unroll
           for (int i = 0; i < kGrpBatch; ++i) {
-            const int g = g0 + i * kTileWaves;
+            const int g = g0 + i * WAVES;
             const int w = g * kGrpWords + lane;
             wd[i] = (g < ngrp && w < nw_kept) ? stream_load(&words[w]) : 0;
             rk[i] = g < ngrp ? ranks[g] : 0;
           }
 #pragma unroll
           for (int i = 0; i < kGrpBatch; ++i) {
-            const int g = g0 + i * kTileWaves;
+            const int g = g0 + i * WAVES;
             if (g < ngrp) {
               const int w = g * kGrpWords + lane;
               unsigned bits = (unsigned)wd[i];
@@ -340,13 +341,13 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
           }
         }
         __syncthreads();
-        for (int r = tid; r < count; r += kTileThreads) stream_store(&c_col[out + r], stage[r]);
+        for (int r = tid; r < count; r += kThreads) stream_store(&c_col[out + r], stage[r]);
         __syncthreads();
-        for (int r = tid; r < count; r += kTileThreads) acc[r] = 0.0;
+        for (int r = tid; r < count; r += kThreads) acc[r] = 0.0;
         SPG_CLK(clk_mark(&ts->clk, 15); clk_add(&ts->clk, 17, 1);)
       } else if (!have) {
         // a pass over the products: which columns of the tile exist in the row
-        for (int w = tid; w < nw; w += kTileThreads) fc[w] = make_uint2(0u, 0u);
+        for (int w = tid; w < nw; w += kThreads) fc[w] = make_uint2(0u, 0u);
         products(std::false_type{}, [&](const Quad<T>& q) {
 #pragma unroll
           for (int i = 0; i < 4; ++i)
@@ -360,7 +361,7 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
         // the columns are decoded from the flag words into the space of the sums, by rank, and
         // leave from there as one coalesced run of C's column indices
         const int wave = uni(tid >> 6), lane = tid & 63;
-        const int wper = ((nw + kTileThreads - 1) / kTileThreads) * kWave;
+        const int wper = ((nw + kThreads - 1) / kThreads) * kWave;
         const int wbase = wave * wper;
         int in_share = 0;
         for (int i = lane; i < wper; i += kWave) {
@@ -372,7 +373,7 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
         __syncthreads();
         int running = 0;
 #pragma unroll
-        for (int w = 0; w < kTileWaves; ++w) running += w < wave ? ts->red[w] : 0;
+        for (int w = 0; w < WAVES; ++w) running += w < wave ? ts->red[w] : 0;
         for (int i0 = 0; i0 < wper; i0 += kWave) {
           const int w = wbase + i0 + lane;
           unsigned bits = w < nw ? fc[w].x : 0u;
@@ -389,19 +390,19 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
           }
         }
         __syncthreads();
-        for (int r = tid; r < count; r += kTileThreads) stream_store(&c_col[out + r], stage[r]);
+        for (int r = tid; r < count; r += kThreads) stream_store(&c_col[out + r], stage[r]);
         __syncthreads();
-        for (int r = tid; r < count; r += kTileThreads) acc[r] = 0.0;
+        for (int r = tid; r < count; r += kThreads) acc[r] = 0.0;
         SPG_CLK(clk_mark(&ts->clk, 13);)
       } else {
         // the symbolic phase left the tile's columns (ascending) in the plan: flag bits and ranks
         // come from that list, and the list is this tile's run of C's column indices
         const int32_t* lst = col_list + list_at + tr.out;
-        for (int w = tid; w < nw; w += kTileThreads) fc[w] = make_uint2(0u, 0u);
-        for (int r = tid; r < count; r += kTileThreads) acc[r] = 0.0;
+        for (int w = tid; w < nw; w += kThreads) fc[w] = make_uint2(0u, 0u);
+        for (int r = tid; r < count; r += kThreads) acc[r] = 0.0;
         __syncthreads();
         SPG_CLK(clk_mark(&ts->clk, 3); clk_add(&ts->clk, 17, 1);)
-        for (int j = tid; j < count; j += kTileThreads) {
+        for (int j = tid; j < count; j += kThreads) {
           const int c = stream_load(&lst[j]);
           int prev = __shfl_up(c, 1, kWave);
           if ((tid & 63) == 0) prev = j > 0 ? lst[j - 1] : -1;   // left neighbour of the wave's first entry
@@ -427,7 +428,7 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
       });
       SPG_CLK(clk_mark(&ts->clk, 5);)
       // compress: sums and columns are already in ascending column order
-      for (int r = tid; r < count; r += kTileThreads) stream_store(&c_val[out + r], (T)acc[r]);
+      for (int r = tid; r < count; r += kThreads) stream_store(&c_val[out + r], (T)acc[r]);
       SPG_CLK(clk_mark(&ts->clk, 6);)
     }
   }
@@ -491,12 +492,57 @@ __global__ __launch_bounds__(kTileThreads, GENERAL ? 4 : 8) void k_num_tiles(Con
       k = a_col[rr.a0 + tid];
       av = a_val[rr.a0 + tid];
     }
-    if (cls < 5 || cls > 6) continue;   // the row's numeric class is not this kernel's
+    if (cls != 3 && cls != 5 && cls != 6) continue;   // the row's numeric class is not this kernel's
     __syncthreads();
     SPG_CLK(clk_mark(&ts->clk, 0); clk_add(&ts->clk, 16, 1);)
-    tile_run<T, GENERAL>(rr, ts, tile, sorted, a_col, a_val, b_rp, b_col, b_val, n_cols, bp, nb1, col_list, b_nnz, out_row, c_col, c_val, k, av);
+    tile_run<kTileWaves, T, GENERAL>(rr, ts, tile, sorted, a_col, a_val, b_rp, b_col, b_val, n_cols, bp, nb1, col_list, b_nnz, out_row, c_col, c_val, k, av);
   }
   SPG_CLK(clk_mark(&ts->clk, 14); clk_flush(&ts->clk, ctl->clk[1]);)
+}
+
+// The rows of numeric class 3 without a tile in the plan (at most kSymHashLarge products), where the matrix has few columns: a row
+// is one tile without structure, a workgroup of four waves each, several on a compute unit.  Marking the columns and ranking
+// them by counting costs two passes over the products, the hash workspace its table, the slowest of 64 compare-and-swap loops
+// and a sort: us hash (all rows of the class) | these kernels (with the rows that have tiles in k_num_tiles): R-MAT scale 14 (fp32)
+// 101 | 46 + 2, of 5003 x 3001 x 7777 rows in any order 70 | 22 + 6, whole call of the numeric phase at scale 11 (fp64) 85 | 57.
+// Up to 65536 columns (16 KB of flag words and ranks, four workgroups on a compute unit); wider matrices take the hash workspace.
+constexpr int kRowTileWaves = 4;
+constexpr int64_t kRowTileMaxCols = 8 * kBlkCols;
+template <typename T>
+__host__ __device__ constexpr size_t row_tile_bytes(int64_t n_cols) {   // flag words and ranks, sums
+  return (size_t)((n_cols + kBlkCols - 1) / kBlkCols) * kRankBlkBytes + (size_t)kNumHashLarge * 8;
+}
+template <typename T>
+constexpr size_t row_tile_lds(int64_t n_cols) { return row_tile_bytes<T>(n_cols) + sizeof(TileScratch<T, true, kRowTileWaves>); }
+
+template <typename T>
+__global__ __launch_bounds__(kRowTileWaves * kWave, 4) void k_row_tiles(const int* __restrict__ perm, const Control* __restrict__ ctl, const int* __restrict__ ip_row, int most_ip,
+                                                                        const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
+                                                                        const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
+                                                                        const int32_t* __restrict__ b_col, const T* __restrict__ b_val, int64_t b_nnz, int64_t n_cols,
+                                                                        const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  TileScratch<T, true, kRowTileWaves>* ts = reinterpret_cast<TileScratch<T, true, kRowTileWaves>*>(smem + row_tile_bytes<T>(n_cols));
+  if (ctl->error) return;
+  const bool sorted = ctl->b_sorted != 0;
+  const unsigned first = ctl->offset[1][3], nrows = ctl->offset[1][4] - first;
+  const int tid = threadIdx.x;
+  for (unsigned i = blockIdx.x; i < nrows; i += gridDim.x) {
+    const int row = perm[first + i];
+    if (ip_row[row] > most_ip) continue;   // done by its tiles
+    const int64_t a0 = a_rp[row], out = c_rp[row];
+    const int d = (int)(a_rp[row + 1] - a0);
+    const int64_t n = c_rp[row + 1] - out;
+    const int cnt = n < kNumHashLarge ? (int)n : kNumHashLarge;
+    if (tid == 0) ts->rec[0] = TileRec{0, (int)((n_cols + kBlkCols - 1) >> kBlkShift), cnt, 0};
+    int k = 0;
+    T av = T(0);
+    if (d <= kRowTileWaves * kWave && tid < d) { k = a_col[a0 + tid]; av = a_val[a0 + tid]; }
+    __syncthreads();
+    tile_run<kRowTileWaves, T, true>(RunRec{row, 0, 1, d, a0, -1}, ts, smem, sorted, a_col, a_val, b_rp, b_col, b_val, n_cols, (const int*)nullptr, 0,
+                                     (const int32_t*)nullptr, b_nnz, out, c_col, c_val, k, av);
+    __syncthreads();
+  }
 }
 
 template <typename T, bool GENERAL>

@@ -1,0 +1,38 @@
+"""Rows of numeric class 3 (193 to 1536 entries): as tiles without structure up to 65536 columns (at most 1536 products), by their
+tiles (more products), by the hash workspace (wider matrices, or on request); few and many entries of A, any order, repeats."""
+import numpy as np
+import pytest
+
+from paper_2404_04541_amd import workloads as W
+from helpers import gpu_product, assert_matches_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("cols", [1537, 8192, 8193, 65536, 65537])
+@pytest.mark.parametrize("ordered", [True, False])
+def test_rows_of_class_3(cols, dtype, ordered):
+    rng = np.random.default_rng(cols)
+    k = 1300
+    lens = np.concatenate([[1, 2, 255, 256, 257, 700, 1200], rng.integers(20, 120, 120)])
+    a_cols = [rng.permutation(k)[:n] for n in lens]
+    A = W.CSR(len(lens), k, np.concatenate([[0], np.cumsum(lens)]).astype(np.int64), np.concatenate(a_cols).astype(np.int32),
+              W.draw_values(int(lens.sum()), -1.0, 1.0, dtype, 1, 1))
+    for per in (1, 11, 24):   # products per entry of A; the columns of a row of B lie within a stretch of 1400 or less
+        b = []
+        for i in range(k):
+            c = (int(rng.integers(0, 8)) + np.arange(per) * 50 + 13 * (i % 97)) % 1500
+            if not ordered:
+                c = rng.permutation(np.concatenate([c[: per // 2], c[: per - per // 2]]))
+            b.append(np.sort(c) + (cols - 1500) if ordered else c + (cols - 1500))
+        B = W.CSR(k, cols, np.arange(k + 1, dtype=np.int64) * per, np.concatenate(b).astype(np.int32),
+                  W.draw_values(k * per, -1.0, 1.0, dtype, 2, 1))
+        ref = None
+        for force in (0, 2):   # 2: the hash workspace
+            got = gpu_product(A, B, force=force)
+            ref = assert_matches_oracle(A, B, got, ref=ref, what=f"{cols} columns, rows of {per}, force {force}")
+        in_class = (ref.cnt > 192) & (ref.ip > 128)   # (no row reaches 1537 entries)
+        assert got[3]["num_bin_rows"][3] == int(in_class.sum()) > 0
+        if per == 11:
+            assert bool(((ref.ip > 1536) & in_class).any()) and bool(((ref.ip <= 1536) & in_class).any())
