@@ -47,21 +47,32 @@ __device__ __forceinline__ unsigned long long wave_sum64(unsigned long long v) {
   return s;
 }
 
-// Adds one row per lane (bin < 0: none) to the bin populations in LDS, the lanes of a bin together: atomics of 64 lanes on the
-// same counter are executed one after the other.  hnz may be null.
-__device__ __forceinline__ void add_to_bins(int bin, unsigned long long ip, unsigned nnz, unsigned* hist, unsigned long long* hip, unsigned long long* hnz) {
-  unsigned long long left = __ballot(bin >= 0);
-  while (left) {
-    const int v = __builtin_amdgcn_readlane(bin, __ffsll((long long)left) - 1);
-    const unsigned long long mine = __ballot(bin == v);
-    const unsigned long long s = wave_sum64(bin == v ? ip : 0ULL);
-    const unsigned long long z = hnz ? wave_sum64(bin == v ? (unsigned long long)nnz : 0ULL) : 0ULL;
-    if (lane_id() == 0) {
-      atomicAdd(&hist[v], (unsigned)__popcll(mine));
-      if (s) atomicAdd(&hip[v], s);
-      if (z) atomicAdd(&hnz[v], z);
+// Adds N rows per lane (bin < 0: none) to the bin populations in LDS, the lanes and rows of a bin together: atomics of 64 lanes on
+// the same counter are executed one after the other.  hnz may be null.  (Four rows a lane at a time, and the bins by number instead of
+// one after another as they come: k_classify_numeric for 16384 rows of a power-law graph 13.5 -> 6.7 us.)
+template <int N>
+__device__ __forceinline__ void add_to_bins(const int (&bin)[N], const unsigned long long (&ip)[N], const unsigned (&nnz)[N], unsigned* hist,
+                                            unsigned long long* hip, unsigned long long* hnz) {
+#pragma unroll
+  for (int v = 0; v < kNumBins; ++v) {
+    unsigned rows = 0;
+    unsigned long long p = 0, z = 0;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      rows += (unsigned)__popcll(__ballot(bin[u] == v));
+      if (bin[u] == v) { p += ip[u]; z += nnz[u]; }
     }
-    left &= ~mine;
+    if (rows == 0) continue;
+    if (v == kEmptyBin) { p = 0; z = 0; }
+    else {
+      p = wave_sum64(p);
+      if (hnz) z = wave_sum64(z);
+    }
+    if (lane_id() == 0) {
+      atomicAdd(&hist[v], rows);
+      if (p) atomicAdd(&hip[v], p);
+      if (hnz && z) atomicAdd(&hnz[v], z);
+    }
   }
 }
 
@@ -104,8 +115,9 @@ __device__ __forceinline__ void validate_b(int part, int parts, int64_t rows, in
 // descriptions written 0.64), a chain of three loads where there are few rows.
 // The first `parts` workgroups check B.  The others count the products of A's rows: a workgroup takes chunks of `chunk_rows`
 // consecutive rows (a chunk of hub rows holds a large share of all entries, hence the widest workgroup): the chunk's A
-// entries are read coalesced, each entry adds the length of its B row to its row's counter in LDS, the lanes that hold the
-// same row together (27 entries a row: 27 additions to one address, one after the other, otherwise).
+// entries are read coalesced, the lengths of their B rows are summed up over the workgroup, and a row takes the difference of the sums
+// at its ends (an addition to the row's counter per entry, after a bisection for its row, was bound by LDS: 27-point
+// stencil of 128^3 rows 494 -> 377 us, 10^7 entries in rows of 2.4 128 -> 95 us, R-MAT scale 14 27 -> 20 us, scale 19 442 -> 400 us).
 // desc (optional): start and length of every A entry's B row, for the kernels of short rows.
 // Writes ip (saturated to int32), the symbolic bin, zero counts for rows without products.
 __global__ __launch_bounds__(kCountThreads) void k_count_rows(int parts, int64_t b_cols, int64_t b_nnz, const int32_t* __restrict__ b_col, int64_t m,
@@ -116,6 +128,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int parts, int64_t
                                                     Control* ctl, int force, int row_block, unsigned long long* __restrict__ desc) {
   __shared__ long long rp[kCountMaxRows + 1];
   __shared__ unsigned long long ipl[kCountMaxRows];
+  __shared__ __align__(16) unsigned pre[kCountThreads * 4 + 1];   // products before every entry of a round
   __shared__ unsigned hist[kNumBins];
   __shared__ unsigned long long hip[kNumBins];
   __shared__ int sums[2][kCountThreads / kWave];
@@ -157,20 +170,23 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int parts, int64_t
     }
     const long long lo = rp[0], hi = rp[nr];
     bool badcol = false;
-    // four entries per thread and round, so that their (dependent) loads overlap
-    for (long long q0 = lo; q0 < hi; q0 += kCountThreads * 4) {   // (all threads together: lanes are combined below)
-      const long long p0 = q0 + tid;
+    // four consecutive entries per thread and round, so that their (dependent) loads overlap
+    for (long long q0 = lo; q0 < hi; q0 += kCountThreads * 4) {   // (all threads together)
+      const long long p0 = q0 + tid * 4;
       int k[4];
       long long len[4];
       int64_t start[4];
+      if (p0 + 4 <= hi) {
+        const Run<int32_t, 4> r = load_run<int32_t, 4>(a_col + p0);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const long long p = p0 + u * kCountThreads;
-        k[u] = p < hi ? a_col[p] : -1;
+        for (int u = 0; u < 4; ++u) k[u] = r.v[u];
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) k[u] = p0 + u < hi ? a_col[p0 + u] : -1;
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const long long p = p0 + u * kCountThreads;
+        const long long p = p0 + u;
         len[u] = 0;
         start[u] = 0;
         if (p < hi) {
@@ -181,37 +197,41 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int parts, int64_t
           if (len[u] < 0) { badcol = true; len[u] = 0; }
         }
       }
+      bool fits = true;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const long long p = p0 + u * kCountThreads;
-        if (q0 + u * kCountThreads >= hi) break;
-        if (desc && p < hi) desc[p] = make_desc(start[u], len[u]);
-        // row of entry p: last t with rp[t] <= p
-        int a = 0, b = nr;
-        while (b - a > 1) {
-          const int mid = (a + b) >> 1;
-          if (rp[mid] <= p) a = mid; else b = mid;
-        }
-        if (__any(len[u] >= (1LL << 27))) {   // (sixteen of these need more than 32 bits)
-          if (len[u] > 0) atomicAdd(&ipl[a], (unsigned long long)len[u]);
-          continue;
-        }
-        // inside a DPP row of 16 lanes the entries of a row are neighbours: the last of them adds what all have
-        const int row = p < hi ? a : -1;
-        unsigned sum = (unsigned)len[u];
-        auto below = [&](auto step) {
-          constexpr int kStep = decltype(step)::value;
-          const int r = __builtin_amdgcn_update_dpp(-2, row, 0x110 + kStep, 0xf, 0xf, false);
-          const unsigned l = (unsigned)__builtin_amdgcn_update_dpp(0, (int)sum, 0x110 + kStep, 0xf, 0xf, false);
-          if (r == row) sum += l;
-        };
-        below(std::integral_constant<int, 1>{});
-        below(std::integral_constant<int, 2>{});
-        below(std::integral_constant<int, 4>{});
-        below(std::integral_constant<int, 8>{});
-        const int next = __builtin_amdgcn_update_dpp(-2, row, 0x101, 0xf, 0xf, false);
-        if (next != row && sum > 0) atomicAdd(&ipl[a], (unsigned long long)sum);
+        if (desc && p0 + u < hi) desc[p0 + u] = make_desc(start[u], len[u]);
+        fits = fits && len[u] < (1LL << 19);   // (4096 of these need less than 32 bits)
       }
+      const int l0 = (int)len[0], l1 = l0 + (int)len[1], l2 = l1 + (int)len[2], l3 = l2 + (int)len[3];
+      const int incl = wave_incl_scan(fits ? l3 : 0);
+      if (lane_id() == kWave - 1) sums[0][tid >> 6] = incl;
+      if (__syncthreads_or(!fits)) {   // some row of B is huge: by row of the entry, the last t with rp[t] <= p
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const long long p = p0 + u;
+          if (p >= hi || len[u] <= 0) continue;
+          int a = 0, b = nr;
+          while (b - a > 1) {
+            const int mid = (a + b) >> 1;
+            if (rp[mid] <= p) a = mid; else b = mid;
+          }
+          atomicAdd(&ipl[a], (unsigned long long)len[u]);
+        }
+      } else {
+        const int w = lane_id() & 15;
+        const int tot = group_incl_scan<16>(sums[0][w]);
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const unsigned e = (unsigned)(incl - l3 + (wave ? __builtin_amdgcn_readlane(tot, wave - 1) : 0));
+        *reinterpret_cast<uint4*>(&pre[tid * 4]) = make_uint4(e, e + l0, e + l1, e + l2);
+        if (tid == kCountThreads - 1) pre[kCountThreads * 4] = e + l3;
+        __syncthreads();
+        if (tid < nr) {   // what the round holds of this thread's row
+          const long long a = rp[tid] > q0 ? rp[tid] : q0, b = rp[tid + 1] < q0 + kCountThreads * 4 ? rp[tid + 1] : q0 + kCountThreads * 4;
+          if (a < b) ipl[tid] += (unsigned long long)(pre[b - q0] - pre[a - q0]);
+        }
+      }
+      __syncthreads();   // (the next round writes sums and pre)
     }
     if (badcol) ctl->error = 1;
     __syncthreads();
@@ -223,7 +243,10 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int parts, int64_t
         bin_out[r0 + tid] = (unsigned char)bin;
         if (bin == kEmptyBin) cnt_out[r0 + tid] = 0;
       }
-      add_to_bins(bin, mine, 0u, hist, hip, nullptr);
+      const int bins[1] = {bin};
+      const unsigned long long ips[1] = {mine};
+      const unsigned none[1] = {0};
+      add_to_bins<1>(bins, ips, none, hist, hip, nullptr);
     }
     if (tid == 0) next_chunk = drawn;
     __syncthreads();
@@ -336,19 +359,30 @@ __global__ __launch_bounds__(kScanThreads) void k_classify_numeric(int64_t m, co
   if (threadIdx.x == 0) total = 0;
   __syncthreads();
   unsigned long long sum = 0;
+  int bin[kScanItems];
+  unsigned long long p[kScanItems];
+  unsigned c[kScanItems];
 #pragma unroll
   for (int u = 0; u < kScanItems; ++u) {
     const int64_t i = (int64_t)blockIdx.x * kScanTile + u * kScanThreads + threadIdx.x;
-    int bin = -1, p = 0, c = 0;
+    bin[u] = -1;
+    p[u] = 0;
+    c[u] = 0;
     if (i < m) {
-      p = ip[i];
-      c = cnt[i];
-      bin = classify_numeric(p, c, force, staged_cap);
-      bin_out[i] = (unsigned char)bin;
-      sum += (unsigned long long)c;
+      p[u] = (unsigned)ip[i];
+      c[u] = (unsigned)cnt[i];
     }
-    add_to_bins(bin, bin == kEmptyBin ? 0ULL : (unsigned long long)p, bin == kEmptyBin ? 0u : (unsigned)c, hist, hip, hnz);
   }
+#pragma unroll
+  for (int u = 0; u < kScanItems; ++u) {
+    const int64_t i = (int64_t)blockIdx.x * kScanTile + u * kScanThreads + threadIdx.x;
+    if (i < m) {
+      bin[u] = classify_numeric((long long)p[u], (int)c[u], force, staged_cap);
+      bin_out[i] = (unsigned char)bin[u];
+      sum += c[u];
+    }
+  }
+  add_to_bins<kScanItems>(bin, p, c, hist, hip, hnz);
   const unsigned long long s = wave_sum64(sum);
   if (lane_id() == 0) atomicAdd(&total, s);
   __syncthreads();
