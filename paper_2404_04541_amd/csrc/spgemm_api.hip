@@ -1230,7 +1230,7 @@ int sptensor_fold(spgemm_handle h, int mode, int64_t I, int64_t J, int64_t K, co
   if (Y->nnz == 0 || Y->rows == 0) return SPGEMM_OK;
   if ((rc = ensure_device(h))) return rc;
   // (the view was built over the output arrays: xa / xb take the row's two coordinates, xc the column)
-  hipLaunchKernelGGL(k_tensor_fold, dim3(grid_for(Y->rows, 4, (int64_t)h->num_cus * 32)), dim3(256), 0, h->stream, Y->rows, v.B, Y->rowptr,
+  hipLaunchKernelGGL(k_tensor_fold, dim3(grid_for(Y->rows + Y->nnz, kFoldTile, (int64_t)h->num_cus * 256)), dim3(256), 0, h->stream, Y->rows, v.B, Y->rowptr,
                      Y->colidx, const_cast<int32_t*>(v.xa), const_cast<int32_t*>(v.xb), const_cast<int32_t*>(v.xc));
   HIP_TRY(h, hipGetLastError());
   return SPGEMM_OK;
@@ -1244,7 +1244,7 @@ int sptensor_fold_mode3(spgemm_handle h, int64_t J, const spgemm_csr* Y, int32_t
   if (Y->nnz > 0 && (!yi || !yj)) return fail(h, SPGEMM_INVALID_ARG, "coordinate arrays null with nnz > 0");
   if (Y->nnz == 0 || Y->rows == 0) return SPGEMM_OK;
   if ((rc = ensure_device(h))) return rc;
-  hipLaunchKernelGGL(k_tensor_fold, dim3(grid_for(Y->rows, 4, (int64_t)h->num_cus * 32)), dim3(256), 0, h->stream, Y->rows, J, Y->rowptr,
+  hipLaunchKernelGGL(k_tensor_fold, dim3(grid_for(Y->rows + Y->nnz, kFoldTile, (int64_t)h->num_cus * 256)), dim3(256), 0, h->stream, Y->rows, J, Y->rowptr,
                      (const int32_t*)nullptr, yi, yj, (int32_t*)nullptr);
   HIP_TRY(h, hipGetLastError());
   return SPGEMM_OK;

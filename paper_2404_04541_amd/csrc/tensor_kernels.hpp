@@ -35,21 +35,72 @@ __global__ __launch_bounds__(kSortThreads) void k_tensor_keys(int64_t nnz, int64
   sort_hist_out(cnt, 1 << bits, blockIdx.x, gridDim.x, hist);
 }
 
-// A row of an unfolded result back to coordinates: per entry the row's two folded coordinates
-// (row / B, row % B) and, when asked for, the column as the third.
-__global__ __launch_bounds__(256) void k_tensor_fold(int64_t rows, int64_t B, const int64_t* __restrict__ rowptr,
-                                                     const int32_t* __restrict__ colidx, int32_t* __restrict__ ya,
-                                                     int32_t* __restrict__ yb, int32_t* __restrict__ yc) {
-  const int64_t stride = (int64_t)gridDim.x * (blockDim.x / kWave);
-  const int lane = threadIdx.x & 63;
-  for (int64_t r = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6); r < rows; r += stride) {
-    const int64_t lo = rowptr[r], hi = rowptr[r + 1];
-    const int32_t a = (int32_t)(r / B), b = (int32_t)(r % B);
-    for (int64_t p = lo + lane; p < hi; p += kWave) {
-      ya[p] = a;
-      yb[p] = b;
+// Rows of an unfolded result back to coordinates: per entry the row's two folded coordinates (row / B, row % B) and, when asked
+// for, the column as the third.  Row ends and entries together are cut into equal tiles, so a workgroup's share is the same whether
+// rows are empty, short or long: it finds its first row and entry, leaves every row's number at its first entry in LDS, and a
+// running maximum gives each entry its row.
+// Bound: memory, 4 bytes read and 12 written per entry.  700 891 rows (a quarter of them not empty) of 1.6 M entries: a wave for every
+// row, with divisions of 64 bits, 47 us; here 15 us.
+constexpr int kFoldTile = 4096;
+__global__ __launch_bounds__(256) void k_tensor_fold(int64_t rows, int64_t B, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
+                                                     int32_t* __restrict__ ya, int32_t* __restrict__ yb, int32_t* __restrict__ yc) {
+  constexpr int kPer = kFoldTile / 256;
+  __shared__ __align__(16) int s_row[kFoldTile];   // row of an entry minus the tile's first: at a row's first entry, then everywhere
+  __shared__ int64_t bound[2];
+  __shared__ int s_max[4];
+  const int wave = threadIdx.x >> 6, lane = lane_id();
+  const int64_t p0 = rowptr[0], total = rows + (rowptr[rows] - p0);
+  int4* mine4 = reinterpret_cast<int4*>(s_row) + threadIdx.x * (kPer / 4);
+  for (int64_t d0 = (int64_t)blockIdx.x * kFoldTile; d0 < total; d0 += (int64_t)gridDim.x * kFoldTile) {
+    const int64_t d1 = d0 + kFoldTile < total ? d0 + kFoldTile : total;
+    if (wave < 2) {   // rows whose end, the rows before them counted, is at or before the tile's edge
+      const int64_t d = wave ? d1 : d0;
+      const int64_t r = wave_first_not(rows, [&](int64_t i) { return i + 1 + (rowptr[i + 1] - p0) <= d; });
+      if (lane == 0) bound[wave] = r;
+    }
+#pragma unroll
+    for (int t = 0; t < kPer / 4; ++t) reinterpret_cast<int4*>(s_row)[t * 256 + threadIdx.x] = make_int4(0, 0, 0, 0);
+    __syncthreads();
+    const int64_t r0 = bound[0], e0 = d0 - r0;
+    const int nr = (int)(bound[1] - r0), left = (int)(d1 - d0) - nr;
+    const int ne = left < kFoldTile ? left : kFoldTile;
+    for (int i = 1 + threadIdx.x; i <= nr; i += 256) {
+      if (r0 + i >= rows) break;
+      const Run<int64_t, 2> v = load_run<int64_t, 2>(rowptr + r0 + i);
+      const int64_t at = v.v[0] - p0 - e0;   // (the last of these rows may begin behind the tile's entries)
+      if (v.v[0] < v.v[1] && at >= 0 && at < ne) s_row[at] = i;
+    }
+    __syncthreads();
+    int x[kPer], top = 0;
+#pragma unroll
+    for (int t = 0; t < kPer / 4; ++t) {
+      const int4 v = mine4[t];
+      x[t * 4] = v.x; x[t * 4 + 1] = v.y; x[t * 4 + 2] = v.z; x[t * 4 + 3] = v.w;
+    }
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) top = x[t] > top ? x[t] : top;
+    const int incl = group_max_scan<kWave>(top);
+    if (lane == kWave - 1) s_max[wave] = incl;
+    int before = __shfl_up(incl, 1, kWave);
+    if (lane == 0) before = 0;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) before = s_max[w] > before ? s_max[w] : before;
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) { before = x[t] > before ? x[t] : before; x[t] = before; }
+#pragma unroll
+    for (int t = 0; t < kPer / 4; ++t) mine4[t] = make_int4(x[t * 4], x[t * 4 + 1], x[t * 4 + 2], x[t * 4 + 3]);
+    __syncthreads();
+    // (there are less than 2^31 rows and B is one of their divisors)
+    const unsigned a0 = (unsigned)r0 / (unsigned)B, b0 = (unsigned)r0 - a0 * (unsigned)B;
+#pragma unroll 4
+    for (int e = threadIdx.x; e < ne; e += 256) {
+      const unsigned b = b0 + (unsigned)s_row[e], q = b / (unsigned)B;
+      const int64_t p = p0 + e0 + e;
+      ya[p] = (int32_t)(a0 + q);
+      yb[p] = (int32_t)(b - q * (unsigned)B);
       if (yc) yc[p] = colidx[p];
     }
+    __syncthreads();
   }
 }
 
