@@ -2,7 +2,7 @@
 // tensor unfolding, the doubly compressed formats and the outer-product workspace.
 //
 // One pass over a digit of at most 8 bits:
-//   k_sort_hist     entries per digit of every range of consecutive tiles (at most kSortMaxRanges ranges)
+//   k_sort_hist     entries per digit of every range of consecutive entries (at most kSortMaxRanges ranges)
 //   k_sort_scan     exclusive scan over the ranges, one workgroup per digit
 //   k_sort_scatter  a workgroup walks its range tile by tile: ranks its entries (ballots inside a wave,
 //                   counters per wave in LDS), puts the tile into digit order in LDS and writes every
@@ -12,16 +12,17 @@
 // through a permutation at the end, which costs a 128-byte line per entry.  Tiles of 8192 entries keep the
 // runs of a digit at 32 entries (256 bytes of keys) on average; a wave that scattered its own 64 entries
 // without the exchange in LDS wrote 4-byte pieces to as many lines.
-// 10^7 tensor entries of 33 key bits and double values, kernel time per pass over a digit: scan of all counters
-// 1290 -> 5 us (one workgroup had walked them all), scatter 210 -> 105 us (3.1 TB/s of key and value moved), counts
-// 27 -> 17 us; the gather of the values behind the last pass (211 us) is gone.  Unfolding as a whole 8.0 -> 0.8 ms.
+// 10^7 tensor entries of 33 key bits and double values, kernel time per pass over a digit: scatter 92 us (3.5 TB/s of key and value
+// moved), counts 18 us, scan of the counters 5 us; unfolding as a whole 0.7 ms.  16.8 M components of 36 bits: scatter 140 us (3.8 TB/s).
+// Two workgroups of 16 waves, 64 registers each, hold a compute unit's LDS; with 8 waves of 16 entries a lane each it was 105 and
+// 163 us.  Payloads are loaded when the keys have left their registers; nothing may spill (with 60 bytes of spills a lane 118 us).
 #pragma once
 #include "common.hpp"
 #include "sort_shape.hpp"
 
 namespace spg {
 
-constexpr int kSortWaves = kSortThreads / kWave;
+constexpr int kSortWaves = kScatterThreads / kWave;
 
 // Adds the digit counts of this workgroup's LDS histogram copies up and writes them for range r of nr.
 constexpr int kHistCopies = 4;
@@ -92,23 +93,24 @@ __device__ __forceinline__ unsigned scan_bins(unsigned v, unsigned* ws) {
 }
 
 // One pass.  P: payload.  col_out (optional): the low bits of the key (key & col_mask), written with the last pass.
-template <typename K, typename P>
-__global__ __launch_bounds__(kSortThreads) void k_sort_scatter(int64_t n, int64_t per_range, int shift, int bits, const K* __restrict__ keys,
-                                                               const P* __restrict__ pay, const unsigned* __restrict__ hist,
-                                                               const unsigned* __restrict__ totals, K* __restrict__ keys_out,
-                                                               P* __restrict__ pay_out, int32_t* __restrict__ col_out, K col_mask) {
+template <typename K, typename P, int ITEMS>
+__global__ __launch_bounds__(kScatterThreads, 8) void k_sort_scatter(int64_t n, int64_t per_range, int shift, int bits, const K* __restrict__ keys,
+                                                                  const P* __restrict__ pay, const unsigned* __restrict__ hist,
+                                                                  const unsigned* __restrict__ totals, K* __restrict__ keys_out,
+                                                                  P* __restrict__ pay_out, int32_t* __restrict__ col_out, K col_mask) {
+  constexpr int kTile = kScatterThreads * ITEMS;
   constexpr size_t kSlot = sizeof(K) > sizeof(P) ? sizeof(K) : sizeof(P);
-  __shared__ __align__(16) unsigned char s_tile[kSortTile * kSlot];   // the tile in digit order: keys, then payloads
-  __shared__ unsigned s_cnt[kSortWaves][kSortBins];   // entries of a digit in every wave, then their prefix over the waves
+  __shared__ __align__(16) unsigned char s_tile[kTile * kSlot];   // the tile in digit order: keys, then payloads
+  __shared__ __align__(16) unsigned short s_cnt[kSortWaves][kSortBins];   // entries of a digit in every wave, then their prefix over the waves
   __shared__ unsigned s_to[kSortBins];                // global position of a digit's run minus its position in the tile
-  __shared__ unsigned s_at[kSortBins];                // position of a digit's run in the tile
+  __shared__ unsigned short s_at[kSortBins];          // position of a digit's run in the tile
   __shared__ unsigned ws[kSortBins / kWave];
+  static_assert(kTile <= 65535, "a position in the tile fits two bytes");
   K* s_key = reinterpret_cast<K*>(s_tile);
   P* s_pay = reinterpret_cast<P*>(s_tile);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
+  const int tid = threadIdx.x;
   const int nbins = 1 << bits;
   const unsigned mask = (unsigned)nbins - 1;
-  const unsigned long long below = lane == 0 ? 0ULL : (~0ULL >> (64 - lane));
   unsigned at_global = 0;   // (thread d < nbins) where the next entry of digit d goes
   {
     const unsigned mine = tid < nbins ? totals[tid] : 0u;
@@ -116,77 +118,91 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(int64_t n, int64_
     if (tid < nbins) at_global = before + hist[(int64_t)tid * gridDim.x + blockIdx.x];
   }
   const int64_t lo = (int64_t)blockIdx.x * per_range, hi = lo + per_range < n ? lo + per_range : n;
-  for (int64_t t0 = lo; t0 < hi; t0 += kSortTile) {
-    const int count = (int)(hi - t0 < kSortTile ? hi - t0 : kSortTile);
-    // a wave owns kSortItems * 64 consecutive entries, 64 at a time
-    const int first = wave * (kSortItems * kWave) + lane;
-    K key[kSortItems];
-    P val[kSortItems];
+  // tiles of equal size, whole steps of a thread's entry each
+  const int tiles = (int)((per_range + kTile - 1) / kTile);
+  const int per_tile = (int)((per_range / kScatterThreads + tiles - 1) / tiles) * kScatterThreads;
+  for (int64_t t0 = lo; t0 < hi; t0 += per_tile) {
+    int tl = tid;
+    asm volatile("" : "+v"(tl));   // (no code: keeps what follows from the thread's number from being computed before the loop and held in registers)
+    const int lane = tl & (kWave - 1), wave = tl >> 6;
+    const int count = (int)(hi - t0 < per_tile ? hi - t0 : per_tile);
+    const int items = (count + kScatterThreads - 1) / kScatterThreads;
+    // a wave owns items * 64 consecutive entries, 64 at a time
+    const int first = wave * (items * kWave) + lane, mine = items * kWave < count - first + lane ? items * kWave : count - first + lane;
+    K key[ITEMS];
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-      const int e = first + i * kWave;
-      key[i] = e < count ? keys[t0 + e] : K(~K(0));   // (behind the end: the last digit, behind every real entry)
-      val[i] = e < count ? pay[t0 + e] : P(0);
+    for (int i = 0; i < ITEMS; ++i) {
+      key[i] = i * kWave + lane < mine ? (keys + t0 + first)[i * kWave] : K(~K(0));   // (behind the end: the last digit, behind every real entry)
     }
-    for (int d = tid; d < kSortWaves * kSortBins; d += kSortThreads) (&s_cnt[0][0])[d] = 0;
+    for (int d = tid; d < kSortWaves * kSortBins / 2; d += kScatterThreads) reinterpret_cast<unsigned*>(&s_cnt[0][0])[d] = 0;
     __syncthreads();
-    unsigned short rank[kSortItems];
+    int pos[ITEMS];
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
+    for (int i = 0; i < ITEMS; ++i) {   // (items that the tile does not have are ranked too, but leave no trace: a branch around them makes the registers spill)
       const unsigned d = (unsigned)(key[i] >> shift) & mask;
       unsigned long long peers = ~0ULL;
 #pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        if (b < bits) {
-          const unsigned long long m = __ballot((d >> b) & 1u);
-          peers &= ((d >> b) & 1u) ? m : ~m;
-        }
+      for (int b = 0; b < 8; ++b) {   // (all eight: a bit that no digit has excludes nobody, and a branch for every bit costs more)
+        const unsigned long long m = __ballot((d >> b) & 1u);
+        peers &= ((d >> b) & 1u) ? m : ~m;
       }
       const unsigned before = s_cnt[wave][d];
-      rank[i] = (unsigned short)(before + (unsigned)__popcll(peers & below));
+      const int below = lanes_below(peers);
+      pos[i] = (int)before + below;
       wave_sync_lds();
-      if ((peers & below) == 0) s_cnt[wave][d] = before + (unsigned)__popcll(peers);
+      if (below == 0 && i < items) s_cnt[wave][d] = (unsigned short)(before + (unsigned)__popcll(peers));
       wave_sync_lds();
     }
     __syncthreads();
     unsigned total = 0;
     if (tid < nbins) {
 #pragma unroll
-      for (int w = 0; w < kSortWaves; ++w) { const unsigned c = s_cnt[w][tid]; s_cnt[w][tid] = total; total += c; }
+      for (int w0 = 0; w0 < kSortWaves; w0 += 4) {
+        unsigned c[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) c[w] = s_cnt[w0 + w][tl];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) { s_cnt[w0 + w][tl] = (unsigned short)total; total += c[w]; }
+      }
     }
     const unsigned at = scan_bins(total, ws);
     if (tid < nbins) {
-      s_at[tid] = at;
+      s_at[tid] = (unsigned short)at;
       s_to[tid] = at_global - at;
       at_global += total;
     }
     __syncthreads();
-    unsigned short pos[kSortItems];
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
+    for (int i = 0; i < ITEMS; ++i) {
       const unsigned d = (unsigned)(key[i] >> shift) & mask;
-      pos[i] = (unsigned short)(s_at[d] + s_cnt[wave][d] + rank[i]);
-      s_key[pos[i]] = key[i];
+      pos[i] += s_at[d] + s_cnt[wave][d];
+      if (i < items) s_key[pos[i]] = key[i];
+    }
+    P val[ITEMS];   // (the keys have left their registers: 64 of them allow two workgroups on a compute unit)
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      val[i] = i * kWave + lane < mine ? (pay + t0 + first)[i * kWave] : P(0);
     }
     __syncthreads();
-    unsigned to[kSortItems];
+    unsigned to[ITEMS];
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-      const int e = i * kSortThreads + tid;
+    for (int i = 0; i < ITEMS; ++i) {
+      const int e = i * kScatterThreads + tl;
+      const K k = s_key[e];   // (behind the tile's entries: anything)
+      to[i] = s_to[(unsigned)(k >> shift) & mask] + (unsigned)e;
       if (e < count) {
-        const K k = s_key[e];
-        to[i] = s_to[(unsigned)(k >> shift) & mask] + (unsigned)e;
         keys_out[to[i]] = k;
         if (col_out) col_out[to[i]] = (int32_t)(k & col_mask);
       }
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) s_pay[pos[i]] = val[i];
+    for (int i = 0; i < ITEMS; ++i)
+      if (i < items) s_pay[pos[i]] = val[i];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-      const int e = i * kSortThreads + tid;
+    for (int i = 0; i < ITEMS; ++i) {
+      const int e = i * kScatterThreads + tl;
       if (e < count) pay_out[to[i]] = s_pay[e];
     }
     __syncthreads();

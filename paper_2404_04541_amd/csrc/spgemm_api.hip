@@ -1055,7 +1055,7 @@ int sort_pairs(spgemm_context* h, int64_t n, const SortShape& sh, K* const keys[
     if (pass > 0 || !first_counted)
       hipLaunchKernelGGL(k_sort_hist<K>, dim3(sh.ranges), dim3(kSortThreads), 0, s, n, sh.per_range, shift, sh.bits, keys[cur], hist);
     hipLaunchKernelGGL(k_sort_scan, dim3(1u << sh.bits), dim3(256), 0, s, sh.ranges, hist, counters);
-    hipLaunchKernelGGL((k_sort_scatter<K, P>), dim3(sh.ranges), dim3(kSortThreads), 0, s, n, sh.per_range, shift, sh.bits, keys[cur], pay_in, hist,
+    hipLaunchKernelGGL((sh.per_range <= kScatterThreads * kSortFewItems ? k_sort_scatter<K, P, kSortFewItems> : k_sort_scatter<K, P, kSortItems>), dim3(sh.ranges), dim3(kScatterThreads), 0, s, n, sh.per_range, shift, sh.bits, keys[cur], pay_in, hist,
                        counters, keys[1 - cur], out, last ? col_out : (int32_t*)nullptr, col_mask);
     pay_in = out;
     cur = 1 - cur;
@@ -1124,7 +1124,7 @@ int unfold_run(spgemm_context* h, const ModeView& v, int64_t nnz, const void* xv
 
 // Scratch of the entry point that allocates nothing: one array per device, held until the process ends.
 constexpr int64_t kNoAllocMaxNnz = SPTENSOR_NOALLOC_MAX_NNZ;
-constexpr size_t kNoAllocScratchBytes = (size_t)kNoAllocMaxNnz * 24 + ((size_t)kNoAllocMaxNnz / kSortTile + 2) * kSortBins * 4 + 8 * 256;
+constexpr size_t kNoAllocScratchBytes = (size_t)kNoAllocMaxNnz * 24 + sort_counter_bytes(kNoAllocMaxNnz) + 8 * 256;
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 constexpr int kMaxDevices = 64;
 unsigned char* g_scratch_ptr[kMaxDevices] = {};   // device address of `scratch` on each device, from hipGetSymbolAddress
