@@ -280,7 +280,9 @@ constexpr int64_t kEscPackCols0 = int64_t(1) << 25, kEscPackCols1 = int64_t(1) <
 // The numeric phase marks the columns again: where B is larger than a die's L2 cache that is a second line of memory per A entry,
 // which pays when the entry brings eight products or more.  10^6 rows (fp64, us sorted list | flags, 4000 columns): 8 entries times
 // rows of 4, B of 10^4 rows 576 | 515, 10^5 589 | 552, 5 10^5 739 | 819, 2 10^6 737 | 1032; 8 times 12: 1230 | 848, 1273 | 929, 1324 |
-// 1152, 1465 | 1390; 3 times 16: 894 | 502, 927 | 525, 971 | 600, 1202 | 728.
+// 1152, 1465 | 1390; 3 times 16: 894 | 502, 927 | 525, 971 | 600, 1202 | 728.  Rows of fewer than four entries leave a lane's four places
+// empty in both phases (whole calls, 8000 columns, near B): 16 times 2 1004 | 1128, 2 times 2 594 | 631, 4 times 3 683 | 697, but 6 times 4
+// 472 | 464.
 constexpr int64_t kFlagMaxNnz = int64_t(1) << 20;
 constexpr size_t kAskFreeAbove = (size_t)64 << 20;   // optional memory below this is taken without asking the device what it has free
 
@@ -288,7 +290,7 @@ size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
 // Whether the rows of classes 0 and 1 take the flag-list workspace (flag_kernels.hpp) instead of the sorted list.
 bool flag_rows_ok(spgemm_context* h, const spgemm_csr* B) {
-  return h->force != 1 && B->cols <= kFlagMaxCols && (B->nnz <= kFlagMaxNnz || B->nnz >= 8 * B->rows);
+  return h->force != 1 && B->cols <= kFlagMaxCols && B->nnz >= (B->nnz <= kFlagMaxNnz ? 4 : 8) * B->rows;
 }
 
 // Whether the row count leaves start and length of every A entry's B row: 8 bytes an entry, written once and read twice, in place
