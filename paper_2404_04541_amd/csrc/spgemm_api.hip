@@ -203,8 +203,9 @@ int ensure_device(spgemm_context* h) {
   if (prop.warpSize != kWave) return fail(h, SPGEMM_UNSUPPORTED, "device is not wave64");
   h->num_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
   int rc;
-  if ((rc = allow_lds(h, k_sym_dense<16>, sym_dense_lds<16>(kSymFlagWords)))) return rc;
-  if ((rc = allow_lds(h, k_sym_dense<8>, sym_dense_lds<8>(kSymNarrowCols / 32)))) return rc;
+  if ((rc = allow_lds(h, k_sym_dense<16, false>, sym_dense_lds<16>(kSymFlagWords)))) return rc;
+  if ((rc = allow_lds(h, k_sym_dense<16, true>, sym_dense_lds<16>(kSymFlagWords)))) return rc;
+  if ((rc = allow_lds(h, k_sym_dense<8, false>, sym_dense_lds<8>(kSymNarrowCols / 32)))) return rc;
   if ((rc = allow_lds(h, k_num_tiles<float, false>, num_tiles_lds<float, false>()))) return rc;
   if ((rc = allow_lds(h, k_num_tiles<double, false>, num_tiles_lds<double, false>()))) return rc;
   if ((rc = allow_lds(h, k_num_tiles<float, true>, num_tiles_lds<float, true>()))) return rc;
@@ -579,7 +580,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     if (rows_dense > 0) {
       Timer t(h, SPGEMM_K_SYM_DENSE);
       const SymDense d = sym_dense_shape(h, rows_dense, B->cols);
-      hipLaunchKernelGGL((d.waves == 16 ? k_sym_dense<16> : k_sym_dense<8>), dim3(d.groups), dim3(d.waves * kWave), d.lds, s, p->perm_sym, p->ctl, A->rowptr, A->colidx, B->rowptr, B->colidx, B->cols, p->ip, p->cnt, p->tiles, p->runs, p->col_list, h->direct_min,
+      hipLaunchKernelGGL((d.waves == 8 ? k_sym_dense<8, false> : B->cols > kSymNarrowCols ? k_sym_dense<16, true> : k_sym_dense<16, false>), dim3(d.groups), dim3(d.waves * kWave), d.lds, s, p->perm_sym, p->ctl, A->rowptr, A->colidx, B->rowptr, B->colidx, B->cols, p->ip, p->cnt, p->tiles, p->runs, p->col_list, h->direct_min,
                          staged, h->search_ratio, p->blk_ptr, p->blk_ptr_cols, B->nnz, run_tiles_of(h, rows_dense));
     }
     {
