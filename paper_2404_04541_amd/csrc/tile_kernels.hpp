@@ -185,7 +185,8 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
         pf1 = row[nx.b1];
       }
     }
-    // All products of the tile, acc(quad) per lane.  Begins and ends with a barrier.
+    // All products of the tile, acc(quad) per lane.  Begins with a barrier; every product is in the tile behind it, but where the
+    // last entries of A have none, waves may still be reading the totals in ts->red.
     auto products = [&](auto with_values, auto acc) {
       for (int sg = 0; sg < nseg; ++sg) {
         if (nseg > 1) {
@@ -369,6 +370,7 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
           if (w < nw) in_share += __popc(fc[w].x);
         }
         in_share = wave_sum(in_share);
+        __syncthreads();   // (the totals in ts->red have been read by all waves)
         if (lane == 0) ts->red[wave] = in_share;
         __syncthreads();
         int running = 0;

@@ -36,3 +36,22 @@ def test_rows_of_class_3(cols, dtype, ordered):
         assert got[3]["num_bin_rows"][3] == int(in_class.sum()) > 0
         if per == 11:
             assert bool(((ref.ip > 1536) & in_class).any()) and bool(((ref.ip <= 1536) & in_class).any())
+
+
+@pytest.mark.parametrize("entries", [257, 300, 1025, 1100])
+def test_rows_whose_last_entries_have_no_products(entries):
+    """More entries of A than a workgroup describes at a time (256 in the tiles without structure, 1024 in the plan's tiles), those
+    behind it with empty rows of B: the last round finds no piece, and the waves go on to count the columns all the same."""
+    from paper_2404_04541_amd import binding as sg
+    rng = np.random.default_rng(entries)
+    full = 256 if entries < 1024 else 1024
+    k = 1400
+    b_lens = np.where(np.arange(k) < full, 4, 0)
+    for cols in (3000, 70_000):
+        B = W.CSR(k, cols, np.concatenate([[0], np.cumsum(b_lens)]).astype(np.int64),
+                  np.concatenate([np.sort(rng.permutation(cols)[:n]) for n in b_lens]).astype(np.int32), W.draw_values(full * 4, -1.0, 1.0, np.float64, 5, 1))
+        row = np.concatenate([np.arange(full), np.arange(full, entries)])
+        rows = 600
+        A = W.CSR(rows, k, np.arange(rows + 1, dtype=np.int64) * entries, np.tile(row, rows).astype(np.int32), W.draw_values(rows * entries, -1.0, 1.0, np.float64, 6, 1))
+        for options in ({}, {sg.OPT_COLUMN_LIST: 0}):
+            assert_matches_oracle(A, B, gpu_product(A, B, options=options), what=f"{cols} columns, {options}")
