@@ -91,8 +91,9 @@ enum {
 typedef struct {
   int64_t ip_total;                     /* intermediate products, sum over rows */
   int64_t nnz_c;                        /* nonzeros of C */
-  /* bins: symbolic 0,1 sorted list; 2,3 hash; 4,5,6 dense; 7 rows without products.
-   *       numeric  0,1 sorted list; 2,3 hash; 4 staged list; 5,6 dense; 7 empty rows of C. */
+  /* bins: symbolic 0,1 sorted list, or flag list (B of at most 8192 columns); 2,3 hash; 4,5,6 dense; 7 rows without products.
+   *       numeric  0,1 as symbolic; 2 hash; 3 (193 to 1536 entries) tiles of the dense workspace or hash; 4 staged list;
+   *                5,6 (more entries) dense; 7 empty rows of C. */
   int64_t sym_bin_rows[SPGEMM_NUM_BINS];
   int64_t num_bin_rows[SPGEMM_NUM_BINS];
   int64_t sym_bin_ip[SPGEMM_NUM_BINS];   /* intermediate products per symbolic bin (rows beyond 2^31-1 products saturate) */
@@ -172,7 +173,7 @@ int spgemm_symbolic(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B,
  *                       (may be null when nnz_c == 0).
  * Only enqueues work (no synchronisation).  A plan may be
  * reused for further numeric calls with new values on the same structures; the entries of a row may then come in
- * another order than before (of an ascending B's row only where no row of the product is dense).
+ * another order than before (of an ascending B's row only where no row of the product is in the numeric bins 5 and 6).
  * Sums are accumulated in double for both value types and rounded once on output (one exception: the
  * staged coordinate list, taken on request only, stages each float product rounded to float).
  * The plan's scratch is read by the enqueued kernels: spgemm_plan_destroy waits for the stream when a

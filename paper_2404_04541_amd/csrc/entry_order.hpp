@@ -2,7 +2,9 @@
 // of an entry in its row, but a plan holds for operands of the same structure whatever the order of a row's entries.  So the
 // columns of both operands are summed with a weight per position (the weights of any two positions differ), once for a plan that
 // its caller holds and again in every numeric phase on it; where the sum is another one, the kernels that go by the plan's order
-// end at once and k_other_order does their rows without it.
+// end at once and k_other_order does their rows without it.  The plan's tiles go by it too where B ascends (which part of a row of B a
+// tile holds): rows of numeric class 3 are then done without tiles, whereas the rows of the dense classes have no other way, which is
+// why the order of an ascending B may not change where there are any.
 // Bound: memory, one pass over the columns (of one operand where both are the same array), and the launches.  Numeric phase on a
 // kept plan, 27-point stencil (fp64): 61^3 rows 256 -> 268 us, 128^3 rows 2.19 -> 2.24 ms; in another order 475 us and 4.36 ms
 // (without any plan of the order, 546 us and 4.79 ms).
@@ -94,6 +96,12 @@ struct OrderOperands {
   int64_t na, nb;
   const int32_t *a_col, *b_col;   // b_col null: as a_col
 };
+// What a numeric phase knows of the order when its kernels run: nobody has looked (or need not), k_order_sum has, k_num_recorded has.
+enum { kOrderNotLooked = 0, kOrderSummed = 1, kOrderBeside = 2 };
+__device__ __forceinline__ bool other_order(const Control* ctl, int looked) {
+  return looked == kOrderSummed ? ctl->order_differs != 0 : looked == kOrderBeside && ctl->order_later != 0;
+}
+
 // Up to this many entries that saves the launch of k_order_sum; beyond, the rows' kernel loses more (its code with the sum in it takes
 // a tenth longer for the rows).  Numeric phase of stencils, us with the launch | inside | without any check: 10 600 entries 19.0 | 13.6 | 11.6,
 // 0.10 M 21.6 | 16.1 | 13.5, 0.83 M 47.9 | 44.7 | 39.1, 1.6 M 71.7 | 71.3 | 63.1, 2.9 M 144 | 148 | 133.

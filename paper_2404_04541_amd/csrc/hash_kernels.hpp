@@ -278,9 +278,10 @@ __global__ __launch_bounds__(256, GROUP > kWave ? 5 : 8) void k_hash(const int* 
                                                const int32_t* __restrict__ b_col, const T* __restrict__ b_val,
                                                int* __restrict__ cnt, const int64_t* __restrict__ c_rp,
                                                int32_t* __restrict__ c_col, T* __restrict__ c_val, int64_t n_cols,
-                                               const int* __restrict__ record_of, int most_ip) {
+                                               const int* __restrict__ record_of, int most_ip, int looked) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (ctl->error) return;
+  if (GROUP > kWave && NUMERIC && other_order(ctl, looked)) most_ip = 0x7fffffff;   // (the tiles leave their rows to this kernel)
   hash_rows<GROUP, LOGH, T, NUMERIC>(smem, blockIdx.x, gridDim.x, perm, ctl, phase, bin, ip_row, a_rp, a_col, a_val, b_rp, b_col, b_val, cnt, c_rp, c_col, c_val,
                                      n_cols, record_of, most_ip);
 }

@@ -133,6 +133,7 @@ struct spgemm_plan_s {
   bool flag_rows = false;        // classes 0 and 1 take the flag-list workspace
   bool all_listed = false;       // every row of the dense classes has its structure in the column list
   bool order_kept = false;       // the checksums of the order of the entries were taken
+  bool tiles_ordered = false;    // rows were planned as tiles of an ascending B
   bool symbolic_done = false;
   bool numeric_pending = false;   // timed numeric launches not yet folded into stats
   bool numeric_in_flight = false; // numeric kernels were enqueued and the stream has not been waited for since
@@ -532,7 +533,8 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   }
   if (rc) return rc;
   alloc_optional(h, p, B, host, list_want, sizeof(T), staged > 0, plan_leaves);
-  p->order_kept = plan_leaves && (p->records || p->esc_words[0] || p->esc_words[1]);
+  p->tiles_ordered = rows_dense > 0 && host.b_sorted != 0;
+  p->order_kept = plan_leaves && (p->records || p->esc_words[0] || p->esc_words[1] || (p->tiles_ordered && p->force != 2));
   if (p->order_kept) {
     Timer t(h, SPGEMM_K_COUNT);
     sum_order(h, p, A, B, 1);
@@ -575,7 +577,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
         hipLaunchKernelGGL((k_hash<256, 12, T, false>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
                            lds_hash_large, s, p->perm_sym, p->ctl, 0, 3, p->ip, A->rowptr, A->colidx,
                            (const T*)nullptr, B->rowptr, B->colidx, (const T*)nullptr, p->cnt, (const int64_t*)nullptr,
-                           (int32_t*)nullptr, (T*)nullptr, B->cols, (const int*)nullptr, 0);
+                           (int32_t*)nullptr, (T*)nullptr, B->cols, (const int*)nullptr, 0, kOrderNotLooked);
     }
     if (rows_dense > 0) {
       Timer t(h, SPGEMM_K_SYM_DENSE);
@@ -628,13 +630,16 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   // On a plan that the caller holds: are the entries in the order of the plan?  If not, the kernels that need it end at once, and
   // k_other_order behind them, which ends at once otherwise (4 us), does their rows.
   const bool check = p->order_kept && (words0 || words1 || p->recorded);
+  // (rows of class 3 with tiles, where no row is dense: in another order they are done without tiles)
+  const bool check3 = p->order_kept && p->tiles_ordered && tiles3 && hist[3] > 0 && hist[5] + hist[6] == 0 && p->stats.dense_runs > 0;
   // (the kernel of recorded rows looks at the order beside its rows where the entries are few: the kernels that need the plan's
   // order then do their rows whatever it is)
   const bool same = same_columns(A, B);
   const bool inside = check && p->recorded && A->nnz + (same ? 0 : B->nnz) <= kOrderInside;
+  const int looked3 = !check3 ? kOrderNotLooked : inside ? kOrderBeside : kOrderSummed;
   {
     Timer t(h, SPGEMM_K_NUM_ESC);
-    if (check && !inside) sum_order(h, p, A, B, 0);
+    if ((check || check3) && !inside) sum_order(h, p, A, B, 0);
     if (p->flag_rows) {
       auto rows = [&](auto wpl) {
         constexpr int W = decltype(wpl)::value;
@@ -679,22 +684,22 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
     if (hist[2] > p->recorded)
       hipLaunchKernelGGL((k_hash<64, 8, T, true>), dim3(grid_for(hist[2], 4, cap_small)), dim3(256), lds_hash_small, s,
                          p->perm_num, p->ctl, 1, 2, p->ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, (int*)nullptr,
-                         c_rp, c_col, c_val, B->cols, p->recorded ? p->record_of : nullptr, 0);
+                         c_rp, c_col, c_val, B->cols, p->recorded ? p->record_of : nullptr, 0, kOrderNotLooked);
     if (check) {
       const unsigned w0 = words0 ? grid_for(hist[0], 16, cap_small) : 0, w1 = words1 ? grid_for(hist[1], 4, cap_small) : 0, w2 = p->recorded ? grid_for(hist[2], 4, cap_small) : 0;
       hipLaunchKernelGGL(k_other_order<T>, dim3(w0 + w1 + w2), dim3(256), other_order_lds_bytes<T>(), s, w0, w1, w2, p->perm_num, p->ctl, p->ip, A->rowptr,
                          A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, pack128, B->nnz, B->cols, inside ? 1 : 0);
     }
-    // (rows of class 3 that have tiles, the others)
-    if (hist[3] && (!tiles3 || p->stats.sym_bin_rows[2] + p->stats.sym_bin_rows[3] > 0)) {
+    // (rows of class 3 that have no tiles; those too that have, in another order than the plan's)
+    if (hist[3] && (!tiles3 || check3 || p->stats.sym_bin_rows[2] + p->stats.sym_bin_rows[3] > 0)) {
       const int most_ip = tiles3 ? kSymHashLarge : 0x7fffffff;
       if (tiles3 && B->cols <= kRowTileMaxCols)
         hipLaunchKernelGGL(k_row_tiles<T>, dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(kRowTileWaves * kWave), row_tile_lds<T>(B->cols), s,
-                           p->perm_num, p->ctl, p->ip, most_ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, B->nnz, B->cols, c_rp, c_col, c_val);
+                           p->perm_num, p->ctl, p->ip, most_ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, B->nnz, B->cols, c_rp, c_col, c_val, looked3);
       else
         hipLaunchKernelGGL((k_hash<256, 11, T, true>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
                            lds_hash_large, s, p->perm_num, p->ctl, 1, 3, p->ip, A->rowptr, A->colidx, a_val, B->rowptr,
-                           B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, B->cols, (const int*)nullptr, most_ip);
+                           B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, B->cols, (const int*)nullptr, most_ip, looked3);
     }
   }
   if (hist[4]) {
@@ -707,7 +712,7 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
     const bool plain = p->blk_ptr && p->all_listed && B->nnz < kTileMaxNnz;   // (the table is built for ascending rows only)
     hipLaunchKernelGGL((plain ? k_num_tiles<T, false> : k_num_tiles<T, true>), dim3(grid_for(p->stats.dense_runs, 1, (int64_t)h->num_cus * 2)), dim3(kTileThreads),
                        (plain ? num_tiles_lds<T, false>() : num_tiles_lds<T, true>()), s, p->ctl, p->bin, p->tiles, p->runs, A->colidx, a_val, B->rowptr,
-                       B->colidx, b_val, B->cols, p->blk_ptr, p->blk_ptr_cols, p->col_list, B->nnz, c_rp, c_col, c_val);
+                       B->colidx, b_val, B->cols, p->blk_ptr, p->blk_ptr_cols, p->col_list, B->nnz, c_rp, c_col, c_val, looked3);
   }
   HIP_TRY(h, hipGetLastError());
   return SPGEMM_OK;

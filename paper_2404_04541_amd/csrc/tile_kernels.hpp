@@ -15,6 +15,7 @@
 // 7710 | 7280 | 6840.
 #pragma once
 #include "common.hpp"
+#include "entry_order.hpp"
 #include "dense_kernels.hpp"
 
 namespace spg {
@@ -442,12 +443,13 @@ __global__ __launch_bounds__(kTileThreads, GENERAL ? 4 : 8) void k_num_tiles(Con
                                                                const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
                                                                const int32_t* __restrict__ b_col, const T* __restrict__ b_val, int64_t n_cols,
                                                                const int* __restrict__ bp, int nb1, const int32_t* __restrict__ col_list, int64_t b_nnz,
-                                                               const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val) {
+                                                               const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val, int looked) {
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* tile = smem;                                                         // kTileBudget bytes
   TileScratch<T, GENERAL>* ts = reinterpret_cast<TileScratch<T, GENERAL>*>(smem + kTileBudget);
   if (ctl->error) return;
   const bool sorted = !GENERAL || ctl->b_sorted != 0;
+  const bool class3 = !other_order(ctl, looked);   // (in another order k_row_tiles or the hash workspace does these rows)
   const int tid = threadIdx.x;
   const unsigned nruns = ctl->run_cursor;
   // The first lanes draw runs ahead of their use: the counter value for the run after next and the record of the next run, a word
@@ -494,7 +496,7 @@ __global__ __launch_bounds__(kTileThreads, GENERAL ? 4 : 8) void k_num_tiles(Con
       k = a_col[rr.a0 + tid];
       av = a_val[rr.a0 + tid];
     }
-    if (cls != 3 && cls != 5 && cls != 6) continue;   // the row's numeric class is not this kernel's
+    if (!(cls == 3 && class3) && cls != 5 && cls != 6) continue;   // the row's numeric class is not this kernel's
     __syncthreads();
     SPG_CLK(clk_mark(&ts->clk, 0); clk_add(&ts->clk, 16, 1);)
     tile_run<kTileWaves, T, GENERAL>(rr, ts, tile, sorted, a_col, a_val, b_rp, b_col, b_val, n_cols, bp, nb1, col_list, b_nnz, out_row, c_col, c_val, k, av);
@@ -502,7 +504,8 @@ __global__ __launch_bounds__(kTileThreads, GENERAL ? 4 : 8) void k_num_tiles(Con
   SPG_CLK(clk_mark(&ts->clk, 14); clk_flush(&ts->clk, ctl->clk[1]);)
 }
 
-// The rows of numeric class 3 without a tile in the plan (at most kSymHashLarge products), where the matrix has few columns: a row
+// The rows of numeric class 3 without a tile in the plan (at most kSymHashLarge products; all of them where the entries of an ascending
+// B come in another order than the plan's: a row as a whole is the same in any order), where the matrix has few columns: a row
 // is one tile without structure, a workgroup of four waves each, several on a compute unit.  Marking the columns and ranking
 // them by counting costs two passes over the products, the hash workspace its table, the slowest of 64 compare-and-swap loops
 // and a sort: us hash (all rows of the class) | these kernels (with the rows that have tiles in k_num_tiles): R-MAT scale 14 (fp32)
@@ -522,10 +525,11 @@ __global__ __launch_bounds__(kRowTileWaves * kWave, 4) void k_row_tiles(const in
                                                                         const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                                         const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
                                                                         const int32_t* __restrict__ b_col, const T* __restrict__ b_val, int64_t b_nnz, int64_t n_cols,
-                                                                        const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val) {
+                                                                        const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val, int looked) {
   extern __shared__ __align__(16) unsigned char smem[];
   TileScratch<T, true, kRowTileWaves>* ts = reinterpret_cast<TileScratch<T, true, kRowTileWaves>*>(smem + row_tile_bytes<T>(n_cols));
   if (ctl->error) return;
+  if (other_order(ctl, looked)) most_ip = 0x7fffffff;
   const bool sorted = ctl->b_sorted != 0;
   const unsigned first = ctl->offset[1][3], nrows = ctl->offset[1][4] - first;
   const int tid = threadIdx.x;

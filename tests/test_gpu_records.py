@@ -138,8 +138,8 @@ def repeated(M, times):
     return W.CSR(M.rows * times, M.cols, rowptr, np.tile(M.colidx, times), W.draw_values(M.nnz * times, -1.0, 1.0, M.values.dtype, 3, 1))
 
 
-def numeric_on_a_plan(plan_of, calls, what, force=0, offset=0):
-    """One plan for the operands plan_of, the numeric phase for each of calls in turn, every result compared."""
+def numeric_on_a_plan(plan_of, calls, what, force=0, offset=0, options=None):
+    """One plan for the operands plan_of, the numeric phase for each of calls in turn, every result compared.  Returns the plan's statistics."""
     import torch
     from paper_2404_04541_amd import binding as sg
 
@@ -151,6 +151,8 @@ def numeric_on_a_plan(plan_of, calls, what, force=0, offset=0):
         return d
     h = sg.Handle()
     h.set_option(sg.OPT_FORCE_WORKSPACE, force)
+    for opt, value in (options or {}).items():
+        h.set_option(opt, value)
     A, B = plan_of
     dA = device(A)
     dB = dA if B is A else device(B)
@@ -163,7 +165,9 @@ def numeric_on_a_plan(plan_of, calls, what, force=0, offset=0):
         sg.spgemm_numeric(h, plan, dA, dB, rp, col, val)
         torch.cuda.synchronize()
         assert_matches_oracle(A, B, (rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy()), what=f"{what}, call {n}")
+    st = plan.stats()
     plan.destroy()
+    return st
 
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
@@ -286,3 +290,59 @@ def test_order_beside_the_rows_and_before_them(entries):
     for v in (last.colidx, last.values):
         v[[-1, -2]] = v[[-2, -1]]
     numeric_on_a_plan((A, B), [(A, B), (last, B), (A, reordered(B, rng)), (A, B)], f"{entries} entries")
+
+
+def rows_of_class_3(cols, dtype, short_rows):
+    """Ascending B; rows of A with 600 entries of eight products each on 1000 columns spread over the matrix (193 to 1536 entries,
+    more than 1536 products, tiles); short_rows: rows with a record among them, and rows of the hash class without tiles."""
+    rng = np.random.default_rng(91)
+    used = np.sort(rng.choice(cols, size=1000, replace=False))
+    B = csr([np.sort(rng.choice(used, size=8, replace=False)) for _ in range(900)], cols, dtype, 92)
+    a = [rng.choice(900, size=600, replace=False) for _ in range(60)]
+    if short_rows:
+        a += [rng.choice(900, size=n, replace=False) for n in (20, 24, 60, 90, 130, 190) for _ in range(20)]
+    return csr(a, 900, dtype, 93), B
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("short_rows", [False, True])
+@pytest.mark.parametrize("cols,options", [(1 << 19, {}), (1 << 20, {5: 0}), (3 << 18, {COLUMN_LIST: 0}), (1 << 19, {6: 100}), (24_000, {3: 256}), (2_000, {3: 256})])
+def test_tiles_of_an_ascending_b_that_no_longer_ascends(cols, options, short_rows, dtype):
+    """Rows of numeric class 3 by several tiles, no row of the dense classes: any order of B's entries is allowed on a kept plan.
+    Options: without the block table, without the structure list, searched tiles, direct tiles."""
+    A, B = rows_of_class_3(cols, dtype, short_rows)
+    rng = np.random.default_rng(94)
+    A2, B2 = reordered(A, rng), reordered(B, rng)
+    st = numeric_on_a_plan((A, B), [(A, B), (A, B2), (A2, B), (A2, B2), (A, B)], f"{cols} columns, {options}", options=options)
+    assert st["num_bin_rows"][3] >= 60 and st["num_bin_rows"][5] + st["num_bin_rows"][6] == 0 and st["dense_runs"] > 0
+    assert st["dense_tiles"] >= (120 if cols > 2_000 and 6 not in options else 60)
+
+
+def test_tiles_of_another_order_under_capture():
+    """A captured numeric phase looks at the order in every replay."""
+    import torch
+    from paper_2404_04541_amd import binding as sg
+    A, B = rows_of_class_3(1 << 19, np.float64, False)
+    rng = np.random.default_rng(95)
+    stream = torch.cuda.Stream()
+    h = sg.Handle(stream=stream)
+    with torch.cuda.stream(stream):
+        dA, dB = sg.to_device(A), sg.to_device(B)
+        rp, nnz, plan = sg.spgemm_symbolic(h, dA, dB)
+        col = torch.empty(nnz, dtype=torch.int32, device="cuda")
+        val = torch.empty(nnz, dtype=torch.float64, device="cuda")
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            sg.spgemm_numeric(h, plan, dA, dB, rp, col, val)
+    for n, (X, Y) in enumerate([(A, B), (A, reordered(B, rng)), (A, B), (reordered(A, rng), reordered(B, rng))]):
+        for d, m in ((dA, X), (dB, Y)):
+            d.colidx.copy_(torch.from_numpy(m.colidx))
+            d.values.copy_(torch.from_numpy(m.values))
+        col.fill_(-1)
+        val.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_matches_oracle(X, Y, (rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy()), what=f"replay {n}")
+    plan.destroy()
