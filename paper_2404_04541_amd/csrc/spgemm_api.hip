@@ -712,7 +712,7 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
     const bool plain = p->blk_ptr && p->all_listed && B->nnz < kTileMaxNnz;   // (the table is built for ascending rows only)
     hipLaunchKernelGGL((plain ? k_num_tiles<T, false> : k_num_tiles<T, true>), dim3(grid_for(p->stats.dense_runs, 1, (int64_t)h->num_cus * 2)), dim3(kTileThreads),
                        (plain ? num_tiles_lds<T, false>() : num_tiles_lds<T, true>()), s, p->ctl, p->bin, p->tiles, p->runs, A->colidx, a_val, B->rowptr,
-                       B->colidx, b_val, B->cols, p->blk_ptr, p->blk_ptr_cols, p->col_list, B->nnz, c_rp, c_col, c_val, looked3);
+                       B->colidx, b_val, B->cols, p->blk_ptr, p->blk_ptr_cols, p->col_list, B->nnz, c_rp, c_col, c_val, tiles3 ? 1 : 0, looked3);
   }
   HIP_TRY(h, hipGetLastError());
   return SPGEMM_OK;

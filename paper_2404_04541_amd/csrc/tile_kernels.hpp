@@ -443,13 +443,13 @@ __global__ __launch_bounds__(kTileThreads, GENERAL ? 4 : 8) void k_num_tiles(Con
                                                                const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
                                                                const int32_t* __restrict__ b_col, const T* __restrict__ b_val, int64_t n_cols,
                                                                const int* __restrict__ bp, int nb1, const int32_t* __restrict__ col_list, int64_t b_nnz,
-                                                               const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val, int looked) {
+                                                               const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val, int tiles3, int looked) {
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* tile = smem;                                                         // kTileBudget bytes
   TileScratch<T, GENERAL>* ts = reinterpret_cast<TileScratch<T, GENERAL>*>(smem + kTileBudget);
   if (ctl->error) return;
   const bool sorted = !GENERAL || ctl->b_sorted != 0;
-  const bool class3 = !other_order(ctl, looked);   // (in another order k_row_tiles or the hash workspace does these rows)
+  const bool class3 = tiles3 != 0 && !other_order(ctl, looked);   // (in another order, or where hashing is asked for, k_row_tiles or the hash workspace does these rows)
   const int tid = threadIdx.x;
   const unsigned nruns = ctl->run_cursor;
   // The first lanes draw runs ahead of their use: the counter value for the run after next and the record of the next run, a word

@@ -55,3 +55,21 @@ def test_rows_whose_last_entries_have_no_products(entries):
         A = W.CSR(rows, k, np.arange(rows + 1, dtype=np.int64) * entries, np.tile(row, rows).astype(np.int32), W.draw_values(rows * entries, -1.0, 1.0, np.float64, 6, 1))
         for options in ({}, {sg.OPT_COLUMN_LIST: 0}):
             assert_matches_oracle(A, B, gpu_product(A, B, options=options), what=f"{cols} columns, {options}")
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_hashing_on_request_beside_dense_rows(dtype):
+    """Hashing is asked for, and a dense row makes the tiles run: the rows of class 3 are still the hash workspace's, which their rows
+    of B show by coming in another order than the plan's (the dense row's stay as they are)."""
+    from test_gpu_records import csr, numeric_on_a_plan
+    rng = np.random.default_rng(3)
+    cols = 1 << 19
+    used = np.sort(rng.choice(cols, size=1000, replace=False))
+    b = [np.sort(rng.choice(used, size=8, replace=False)) for _ in range(900)] + [np.sort(rng.choice(cols, size=2000, replace=False)) for _ in range(3)]
+    B = csr(b, cols, dtype, 4)
+    A = csr([rng.choice(900, size=600, replace=False) for _ in range(60)] + [[900, 901, 902]], len(b), dtype, 5)
+    B2 = W.CSR(B.rows, B.cols, B.rowptr, B.colidx.copy(), B.values.copy())
+    for v in (B2.colidx, B2.values):
+        v[:7200] = v[:7200].reshape(900, 8)[:, ::-1].ravel()
+    st = numeric_on_a_plan((A, B), [(A, B), (A, B2)], "hashing", force=2)
+    assert st["num_bin_rows"][3] == 60 and st["num_bin_rows"][5] + st["num_bin_rows"][6] == 1
