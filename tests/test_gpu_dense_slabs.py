@@ -50,3 +50,18 @@ def test_list_bytes_used_are_those_of_the_rows(rows):
     got = gpu_product(A, B, options={4: 4096})   # (SPGEMM_OPT_COLUMN_LIST)
     assert_matches_oracle(A, B, got, what=f"{rows} rows, no room")
     assert got[3]["plan_list_used"] == 0 and got[3]["plan_list_bytes"] == 4096
+
+
+@pytest.mark.parametrize("cols", [100_000, 300_000])
+@pytest.mark.parametrize("room", [2.0, 1.0, 0.6])
+def test_rows_of_one_length_that_draw_at_the_same_moment(cols, room):
+    """Several rows for each of hundreds of workgroups, all of about the same length, so that slabs run out together; lists for all of them
+    with the ends of the slabs, for the rows alone, for some: what is written stays within the list and no row gets another's place."""
+    A = W.uniform_rows(6000, 3000, 50, 97, 1, np.float32)
+    B = W.uniform_rows(3000, cols, 50, 97, 3, np.float32)
+    got = gpu_product(A, B)
+    ref = assert_matches_oracle(A, B, got, what="any list")
+    need = int(((ref.cnt + 3) // 4 * 4).sum()) * 4
+    got = gpu_product(A, B, options={4: int(need * room)})   # (SPGEMM_OPT_COLUMN_LIST)
+    assert_matches_oracle(A, B, got, ref=ref, what=f"room for {room} of the rows")
+    assert 0 < got[3]["plan_list_used"] <= got[3]["plan_list_bytes"] <= need * room
