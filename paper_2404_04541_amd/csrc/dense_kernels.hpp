@@ -92,7 +92,7 @@ __host__ __device__ __forceinline__ unsigned run_slab(int64_t rows, int64_t work
   const int64_t s = rows / (8 * workgroups);
   return (unsigned)(s < 1 ? 1 : (s > kRunSlab ? kRunSlab : s));
 }
-// List entries that a symbolic workgroup draws at a time: together at most a quarter of the list, so that a short list is not
+// List entries that a symbolic workgroup draws at a time, at most: together a quarter of the list, so that a short list is not
 // spent on slack.
 __host__ __device__ __forceinline__ unsigned long long list_slab_of(unsigned long long list_cap, int64_t workgroups) {
   const unsigned long long s = (list_cap / (4ULL * (unsigned long long)workgroups)) & ~3ULL;
@@ -471,11 +471,12 @@ __device__ __forceinline__ bool reserve_below(unsigned long long* cursor, unsign
 
 // Draws up to `amount` from a shared cursor by addition and returns how much it got; nothing where less than that is left.  (Workgroups
 // with rows of similar length draw at the same moment, and of hundreds that compare and exchange one gets through at a time: 12 770 rows
-// of 3700 entries, 300 000 columns, 512 workgroups, symbolic kernel 5250 | 365 us.)  Draws that pass the look at the cursor together may
-// take it beyond the capacity, where it stays: nobody begins there, and who began before it has what is left.
+// of 3700 entries, 300 000 columns, 512 workgroups, symbolic kernel 5250 | 365 us.)  A draw may take the cursor beyond the capacity, where it
+// stays: nobody begins there, and who began before it has what is left.  look: for an amount that would take much room with it that
+// way (every look and every draw costs all workgroups together about 12 ns: 640 us with both for every row).
 __device__ __forceinline__ unsigned long long draw_below(unsigned long long* cursor, unsigned long long amount, unsigned long long cap,
-                                                         unsigned long long& base) {
-  if (__hip_atomic_load(cursor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + amount > cap) return 0;
+                                                         bool look, unsigned long long& base) {
+  if (look && __hip_atomic_load(cursor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + amount > cap) return 0;
   base = atomicAdd(cursor, amount);
   return base >= cap ? 0 : (cap - base < amount ? cap - base : amount);
 }
@@ -637,11 +638,17 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
         if (want_list) {
           if (need <= tp->sl_left) {
             at = tp->sl_pos; tp->sl_pos += need; tp->sl_left -= need; listed = true;
-          } else {   // (what is left of the old slab stays unused)
+          } else {
+            // (room for a power of two of rows like this one: rows are of similar length, and what is left of the old slab stays
+            // unused; a row that takes more than half of a slab draws for itself alone)
+            unsigned grab = (unsigned)need;
+            while ((unsigned long long)grab * 2 <= list_slab) grab *= 2;
+            const bool alone = grab == (unsigned)need;
             unsigned long long base;
-            const unsigned long long got = draw_below(&ctl->list_cursor, need > list_slab ? need : list_slab, list_cap, base);
+            const unsigned long long got = draw_below(&ctl->list_cursor, grab, list_cap, alone, base);
             if (got >= need) {
-              at = base; tp->sl_pos = base + need; tp->sl_left = got - need; listed = true;
+              at = base; listed = true;
+              if (!alone) { tp->sl_pos = base + need; tp->sl_left = got - need; }
             } else {
               if (got > tp->sl_left) { tp->sl_pos = base; tp->sl_left = got; }   // (the end of the list, for a shorter row)
               if (reserve_below(&ctl->list_cursor, need, list_cap, base)) { at = base; listed = true; }   // (no room for a slab, but for the row alone)

@@ -397,11 +397,15 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
   p->blk_ptr = with_bp ? reinterpret_cast<int*>(base + o_bp) : nullptr;
   // Column list: the dense symbolic kernel leaves the columns of its ranked tiles there, which saves
   // the numeric kernel one pass over those tiles' products.  (Every row's share is rounded up to 16 bytes.)
-  // On top of it the first slab of every workgroup of the symbolic kernel (a quarter of the list, at most kListSlab entries each:
-  // list_slab_of): a workgroup whose rows are longer than the slab leaves it unused, and without room for that a quarter of the
-  // rows of a product with few repeated columns lost their place in the list (300 rows of 3000 entries: 225 of them listed).
-  const double entries_want = entries + 4.0 * rows_d * spans, slabs = wgs * kListSlab;
-  *list_want = (entries_want + (entries_want / 3.0 < slabs ? entries_want / 3.0 : slabs) + 64.0) * 4.0;   // (+ 64: it is cut to whole 256 bytes)
+  // On top of it what the workgroups of the symbolic kernel draw and leave unused: the first or last slab of each (a quarter of the list, at
+  // most kListSlab entries each: list_slab_of) and the ends of the others.  Without room for that a quarter of the rows of a product with
+  // few repeated columns lost their place in the list (300 rows of 3000 entries: 225 of them listed), and one such row sends all
+  // tiles to the general numeric kernel.
+  // (a row takes no more than the flag words of its spans, or the columns of a searched one)
+  const double words = (double)(span_flag_words(B->cols, 0) + span_rank_slots(span_flag_words(B->cols, 0)));
+  const double row_most = spans * (words > (double)kSearchRow ? words : (double)kSearchRow);
+  const double entries_want = (entries < rows_d * row_most ? entries : rows_d * row_most) + 4.0 * rows_d * spans, slabs = wgs * kListSlab;
+  *list_want = (1.15 * entries_want + (0.4 * entries_want < slabs ? 0.4 * entries_want : slabs) + 64.0) * 4.0;   // (+ 64: it is cut to whole 256 bytes)
   return SPGEMM_OK;
 }
 

@@ -65,3 +65,14 @@ def test_rows_of_one_length_that_draw_at_the_same_moment(cols, room):
     got = gpu_product(A, B, options={4: int(need * room)})   # (SPGEMM_OPT_COLUMN_LIST)
     assert_matches_oracle(A, B, got, ref=ref, what=f"room for {room} of the rows")
     assert 0 < got[3]["plan_list_used"] <= got[3]["plan_list_bytes"] <= need * room
+
+
+@pytest.mark.parametrize("rows,mean,b_mean,cols", [(6000, 50, 50, 100_000), (6000, 50, 50, 300_000), (700, 300, 20, 400_000), (3000, 12, 400, 1_000_000)])
+def test_every_row_of_one_length_finds_room(rows, mean, b_mean, cols):
+    """Hardly a column twice, several rows for each workgroup: the list of a plan without a limit has room for all columns."""
+    A = W.uniform_rows(rows, 3000, mean, 97, 1, np.float32)
+    B = W.uniform_rows(3000, cols, b_mean, 97, 3, np.float32)
+    got = gpu_product(A, B)
+    ref = assert_matches_oracle(A, B, got, what=f"{rows} rows")
+    assert got[3]["num_bin_rows"][5] + got[3]["num_bin_rows"][6] == rows
+    assert got[3]["plan_list_used"] == int(((ref.cnt + 3) // 4 * 4).sum()) * 4
