@@ -17,7 +17,7 @@
 //   2750 | 1300 | -, four row blocks of it - | 2210 | 1750, scale 19 15.8 | 12.0 ms | -; the heaviest rows are what 8 waves take too
 //   long for (1500 rows of a block of scale 15: 73 us a block with 16 waves, 123 with 8).  Deduplication sweep, 10000 columns: 1134 |
 //   695 (four of 8 waves) | 760.
-// Numeric (k_num_tiles), one tile at a time, one pass over the tile's products:
+// Numeric (k_num_tiles, or k_num_wide), one tile at a time, one pass over the tile's products:
 //   direct tile (one block of kBlkCols columns in which the row is dense): sums live in a
 //     dense array indexed by column; the flags say which exist; flags and sums are compressed
 //     at the end ("boolean indexing" in the paper's words).
@@ -39,7 +39,8 @@ constexpr int kSymFlagWords = 32768;    // 2^20 columns per symbolic span (128 K
 constexpr int kBlkCols = 8192;          // tile boundaries are multiples of this many columns
 constexpr int kBlkShift = 13;
 constexpr int kSpanBlocks = kSymFlagWords * 32 / kBlkCols;   // 128 blocks per symbolic span
-constexpr int kTileBudget = 66 * 1024; // LDS bytes of one numeric tile (flags + ranks + sums)
+constexpr int kTileBudget = 66 * 1024; // LDS bytes of one numeric tile (flags + ranks + sums): two workgroups on a compute unit
+constexpr int kWideTileBudget = 135 * 1024;   // ... of a wide one: one workgroup (wide_tiles_from says which products)
 constexpr int kRankBlkBytes = kBlkCols / 32 * 8;   // flag word + rank per 32 columns of a ranked tile
 constexpr int kRankEntryBytes = 8;                // sum per entry of a ranked tile (its column goes straight to C)
 constexpr int kDirectMinDefault = 6144; // a block with at least this many entries becomes a direct tile
@@ -51,11 +52,11 @@ constexpr int kDirectBit = 1 << 30;     // in TileRec::cnt
 constexpr int kSearchBit = 1 << 29;     // in TileRec::cnt: a searched tile (ranks by bisection of the column list)
 constexpr int kCountMask = kSearchBit - 1;
 constexpr int kSearchCap = 5632;      // entries of a searched tile (column 4 B + sum 8 B each)
-constexpr int kSearchRow = 2 * kSearchCap;   // entries of a row that becomes searched tiles: one, or two
+constexpr int kSearchRow = 2 * kSearchCap;   // entries of a row that becomes searched tiles: one, or two (one wide one)
 constexpr int kBlkWords = kBlkCols / 32;
 constexpr int kListStage = 5 * kWave;   // entries that a wave gathers in LDS (the piece walker's, free by then) before writing them to the column list
 // every tile kind must fit the tile area of the numeric kernel
-static_assert((long long)kSearchCap * 12 <= kTileBudget, "searched tile: 4 B column + 8 B sum per entry");
+static_assert((long long)kSearchCap * 12 <= kTileBudget && (long long)kSearchRow * 12 <= kWideTileBudget, "searched tile: 4 B column + 8 B sum per entry");
 static_assert((long long)kBlkCols * 8 + kBlkCols / 8 <= kTileBudget, "direct tile: sums, flag words");
 static_assert(kRankBlkBytes + 8LL * kBlkCols <= kTileBudget, "ranked tile: one block must fit even when it is full");
 constexpr long long kListBias = 1LL << 40;   // RunRec::list holds position + bias (so that -1 can mean "none")
@@ -337,6 +338,14 @@ struct SearchRange {   // binary search in an ascending row
   }
 };
 
+// What a workgroup has left of the slabs drawn from the plan's lists, and what its rows have taken.
+struct Slabs {
+  unsigned long long list_used;         // list entries taken
+  unsigned long long sl_pos, sl_left;   // left: list entries,
+  unsigned st_pos, st_left, sr_pos, sr_left;   // tile records, run records
+  unsigned used_tiles, used_runs;
+};
+
 // LDS of the tile planner.
 struct __align__(16) TilePlan {
   int grp[kSpanGroups];   // entries per group of kGrpWords flag words
@@ -351,10 +360,7 @@ struct __align__(16) TilePlan {
   int span_out0;          // row_out when the span began
   long long list_base;    // position of the span's first entry (or first flag word) in the plan's list, -1 = none
   int list_words;         // > 0: the span's structure goes to the list as that many flag words instead of columns
-  unsigned long long list_used;   // list entries that this workgroup's rows have taken
-  unsigned long long sl_pos, sl_left;   // what is left of the slabs drawn from the plan's lists: list entries,
-  unsigned st_pos, st_left, sr_pos, sr_left;   // tile records, run records
-  unsigned used_tiles, used_runs;
+  Slabs slabs;
 };
 
 // index of the lowest set bit at or above position b in the 128-bit mask (hi:lo); 128 when none
@@ -384,7 +390,7 @@ __device__ __forceinline__ int prev_bit128(unsigned long long lo, unsigned long 
 
 // Cuts the nb blocks of one span (counts in tp->blk_cnt) into tiles; run by wave 0.
 // A block with at least direct_min entries is a direct tile of its own; the blocks between
-// are grouped greedily into ranked tiles of at most kTileBudget bytes
+// are grouped greedily into ranked tiles of at most `budget` bytes
 // (kRankBlkBytes per block + kRankEntryBytes per entry).  Records land in tp->rec, their number in tp->ntiles.
 // First part (wave 0): entry prefix over the blocks and the span's total.
 constexpr bool kSpanTwoHalves = kSpanBlocks > kWave;   // a lane plans one block, or two
@@ -408,7 +414,7 @@ __device__ __forceinline__ void plan_head(TilePlan* tp, int nb, bool count_only)
 }
 
 // Second part (wave 0): the tile records (direct and ranked tiles).
-__device__ __forceinline__ void plan_tail(TilePlan* tp, int nb, int block0, int direct_min) {
+__device__ __forceinline__ void plan_tail(TilePlan* tp, int nb, int block0, int direct_min, int budget) {
   const int l = lane_id();
   const int c0 = l < nb ? tp->blk_cnt[l] : 0;
   const int c1 = (kSpanTwoHalves && l + 64 < nb) ? tp->blk_cnt[l + 64] : 0;
@@ -424,7 +430,7 @@ __device__ __forceinline__ void plan_tail(TilePlan* tp, int nb, int block0, int 
       int lo = b + 1, hi = lim;             // largest e in [b+1, lim] that fits
       while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if ((long long)(mid - b) * kRankBlkBytes + (long long)kRankEntryBytes * (tp->cum[mid] - base) <= kTileBudget) lo = mid; else hi = mid - 1;
+        if ((long long)(mid - b) * kRankBlkBytes + (long long)kRankEntryBytes * (tp->cum[mid] - base) <= budget) lo = mid; else hi = mid - 1;
       }
       tp->nxt[b] = lo;
     }
@@ -502,7 +508,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
                                                              int64_t n_cols, const int* __restrict__ ip, int* __restrict__ cnt,
                                                              TileRec* __restrict__ tiles, RunRec* __restrict__ runs,
                                                              int32_t* __restrict__ col_list, int direct_min, int no_tiles_ip,
-                                                             int search_ratio, const int* __restrict__ bp, int nb1, int64_t b_nnz, int run_tiles) {
+                                                             int search_ratio, const int* __restrict__ bp, int nb1, int64_t b_nnz, int run_tiles, int wide) {
   constexpr int kThreads = WAVES * kWave;
   extern __shared__ __align__(16) unsigned char smem[];
   const int flag_words = sym_flag_words(n_cols);
@@ -517,20 +523,18 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
   const unsigned tile_cap = ctl->tile_cap, run_cap = ctl->run_cap;
   const unsigned long long list_cap = ctl->list_cap;
   SPG_CLK(clk_begin(&rs->clk);)
-  if (tid == 0) tp->list_used = 0;
   int row = next_dense_row(perm, ctl, &rs->s_row);
   int next_row = -1;   // (thread 0) the row after this one, fetched while this one is in the works
-  // Thread 0's slabs of the plan's lists are in LDS (its registers would be everybody's).  The first slab of
+  // Thread 0's slabs of the plan's lists are in LDS (its registers would be everybody's), but where there are registers to spare (R-MAT
+  // scale 20: 44.6 | 43.0 ms).  The first slab of
   // every workgroup is its own by its number (the cursors start behind these: k_set_caps); when all workgroups drew their
   // first slab from the shared cursors at the same moment, the compare-and-swaps of 256 of them took 0.2 ms (1071 rows: 366 -> 73 us).
   const unsigned long long list_slab = list_slab_of(list_cap, gridDim.x);
   const unsigned rslab = run_slab(row_hi - row_lo, gridDim.x);
-  if (tid == 0) {
-    tp->sl_pos = blockIdx.x * list_slab; tp->sl_left = list_slab;
-    tp->st_pos = blockIdx.x * (unsigned)kTileSlab; tp->st_left = kTileSlab;
-    tp->sr_pos = blockIdx.x * rslab; tp->sr_left = rslab;
-    tp->used_tiles = 0; tp->used_runs = 0;
-  }
+  Slabs own{};
+  Slabs& sl = ALONE ? own : tp->slabs;
+  if (tid == 0)
+    sl = Slabs{0, blockIdx.x * list_slab, list_slab, blockIdx.x * (unsigned)kTileSlab, (unsigned)kTileSlab, blockIdx.x * rslab, rslab, 0, 0};
   while (row >= 0) {
     unsigned nx = 0;   // (thread 0) the draw for the row after this one: on its way while this row is in the works
     if (tid == 0) nx = atomicAdd(&ctl->work[0], 1u);
@@ -595,7 +599,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
       const int block0 = (int)(c0 >> kBlkShift);
       if (tid < kWave) {
         plan_head(tp, nb, count_only);
-        if (!count_only) plan_tail(tp, nb, block0, direct_min);
+        if (!count_only) plan_tail(tp, nb, block0, direct_min, wide ? kWideTileBudget : kTileBudget);
       }
       __syncthreads();
       SPG_CLK(clk_mark(&rs->clk, 6);)
@@ -603,9 +607,10 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
         // Everything this span needs from the plan's shared lists, and the next row, in one round trip:
         // room for the entries in the column list (without it the numeric kernel rebuilds the flags
         // itself), tile and run records.  A span that got room in the list and has at
-        // most kSearchRow entries and at most search_ratio products per entry becomes one searched tile, or two, where that is
-        // less than half of the tiles planned above (whose records then stay unused): a bisection costs three times the
-        // look-up in a ranked tile (R-MAT scale 17, searched wherever a tile was saved: row blocks 7.27 ms, now 6.83).
+        // most search_ratio products per entry becomes searched tiles (the records planned above then stay unused): one of at most
+        // kSearchCap entries, or two of an ascending B, where that is less than half of the tiles planned: a bisection costs
+        // three times the look-up in a ranked tile (R-MAT scale 17, searched wherever a tile was saved: row blocks 7.27 ms, now 6.83).
+        // Wide tiles: one of at most kSearchRow entries wherever a tile is saved.
         const int total = tp->cum[kSpanBlocks];
         const int nt = tp->ntiles;
         const int nr = (nt + run_tiles - 1) / run_tiles;
@@ -617,9 +622,9 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
         const long long span_products = (n_cols > span && sorted) ? (long long)rs->span_ip : (long long)ip[row];
         // (a searched tile takes every product of its pieces: with unordered B rows the pieces are whole rows,
         // so the tile must be the whole row)
-        bool search_row = (sorted || n_cols <= span) && total <= kSearchRow && nt > (total <= kSearchCap ? 2 : 4) && span_products <= (long long)search_ratio * total;
+        bool search_row = (sorted || n_cols <= span) && total <= kSearchRow && nt > (wide ? 1 : total <= kSearchCap ? 2 : 4) && span_products <= (long long)search_ratio * total;
         int cut = nb;   // where the second searched tile begins
-        if (search_row && total > kSearchCap) {
+        if (search_row && !wide && total > kSearchCap) {
           int e = 0;   // as many blocks as one tile holds
           for (int step = kSpanBlocks / 2; step > 0; step >>= 1)
             if (e + step < nb && tp->cum[e + step] <= kSearchCap) e += step;
@@ -636,8 +641,8 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
         unsigned tb = 0, rb = 0;
         bool listed = false;
         if (want_list) {
-          if (need <= tp->sl_left) {
-            at = tp->sl_pos; tp->sl_pos += need; tp->sl_left -= need; listed = true;
+          if (need <= sl.sl_left) {
+            at = sl.sl_pos; sl.sl_pos += need; sl.sl_left -= need; listed = true;
           } else {
             // (room for a power of two of rows like this one: rows are of similar length, and what is left of the old slab stays
             // unused; a row that takes more than half of a slab draws for itself alone)
@@ -648,33 +653,33 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
             const unsigned long long got = draw_below(&ctl->list_cursor, grab, list_cap, alone, base);
             if (got >= need) {
               at = base; listed = true;
-              if (!alone) { tp->sl_pos = base + need; tp->sl_left = got - need; }
+              if (!alone) { sl.sl_pos = base + need; sl.sl_left = got - need; }
             } else {
-              if (got > tp->sl_left) { tp->sl_pos = base; tp->sl_left = got; }   // (the end of the list, for a shorter row)
+              if (got > sl.sl_left) { sl.sl_pos = base; sl.sl_left = got; }   // (the end of the list, for a shorter row)
               if (reserve_below(&ctl->list_cursor, need, list_cap, base)) { at = base; listed = true; }   // (no room for a slab, but for the row alone)
             }
           }
         }
         bool room = true;
         if (nt > 0) {
-          if ((unsigned)nt > tp->st_left) {
-            tp->st_pos = atomicAdd(&ctl->tile_cursor, (unsigned)kTileSlab);
-            room = tp->st_pos + (unsigned)kTileSlab <= tile_cap;
-            tp->st_left = room ? (unsigned)kTileSlab : 0u;
+          if ((unsigned)nt > sl.st_left) {
+            sl.st_pos = atomicAdd(&ctl->tile_cursor, (unsigned)kTileSlab);
+            room = sl.st_pos + (unsigned)kTileSlab <= tile_cap;
+            sl.st_left = room ? (unsigned)kTileSlab : 0u;
           }
-          if (room && (unsigned)nr > tp->sr_left) {
-            for (unsigned i = 0; i < tp->sr_left; ++i) runs[tp->sr_pos + i].count = 0;   // (slots left behind: empty records)
+          if (room && (unsigned)nr > sl.sr_left) {
+            for (unsigned i = 0; i < sl.sr_left; ++i) runs[sl.sr_pos + i].count = 0;   // (slots left behind: empty records)
             const unsigned grab = (unsigned)nr > rslab ? (unsigned)nr : rslab;
-            tp->sr_pos = atomicAdd(&ctl->run_cursor, grab);
-            room = tp->sr_pos + grab <= run_cap;
-            tp->sr_left = room ? grab : 0u;
+            sl.sr_pos = atomicAdd(&ctl->run_cursor, grab);
+            room = sl.sr_pos + grab <= run_cap;
+            sl.sr_left = room ? grab : 0u;
           }
           if (room) {
-            tb = tp->st_pos; tp->st_pos += (unsigned)nt; tp->st_left -= (unsigned)nt;
-            rb = tp->sr_pos; tp->sr_pos += (unsigned)nr; tp->sr_left -= (unsigned)nr;
+            tb = sl.st_pos; sl.st_pos += (unsigned)nt; sl.st_left -= (unsigned)nt;
+            rb = sl.sr_pos; sl.sr_pos += (unsigned)nr; sl.sr_left -= (unsigned)nr;
           }
         }
-        if (listed) tp->list_used += need;
+        if (listed) sl.list_used += need;
         else if (total > 0 && !count_only) ctl->unlisted = 1;
         tp->list_base = listed ? (long long)at : -1;
         tp->list_words = listed && as_words ? fwords : 0;
@@ -697,8 +702,8 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
         } else if (tp->ndirect > 0) {
           atomicAdd(&ctl->direct_tiles, (unsigned)tp->ndirect);
         }
-        tp->used_tiles += (unsigned)tp->ntiles;
-        tp->used_runs += (unsigned)tp->nruns;
+        sl.used_tiles += (unsigned)tp->ntiles;
+        sl.used_runs += (unsigned)tp->nruns;
         if (last_span) next_row = nx < row_hi - row_lo ? perm[row_hi - 1 - nx] : -1;
       }
       __syncthreads();
@@ -813,10 +818,10 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
     row = rs->s_row;
   }
   if (tid == 0) {
-    for (unsigned i = 0; i < tp->sr_left; ++i) runs[tp->sr_pos + i].count = 0;
-    if (tp->used_tiles) atomicAdd(&ctl->tiles_used, tp->used_tiles);
-    if (tp->used_runs) atomicAdd(&ctl->runs_used, tp->used_runs);
-    if (tp->list_used) atomicAdd(&ctl->list_used, tp->list_used);
+    for (unsigned i = 0; i < sl.sr_left; ++i) runs[sl.sr_pos + i].count = 0;
+    if (sl.used_tiles) atomicAdd(&ctl->tiles_used, sl.used_tiles);
+    if (sl.used_runs) atomicAdd(&ctl->runs_used, sl.used_runs);
+    if (sl.list_used) atomicAdd(&ctl->list_used, sl.list_used);
   }
   SPG_CLK(clk_mark(&rs->clk, 9); clk_flush(&rs->clk, ctl->clk[0]);)
 }

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
@@ -22,6 +23,7 @@
 #include "hash_kernels.hpp"
 #include "dense_kernels.hpp"
 #include "tile_kernels.hpp"
+#include "wide_kernels.hpp"
 #include "staged_kernels.hpp"
 #include "sort_kernels.hpp"
 #include "tensor_kernels.hpp"
@@ -29,10 +31,10 @@
 
 using namespace spg;
 
-// a workgroup of the big kernels owns the whole LDS of a compute unit (160 KB)
-static_assert(num_tiles_lds<double, true>() <= 160 * 1024 && num_tiles_lds<float, true>() <= 160 * 1024, "numeric dense kernel exceeds LDS");
+// the LDS of a compute unit (160 KB) belongs to one workgroup of the big kernels, or to two
+static_assert(num_wide_lds<double>() <= 160 * 1024, "numeric dense kernel exceeds LDS");
 static_assert(sym_dense_lds<16>(kSymFlagWords) <= 160 * 1024, "symbolic dense kernel exceeds LDS");
-static_assert(sym_dense_lds<8>(kSymNarrowCols / 32) <= 80 * 1024 && sym_dense_lds<16>(kSymShortCols / 32) <= 80 * 1024 && num_tiles_lds<double, false>() <= 80 * 1024 && num_tiles_lds<float, false>() <= 80 * 1024, "two workgroups on a compute unit");
+static_assert(sym_dense_lds<8>(kSymNarrowCols / 32) <= 80 * 1024 && sym_dense_lds<16>(kSymShortCols / 32) <= 80 * 1024 && num_tiles_lds<double>() <= 80 * 1024, "two workgroups on a compute unit");
 static_assert(staged_lds<double>() <= 160 * 1024 && staged_lds<float>() <= 160 * 1024, "staged kernel exceeds LDS");
 
 // Pinned host memory where the symbolic kernels leave the control block for the host.  Allocating and releasing it costs 50 to
@@ -92,6 +94,7 @@ struct spgemm_context {
   int block_table = 1;    // 0: never build the block-offset table of B (pieces are bisected)
   int search_ratio = 4;   // searched tiles for rows with at most this many products per entry (0: never)
   int row_block = 0;      // 1: A is a block of rows of a larger matrix (row pointer values are that matrix's positions)
+  double whole_ip = 0;    // ... and the products of all its rows
   std::string err = "";
   bool device_ready = false;
   int num_cus = 0;
@@ -134,6 +137,7 @@ struct spgemm_plan_s {
   bool all_listed = false;       // every row of the dense classes has its structure in the column list
   bool order_kept = false;       // the checksums of the order of the entries were taken
   bool tiles_ordered = false;    // rows were planned as tiles of an ascending B
+  bool wide_tiles = false;       // the tiles are planned for a workgroup that has a compute unit to itself
   bool symbolic_done = false;
   bool numeric_pending = false;   // timed numeric launches not yet folded into stats
   bool numeric_in_flight = false; // numeric kernels were enqueued and the stream has not been waited for since
@@ -207,10 +211,10 @@ int ensure_device(spgemm_context* h) {
   if ((rc = allow_lds(h, k_sym_dense<16, false>, sym_dense_lds<16>(kSymFlagWords)))) return rc;
   if ((rc = allow_lds(h, k_sym_dense<16, true>, sym_dense_lds<16>(kSymFlagWords)))) return rc;
   if ((rc = allow_lds(h, k_sym_dense<8, false>, sym_dense_lds<8>(kSymNarrowCols / 32)))) return rc;
-  if ((rc = allow_lds(h, k_num_tiles<float, false>, num_tiles_lds<float, false>()))) return rc;
-  if ((rc = allow_lds(h, k_num_tiles<double, false>, num_tiles_lds<double, false>()))) return rc;
-  if ((rc = allow_lds(h, k_num_tiles<float, true>, num_tiles_lds<float, true>()))) return rc;
-  if ((rc = allow_lds(h, k_num_tiles<double, true>, num_tiles_lds<double, true>()))) return rc;
+  if ((rc = allow_lds(h, k_num_tiles<float>, num_tiles_lds<float>()))) return rc;
+  if ((rc = allow_lds(h, k_num_tiles<double>, num_tiles_lds<double>()))) return rc;
+  if ((rc = allow_lds(h, k_num_wide<float>, num_wide_lds<float>()))) return rc;
+  if ((rc = allow_lds(h, k_num_wide<double>, num_wide_lds<double>()))) return rc;
   if ((rc = allow_lds(h, k_num_staged<float>, staged_lds<float>()))) return rc;
   if ((rc = allow_lds(h, k_num_staged<double>, staged_lds<double>()))) return rc;
   h->device_ready = true;
@@ -356,6 +360,30 @@ SymDense sym_dense_shape(spgemm_context* h, int64_t rows, int64_t cols) {
 // tile; 5266 rows of scale 14: 153 together, 161 by tile).
 int run_tiles_of(spgemm_context* h, int64_t rows) { return rows <= (int64_t)h->num_cus * 8 ? 1 : kRunTiles; }
 
+// Whether the tiles are planned for k_num_wide, one workgroup on a compute unit, from what is known before: the dense rows and their
+// products, and the products of an entry of A.  (Later only whether the list holds all rows: run_symbolic.)
+// k_num_tiles hides what a tile costs beside its products behind its neighbour's products, but has twice as many tiles.  It gains where a
+// row's searched tiles or its only tile are few products, and where many products of an entry of A fall into a tile; it loses where
+// these are few.  us for 3000 rows of uniform columns, wide | two workgroups: rows of B of 60 entries, 24 000 products a row, 20 000 columns
+// 224 | 337 (3 small tiles a row), 150 000 columns 346 | 435 (4), 60 000 products 960 | 1574 (9), 150 000 products 2953 | 8108 (18);
+// of 250 entries 285 | 298, 602 | 662, 1295 | 2143; of 1000 entries 281 | 291, 569 | 584, 1150 | 1318; one tile a row 114 | 107, 111 | 95, 111 |
+// 97; direct tiles only (20 000 columns, 150 000 products) 1373 | 1270, 797 | 710, 715 | 596.  R-MAT squared, 16 edges: scale 14 204 | 169,
+// scale 17 3311 | 2812, scale 19 25.9 | 23.4 ms; 4 edges, scale 18 1348 | 1210.  6000 products a row, 400 000 columns 293 | 186 us.
+// Beyond 2^19 columns a row's flag words alone are four small tiles: 24 000 products, 10^6 columns 410 | 478 to 511 | 694 us, R-MAT scale 20
+// 70.5 | 74.9 ms; but rows that are mostly searched 3.28 | 2.35 ms (600 000 columns, 4800 products).
+bool wide_tiles_from(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, bool with_table, double rows_d, double ip_d, double ip_all) {
+  if (!with_table || B->nnz >= kTileMaxNnz) return true;   // (k_num_tiles has no way without)
+  const double ip_row = ip_d / rows_d, n = (double)B->cols, blocks = (double)ceil_div(B->cols, kBlkCols);
+  if (ip_row <= (double)kSearchRow) return false;
+  if (B->cols > kSymNarrowCols) return true;
+  const double entries = n * -std::expm1(-ip_row / n);   // (of a row of C, were its columns drawn uniformly)
+  const bool direct = entries >= h->direct_min * n / kBlkCols;
+  const double per_tile = std::floor(kTileBudget / (kRankBlkBytes + kRankEntryBytes * entries / blocks));   // blocks
+  const double tiles = direct || per_tile < 1.0 ? blocks : std::ceil(blocks / per_tile);
+  const double per_entry = p->nnz_a > 0 ? ip_all / (double)p->nnz_a : 0.0;
+  return tiles > 1.0 && per_entry < (direct ? 16.0 : 64.0) * tiles;
+}
+
 // Sizes and allocates what the dense kernels need beyond the per-row arrays: the tile and run
 // lists (from an upper bound of the number of tiles) and the table of block offsets of B.
 int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, const Control& host, unsigned* tile_cap,
@@ -375,15 +403,16 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
   const double weight = rows_d * blocks * kRankBlkBytes + (double)kRankEntryBytes * entries;
   // (+ a slab per workgroup of the symbolic kernel: what a workgroup has drawn and not used; a row whose runs do not fit
   // what is left of a run slab leaves fewer records behind than it takes, hence twice the runs)
+  p->blk_ptr_cols = (int)blocks + 1;
+  const size_t bp_bytes = (size_t)B->rows * (size_t)p->blk_ptr_cols * 4;
+  const bool with_bp = h->block_table && host.b_sorted && B->nnz > 0 && bp_bytes <= ((size_t)1 << 30);
+  p->wide_tiles = wide_tiles_from(h, p, B, with_bp, rows_d, ip_d, h->row_block ? h->whole_ip : (double)host.ip_total);
   const double wgs = (double)sym_dense_shape(h, (int64_t)rows_d, B->cols).groups + 1.0;
-  const double tiles = 2.0 * direct + 2.0 * weight / kTileBudget + 4.0 * rows_d * spans + 16.0 + wgs * kTileSlab;
+  const double tiles = 2.0 * direct + 2.0 * weight / (p->wide_tiles ? kWideTileBudget : kTileBudget) + 4.0 * rows_d * spans + 16.0 + wgs * kTileSlab;
   const double runs = 2.0 * ((tiles - wgs * kTileSlab) / run_tiles_of(h, (int64_t)rows_d) + rows_d * spans + 16.0) + wgs * kRunSlab;
   if (tiles > 4.0e9) return fail(h, SPGEMM_UNSUPPORTED, "tile list of the dense workspace would exceed 2^32 records");
   *tile_cap = (unsigned)tiles;
   *run_cap = (unsigned)runs;
-  p->blk_ptr_cols = (int)blocks + 1;
-  const size_t bp_bytes = (size_t)B->rows * (size_t)p->blk_ptr_cols * 4;
-  const bool with_bp = h->block_table && host.b_sorted && B->nnz > 0 && bp_bytes <= ((size_t)1 << 30);
   size_t off = 0;
   const size_t o_tiles = off; off = align_up(off + (size_t)*tile_cap * sizeof(TileRec));
   const size_t o_runs = off; off = align_up(off + (size_t)*run_cap * sizeof(RunRec));
@@ -537,6 +566,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   }
   if (rc) return rc;
   alloc_optional(h, p, B, host, list_want, sizeof(T), staged > 0, plan_leaves);
+  if ((double)p->list_bytes + 256.0 <= list_want) p->wide_tiles = true;   // (some row may find no room in the list)
   p->tiles_ordered = rows_dense > 0 && host.b_sorted != 0;
   p->order_kept = plan_leaves && (p->records || p->esc_words[0] || p->esc_words[1] || (p->tiles_ordered && p->force != 2));
   if (p->order_kept) {
@@ -587,7 +617,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
       Timer t(h, SPGEMM_K_SYM_DENSE);
       const SymDense d = sym_dense_shape(h, rows_dense, B->cols);
       hipLaunchKernelGGL((d.waves == 8 ? k_sym_dense<8, false> : B->cols > kSymNarrowCols ? k_sym_dense<16, true> : k_sym_dense<16, false>), dim3(d.groups), dim3(d.waves * kWave), d.lds, s, p->perm_sym, p->ctl, A->rowptr, A->colidx, B->rowptr, B->colidx, B->cols, p->ip, p->cnt, p->tiles, p->runs, p->col_list, h->direct_min,
-                         staged, h->search_ratio, p->blk_ptr, p->blk_ptr_cols, B->nnz, run_tiles_of(h, rows_dense));
+                         staged, h->search_ratio, p->blk_ptr, p->blk_ptr_cols, B->nnz, run_tiles_of(h, rows_dense), p->wide_tiles ? 1 : 0);
     }
     {
       Timer t(h, SPGEMM_K_BIN);
@@ -713,10 +743,11 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   }
   if (hist[5] + hist[6] > 0 || (tiles3 && hist[3] > 0 && p->stats.dense_runs > 0)) {
     Timer t(h, SPGEMM_K_NUM_DENSE);
-    const bool plain = p->blk_ptr && p->all_listed && B->nnz < kTileMaxNnz;   // (the table is built for ascending rows only)
-    hipLaunchKernelGGL((plain ? k_num_tiles<T, false> : k_num_tiles<T, true>), dim3(grid_for(p->stats.dense_runs, 1, (int64_t)h->num_cus * 2)), dim3(kTileThreads),
-                       (plain ? num_tiles_lds<T, false>() : num_tiles_lds<T, true>()), s, p->ctl, p->bin, p->tiles, p->runs, A->colidx, a_val, B->rowptr,
-                       B->colidx, b_val, B->cols, p->blk_ptr, p->blk_ptr_cols, p->col_list, B->nnz, c_rp, c_col, c_val, tiles3 ? 1 : 0, looked3);
+    // (k_num_tiles has no way around the table, which is built for ascending rows only, or the list; k_num_wide takes tiles of any size)
+    const bool wide = p->wide_tiles || !p->blk_ptr || !p->all_listed || B->nnz >= kTileMaxNnz;
+    hipLaunchKernelGGL((wide ? k_num_wide<T> : k_num_tiles<T>), dim3(grid_for(p->stats.dense_runs, 1, (int64_t)h->num_cus * (wide ? 1 : 2))),
+                       dim3(wide ? kWideThreads : kTileThreads), (wide ? num_wide_lds<T>() : num_tiles_lds<T>()), s, p->ctl, p->bin, p->tiles, p->runs, A->colidx,
+                       a_val, B->rowptr, B->colidx, b_val, B->cols, p->blk_ptr, p->blk_ptr_cols, p->col_list, B->nnz, c_rp, c_col, c_val, tiles3 ? 1 : 0, looked3);
   }
   HIP_TRY(h, hipGetLastError());
   return SPGEMM_OK;
@@ -1298,8 +1329,8 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
     if (e != hipSuccess) return fail(h, SPGEMM_HIP_ERROR, std::string("row-block planning: ") + hipGetErrorString(e));
     if (host.error) return fail(h, SPGEMM_INVALID_INPUT, "device-side input check failed (column out of range or rowptr not monotone)");
   }
+  double total = 0;
   {
-    double total = 0;
     for (int64_t i = 0; i < m; ++i) total += ip_host[(size_t)i] + 1.0;   // (+1: rows without products still cost a little)
     double run = 0;
     int t = 1;
@@ -1317,6 +1348,7 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
   spgemm_context h2 = *h;
   h2.stream = s2;
   h2.row_block = 1;
+  h2.whole_ip = total - (double)m;
   h2.timing = 0;
   h2.timed.clear();
   h2.event_pool.clear();

@@ -2,11 +2,8 @@
 //
 // A workgroup of 1024 threads works on a tile of at most 66 KB; two of them share a compute unit, so that one accumulates
 // products while the other waits for flag words, decodes columns or writes its tile out.  That takes 64 registers a thread and 80
-// KB of LDS a workgroup, hence two variants:
-//   plain (GENERAL = false): B's rows ascend, the block-offset table is there, B has fewer than 2^30 entries, and every row of the
-//     dense classes has its structure in the plan;
-//   general: whatever else is legal - B rows in any order (a tile then filters the products of whole rows), bisected pieces,
-//     rows without structure (a first pass over the products marks the flags).
+// KB of LDS a workgroup, which is enough where B's rows ascend, the block-offset table is there, B has fewer than 2^30 entries, and
+// every row of the dense classes has its structure in the plan; other plans, and some of these, are k_num_wide's (wide_tiles_from).
 // Ranked tiles take 50 to 55 LDS cycles for 64 products (a look-up of 14, an addition of 27, the search for the piece), wide
 // matrices beside that what the tile costs by itself: reads and writes run at 5.8 TB/s at scale 19 (B's entries come from behind
 // the L2 caches).  Before, one workgroup of 16 waves with a tile of 135 KB had a compute unit to itself and accumulated products
@@ -22,12 +19,13 @@ namespace spg {
 
 constexpr int kTileThreads = 1024;
 constexpr int kTileWaves = kTileThreads / kWave;
-constexpr int64_t kTileMaxNnz = int64_t(1) << 30;   // plain: a piece's start shares 32 bits with two others
+constexpr int64_t kTileMaxNnz = int64_t(1) << 30;   // a piece's start shares 32 bits with two others
 
-template <typename T, bool GENERAL, int WAVES = kTileWaves>
+// WHOLE: a tile is a whole row, without structure in the plan (k_row_tiles).
+template <typename T, bool WHOLE, int WAVES = kTileWaves>
 struct TileScratch {
-  using Start = std::conditional_t<GENERAL, unsigned long long, unsigned>;
-  static constexpr int kPieces = WAVES < kTileWaves ? WAVES * kWave : (GENERAL ? 512 : 768);   // pieces of B rows described at a time
+  using Start = std::conditional_t<WHOLE, unsigned long long, unsigned>;
+  static constexpr int kPieces = WHOLE ? WAVES * kWave : 768;   // pieces of B rows described at a time
   Start s[kPieces];               // a piece's first B entry, shifted left by two; entries missing in its last quad below
   int cpre[kPieces + 1];          // exclusive prefix of the pieces' quad counts
   T av[kPieces];                  // a_ik of the piece
@@ -38,23 +36,6 @@ struct TileScratch {
   int split;                      // quads before the pieces of the second round
   SPG_CLK(ClkLds clk;)
 };
-
-// The piece [s, s + len) of B row k that falls into the tile (blocks [b0, b1), columns [t_lo, t_hi)).
-__device__ __forceinline__ void piece_range(int k, long long rs, long long re, int b0, int b1, int t_lo, int64_t t_hi, bool sorted,
-                                            const int* __restrict__ bp, int nb1, const int32_t* __restrict__ b_col,
-                                            long long& s, int& len) {
-  if (sorted && bp) {
-    const int* row = bp + (int64_t)k * nb1;
-    const int o0 = row[b0], o1 = row[b1];
-    s = rs + o0;
-    len = o1 - o0;
-  } else {
-    int64_t st = rs, en = re;
-    if (sorted) SearchRange{b_col, t_lo, t_hi}(k, st, en);
-    s = st;
-    len = (int)(en - st);
-  }
-}
 
 // Records of a run and of a tile, the same for the whole workgroup, in scalar registers (read from LDS they took 30 vector registers).
 __device__ __forceinline__ RunRec uni_run(const RunRec& r) {
@@ -83,10 +64,10 @@ __device__ __forceinline__ void direct_out(const double* acc, const unsigned* fl
 
 // Visits every product of np pieces (nq quads) once, g(quad) per lane: as quad_pass, with the pieces' values and without their
 // lengths (a piece's last quad says how many of its entries are missing).
-template <int WAVES, bool WITH_VALUES, typename T, bool GENERAL, class G>
-__device__ __forceinline__ void tile_pass(int np, int nq, const TileScratch<T, GENERAL, WAVES>* ts, const int32_t* __restrict__ b_col,
+template <int WAVES, bool WITH_VALUES, typename T, bool WHOLE, class G>
+__device__ __forceinline__ void tile_pass(int np, int nq, const TileScratch<T, WHOLE, WAVES>* ts, const int32_t* __restrict__ b_col,
                                           const T* __restrict__ b_val, int64_t b_nnz, G g) {
-  using Start = typename TileScratch<T, GENERAL>::Start;
+  using Start = typename TileScratch<T, WHOLE, WAVES>::Start;
   const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int nb = (nq + kWave - 1) >> 6;
   const int per = (nb + WAVES - 1) / WAVES;
@@ -95,7 +76,7 @@ __device__ __forceinline__ void tile_pass(int np, int nq, const TileScratch<T, G
   if (c >= cend) return;
   int p;   // last piece whose first quad is <= c: among every sixteenth piece first, then among the sixteen
   {
-    static_assert(TileScratch<T, GENERAL, WAVES>::kPieces <= 16 * kWave, "64 steps of sixteen pieces");
+    static_assert(TileScratch<T, WHOLE, WAVES>::kPieces <= 16 * kWave, "64 steps of sixteen pieces");
     const int i0 = lane * 16;
     const int hi = __popcll(__ballot(i0 < np && ts->cpre[i0 < np ? i0 : 0] <= c)) - 1;
     const int i1 = hi * 16 + lane;
@@ -133,18 +114,18 @@ __device__ __forceinline__ void tile_pass(int np, int nq, const TileScratch<T, G
 }
 
 // The tiles of one run; k, av: this thread's A entry, in rows of at most kThreads of them.
-template <int WAVES, typename T, bool GENERAL>
-__device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL, WAVES>* ts, unsigned char* tile, bool sorted, const int32_t* __restrict__ a_col,
+template <int WAVES, typename T, bool WHOLE>
+__device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, WHOLE, WAVES>* ts, unsigned char* tile, const int32_t* __restrict__ a_col,
                                          const T* __restrict__ a_val, const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col,
                                          const T* __restrict__ b_val, int64_t n_cols, const int* __restrict__ bp, int nb1,
                                          const int32_t* __restrict__ col_list, int64_t b_nnz, int64_t out_row, int32_t* __restrict__ c_col,
                                          T* __restrict__ c_val, int k, T av) {
-  using Start = typename TileScratch<T, GENERAL, WAVES>::Start;
-  constexpr int kPieces = TileScratch<T, GENERAL, WAVES>::kPieces;
+  using Start = typename TileScratch<T, WHOLE, WAVES>::Start;
+  constexpr int kPieces = TileScratch<T, WHOLE, WAVES>::kPieces;
   constexpr int kThreads = WAVES * kWave;
   const int tid = threadIdx.x;
-  // the row's structure in the plan: its columns, its flag words, or (general) none
-  const bool have = !GENERAL || rr.list >= 0;
+  // the row's structure in the plan: its columns, its flag words, or (whole rows) none
+  constexpr bool have = !WHOLE;
   const bool have_words = have && (rr.list & kListFlagWords) != 0;
   const long long list_at = (rr.list & (kListFlagWords - 1)) - kListBias;   // entry 0 of the row, or the span's kept structure
   const int nseg = (rr.d + kThreads - 1) / kThreads;
@@ -153,7 +134,7 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
   unsigned crs = 0;
   int pf0 = 0, pf1 = 0;
   const bool mine = nseg == 1 && tid < rr.d;
-  if (!GENERAL && mine) {
+  if (!WHOLE && mine) {
     const TileRec nx = uni_tile(ts->rec[0]);
     crs = (unsigned)b_rp[k];
     const int* row = bp + (int64_t)k * nb1;
@@ -163,8 +144,8 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
   SPG_CLK(clk_mark(&ts->clk, 1);)
   for (int t = 0; t < rr.count; ++t) {
     const TileRec tr = uni_tile(ts->rec[t]);
-    const bool direct = (tr.cnt & kDirectBit) != 0;
-    const bool searched = (tr.cnt & kSearchBit) != 0;
+    const bool direct = have && (tr.cnt & kDirectBit) != 0;
+    const bool searched = have && (tr.cnt & kSearchBit) != 0;
     const int count = tr.cnt & kCountMask;
     const int t_lo = tr.b0 << kBlkShift;
     int64_t t_hi = (int64_t)tr.b1 << kBlkShift;
@@ -172,10 +153,10 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
     const int64_t out = out_row + tr.out;
     Start s = 0;
     int len = 0;
-    if (GENERAL && mine) {
-      long long ps;
-      piece_range(k, b_rp[k], b_rp[k + 1], tr.b0, tr.b1, t_lo, t_hi, sorted, bp, nb1, b_col, ps, len);
-      s = (Start)ps;
+    if (WHOLE && mine) {
+      const Run<int64_t, 2> bounds = load_run<int64_t, 2>(b_rp + k);
+      s = (Start)bounds.v[0];
+      len = (int)(bounds.v[1] - bounds.v[0]);
     } else if (mine) {
       s = crs + (unsigned)pf0;
       len = pf1 - pf0;
@@ -196,10 +177,10 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
           if (e < rr.d) {
             const int ke = a_col[rr.a0 + e];
             av = a_val[rr.a0 + e];
-            if (GENERAL) {
-              long long ps;
-              piece_range(ke, b_rp[ke], b_rp[ke + 1], tr.b0, tr.b1, t_lo, t_hi, sorted, bp, nb1, b_col, ps, len);
-              s = (Start)ps;
+            if (WHOLE) {
+              const Run<int64_t, 2> bounds = load_run<int64_t, 2>(b_rp + ke);
+              s = (Start)bounds.v[0];
+              len = (int)(bounds.v[1] - bounds.v[0]);
             } else {
               const int* row = bp + (int64_t)ke * nb1;
               const int o0 = row[tr.b0];
@@ -228,16 +209,16 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
           if (tid == 0 && i1 == np) ts->cpre[i1 - i0] = nq - q0;
           __syncthreads();
           const int q1 = i1 == np ? nq : uni(ts->split);
-          tile_pass<WAVES, decltype(with_values)::value, T, GENERAL>(i1 - i0, q1 - q0, ts, b_col, b_val, b_nnz, acc);
+          tile_pass<WAVES, decltype(with_values)::value, T, WHOLE>(i1 - i0, q1 - q0, ts, b_col, b_val, b_nnz, acc);
           __syncthreads();
         }
       }
     };
-    // (pieces of unordered B rows are whole rows)
-    auto in_tile = [&](const Quad<T>& q, int i) { return i < q.n && (!GENERAL || (q.col.v[i] >= t_lo && (int64_t)q.col.v[i] < t_hi)); };
+    // (whole rows: operands of another structure than the plan's stay inside the tile)
+    auto in_tile = [&](const Quad<T>& q, int i) { return i < q.n && (!WHOLE || (q.col.v[i] >= t_lo && (int64_t)q.col.v[i] < t_hi)); };
     __syncthreads();   // the previous tile's output has left the tile area
     SPG_CLK(clk_mark(&ts->clk, 2); clk_add(&ts->clk, 22, (unsigned long long)count);)
-    if (searched) {   // (of unordered B rows only where the tile is the whole row)
+    if (searched) {
       // the tile's columns (from the plan's list) and their sums, by rank; a product finds the rank of
       // its column by bisection, so the tile may be as wide as the matrix
       int* cols = reinterpret_cast<int*>(tile);
@@ -282,7 +263,7 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
         const int64_t span_c0 = (int64_t)(tr.b0 / kSpanBlocks) * kSpanBlocks * kBlkCols;
         const int32_t* words = have_words ? col_list + list_at + span_rank_slots(span_flag_words(n_cols, span_c0)) + ((t_lo - span_c0) >> 5)
                                           : col_list + list_at + tr.out;
-        flags[tid] = !have ? 0u : !have_words || tid < (int)((t_hi - t_lo + 31) >> 5) ? (unsigned)words[tid] : 0u;
+        flags[tid] = !have_words || tid < (int)((t_hi - t_lo + 31) >> 5) ? (unsigned)words[tid] : 0u;
       }
       SPG_CLK(clk_mark(&ts->clk, 7); clk_add(&ts->clk, 18, 1);)
       products(std::true_type{}, [&](const Quad<T>& q) {
@@ -290,7 +271,6 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
         for (int i = 0; i < 4; ++i)
           if (in_tile(q, i)) {
             const int rel = q.col.v[i] - t_lo;
-            if (!have) atomicOr(&flags[rel >> 5], 1u << (rel & 31));
             __hip_atomic_fetch_add(&acc[rel], (double)q.a * (double)q.b.v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           }
       });
@@ -437,8 +417,8 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, GENERAL
   }
 }
 
-template <typename T, bool GENERAL>
-__global__ __launch_bounds__(kTileThreads, GENERAL ? 4 : 8) void k_num_tiles(Control* ctl, const unsigned char* __restrict__ numbin, const TileRec* __restrict__ tiles,
+template <typename T>
+__global__ __launch_bounds__(kTileThreads, 8) void k_num_tiles(Control* ctl, const unsigned char* __restrict__ numbin, const TileRec* __restrict__ tiles,
                                                                const RunRec* __restrict__ runs, const int32_t* __restrict__ a_col,
                                                                const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
                                                                const int32_t* __restrict__ b_col, const T* __restrict__ b_val, int64_t n_cols,
@@ -446,9 +426,8 @@ __global__ __launch_bounds__(kTileThreads, GENERAL ? 4 : 8) void k_num_tiles(Con
                                                                const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val, int tiles3, int looked) {
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* tile = smem;                                                         // kTileBudget bytes
-  TileScratch<T, GENERAL>* ts = reinterpret_cast<TileScratch<T, GENERAL>*>(smem + kTileBudget);
+  TileScratch<T, false>* ts = reinterpret_cast<TileScratch<T, false>*>(smem + kTileBudget);
   if (ctl->error) return;
-  const bool sorted = !GENERAL || ctl->b_sorted != 0;
   const bool class3 = tiles3 != 0 && !other_order(ctl, looked);   // (in another order, or where hashing is asked for, k_row_tiles or the hash workspace does these rows)
   const int tid = threadIdx.x;
   const unsigned nruns = ctl->run_cursor;
@@ -499,7 +478,7 @@ __global__ __launch_bounds__(kTileThreads, GENERAL ? 4 : 8) void k_num_tiles(Con
     if (!(cls == 3 && class3) && cls != 5 && cls != 6) continue;   // the row's numeric class is not this kernel's
     __syncthreads();
     SPG_CLK(clk_mark(&ts->clk, 0); clk_add(&ts->clk, 16, 1);)
-    tile_run<kTileWaves, T, GENERAL>(rr, ts, tile, sorted, a_col, a_val, b_rp, b_col, b_val, n_cols, bp, nb1, col_list, b_nnz, out_row, c_col, c_val, k, av);
+    tile_run<kTileWaves, T, false>(rr, ts, tile, a_col, a_val, b_rp, b_col, b_val, n_cols, bp, nb1, col_list, b_nnz, out_row, c_col, c_val, k, av);
   }
   SPG_CLK(clk_mark(&ts->clk, 14); clk_flush(&ts->clk, ctl->clk[1]);)
 }
@@ -530,7 +509,6 @@ __global__ __launch_bounds__(kRowTileWaves * kWave, 4) void k_row_tiles(const in
   TileScratch<T, true, kRowTileWaves>* ts = reinterpret_cast<TileScratch<T, true, kRowTileWaves>*>(smem + row_tile_bytes<T>(n_cols));
   if (ctl->error) return;
   if (other_order(ctl, looked)) most_ip = 0x7fffffff;
-  const bool sorted = ctl->b_sorted != 0;
   const unsigned first = ctl->offset[1][3], nrows = ctl->offset[1][4] - first;
   const int tid = threadIdx.x;
   for (unsigned i = blockIdx.x; i < nrows; i += gridDim.x) {
@@ -545,13 +523,13 @@ __global__ __launch_bounds__(kRowTileWaves * kWave, 4) void k_row_tiles(const in
     T av = T(0);
     if (d <= kRowTileWaves * kWave && tid < d) { k = a_col[a0 + tid]; av = a_val[a0 + tid]; }
     __syncthreads();
-    tile_run<kRowTileWaves, T, true>(RunRec{row, 0, 1, d, a0, -1}, ts, smem, sorted, a_col, a_val, b_rp, b_col, b_val, n_cols, (const int*)nullptr, 0,
+    tile_run<kRowTileWaves, T, true>(RunRec{row, 0, 1, d, a0, -1}, ts, smem, a_col, a_val, b_rp, b_col, b_val, n_cols, (const int*)nullptr, 0,
                                      (const int32_t*)nullptr, b_nnz, out, c_col, c_val, k, av);
     __syncthreads();
   }
 }
 
-template <typename T, bool GENERAL>
-constexpr size_t num_tiles_lds() { return (size_t)kTileBudget + sizeof(TileScratch<T, GENERAL>); }
+template <typename T>
+constexpr size_t num_tiles_lds() { return (size_t)kTileBudget + sizeof(TileScratch<T, false>); }
 
 }  // namespace spg
