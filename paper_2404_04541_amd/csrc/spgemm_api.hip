@@ -657,7 +657,8 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   const int64_t* hist = p->stats.num_bin_rows;
   // (rows of class 3 with more products than the symbolic hash takes have tiles: those do them, unless hashing is asked for)
   const bool tiles3 = p->force != 2;
-  if (hist[4] + hist[5] + hist[6] + (tiles3 ? hist[3] : 0) > 0) hipLaunchKernelGGL(k_reset_numeric_work, dim3(1), dim3(64), 0, s, p->ctl);
+  const bool run_tiles = hist[5] + hist[6] > 0 || (tiles3 && hist[3] > 0 && p->stats.dense_runs > 0);
+  if (hist[4] > 0 || run_tiles) hipLaunchKernelGGL(k_reset_numeric_work, dim3(1), dim3(64), 0, s, p->ctl);
   // (the words were sorted for the rows of the symbolic bin: they serve when the numeric one holds the same rows)
   const bool words0 = hist[0] && p->esc_words[0] && hist[0] == p->stats.sym_bin_rows[0];
   const bool words1 = hist[1] && p->esc_words[1] && hist[1] == p->stats.sym_bin_rows[1];
@@ -741,7 +742,7 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
     hipLaunchKernelGGL(k_num_staged<T>, dim3(grid_for(hist[4], 1, h->num_cus)), dim3(kStThreads), staged_lds<T>(), s, p->perm_num,
                        p->ctl, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, B->cols, c_rp, c_col, c_val);
   }
-  if (hist[5] + hist[6] > 0 || (tiles3 && hist[3] > 0 && p->stats.dense_runs > 0)) {
+  if (run_tiles) {
     Timer t(h, SPGEMM_K_NUM_DENSE);
     // (k_num_tiles has no way around the table, which is built for ascending rows only, or the list; k_num_wide takes tiles of any size)
     const bool wide = p->wide_tiles || !p->blk_ptr || !p->all_listed || B->nnz >= kTileMaxNnz;
