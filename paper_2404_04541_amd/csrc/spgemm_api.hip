@@ -290,11 +290,15 @@ constexpr int64_t kEscPackCols0 = int64_t(1) << 25, kEscPackCols1 = int64_t(1) <
 // empty in both phases (whole calls, 8000 columns, near B): 16 times 2 1004 | 1128, 2 times 2 594 | 631, 4 times 3 683 | 697, but 6 times 4
 // 472 | 464.
 constexpr int64_t kFlagMaxNnz = int64_t(1) << 20;
+// Few rows do not fill the card: then what counts is how long a row takes, and the numeric phase of 128 products takes longer.  Rows of 100
+// products, both phases, us sorted list | flags: 500 rows 10.8 | 12.4, 2000 11.0 | 12.2, 4000 13.2 | 13.1, 8000 17.9 | 14.8, 32 000 44.8 | 26.6.
+constexpr int64_t kFlagMinRows = 4096;
 constexpr size_t kAskFreeAbove = (size_t)64 << 20;   // optional memory below this is taken without asking the device what it has free
 
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Whether the rows of classes 0 and 1 take the flag-list workspace (flag_kernels.hpp) instead of the sorted list.
+// Whether the rows of classes 0 and 1 take the flag-list workspace (flag_kernels.hpp) instead of the sorted list, where there are
+// kFlagMinRows of them.
 bool flag_rows_ok(spgemm_context* h, const spgemm_csr* B) {
   return h->force != 1 && B->cols <= kFlagMaxCols && B->nnz >= (B->nnz <= kFlagMaxNnz ? 4 : 8) * B->rows;
 }
@@ -559,6 +563,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   unsigned tile_cap = 0, run_cap = 0;
   double list_want = 0;
   if (hist[0] + hist[1] == 0) drop_desc(h, p);   // (nobody reads it)
+  if ((int64_t)hist[0] + hist[1] < kFlagMinRows) p->flag_rows = false;
   int rc = alloc_dense_lists(h, p, B, host, &tile_cap, &run_cap, &list_want);
   if (rc == SPGEMM_ALLOC_FAILED && p->desc) {
     drop_desc(h, p);

@@ -50,3 +50,40 @@ def test_numeric_phase_on_a_kept_plan_in_another_order():
         torch.cuda.synchronize()
         assert_matches_oracle(A, B, (rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy()), what=f"turn {turn}")
     plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("cols", [1, 33, 2047, 2048, 2049, 4096, 4097, 8192, 8193])
+@pytest.mark.parametrize("rows", [4095, 4096, 5003])
+def test_enough_rows_for_the_flag_list(rows, cols, dtype):
+    """Fewer than 4096 rows take the sorted list whatever the widths; no row of A is empty, so that all count."""
+    rng = np.random.default_rng(rows + cols)
+    for repeats, b_most in ((True, 4), (False, 5), (True, 16)):
+        b_lens = np.minimum(rng.integers(1, 2 * b_most + 1, 300), 1 << 30 if repeats else cols)
+        most = 128 // int(b_lens.max())
+        A = some_rows(rng.integers(1, 1 + most, rows), 300, rng, True, 7, dtype)
+        B = some_rows(b_lens, cols, rng, repeats, 8, dtype)
+        got = gpu_product(A, B)
+        assert_matches_oracle(A, B, got, what=f"{rows} rows, {cols} columns, rows of {b_most}")
+        assert got[3]["num_bin_rows"][0] + got[3]["num_bin_rows"][1] == rows
+
+
+def test_enough_rows_on_a_kept_plan_in_another_order():
+    import torch
+    rng = np.random.default_rng(4)
+    A = some_rows(rng.integers(1, 12, 6000), 700, rng, False, 9, np.float64)
+    B = some_rows(rng.integers(1, 11, 700), 900, rng, False, 10, np.float64)
+    h = sg.Handle()
+    dA, dB = sg.to_device(A), sg.to_device(B)
+    rp, nnz, plan = sg.spgemm_symbolic(h, dA, dB)
+    for turn in range(2):
+        if turn:
+            for r in range(B.rows):
+                s = slice(int(B.rowptr[r]), int(B.rowptr[r + 1]))
+                B.colidx[s] = B.colidx[s][::-1].copy()
+                B.values[s] = B.values[s][::-1] * 0.5
+            dB = sg.to_device(B)
+        col, val = sg.spgemm_numeric(h, plan, dA, dB, rp)
+        torch.cuda.synchronize()
+        assert_matches_oracle(A, B, (rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy()), what=f"turn {turn}")
+    plan.destroy()
