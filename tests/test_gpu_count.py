@@ -37,3 +37,16 @@ def test_rows_at_the_edges_of_a_round(a_lens):
 @pytest.mark.parametrize("longest", [(1 << 19) - 1, 1 << 19, (1 << 19) + 1])
 def test_huge_rows_of_b(longest):
     count([1, 2, 0, 7, 100], [longest, 3, 0, 9], 4)
+
+
+@pytest.mark.parametrize("a_lens", [[1024], [1025], [1023, 1, 0, 1], [1, 1022, 1], [0] * 63 + [1024], [17] * 60, [16] * 64, [16] * 63 + [17], [2] * 5000, [0, 0, 1]])
+def test_chunks_of_about_as_many_entries_as_threads(a_lens):
+    """Up to 1024 entries in a chunk of rows an entry is one thread's; with one more they are taken in rounds."""
+    count(a_lens, [1, 0, 3, 17, 5, 40, 300], 5)
+
+
+@pytest.mark.parametrize("entries", [900, 3000, 9000])
+@pytest.mark.parametrize("longest", [(1 << 19) - 1, 1 << 19])
+def test_a_huge_row_of_b_among_short_ones(longest, entries):
+    """(the first, the only and a later round of a row hold it)"""
+    count([entries, 5], [longest] + [1] * 3000, 6)
