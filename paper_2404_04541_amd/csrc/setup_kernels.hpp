@@ -53,8 +53,12 @@ __device__ __forceinline__ unsigned long long wave_sum64(unsigned long long v) {
 template <int N>
 __device__ __forceinline__ void add_to_bins(const int (&bin)[N], const unsigned long long (&ip)[N], const unsigned (&nnz)[N], unsigned* hist,
                                             unsigned long long* hip, unsigned long long* hnz) {
+  unsigned mine = 0;   // bins of the lane's rows
+#pragma unroll
+  for (int u = 0; u < N; ++u) mine |= bin[u] >= 0 ? 1u << bin[u] : 0u;
 #pragma unroll
   for (int v = 0; v < kNumBins; ++v) {
+    if (!__any((mine >> v) & 1u)) continue;
     unsigned rows = 0;
     unsigned long long p = 0, z = 0;
 #pragma unroll
@@ -62,7 +66,6 @@ __device__ __forceinline__ void add_to_bins(const int (&bin)[N], const unsigned 
       rows += (unsigned)__popcll(__ballot(bin[u] == v));
       if (bin[u] == v) { p += ip[u]; z += nnz[u]; }
     }
-    if (rows == 0) continue;
     if (v == kEmptyBin) { p = 0; z = 0; }
     else {
       p = wave_sum64(p);
