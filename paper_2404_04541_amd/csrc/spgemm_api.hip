@@ -97,6 +97,7 @@ struct spgemm_context {
   double whole_ip = 0;    // ... and the products of all its rows
   std::string err = "";
   bool device_ready = false;
+  bool big_lds_ready = false;
   int num_cus = 0;
   std::vector<TimedLaunch> timed;        // launches of the phase in flight
   std::vector<hipEvent_t> event_pool;
@@ -207,6 +208,14 @@ int ensure_device(spgemm_context* h) {
   HIP_TRY(h, hipGetDeviceProperties(&prop, dev));
   if (prop.warpSize != kWave) return fail(h, SPGEMM_UNSUPPORTED, "device is not wave64");
   h->num_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
+  h->device_ready = true;
+  return SPGEMM_OK;
+}
+
+// The kernels that use more LDS than a kernel gets unasked are allowed it when a handle first has rows for them (a call each: for a handle
+// that never has, that was 10 us of its first product).
+int ensure_big_lds(spgemm_context* h) {
+  if (h->big_lds_ready) return SPGEMM_OK;
   int rc;
   if ((rc = allow_lds(h, k_sym_dense<16, false>, sym_dense_lds<16>(kSymFlagWords)))) return rc;
   if ((rc = allow_lds(h, k_sym_dense<16, true>, sym_dense_lds<16>(kSymFlagWords)))) return rc;
@@ -217,7 +226,7 @@ int ensure_device(spgemm_context* h) {
   if ((rc = allow_lds(h, k_num_wide<double>, num_wide_lds<double>()))) return rc;
   if ((rc = allow_lds(h, k_num_staged<float>, staged_lds<float>()))) return rc;
   if ((rc = allow_lds(h, k_num_staged<double>, staged_lds<double>()))) return rc;
-  h->device_ready = true;
+  h->big_lds_ready = true;
   return SPGEMM_OK;
 }
 
@@ -562,6 +571,10 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   const int staged = (h->force == 4 && ceil_div(B->cols, kStWinCols) <= kStMaxWindows) ? staged_cap<T>() : 0;
   unsigned tile_cap = 0, run_cap = 0;
   double list_want = 0;
+  if (rows_dense > 0 || staged > 0) {
+    const int lds = ensure_big_lds(h);
+    if (lds) return lds;
+  }
   if (hist[0] + hist[1] == 0) drop_desc(h, p);   // (nobody reads it)
   if ((int64_t)hist[0] + hist[1] < kFlagMinRows) p->flag_rows = false;
   int rc = alloc_dense_lists(h, p, B, host, &tile_cap, &run_cap, &list_want);
@@ -1348,6 +1361,7 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
     while (t <= nblocks) block_rows[t++] = m;
     block_rows[nblocks] = m;
   }
+  if ((rc = ensure_big_lds(h))) return rc;   // (here, so that the copy below need not for every call)
   // 2. a second context on a stream of its own (same priority) for the symbolic phases
   hipStream_t s2 = nullptr;
   HIP_TRY(h, hipStreamCreateWithFlags(&s2, hipStreamNonBlocking));
