@@ -108,7 +108,7 @@ struct RunRec { int row; unsigned first; int count, d; long long a0, list; };
 
 // Per-workgroup bookkeeping of the piece walker below.
 template <int WAVES>
-struct RowScratch {
+struct __align__(16) RowScratch {   // (the tile planner's arrays, written 16 bytes at a time, lie behind it)
   static constexpr int kPieces = WAVES * kWave;   // A entries described in LDS at a time: one per thread
   long long start[kPieces];   // first B entry of each A entry's piece
   int plen[kPieces];          // piece length
@@ -826,6 +826,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
   SPG_CLK(clk_mark(&rs->clk, 9); clk_flush(&rs->clk, ctl->clk[0]);)
 }
 
+static_assert(sizeof(RowScratch<8>) % 16 == 0 && sizeof(RowScratch<16>) % 16 == 0 && alignof(TilePlan) == 16, "the planner's arrays start on 16 bytes");
 template <int WAVES>
 constexpr size_t sym_dense_lds(int64_t flag_words) { return (size_t)flag_words * 4 + sizeof(RowScratch<WAVES>) + sizeof(TilePlan); }
 // Half a span of flag words (64 KB): up to that many columns two workgroups of 8 waves share a compute unit.
