@@ -274,7 +274,8 @@ __global__ __launch_bounds__(256) void k_key_ptr(int64_t n, int64_t rows, int sh
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
       const int x = x0 + u * 256 + threadIdx.x;
-      if (x < len && (x == 0 || (k[u] >> shift) != (before[u] >> shift))) s_at[(int)((int64_t)(k[u] >> shift) - r0)] = x;
+      const uint64_t r = (uint64_t)(k[u] >> shift) - (uint64_t)r0;   // (keys that do not ascend, of indices beyond their range: nowhere)
+      if (x < len && r < kPtrRows && (x == 0 || (k[u] >> shift) != (before[u] >> shift))) s_at[r] = x;
     }
   }
   __syncthreads();
