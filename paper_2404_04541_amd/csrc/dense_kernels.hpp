@@ -1,6 +1,6 @@
 // Dense LDS workspaces for long rows (Gustavson's flag list / coordinate list of the
 // paper's section 4.4, and the dense first-order workspace of section 7.2): the symbolic
-// kernel and what it shares with the numeric one (tile_kernels.hpp).
+// kernel and what it shares with the numeric ones (tile_kernels.hpp, wide_kernels.hpp).
 //
 // Symbolic (k_sym_dense), a workgroup per row: a flag list with one bit per column (up to 2^20 columns per span in
 //   128 KB of LDS); products set bits, the row's size is the population count.  From the
@@ -174,7 +174,7 @@ struct Quad {
 // g(quad) is called per lane and batch (a, b only meaningful when WITH_VALUES).
 // What bounds the pass is not traffic but what a wave does between loads: chunks of 64 elements with wave-uniform descriptors
 // took about 35 scalar and 10 vector instructions a chunk and were 70 % full with pieces of 122 entries; quads are 98 % full
-// and take about 45 per 256 elements.  R-MAT scale 19 squared (fp32), numeric kernel 27.9 -> 25.9 ms; scale 14: numeric 218 ->
+// and take about 45 per 256 elements.  R-MAT scale 19 squared (fp32), k_num_wide 27.9 -> 25.9 ms; scale 14: numeric 218 ->
 // 190 us, symbolic 229 -> 208 us; deduplication sweep (fp64) 1.64 -> 1.59 ms.  With values one batch at a time is best (two in
 // flight 26.5 ms, three 29.7, four 31.8: registers; the next one prefetched 25.9, but 1.69 for the sweep); without them the
 // next batch is prefetched (15.8 ms at scale 19 against 16.5).  At scale 20 the symbolic kernel lost a little against the chunks
@@ -500,7 +500,7 @@ __device__ __forceinline__ int next_dense_row(const int* __restrict__ perm, Cont
 }
 
 // ALONE: LDS leaves room for one workgroup on a compute unit, so it may take the registers it wants (R-MAT scale 20: 45.8 ms in 64
-// registers, with spills, 44.4 in 75).
+// registers, with spills, 44.4 in 75).  The narrow form of 16 waves spills seven registers (32 bytes a lane), outside its loops over products.
 template <int WAVES, bool ALONE>
 __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_sym_dense(const int* __restrict__ perm, Control* ctl,
                                                              const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,

@@ -35,12 +35,9 @@ __device__ __forceinline__ void flags_clear(unsigned* flags, int gl) {
 
 // The quads (up to four consecutive products) of a chunk of a row's A entries, an entry to a lane: with B rows of at most four
 // entries a lane takes its own, otherwise the quads of all entries are dealt to the lanes.
-struct __align__(16) FlagEntry { unsigned bs_lo, bs_hi; int len, first_pos; };   // start of the B row, products, first quad | position of the first product << 16
+// (described in LDS as the sorted list does it: EscEntry, EscLds)
 template <int CAP>
-struct FlagLds {
-  FlagEntry ent[kFlagGroup];
-  __align__(8) unsigned char map[CAP];   // lane + 1 of the entry whose first quad this is, 0: a later quad of the entry before
-};
+using FlagLds = EscLds<kFlagGroup, CAP>;
 
 template <int CAP>
 struct FlagWalk {
@@ -145,6 +142,7 @@ __global__ __launch_bounds__(256, 6) void k_flag_sym(const int* __restrict__ per
 // The rows of C.  The products go to LDS by number while their columns are marked; with the places known every lane takes its
 // share of them back (kept in registers as quads instead they spill: 32-product rows 484 -> 1330 us) and puts them there, or
 // adds them where a column comes twice.
+// (Four waves a SIMD by registers for rows of 128 products; with 16 words of flags a lane the 48 KB of LDS leave three.)
 template <int CAP, int WPL, typename T>
 __global__ __launch_bounds__(256, CAP == 32 ? 5 : 4) void k_flag_num(const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const int64_t* __restrict__ a_rp,
                                                      const int32_t* __restrict__ a_col, const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,

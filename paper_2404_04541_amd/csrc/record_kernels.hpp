@@ -119,7 +119,6 @@ __global__ __launch_bounds__(256) void k_sym_wave(const int* __restrict__ perm, 
   ch.start(row_at);
   for (; row_at < nrows; row_at += gridDim.x * 4) {
     const int row = ch.row, d = ch.d;
-    const int64_t a0 = ch.a0;
     const RowChain<kWave>::Ahead nx = ch.fetch();
     {
       int4* t4 = reinterpret_cast<int4*>(table);

@@ -15,7 +15,8 @@
 // 10^7 tensor entries of 33 key bits and double values, kernel time per pass over a digit: scatter 92 us (3.5 TB/s of key and value
 // moved), counts 18 us, scan of the counters 5 us; unfolding as a whole 0.7 ms.  16.8 M components of 36 bits: scatter 140 us (3.8 TB/s).
 // Two workgroups of 16 waves, 64 registers each, hold a compute unit's LDS; with 8 waves of 16 entries a lane each it was 105 and
-// 163 us.  Payloads are loaded when the keys have left their registers; nothing may spill (with 60 bytes of spills a lane 118 us).
+// 163 us.  Payloads are loaded when the keys have left their registers, so that little spills: the figures above are with 32 bytes a lane (keys of 64
+// bits, of which nine registers go to memory), with 60 bytes a pass takes 118 us; keys of 32 bits spill two registers or none.
 #pragma once
 #include "common.hpp"
 #include "sort_shape.hpp"

@@ -6,7 +6,9 @@
 // every row of the dense classes has its structure in the plan; other plans, and some of these, are k_num_wide's (wide_tiles_from).
 // Ranked tiles take 50 to 55 LDS cycles for 64 products (a look-up of 14, an addition of 27, the search for the piece), wide
 // matrices beside that what the tile costs by itself: reads and writes run at 5.8 TB/s at scale 19 (B's entries come from behind
-// the L2 caches).  Before, one workgroup of 16 waves with a tile of 135 KB had a compute unit to itself and accumulated products
+// the L2 caches).  The 64 registers fall 15 (fp32) or 22 (fp64) short: a run's and a tile's numbers stay in memory and are read once or
+// twice a tile, none inside a loop over products.  Before, one workgroup of 16 waves with a tile of 135 KB had a compute unit to itself
+// and accumulated products
 // for 36 % of its time.  us before | two workgroups of 8 waves | of 16 waves: R-MAT squared (fp32) scale 14 192 | 158 | 158, scale 19
 // 25871 | 23670 | 23400; deduplication sweep, 10000 columns (fp64), 1586 | 1360 | 1390; four row blocks of scale 17, whole call,
 // 7710 | 7280 | 6840.
