@@ -526,13 +526,13 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
   int row = next_dense_row(perm, ctl, &rs->s_row);
   int next_row = -1;   // (thread 0) the row after this one, fetched while this one is in the works
   // Thread 0's slabs of the plan's lists are in LDS (its registers would be everybody's), but where there are registers to spare (R-MAT
-  // scale 20: 44.6 | 43.0 ms).  The first slab of
+  // scale 20: 44.6 | 43.0 ms, scale 19, 8 waves, 12.27 | 12.10).  The first slab of
   // every workgroup is its own by its number (the cursors start behind these: k_set_caps); when all workgroups drew their
   // first slab from the shared cursors at the same moment, the compare-and-swaps of 256 of them took 0.2 ms (1071 rows: 366 -> 73 us).
   const unsigned long long list_slab = list_slab_of(list_cap, gridDim.x);
   const unsigned rslab = run_slab(row_hi - row_lo, gridDim.x);
   Slabs own{};
-  Slabs& sl = ALONE ? own : tp->slabs;
+  Slabs& sl = WAVES == 8 || ALONE ? own : tp->slabs;
   if (tid == 0)
     sl = Slabs{0, blockIdx.x * list_slab, list_slab, blockIdx.x * (unsigned)kTileSlab, (unsigned)kTileSlab, blockIdx.x * rslab, rslab, 0, 0};
   while (row >= 0) {
