@@ -28,8 +28,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_num_tiles_rmat20_hbm_traffic.txt")
-KERNEL_SOURCES = ("common.hpp", "dense_kernels.hpp", "tile_kernels.hpp")   # what the dense kernels are compiled from
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_num_wide_rmat20_hbm_traffic.txt")
+KERNEL_SOURCES = ("common.hpp", "dense_kernels.hpp", "entry_order.hpp", "wide_kernels.hpp")   # what the dense kernels are compiled from
 
 
 def kernel_source_hash() -> str:
@@ -200,7 +200,8 @@ def main() -> int:
         "effective_hbm": {"bytes_per_step": bytes_stream, "GB/s": eff_gbs, "frac_of_peak": eff_gbs / HBM_PEAK_GBS,
                           "model": "IP*(8+v) + nnzC*(4+v) + nnzA*(60+v) + rows*60, v = value bytes"},
         "kernel_ms_per_step": {k: per_kernel[k] / args.steps for k in per_kernel},
-        "roofline": {"kernel": "k_num_tiles<float, false>", "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
+        "roofline": {"kernel": "k_num_wide<float>" if B.cols > 1 << 19 else "k_num_tiles<float>",   # (at scale 20 the former)
+                     "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(),
                      "bytes_per_launch": dense_bytes, "ms_per_launch": dense_ms},
         "roofline_other": [{"kernel": "k_sym_dense", "bound": "hbm", "achieved": sym_achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",

@@ -52,7 +52,7 @@ def main() -> int:
         plan.destroy()
     clk = np.array(list(buf), dtype=np.float64).reshape(2, 32)
     print(f"R-MAT scale {args.scale} A*A: products {st['ip_total']}, nnz(C) {st['nnz_c']}; third pass of three")
-    for name, tab, row, key in (("k_sym_dense", SYM, clk[0], "sym_dense"), ("k_num_tiles", NUM, clk[1], "num_dense")):
+    for name, tab, row, key in (("k_sym_dense", SYM, clk[0], "sym_dense"), ("k_num_wide" if args.scale > 19 else "k_num_tiles", NUM, clk[1], "num_dense")):
         ms, tot = st["kernel_ms"][key], row[:16].sum()
         print(f"{name}: {ms:.2f} ms (HIP events)")
         for i in range(16):
