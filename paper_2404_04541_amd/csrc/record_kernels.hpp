@@ -7,16 +7,21 @@
 // Symbolic: an LDS hash set of the columns.  A new column gets the next free number of the row; when the row has at most
 //   kNumHashSmall of them, the (column, number) words are sorted in registers and the row's record is written:
 //   one byte per product (the rank of its column in the row, in quad order) and the columns in ascending order.
+//   Rows of discretised operators are mostly the same row moved to other columns.  A wave keeps a row as its model; a later row with as many
+//   entries and as many products of each has its columns compared with the model's, and where all differ by the same shift nothing is
+//   inserted, sorted or written: the row takes the model's record and the shift.
 // Numeric: with the record a product is one byte, one multiplication and one addition at its rank; nothing is hashed,
-//   searched or sorted again.  Rows without a record take the hash workspace.
+//   searched or sorted again.  The record stays in registers as long as the wave's rows have the same one.  Rows without a record take the
+//   hash workspace.
 // The record costs one byte per product and four per entry, written and read once; finding the ranks again costs a
 // compare-and-swap loop per product (the slowest of 64 lanes decides) and a sort per row.
-// Bounds: the symbolic kernel issues about 600 vector instructions per row (insertion 300, sort and ranks 160; vector units 0.6, LDS
-// 0.66 of the cycles on the stencil below); the numeric one is bound by memory: 9.9 GB between L2 and memory in 2.2 ms, 4.5 TB/s of
-// the 4.7 that a large copy reaches (records 3.2, C 3.1, A 0.7 GB, the rest B's values, which every die fetches for itself), with LDS
-// active for half of the cycles.
-// 27-point stencil of 128^3 rows, fp64 (729 products and 125 entries per row): hash workspace 2.39 + 4.80 ms, here 3.13 + 2.22 ms;
-// of 61^3 rows, numeric phase on a kept plan: 480 -> 255 us.
+// Bounds: the symbolic kernel issues about 600 vector instructions for a row by itself (insertion 300, sort and ranks 160) and 140 for one
+// that is the model moved; the numeric one adds 729 products a row in 250 LDS cycles of 500 (without the stores 1.35 of 2.02 ms, without
+// additions 1.95): what it waits for is memory, C's 3.1 GB written and 2.7 GB of A and B read.
+// 27-point stencil of 128^3 rows, fp64 (729 products and 125 entries per row), every row by itself | with models: symbolic 3.08 | 1.12 ms,
+// numeric 2.20 | 2.02 ms; of 61^3 rows 463 | 212 us and 255 | 190 us.  (Hash workspace: 2.39 + 4.80 ms.)
+// Measured and not kept in the numeric kernel: the next row's values asked for before this one's stores, with the loads free of conditions
+// (2.08 ms: 142 registers); two products a load (2.08); 24 or 32 waves on a compute unit (2.36, 2.40).
 #pragma once
 #include "common.hpp"
 #include "entry_order.hpp"
@@ -32,9 +37,12 @@ constexpr int kRecWords = kRecRankWords + kNumHashSmall;       // 32-bit words o
 constexpr int kRecColBits = 23;                                // a column and its number (8 bits) share 31 bits
 static_assert(kNumHashSmall <= 256, "a rank fits a byte");
 static_assert(kRecWords % 4 == 0 && kRecRankWords % 4 == 0, "records and their column lists start on 16 bytes");
+struct __align__(8) RecordOf { int record, shift; };          // of a row: its record (-1: none), and how far the record's columns are from its own
+constexpr int kRecordGroups = 4;                               // workgroups of these kernels on a compute unit
 constexpr int kSymLogSlots = 10;
 constexpr int kSymSlots = 1 << kSymLogSlots;
-constexpr int kNumQuads = 2;                                   // quads in flight per lane (numeric)
+constexpr int kRecSums = 256 + kWave;                          // sums of a row in LDS (a rank is a byte), and a place for every lane's missing products
+static_assert(4 * kRecSums * 8 <= 65536, "a sum's place in the workgroup's LDS fits 16 bits");
 
 struct __align__(16) QuadEntry { int first, len; int64_t bs; };   // first quad of an A entry, its products, the start of its B row
 
@@ -81,26 +89,37 @@ __device__ __forceinline__ QuadMap quad_map(int64_t bs, int len, int nent, QuadE
   return m;
 }
 
-// Quad q of the map (below nq): the position of its entry, the products left in the entry from the quad on, and where they are.
-__device__ __forceinline__ int quad_entry(const QuadMap& m, int q, const QuadEntry* ent, int& left, int64_t& at) {
-  QuadEntry en;
-  const int pos = find_quad(ent, q, m.per_quad, en);
-  const int off = (q - en.first) * 4;
-  left = en.len - off;
-  at = en.bs + off;
-  return pos;
-}
-
 // Home slot of a column (24-bit multiplication: a 32-bit one takes four issue slots).
 __device__ __forceinline__ unsigned set_home(int col) {
   return (__umul24((unsigned)col ^ ((unsigned)col >> 20), 0x9E3779u) >> (32 - kSymLogSlots)) & (kSymSlots - 1);
 }
 
-__global__ __launch_bounds__(256) void k_sym_wave(const int* __restrict__ perm, Control* __restrict__ ctl, int bin,
+// Where a quad's products come from, in one word: the lane of its entry, how many there are (left: to the entry's end), its first
+// product inside the entry.
+__device__ __forceinline__ unsigned pack_quad(int src, int left, int off) {
+  const int n = left < 0 ? 0 : (left < 4 ? left : 4);
+  return (unsigned)src | ((unsigned)n << 6) | ((unsigned)off << 9);
+}
+__device__ __forceinline__ int quad_src(unsigned w) { return (int)(w & 63u); }
+__device__ __forceinline__ int quad_count(unsigned w) { return (int)((w >> 6) & 7u); }
+__device__ __forceinline__ int quad_off(unsigned w) { return (int)(w >> 9); }
+struct NumRow {   // record (-1: no row, -2: none), how far its columns are from the row's, entries of A, entries of C
+  int record = -1, shift = 0, d = 0, n = 0;
+  int64_t a0 = 0, out = 0;
+  __device__ __forceinline__ bool there() const { return record != -1; }
+};
+struct SymRow {   // a row, its entries of A (none: row < 0)
+  int row = -1, d = 0;
+  int64_t a0 = 0;
+  __device__ __forceinline__ bool there() const { return row >= 0; }
+};
+constexpr int kAlikeTries = 8;   // rows that only look alike a wave compares in vain before it stops
+
+__global__ __launch_bounds__(256, kRecordGroups) void k_sym_wave(const int* __restrict__ perm, Control* __restrict__ ctl, int bin,
                                                   const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                   const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col, int64_t b_nnz,
                                                   int* __restrict__ cnt, unsigned* __restrict__ records, unsigned record_rows,
-                                                  int* __restrict__ record_of) {
+                                                  RecordOf* __restrict__ record_of) {
   __shared__ __align__(16) int s_table[4][kSymSlots];
   __shared__ QuadEntry s_ent[4][kQuadEntries];
   __shared__ unsigned short s_slot[4][kNumHashSmall];   // slot of the column with a number
@@ -114,46 +133,156 @@ __global__ __launch_bounds__(256) void k_sym_wave(const int* __restrict__ perm, 
   static_assert(sizeof(QuadEntry) * kQuadEntries >= kNumHashSmall * sizeof(unsigned), "the words fit the entries' space");
   unsigned short* slot_of = s_slot[g];
   unsigned kept = 0;
-  RowChain<kWave> ch{perm + first, a_rp, a_col, b_rp, nullptr, nrows, gridDim.x * 4};
-  unsigned row_at = blockIdx.x * 4 + g;
-  ch.start(row_at);
-  for (; row_at < nrows; row_at += gridDim.x * 4) {
-    const int row = ch.row, d = ch.d;
-    const RowChain<kWave>::Ahead nx = ch.fetch();
-    {
-      int4* t4 = reinterpret_cast<int4*>(table);
-#pragma unroll
-      for (int t = 0; t < kSymSlots / 4 / kWave; ++t) t4[t * kWave + lane] = make_int4(kEmptyKey, kEmptyKey, kEmptyKey, kEmptyKey);
+  // The model: the row that later ones are compared with.  Its entries and their products (d < 0: there is none), where its quads
+  // come from and their columns, what became of it, and how the comparisons with it went.
+  int m_d = -1, m_len = 0, m_nq = 0, m_found = 0, m_rec = -1, m_hits = 0, m_missed = 0, vain = 0;
+  unsigned m_quad[kQuadRounds] = {};
+  int m_col[kQuadRounds][4] = {};
+  const DieRows order(blockIdx.x, gridDim.x, g, nrows);
+  if (order.count == 0) return;   // (the wave)
+  auto load = [&](unsigned t) {
+    SymRow r;
+    const unsigned at = order.at(t);
+    if (at < nrows) {
+      r.row = perm[first + at];
+      const Run<int64_t, 2> v = load_run<int64_t, 2>(a_rp + r.row);
+      r.a0 = v.v[0];
+      r.d = (int)(v.v[1] - v.v[0]);
     }
+    return r;
+  };
+  RowRing<SymRow> rows;
+  rows.start(load);
+  auto entries = [&](int ahead) { return rows.get(ahead, [](const SymRow& r) { return r.d; }); };
+  // The loads of the rows to come have no conditions (lanes without an entry load the row's first), so that it is known how many are on
+  // their way when one is waited for: loads and stores return in order, and a wait that does not know what is behind waits for everything.
+  auto place = [&](int ahead) { return rows.get64(ahead, [](const SymRow& r) { return r.a0; }) + (lane < entries(ahead) ? lane : 0); };
+  auto bounds_of = [&](int k) { return load_run<int64_t, 2>(b_rp + k); };
+  int col[kQuadRounds][4];
+  unsigned quad[kQuadRounds];
+  const int32_t* const from = b_nnz >= 4 ? b_col : reinterpret_cast<const int32_t*>(ctl);
+  const int64_t last = b_nnz >= 4 ? b_nnz - 4 : 0;
+  int k2 = a_col[place(0)];
+  const int k1 = a_col[place(1)];
+  Run<int64_t, 2> bounds1 = bounds_of(k2);
+  k2 = k1;
+  int64_t bs = 0;         // of the row in the works: where the lane's entry's products begin, and how many there are
+  int len = 0;
+  bool compare = false;   // it has as many entries as the model, and they as many products: its quads are the model's, its columns are on their way
+  auto begin = [&] {
+    const int d = entries(0);
+    bs = bounds1.v[0];
+    len = lane < d ? (int)(bounds1.v[1] - bs) : 0;
+    // (a quad that reaches behind the end of B is loaded further in front: such a row is not compared)
+    compare = d == m_d && vain < kAlikeTries && !__any(len != m_len || (len > 0 && bs + len + 3 > b_nnz));
+    wave_sync_lds();
+    ent[lane].bs = bs;
+    wave_sync_lds();
+    auto fetch = [&](int r) {
+      const int64_t p = ent[quad_src(m_quad[r])].bs + quad_off(m_quad[r]);
+      const Run<int32_t, 4> v = load_run<int32_t, 4>(from + (p < last ? p : last));
+#pragma unroll
+      for (int u = 0; u < 4; ++u) col[r][u] = v.v[u];
+    };
+    static_assert(kQuadRounds == 4, "two rounds that rows may not have, two that are loaded always");
+    if (m_nq > 3 * kWave) fetch(3);
+    if (m_nq > 2 * kWave) fetch(2);
+    fetch(1);
+    fetch(0);
+    wave_sync_lds();
+    bounds1 = bounds_of(k2);
+    k2 = a_col[place(2)];
+  };
+  begin();
+  while (rows.t < order.count) {
+    const unsigned row_at = order.at(rows.t);
+    const int row = rows.get(0, [](const SymRow& r) { return r.row; }), d = entries(0);
     const bool want = row_at < record_rows && d <= kQuadEntries;
     int found = 0;                                 // (wave-uniform) distinct columns so far
+    int in_record = -1, shift = 0;
     unsigned slots[kQuadRounds][2] = {};           // of a recorded row's products, two to a word
     int nq_row = 0;
-    for (int base = 0; base < d; base += kQuadEntries) {
-      if (base > 0) ch.fetch_more(base);
-      const QuadMap map = quad_map(ch.bounds.v[0], (int)(ch.bounds.v[1] - ch.bounds.v[0]), d - base < kQuadEntries ? d - base : kQuadEntries, ent, [] {});
-      nq_row = map.nq;
-      int col[kQuadRounds][4];
-      int n_of[kQuadRounds];
+    bool alike = false;
+    if (compare) {   // is the row the model moved to other columns?
+      shift = __builtin_amdgcn_readfirstlane(col[0][0]) - __builtin_amdgcn_readfirstlane(m_col[0][0]);
+      bool other = false;
 #pragma unroll
-      for (int r = 0; r < kQuadRounds; ++r) {
-        n_of[r] = 0;
-        if (r * kWave < map.nq) {
-          int64_t p = 0;
-          if (r * kWave + lane < map.nq) (void)quad_entry(map, r * kWave + lane, ent, n_of[r], p);
-          load_quad<int32_t>(b_col, p, n_of[r], b_nnz, col[r]);
+      for (int r = 0; r < kQuadRounds; ++r)
+        if (r * kWave < m_nq) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) other = other || (u < quad_count(m_quad[r]) && col[r][u] - m_col[r][u] != shift);
+        }
+      alike = !__any(other);
+      if (alike) {
+        ++m_hits;
+        m_missed = 0;
+        found = m_found;
+        in_record = m_rec;
+      } else {
+        shift = 0;
+        if (m_hits == 0) ++vain;
+      }
+    }
+    for (int base = 0; base < d && !alike; base += kQuadEntries) {
+      int nq = m_nq;
+      if (base > 0 || !compare) {
+        int64_t from_here = bs;
+        int n_here = len;
+        if (base > 0) {
+          const int64_t a0 = rows.get64(0, [](const SymRow& r) { return r.a0; });
+          Run<int64_t, 2> v;
+          v.v[0] = 0; v.v[1] = 0;
+          if (base + lane < d) v = bounds_of(a_col[a0 + base + lane]);
+          from_here = v.v[0];
+          n_here = (int)(v.v[1] - v.v[0]);
+        }
+        const QuadMap map = quad_map(from_here, n_here, d - base < kQuadEntries ? d - base : kQuadEntries, ent, [] {});
+        nq = map.nq;
+#pragma unroll
+        for (int r = 0; r < kQuadRounds; ++r) {
+          quad[r] = 0;
+          if (r * kWave < nq) {
+            int64_t p = 0;
+            if (r * kWave + lane < nq) {
+              QuadEntry en;
+              const int q = r * kWave + lane, src = find_quad(ent, q, map.per_quad, en), off = (q - en.first) * 4;
+              quad[r] = pack_quad(src, en.len - off, off);
+              p = en.bs + off;
+            }
+            load_quad<int32_t>(b_col, p, quad_count(quad[r]), b_nnz, col[r]);
+          }
+        }
+        wave_sync_lds();   // (the entries have been read: a recorded row's words take their place)
+      } else {
+#pragma unroll
+        for (int r = 0; r < kQuadRounds; ++r) quad[r] = m_quad[r];
+      }
+      nq_row = nq;
+      if (base == 0) {
+        int4* t4 = reinterpret_cast<int4*>(table);
+#pragma unroll
+        for (int t = 0; t < kSymSlots / 4 / kWave; ++t) t4[t * kWave + lane] = make_int4(kEmptyKey, kEmptyKey, kEmptyKey, kEmptyKey);
+        wave_sync_lds();
+        if (d <= kQuadEntries && (m_hits == 0 || ++m_missed > 1)) {   // (one row at an edge leaves the model what it is)
+          m_d = d; m_len = len; m_nq = nq; m_hits = 0; m_missed = 0;
+#pragma unroll
+          for (int r = 0; r < kQuadRounds; ++r) {
+            m_quad[r] = quad[r];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) m_col[r][u] = col[r][u];
+          }
+          m_rec = -2;
         }
       }
-      wave_sync_lds();   // (the entries have been read: a recorded row's words take their place)
 #pragma unroll
       for (int r = 0; r < kQuadRounds; ++r) {
-        if (r * kWave >= map.nq) break;
+        if (r * kWave >= nq) break;
         unsigned slot[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           slot[u] = set_home(col[r][u]);
           bool is_new = false;
-          if (u < n_of[r]) {
+          if (u < quad_count(quad[r])) {
             while (true) {
               const int old = atomicCAS(&table[slot[u]], kEmptyKey, col[r][u]);
               if (old == kEmptyKey) { is_new = true; break; }
@@ -175,13 +304,14 @@ __global__ __launch_bounds__(256) void k_sym_wave(const int* __restrict__ perm, 
         slots[r][1] = slot[2] | (slot[3] << 16);
       }
     }
-    const bool keep = want && found <= kNumHashSmall;
-    if (lane == 0) {
-      cnt[row] = found;
-      if (record_of) record_of[row] = keep ? (int)row_at : -1;
+    const bool keep = !alike && want && found <= kNumHashSmall;
+    if (keep) in_record = (int)row_at;
+    if (m_rec == -2) {   // the row is the model
+      m_found = found;
+      m_rec = in_record;
     }
+    if (in_record >= 0) ++kept;
     if (keep) {
-      ++kept;
       unsigned* rec = records + (size_t)row_at * kRecWords;
       wave_sync_lds();
       auto ranks = [&](auto per_lane) {
@@ -221,7 +351,13 @@ __global__ __launch_bounds__(256) void k_sym_wave(const int* __restrict__ perm, 
       }
     }
     wave_sync_lds();
-    ch.advance(nx);
+    rows.step(load);
+    begin();
+    // (behind the loads of the rows to come, which are waited for in order with the stores)
+    if (lane == 0) {
+      cnt[row] = found;
+      if (record_of) record_of[row] = RecordOf{in_record, shift};
+    }
   }
   if (lane == 0 && kept) atomicAdd(&ctl->recorded, kept);
 }
@@ -229,12 +365,11 @@ __global__ __launch_bounds__(256) void k_sym_wave(const int* __restrict__ perm, 
 // Numeric pass over the recorded rows of a bin, a wave per row; rows without a record are left to the hash workspace.
 // SUM: the first order.parts workgroups look at the order of the entries (order_later) while the others do the rows.
 template <typename T, bool SUM>
-__global__ __launch_bounds__(256) void k_num_recorded(const int* __restrict__ perm, std::conditional_t<SUM, Control, const Control>* __restrict__ ctl, int bin, const int* __restrict__ ip_row,
-                                                      const unsigned* __restrict__ records, const int* __restrict__ record_of,
+__global__ __launch_bounds__(256) void k_num_recorded(const int* __restrict__ perm, std::conditional_t<SUM, Control, const Control>* __restrict__ ctl, int bin, const unsigned* __restrict__ records, const RecordOf* __restrict__ record_of,
                                                       const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const T* __restrict__ a_val,
                                                       const int64_t* __restrict__ b_rp, const T* __restrict__ b_val, int64_t b_nnz,
                                                       const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val, const OrderOperands order) {
-  __shared__ double s_acc[4][256];   // (a rank is a byte)
+  __shared__ double s_acc[4][kRecSums];
   __shared__ QuadEntry s_ent[4][kQuadEntries];
   __shared__ T s_av[4][kQuadEntries];
   if (ctl->error || (!SUM && ctl->order_differs)) return;
@@ -247,81 +382,128 @@ __global__ __launch_bounds__(256) void k_num_recorded(const int* __restrict__ pe
     wg -= order.parts;
     wgs -= order.parts;
   }
-  const unsigned first = ctl->offset[1][bin];
-  const unsigned nrows = ctl->offset[1][bin + 1] - first;
+  const unsigned first = ctl->offset[0][bin];   // (the order of the symbolic kernel: a wave meets the rows of a record one after the other)
+  const unsigned nrows = ctl->offset[0][bin + 1] - first;
   const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
   double* acc = s_acc[g];
   QuadEntry* ent = s_ent[g];
   T* s_a = s_av[g];
-  auto record = [&](int row) { return row >= 0 && ip_row[row] <= kSymHashSmall ? record_of[row] : -1; };
-  auto range = [&](int row, int64_t& lo, int& n) {
-    lo = 0; n = 0;
-    // (a recorded row has no more entries than that, whatever room the row pointer leaves behind them)
-    if (row >= 0) { const Run<int64_t, 2> v = load_run<int64_t, 2>(c_rp + row); lo = v.v[0]; n = v.v[1] - v.v[0] < kNumHashSmall ? (int)(v.v[1] - v.v[0]) : kNumHashSmall; }
+  const DieRows in_order(wg, wgs, g, nrows);
+  auto load = [&](unsigned t) {
+    NumRow r;
+    const unsigned at = in_order.at(t);
+    if (at < nrows) {
+      const int row = perm[first + at];
+      const RecordOf of = record_of[row];
+      const Run<int64_t, 2> a = load_run<int64_t, 2>(a_rp + row), c = load_run<int64_t, 2>(c_rp + row);
+      r.record = of.record >= 0 ? of.record : -2;
+      r.shift = of.shift;
+      r.a0 = a.v[0];
+      r.d = (int)(a.v[1] - a.v[0]);
+      r.out = c.v[0];
+      // (a recorded row has no more entries than that, whatever room the row pointer leaves behind them)
+      r.n = c.v[1] - c.v[0] < kNumHashSmall ? (int)(c.v[1] - c.v[0]) : kNumHashSmall;
+    }
+    return r;
   };
-  auto value = [&](int64_t a, int n) { return lane < n ? a_val[a + lane] : T(0); };
-  RowChain<kWave> ch{perm + first, a_rp, a_col, b_rp, nullptr, nrows, wgs * 4};
-  unsigned row_at = wg * 4 + g;
-  ch.start(row_at);
-  int at0 = record(ch.row), at1 = record(ch.row1), at2 = record(ch.row2);
-  int64_t out0, out1, out2;
-  int n0, n1, n2;
-  range(ch.row, out0, n0);
-  range(ch.row1, out1, n1);
-  range(ch.row2, out2, n2);
-  T av0 = value(ch.a0, ch.d), av1 = value(ch.a01, ch.d1);
-  for (; row_at < nrows; row_at += wgs * 4) {
-    const RowChain<kWave>::Ahead nx = ch.fetch();
-    int64_t out3;
-    int n3;
-    const T av2 = value(ch.a02, ch.d2);
-    range(ch.row3, out3, n3);
-    const int at3 = record(ch.row3);
-    if (at0 >= 0) {
-      const unsigned* rec = records + (size_t)at0 * kRecWords;
-      for (int t = lane; t < n0; t += kWave) acc[t] = 0.0;
+  if (in_order.count == 0) return;   // (the wave)
+  RowRing<NumRow> rows;
+  rows.start(load);
+  auto record = [&](int ahead) { return rows.get(ahead, [](const NumRow& r) { return r.record; }); };
+  auto entries = [&](int ahead) { return rows.get(ahead, [](const NumRow& r) { return r.d; }); };
+  // (lanes without an entry load the row's first)
+  auto place = [&](int ahead) { return rows.get64(ahead, [](const NumRow& r) { return r.a0; }) + (lane < entries(ahead) ? lane : 0); };
+  auto bounds_of = [&](int k) { return load_run<int64_t, 2>(b_rp + k); };
+  // The record in registers: which one, of a row with how many entries (and products of this lane's), its quads (the lane of the entry,
+  // the place inside it and how many there are), where in LDS their products are added up (two 16-bit offsets a word; what a quad has
+  // not goes to a place of its own behind the row's sums) and the columns.
+  int h_rec = -1, h_n = 0, h_d = 0, h_len = 0, h_nq = 0, h_col[kNumHashSmall / kWave] = {};
+  unsigned h_quad[kQuadRounds] = {}, h_sum[kQuadRounds][2] = {};
+  // (the loads that lead to a row's products depend on each other: each is on its way while the rows before are in the works)
+  int k1 = a_col[place(0)], k2 = a_col[place(1)];
+  Run<int64_t, 2> bounds = bounds_of(k1);
+  T av = a_val[place(0)];
+  for (; rows.t < in_order.count; rows.step(load)) {
+    const int at = record(0), n = rows.get(0, [](const NumRow& r) { return r.n; }), d = entries(0);
+    const int64_t bs = bounds.v[0];
+    const int len = lane < d ? (int)(bounds.v[1] - bs) : 0;
+    if (at >= 0) {
+#pragma unroll
+      for (int i = 0; i < kNumHashSmall / kWave; ++i)
+        if (i * kWave < n) acc[i * kWave + lane] = 0.0;
       // (operands of another structure than the plan's read no further than the record)
-      const QuadMap map = quad_map(ch.bounds.v[0], (int)(ch.bounds.v[1] - ch.bounds.v[0]), ch.d, ent, [&] { s_a[lane] = av0; });
+      if (at != h_rec || n != h_n || d != h_d || __any(len != h_len)) {
+        const unsigned* rec = records + (size_t)at * kRecWords;
+        const QuadMap map = quad_map(bs, len, d, ent, [] {});
+        h_rec = at; h_n = n; h_d = d; h_len = len; h_nq = map.nq;
 #pragma unroll
-      for (int r0 = 0; r0 < kQuadRounds; r0 += kNumQuads) {
-        if (r0 * kWave >= map.nq) break;
-        T b[kNumQuads][4];
-        unsigned w[kNumQuads];
-        int left[kNumQuads];
-        double a[kNumQuads];
-#pragma unroll
-        for (int i = 0; i < kNumQuads; ++i) {
-          const int q = (r0 + i) * kWave + lane;
-          left[i] = 0;
-          w[i] = 0;
-          a[i] = 0.0;
-          int64_t p = 0;
-          if (q < map.nq) {
-            w[i] = rec[q];
-            const int at = quad_entry(map, q, ent, left[i], p);
-            a[i] = (double)s_a[at];
+        for (int r = 0; r < kQuadRounds; ++r) {
+          const int q = r * kWave + lane;
+          unsigned rank = 0;
+          h_quad[r] = 0;
+          if (r * kWave < map.nq && q < map.nq) {
+            rank = rec[q];
+            QuadEntry en;
+            const int src = find_quad(ent, q, map.per_quad, en), off = (q - en.first) * 4;
+            h_quad[r] = pack_quad(src, en.len - off, off);
           }
-          load_quad<T>(b_val, p, left[i], b_nnz, b[i]);
+          unsigned to[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) to[u] = g * (unsigned)sizeof(s_acc[0]) + (u < quad_count(h_quad[r]) ? (rank >> (8 * u)) & 255u : 256u + lane) * 8u;
+          h_sum[r][0] = to[0] | (to[1] << 16);
+          h_sum[r][1] = to[2] | (to[3] << 16);
         }
 #pragma unroll
-        for (int i = 0; i < kNumQuads; ++i)
+        for (int i = 0; i < kNumHashSmall / kWave; ++i) h_col[i] = i * kWave + lane < n ? (int)rec[kRecRankWords + i * kWave + lane] : 0;
+      }
+      const bool tight = __any(len > 0 && bs + len + 3 > b_nnz);   // (a quad might reach behind the end of B)
+      wave_sync_lds();
+      ent[lane].bs = bs;
+      s_a[lane] = av;
+      wave_sync_lds();
+      T b[kQuadRounds][4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (u < left[i])
-              __hip_atomic_fetch_add(&acc[(w[i] >> (8 * u)) & 255u], a[i] * (double)b[i][u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      for (int r = 0; r < kQuadRounds; ++r) {
+        if (r * kWave >= h_nq) break;
+        const int64_t p = ent[quad_src(h_quad[r])].bs + quad_off(h_quad[r]);
+        if (!tight) {
+          const Run<T, 4> v = load_run<T, 4>(b_val + p);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) b[r][u] = v.v[u];
+        } else {
+          int n4 = quad_count(h_quad[r]);
+          asm volatile("" : "+v"(n4));   // (no code: keeps this first load from being shared with the wide one, which then is three)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) b[r][u] = u < n4 ? b_val[p + u] : T(0);
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < kQuadRounds; ++r) {
+        if (r * kWave >= h_nq) break;
+        const double a = (double)s_a[quad_src(h_quad[r])];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const unsigned to = (h_sum[r][u >> 1] >> (16 * (u & 1))) & 0xffffu;
+          __hip_atomic_fetch_add(static_cast<double*>(__builtin_assume_aligned(reinterpret_cast<unsigned char*>(s_acc) + to, 8)), a * (double)b[r][u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
       }
       wave_sync_lds();
-      for (int t = lane; t < n0; t += kWave) {
-        c_col[out0 + t] = (int32_t)rec[kRecRankWords + t];
-        c_val[out0 + t] = (T)acc[t];
+      const int shift = rows.get(0, [](const NumRow& r) { return r.shift; });
+      const int64_t out = rows.get64(0, [](const NumRow& r) { return r.out; });
+#pragma unroll
+      for (int i = 0; i < kNumHashSmall / kWave; ++i) {
+        const int t = i * kWave + lane;
+        if (t < n) {
+          __builtin_nontemporal_store(h_col[i] + shift, &c_col[out + t]);
+          __builtin_nontemporal_store((T)acc[t], &c_val[out + t]);
+        }
       }
       wave_sync_lds();
     }
-    ch.advance(nx);
-    out0 = out1; out1 = out2; out2 = out3;
-    n0 = n1; n1 = n2; n2 = n3;
-    at0 = at1; at1 = at2; at2 = at3;
-    av0 = av1; av1 = av2;
+    // a step further for the rows behind
+    bounds = bounds_of(k2);
+    av = a_val[place(1)];
+    k2 = a_col[place(2)];
   }
 }
 

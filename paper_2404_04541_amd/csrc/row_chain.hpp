@@ -98,4 +98,49 @@ struct RowChain {
   }
 };
 
+// The rows of a list that a wave takes, for a grid of whole multiples of kDies workgroups of four waves that stays on the chip: a die's
+// waves take stretches of consecutive rows, `rounds` rows a wave, and the dies take the stretches in turn.  Neighbouring rows mostly want
+// the same rows of B, which then come into one die's L2 cache instead of all of them (27-point stencil of 128^3 rows, numeric phase: 6.7 -> 3.6
+// GB read from behind the caches); the stretches are short enough that a list that begins with its heaviest rows is shared out evenly.
+constexpr unsigned kDies = 8;   // (workgroups are dealt to the dies in turn)
+struct DieRows {
+  unsigned waves, rounds, first, count;   // count: rows of this wave
+  __device__ __forceinline__ DieRows(unsigned wg, unsigned wgs, int wave, unsigned nrows) {
+    waves = wgs / kDies * 4;
+    rounds = nrows / (waves * kDies * 8);
+    rounds = rounds < 1 ? 1 : (rounds < 32 ? rounds : 32);
+    first = wg % kDies * waves * rounds + wg / kDies * 4 + wave;
+    const unsigned all = waves * rounds * kDies, left = nrows % all;
+    const unsigned more = left > first ? (left - first + waves - 1) / waves : 0;
+    count = nrows / all * rounds + (more < rounds ? more : rounds);
+  }
+  __device__ __forceinline__ unsigned at(unsigned t) const { return first + t / rounds * (waves * rounds * kDies) + t % rounds * waves; }   // the wave's t-th row
+};
+
+// What is known of a wave's rows, 64 of them at a time, row t in lane t mod 64 (Row: its numbers): the loads that lead to it are paid once
+// for 32 rows, and they are loads of the vector kind: scalar ones are waited for together with LDS, in no order.
+template <class Row>
+struct RowRing {
+  Row rows;
+  unsigned t;   // the row in the works
+  template <class Load>   // load(t): what is known of the wave's row t
+  __device__ __forceinline__ void start(Load load) { t = 0; rows = load((unsigned)lane_id()); }
+  template <class Load>
+  __device__ __forceinline__ void step(Load load) {
+    ++t;
+    if ((t & (kWave / 2 - 1)) == 0) {   // (the rows of half of the lanes are done)
+      const unsigned mine = (unsigned)lane_id();
+      if (((mine ^ t) & (kWave / 2)) != 0) rows = load((t & ~(unsigned)(kWave - 1)) + kWave + mine - ((t & (kWave / 2)) ? 0 : kWave));
+    }
+  }
+  template <class F>   // a number of the row `ahead` rows behind the one in the works (at most 31)
+  __device__ __forceinline__ int get(int ahead, F number) const { return __builtin_amdgcn_readlane(number(rows), (int)((t + ahead) & (kWave - 1))); }
+  template <class F>
+  __device__ __forceinline__ int64_t get64(int ahead, F number) const {
+    const unsigned lo = (unsigned)get(ahead, [&](const Row& r) { return (int)(unsigned)(unsigned long long)number(r); });
+    const unsigned hi = (unsigned)get(ahead, [&](const Row& r) { return (int)(unsigned)((unsigned long long)number(r) >> 32); });
+    return (int64_t)(((unsigned long long)hi << 32) | lo);
+  }
+};
+
 }  // namespace spg

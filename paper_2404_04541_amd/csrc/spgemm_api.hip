@@ -128,7 +128,7 @@ struct spgemm_plan_s {
   size_t list_bytes = 0, short_bytes = 0;
   unsigned* esc_words[2] = {nullptr, nullptr};   // sorted words of the rows of symbolic bins 0 and 1
   unsigned* records = nullptr;   // rows of symbolic bin 2
-  int* record_of = nullptr;      // per row of A: its record, -1 = none (written for the rows of symbolic bin 2)
+  RecordOf* record_of = nullptr; // per row of A: its record (written for the rows of symbolic bin 2)
   unsigned record_rows = 0;      // rows of the bin that have room for a record
   Control* ctl = nullptr;
   int64_t scan_blocks = 0;
@@ -357,6 +357,13 @@ int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const sp
   return SPGEMM_OK;
 }
 
+// Workgroups of the kernels of recorded rows: as many as are resident together, the same number in both phases, so that a wave of the numeric
+// one meets the rows that a wave of the symbolic one has given the same record.
+unsigned record_grid(spgemm_context* h, int64_t rows) {
+  const unsigned most = (unsigned)(ceil_div((int64_t)h->num_cus * kRecordGroups, kDies) * kDies);
+  return (unsigned)(ceil_div(grid_for(rows, 4, most), kDies) * kDies);
+}
+
 // The dense symbolic kernel's workgroups: waves of one, and how many are resident on the card.
 struct SymDense { int waves; size_t lds; unsigned groups; };
 SymDense sym_dense_shape(spgemm_context* h, int64_t rows, int64_t cols) {
@@ -471,7 +478,7 @@ void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, co
     words[b] = with_words && B->cols <= max_cols[b] ? align_up(host.hist[0][b] * word_bytes[b]) : 0;
     want += words[b];
   }
-  const size_t rec_bytes = (size_t)kRecWords * 4, map = align_up((size_t)p->m * 4);
+  const size_t rec_bytes = (size_t)kRecWords * 4, map = align_up((size_t)p->m * sizeof(RecordOf));
   if (rec_rows) want += map + rec_rows * rec_bytes;
   const double asked = h->col_list > 1 ? (double)h->col_list : 1.0e30;
   size_t limit = asked - (double)p->desc_bytes < (double)want ? (size_t)(asked - (double)p->desc_bytes) : want;
@@ -515,7 +522,7 @@ void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, co
   p->list_bytes = list_bytes;
   for (int b = 0; b < 2; ++b) if (words[b]) p->esc_words[b] = reinterpret_cast<unsigned*>(base + o_words[b]);
   if (rows) {
-    p->record_of = reinterpret_cast<int*>(base + o_map);
+    p->record_of = reinterpret_cast<RecordOf*>(base + o_map);
     p->records = reinterpret_cast<unsigned*>(base + o_map + map);
     p->record_rows = (unsigned)rows;
   }
@@ -623,13 +630,13 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     {
       Timer t(h, SPGEMM_K_SYM_HASH);
       if (hist[2])
-        hipLaunchKernelGGL(k_sym_wave, dim3(grid_for(hist[2], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 2, A->rowptr, A->colidx,
+        hipLaunchKernelGGL(k_sym_wave, dim3(record_grid(h, hist[2])), dim3(256), 0, s, p->perm_sym, p->ctl, 2, A->rowptr, A->colidx,
                            B->rowptr, B->colidx, B->nnz, p->cnt, p->records, p->record_rows, p->record_of);
       if (hist[3])
         hipLaunchKernelGGL((k_hash<256, 12, T, false>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
                            lds_hash_large, s, p->perm_sym, p->ctl, 0, 3, p->ip, A->rowptr, A->colidx,
                            (const T*)nullptr, B->rowptr, B->colidx, (const T*)nullptr, p->cnt, (const int64_t*)nullptr,
-                           (int32_t*)nullptr, (T*)nullptr, B->cols, (const int*)nullptr, 0, kOrderNotLooked);
+                           (int32_t*)nullptr, (T*)nullptr, B->cols, (const RecordOf*)nullptr, 0, kOrderNotLooked);
     }
     if (rows_dense > 0) {
       Timer t(h, SPGEMM_K_SYM_DENSE);
@@ -723,14 +730,14 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
     // (rows of the bin with a record, then the ones without; a row that has a record is in this bin: it has more than
     // kEscLargeCap products, or hashing is forced, and at most kNumHashSmall entries)
     if (p->recorded) {
-      const unsigned grid = grid_for(hist[2], 4, cap_small);
+      const unsigned grid = record_grid(h, p->stats.sym_bin_rows[2]);
       if (inside) {
         const int64_t most = A->nnz > B->nnz ? A->nnz : B->nnz;
         const OrderOperands order{(int)grid_for(most, kOrderInsideTile, kOrderParts), A->nnz, B->nnz, A->colidx, same ? nullptr : B->colidx};
-        hipLaunchKernelGGL((k_num_recorded<T, true>), dim3(grid + order.parts), dim3(256), 0, s, p->perm_num, p->ctl, 2, p->ip, p->records, p->record_of,
+        hipLaunchKernelGGL((k_num_recorded<T, true>), dim3(grid + order.parts), dim3(256), 0, s, p->perm_sym, p->ctl, 2, p->records, p->record_of,
                            A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val, order);
       } else {
-        hipLaunchKernelGGL((k_num_recorded<T, false>), dim3(grid), dim3(256), 0, s, p->perm_num, p->ctl, 2, p->ip, p->records, p->record_of,
+        hipLaunchKernelGGL((k_num_recorded<T, false>), dim3(grid), dim3(256), 0, s, p->perm_sym, p->ctl, 2, p->records, p->record_of,
                            A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val, OrderOperands{});
       }
     }
@@ -752,7 +759,7 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
       else
         hipLaunchKernelGGL((k_hash<256, 11, T, true>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
                            lds_hash_large, s, p->perm_num, p->ctl, 1, 3, p->ip, A->rowptr, A->colidx, a_val, B->rowptr,
-                           B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, B->cols, (const int*)nullptr, most_ip, looked3);
+                           B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, B->cols, (const RecordOf*)nullptr, most_ip, looked3);
     }
   }
   if (hist[4]) {
