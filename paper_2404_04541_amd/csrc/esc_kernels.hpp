@@ -87,24 +87,27 @@ __device__ __forceinline__ int group_number() {   // (wave-uniform where a group
 // cnt[row] = different columns of the row; words (optional): CAP per row of the bin, (column << log2 CAP) | position, sorted.
 // DESC: the row count has left the B rows of A's entries (desc).  pack != 0: such words fit 32 bits with the padding behind them.
 // (the register bounds are the smallest that spill nothing to speak of: one step further costs half of the speed)
+template <int GROUP, int CAP>
+struct EscSymLds {
+  __align__(16) unsigned keys[256 / GROUP][CAP];
+  EscLds<GROUP, CAP> quads[256 / GROUP];
+};
+
 template <int GROUP, int CAP, bool DESC>
-__global__ __launch_bounds__(256, 6) void k_esc_sym(const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const int64_t* __restrict__ a_rp,
+__device__ __forceinline__ void esc_sym_rows(EscSymLds<GROUP, CAP>* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const int64_t* __restrict__ a_rp,
                                                  const int32_t* __restrict__ a_col, const int64_t* __restrict__ b_rp, const unsigned long long* __restrict__ desc, const int32_t* __restrict__ b_col,
                                                  int64_t b_nnz, int pack, int* __restrict__ cnt, unsigned* __restrict__ words) {
   static_assert(CAP == 2 * GROUP && (CAP == 32 || CAP == 128), "each lane owns two list positions");
   constexpr int kGroups = 256 / GROUP;
   constexpr int kLogCap = CAP == 32 ? 5 : 7;
-  __shared__ __align__(16) unsigned s_keys[kGroups][CAP];
-  __shared__ EscLds<GROUP, CAP> s_lds[kGroups];
-  if (ctl->error) return;
   const unsigned first = ctl->offset[0][bin];
   const unsigned nrows = ctl->offset[0][bin + 1] - first;
   const int g = group_number<GROUP>(), gl = threadIdx.x % GROUP;
-  unsigned* keys = s_keys[g];
+  unsigned* keys = lds->keys[g];
   const int shift = pack ? kLogCap : 0, pmask = pack ? CAP - 1 : 0;
-  const unsigned ngroups = gridDim.x * kGroups;
+  const unsigned ngroups = wgs * kGroups;
   RowChain<GROUP> ch{perm + first, a_rp, a_col, b_rp, DESC ? desc : nullptr, nrows, ngroups};
-  unsigned slot = blockIdx.x * kGroups + g;
+  unsigned slot = wg * kGroups + g;
   ch.start(slot);
   const unsigned rounds = (nrows + ngroups - 1) / ngroups;   // (the same for every group: the wave's lanes stay together)
   for (unsigned r = 0; r < rounds; ++r, slot += ngroups) {
@@ -115,7 +118,7 @@ __global__ __launch_bounds__(256, 6) void k_esc_sym(const int* __restrict__ perm
       if (c > 0) ch.fetch_more(c);
       const int len = (int)(ch.bounds.v[1] - ch.bounds.v[0]);
       const int incl = group_incl_scan<GROUP>(len);
-      esc_quads<GROUP, CAP>(ch.bounds.v[0], len, filled + incl - len, &s_lds[g], [&](int, int pos, int64_t q, int n) {
+      esc_quads<GROUP, CAP>(ch.bounds.v[0], len, filled + incl - len, &lds->quads[g], [&](int, int pos, int64_t q, int n) {
         int col[4];
         load_quad<int32_t>(b_col, q, n, b_nnz, col);
 #pragma unroll
@@ -148,31 +151,43 @@ __global__ __launch_bounds__(256, 6) void k_esc_sym(const int* __restrict__ perm
   }
 }
 
+template <int GROUP, int CAP, bool DESC>
+__global__ __launch_bounds__(256, 6) void k_esc_sym(const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const int64_t* __restrict__ a_rp,
+                                                 const int32_t* __restrict__ a_col, const int64_t* __restrict__ b_rp, const unsigned long long* __restrict__ desc, const int32_t* __restrict__ b_col,
+                                                 int64_t b_nnz, int pack, int* __restrict__ cnt, unsigned* __restrict__ words) {
+  __shared__ EscSymLds<GROUP, CAP> lds;
+  if (ctl->error) return;
+  esc_sym_rows<GROUP, CAP, DESC>(&lds, blockIdx.x, gridDim.x, perm, ctl, bin, a_rp, a_col, b_rp, desc, b_col, b_nnz, pack, cnt, words);
+}
+
 // The rows of C from the plan's sorted words.  Lane gl owns the sorted positions gl and gl + GROUP.
+template <int GROUP, int CAP>
+struct EscNumLds {
+  double vals[256 / GROUP][CAP];
+  unsigned cols[256 / GROUP][CAP];
+  EscLds<GROUP, CAP> quads[256 / GROUP];
+  double av[256 / GROUP][GROUP];
+};
+
 template <int GROUP, int CAP, typename T, bool DESC>
-__global__ __launch_bounds__(256, GROUP == kWave ? 6 : 5) void k_esc_num(const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const int64_t* __restrict__ a_rp,
+__device__ __forceinline__ void esc_num_rows(EscNumLds<GROUP, CAP>* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const int64_t* __restrict__ a_rp,
                                                  const int32_t* __restrict__ a_col, const T* __restrict__ a_val, const int64_t* __restrict__ b_rp, const unsigned long long* __restrict__ desc,
                                                  const T* __restrict__ b_val, int64_t b_nnz, const unsigned* __restrict__ words,
                                                  const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val) {
   static_assert(CAP == 2 * GROUP && (CAP == 32 || CAP == 128), "each lane owns two list positions");
   constexpr int kGroups = 256 / GROUP;
   constexpr int kLogCap = CAP == 32 ? 5 : 7;
-  __shared__ double s_vals[kGroups][CAP];
-  __shared__ unsigned s_cols[kGroups][CAP];
-  __shared__ EscLds<GROUP, CAP> s_lds[kGroups];
-  __shared__ double s_av[kGroups][GROUP];
-  if (ctl->error || ctl->order_differs) return;
   const unsigned first = ctl->offset[0][bin];   // (the bins of rows this short are the same in both phases)
   const unsigned nrows = ctl->offset[0][bin + 1] - first;
   const int g = group_number<GROUP>(), gl = threadIdx.x % GROUP;
-  double* vals = s_vals[g];
-  unsigned* cols = s_cols[g];
-  double* s_a = s_av[g];
-  const unsigned ngroups = gridDim.x * kGroups;
+  double* vals = lds->vals[g];
+  unsigned* cols = lds->cols[g];
+  double* s_a = lds->av[g];
+  const unsigned ngroups = wgs * kGroups;
   auto value = [&](int64_t a, int n) { return gl < n ? a_val[a + gl] : T(0); };
   auto position = [&](int row) { return row >= 0 ? c_rp[row] : 0; };
   RowChain<GROUP> ch{perm + first, a_rp, a_col, b_rp, DESC ? desc : nullptr, nrows, ngroups};
-  unsigned slot = blockIdx.x * kGroups + g;
+  unsigned slot = wg * kGroups + g;
   ch.start(slot);
   T av0 = value(ch.a0, ch.d), av1 = value(ch.a01, ch.d1);
   int64_t out0 = position(ch.row), out1 = position(ch.row1), out2 = position(ch.row2);
@@ -197,7 +212,7 @@ __global__ __launch_bounds__(256, GROUP == kWave ? 6 : 5) void k_esc_num(const i
       const int incl = group_incl_scan<GROUP>(len);
       s_a[gl] = (double)av;
       group_sync<GROUP>();
-      esc_quads<GROUP, CAP>(ch.bounds.v[0], len, filled + incl - len, &s_lds[g], [&](int src, int pos, int64_t q, int n) {
+      esc_quads<GROUP, CAP>(ch.bounds.v[0], len, filled + incl - len, &lds->quads[g], [&](int src, int pos, int64_t q, int n) {
         T b[4];
         load_quad<T>(b_val, q, n, b_nnz, b);
         const double a = s_a[src];
@@ -233,6 +248,16 @@ __global__ __launch_bounds__(256, GROUP == kWave ? 6 : 5) void k_esc_num(const i
     av0 = av1; av1 = av2;
     out0 = out1; out1 = out2; out2 = out3;
   }
+}
+
+template <int GROUP, int CAP, typename T, bool DESC>
+__global__ __launch_bounds__(256, GROUP == kWave ? 6 : 5) void k_esc_num(const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const int64_t* __restrict__ a_rp,
+                                                 const int32_t* __restrict__ a_col, const T* __restrict__ a_val, const int64_t* __restrict__ b_rp, const unsigned long long* __restrict__ desc,
+                                                 const T* __restrict__ b_val, int64_t b_nnz, const unsigned* __restrict__ words,
+                                                 const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val) {
+  __shared__ EscNumLds<GROUP, CAP> lds;
+  if (ctl->error || ctl->order_differs) return;
+  esc_num_rows<GROUP, CAP, T, DESC>(&lds, blockIdx.x, gridDim.x, perm, ctl, bin, a_rp, a_col, a_val, b_rp, desc, b_val, b_nnz, words, c_rp, c_col, c_val);
 }
 
 // ---- without them --------------------------------------------------------------------------

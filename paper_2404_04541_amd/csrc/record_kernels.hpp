@@ -9,7 +9,8 @@
 //   one byte per product (the rank of its column in the row, in quad order) and the columns in ascending order.
 //   Rows of discretised operators are mostly the same row moved to other columns.  A wave keeps a row as its model; a later row with as many
 //   entries and as many products of each has its columns compared with the model's, and where all differ by the same shift nothing is
-//   inserted, sorted or written: the row takes the model's record and the shift.
+//   inserted, sorted or written: the row takes the model's record and the shift.  (Where the row count has seen that rows are mostly like the ones
+//   before them; otherwise the model's registers cost a fifth of the waves.)
 // Numeric: with the record a product is one byte, one multiplication and one addition at its rank; nothing is hashed,
 //   searched or sorted again.  The record stays in registers as long as the wave's rows have the same one.  Rows without a record take the
 //   hash workspace.
@@ -115,31 +116,48 @@ struct SymRow {   // a row, its entries of A (none: row < 0)
 };
 constexpr int kAlikeTries = 8;   // rows that only look alike a wave compares in vain before it stops
 
-__global__ __launch_bounds__(256, kRecordGroups) void k_sym_wave(const int* __restrict__ perm, Control* __restrict__ ctl, int bin,
+struct SymWaveLds {
+  __align__(16) int table[4][kSymSlots];
+  QuadEntry ent[4][kQuadEntries];
+  unsigned short slot[4][kNumHashSmall];   // slot of the column with a number
+  unsigned kept, done;                     // rows with a record, waves that have no more rows
+};
+
+template <bool ALIKE>
+__device__ __forceinline__ void sym_wave_rows(SymWaveLds* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, Control* __restrict__ ctl, int bin,
                                                   const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                   const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col, int64_t b_nnz,
                                                   int* __restrict__ cnt, unsigned* __restrict__ records, unsigned record_rows,
                                                   RecordOf* __restrict__ record_of) {
-  __shared__ __align__(16) int s_table[4][kSymSlots];
-  __shared__ QuadEntry s_ent[4][kQuadEntries];
-  __shared__ unsigned short s_slot[4][kNumHashSmall];   // slot of the column with a number
-  if (ctl->error) return;
+  if (threadIdx.x == 0) { lds->kept = 0; lds->done = 0; }
+  __syncthreads();
   const unsigned first = ctl->offset[0][bin];
   const unsigned nrows = ctl->offset[0][bin + 1] - first;
   const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
-  int* table = s_table[g];
-  QuadEntry* ent = s_ent[g];
-  unsigned* words = reinterpret_cast<unsigned*>(s_ent[g]);   // (column, number) by number, once the entries are no longer needed
+  int* table = lds->table[g];
+  QuadEntry* ent = lds->ent[g];
+  unsigned* words = reinterpret_cast<unsigned*>(lds->ent[g]);   // (column, number) by number, once the entries are no longer needed
   static_assert(sizeof(QuadEntry) * kQuadEntries >= kNumHashSmall * sizeof(unsigned), "the words fit the entries' space");
-  unsigned short* slot_of = s_slot[g];
+  unsigned short* slot_of = lds->slot[g];
   unsigned kept = 0;
   // The model: the row that later ones are compared with.  Its entries and their products (d < 0: there is none), where its quads
   // come from and their columns, what became of it, and how the comparisons with it went.
   int m_d = -1, m_len = 0, m_nq = 0, m_found = 0, m_rec = -1, m_hits = 0, m_missed = 0, vain = 0;
   unsigned m_quad[kQuadRounds] = {};
   int m_col[kQuadRounds][4] = {};
-  const DieRows order(blockIdx.x, gridDim.x, g, nrows);
-  if (order.count == 0) return;   // (the wave)
+  const DieRows order(wg, wgs, g, nrows);
+  // One atomic a workgroup that has kept rows: they come from all workgroups to one counter, about 12 ns each (one a wave: 300 000 rows of 256
+  // products 470 us, of which the rows are 250).
+  auto finish = [&] {
+    if (lane != 0) return;
+    if (kept) atomicAdd(&lds->kept, kept);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    if (atomicAdd(&lds->done, 1u) == 3 && lds->kept) atomicAdd(&ctl->recorded, lds->kept);
+  };
+  if (order.count == 0) {   // (the wave)
+    finish();
+    return;
+  }
   auto load = [&](unsigned t) {
     SymRow r;
     const unsigned at = order.at(t);
@@ -173,6 +191,7 @@ __global__ __launch_bounds__(256, kRecordGroups) void k_sym_wave(const int* __re
     const int d = entries(0);
     bs = bounds1.v[0];
     len = lane < d ? (int)(bounds1.v[1] - bs) : 0;
+    if constexpr (ALIKE) {
     // (a quad that reaches behind the end of B is loaded further in front: such a row is not compared)
     compare = d == m_d && vain < kAlikeTries && !__any(len != m_len || (len > 0 && bs + len + 3 > b_nnz));
     wave_sync_lds();
@@ -190,6 +209,7 @@ __global__ __launch_bounds__(256, kRecordGroups) void k_sym_wave(const int* __re
     fetch(1);
     fetch(0);
     wave_sync_lds();
+    }
     bounds1 = bounds_of(k2);
     k2 = a_col[place(2)];
   };
@@ -203,7 +223,7 @@ __global__ __launch_bounds__(256, kRecordGroups) void k_sym_wave(const int* __re
     unsigned slots[kQuadRounds][2] = {};           // of a recorded row's products, two to a word
     int nq_row = 0;
     bool alike = false;
-    if (compare) {   // is the row the model moved to other columns?
+    if (ALIKE && compare) {   // is the row the model moved to other columns?
       shift = __builtin_amdgcn_readfirstlane(col[0][0]) - __builtin_amdgcn_readfirstlane(m_col[0][0]);
       bool other = false;
 #pragma unroll
@@ -225,7 +245,7 @@ __global__ __launch_bounds__(256, kRecordGroups) void k_sym_wave(const int* __re
     }
     for (int base = 0; base < d && !alike; base += kQuadEntries) {
       int nq = m_nq;
-      if (base > 0 || !compare) {
+      if (!ALIKE || base > 0 || !compare) {
         int64_t from_here = bs;
         int n_here = len;
         if (base > 0) {
@@ -263,7 +283,7 @@ __global__ __launch_bounds__(256, kRecordGroups) void k_sym_wave(const int* __re
 #pragma unroll
         for (int t = 0; t < kSymSlots / 4 / kWave; ++t) t4[t * kWave + lane] = make_int4(kEmptyKey, kEmptyKey, kEmptyKey, kEmptyKey);
         wave_sync_lds();
-        if (d <= kQuadEntries && (m_hits == 0 || ++m_missed > 1)) {   // (one row at an edge leaves the model what it is)
+        if (ALIKE && d <= kQuadEntries && (m_hits == 0 || ++m_missed > 1)) {   // (one row at an edge leaves the model what it is)
           m_d = d; m_len = len; m_nq = nq; m_hits = 0; m_missed = 0;
 #pragma unroll
           for (int r = 0; r < kQuadRounds; ++r) {
@@ -306,7 +326,7 @@ __global__ __launch_bounds__(256, kRecordGroups) void k_sym_wave(const int* __re
     }
     const bool keep = !alike && want && found <= kNumHashSmall;
     if (keep) in_record = (int)row_at;
-    if (m_rec == -2) {   // the row is the model
+    if (ALIKE && m_rec == -2) {   // the row is the model
       m_found = found;
       m_rec = in_record;
     }
@@ -359,35 +379,41 @@ __global__ __launch_bounds__(256, kRecordGroups) void k_sym_wave(const int* __re
       if (record_of) record_of[row] = RecordOf{in_record, shift};
     }
   }
-  if (lane == 0 && kept) atomicAdd(&ctl->recorded, kept);
+  finish();
+}
+
+// ALIKE: rows are compared with a model.
+template <bool ALIKE>
+__global__ __launch_bounds__(256, ALIKE ? kRecordGroups : 5) void k_sym_wave(const int* __restrict__ perm, Control* __restrict__ ctl, int bin,
+                                                  const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
+                                                  const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col, int64_t b_nnz,
+                                                  int* __restrict__ cnt, unsigned* __restrict__ records, unsigned record_rows,
+                                                  RecordOf* __restrict__ record_of) {
+  __shared__ SymWaveLds lds;
+  if (ctl->error) return;
+  sym_wave_rows<ALIKE>(&lds, blockIdx.x, gridDim.x, perm, ctl, bin, a_rp, a_col, b_rp, b_col, b_nnz, cnt, records, record_rows, record_of);
 }
 
 // Numeric pass over the recorded rows of a bin, a wave per row; rows without a record are left to the hash workspace.
-// SUM: the first order.parts workgroups look at the order of the entries (order_later) while the others do the rows.
-template <typename T, bool SUM>
-__global__ __launch_bounds__(256) void k_num_recorded(const int* __restrict__ perm, std::conditional_t<SUM, Control, const Control>* __restrict__ ctl, int bin, const unsigned* __restrict__ records, const RecordOf* __restrict__ record_of,
+template <typename T>
+struct NumRecordedLds {
+  double acc[4][kRecSums];
+  QuadEntry ent[4][kQuadEntries];
+  T av[4][kQuadEntries];
+};
+
+// ALIKE: neighbouring rows of a wave have the same record; otherwise fewer registers (two quads in flight a lane) and more waves are worth more.
+template <bool ALIKE, typename T>
+__device__ __forceinline__ void num_recorded_rows(NumRecordedLds<T>* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const unsigned* __restrict__ records, const RecordOf* __restrict__ record_of,
                                                       const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const T* __restrict__ a_val,
                                                       const int64_t* __restrict__ b_rp, const T* __restrict__ b_val, int64_t b_nnz,
-                                                      const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val, const OrderOperands order) {
-  __shared__ double s_acc[4][kRecSums];
-  __shared__ QuadEntry s_ent[4][kQuadEntries];
-  __shared__ T s_av[4][kQuadEntries];
-  if (ctl->error || (!SUM && ctl->order_differs)) return;
-  unsigned wg = blockIdx.x, wgs = gridDim.x;
-  if constexpr (SUM) {
-    if ((int)wg < order.parts) {
-      order_add<256>(order_share<256>(order.na, order.a_col, order.nb, order.b_col, wg, order.parts), order.parts, ctl, 0, &ctl->order_later);
-      return;
-    }
-    wg -= order.parts;
-    wgs -= order.parts;
-  }
+                                                      const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val) {
   const unsigned first = ctl->offset[0][bin];   // (the order of the symbolic kernel: a wave meets the rows of a record one after the other)
   const unsigned nrows = ctl->offset[0][bin + 1] - first;
   const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
-  double* acc = s_acc[g];
-  QuadEntry* ent = s_ent[g];
-  T* s_a = s_av[g];
+  double* acc = lds->acc[g];
+  QuadEntry* ent = lds->ent[g];
+  T* s_a = lds->av[g];
   const DieRows in_order(wg, wgs, g, nrows);
   auto load = [&](unsigned t) {
     NumRow r;
@@ -449,7 +475,7 @@ __global__ __launch_bounds__(256) void k_num_recorded(const int* __restrict__ pe
           }
           unsigned to[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) to[u] = g * (unsigned)sizeof(s_acc[0]) + (u < quad_count(h_quad[r]) ? (rank >> (8 * u)) & 255u : 256u + lane) * 8u;
+          for (int u = 0; u < 4; ++u) to[u] = g * (unsigned)sizeof(lds->acc[0]) + (u < quad_count(h_quad[r]) ? (rank >> (8 * u)) & 255u : 256u + lane) * 8u;
           h_sum[r][0] = to[0] | (to[1] << 16);
           h_sum[r][1] = to[2] | (to[3] << 16);
         }
@@ -461,30 +487,37 @@ __global__ __launch_bounds__(256) void k_num_recorded(const int* __restrict__ pe
       ent[lane].bs = bs;
       s_a[lane] = av;
       wave_sync_lds();
-      T b[kQuadRounds][4];
+      constexpr int kAhead = ALIKE ? kQuadRounds : 2;   // quads in flight a lane
 #pragma unroll
-      for (int r = 0; r < kQuadRounds; ++r) {
-        if (r * kWave >= h_nq) break;
-        const int64_t p = ent[quad_src(h_quad[r])].bs + quad_off(h_quad[r]);
-        if (!tight) {
-          const Run<T, 4> v = load_run<T, 4>(b_val + p);
+      for (int r0 = 0; r0 < kQuadRounds; r0 += kAhead) {
+        if (r0 * kWave >= h_nq) break;
+        T b[kAhead][4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) b[r][u] = v.v[u];
-        } else {
-          int n4 = quad_count(h_quad[r]);
-          asm volatile("" : "+v"(n4));   // (no code: keeps this first load from being shared with the wide one, which then is three)
+        for (int i = 0; i < kAhead; ++i) {
+          const int r = r0 + i;
+          if (r * kWave >= h_nq) break;
+          const int64_t p = ent[quad_src(h_quad[r])].bs + quad_off(h_quad[r]);
+          if (!tight) {
+            const Run<T, 4> v = load_run<T, 4>(b_val + p);
 #pragma unroll
-          for (int u = 0; u < 4; ++u) b[r][u] = u < n4 ? b_val[p + u] : T(0);
+            for (int u = 0; u < 4; ++u) b[i][u] = v.v[u];
+          } else {
+            int n4 = quad_count(h_quad[r]);
+            asm volatile("" : "+v"(n4));   // (no code: keeps this first load from being shared with the wide one, which then is three)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) b[i][u] = u < n4 ? b_val[p + u] : T(0);
+          }
         }
-      }
 #pragma unroll
-      for (int r = 0; r < kQuadRounds; ++r) {
-        if (r * kWave >= h_nq) break;
-        const double a = (double)s_a[quad_src(h_quad[r])];
+        for (int i = 0; i < kAhead; ++i) {
+          const int r = r0 + i;
+          if (r * kWave >= h_nq) break;
+          const double a = (double)s_a[quad_src(h_quad[r])];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const unsigned to = (h_sum[r][u >> 1] >> (16 * (u & 1))) & 0xffffu;
-          __hip_atomic_fetch_add(static_cast<double*>(__builtin_assume_aligned(reinterpret_cast<unsigned char*>(s_acc) + to, 8)), a * (double)b[r][u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          for (int u = 0; u < 4; ++u) {
+            const unsigned to = (h_sum[r][u >> 1] >> (16 * (u & 1))) & 0xffffu;
+            __hip_atomic_fetch_add(static_cast<double*>(__builtin_assume_aligned(reinterpret_cast<unsigned char*>(lds->acc) + to, 8)), a * (double)b[i][u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
         }
       }
       wave_sync_lds();
@@ -505,6 +538,26 @@ __global__ __launch_bounds__(256) void k_num_recorded(const int* __restrict__ pe
     av = a_val[place(1)];
     k2 = a_col[place(2)];
   }
+}
+
+// SUM: the first order.parts workgroups look at the order of the entries (order_later) while the others do the rows.
+template <typename T, bool SUM, bool ALIKE>
+__global__ __launch_bounds__(256, ALIKE ? kRecordGroups : 8) void k_num_recorded(const int* __restrict__ perm, std::conditional_t<SUM, Control, const Control>* __restrict__ ctl, int bin, const unsigned* __restrict__ records, const RecordOf* __restrict__ record_of,
+                                                      const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const T* __restrict__ a_val,
+                                                      const int64_t* __restrict__ b_rp, const T* __restrict__ b_val, int64_t b_nnz,
+                                                      const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val, const OrderOperands order) {
+  __shared__ NumRecordedLds<T> lds;
+  if (ctl->error || (!SUM && ctl->order_differs)) return;
+  unsigned wg = blockIdx.x, wgs = gridDim.x;
+  if constexpr (SUM) {
+    if ((int)wg < order.parts) {
+      order_add<256>(order_share<256>(order.na, order.a_col, order.nb, order.b_col, wg, order.parts), order.parts, ctl, 0, &ctl->order_later);
+      return;
+    }
+    wg -= order.parts;
+    wgs -= order.parts;
+  }
+  num_recorded_rows<ALIKE, T>(&lds, wg, wgs, perm, ctl, bin, records, record_of, a_rp, a_col, a_val, b_rp, b_val, b_nnz, c_rp, c_col, c_val);
 }
 
 }  // namespace spg

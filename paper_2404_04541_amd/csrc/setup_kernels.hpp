@@ -114,6 +114,23 @@ __device__ __forceinline__ void validate_b(int part, int parts, int64_t rows, in
   }
 }
 
+// Are rows mostly the row before moved to other columns (as many entries, the first and the last moved by the same), as those of
+// discretised operators are?  A pair of rows for every thread of one workgroup, spread over all rows.
+__device__ __forceinline__ void sample_rows(int64_t m, int64_t nnz_a, const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, Control* ctl) {
+  const int64_t r = (m - 1) * (int64_t)threadIdx.x / kCountThreads;
+  bool looked = false, moved = false;
+  if (r + 2 <= m) {
+    const int64_t p0 = a_rp[r], p1 = a_rp[r + 1], p2 = a_rp[r + 2];
+    looked = p0 >= 0 && p0 + 1 < p1 && p1 < p2 && p2 <= nnz_a;   // (nobody has checked them yet)
+    if (looked) moved = p2 - p1 == p1 - p0 && (unsigned)a_col[p1] - (unsigned)a_col[p0] == (unsigned)a_col[p2 - 1] - (unsigned)a_col[p1 - 1];
+  }
+  const int all = __popcll(__ballot(looked)), some = __popcll(__ballot(moved));
+  if (lane_id() == 0 && all) {
+    atomicAdd(&ctl->looked, (unsigned)all);
+    if (some) atomicAdd(&ctl->moved, (unsigned)some);
+  }
+}
+
 // Bound: the gather of B's row pointer (a line per entry of A where it does not fit the L2 cache: 33.5 M entries 0.56 ms, with the
 // descriptions written 0.64), a chain of three loads where there are few rows.
 // The first `parts` workgroups check B.  The others count the products of A's rows: a workgroup takes chunks of `chunk_rows`
@@ -137,6 +154,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int parts, int64_t
   __shared__ int sums[2][kCountThreads / kWave];
   __shared__ int bad;
   if ((int)blockIdx.x < parts) {
+    if (blockIdx.x == 0) sample_rows(m, nnz_a, a_rp, a_col, ctl);
     validate_b(blockIdx.x, parts, b_rows, b_cols, b_nnz, b_rp, b_col, ctl, sums);
     return;
   }

@@ -24,6 +24,7 @@
 #include "dense_kernels.hpp"
 #include "tile_kernels.hpp"
 #include "wide_kernels.hpp"
+#include "short_kernels.hpp"
 #include "staged_kernels.hpp"
 #include "sort_kernels.hpp"
 #include "tensor_kernels.hpp"
@@ -134,6 +135,7 @@ struct spgemm_plan_s {
   int64_t scan_blocks = 0;
   int64_t recorded = 0;          // rows that have a record
   int force = 0;                 // SPGEMM_OPT_FORCE_WORKSPACE of the symbolic phase
+  bool alike = false;            // rows are mostly the row before moved to other columns
   bool flag_rows = false;        // classes 0 and 1 take the flag-list workspace
   bool all_listed = false;       // every row of the dense classes has its structure in the column list
   bool order_kept = false;       // the checksums of the order of the entries were taken
@@ -357,12 +359,26 @@ int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const sp
   return SPGEMM_OK;
 }
 
-// Workgroups of the kernels of recorded rows: as many as are resident together, the same number in both phases, so that a wave of the numeric
-// one meets the rows that a wave of the symbolic one has given the same record.
-unsigned record_grid(spgemm_context* h, int64_t rows) {
-  const unsigned most = (unsigned)(ceil_div((int64_t)h->num_cus * kRecordGroups, kDies) * kDies);
+// Workgroups of the kernels of recorded rows.  Where rows are alike, as many as are resident together, the same number in both phases, so that a
+// wave of the numeric one meets the rows that a wave of the symbolic one has given the same record; otherwise twice as many, which evens out rows
+// that differ (symbolic us with 32 | 10 | 5 on a compute unit: 30 000 rows of 256 products 99 | 53 | 46, 300 000 336 | 331 | 358, 32 000 ragged
+// ones 193 | 197 | 208).
+unsigned record_grid(spgemm_context* h, const spgemm_plan_s* p, int64_t rows) {
+  const unsigned most = (unsigned)(ceil_div((int64_t)h->num_cus * (p->alike ? kRecordGroups : 10), kDies) * kDies);
   return (unsigned)(ceil_div(grid_for(rows, 4, most), kDies) * kDies);
 }
+
+// Whether the classes of shorter rows share a launch (short_kernels.hpp): where there are rows of two of them, and no more than fill the chip
+// kShortRounds times (each class counted in the workgroups it would like).
+constexpr int64_t kShortRounds = 16;
+template <typename N>
+bool short_rows_ok(spgemm_context* h, const N* hist) {
+  int kinds = 0;
+  for (int b = 0; b < 4; ++b) kinds += hist[b] > 0 ? 1 : 0;
+  const int64_t wgs = (int64_t)hist[0] / 16 + (int64_t)hist[1] / 4 + (int64_t)hist[2] / 4 + (int64_t)hist[3];
+  return !h->timing && kinds > 1 && wgs <= kShortRounds * kShortGroups * h->num_cus;   // (with timing every class has a time of its own)
+}
+unsigned short_grid(int64_t rows, int64_t per_block) { return rows > 0 ? (unsigned)(ceil_div(ceil_div(rows, per_block), kDies) * kDies) : 0; }
 
 // The dense symbolic kernel's workgroups: waves of one, and how many are resident on the card.
 struct SymDense { int waves; size_t lds; unsigned groups; };
@@ -582,6 +598,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     const int lds = ensure_big_lds(h);
     if (lds) return lds;
   }
+  p->alike = host.moved > 0 && host.moved * 2 >= host.looked;
   if (hist[0] + hist[1] == 0) drop_desc(h, p);   // (nobody reads it)
   if ((int64_t)hist[0] + hist[1] < kFlagMinRows) p->flag_rows = false;
   int rc = alloc_dense_lists(h, p, B, host, &tile_cap, &run_cap, &list_want);
@@ -608,35 +625,41 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     }
   }
   if (m > 0) {
-    {
-      Timer t(h, SPGEMM_K_SYM_ESC);
-      if (p->flag_rows) {
-        auto rows = [&](auto wpl) {
-          constexpr int W = decltype(wpl)::value;
-          if (hist[0])
-            hipLaunchKernelGGL((k_flag_sym<32, W>), dim3(grid_for(hist[0], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0, A->rowptr, A->colidx, B->rowptr, B->colidx, B->nnz, p->cnt);
-          if (hist[1])
-            hipLaunchKernelGGL((k_flag_sym<128, W>), dim3(grid_for(hist[1], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx, B->rowptr, B->colidx, B->nnz, p->cnt);
-        };
-        with_flag_words(B->cols, rows);
+    if (!p->flag_rows && !p->desc && short_rows_ok(h, hist)) {
+      const SymShort sh{{short_grid(hist[3], 1), hist[2] ? record_grid(h, p, hist[2]) : 0u, short_grid(hist[1], 4), short_grid(hist[0], 16)}, p->perm_sym, p->ip, A->rowptr, B->rowptr,
+                        A->colidx, B->colidx, B->nnz, B->cols, pack32, pack128, p->cnt, p->esc_words[0], p->esc_words[1], p->records, p->record_rows, p->record_of};
+      hipLaunchKernelGGL((p->alike ? k_sym_short<true> : k_sym_short<false>), dim3(sh.wgs[0] + sh.wgs[1] + sh.wgs[2] + sh.wgs[3]), dim3(256), sym_short_lds(), s, p->ctl, sh);
+    } else {
+      {
+        Timer t(h, SPGEMM_K_SYM_ESC);
+        if (p->flag_rows) {
+          auto rows = [&](auto wpl) {
+            constexpr int W = decltype(wpl)::value;
+            if (hist[0])
+              hipLaunchKernelGGL((k_flag_sym<32, W>), dim3(grid_for(hist[0], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0, A->rowptr, A->colidx, B->rowptr, B->colidx, B->nnz, p->cnt);
+            if (hist[1])
+              hipLaunchKernelGGL((k_flag_sym<128, W>), dim3(grid_for(hist[1], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx, B->rowptr, B->colidx, B->nnz, p->cnt);
+          };
+          with_flag_words(B->cols, rows);
+        }
+        if (hist[0] && !p->flag_rows)
+          hipLaunchKernelGGL((p->desc ? k_esc_sym<16, 32, true> : k_esc_sym<16, 32, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0, A->rowptr, A->colidx,
+                             B->rowptr, p->desc, B->colidx, B->nnz, pack32, p->cnt, p->esc_words[0]);
+        if (hist[1] && !p->flag_rows)
+          hipLaunchKernelGGL((p->desc ? k_esc_sym<64, 128, true> : k_esc_sym<64, 128, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx,
+                             B->rowptr, p->desc, B->colidx, B->nnz, pack128, p->cnt, p->esc_words[1]);
       }
-      if (hist[0] && !p->flag_rows)
-        hipLaunchKernelGGL((p->desc ? k_esc_sym<16, 32, true> : k_esc_sym<16, 32, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0, A->rowptr, A->colidx,
-                           B->rowptr, p->desc, B->colidx, B->nnz, pack32, p->cnt, p->esc_words[0]);
-      if (hist[1] && !p->flag_rows)
-        hipLaunchKernelGGL((p->desc ? k_esc_sym<64, 128, true> : k_esc_sym<64, 128, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx,
-                           B->rowptr, p->desc, B->colidx, B->nnz, pack128, p->cnt, p->esc_words[1]);
-    }
-    {
-      Timer t(h, SPGEMM_K_SYM_HASH);
-      if (hist[2])
-        hipLaunchKernelGGL(k_sym_wave, dim3(record_grid(h, hist[2])), dim3(256), 0, s, p->perm_sym, p->ctl, 2, A->rowptr, A->colidx,
-                           B->rowptr, B->colidx, B->nnz, p->cnt, p->records, p->record_rows, p->record_of);
-      if (hist[3])
-        hipLaunchKernelGGL((k_hash<256, 12, T, false>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
-                           lds_hash_large, s, p->perm_sym, p->ctl, 0, 3, p->ip, A->rowptr, A->colidx,
-                           (const T*)nullptr, B->rowptr, B->colidx, (const T*)nullptr, p->cnt, (const int64_t*)nullptr,
-                           (int32_t*)nullptr, (T*)nullptr, B->cols, (const RecordOf*)nullptr, 0, kOrderNotLooked);
+      {
+        Timer t(h, SPGEMM_K_SYM_HASH);
+        if (hist[2])
+          hipLaunchKernelGGL((p->alike ? k_sym_wave<true> : k_sym_wave<false>), dim3(record_grid(h, p, hist[2])), dim3(256), 0, s, p->perm_sym, p->ctl, 2, A->rowptr, A->colidx,
+                             B->rowptr, B->colidx, B->nnz, p->cnt, p->records, p->record_rows, p->record_of);
+        if (hist[3])
+          hipLaunchKernelGGL((k_hash<256, 12, T, false>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
+                             lds_hash_large, s, p->perm_sym, p->ctl, 0, 3, p->ip, A->rowptr, A->colidx,
+                             (const T*)nullptr, B->rowptr, B->colidx, (const T*)nullptr, p->cnt, (const int64_t*)nullptr,
+                             (int32_t*)nullptr, (T*)nullptr, B->cols, (const RecordOf*)nullptr, 0, kOrderNotLooked);
+      }
     }
     if (rows_dense > 0) {
       Timer t(h, SPGEMM_K_SYM_DENSE);
@@ -697,69 +720,97 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   const bool same = same_columns(A, B);
   const bool inside = check && p->recorded && A->nnz + (same ? 0 : B->nnz) <= kOrderInside;
   const int looked3 = !check3 ? kOrderNotLooked : inside ? kOrderBeside : kOrderSummed;
-  {
-    Timer t(h, SPGEMM_K_NUM_ESC);
-    if ((check || check3) && !inside) sum_order(h, p, A, B, 0);
-    if (p->flag_rows) {
-      auto rows = [&](auto wpl) {
-        constexpr int W = decltype(wpl)::value;
-        if (hist[0])
-          hipLaunchKernelGGL((k_flag_num<32, W, T>), dim3(grid_for(hist[0], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 0, A->rowptr, A->colidx, a_val,
-                             B->rowptr, B->colidx, b_val, B->nnz, c_rp, c_col, c_val);
-        if (hist[1])
-          hipLaunchKernelGGL((k_flag_num<128, W, T>), dim3(grid_for(hist[1], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, A->rowptr, A->colidx, a_val,
-                             B->rowptr, B->colidx, b_val, B->nnz, c_rp, c_col, c_val);
-      };
-      with_flag_words(B->cols, rows);
-    } else if (words0)
-      hipLaunchKernelGGL((p->desc ? k_esc_num<16, 32, T, true> : k_esc_num<16, 32, T, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0,
-                         A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[0], c_rp, c_col, c_val);
-    else if (hist[0])
-      hipLaunchKernelGGL((k_esc<16, 32, T>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 0,
-                         A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, B->nnz);
-    if (p->flag_rows) {
-    } else if (words1)
-      hipLaunchKernelGGL((p->desc ? k_esc_num<64, 128, T, true> : k_esc_num<64, 128, T, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1,
-                         A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[1], c_rp, c_col, c_val);
-    else if (hist[1])
-      hipLaunchKernelGGL((k_esc<64, 128, T>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 1,
-                         A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack128, B->nnz);
-  }
-  {
-    Timer t(h, SPGEMM_K_NUM_HASH);
-    // (rows of the bin with a record, then the ones without; a row that has a record is in this bin: it has more than
-    // kEscLargeCap products, or hashing is forced, and at most kNumHashSmall entries)
-    if (p->recorded) {
-      const unsigned grid = record_grid(h, p->stats.sym_bin_rows[2]);
-      if (inside) {
-        const int64_t most = A->nnz > B->nnz ? A->nnz : B->nnz;
-        const OrderOperands order{(int)grid_for(most, kOrderInsideTile, kOrderParts), A->nnz, B->nnz, A->colidx, same ? nullptr : B->colidx};
-        hipLaunchKernelGGL((k_num_recorded<T, true>), dim3(grid + order.parts), dim3(256), 0, s, p->perm_sym, p->ctl, 2, p->records, p->record_of,
-                           A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val, order);
-      } else {
-        hipLaunchKernelGGL((k_num_recorded<T, false>), dim3(grid), dim3(256), 0, s, p->perm_sym, p->ctl, 2, p->records, p->record_of,
-                           A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val, OrderOperands{});
+  // (rows of class 3 that have no tiles; those too that have, in another order than the plan's)
+  const bool rows3 = hist[3] && (!tiles3 || check3 || p->stats.sym_bin_rows[2] + p->stats.sym_bin_rows[3] > 0);
+  const int most_ip = tiles3 ? kSymHashLarge : 0x7fffffff;
+  const bool row_tiles = tiles3 && B->cols <= kRowTileMaxCols;
+  auto other_order_rows = [&] {
+    const unsigned w0 = words0 ? grid_for(hist[0], 16, cap_small) : 0, w1 = words1 ? grid_for(hist[1], 4, cap_small) : 0, w2 = p->recorded ? grid_for(hist[2], 4, cap_small) : 0;
+    hipLaunchKernelGGL(k_other_order<T>, dim3(w0 + w1 + w2), dim3(256), other_order_lds_bytes<T>(), s, w0, w1, w2, p->perm_num, p->ctl, p->ip, A->rowptr,
+                       A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, pack128, B->nnz, B->cols, inside ? 1 : 0);
+  };
+  if (!p->flag_rows && !p->desc && !inside && !check3 && short_rows_ok(h, hist)) {
+    if (check) sum_order(h, p, A, B, 0);
+    NumShort<T> sh{};
+    sh.wgs[0] = rows3 ? short_grid(hist[3], 1) : 0;
+    sh.wgs[1] = p->recorded ? record_grid(h, p, p->stats.sym_bin_rows[2]) : 0;
+    sh.wgs[2] = hist[2] > p->recorded ? short_grid(hist[2], 4) : 0;
+    sh.wgs[3] = short_grid(hist[1], 4);
+    sh.wgs[4] = short_grid(hist[0], 16);
+    sh.perm_sym = p->perm_sym; sh.perm_num = p->perm_num; sh.ip = p->ip;
+    sh.a_rp = A->rowptr; sh.a_col = A->colidx; sh.a_val = a_val;
+    sh.b_rp = B->rowptr; sh.b_col = B->colidx; sh.b_val = b_val; sh.b_nnz = B->nnz; sh.n_cols = B->cols;
+    sh.pack32 = pack32; sh.pack128 = pack128;
+    sh.words32 = words0 ? p->esc_words[0] : nullptr;
+    sh.words128 = words1 ? p->esc_words[1] : nullptr;
+    sh.records = p->records; sh.record_of = p->recorded ? p->record_of : nullptr;
+    sh.c_rp = c_rp; sh.c_col = c_col; sh.c_val = c_val;
+    sh.tiles = row_tiles ? 1 : 0; sh.most_ip = most_ip; sh.looked = looked3;
+    size_t lds = num_short_lds<T>();
+    const size_t lds3 = rows3 ? (row_tiles ? row_tile_lds<T>(B->cols) : lds_hash_large) : 0;
+    if (lds < lds3) lds = lds3;
+    const unsigned wgs = sh.wgs[0] + sh.wgs[1] + sh.wgs[2] + sh.wgs[3] + sh.wgs[4];
+    if (wgs) hipLaunchKernelGGL(k_num_short<T>, dim3(wgs), dim3(256), lds, s, p->ctl, sh);
+    if (check) other_order_rows();
+  } else {
+    {
+      Timer t(h, SPGEMM_K_NUM_ESC);
+      if ((check || check3) && !inside) sum_order(h, p, A, B, 0);
+      if (p->flag_rows) {
+        auto rows = [&](auto wpl) {
+          constexpr int W = decltype(wpl)::value;
+          if (hist[0])
+            hipLaunchKernelGGL((k_flag_num<32, W, T>), dim3(grid_for(hist[0], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 0, A->rowptr, A->colidx, a_val,
+                               B->rowptr, B->colidx, b_val, B->nnz, c_rp, c_col, c_val);
+          if (hist[1])
+            hipLaunchKernelGGL((k_flag_num<128, W, T>), dim3(grid_for(hist[1], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, A->rowptr, A->colidx, a_val,
+                               B->rowptr, B->colidx, b_val, B->nnz, c_rp, c_col, c_val);
+        };
+        with_flag_words(B->cols, rows);
+      } else if (words0)
+        hipLaunchKernelGGL((p->desc ? k_esc_num<16, 32, T, true> : k_esc_num<16, 32, T, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0,
+                           A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[0], c_rp, c_col, c_val);
+      else if (hist[0])
+        hipLaunchKernelGGL((k_esc<16, 32, T>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 0,
+                           A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, B->nnz);
+      if (p->flag_rows) {
+      } else if (words1)
+        hipLaunchKernelGGL((p->desc ? k_esc_num<64, 128, T, true> : k_esc_num<64, 128, T, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1,
+                           A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[1], c_rp, c_col, c_val);
+      else if (hist[1])
+        hipLaunchKernelGGL((k_esc<64, 128, T>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 1,
+                           A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack128, B->nnz);
+    }
+    {
+      Timer t(h, SPGEMM_K_NUM_HASH);
+      // (rows of the bin with a record, then the ones without; a row that has a record is in this bin: it has more than
+      // kEscLargeCap products, or hashing is forced, and at most kNumHashSmall entries)
+      if (p->recorded) {
+        const unsigned grid = record_grid(h, p, p->stats.sym_bin_rows[2]);
+        if (inside) {
+          const int64_t most = A->nnz > B->nnz ? A->nnz : B->nnz;
+          const OrderOperands order{(int)grid_for(most, kOrderInsideTile, kOrderParts), A->nnz, B->nnz, A->colidx, same ? nullptr : B->colidx};
+          hipLaunchKernelGGL((p->alike ? k_num_recorded<T, true, true> : k_num_recorded<T, true, false>), dim3(grid + order.parts), dim3(256), 0, s, p->perm_sym, p->ctl, 2, p->records, p->record_of,
+                             A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val, order);
+        } else {
+          hipLaunchKernelGGL((p->alike ? k_num_recorded<T, false, true> : k_num_recorded<T, false, false>), dim3(grid), dim3(256), 0, s, p->perm_sym, p->ctl, 2, p->records, p->record_of,
+                             A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val, OrderOperands{});
+        }
       }
-    }
-    if (hist[2] > p->recorded)
-      hipLaunchKernelGGL((k_hash<64, 8, T, true>), dim3(grid_for(hist[2], 4, cap_small)), dim3(256), lds_hash_small, s,
-                         p->perm_num, p->ctl, 1, 2, p->ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, (int*)nullptr,
-                         c_rp, c_col, c_val, B->cols, p->recorded ? p->record_of : nullptr, 0, kOrderNotLooked);
-    if (check) {
-      const unsigned w0 = words0 ? grid_for(hist[0], 16, cap_small) : 0, w1 = words1 ? grid_for(hist[1], 4, cap_small) : 0, w2 = p->recorded ? grid_for(hist[2], 4, cap_small) : 0;
-      hipLaunchKernelGGL(k_other_order<T>, dim3(w0 + w1 + w2), dim3(256), other_order_lds_bytes<T>(), s, w0, w1, w2, p->perm_num, p->ctl, p->ip, A->rowptr,
-                         A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, pack128, B->nnz, B->cols, inside ? 1 : 0);
-    }
-    // (rows of class 3 that have no tiles; those too that have, in another order than the plan's)
-    if (hist[3] && (!tiles3 || check3 || p->stats.sym_bin_rows[2] + p->stats.sym_bin_rows[3] > 0)) {
-      const int most_ip = tiles3 ? kSymHashLarge : 0x7fffffff;
-      if (tiles3 && B->cols <= kRowTileMaxCols)
-        hipLaunchKernelGGL(k_row_tiles<T>, dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(kRowTileWaves * kWave), row_tile_lds<T>(B->cols), s,
-                           p->perm_num, p->ctl, p->ip, most_ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, B->nnz, B->cols, c_rp, c_col, c_val, looked3);
-      else
-        hipLaunchKernelGGL((k_hash<256, 11, T, true>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
-                           lds_hash_large, s, p->perm_num, p->ctl, 1, 3, p->ip, A->rowptr, A->colidx, a_val, B->rowptr,
-                           B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, B->cols, (const RecordOf*)nullptr, most_ip, looked3);
+      if (hist[2] > p->recorded)
+        hipLaunchKernelGGL((k_hash<64, 8, T, true>), dim3(grid_for(hist[2], 4, cap_small)), dim3(256), lds_hash_small, s,
+                           p->perm_num, p->ctl, 1, 2, p->ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, (int*)nullptr,
+                           c_rp, c_col, c_val, B->cols, p->recorded ? p->record_of : nullptr, 0, kOrderNotLooked);
+      if (check) other_order_rows();
+      if (rows3) {
+        if (row_tiles)
+          hipLaunchKernelGGL(k_row_tiles<T>, dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(kRowTileWaves * kWave), row_tile_lds<T>(B->cols), s,
+                             p->perm_num, p->ctl, p->ip, most_ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, B->nnz, B->cols, c_rp, c_col, c_val, looked3);
+        else
+          hipLaunchKernelGGL((k_hash<256, 11, T, true>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
+                             lds_hash_large, s, p->perm_num, p->ctl, 1, 3, p->ip, A->rowptr, A->colidx, a_val, B->rowptr,
+                             B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, B->cols, (const RecordOf*)nullptr, most_ip, looked3);
+      }
     }
   }
   if (hist[4]) {
