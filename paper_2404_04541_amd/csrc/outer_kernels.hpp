@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void k_outer_count(int64_t na, const int32_t* 
 constexpr int kInsertTile = 4096;
 constexpr int kInsertCols = 2048;
 template <typename T>
-__global__ __launch_bounds__(kSortThreads) void k_outer_insert(int64_t t0, int64_t n, int64_t per_range, int bits, int64_t na, const long long* __restrict__ off,
+__global__ __launch_bounds__(kSortThreads) void k_outer_insert(int64_t t0, int64_t n, int64_t per_range, int shift, int bits, int64_t na, const long long* __restrict__ off,
                                                       const int32_t* __restrict__ match, const int64_t* __restrict__ a_ptr,
                                                       const int32_t* __restrict__ a_idx, const T* __restrict__ a_val,
                                                       const int64_t* __restrict__ b_ptr, const int32_t* __restrict__ b_idx,
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kSortThreads) void k_outer_insert(int64_t t0, int64
       const unsigned long long key = ((unsigned long long)(unsigned)a_idx[pa] << col_bits) | (unsigned)b_idx[pb];
       keys[x] = key;
       vals[x] = (double)a_val[pa] * (double)b_val[pb];
-      atomicAdd(&mine[(unsigned)key & mask], 1u);
+      atomicAdd(&mine[(unsigned)(key >> shift) & mask], 1u);
     }
   }
   sort_hist_out(cnt, 1 << bits, blockIdx.x, gridDim.x, hist);

@@ -4,6 +4,7 @@
 // One pass over a digit of at most 8 bits:
 //   k_sort_hist     entries per digit of every range of consecutive entries (at most kSortMaxRanges ranges)
 //   k_sort_scan     exclusive scan over the ranges, one workgroup per digit
+//   (the last bits of long keys: k_sort_buckets)
 //   k_sort_scatter  a workgroup walks its range tile by tile: ranks its entries (ballots inside a wave,
 //                   counters per wave in LDS), puts the tile into digit order in LDS and writes every
 //                   digit's entries as one run
@@ -20,6 +21,7 @@
 #pragma once
 #include "common.hpp"
 #include "sort_shape.hpp"
+#include "share_sort.hpp"
 
 namespace spg {
 
@@ -223,6 +225,126 @@ __device__ __forceinline__ int64_t wave_first_not(int64_t n, F before) {
     hi = lo + step - 1 < hi ? lo + step - 1 : hi;
   }
   return lo;
+}
+
+// Keys that the passes have sorted by their upper bits (key >> low) are sorted by all, with their payloads: a wave takes a bucket of at most
+// kBucketWave entries with the same upper bits, the workgroup one of at most kBucketGroup.  An entry's lower bits and its place in the bucket make one
+// word, so that a sort of distinct words (registers, lane_sort; sort_shares) is a stable one of the entries; the words then say
+// where payloads come from.  *too_long is set where a bucket has more entries, and its entries are left out: the caller sorts again by passes alone.
+// Bound: the loads that find a bucket (three to five that wait for each other), then the network and memory.  16.8 M components of 36 bits: three passes
+// of 188 us each with their counts | one of these kernels 135 to 150 us (166 to 210 with a search of all keys, 64 probes a round, for either end); 10^7
+// tensor entries of 33 bits 345 | 118 us; 200 003 entries, whole call 281 | 262 us.
+constexpr int kBucketWave = 512;
+constexpr int kBucketGroup = 2048;
+template <typename P>
+struct BucketLds {
+  P pay[kBucketGroup];
+  int words[kBucketGroup];
+  int64_t begin[5];
+};
+
+template <typename K, typename P>
+__global__ __launch_bounds__(256) void k_sort_buckets(int64_t n, int64_t buckets, int low, const K* __restrict__ keys, const P* __restrict__ pay, K* __restrict__ keys_out,
+                                                      P* __restrict__ pay_out, int32_t* __restrict__ col_out, K col_mask, int* __restrict__ too_long) {
+  __shared__ BucketLds<P> lds;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
+  const int64_t b0 = (int64_t)blockIdx.x * 4;
+  {
+    // Where the wave's bucket begins and where it ends: half of the lanes look for either, 32 probes a round.  First around the place where it is if the
+    // keys are spread evenly up to the largest (a round of loads less, mostly two), otherwise everywhere.
+    const int64_t b = b0 + wave + (lane >> 5);
+    const int probe = lane & 31;
+    auto before = [&](int64_t p) { return (int64_t)(keys[p] >> low) < b; };
+    auto held_of = [&](bool held) { const unsigned long long m = __ballot(held); return __popc((unsigned)(lane < 32 ? m : m >> 32)); };
+    constexpr int64_t kNear = 256;
+    const int64_t guess = (int64_t)((double)b * ((double)n / ((double)(int64_t)(keys[n - 1] >> low) + 1.0))) + (probe - 16) * kNear;
+    const int64_t near = guess < 0 ? 0 : (guess < n ? guess : n - 1);
+    const int held = held_of(before(near));
+    const int src = (lane & 32) + (held > 0 ? held - 1 : 0), dst = (lane & 32) + (held < 32 ? held : 31);
+    int64_t lo = __shfl((long long)near, src, kWave) + 1, hi = __shfl((long long)near, dst, kWave);   // the first position that is not before is in [lo, hi]
+    if (held == 0) lo = 0;
+    if (held == 32) hi = n;
+    if (lo > hi) lo = hi;
+    while (__any(lo < hi)) {
+      const int64_t step = (hi - lo + 31) / 32;
+      const int64_t at = lo + (probe + 1) * step - 1;   // (every lane's stretch ends with its probe)
+      const int64_t n_held = held_of(lo < hi && at < hi && before(at));
+      if (lo < hi) {
+        lo += n_held * step;
+        if (lo > hi) lo = hi;
+        hi = lo + step - 1 < hi ? lo + step - 1 : hi;
+      }
+    }
+    if ((lane & 31) == 0 && (lane == 0 || wave == 3)) lds.begin[wave + (lane >> 5)] = lo;
+  }
+  __syncthreads();
+  const K low_mask = (K)(((K)1 << low) - 1);
+  // entry `at` of bucket b goes where its word stands
+  auto put = [&](int64_t b, int64_t to, unsigned word, int place_bits, P v) {
+    const K k = ((K)b << low) | (K)(word >> place_bits);
+    keys_out[to] = k;
+    pay_out[to] = v;
+    if (col_out) col_out[to] = (int32_t)(k & col_mask);
+  };
+  {
+    const int64_t from = lds.begin[wave];
+    const int count = lds.begin[wave + 1] - from <= kBucketWave ? (int)(lds.begin[wave + 1] - from) : 0;
+    P* w_pay = lds.pay + wave * kBucketWave;
+    int* w_words = lds.words + wave * kBucketWave;
+    constexpr int kPlaceBits = 9;
+    auto sort = [&](auto per_lane) {
+      constexpr int kPer = decltype(per_lane)::value;
+      unsigned word[kPer];
+      P v[kPer];
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        const int t = q * kWave + lane;
+        const bool on = t < count;
+        const K k = on ? keys[from + t] : K(0);
+        v[q] = on ? pay[from + t] : P(0);
+        word[q] = on ? ((unsigned)(k & low_mask) << kPlaceBits) | (unsigned)t : ~0u;
+      }
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) w_pay[q * kWave + lane] = v[q];
+      lane_sort<kPer * kWave, kPer>(word, lane);
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) w_words[lane * kPer + q] = (int)word[q];
+      wave_sync_lds();
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        const int t = q * kWave + lane;
+        if (t < count) {
+          const unsigned w = (unsigned)w_words[t];
+          put(b0 + wave, from + t, w, kPlaceBits, w_pay[w & (kBucketWave - 1)]);
+        }
+      }
+    };
+    if (count > 4 * kWave) sort(std::integral_constant<int, 8>{});
+    else if (count > 2 * kWave) sort(std::integral_constant<int, 4>{});
+    else if (count > 0) sort(std::integral_constant<int, 2>{});
+  }
+  for (int w = 0; w < 4; ++w) {
+    const int64_t from = lds.begin[w], count = lds.begin[w + 1] - from;   // (the same for the workgroup)
+    if (count <= kBucketWave) continue;
+    if (count > kBucketGroup) {
+      if (threadIdx.x == 0) *too_long = 1;
+      continue;
+    }
+    constexpr int kPlaceBits = 11;
+    static_assert(kBucketBits + kPlaceBits < 32 && kBucketGroup == 1 << kPlaceBits, "lower bits and place make a word");
+    __syncthreads();   // (the waves' buckets, or the long one before, have left LDS)
+    for (int t = threadIdx.x; t < kBucketGroup; t += 256) {
+      const bool on = t < (int)count;
+      lds.words[t] = on ? (int)(((unsigned)(keys[from + t] & low_mask) << kPlaceBits) | (unsigned)t) : -1;
+      if (on) lds.pay[t] = pay[from + t];
+    }
+    __syncthreads();
+    sort_shares<256, kBucketGroup / 256>(lds.words, (int)count);
+    for (int t = threadIdx.x; t < (int)count; t += 256) {
+      const unsigned word = (unsigned)lds.words[t];
+      put(b0 + w, from + t, word, kPlaceBits, lds.pay[word & (kBucketGroup - 1)]);
+    }
+  }
 }
 
 // ptr[r] = first position of the sorted keys whose high part (key >> shift) is r or more (r = 0 .. rows).  A workgroup takes

@@ -37,6 +37,27 @@ inline SortShape sort_shape(int64_t n, int nbits, int first_bit = 0) {
   return sh;
 }
 
+// Sorts of many bits: passes over the upper ones only, as many as leave kBucketMean entries on average with the same ones, and such a bucket is then
+// sorted by its lower bits at once (k_sort_buckets).  That is one pass in place of all over the lower bits: where it saves two at least.
+constexpr int kBucketMean = 192;
+constexpr int kBucketBits = 20;     // lower bits at most: with an entry's place (11 bits) they make a word that is not the largest
+struct SortPlan {
+  SortShape sh;
+  int low;   // lower bits left to the buckets (0: the passes sort by all)
+};
+inline SortPlan sort_plan(int64_t n, int nbits, bool plain) {
+  SortPlan p{sort_shape(n, nbits), 0};
+  if (plain) return p;
+  int top = 1;
+  while (top < 24 && ((int64_t)kBucketMean << top) < n) ++top;
+  if (top > 16 && ((int64_t)kBucketMean << 16) * 3 / 2 >= n) top = 16;   // (a third pass is not worth buckets of less than 288)
+  if (top < nbits - kBucketBits) top = nbits - kBucketBits;
+  if ((top + 7) / 8 + 2 > p.sh.passes || top > 24 || ((int64_t)1 << top) > n / 16 + 1024) return p;   // (a wave for every bucket, empty ones too)
+  p.low = nbits - top;
+  p.sh = sort_shape(n, top, p.low);
+  return p;
+}
+
 // Counters of sorts of up to n entries: one per digit value and range, and the digits' totals.  The number of ranges does not
 // grow with n throughout, so the room is for as many ranges as any smaller sort takes.
 constexpr size_t sort_counter_bytes(int64_t n) {

@@ -1149,8 +1149,8 @@ int check_tensor(spgemm_context* h, int mode, int64_t I, int64_t J, int64_t K, i
   return SPGEMM_OK;
 }
 
-__global__ void k_clear_int(int* p) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0;
+__global__ void k_clear_ints(int* p) {   // two of them
+  if (threadIdx.x < 2 && blockIdx.x == 0) p[threadIdx.x] = 0;
 }
 
 int bits_of(int64_t n) {   // bits that hold 0 .. n-1
@@ -1161,23 +1161,31 @@ int bits_of(int64_t n) {   // bits that hold 0 .. n-1
 
 // Stable radix sort of n (key, payload) pairs.  keys[0] holds the keys; the payloads start in pay_in and end in pay_a (pay_b is
 // the other buffer; pay_in may be the one of the two that the first pass does not write).  first_counted: the first digit's
-// counts are in `counters` already.  Returns which of the two key buffers holds the result.
+// counts are in `counters` already.  low: bits that the passes leave to k_sort_buckets, which may set *too_long: then the result is none, and the
+// caller begins again without.  Returns which of the two key buffers holds the result.
 template <typename K, typename P>
 int sort_pairs(spgemm_context* h, int64_t n, const SortShape& sh, K* const keys[2], const P* pay_in, P* pay_a, P* pay_b, unsigned* counters,
-               bool first_counted, int32_t* col_out, K col_mask) {
+               bool first_counted, int32_t* col_out, K col_mask, int low = 0, int* too_long = nullptr) {
   hipStream_t s = h->stream;
   unsigned* hist = counters + kSortBins;
+  const int steps = sh.passes + (low > 0 ? 1 : 0);
   int cur = 0;
   for (int pass = 0; pass < sh.passes; ++pass) {
     const int shift = sh.first_bit + pass * sh.bits;
-    const bool last = pass + 1 == sh.passes;
-    P* out = (sh.passes - 1 - pass) % 2 == 0 ? pay_a : pay_b;
+    const bool last = pass + 1 == steps;
+    P* out = (steps - 1 - pass) % 2 == 0 ? pay_a : pay_b;
     if (pass > 0 || !first_counted)
       hipLaunchKernelGGL(k_sort_hist<K>, dim3(sh.ranges), dim3(kSortThreads), 0, s, n, sh.per_range, shift, sh.bits, keys[cur], hist);
     hipLaunchKernelGGL(k_sort_scan, dim3(1u << sh.bits), dim3(256), 0, s, sh.ranges, hist, counters);
     hipLaunchKernelGGL((sh.per_range <= kScatterThreads * kSortFewItems ? k_sort_scatter<K, P, kSortFewItems> : k_sort_scatter<K, P, kSortItems>), dim3(sh.ranges), dim3(kScatterThreads), 0, s, n, sh.per_range, shift, sh.bits, keys[cur], pay_in, hist,
                        counters, keys[1 - cur], out, last ? col_out : (int32_t*)nullptr, col_mask);
     pay_in = out;
+    cur = 1 - cur;
+  }
+  if (low > 0) {
+    const int64_t buckets = (int64_t)1 << (sh.passes * sh.bits);   // (the passes may have sorted by a bit or two above the keys')
+    hipLaunchKernelGGL((k_sort_buckets<K, P>), dim3((unsigned)ceil_div(buckets, 4)), dim3(256), 0, s, n, buckets, low, keys[cur], pay_in, keys[1 - cur], pay_a, col_out,
+                       col_mask, too_long);
     cur = 1 - cur;
   }
   return cur;
@@ -1195,24 +1203,26 @@ UnfoldTmp unfold_tmp_layout(int64_t nnz) {
   t.o_k1 = off; off = align_up(off + (size_t)nnz * 8);
   t.o_v = off; off = align_up(off + (size_t)nnz * 8);
   t.o_h = off; off = align_up(off + sort_counter_bytes(nnz));
-  t.o_bad = off; off = align_up(off + 4);
+  t.o_bad = off; off = align_up(off + 8);   // (and whether a bucket of the sort was too long)
   t.bytes = off;
   return t;
 }
 
 template <typename K, typename T>
 void unfold_launch(spgemm_context* h, const ModeView& v, int64_t nnz, const T* xval, unsigned char* tmp, const UnfoldTmp& lay, int col_bits,
-                   int row_bits, int64_t* rp, int32_t* col, T* val) {
+                   int row_bits, bool plain, int64_t* rp, int32_t* col, T* val) {
   hipStream_t s = h->stream;
   const int64_t rows = v.A * v.B;
   K* keys[2] = {reinterpret_cast<K*>(tmp + lay.o_k0), reinterpret_cast<K*>(tmp + lay.o_k1)};
   unsigned* counters = reinterpret_cast<unsigned*>(tmp + lay.o_h);
   int cur = 0;
   if (nnz > 0) {
-    const SortShape sh = sort_shape(nnz, col_bits + row_bits);
-    hipLaunchKernelGGL(k_tensor_keys<K>, dim3(sh.ranges), dim3(kSortThreads), 0, s, nnz, sh.per_range, v.A, v.B, v.C, col_bits, sh.bits, v.xa, v.xb,
-                       v.xc, keys[0], counters + kSortBins, reinterpret_cast<int*>(tmp + lay.o_bad));
-    cur = sort_pairs<K, T>(h, nnz, sh, keys, xval, val, reinterpret_cast<T*>(tmp + lay.o_v), counters, true, col, (K)(((K)1 << col_bits) - 1));
+    const SortPlan plan = sort_plan(nnz, col_bits + row_bits, plain);
+    const SortShape& sh = plan.sh;
+    int* flags = reinterpret_cast<int*>(tmp + lay.o_bad);
+    hipLaunchKernelGGL(k_tensor_keys<K>, dim3(sh.ranges), dim3(kSortThreads), 0, s, nnz, sh.per_range, v.A, v.B, v.C, col_bits, sh.first_bit, sh.bits, v.xa, v.xb,
+                       v.xc, keys[0], counters + kSortBins, flags);
+    cur = sort_pairs<K, T>(h, nnz, sh, keys, xval, val, reinterpret_cast<T*>(tmp + lay.o_v), counters, true, col, (K)(((K)1 << col_bits) - 1), plan.low, flags + 1);
   }
   hipLaunchKernelGGL(k_key_ptr<K>, dim3((unsigned)ceil_div(rows + 1, kPtrRows)), dim3(256), 0, s, nnz, rows, col_bits, keys[cur], rp);
 }
@@ -1223,22 +1233,25 @@ int unfold_run(spgemm_context* h, const ModeView& v, int64_t nnz, const void* xv
                int64_t* rp, int32_t* col, void* val) {
   hipStream_t s = h->stream;
   int* bad = reinterpret_cast<int*>(tmp + lay.o_bad);
-  int host_bad = 0;
-  hipLaunchKernelGGL(k_clear_int, dim3(1), dim3(64), 0, s, bad);
   const int col_bits = bits_of(v.C), row_bits = bits_of(v.A * v.B);
   const bool narrow = col_bits + row_bits <= 32;
-  if (dtype == SPGEMM_F32) {
-    if (narrow) unfold_launch<uint32_t>(h, v, nnz, static_cast<const float*>(xval), tmp, lay, col_bits, row_bits, rp, col, static_cast<float*>(val));
-    else unfold_launch<unsigned long long>(h, v, nnz, static_cast<const float*>(xval), tmp, lay, col_bits, row_bits, rp, col, static_cast<float*>(val));
-  } else {
-    if (narrow) unfold_launch<uint32_t>(h, v, nnz, static_cast<const double*>(xval), tmp, lay, col_bits, row_bits, rp, col, static_cast<double*>(val));
-    else unfold_launch<unsigned long long>(h, v, nnz, static_cast<const double*>(xval), tmp, lay, col_bits, row_bits, rp, col, static_cast<double*>(val));
+  int flags[2] = {0, 0};   // a coordinate out of range; a bucket of the sort too long
+  for (int plain = 0; plain < 2; ++plain) {
+    hipLaunchKernelGGL(k_clear_ints, dim3(1), dim3(64), 0, s, bad);
+    if (dtype == SPGEMM_F32) {
+      if (narrow) unfold_launch<uint32_t>(h, v, nnz, static_cast<const float*>(xval), tmp, lay, col_bits, row_bits, plain != 0, rp, col, static_cast<float*>(val));
+      else unfold_launch<unsigned long long>(h, v, nnz, static_cast<const float*>(xval), tmp, lay, col_bits, row_bits, plain != 0, rp, col, static_cast<float*>(val));
+    } else {
+      if (narrow) unfold_launch<uint32_t>(h, v, nnz, static_cast<const double*>(xval), tmp, lay, col_bits, row_bits, plain != 0, rp, col, static_cast<double*>(val));
+      else unfold_launch<unsigned long long>(h, v, nnz, static_cast<const double*>(xval), tmp, lay, col_bits, row_bits, plain != 0, rp, col, static_cast<double*>(val));
+    }
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(flags, bad, 8, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return fail(h, SPGEMM_HIP_ERROR, std::string("unfolding: ") + hipGetErrorString(e));
+    if (flags[0]) return fail(h, SPGEMM_INVALID_INPUT, "a tensor coordinate is outside its mode's range");
+    if (!flags[1]) break;
   }
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipMemcpyAsync(&host_bad, bad, 4, hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) return fail(h, SPGEMM_HIP_ERROR, std::string("unfolding: ") + hipGetErrorString(e));
-  if (host_bad) return fail(h, SPGEMM_INVALID_INPUT, "a tensor coordinate is outside its mode's range");
   return SPGEMM_OK;
 }
 
@@ -1602,7 +1615,8 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
   unsigned long long* keys[2] = {bufs.get<unsigned long long>((size_t)cap), bufs.get<unsigned long long>((size_t)cap)};
   double* vals[2] = {bufs.get<double>((size_t)cap), bufs.get<double>((size_t)cap)};
   unsigned* counters = bufs.get<unsigned>(sort_counter_bytes(cap) / 4);   // (the last batch is shorter and may take more ranges)
-  if (!keys[0] || !keys[1] || !vals[0] || !vals[1] || !counters) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the accumulation array failed");
+  int* too_long = bufs.get<int>(2);
+  if (!keys[0] || !keys[1] || !vals[0] || !vals[1] || !counters || !too_long) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the accumulation array failed");
   // all array: sorted, unique coordinates with their sums
   unsigned long long* all_k = nullptr;
   double* all_v = nullptr;
@@ -1628,24 +1642,42 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
     HIP_TRY(h, hipStreamSynchronize(s));
     return SPGEMM_OK;
   };
+  bool plain_sorts = false;
   for (long long t0 = 0; t0 < total; t0 += cap) {
     const int64_t cnt = total - t0 < cap ? total - t0 : cap;
     const bool last = t0 + cap >= total;
-    // insert
-    const SortShape sh = sort_shape(cnt, col_bits + bits_of(m));
-    hipLaunchKernelGGL(k_outer_insert<T>, dim3(sh.ranges), dim3(kSortThreads), 0, s, (int64_t)t0, cnt, sh.per_range, sh.bits, na, off, match, A->ptr, A->idx,
-                       static_cast<const T*>(A->values), B->ptr, B->idx, static_cast<const T*>(B->values), col_bits, keys[0], vals[0], counters + kSortBins);
-    // sort
-    double* const sorted = vals[sh.passes & 1];
-    const int cur = sort_pairs<unsigned long long, double>(h, cnt, sh, keys, vals[0], sorted, vals[1 - (sh.passes & 1)], counters, true, nullptr, 0ULL);
+    double* sorted = nullptr;
+    int cur = 0;
+    auto insert_and_sort = [&](bool plain) {
+      const SortPlan plan = sort_plan(cnt, col_bits + bits_of(m), plain);
+      const SortShape& sh = plan.sh;
+      hipLaunchKernelGGL(k_clear_ints, dim3(1), dim3(64), 0, s, too_long);
+      // insert
+      hipLaunchKernelGGL(k_outer_insert<T>, dim3(sh.ranges), dim3(kSortThreads), 0, s, (int64_t)t0, cnt, sh.per_range, sh.first_bit, sh.bits, na, off, match, A->ptr, A->idx,
+                         static_cast<const T*>(A->values), B->ptr, B->idx, static_cast<const T*>(B->values), col_bits, keys[0], vals[0], counters + kSortBins);
+      // sort
+      const int steps = sh.passes + (plan.low > 0 ? 1 : 0);
+      sorted = vals[steps & 1];
+      cur = sort_pairs<unsigned long long, double>(h, cnt, sh, keys, vals[0], sorted, vals[1 - (steps & 1)], counters, true, nullptr, 0ULL, plan.low, too_long);
+      return plan.low > 0;
+    };
+    const bool buckets = insert_and_sort(plain_sorts);
     // merge: equal coordinates of the batch, then the batch into the all array
     const int64_t tiles = ceil_div(cnt, kRunTile);
     unsigned* sums = bufs.get<unsigned>((size_t)tiles + 1);
     if (!sums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the merge stage failed");
     hipLaunchKernelGGL(k_run_count, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sums);
     unsigned uniq = 0;
-    int rc = total_of(tiles, sums, &uniq);
+    int rc = SPGEMM_OK, long_bucket = 0;
+    if (buckets) HIP_TRY(h, hipMemcpyAsync(&long_bucket, too_long, 4, hipMemcpyDeviceToHost, s));
+    rc = total_of(tiles, sums, &uniq);   // (waits)
     if (rc) return rc;
+    if (long_bucket) {   // (again, and the batches after this one too, by passes alone)
+      plain_sorts = true;
+      (void)insert_and_sort(true);
+      hipLaunchKernelGGL(k_run_count, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sums);
+      if ((rc = total_of(tiles, sums, &uniq))) return rc;
+    }
     OuterOut<T> batch{};
     if ((rc = room(uniq, last && all_n == 0, &batch))) return rc;
     hipLaunchKernelGGL(k_run_sum<T>, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sorted, sums, batch);

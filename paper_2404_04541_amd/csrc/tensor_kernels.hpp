@@ -13,7 +13,7 @@ namespace spg {
 
 // A workgroup takes one range of entries of the sort: keys and the range's counts of the first digit.
 template <typename Key>
-__global__ __launch_bounds__(kSortThreads) void k_tensor_keys(int64_t nnz, int64_t per_range, int64_t I, int64_t J, int64_t K, int col_bits, int bits,
+__global__ __launch_bounds__(kSortThreads) void k_tensor_keys(int64_t nnz, int64_t per_range, int64_t I, int64_t J, int64_t K, int col_bits, int shift, int bits,
                                                               const int32_t* __restrict__ xi, const int32_t* __restrict__ xj,
                                                               const int32_t* __restrict__ xk, Key* __restrict__ keys, unsigned* __restrict__ hist,
                                                               int* __restrict__ bad) {
@@ -30,7 +30,7 @@ __global__ __launch_bounds__(kSortThreads) void k_tensor_keys(int64_t nnz, int64
     if (i < 0 || i >= I || j < 0 || j >= J || k < 0 || k >= K) *bad = 1;
     else key = ((Key)((long long)i * J + j) << col_bits) | (Key)(unsigned)k;
     keys[p] = key;
-    atomicAdd(&mine[(unsigned)key & mask], 1u);
+    atomicAdd(&mine[(unsigned)(key >> shift) & mask], 1u);
   }
   sort_hist_out(cnt, 1 << bits, blockIdx.x, gridDim.x, hist);
 }

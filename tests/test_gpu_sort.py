@@ -42,6 +42,52 @@ def test_unfolding_at_the_edges_of_the_sort(n, shape):
         assert np.array_equal(got.values.cpu().numpy(), x.values[order])
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n,shape,crowd", [
+    (200_003, (301, 997, 703), 0),          # two passes and buckets of some 50 entries
+    (3_000_000, (600, 700, 900), 0),        # buckets of one wave's registers of four
+    (12_600_000, (2000, 2000, 2000), 0),    # of eight
+    (3_000_000, (600, 700, 900), 700),      # some buckets of one workgroup
+    (3_000_000, (600, 700, 900), 3000),     # and some that are too long: sorted again by passes alone
+    (3_000_000, (8, 8, 900), 0),            # (too few bits for buckets)
+])
+def test_buckets_of_the_sort(n, shape, crowd, dtype):
+    import torch
+    from paper_2404_04541_amd import binding as sg
+    g = torch.Generator(device="cuda").manual_seed(n + crowd)
+    c = [torch.randint(e, (n,), device="cuda", generator=g) for e in shape]
+    if crowd:   # so many entries more in each of a few rows, in few columns: repeated coordinates, which stay in their order
+        at = torch.randperm(n, device="cuda", generator=g)[:crowd * 5]
+        for d in range(3): c[d][at] = torch.randint(5 if d < 2 else 40, (1,), device="cuda", generator=g) if d < 2 else torch.randint(40, (crowd * 5,), device="cuda", generator=g)
+        c[1][at] = torch.arange(crowd * 5, device="cuda") % 5 * 17
+    v = torch.rand(n, dtype=torch.float64, device="cuda", generator=g).to(torch.float32 if dtype == np.float32 else torch.float64)
+    got = sg.sptensor_unfold(sg.Handle(), 3, shape, *[x.to(torch.int32) for x in c], v)
+    row = c[0] * shape[1] + c[1]
+    order = torch.sort(row * shape[2] + c[2], stable=True).indices
+    assert torch.equal(got.colidx.long(), c[2][order]) and torch.equal(got.values, v[order])
+    assert torch.equal(got.rowptr, torch.searchsorted(row[order], torch.arange(shape[0] * shape[1] + 1, device="cuda")))
+
+
+@pytest.mark.parametrize("hub", [0, 1500, 4000])
+def test_outer_product_with_a_crowded_row(hub):
+    """One row of A with so many entries more, times rows of B in few columns: its products are one bucket, or too many for one."""
+    from oracle import spgemm as reference
+    from paper_2404_04541_amd import binding as sg
+    rng = np.random.default_rng(hub)
+    rows, k, cols = 60000, 5000, 1 << 20
+    lens = np.full(rows, 3); lens[777] += hub
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    colidx = np.concatenate([np.sort(rng.choice(k, size=n, replace=False)) for n in lens]).astype(np.int32)
+    A = W.CSR(rows, k, rowptr, colidx, W.draw_values(int(rowptr[-1]), -1.0, 1.0, np.float64, 1, 3))
+    bcol = np.concatenate([np.sort(rng.choice(cols if not hub else 500, size=4, replace=False)) for _ in range(k)]).astype(np.int32)
+    B = W.CSR(k, cols, np.arange(k + 1, dtype=np.int64) * 4, bcol, W.draw_values(4 * k, -1.0, 1.0, np.float64, 2, 3))
+    h = sg.Handle()
+    C = sg.spgemm_outer(h, sg.dcsc_from_csr(h, sg.to_device(A)), sg.dcsr_from_csr(h, sg.to_device(B)), 400_000)
+    ref = reference(A, B)
+    assert np.array_equal(C.rowptr.cpu().numpy(), ref.rowptr) and np.array_equal(C.colidx.cpu().numpy(), ref.colidx)
+    assert np.all(np.abs(C.values.cpu().numpy() - ref.values) <= 1e-12 * ref.absum)
+
+
 @pytest.mark.parametrize("rows", [1, 4095, 4096, 4097, 4096 * 4096 + 3])
 def test_doubly_compressed_rows_at_the_edges_of_the_scan(rows):
     import torch
