@@ -551,4 +551,78 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_final(int64_t m, int64_t 
   }
 }
 
+// ---- row blocks of about equal work -----------------------------------------------------
+// Sums of the tiles' weights: a row's products and one (rows without products still cost a little).
+__global__ __launch_bounds__(kScanThreads) void k_weight_sums(int64_t m, const int* __restrict__ ip, unsigned long long* __restrict__ sums) {
+  __shared__ unsigned long long part[kScanWaves];
+  unsigned long long s = 0;
+#pragma unroll
+  for (int u = 0; u < kScanItems; ++u) {
+    const int64_t i = tile_row(u);
+    if (i < m) s += (unsigned)ip[i] + 1ULL;
+  }
+  s = wave_sum64(s);
+  if (lane_id() == 0) part[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kScanWaves; ++w) s += part[w];
+    sums[blockIdx.x] = s;
+  }
+}
+
+// first[t] = rows of the blocks before block t (t = 1 .. blocks - 1): the first boundary that has t / blocks of the whole weight in front of it; first[blocks + 1] = the
+// whole weight.  sums: of the tiles, exclusive afterwards.  One workgroup; a wave a boundary.
+// Bound by the chain of dependent loads.  (All rows' products copied to the host and added up there: an R-MAT graph of scale 17 in four blocks 6.30 ms | with
+// these kernels 6.16; scale 16 in eight, fp64, 3.79 | 3.72; scale 12 in two 0.544 | 0.535.)
+__global__ __launch_bounds__(kScanThreads) void k_block_rows(int64_t m, int64_t tiles, int blocks, const int* __restrict__ ip, unsigned long long* __restrict__ sums,
+                                                             long long* __restrict__ first) {
+  __shared__ unsigned long long all;
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  if (wave == 0) {
+    unsigned long long run = 0;
+    for (int64_t t0 = 0; t0 < tiles; t0 += kWave) {
+      const unsigned long long v = t0 + lane < tiles ? sums[t0 + lane] : 0ULL;
+      unsigned long long incl = v;
+#pragma unroll
+      for (int d = 1; d < kWave; d <<= 1) {
+        const unsigned long long o = __shfl_up(incl, d, kWave);
+        if (lane >= d) incl += o;
+      }
+      if (t0 + lane < tiles) sums[t0 + lane] = run + incl - v;
+      run += __shfl(incl, kWave - 1, kWave);
+    }
+    if (lane == 0) all = run;
+  }
+  __threadfence();
+  __syncthreads();
+  const double total = (double)all;
+  if (threadIdx.x == 0) first[blocks + 1] = (long long)all;
+  for (int t = 1 + wave; t < blocks; t += kScanWaves) {
+    const double want = total * t / blocks;
+    int64_t lo = 0, hi = tiles;   // the last tile with less in front of it
+    while (hi - lo > 1) {
+      const int64_t mid = (lo + hi) >> 1;
+      if ((double)__hip_atomic_load(&sums[mid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < want) lo = mid; else hi = mid;
+    }
+    unsigned long long run = __hip_atomic_load(&sums[lo], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    long long at = m;
+    for (int64_t i0 = lo * kScanTile; i0 < m; i0 += kWave) {   // (a step beyond the tile at most)
+      const int64_t i = i0 + lane;
+      unsigned long long incl = i < m ? (unsigned)ip[i] + 1ULL : 0ULL;
+#pragma unroll
+      for (int d = 1; d < kWave; d <<= 1) {
+        const unsigned long long o = __shfl_up(incl, d, kWave);
+        if (lane >= d) incl += o;
+      }
+      const unsigned long long there = __ballot(i < m && (double)(run + incl) >= want);
+      if (there) {
+        at = i0 + __ffsll((long long)there);
+        break;
+      }
+      run += __shfl(incl, kWave - 1, kWave);
+    }
+    if (lane == 0) first[t] = at;
+  }
+}
+
 }  // namespace spg

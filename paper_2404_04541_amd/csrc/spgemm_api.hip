@@ -1394,43 +1394,40 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
   if ((rc = ensure_device(h))) return rc;
   const int64_t m = A->rows;
   for (int t = 0; t < nblocks; ++t) std::memset(&C_blocks[t], 0, sizeof(spgemm_csr));
-  // 1. products per row of the whole A (the count kernel), their prefix on the host, block boundaries of equal work
-  std::vector<int> ip_host((size_t)m);
-  {
+  // 1. products per row of the whole A (the count kernel), block boundaries of equal work
+  double total = 0;
+  for (int t = 0; t <= nblocks; ++t) block_rows[t] = t == 0 ? 0 : m;
+  if (m > 0) {
+    const int64_t tiles = ceil_div(m, kScanTile);
     size_t off = 0;
     const size_t o_ctl = off; off = align_up(off + sizeof(Control));
+    const size_t o_first = off; off = align_up(off + (size_t)(nblocks + 2) * 8);
+    const size_t o_sums = off; off = align_up(off + (size_t)tiles * 8);
     const size_t o_ip = off; off = align_up(off + (size_t)m * 4);
     const size_t o_cnt = off; off = align_up(off + (size_t)m * 4);
     const size_t o_bin = off; off = align_up(off + (size_t)m);
     unsigned char* tmp = static_cast<unsigned char*>(dev_alloc(h, off));
     if (!tmp) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the row-block planning failed");
     Control* ctl = reinterpret_cast<Control*>(tmp + o_ctl);
+    int* ip = reinterpret_cast<int*>(tmp + o_ip);
+    unsigned long long* sums = reinterpret_cast<unsigned long long*>(tmp + o_sums);
     Control host{};
+    std::vector<long long> first((size_t)nblocks + 2);
     const int chunk = count_chunk(h, m);
     hipLaunchKernelGGL(k_init_control, dim3(1), dim3(kCountThreads), 0, h->stream, ctl, m, A->rowptr, chunk, h->num_cus);
-    if (m > 0)
-      hipLaunchKernelGGL(k_count_rows, dim3(grid_for(m, chunk, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, h->stream, 0, B->cols, B->nnz, B->colidx, m,
-                         A->nnz, B->rows, A->rowptr, A->colidx, B->rowptr, reinterpret_cast<int*>(tmp + o_ip), tmp + o_bin, reinterpret_cast<int*>(tmp + o_cnt), ctl, 0, 0, (unsigned long long*)nullptr);
+    hipLaunchKernelGGL(k_count_rows, dim3(grid_for(m, chunk, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, h->stream, 0, B->cols, B->nnz, B->colidx, m,
+                       A->nnz, B->rows, A->rowptr, A->colidx, B->rowptr, ip, tmp + o_bin, reinterpret_cast<int*>(tmp + o_cnt), ctl, 0, 0, (unsigned long long*)nullptr);
+    hipLaunchKernelGGL(k_weight_sums, dim3((unsigned)tiles), dim3(kScanThreads), 0, h->stream, m, ip, sums);
+    hipLaunchKernelGGL(k_block_rows, dim3(1), dim3(kScanThreads), 0, h->stream, m, tiles, nblocks, ip, sums, reinterpret_cast<long long*>(tmp + o_first));
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && m > 0) e = hipMemcpyAsync(ip_host.data(), tmp + o_ip, (size_t)m * 4, hipMemcpyDeviceToHost, h->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(first.data(), tmp + o_first, first.size() * 8, hipMemcpyDeviceToHost, h->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(&host, ctl, sizeof(Control), hipMemcpyDeviceToHost, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     dev_free(h, tmp);
     if (e != hipSuccess) return fail(h, SPGEMM_HIP_ERROR, std::string("row-block planning: ") + hipGetErrorString(e));
     if (host.error) return fail(h, SPGEMM_INVALID_INPUT, "device-side input check failed (column out of range or rowptr not monotone)");
-  }
-  double total = 0;
-  {
-    for (int64_t i = 0; i < m; ++i) total += ip_host[(size_t)i] + 1.0;   // (+1: rows without products still cost a little)
-    double run = 0;
-    int t = 1;
-    block_rows[0] = 0;
-    for (int64_t i = 0; i < m && t < nblocks; ++i) {
-      run += ip_host[(size_t)i] + 1.0;
-      while (t < nblocks && run >= total * t / nblocks) block_rows[t++] = i + 1;
-    }
-    while (t <= nblocks) block_rows[t++] = m;
-    block_rows[nblocks] = m;
+    for (int t = 1; t < nblocks; ++t) block_rows[t] = first[(size_t)t];
+    total = (double)first[(size_t)nblocks + 1];
   }
   if ((rc = ensure_big_lds(h))) return rc;   // (here, so that the copy below need not for every call)
   // 2. a second context on a stream of its own (same priority) for the symbolic phases

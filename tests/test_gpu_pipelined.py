@@ -71,3 +71,30 @@ def test_pipeline_more_blocks_than_rows_and_empty_operands():
     with pytest.raises(sg.SpgemmError) as e:
         sg.spgemm_pipelined(h, sg.to_device(A), sg.to_device(B), 0)
     assert e.value.status == -1
+
+
+# the tiles hold 4096 rows, a wave takes 64 of their sums (or of a tile's rows) at a time
+@pytest.mark.parametrize("m,nblocks", [(1, 1), (1, 3), (63, 7), (64, 64), (65, 200), (4095, 3), (4096, 4), (4097, 17), (64 * 4096 + 1, 2), (70 * 4096, 300)])
+@pytest.mark.parametrize("shape", ["even", "empty rows", "one row holds all"])
+def test_block_boundaries_share_the_work(m, nblocks, shape):
+    from paper_2404_04541_amd import binding as sg
+    rng = np.random.default_rng(m + nblocks)
+    if shape == "even":
+        d = np.ones(m, np.int64)
+    elif shape == "empty rows":
+        d = rng.integers(0, 4, m) * (rng.random(m) < 0.3)
+    else:
+        d = np.zeros(m, np.int64)
+        d[m // 2] = 50
+    rp = np.concatenate([[0], np.cumsum(d)])
+    cols = (np.arange(rp[-1]) * 7 % 50).astype(np.int32)
+    A = W.CSR(m, 50, rp, cols, np.ones(cols.size))
+    B = W.random_csr(50, 60, 5, 3)
+    ip = np.add.reduceat(np.append(np.diff(B.rowptr)[cols], 0), np.minimum(rp[:-1], cols.size)) * (d > 0)
+    weight = np.cumsum(ip + 1).astype(np.float64)
+    first = [0]
+    for t in range(1, nblocks):
+        first.append(int(np.searchsorted(weight, weight[-1] * t / nblocks)) + 1)
+    blocks, got = sg.spgemm_pipelined(sg.Handle(), sg.to_device(A), sg.to_device(B), nblocks)
+    assert list(got) == first + [m]
+    assert [b.rows for b in blocks] == list(np.diff(first + [m]))
