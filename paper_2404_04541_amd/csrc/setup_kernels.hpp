@@ -345,11 +345,12 @@ __device__ __forceinline__ int64_t tile_row(int u) {
 struct ScatterLds {
   unsigned count[kNumBins][kScanWaves], base[kNumBins], offset[kNumBins + 1];
 };
-__device__ __forceinline__ void scatter_bins(const int (&bin)[kScanItems], int* __restrict__ perm, Control* ctl, int phase, ScatterLds* sl) {
+// hist: rows of every bin, of all tiles.
+__device__ __forceinline__ void scatter_bins(const int (&bin)[kScanItems], const unsigned* hist, int* __restrict__ perm, Control* ctl, int phase, ScatterLds* sl) {
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
   if (tid == 0) {
     unsigned run = 0;
-    for (int b = 0; b < kNumBins; ++b) { sl->offset[b] = run; run += ctl->hist[phase][b]; }
+    for (int b = 0; b < kNumBins; ++b) { sl->offset[b] = run; run += hist[b]; }
     sl->offset[kNumBins] = run;
   }
   int rank[kScanItems];
@@ -398,7 +399,7 @@ __global__ __launch_bounds__(kScanThreads) void k_bin_scatter(int64_t m, const u
     bin[u] = i < m ? bin_of[i] : -1;
   }
   // (an error of the count leaves rows without a bin; the one that is set below does not matter here, whoever sees it)
-  if (ctl->error != 1) scatter_bins(bin, perm, ctl, 0, &sl);
+  if (ctl->error != 1) scatter_bins(bin, ctl->hist[0], perm, ctl, 0, &sl);
   if (blockIdx.x == 0) {
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -411,22 +412,19 @@ __global__ __launch_bounds__(kScanThreads) void k_bin_scatter(int64_t m, const u
   }
 }
 
-// Numeric classes from ip and the symbolic counts, and the sum of the counts of every tile.
-__global__ __launch_bounds__(kScanThreads) void k_classify_numeric(int64_t m, const int* __restrict__ ip, const int* __restrict__ cnt,
-                                   unsigned char* __restrict__ bin_out, long long* __restrict__ partial, Control* ctl, int force, int staged_cap) {
-  __shared__ unsigned hist[kNumBins];
-  __shared__ unsigned long long hip[kNumBins], hnz[kNumBins];
-  __shared__ unsigned long long total;
-  if (threadIdx.x < kNumBins) { hist[threadIdx.x] = 0; hip[threadIdx.x] = 0; hnz[threadIdx.x] = 0; }
-  if (threadIdx.x == 0) total = 0;
-  __syncthreads();
-  unsigned long long sum = 0;
-  int bin[kScanItems];
+// Numeric classes of a tile's rows from ip and the symbolic counts; their numbers, products and entries are added to the workgroup's (all threads together; the
+// barrier after it is the caller's).
+struct ClassLds {
+  unsigned hist[kNumBins];
+  unsigned long long ip[kNumBins], nnz[kNumBins];
+};
+__device__ __forceinline__ void classify_tile(int64_t m, const int* __restrict__ ip, const int* __restrict__ cnt, unsigned char* __restrict__ bin_out,
+                                              int force, int staged_cap, int (&bin)[kScanItems], unsigned (&c)[kScanItems], ClassLds* cl) {
+  if (threadIdx.x < kNumBins) { cl->hist[threadIdx.x] = 0; cl->ip[threadIdx.x] = 0; cl->nnz[threadIdx.x] = 0; }
   unsigned long long p[kScanItems];
-  unsigned c[kScanItems];
 #pragma unroll
   for (int u = 0; u < kScanItems; ++u) {
-    const int64_t i = (int64_t)blockIdx.x * kScanTile + u * kScanThreads + threadIdx.x;
+    const int64_t i = tile_row(u);
     bin[u] = -1;
     p[u] = 0;
     c[u] = 0;
@@ -437,22 +435,40 @@ __global__ __launch_bounds__(kScanThreads) void k_classify_numeric(int64_t m, co
   }
 #pragma unroll
   for (int u = 0; u < kScanItems; ++u) {
-    const int64_t i = (int64_t)blockIdx.x * kScanTile + u * kScanThreads + threadIdx.x;
+    const int64_t i = tile_row(u);
     if (i < m) {
       bin[u] = classify_numeric((long long)p[u], (int)c[u], force, staged_cap);
       bin_out[i] = (unsigned char)bin[u];
-      sum += c[u];
     }
   }
-  add_to_bins<kScanItems>(bin, p, c, hist, hip, hnz);
+  __syncthreads();
+  add_to_bins<kScanItems>(bin, p, c, cl->hist, cl->ip, cl->nnz);
+}
+
+__device__ __forceinline__ void report_classes(const ClassLds* cl, Control* ctl) {
+  if (threadIdx.x < kNumBins && cl->hist[threadIdx.x]) {
+    atomicAdd(&ctl->hist[1][threadIdx.x], cl->hist[threadIdx.x]);
+    atomicAdd(&ctl->bin_ip[1][threadIdx.x], cl->ip[threadIdx.x]);
+    atomicAdd(&ctl->bin_nnz[threadIdx.x], cl->nnz[threadIdx.x]);
+  }
+}
+
+// The classes, and the sum of the counts of every tile.
+__global__ __launch_bounds__(kScanThreads) void k_classify_numeric(int64_t m, const int* __restrict__ ip, const int* __restrict__ cnt,
+                                   unsigned char* __restrict__ bin_out, long long* __restrict__ partial, Control* ctl, int force, int staged_cap) {
+  __shared__ ClassLds cl;
+  __shared__ unsigned long long total;
+  if (threadIdx.x == 0) total = 0;
+  int bin[kScanItems];
+  unsigned c[kScanItems];
+  classify_tile(m, ip, cnt, bin_out, force, staged_cap, bin, c, &cl);
+  unsigned long long sum = 0;
+#pragma unroll
+  for (int u = 0; u < kScanItems; ++u) sum += c[u];
   const unsigned long long s = wave_sum64(sum);
   if (lane_id() == 0) atomicAdd(&total, s);
   __syncthreads();
-  if (threadIdx.x < kNumBins && hist[threadIdx.x]) {
-    atomicAdd(&ctl->hist[1][threadIdx.x], hist[threadIdx.x]);
-    atomicAdd(&ctl->bin_ip[1][threadIdx.x], hip[threadIdx.x]);
-    atomicAdd(&ctl->bin_nnz[threadIdx.x], hnz[threadIdx.x]);
-  }
+  report_classes(&cl, ctl);
   if (threadIdx.x == 0) partial[blockIdx.x] = (long long)total;
 }
 
@@ -492,21 +508,32 @@ __global__ __launch_bounds__(kScanBlockThreads) void k_scan_blocks(int64_t nbloc
 // 700 000; the two of now 14 and 25 us, and the control block reaches the host without a copy (two copies of 10 to 15 us each).
 // The row pointer and the lists of the numeric bins.  direct: partial holds the sums of the tiles (at most kScanDirect), of
 // which every workgroup adds up its own share; otherwise their exclusive prefix (k_scan_blocks).
+// ONE: a single tile.  Its workgroup needs nobody else's numbers and classifies its rows itself: one launch instead of two (whole calls, us: 1000 rows of
+// 10 x 10 88.6 | 87.0, 4096 rows 90.9 | 88.1, R-MAT scale 12 197 | 195, 27-point stencil of 12^3 rows 109 | 106).
+template <bool ONE>
 __global__ __launch_bounds__(kScanThreads) void k_scan_final(int64_t m, int64_t tiles, int direct, const int* __restrict__ cnt, const long long* __restrict__ partial,
-                                                             const unsigned char* __restrict__ bin_of, int* __restrict__ perm,
-                                                             int64_t* __restrict__ rowptr, Control* ctl, Control* host) {
+                                                             const int* __restrict__ ip, int force, int staged_cap, unsigned char* __restrict__ bin_of,
+                                                             int* __restrict__ perm, int64_t* __restrict__ rowptr, Control* ctl, Control* host) {
   __shared__ ScatterLds sl;
+  __shared__ ClassLds cl;
   __shared__ unsigned long long before, all;
   __shared__ long long waves[kScanWaves];
   const int tid = threadIdx.x;
   if (tid == 0) { before = 0; all = 0; }
   int v[kScanItems], bin[kScanItems];
   long long excl[kScanItems], s = 0;   // entries of the wave's rows before a row, and of all its rows
+  if (ONE) {
+    unsigned c[kScanItems];
+    classify_tile(m, ip, cnt, bin_of, force, staged_cap, bin, c, &cl);
 #pragma unroll
-  for (int u = 0; u < kScanItems; ++u) {
-    const int64_t i = tile_row(u);
-    v[u] = i < m ? cnt[i] : 0;
-    bin[u] = i < m ? bin_of[i] : -1;
+    for (int u = 0; u < kScanItems; ++u) v[u] = (int)c[u];
+  } else {
+#pragma unroll
+    for (int u = 0; u < kScanItems; ++u) {
+      const int64_t i = tile_row(u);
+      v[u] = i < m ? cnt[i] : 0;
+      bin[u] = i < m ? bin_of[i] : -1;
+    }
   }
 #pragma unroll
   for (int u = 0; u < kScanItems; ++u) {
@@ -520,7 +547,9 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_final(int64_t m, int64_t 
     }
   }
   __syncthreads();
-  if (direct) {
+  if (ONE) {
+    report_classes(&cl, ctl);
+  } else if (direct) {
     unsigned long long b = 0, a = 0;
     for (int64_t t = tid; t < tiles; t += kScanThreads) {
       if (t >= (int64_t)blockIdx.x && blockIdx.x != 0) break;   // (the first workgroup wants the total)
@@ -544,9 +573,10 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_final(int64_t m, int64_t 
     const int64_t i = tile_row(u);
     if (i < m) rowptr[i] = run + excl[u];
   }
-  scatter_bins(bin, perm, ctl, 1, &sl);
+  scatter_bins(bin, ONE ? cl.hist : ctl->hist[1], perm, ctl, 1, &sl);
+  if (ONE && tid == kScanThreads - 1) { rowptr[m] = run + s; ctl->nnz_c = run + s; }
   if (blockIdx.x == 0) {
-    if (direct && tid == 0) { rowptr[m] = (int64_t)all; ctl->nnz_c = (long long)all; }
+    if (!ONE && direct && tid == 0) { rowptr[m] = (int64_t)all; ctl->nnz_c = (long long)all; }
     control_out(ctl, host);
   }
 }

@@ -667,7 +667,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
       hipLaunchKernelGGL((d.waves == 8 ? k_sym_dense<8, false> : B->cols > kSymNarrowCols ? k_sym_dense<16, true> : k_sym_dense<16, false>), dim3(d.groups), dim3(d.waves * kWave), d.lds, s, p->perm_sym, p->ctl, A->rowptr, A->colidx, B->rowptr, B->colidx, B->cols, p->ip, p->cnt, p->tiles, p->runs, p->col_list, h->direct_min,
                          staged, h->search_ratio, p->blk_ptr, p->blk_ptr_cols, B->nnz, run_tiles_of(h, rows_dense), p->wide_tiles ? 1 : 0);
     }
-    {
+    if (p->scan_blocks > 1) {
       Timer t(h, SPGEMM_K_BIN);
       hipLaunchKernelGGL(k_classify_numeric, dim3((unsigned)p->scan_blocks), dim3(kScanThreads), 0, s, m, p->ip, p->cnt, p->bin, p->partial, p->ctl,
                          h->force, staged);
@@ -677,8 +677,8 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     Timer t(h, SPGEMM_K_SCAN);
     const int direct = p->scan_blocks <= kScanDirect ? 1 : 0;
     if (!direct) hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanBlockThreads), 0, s, p->scan_blocks, p->partial, m, c_rowptr, p->ctl);
-    hipLaunchKernelGGL(k_scan_final, dim3(p->scan_blocks > 0 ? (unsigned)p->scan_blocks : 1u), dim3(kScanThreads), 0, s, m, p->scan_blocks, direct, p->cnt,
-                       p->partial, p->bin, p->perm_num, c_rowptr, p->ctl, pinned);
+    hipLaunchKernelGGL((p->scan_blocks == 1 ? k_scan_final<true> : k_scan_final<false>), dim3(p->scan_blocks > 0 ? (unsigned)p->scan_blocks : 1u), dim3(kScanThreads), 0, s, m,
+                       p->scan_blocks, direct, p->cnt, p->partial, p->ip, h->force, staged, p->bin, p->perm_num, c_rowptr, p->ctl, pinned);
   }
   HIP_TRY(h, hipGetLastError());
   return SPGEMM_OK;
