@@ -131,8 +131,73 @@ __device__ __forceinline__ void sample_rows(int64_t m, int64_t nnz_a, const int6
   }
 }
 
-// Bound: the gather of B's row pointer (a line per entry of A where it does not fit the L2 cache: 33.5 M entries 0.56 ms, with the
-// descriptions written 0.64), a chain of three loads where there are few rows.
+// Starts and lengths of 12 rows of B in a load: B's row pointer in a sixth of its size, for the row count, which looks rows up in any order.
+constexpr int kLensRows = 12;
+struct __align__(16) RowLens {
+  unsigned start;               // of the first row
+  unsigned len[kLensRows / 4];  // a byte a row
+};
+static_assert(sizeof(RowLens) == 16, "one load");
+constexpr unsigned kLensNear = 64;
+constexpr int kLensThreads = 256;
+constexpr int kLensGroup = kLensThreads / 4;   // of a workgroup, a thread writes a word
+
+// Bound by reading the row pointer.  Rows that do not fit (more than 255 entries, a start beyond 32 bits, a row pointer that is not one) are reported, and nobody
+// uses the table then.  Nor where most of 256 rows of A begin close to where the row before begins: their lookups share lines as it is, and taking
+// the lengths out of the table costs more than it saves (27-point stencil of 110^3 rows, both phases, 2532 us without, 2569 with).
+__global__ __launch_bounds__(kLensThreads) void k_row_lens(int64_t b_rows, const int64_t* __restrict__ b_rp, int64_t m, int64_t nnz_a, const int64_t* __restrict__ a_rp,
+                                                           const int32_t* __restrict__ a_col, unsigned* __restrict__ out, Control* ctl) {
+  if (blockIdx.x == 0) {
+    const int64_t r = (m - 1) * (int64_t)threadIdx.x / kLensThreads;
+    bool looked = false, close = false;
+    if (r + 1 < m) {
+      const int64_t p0 = a_rp[r], p1 = a_rp[r + 1];
+      looked = p0 >= 0 && p0 < p1 && p1 < nnz_a;   // (nobody has checked them yet)
+      if (looked) close = (unsigned)a_col[p1] - (unsigned)a_col[p0] + kLensNear <= 2 * kLensNear;
+    }
+    if (2 * __syncthreads_count(close) > __syncthreads_count(looked) && threadIdx.x == 0) ctl->no_lens = 1;
+  }
+  __shared__ unsigned words[kLensThreads];
+  unsigned char* bytes = reinterpret_cast<unsigned char*>(words);
+  const int64_t r0 = (int64_t)blockIdx.x * (kLensGroup * kLensRows);
+  bool fits = true;
+  for (int t = threadIdx.x; t < kLensGroup * kLensRows; t += kLensThreads) {
+    const int64_t r = r0 + t;
+    const int g = t / kLensRows, j = t - g * kLensRows;
+    int64_t start = 0, len = 0;
+    if (r < b_rows) {
+      const Run<int64_t, 2> bounds = load_run<int64_t, 2>(b_rp + r);
+      start = bounds.v[0];
+      len = bounds.v[1] - start;
+      fits = fits && start >= 0 && start <= 0xffffffffLL && len >= 0 && len < 256;
+    }
+    bytes[g * 16 + 4 + j] = (unsigned char)len;
+    if (j == 0) words[g * 4] = (unsigned)start;
+  }
+  if (__any(!fits) && lane_id() == 0) ctl->no_lens = 1;
+  __syncthreads();
+  const int64_t g0 = (int64_t)blockIdx.x * kLensGroup + threadIdx.x / 4;
+  if (g0 * kLensRows < b_rows) out[(int64_t)blockIdx.x * kLensThreads + threadIdx.x] = words[threadIdx.x];
+}
+
+// Start and length of row k.
+__device__ __forceinline__ void lens_row(const RowLens& g, unsigned j, int64_t* start, long long* len) {
+  unsigned before = 0, word = 0;
+#pragma unroll
+  for (unsigned w = 0; w < kLensRows / 4; ++w) {
+    const unsigned bits = j > 4 * w ? (j - 4 * w) * 8 : 0;
+    before = __builtin_amdgcn_sad_u8(bits >= 32 ? g.len[w] : g.len[w] & ((1u << bits) - 1), 0u, before);
+    if (j >> 2 == w) word = g.len[w];
+  }
+  *start = (int64_t)g.start + before;
+  *len = (word >> (j & 3) * 8) & 255;
+}
+
+// Bound: the gather of B's row pointer (a line per entry of A where it does not fit the L2 cache), a chain of three loads where there are few rows.
+// COMPACT: out of the table of lens instead, unless it is not to be used (with the table and the descriptions written, 33.5 M entries, 4 M rows of B 0.71 | 0.50 ms,
+// 16 M entries, 1 M rows 0.225 | 0.161; groups of 28 rows in 32 bytes 0.52 and 82 registers).
+// Two workgroups on a compute unit, or nobody works while one waits at its barriers (the compiler took 7 waves a SIMD, one workgroup: 27-point stencil of
+// 128^3 rows 391 | 274 us, 16 M entries in rows of 8 248 | 225).
 // The first `parts` workgroups check B.  The others count the products of A's rows: a workgroup takes chunks of `chunk_rows`
 // consecutive rows (a chunk of hub rows holds a large share of all entries, hence the widest workgroup): the chunk's A
 // entries are read coalesced, the lengths of their B rows are summed up over the workgroup, and a row takes the difference of the sums
@@ -140,12 +205,14 @@ __device__ __forceinline__ void sample_rows(int64_t m, int64_t nnz_a, const int6
 // stencil of 128^3 rows 494 -> 377 us, 10^7 entries in rows of 2.4 128 -> 95 us, R-MAT scale 14 27 -> 20 us, scale 19 442 -> 400 us).
 // desc (optional): start and length of every A entry's B row, for the kernels of short rows.
 // Writes ip (saturated to int32), the symbolic bin, zero counts for rows without products.
-__global__ __launch_bounds__(kCountThreads) void k_count_rows(int parts, int64_t b_cols, int64_t b_nnz, const int32_t* __restrict__ b_col, int64_t m,
+// lens (COMPACT): of all rows of B, or reported as not to be had.
+template <bool COMPACT>
+__global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int64_t b_cols, int64_t b_nnz, const int32_t* __restrict__ b_col, int64_t m,
                                                     int64_t nnz_a, int64_t b_rows,
                                                     const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                     const int64_t* __restrict__ b_rp, int* __restrict__ ip_out,
                                                     unsigned char* __restrict__ bin_out, int* __restrict__ cnt_out,
-                                                    Control* ctl, int force, int row_block, unsigned long long* __restrict__ desc) {
+                                                    Control* ctl, int force, int row_block, unsigned long long* __restrict__ desc, const RowLens* __restrict__ lens) {
   __shared__ long long rp[kCountMaxRows + 1];
   __shared__ unsigned long long ipl[kCountMaxRows];
   __shared__ __align__(16) unsigned pre[kCountThreads * 4 + 1];   // products before every entry of a round
@@ -160,6 +227,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int parts, int64_t
   }
   const int tid = threadIdx.x;
   const int chunk_rows = ctl->chunk_rows;
+  const bool compact = COMPACT && !ctl->no_lens;
   if (tid < kNumBins) { hist[tid] = 0; hip[tid] = 0; }
   // a workgroup takes several chunks and reports its bin populations once (thousands of workgroups adding to
   // the same few counters cost more than the counting)
@@ -252,17 +320,35 @@ __global__ __launch_bounds__(kCountThreads) void k_count_rows(int parts, int64_t
 #pragma unroll
         for (int u = 0; u < 4; ++u) k[u] = p0 + u < hi ? a_col[p0 + u] : -1;
       }
+      if (compact) {
+        RowLens g[4];
+        unsigned at[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const long long p = p0 + u;
-        len[u] = 0;
-        start[u] = 0;
-        if (p < hi) {
-          if (k[u] < 0 || k[u] >= b_rows) { badcol = true; continue; }
-          const Run<int64_t, 2> bounds = load_run<int64_t, 2>(b_rp + k[u]);   // (both ends of the row in one load)
-          start[u] = bounds.v[0];
-          len[u] = bounds.v[1] - bounds.v[0];
-          if (len[u] < 0) { badcol = true; len[u] = 0; }
+        for (int u = 0; u < 4; ++u) {   // (an entry that is none, or not a row of B, reads the first)
+          const bool row = k[u] >= 0 && k[u] < b_rows;
+          if (p0 + u < hi && !row) badcol = true;
+          const unsigned of = row ? (unsigned)k[u] : 0u;
+          g[u] = lens[of / kLensRows];
+          at[u] = of % kLensRows;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          lens_row(g[u], at[u], &start[u], &len[u]);
+          if (k[u] < 0 || k[u] >= b_rows) { len[u] = 0; start[u] = 0; }
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const long long p = p0 + u;
+          len[u] = 0;
+          start[u] = 0;
+          if (p < hi) {
+            if (k[u] < 0 || k[u] >= b_rows) { badcol = true; continue; }
+            const Run<int64_t, 2> bounds = load_run<int64_t, 2>(b_rp + k[u]);   // (both ends of the row in one load)
+            start[u] = bounds.v[0];
+            len[u] = bounds.v[1] - bounds.v[0];
+            if (len[u] < 0) { badcol = true; len[u] = 0; }
+          }
         }
       }
       bool fits = true;

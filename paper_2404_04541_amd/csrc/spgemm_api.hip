@@ -335,6 +335,12 @@ void drop_desc(spgemm_context* h, spgemm_plan_s* p) {   // (no kernel that uses 
 // where there are too few rows to fill the card.  16384 rows of a power-law graph: 256 rows 57 us, 64 rows 27 us.
 int count_chunk(spgemm_context* h, int64_t m) { return m >= (int64_t)256 * 2 * h->num_cus ? 256 : 64; }
 
+// Lengths of B's rows in a byte each for the row count: where the row pointer is larger than a die's 4 MB of L2 cache and looked up more often than it has entries, and the
+// table finds room where the lists of rows come to lie afterwards.  (Rows that do not fit a byte are found on the way: the row count looks into the row pointer then.)
+bool row_lens_ok(const spgemm_csr* A, const spgemm_csr* B) {
+  return B->rows * 8 > ((int64_t)4 << 20) && A->nnz >= 2 * B->rows && ceil_div(B->rows, kLensRows) * (int64_t)sizeof(RowLens) <= A->rows * 4;
+}
+
 // Symbolic phase, first part: count, check, bin.  Ends with the control block on the host
 // (one synchronisation): the second part sizes its lists and launches from the bin populations.
 int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const spgemm_csr* B, Control* pinned, Control* host) {
@@ -346,8 +352,12 @@ int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const sp
     hipLaunchKernelGGL(k_init_control, dim3(1), dim3(kCountThreads), 0, s, p->ctl, m, A->rowptr, chunk, h->num_cus);
     const unsigned parts = grid_for(B->nnz > B->rows ? B->nnz : B->rows, kCountThreads * 8, (int64_t)h->num_cus * 4);
     const unsigned groups = m > 0 ? grid_for(m, chunk, (int64_t)h->num_cus * 8) : 0;
-    hipLaunchKernelGGL(k_count_rows, dim3(parts + groups), dim3(kCountThreads), 0, s, (int)parts, B->cols, B->nnz, B->colidx, m, A->nnz, B->rows,
-                       A->rowptr, A->colidx, B->rowptr, p->ip, p->bin, p->cnt, p->ctl, h->force, h->row_block, p->desc);
+    RowLens* lens = row_lens_ok(A, B) ? reinterpret_cast<RowLens*>(p->perm_sym) : nullptr;   // (perm_sym is written afterwards)
+    if (lens)
+      hipLaunchKernelGGL(k_row_lens, dim3((unsigned)ceil_div(B->rows, kLensGroup * kLensRows)), dim3(kLensThreads), 0, s, B->rows, B->rowptr, m, A->nnz, A->rowptr, A->colidx,
+                         reinterpret_cast<unsigned*>(lens), p->ctl);
+    hipLaunchKernelGGL((lens ? k_count_rows<true> : k_count_rows<false>), dim3(parts + groups), dim3(kCountThreads), 0, s, (int)parts, B->cols, B->nnz, B->colidx, m, A->nnz, B->rows,
+                       A->rowptr, A->colidx, B->rowptr, p->ip, p->bin, p->cnt, p->ctl, h->force, h->row_block, p->desc, lens);
   }
   {
     Timer t(h, SPGEMM_K_BIN);
@@ -1415,8 +1425,8 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
     std::vector<long long> first((size_t)nblocks + 2);
     const int chunk = count_chunk(h, m);
     hipLaunchKernelGGL(k_init_control, dim3(1), dim3(kCountThreads), 0, h->stream, ctl, m, A->rowptr, chunk, h->num_cus);
-    hipLaunchKernelGGL(k_count_rows, dim3(grid_for(m, chunk, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, h->stream, 0, B->cols, B->nnz, B->colidx, m,
-                       A->nnz, B->rows, A->rowptr, A->colidx, B->rowptr, ip, tmp + o_bin, reinterpret_cast<int*>(tmp + o_cnt), ctl, 0, 0, (unsigned long long*)nullptr);
+    hipLaunchKernelGGL(k_count_rows<false>, dim3(grid_for(m, chunk, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, h->stream, 0, B->cols, B->nnz, B->colidx, m,
+                       A->nnz, B->rows, A->rowptr, A->colidx, B->rowptr, ip, tmp + o_bin, reinterpret_cast<int*>(tmp + o_cnt), ctl, 0, 0, (unsigned long long*)nullptr, (const RowLens*)nullptr);
     hipLaunchKernelGGL(k_weight_sums, dim3((unsigned)tiles), dim3(kScanThreads), 0, h->stream, m, ip, sums);
     hipLaunchKernelGGL(k_block_rows, dim3(1), dim3(kScanThreads), 0, h->stream, m, tiles, nblocks, ip, sums, reinterpret_cast<long long*>(tmp + o_first));
     hipError_t e = hipGetLastError();
