@@ -200,10 +200,10 @@ __global__ __launch_bounds__(256) void k_run_sum(int64_t n, const unsigned long 
 
 // Merge stage: the sorted batch (b, unique coordinates) into the all array (a, sorted, unique), equal coordinates added.  The
 // merged order (a's component first where both hold a coordinate) is cut into tiles of kMergeTile; a tile's share of either
-// array comes from a bisection along the diagonal, places inside the tile from bisections in LDS.  b's component of a coordinate
-// that a holds too is a repeat: a's component takes its value along.
+// array comes from a bisection along the diagonal, and so does a thread's share of a tile.  b's component of a coordinate
+// that a holds too is a repeat: a's component takes its value along.  Bound by reading and writing the components (four arrays of 8 bytes in, 20 to 24 bytes out).
 // Two sorted arrays of 16.7 M components each: bisection of the other array per component, head flags, their scan and a walk
-// over the runs 1.47 ms, here 0.61 ms.
+// over the runs 1.47 ms, tiles with a bisection in LDS per component 0.61 (count 137 us, put 437), here 0.35 (92, 228).
 constexpr int kMergeTile = 2048;
 
 // split[t] = components of a among the first t * kMergeTile of the merged order
@@ -222,47 +222,66 @@ __global__ __launch_bounds__(256) void k_merge_split(int64_t na, const unsigned 
 
 struct MergeLds {
   unsigned long long key[kMergeTile];   // a's components of the tile, then b's
-  int repeats[kMergeTile + 1];          // repeats among b's components before a position
+  unsigned from[kMergeTile];            // of every component that stays: its place in key, and 1 + the place in b of the value to be added to it
   int part[4];
 };
+constexpr unsigned kFromBits = 12;
+static_assert((1u << kFromBits) > kMergeTile, "places of a tile");
 
-// Loads the tile's keys and finds b's repeats: ml->repeats is their exclusive prefix.  Returns their number.
-__device__ __forceinline__ int merge_tile(int64_t na, const unsigned long long* __restrict__ ka, const unsigned long long* __restrict__ kb,
+// Loads the tile's keys and merges them, kPer consecutive components of the merged order to a thread: a bisection along its diagonal, then a step each.  Returns how many
+// stay; PUT: lists them in ml->from.
+template <bool PUT>
+__device__ __forceinline__ int merge_tile(int64_t na, const unsigned long long* __restrict__ ka, int64_t nb, const unsigned long long* __restrict__ kb,
                                           int64_t a0, int an, int64_t b0, int bn, MergeLds* ml) {
   constexpr int kPer = kMergeTile / 256;
   for (int x = threadIdx.x; x < an; x += 256) ml->key[x] = ka[a0 + x];
   for (int x = threadIdx.x; x < bn; x += 256) ml->key[an + x] = kb[b0 + x];
+  // the neighbours in the tiles around: a's component before the first, b's after the last
+  bool have = a0 > 0;
+  unsigned long long before = have ? ka[a0 - 1] : 0ULL;
+  const bool more = b0 + bn < nb;
+  const unsigned long long after = more ? kb[b0 + bn] : 0ULL;
   __syncthreads();
-  int flag[kPer], mine = 0;   // a thread owns kPer consecutive components of b
+  const int n = an + bn, d = (int)threadIdx.x * kPer < n ? (int)threadIdx.x * kPer : n;
+  int i = d > bn ? d - bn : 0, hi = d < an ? d : an;
+  while (i < hi) {   // (as in k_merge_split)
+    const int mid = (i + hi) >> 1;
+    if (ml->key[mid] <= ml->key[an + d - 1 - mid]) i = mid + 1; else hi = mid;
+  }
+  int j = d - i;
+  if (i > 0) { have = true; before = ml->key[i - 1]; }
+  unsigned long long x = i < an ? ml->key[i] : 0ULL, y = j < bn ? ml->key[an + j] : 0ULL;
+  unsigned from[kPer], stay = 0;
 #pragma unroll
   for (int t = 0; t < kPer; ++t) {
-    const int j = threadIdx.x * kPer + t;
-    flag[t] = 0;
-    if (j < bn) {
-      const unsigned long long key = ml->key[an + j];
-      int lo = 0, hi = an;   // components of a up to and including key
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (ml->key[mid] <= key) lo = mid + 1; else hi = mid;
-      }
-      flag[t] = lo > 0 ? (ml->key[lo - 1] == key ? 1 : 0) : (a0 > 0 && ka[a0 - 1] == key ? 1 : 0);
+    from[t] = 0;
+    if (d + t >= n) continue;
+    if (i < an && (j >= bn || x <= y)) {
+      const bool both = j < bn ? x == y : more && x == after;
+      from[t] = (unsigned)i | (both ? (unsigned)(j + 1) << kFromBits : 0u);
+      stay |= 1u << t;
+      have = true;
+      before = x;
+      if (++i < an) x = ml->key[i];
+    } else {   // (all of a's components up to this one have been taken)
+      from[t] = (unsigned)(an + j);
+      if (!(have && before == y)) stay |= 1u << t;
+      if (++j < bn) y = ml->key[an + j];
     }
-    mine += flag[t];
   }
+  const int mine = __popc(stay);
   const int incl = wave_incl_scan(mine);
   if (lane_id() == kWave - 1) ml->part[threadIdx.x >> 6] = incl;
   __syncthreads();
-  int run = incl - mine, total = 0;
+  int at = incl - mine, total = 0;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) { const int c = ml->part[w]; if (w < (int)(threadIdx.x >> 6)) run += c; total += c; }
+  for (int w = 0; w < 4; ++w) { const int c = ml->part[w]; if (w < (int)(threadIdx.x >> 6)) at += c; total += c; }
+  if (PUT) {
 #pragma unroll
-  for (int t = 0; t < kPer; ++t) {
-    const int j = threadIdx.x * kPer + t;
-    if (j <= bn) ml->repeats[j] = run;
-    run += flag[t];
+    for (int t = 0; t < kPer; ++t)
+      if (stay >> t & 1) ml->from[at++] = from[t];
+    __syncthreads();
   }
-  if (threadIdx.x == 0 && bn == kMergeTile) ml->repeats[kMergeTile] = total;
-  __syncthreads();
   return total;
 }
 
@@ -272,8 +291,8 @@ __global__ __launch_bounds__(256) void k_merge_count(int64_t na, const unsigned 
   __shared__ MergeLds ml;
   const int64_t d0 = (int64_t)blockIdx.x * kMergeTile, d1 = d0 + kMergeTile < na + nb ? d0 + kMergeTile : na + nb;
   const int64_t a0 = split[blockIdx.x], a1 = split[blockIdx.x + 1];
-  const int repeats = merge_tile(na, ka, kb, a0, (int)(a1 - a0), d0 - a0, (int)((d1 - a1) - (d0 - a0)), &ml);
-  if (threadIdx.x == 0) sums[blockIdx.x] = (unsigned)((int)(d1 - d0) - repeats);
+  const int stay = merge_tile<false>(na, ka, nb, kb, a0, (int)(a1 - a0), d0 - a0, (int)((d1 - a1) - (d0 - a0)), &ml);
+  if (threadIdx.x == 0) sums[blockIdx.x] = (unsigned)stay;
 }
 
 template <typename T>
@@ -285,29 +304,14 @@ __global__ __launch_bounds__(256) void k_merge_put(int64_t na, const unsigned lo
   const int64_t a0 = split[blockIdx.x], a1 = split[blockIdx.x + 1];
   const int64_t b0 = d0 - a0;
   const int an = (int)(a1 - a0), bn = (int)((d1 - a1) - b0);
-  (void)merge_tile(na, ka, kb, a0, an, b0, bn, &ml);
+  const int stay = merge_tile<true>(na, ka, nb, kb, a0, an, b0, bn, &ml);
   const int64_t at = sums[blockIdx.x];
-  for (int i = threadIdx.x; i < an; i += 256) {
-    const unsigned long long key = ml.key[i];
-    int lo = 0, hi = bn;   // components of b below key
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (ml.key[an + mid] < key) lo = mid + 1; else hi = mid;
-    }
-    double v = va[a0 + i];
-    const bool both = lo < bn ? ml.key[an + lo] == key : (b0 + bn < nb && kb[b0 + bn] == key);
-    if (both) v += vb[b0 + lo];
-    out.put(at + i + lo - ml.repeats[lo], key, v);
-  }
-  for (int j = threadIdx.x; j < bn; j += 256) {
-    const unsigned long long key = ml.key[an + j];
-    int lo = 0, hi = an;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (ml.key[mid] <= key) lo = mid + 1; else hi = mid;
-    }
-    const bool repeat = lo > 0 ? ml.key[lo - 1] == key : (a0 > 0 && ka[a0 - 1] == key);
-    if (!repeat) out.put(at + lo + j - ml.repeats[j], key, vb[b0 + j]);
+  for (int x = threadIdx.x; x < stay; x += 256) {
+    const unsigned w = ml.from[x], add = w >> kFromBits;
+    const int p = (int)(w & ((1u << kFromBits) - 1));
+    double v = p < an ? va[a0 + p] : vb[b0 + (p - an)];
+    if (add) v += vb[b0 + add - 1];
+    out.put(at + x, ml.key[p], v);
   }
 }
 
