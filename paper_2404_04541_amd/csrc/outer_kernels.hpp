@@ -58,7 +58,8 @@ __global__ __launch_bounds__(256) void k_outer_count(int64_t na, const int32_t* 
 // Insert stage: products [t0, t0 + n) of the k -> i -> j order fill the accumulation array.  A workgroup takes one range of the
 // sort that follows, kInsertTile products at a time: the columns of A that a tile touches are found once (two bisections of the
 // offsets), a product then only looks among those, in LDS when they are few; the first digit's counts of the range on the way.
-// 16.8 M products over 10^6 columns: 338 us with a bisection of all offsets per product (and 27 for the counts), 169 us now.
+// 16.8 M products over 10^6 columns: 338 us with a bisection of all offsets per product (and 27 for the counts), 162 with the two per tile by a thread each (twenty
+// loads that wait for one another), 144 by a wave each.
 constexpr int kInsertTile = 4096;
 constexpr int kInsertCols = 2048;
 template <typename T>
@@ -78,14 +79,16 @@ __global__ __launch_bounds__(kSortThreads) void k_outer_insert(int64_t t0, int64
   for (int64_t x0 = lo; x0 < hi; x0 += kInsertTile) {
     const int64_t x1 = x0 + kInsertTile < hi ? x0 + kInsertTile : hi;
     __syncthreads();   // (the counters are cleared; the tile before has left the offsets)
-    if (threadIdx.x < 2) {
-      const int64_t t = t0 + (threadIdx.x == 0 ? x0 : x1 - 1);
-      int64_t l = 0, h = na;   // last column whose first product is <= t
+    if (threadIdx.x < 2 * kWave) {   // a wave an end: last column whose first product is <= t, in 64 parts at a time
+      const int64_t t = t0 + (threadIdx.x < kWave ? x0 : x1 - 1);
+      int64_t l = 0, h = na;
       while (h - l > 1) {
-        const int64_t mid = l + ((h - l) >> 1);
-        if (off[mid] <= t) l = mid; else h = mid;
+        const int64_t step = (h - l + kWave - 1) / kWave, c = l + lane_id() * step;
+        const unsigned long long below = __ballot(c < h && off[c < h ? c : l] <= t);
+        l += (63 - __clzll((long long)(below | 1))) * step;
+        h = l + step < h ? l + step : h;
       }
-      bound[threadIdx.x] = l;
+      if (lane_id() == 0) bound[threadIdx.x / kWave] = l;
     }
     __syncthreads();
     const int64_t c0 = bound[0], c1 = bound[1] + 1;
