@@ -174,8 +174,10 @@ __global__ __launch_bounds__(kLensThreads) void k_row_lens(int64_t b_rows, const
     bytes[g * 16 + 4 + j] = (unsigned char)len;
     if (j == 0) words[g * 4] = (unsigned)start;
   }
-  if (__any(!fits) && lane_id() == 0) ctl->no_lens = 1;
-  __syncthreads();
+  if (__syncthreads_or(!fits)) {
+    if (threadIdx.x == 0) ctl->no_lens = 1;
+    return;
+  }
   const int64_t g0 = (int64_t)blockIdx.x * kLensGroup + threadIdx.x / 4;
   if (g0 * kLensRows < b_rows) out[(int64_t)blockIdx.x * kLensThreads + threadIdx.x] = words[threadIdx.x];
 }
@@ -194,10 +196,10 @@ __device__ __forceinline__ void lens_row(const RowLens& g, unsigned j, int64_t* 
 }
 
 // Bound: the gather of B's row pointer (a line per entry of A where it does not fit the L2 cache), a chain of three loads where there are few rows.
-// COMPACT: out of the table of lens instead, unless it is not to be used (with the table and the descriptions written, 33.5 M entries, 4 M rows of B 0.71 | 0.50 ms,
-// 16 M entries, 1 M rows 0.225 | 0.161; groups of 28 rows in 32 bytes 0.52 and 82 registers).
+// COMPACT: out of the table of lens instead, unless it is not to be used (with the table and the descriptions written, 33.5 M entries, 4 M rows of B 0.71 | 0.45 ms,
+// 16 M entries, 1 M rows 0.225 | 0.169; groups of 28 rows in 32 bytes 0.52 and 82 registers).
 // Two workgroups on a compute unit, or nobody works while one waits at its barriers (the compiler took 7 waves a SIMD, one workgroup: 27-point stencil of
-// 128^3 rows 391 | 274 us, 16 M entries in rows of 8 248 | 225).
+// 128^3 rows 391 | 274 us, 16 M entries in rows of 8 248 | 225; power-law graphs lose a tenth of the count, 2 in 1000 of their calls: R-MAT scale 17 131 | 142 us, scale 20 with 6 edges 337 | 392).
 // The first `parts` workgroups check B.  The others count the products of A's rows: a workgroup takes chunks of `chunk_rows`
 // consecutive rows (a chunk of hub rows holds a large share of all entries, hence the widest workgroup): the chunk's A
 // entries are read coalesced, the lengths of their B rows are summed up over the workgroup, and a row takes the difference of the sums
@@ -205,7 +207,8 @@ __device__ __forceinline__ void lens_row(const RowLens& g, unsigned j, int64_t* 
 // stencil of 128^3 rows 494 -> 377 us, 10^7 entries in rows of 2.4 128 -> 95 us, R-MAT scale 14 27 -> 20 us, scale 19 442 -> 400 us).
 // desc (optional): start and length of every A entry's B row, for the kernels of short rows.
 // Writes ip (saturated to int32), the symbolic bin, zero counts for rows without products.
-// lens (COMPACT): of all rows of B, or reported as not to be had.
+// lens: of all rows of B, or reported as not to be used.  Both kernels are launched then, and the one that is not meant leaves at once (as two ways inside one kernel,
+// 4 M rows of B take 0.50 instead of 0.45 ms and an R-MAT graph of scale 20, which has no use for the table, 0.42 instead of 0.40; the launch costs 10 us).
 template <bool COMPACT>
 __global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int64_t b_cols, int64_t b_nnz, const int32_t* __restrict__ b_col, int64_t m,
                                                     int64_t nnz_a, int64_t b_rows,
@@ -220,6 +223,7 @@ __global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int6
   __shared__ unsigned long long hip[kNumBins];
   __shared__ int sums[2][kCountThreads / kWave];
   __shared__ int bad;
+  if (lens && COMPACT == (ctl->no_lens != 0)) return;
   if ((int)blockIdx.x < parts) {
     if (blockIdx.x == 0) sample_rows(m, nnz_a, a_rp, a_col, ctl);
     validate_b(blockIdx.x, parts, b_rows, b_cols, b_nnz, b_rp, b_col, ctl, sums);
@@ -227,7 +231,6 @@ __global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int6
   }
   const int tid = threadIdx.x;
   const int chunk_rows = ctl->chunk_rows;
-  const bool compact = COMPACT && !ctl->no_lens;
   if (tid < kNumBins) { hist[tid] = 0; hip[tid] = 0; }
   // a workgroup takes several chunks and reports its bin populations once (thousands of workgroups adding to
   // the same few counters cost more than the counting)
@@ -320,7 +323,7 @@ __global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int6
 #pragma unroll
         for (int u = 0; u < 4; ++u) k[u] = p0 + u < hi ? a_col[p0 + u] : -1;
       }
-      if (compact) {
+      if constexpr (COMPACT) {
         RowLens g[4];
         unsigned at[4];
 #pragma unroll

@@ -335,10 +335,11 @@ void drop_desc(spgemm_context* h, spgemm_plan_s* p) {   // (no kernel that uses 
 // where there are too few rows to fill the card.  16384 rows of a power-law graph: 256 rows 57 us, 64 rows 27 us.
 int count_chunk(spgemm_context* h, int64_t m) { return m >= (int64_t)256 * 2 * h->num_cus ? 256 : 64; }
 
-// Lengths of B's rows in a byte each for the row count: where the row pointer is larger than a die's 4 MB of L2 cache and looked up more often than it has entries, and the
-// table finds room where the lists of rows come to lie afterwards.  (Rows that do not fit a byte are found on the way: the row count looks into the row pointer then.)
+// Lengths of B's rows in a byte each for the row count: where the row pointer is half as large again as a die's 4 MB of L2 cache (600 000 rows,
+// 3 M lookups: no gain, and two launches of 10 us; 10^6 rows, 16 M lookups 225 | 169 us) and looked up more often than it has entries, and the table finds room where the lists of
+// rows come to lie afterwards.  (Rows that do not fit a byte are found on the way: the row count looks into the row pointer then.)
 bool row_lens_ok(const spgemm_csr* A, const spgemm_csr* B) {
-  return B->rows * 8 > ((int64_t)4 << 20) && A->nnz >= 2 * B->rows && ceil_div(B->rows, kLensRows) * (int64_t)sizeof(RowLens) <= A->rows * 4;
+  return B->rows * 8 > ((int64_t)6 << 20) && A->nnz >= 2 * B->rows && ceil_div(B->rows, kLensRows) * (int64_t)sizeof(RowLens) <= A->rows * 4;
 }
 
 // Symbolic phase, first part: count, check, bin.  Ends with the control block on the host
@@ -351,13 +352,14 @@ int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const sp
     const int chunk = count_chunk(h, m);
     hipLaunchKernelGGL(k_init_control, dim3(1), dim3(kCountThreads), 0, s, p->ctl, m, A->rowptr, chunk, h->num_cus);
     const unsigned parts = grid_for(B->nnz > B->rows ? B->nnz : B->rows, kCountThreads * 8, (int64_t)h->num_cus * 4);
-    const unsigned groups = m > 0 ? grid_for(m, chunk, (int64_t)h->num_cus * 8) : 0;
+    const unsigned groups = m > 0 ? grid_for(m, chunk, (int64_t)h->num_cus * 2) : 0;   // (as many as run at a time; chunks are drawn: four times as many 500 000 rows 62 | 58 us)
     RowLens* lens = row_lens_ok(A, B) ? reinterpret_cast<RowLens*>(p->perm_sym) : nullptr;   // (perm_sym is written afterwards)
     if (lens)
       hipLaunchKernelGGL(k_row_lens, dim3((unsigned)ceil_div(B->rows, kLensGroup * kLensRows)), dim3(kLensThreads), 0, s, B->rows, B->rowptr, m, A->nnz, A->rowptr, A->colidx,
                          reinterpret_cast<unsigned*>(lens), p->ctl);
-    hipLaunchKernelGGL((lens ? k_count_rows<true> : k_count_rows<false>), dim3(parts + groups), dim3(kCountThreads), 0, s, (int)parts, B->cols, B->nnz, B->colidx, m, A->nnz, B->rows,
-                       A->rowptr, A->colidx, B->rowptr, p->ip, p->bin, p->cnt, p->ctl, h->force, h->row_block, p->desc, lens);
+    for (int with = lens ? 1 : 0; with >= 0; --with)
+      hipLaunchKernelGGL((with ? k_count_rows<true> : k_count_rows<false>), dim3(parts + groups), dim3(kCountThreads), 0, s, (int)parts, B->cols, B->nnz, B->colidx, m, A->nnz, B->rows,
+                         A->rowptr, A->colidx, B->rowptr, p->ip, p->bin, p->cnt, p->ctl, h->force, h->row_block, p->desc, lens);
   }
   {
     Timer t(h, SPGEMM_K_BIN);

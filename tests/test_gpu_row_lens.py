@@ -25,18 +25,18 @@ def operands(k, m, d, longest, near, seed=1):
 
 
 @pytest.mark.parametrize("k,m,d,longest,near", [
-    (600000, 300000, 4, 40, False), (600001, 300000, 4, 255, False), (600011, 300000, 4, 256, False),   # (the last row of a group, the first, the longest that fit and do not)
-    (524288, 300000, 4, 40, False), (524289, 300000, 4, 40, False), (600000, 200000, 6, 40, False), (600000, 199999, 7, 40, False),   # (sides of the rule)
-    (600000, 300000, 4, 40, True)])
+    (800004, 400000, 4, 40, False), (800005, 400000, 4, 255, False), (800015, 400000, 4, 256, False),   # (the last row of a group, the first, the longest that fit and do not)
+    (786432, 400000, 4, 40, False), (786433, 400000, 4, 40, False), (800004, 266668, 7, 40, False), (800004, 266667, 7, 40, False),   # (sides of the rule)
+    (800004, 400001, 4, 40, False), (800004, 400002, 4, 40, False), (800004, 400000, 4, 40, True)])
 def test_products_are_counted_right(k, m, d, longest, near):
     A, B = operands(k, m, d, longest, near)
     assert_matches_oracle(A, B, gpu_product(A, B), what=f"{k} rows of B, {m} of A")
 
 
-@pytest.mark.parametrize("column", [-1, 600000, 2147483647])
+@pytest.mark.parametrize("column", [-1, 800004, 2147483647])
 def test_a_column_that_is_no_row_is_refused(column):
     from paper_2404_04541_amd import binding as sg
-    A, B = operands(600000, 300000, 4, 40, False)
+    A, B = operands(800004, 400002, 4, 40, False)
     A.colidx[777777] = column
     with pytest.raises(sg.SpgemmError) as e:
         gpu_product(A, B)
@@ -45,7 +45,7 @@ def test_a_column_that_is_no_row_is_refused(column):
 
 def test_a_row_pointer_that_descends_is_refused():
     from paper_2404_04541_amd import binding as sg
-    A, B = operands(600000, 300000, 4, 40, False)
+    A, B = operands(800004, 400002, 4, 40, False)
     B.rowptr[345678] = B.rowptr[345680] + 5
     with pytest.raises(sg.SpgemmError) as e:
         gpu_product(A, B)
