@@ -26,6 +26,7 @@
 #pragma once
 #include "common.hpp"
 #include "entry_order.hpp"
+#include "quad_reads.hpp"
 #include "row_chain.hpp"
 
 namespace spg {
@@ -95,15 +96,6 @@ __device__ __forceinline__ unsigned set_home(int col) {
   return (__umul24((unsigned)col ^ ((unsigned)col >> 20), 0x9E3779u) >> (32 - kSymLogSlots)) & (kSymSlots - 1);
 }
 
-// Where a quad's products come from, in one word: the lane of its entry, how many there are (left: to the entry's end), its first
-// product inside the entry.
-__device__ __forceinline__ unsigned pack_quad(int src, int left, int off) {
-  const int n = left < 0 ? 0 : (left < 4 ? left : 4);
-  return (unsigned)src | ((unsigned)n << 6) | ((unsigned)off << 9);
-}
-__device__ __forceinline__ int quad_src(unsigned w) { return (int)(w & 63u); }
-__device__ __forceinline__ int quad_count(unsigned w) { return (int)((w >> 6) & 7u); }
-__device__ __forceinline__ int quad_off(unsigned w) { return (int)(w >> 9); }
 struct NumRow {   // record (-1: no row, -2: none), how far its columns are from the row's, entries of A, entries of C
   int record = -1, shift = 0, d = 0, n = 0;
   int64_t a0 = 0, out = 0;
@@ -482,7 +474,7 @@ __device__ __forceinline__ void num_recorded_rows(NumRecordedLds<T>* lds, unsign
 #pragma unroll
         for (int i = 0; i < kNumHashSmall / kWave; ++i) h_col[i] = i * kWave + lane < n ? (int)rec[kRecRankWords + i * kWave + lane] : 0;
       }
-      const bool tight = __any(len > 0 && bs + len + 3 > b_nnz);   // (a quad might reach behind the end of B)
+      const bool tight = __any(quads_leave(lane, bs, len, b_nnz));   // (a quad might reach behind the end of B)
       wave_sync_lds();
       ent[lane].bs = bs;
       s_a[lane] = av;

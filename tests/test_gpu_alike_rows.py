@@ -51,3 +51,18 @@ def test_rows_moved(shape, cols, dtype):
         torch.cuda.synchronize()
         assert_matches_oracle(A, B, (rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy()), what=f"{shape} {cols} values {seed}")
     plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("last", [[0], [0, 1], [0, 3], [0, 4]])
+@pytest.mark.parametrize("rows,alike,short", [(3000, True, 0), (3000, False, 0), (400, True, 40), (400, False, 40)])   # (short: rows of class 0 beside them, in one launch)
+def test_a_first_entry_that_is_an_empty_row_at_the_end_of_b(rows, alike, short, last, dtype):
+    rng = np.random.default_rng(rows + len(last))
+    b = [(k % 100) + np.arange(5) for k in range(1000)] + [np.arange(n) for n in last]
+    a = []
+    for i in range(rows):
+        r = (i + np.arange(40)) % 1000 if alike else rng.choice(1000, size=40, replace=False)
+        a.append(np.concatenate([[1000], r]) if i % 5 == 2 or not alike else r)   # 200 products in 80 quads: 48 lanes of the second round have none
+    a += [[1000, 3, 7]] * short
+    A, B = csr(a, len(b), dtype, 3), csr(b, 150, dtype, 4)
+    assert_matches_oracle(A, B, gpu_product(A, B), what=f"{rows} {alike} {last}")
