@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2404_04541_amd import workloads as W
-from helpers import assert_matches_oracle
+from helpers import gpu_product, assert_matches_oracle
 from test_gpu_records import csr
 
 pytestmark = pytest.mark.gpu
