@@ -55,6 +55,26 @@ __global__ __launch_bounds__(256) void k_outer_count(int64_t na, const int32_t* 
   }
 }
 
+// The coordinate of product t0 + x of the k -> i -> j order, by a bisection of all offsets (for a few of them).
+struct OuterKey {
+  int64_t t0, na;
+  int col_bits;
+  const long long* off;
+  const int32_t* match;
+  const int64_t *a_ptr, *b_ptr;
+  const int32_t *a_idx, *b_idx;
+  __device__ __forceinline__ unsigned long long operator()(int64_t x) const {
+    const int64_t t = t0 + x;
+    int64_t l = 0, h = na;
+    while (h - l > 1) {
+      const int64_t mid = l + ((h - l) >> 1);
+      if (off[mid] <= t) l = mid; else h = mid;
+    }
+    const int64_t q = match[l], b0 = b_ptr[q], lb = b_ptr[q + 1] - b0, local = t - off[l];
+    return ((unsigned long long)(unsigned)a_idx[a_ptr[l] + local / lb] << col_bits) | (unsigned)b_idx[b0 + local % lb];
+  }
+};
+
 // Insert stage: products [t0, t0 + n) of the k -> i -> j order fill the accumulation array.  A workgroup takes one range of the
 // sort that follows, kInsertTile products at a time: the columns of A that a tile touches are found once (two bisections of the
 // offsets), a product then only looks among those, in LDS when they are few; the first digit's counts of the range on the way.

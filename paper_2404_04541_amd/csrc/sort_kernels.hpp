@@ -233,9 +233,9 @@ __device__ __forceinline__ int64_t wave_first_not(int64_t n, F before) {
 // where payloads come from.  *too_long is set where a bucket has more entries, and its entries are left out: the caller sorts again by passes alone.
 // Bound: the loads that find a bucket (three to five that wait for each other), then the network and memory.  16.8 M components of 36 bits: three passes
 // of 188 us each with their counts | one of these kernels 135 to 150 us (166 to 210 with a search of all keys, 64 probes a round, for either end); 10^7
-// tensor entries of 33 bits 345 | 118 us; 200 003 entries, whole call 281 | 262 us.
+// tensor entries of 33 bits 345 | 118 us.
 constexpr int kBucketWave = 512;
-constexpr int kBucketGroup = 2048;
+static_assert(kBucketWave * 4 == kBucketGroup, "the waves' buckets and the workgroup's share LDS");
 template <typename P>
 struct BucketLds {
   P pay[kBucketGroup];
@@ -345,6 +345,47 @@ __global__ __launch_bounds__(256) void k_sort_buckets(int64_t n, int64_t buckets
       put(b0 + w, from + t, word, kPlaceBits, lds.pay[word & (kBucketGroup - 1)]);
     }
   }
+}
+
+// Counts a sample of the keys (key_at(p): the key of entry p) by their upper bits in counts[buckets + 1], which are cleared; *crowded (in host memory, cleared) is
+// set where one is met kSampleCrowded times (once: what goes to the host is slow; the last of the counts says that it is on its way).  Of every kSampleStride consecutive entries one at a changing place: one in order, or with a period,
+// is seen as it is.  A workgroup's entries are counted in LDS first: atomics on one counter in memory take 12 ns each.
+// Bound by its chain of loads, LDS and atomics: 10^7 tensor entries 14 us, 27 where they crowd (one of 64 entries 24 and 47), 16 M products of an outer product 29.
+constexpr int kSampleThreads = 256;
+constexpr int kSamplePer = 2;
+__global__ __launch_bounds__(kSampleThreads) void k_sample_clear(unsigned buckets, unsigned* __restrict__ counts) {
+  const unsigned b = blockIdx.x * kSampleThreads + threadIdx.x;
+  if (b <= buckets) counts[b] = 0;
+}
+template <class KeyAt>
+__global__ __launch_bounds__(kSampleThreads) void k_sort_sample(int64_t n, const KeyAt key_at, int low, unsigned buckets, unsigned* __restrict__ counts, int* __restrict__ crowded) {
+  constexpr unsigned kSlots = 2 * kSampleThreads * kSamplePer, kFree = ~0u;
+  __shared__ unsigned bucket[kSlots], met[kSlots];
+  for (unsigned t = threadIdx.x; t < kSlots; t += kSampleThreads) { bucket[t] = kFree; met[t] = 0; }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kSamplePer; ++u) {
+    const int64_t t = ((int64_t)blockIdx.x * kSamplePer + u) * kSampleThreads + threadIdx.x;
+    const int64_t p = t * kSampleStride + ((unsigned)t * 2654435761u >> 25);
+    if (p >= n) continue;
+    const unsigned long long b = (unsigned long long)key_at(p) >> low;
+    if (b >= buckets) continue;   // (a coordinate out of range)
+    unsigned slot = ((unsigned)b * 2654435761u >> 16) & (kSlots - 1);
+    while (true) {   // (half of the slots stay free)
+      const unsigned old = atomicCAS(&bucket[slot], kFree, (unsigned)b);
+      if (old == kFree || old == (unsigned)b) break;
+      slot = (slot + 1) & (kSlots - 1);
+    }
+    atomicAdd(&met[slot], 1u);
+  }
+  __syncthreads();
+  bool seen = false;
+  for (unsigned t = threadIdx.x; t < kSlots; t += kSampleThreads) {
+    const unsigned c = met[t];
+    if (c) seen = seen || atomicAdd(&counts[bucket[t]], c) + c >= kSampleCrowded;
+  }
+  if (__syncthreads_or(seen) && threadIdx.x == 0 && atomicAdd(&counts[buckets], 1u) == 0)
+    __hip_atomic_store(crowded, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ptr[r] = first position of the sorted keys whose high part (key >> shift) is r or more (r = 0 .. rows).  A workgroup takes

@@ -1194,14 +1194,61 @@ int sort_pairs(spgemm_context* h, int64_t n, const SortShape& sh, K* const keys[
     pay_in = out;
     cur = 1 - cur;
   }
-  if (low > 0) {
-    const int64_t buckets = (int64_t)1 << (sh.passes * sh.bits);   // (the passes may have sorted by a bit or two above the keys')
-    hipLaunchKernelGGL((k_sort_buckets<K, P>), dim3((unsigned)ceil_div(buckets, 4)), dim3(256), 0, s, n, buckets, low, keys[cur], pay_in, keys[1 - cur], pay_a, col_out,
-                       col_mask, too_long);
-    cur = 1 - cur;
+  if constexpr (sizeof(K) == 8) {   // (narrow keys have no buckets: buckets_pay)
+    if (low > 0) {
+      const int64_t buckets = (int64_t)1 << (sh.passes * sh.bits);   // (the passes may have sorted by a bit or two above the keys')
+      hipLaunchKernelGGL((k_sort_buckets<K, P>), dim3((unsigned)ceil_div(buckets, 4)), dim3(256), 0, s, n, buckets, low, keys[cur], pay_in, keys[1 - cur], pay_a, col_out,
+                         col_mask, too_long);
+      cur = 1 - cur;
+    }
   }
   return cur;
 }
+
+// Whether some bucket of a sort would be too long (k_sort_sample): asked for before the kernel that makes the keys, which the answer is then
+// waited beside.  counts: room for 2^(upper bits) numbers and one, free until then.
+class BucketSample {
+ public:
+  template <class KeyAt>
+  BucketSample(spgemm_context* h, int64_t n, int nbits, bool wanted, const SortPlan& plan, const KeyAt& key_at, void* counts) : h_(h) {
+    if (!wanted || plan.low == 0) return;
+    asked_ = true;
+    if (!block_.p) return;
+    flag_ = reinterpret_cast<int*>(block_.p);
+    *flag_ = 0;
+    const unsigned buckets = 1u << (nbits - plan.low);
+    hipLaunchKernelGGL(k_sample_clear, dim3((unsigned)ceil_div(buckets + 1, kSampleThreads)), dim3(kSampleThreads), 0, h->stream, buckets, static_cast<unsigned*>(counts));
+    hipLaunchKernelGGL(k_sort_sample<KeyAt>, dim3((unsigned)ceil_div(ceil_div(n, kSampleStride), kSampleThreads * kSamplePer)), dim3(kSampleThreads), 0, h->stream, n, key_at, plan.low,
+                       buckets, static_cast<unsigned*>(counts), flag_);
+    done_ = take_event(h);
+    if (done_ && hipEventRecord(done_, h->stream) != hipSuccess) {
+      (void)hipGetLastError();
+      h->event_pool.push_back(done_);
+      done_ = nullptr;
+    }
+  }
+  ~BucketSample() { (void)crowded(); }
+  BucketSample(const BucketSample&) = delete;
+  BucketSample& operator=(const BucketSample&) = delete;
+  bool crowded() {   // waits for the answer
+    if (flag_) {
+      const hipError_t e = done_ ? hipEventSynchronize(done_) : hipStreamSynchronize(h_->stream);
+      crowded_ = e != hipSuccess || *static_cast<volatile int*>(flag_) != 0;
+      flag_ = nullptr;
+      if (done_) h_->event_pool.push_back(done_);
+    } else if (asked_ && !block_.p) {
+      crowded_ = true;   // (no answer)
+    }
+    return crowded_;
+  }
+
+ private:
+  spgemm_context* h_;
+  PinnedLease block_;
+  int* flag_ = nullptr;
+  hipEvent_t done_ = nullptr;
+  bool asked_ = false, crowded_ = false;
+};
 
 // Temporary memory of one unfolding: two key buffers, one value buffer (the output is the other), the sort's counters, one flag.
 struct UnfoldTmp {
@@ -1229,12 +1276,14 @@ void unfold_launch(spgemm_context* h, const ModeView& v, int64_t nnz, const T* x
   unsigned* counters = reinterpret_cast<unsigned*>(tmp + lay.o_h);
   int cur = 0;
   if (nnz > 0) {
-    const SortPlan plan = sort_plan(nnz, col_bits + row_bits, plain);
-    const SortShape& sh = plan.sh;
+    SortPlan plan = sort_plan(nnz, col_bits + row_bits, plain || !buckets_pay(nnz, col_bits + row_bits));
     int* flags = reinterpret_cast<int*>(tmp + lay.o_bad);
-    hipLaunchKernelGGL(k_tensor_keys<K>, dim3(sh.ranges), dim3(kSortThreads), 0, s, nnz, sh.per_range, v.A, v.B, v.C, col_bits, sh.first_bit, sh.bits, v.xa, v.xb,
+    BucketSample sample(h, nnz, col_bits + row_bits, true, plan, TensorKey<unsigned long long>{v.A, v.B, v.C, col_bits, v.xa, v.xb, v.xc}, keys[1]);
+    hipLaunchKernelGGL(k_tensor_keys<K>, dim3(plan.sh.ranges), dim3(kSortThreads), 0, s, nnz, plan.sh.per_range, v.A, v.B, v.C, col_bits, plan.sh.first_bit, plan.sh.bits, v.xa, v.xb,
                        v.xc, keys[0], counters + kSortBins, flags);
-    cur = sort_pairs<K, T>(h, nnz, sh, keys, xval, val, reinterpret_cast<T*>(tmp + lay.o_v), counters, true, col, (K)(((K)1 << col_bits) - 1), plan.low, flags + 1);
+    const bool crowded = sample.crowded();
+    if (crowded) plan = sort_plan(nnz, col_bits + row_bits, true);
+    cur = sort_pairs<K, T>(h, nnz, plan.sh, keys, xval, val, reinterpret_cast<T*>(tmp + lay.o_v), counters, !crowded, col, (K)(((K)1 << col_bits) - 1), plan.low, flags + 1);
   }
   hipLaunchKernelGGL(k_key_ptr<K>, dim3((unsigned)ceil_div(rows + 1, kPtrRows)), dim3(256), 0, s, nnz, rows, col_bits, keys[cur], rp);
 }
@@ -1658,16 +1707,23 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
     double* sorted = nullptr;
     int cur = 0;
     auto insert_and_sort = [&](bool plain) {
-      const SortPlan plan = sort_plan(cnt, col_bits + bits_of(m), plain);
+      SortPlan plan = sort_plan(cnt, col_bits + bits_of(m), plain || !buckets_pay(cnt, col_bits + bits_of(m)));
       const SortShape& sh = plan.sh;
       hipLaunchKernelGGL(k_clear_ints, dim3(1), dim3(64), 0, s, too_long);
+      // (the batches after the first are taken to be like it; one that is not is sorted again)
+      BucketSample sample(h, cnt, col_bits + bits_of(m), t0 == 0, plan, OuterKey{(int64_t)t0, na, col_bits, off, match, A->ptr, B->ptr, A->idx, B->idx}, keys[1]);
       // insert
       hipLaunchKernelGGL(k_outer_insert<T>, dim3(sh.ranges), dim3(kSortThreads), 0, s, (int64_t)t0, cnt, sh.per_range, sh.first_bit, sh.bits, na, off, match, A->ptr, A->idx,
                          static_cast<const T*>(A->values), B->ptr, B->idx, static_cast<const T*>(B->values), col_bits, keys[0], vals[0], counters + kSortBins);
       // sort
+      const bool crowded = sample.crowded();
+      if (crowded) {
+        plan = sort_plan(cnt, col_bits + bits_of(m), true);
+        plain_sorts = true;
+      }
       const int steps = sh.passes + (plan.low > 0 ? 1 : 0);
       sorted = vals[steps & 1];
-      cur = sort_pairs<unsigned long long, double>(h, cnt, sh, keys, vals[0], sorted, vals[1 - (steps & 1)], counters, true, nullptr, 0ULL, plan.low, too_long);
+      cur = sort_pairs<unsigned long long, double>(h, cnt, sh, keys, vals[0], sorted, vals[1 - (steps & 1)], counters, !crowded, nullptr, 0ULL, plan.low, too_long);
       return plan.low > 0;
     };
     const bool buckets = insert_and_sort(plain_sorts);

@@ -11,6 +11,27 @@
 
 namespace spg {
 
+// The key of the entry (i, j, k); false: a coordinate is out of range, the key 0.
+template <typename Key>
+__device__ __forceinline__ bool tensor_key(int i, int j, int k, int64_t I, int64_t J, int64_t K, int col_bits, Key* key) {
+  *key = 0;
+  if (i < 0 || i >= I || j < 0 || j >= J || k < 0 || k >= K) return false;
+  *key = ((Key)((long long)i * J + j) << col_bits) | (Key)(unsigned)k;
+  return true;
+}
+
+template <typename Key>
+struct TensorKey {   // of entry p
+  int64_t I, J, K;
+  int col_bits;
+  const int32_t *xi, *xj, *xk;
+  __device__ __forceinline__ Key operator()(int64_t p) const {
+    Key key;
+    (void)tensor_key<Key>(xi[p], xj[p], xk[p], I, J, K, col_bits, &key);
+    return key;
+  }
+};
+
 // A workgroup takes one range of entries of the sort: keys and the range's counts of the first digit.
 template <typename Key>
 __global__ __launch_bounds__(kSortThreads) void k_tensor_keys(int64_t nnz, int64_t per_range, int64_t I, int64_t J, int64_t K, int col_bits, int shift, int bits,
@@ -25,10 +46,8 @@ __global__ __launch_bounds__(kSortThreads) void k_tensor_keys(int64_t nnz, int64
   unsigned* mine = cnt[threadIdx.x & (kHistCopies - 1)];
 #pragma unroll 4
   for (int64_t p = lo + threadIdx.x; p < hi; p += kSortThreads) {
-    const int i = xi[p], j = xj[p], k = xk[p];
-    Key key = 0;
-    if (i < 0 || i >= I || j < 0 || j >= J || k < 0 || k >= K) *bad = 1;
-    else key = ((Key)((long long)i * J + j) << col_bits) | (Key)(unsigned)k;
+    Key key;
+    if (!tensor_key<Key>(xi[p], xj[p], xk[p], I, J, K, col_bits, &key)) *bad = 1;
     keys[p] = key;
     atomicAdd(&mine[(unsigned)(key >> shift) & mask], 1u);
   }

@@ -42,24 +42,42 @@ def test_unfolding_at_the_edges_of_the_sort(n, shape):
         assert np.array_equal(got.values.cpu().numpy(), x.values[order])
 
 
+SAMPLE = 128           # entries of which one is counted before buckets are made
+
+
+def sampled(n):
+    t = np.arange((n + SAMPLE - 1) // SAMPLE, dtype=np.uint64)
+    return (t * SAMPLE + ((t * 2654435761 & 0xffffffff) >> 25)).astype(np.int64)
+
+
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
-@pytest.mark.parametrize("n,shape,crowd", [
-    (200_003, (301, 997, 703), 0),          # two passes and buckets of some 50 entries
-    (3_000_000, (600, 700, 900), 0),        # buckets of one wave's registers of four
-    (12_600_000, (2000, 2000, 2000), 0),    # of eight
-    (3_000_000, (600, 700, 900), 700),      # some buckets of one workgroup
-    (3_000_000, (600, 700, 900), 3000),     # and some that are too long: sorted again by passes alone
-    (3_000_000, (8, 8, 900), 0),            # (too few bits for buckets)
+@pytest.mark.parametrize("n,shape,crowd,seen", [
+    (200_003, (301, 997, 703), 0, True),          # (too few entries, and bits, for buckets)
+    (1_048_576, (2000, 2000, 2000), 0, True),     # the last size without buckets
+    (1_048_577, (2000, 2000, 2000), 0, True),     # and the first with: two passes and some 130 entries
+    (3_000_000, (2000, 2000, 2000), 0, True),     # buckets of one wave's registers of four
+    (12_600_000, (2000, 2000, 2000), 0, True),    # of eight
+    (3_000_000, (2000, 2000, 2000), 700, True),   # some buckets of one workgroup
+    (3_000_000, (2000, 2000, 2000), 700, False),
+    (3_000_000, (2000, 2000, 2000), 4000, True),  # and some that are too long: by passes alone
+    (3_000_000, (2000, 2000, 2000), 4000, False),  # where the sample meets none of their entries: sorted again
+    (3_000_000, (600, 700, 900), 4000, True),     # (too few bits)
 ])
-def test_buckets_of_the_sort(n, shape, crowd, dtype):
+def test_buckets_of_the_sort(n, shape, crowd, seen, dtype):
     import torch
     from paper_2404_04541_amd import binding as sg
     g = torch.Generator(device="cuda").manual_seed(n + crowd)
     c = [torch.randint(e, (n,), device="cuda", generator=g) for e in shape]
     if crowd:   # so many entries more in each of a few rows, in few columns: repeated coordinates, which stay in their order
-        at = torch.randperm(n, device="cuda", generator=g)[:crowd * 5]
-        for d in range(3): c[d][at] = torch.randint(5 if d < 2 else 40, (1,), device="cuda", generator=g) if d < 2 else torch.randint(40, (crowd * 5,), device="cuda", generator=g)
-        c[1][at] = torch.arange(crowd * 5, device="cuda") % 5 * 17
+        at = torch.randperm(n, device="cuda", generator=g)
+        if not seen:
+            free = torch.ones(n, dtype=torch.bool, device="cuda")
+            free[torch.from_numpy(sampled(n)[sampled(n) < n]).cuda()] = False
+            at = at[free[at]]
+        at = at[:crowd * 5]
+        c[0][at] = 5
+        c[1][at] = torch.arange(crowd * 5, device="cuda") % 5 * (shape[1] // 6)
+        c[2][at] = torch.randint(40, (crowd * 5,), device="cuda", generator=g)
     v = torch.rand(n, dtype=torch.float64, device="cuda", generator=g).to(torch.float32 if dtype == np.float32 else torch.float64)
     got = sg.sptensor_unfold(sg.Handle(), 3, shape, *[x.to(torch.int32) for x in c], v)
     row = c[0] * shape[1] + c[1]
@@ -68,21 +86,46 @@ def test_buckets_of_the_sort(n, shape, crowd, dtype):
     assert torch.equal(got.rowptr, torch.searchsorted(row[order], torch.arange(shape[0] * shape[1] + 1, device="cuda")))
 
 
-@pytest.mark.parametrize("hub", [0, 1500, 4000])
-def test_outer_product_with_a_crowded_row(hub):
+def test_crowded_entries_are_sorted_once():
+    """Unfolding of entries that crowd in a corner of the tensor: 2.8 times as long as of evenly spread ones when their buckets were found too
+    long after the sort; 1.0 times by passes alone, which buckets beat by a third where they are not."""
+    import time
+    import torch
+    from paper_2404_04541_amd import binding as sg
+    n, h = 10_000_000, sg.Handle()
+    g = torch.Generator(device="cuda").manual_seed(3)
+    u = [torch.rand(n, dtype=torch.float64, device="cuda", generator=g) for _ in range(3)]
+    v = torch.rand(n, dtype=torch.float64, device="cuda", generator=g)
+    even, crowded = ([(t ** p * 2048).to(torch.int32) for t in u] for p in (1, 3))
+
+    def best(x):
+        times = []
+        for _ in range(8):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            sg.sptensor_unfold(h, 3, (2048,) * 3, *x, v)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t0)
+        return min(times)
+    assert best(crowded) < 2 * best(even)
+
+
+@pytest.mark.parametrize("hub,late", [(0, False), (250, False), (4000, False), (4000, True)])   # (late: only in the second batch, behind the sample)
+def test_outer_product_with_a_crowded_row(hub, late):
     """One row of A with so many entries more, times rows of B in few columns: its products are one bucket, or too many for one."""
     from oracle import spgemm as reference
     from paper_2404_04541_amd import binding as sg
     rng = np.random.default_rng(hub)
-    rows, k, cols = 60000, 5000, 1 << 20
-    lens = np.full(rows, 3); lens[777] += hub
-    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
-    colidx = np.concatenate([np.sort(rng.choice(k, size=n, replace=False)) for n in lens]).astype(np.int32)
-    A = W.CSR(rows, k, rowptr, colidx, W.draw_values(int(rowptr[-1]), -1.0, 1.0, np.float64, 1, 3))
-    bcol = np.concatenate([np.sort(rng.choice(cols if not hub else 500, size=4, replace=False)) for _ in range(k)]).astype(np.int32)
-    B = W.CSR(k, cols, np.arange(k + 1, dtype=np.int64) * 4, bcol, W.draw_values(4 * k, -1.0, 1.0, np.float64, 2, 3))
+    rows, k, cols = 60000, 10000, 1 << 20
+    lens = np.full(rows, 6)
+    colidx = [np.sort(rng.choice(k, size=n, replace=False)) for n in lens]
+    if hub: colidx[777] = np.sort(rng.choice(4000, size=hub, replace=False)) + (6000 if late else 0)
+    rowptr = np.concatenate([[0], np.cumsum([c.size for c in colidx])]).astype(np.int64)
+    A = W.CSR(rows, k, rowptr, np.concatenate(colidx).astype(np.int32), W.draw_values(int(rowptr[-1]), -1.0, 1.0, np.float64, 1, 3))
+    bcol = np.concatenate([np.sort(rng.choice(cols if not hub else 500, size=8, replace=False)) for _ in range(k)]).astype(np.int32)
+    B = W.CSR(k, cols, np.arange(k + 1, dtype=np.int64) * 8, bcol, W.draw_values(8 * k, -1.0, 1.0, np.float64, 2, 3))
     h = sg.Handle()
-    C = sg.spgemm_outer(h, sg.dcsc_from_csr(h, sg.to_device(A)), sg.dcsr_from_csr(h, sg.to_device(B)), 400_000)
+    C = sg.spgemm_outer(h, sg.dcsc_from_csr(h, sg.to_device(A)), sg.dcsr_from_csr(h, sg.to_device(B)), 1_500_000)
     ref = reference(A, B)
     assert np.array_equal(C.rowptr.cpu().numpy(), ref.rowptr) and np.array_equal(C.colidx.cpu().numpy(), ref.colidx)
     assert np.all(np.abs(C.values.cpu().numpy() - ref.values) <= 1e-12 * ref.absum)
