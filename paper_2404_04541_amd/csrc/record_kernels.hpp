@@ -143,8 +143,9 @@ __device__ __forceinline__ void sym_wave_rows(SymWaveLds* lds, unsigned wg, unsi
   auto finish = [&] {
     if (lane != 0) return;
     if (kept) atomicAdd(&lds->kept, kept);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-    if (atomicAdd(&lds->done, 1u) == 3 && lds->kept) atomicAdd(&ctl->recorded, lds->kept);
+    if (__hip_atomic_fetch_add(&lds->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) != 3) return;   // (the last one sees what all have added)
+    const unsigned all = __hip_atomic_load(&lds->kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (all) atomicAdd(&ctl->recorded, all);
   };
   if (order.count == 0) {   // (the wave)
     finish();
