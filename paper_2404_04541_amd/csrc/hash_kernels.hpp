@@ -64,7 +64,7 @@ __device__ __forceinline__ void hash_rows(unsigned char* smem, unsigned wg, unsi
                                                const int32_t* __restrict__ b_col, const T* __restrict__ b_val,
                                                int* __restrict__ cnt, const int64_t* __restrict__ c_rp,
                                                int32_t* __restrict__ c_col, T* __restrict__ c_val, int64_t n_cols,
-                                               const RecordOf* __restrict__ record_of, int most_ip) {
+                                               const int* __restrict__ record_of, int most_ip) {
   constexpr int H = 1 << LOGH;
   const bool packable = n_cols <= (int64_t(1) << (31 - LOGH));   // column << LOGH stays below the pad key
   constexpr int kGroups = 256 / GROUP;
@@ -95,7 +95,7 @@ __device__ __forceinline__ void hash_rows(unsigned char* smem, unsigned wg, unsi
     const int row = live ? perm[first + slot] : 0;
     // (wave-uniform) rows whose ranks the symbolic pass has recorded are done elsewhere
     if constexpr (GROUP == kWave && NUMERIC)
-      if (record_of && live && ip_row[row] <= kSymHashSmall && record_of[row].record >= 0) continue;
+      if (record_of && live && ip_row[row] <= kSymHashSmall && record_of[row] >= 0) continue;
     // (the same for the workgroup) rows of more products are done by their tiles
     if constexpr (GROUP > kWave && NUMERIC)
       if (ip_row[row] > most_ip) continue;
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256, GROUP > kWave ? 5 : 8) void k_hash(const int* 
                                                const int32_t* __restrict__ b_col, const T* __restrict__ b_val,
                                                int* __restrict__ cnt, const int64_t* __restrict__ c_rp,
                                                int32_t* __restrict__ c_col, T* __restrict__ c_val, int64_t n_cols,
-                                               const RecordOf* __restrict__ record_of, int most_ip, int looked) {
+                                               const int* __restrict__ record_of, int most_ip, int looked) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (ctl->error) return;
   if (GROUP > kWave && NUMERIC && other_order(ctl, looked)) most_ip = 0x7fffffff;   // (the tiles leave their rows to this kernel)
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(256) void k_other_order(unsigned wgs0, unsigned wgs
     return;
   }
   wg -= wgs1;
-  hash_rows<64, 8, T, true>(smem, wg, wgs2, perm, ctl, 1, 2, ip_row, a_rp, a_col, a_val, b_rp, b_col, b_val, (int*)nullptr, c_rp, c_col, c_val, n_cols, (const RecordOf*)nullptr, 0);
+  hash_rows<64, 8, T, true>(smem, wg, wgs2, perm, ctl, 1, 2, ip_row, a_rp, a_col, a_val, b_rp, b_col, b_val, (int*)nullptr, c_rp, c_col, c_val, n_cols, (const int*)nullptr, 0);
 }
 
 template <typename T>

@@ -39,7 +39,6 @@ constexpr int kRecWords = kRecRankWords + kNumHashSmall;       // 32-bit words o
 constexpr int kRecColBits = 23;                                // a column and its number (8 bits) share 31 bits
 static_assert(kNumHashSmall <= 256, "a rank fits a byte");
 static_assert(kRecWords % 4 == 0 && kRecRankWords % 4 == 0, "records and their column lists start on 16 bytes");
-struct __align__(8) RecordOf { int record, shift; };          // of a row: its record (-1: none), and how far the record's columns are from its own
 constexpr int kRecordGroups = 4;                               // workgroups of these kernels on a compute unit
 constexpr int kSymLogSlots = 10;
 constexpr int kSymSlots = 1 << kSymLogSlots;
@@ -120,7 +119,7 @@ __device__ __forceinline__ void sym_wave_rows(SymWaveLds* lds, unsigned wg, unsi
                                                   const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                   const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col, int64_t b_nnz,
                                                   int* __restrict__ cnt, unsigned* __restrict__ records, unsigned record_rows,
-                                                  RecordOf* __restrict__ record_of) {
+                                                  int* __restrict__ record_of, int* __restrict__ shift_of) {
   if (threadIdx.x == 0) { lds->kept = 0; lds->done = 0; }
   __syncthreads();
   const unsigned first = ctl->offset[0][bin];
@@ -369,7 +368,8 @@ __device__ __forceinline__ void sym_wave_rows(SymWaveLds* lds, unsigned wg, unsi
     // (behind the loads of the rows to come, which are waited for in order with the stores)
     if (lane == 0) {
       cnt[row] = found;
-      if (record_of) record_of[row] = RecordOf{in_record, shift};
+      if (record_of) record_of[row] = in_record;
+      if (ALIKE && shift_of) shift_of[row] = shift;
     }
   }
   finish();
@@ -381,10 +381,10 @@ __global__ __launch_bounds__(256, ALIKE ? kRecordGroups : 5) void k_sym_wave(con
                                                   const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                   const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col, int64_t b_nnz,
                                                   int* __restrict__ cnt, unsigned* __restrict__ records, unsigned record_rows,
-                                                  RecordOf* __restrict__ record_of) {
+                                                  int* __restrict__ record_of, int* __restrict__ shift_of) {
   __shared__ SymWaveLds lds;
   if (ctl->error) return;
-  sym_wave_rows<ALIKE>(&lds, blockIdx.x, gridDim.x, perm, ctl, bin, a_rp, a_col, b_rp, b_col, b_nnz, cnt, records, record_rows, record_of);
+  sym_wave_rows<ALIKE>(&lds, blockIdx.x, gridDim.x, perm, ctl, bin, a_rp, a_col, b_rp, b_col, b_nnz, cnt, records, record_rows, record_of, shift_of);
 }
 
 // Numeric pass over the recorded rows of a bin, a wave per row; rows without a record are left to the hash workspace.
@@ -397,7 +397,7 @@ struct NumRecordedLds {
 
 // ALIKE: neighbouring rows of a wave have the same record; otherwise fewer registers (two quads in flight a lane) and more waves are worth more.
 template <bool ALIKE, typename T>
-__device__ __forceinline__ void num_recorded_rows(NumRecordedLds<T>* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const unsigned* __restrict__ records, const RecordOf* __restrict__ record_of,
+__device__ __forceinline__ void num_recorded_rows(NumRecordedLds<T>* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const unsigned* __restrict__ records, const int* __restrict__ record_of, const int* __restrict__ shift_of,
                                                       const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const T* __restrict__ a_val,
                                                       const int64_t* __restrict__ b_rp, const T* __restrict__ b_val, int64_t b_nnz,
                                                       const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val) {
@@ -413,10 +413,10 @@ __device__ __forceinline__ void num_recorded_rows(NumRecordedLds<T>* lds, unsign
     const unsigned at = in_order.at(t);
     if (at < nrows) {
       const int row = perm[first + at];
-      const RecordOf of = record_of[row];
+      const int of = record_of[row];
       const Run<int64_t, 2> a = load_run<int64_t, 2>(a_rp + row), c = load_run<int64_t, 2>(c_rp + row);
-      r.record = of.record >= 0 ? of.record : -2;
-      r.shift = of.shift;
+      r.record = of >= 0 ? of : -2;
+      if (ALIKE) r.shift = shift_of ? shift_of[row] : 0;
       r.a0 = a.v[0];
       r.d = (int)(a.v[1] - a.v[0]);
       r.out = c.v[0];
@@ -535,7 +535,7 @@ __device__ __forceinline__ void num_recorded_rows(NumRecordedLds<T>* lds, unsign
 
 // SUM: the first order.parts workgroups look at the order of the entries (order_later) while the others do the rows.
 template <typename T, bool SUM, bool ALIKE>
-__global__ __launch_bounds__(256, ALIKE ? kRecordGroups : 8) void k_num_recorded(const int* __restrict__ perm, std::conditional_t<SUM, Control, const Control>* __restrict__ ctl, int bin, const unsigned* __restrict__ records, const RecordOf* __restrict__ record_of,
+__global__ __launch_bounds__(256, ALIKE ? kRecordGroups : 8) void k_num_recorded(const int* __restrict__ perm, std::conditional_t<SUM, Control, const Control>* __restrict__ ctl, int bin, const unsigned* __restrict__ records, const int* __restrict__ record_of, const int* __restrict__ shift_of,
                                                       const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const T* __restrict__ a_val,
                                                       const int64_t* __restrict__ b_rp, const T* __restrict__ b_val, int64_t b_nnz,
                                                       const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val, const OrderOperands order) {
@@ -550,7 +550,7 @@ __global__ __launch_bounds__(256, ALIKE ? kRecordGroups : 8) void k_num_recorded
     wg -= order.parts;
     wgs -= order.parts;
   }
-  num_recorded_rows<ALIKE, T>(&lds, wg, wgs, perm, ctl, bin, records, record_of, a_rp, a_col, a_val, b_rp, b_val, b_nnz, c_rp, c_col, c_val);
+  num_recorded_rows<ALIKE, T>(&lds, wg, wgs, perm, ctl, bin, records, record_of, shift_of, a_rp, a_col, a_val, b_rp, b_val, b_nnz, c_rp, c_col, c_val);
 }
 
 }  // namespace spg

@@ -28,7 +28,7 @@ struct SymShort {
   int* cnt;
   unsigned *words32, *words128, *records;
   unsigned record_rows;
-  RecordOf* record_of;
+  int *record_of, *shift_of;
 };
 
 constexpr size_t sym_short_lds() {
@@ -46,12 +46,12 @@ __global__ __launch_bounds__(256, kShortGroups) void k_sym_short(Control* __rest
   unsigned wg = blockIdx.x;
   if (wg < s.wgs[0]) {
     hash_rows<256, 12, float, false>(smem, wg, s.wgs[0], s.perm, ctl, 0, 3, s.ip, s.a_rp, s.a_col, (const float*)nullptr, s.b_rp, s.b_col, (const float*)nullptr, s.cnt,
-                                     (const int64_t*)nullptr, (int32_t*)nullptr, (float*)nullptr, s.n_cols, (const RecordOf*)nullptr, 0);
+                                     (const int64_t*)nullptr, (int32_t*)nullptr, (float*)nullptr, s.n_cols, (const int*)nullptr, 0);
     return;
   }
   wg -= s.wgs[0];
   if (wg < s.wgs[1]) {
-    sym_wave_rows<ALIKE>(reinterpret_cast<SymWaveLds*>(smem), wg, s.wgs[1], s.perm, ctl, 2, s.a_rp, s.a_col, s.b_rp, s.b_col, s.b_nnz, s.cnt, s.records, s.record_rows, s.record_of);
+    sym_wave_rows<ALIKE>(reinterpret_cast<SymWaveLds*>(smem), wg, s.wgs[1], s.perm, ctl, 2, s.a_rp, s.a_col, s.b_rp, s.b_col, s.b_nnz, s.cnt, s.records, s.record_rows, s.record_of, s.shift_of);
     return;
   }
   wg -= s.wgs[1];
@@ -73,7 +73,7 @@ struct NumShort {
   int64_t b_nnz, n_cols;
   int pack32, pack128;
   const unsigned *words32, *words128, *records;   // (no words: the rows are sorted here)
-  const RecordOf* record_of;
+  const int *record_of, *shift_of;   // (no shifts: all are none)
   int32_t* c_col;
   T* c_val;
   int tiles, most_ip, looked;   // rows of class 3: as a tile without structure, or hashed; see run_numeric
@@ -101,14 +101,14 @@ __global__ __launch_bounds__(256, kShortGroups) void k_num_short(const Control* 
     } else {
       const int most_ip = other_order(ctl, s.looked) ? 0x7fffffff : s.most_ip;
       hash_rows<256, 11, T, true>(smem, wg, s.wgs[0], s.perm_num, ctl, 1, 3, s.ip, s.a_rp, s.a_col, s.a_val, s.b_rp, s.b_col, s.b_val, (int*)nullptr, s.c_rp, s.c_col, s.c_val, s.n_cols,
-                                  (const RecordOf*)nullptr, most_ip);
+                                  (const int*)nullptr, most_ip);
     }
     return;
   }
   wg -= s.wgs[0];
   if (wg < s.wgs[1]) {
     if (ctl->order_differs) return;
-    num_recorded_rows<true, T>(reinterpret_cast<NumRecordedLds<T>*>(smem), wg, s.wgs[1], s.perm_sym, ctl, 2, s.records, s.record_of, s.a_rp, s.a_col, s.a_val, s.b_rp, s.b_val, s.b_nnz, s.c_rp,
+    num_recorded_rows<true, T>(reinterpret_cast<NumRecordedLds<T>*>(smem), wg, s.wgs[1], s.perm_sym, ctl, 2, s.records, s.record_of, s.shift_of, s.a_rp, s.a_col, s.a_val, s.b_rp, s.b_val, s.b_nnz, s.c_rp,
                          s.c_col, s.c_val);
     return;
   }

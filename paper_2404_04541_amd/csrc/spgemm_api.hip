@@ -129,7 +129,8 @@ struct spgemm_plan_s {
   size_t list_bytes = 0, short_bytes = 0;
   unsigned* esc_words[2] = {nullptr, nullptr};   // sorted words of the rows of symbolic bins 0 and 1
   unsigned* records = nullptr;   // rows of symbolic bin 2
-  RecordOf* record_of = nullptr; // per row of A: its record (written for the rows of symbolic bin 2)
+  int* record_of = nullptr;      // per row of A: its record, -1 = none (written for the rows of symbolic bin 2)
+  int* shift_of = nullptr;       // where rows are alike, per row of A: how far its columns are from the record's
   unsigned record_rows = 0;      // rows of the bin that have room for a record
   Control* ctl = nullptr;
   int64_t scan_blocks = 0;
@@ -506,8 +507,8 @@ void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, co
     words[b] = with_words && B->cols <= max_cols[b] ? align_up(host.hist[0][b] * word_bytes[b]) : 0;
     want += words[b];
   }
-  const size_t rec_bytes = (size_t)kRecWords * 4, map = align_up((size_t)p->m * sizeof(RecordOf));
-  if (rec_rows) want += map + rec_rows * rec_bytes;
+  const size_t rec_bytes = (size_t)kRecWords * 4, map = align_up((size_t)p->m * 4);
+  if (rec_rows) want += map * (p->alike ? 2 : 1) + rec_rows * rec_bytes;
   const double asked = h->col_list > 1 ? (double)h->col_list : 1.0e30;
   size_t limit = asked - (double)p->desc_bytes < (double)want ? (size_t)(asked - (double)p->desc_bytes) : want;
   if ((double)(want + p->desc_bytes) + list_want > (double)kAskFreeAbove) {
@@ -533,10 +534,12 @@ void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, co
   }
   size_t rows = 0;
   const size_t o_map = off;
-  if (rec_rows && off + map + rec_bytes <= limit) {
-    rows = (limit - off - map) / rec_bytes;
+  if (rec_rows && off + map + rec_bytes <= limit && off + 2 * map + rec_bytes > limit) p->alike = false;   // (room for records, but not for shifts)
+  const size_t maps = map * (p->alike ? 2 : 1);
+  if (rec_rows && off + maps + rec_bytes <= limit) {
+    rows = (limit - off - maps) / rec_bytes;
     if (rows > rec_rows) rows = rec_rows;
-    off = align_up(off + map + rows * rec_bytes);
+    off = align_up(off + maps + rows * rec_bytes);
   }
   if (off + list_bytes == 0) return;
   unsigned char* base = static_cast<unsigned char*>(dev_alloc(h, off + list_bytes));
@@ -550,8 +553,9 @@ void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, co
   p->list_bytes = list_bytes;
   for (int b = 0; b < 2; ++b) if (words[b]) p->esc_words[b] = reinterpret_cast<unsigned*>(base + o_words[b]);
   if (rows) {
-    p->record_of = reinterpret_cast<RecordOf*>(base + o_map);
-    p->records = reinterpret_cast<unsigned*>(base + o_map + map);
+    p->record_of = reinterpret_cast<int*>(base + o_map);
+    if (p->alike) p->shift_of = reinterpret_cast<int*>(base + o_map + map);
+    p->records = reinterpret_cast<unsigned*>(base + o_map + maps);
     p->record_rows = (unsigned)rows;
   }
   if (list_bytes) {
@@ -639,7 +643,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   if (m > 0) {
     if (!p->flag_rows && !p->desc && short_rows_ok(h, hist)) {
       const SymShort sh{{short_grid(hist[3], 1), hist[2] ? record_grid(h, p, hist[2]) : 0u, short_grid(hist[1], 4), short_grid(hist[0], 16)}, p->perm_sym, p->ip, A->rowptr, B->rowptr,
-                        A->colidx, B->colidx, B->nnz, B->cols, pack32, pack128, p->cnt, p->esc_words[0], p->esc_words[1], p->records, p->record_rows, p->record_of};
+                        A->colidx, B->colidx, B->nnz, B->cols, pack32, pack128, p->cnt, p->esc_words[0], p->esc_words[1], p->records, p->record_rows, p->record_of, p->shift_of};
       hipLaunchKernelGGL((p->alike ? k_sym_short<true> : k_sym_short<false>), dim3(sh.wgs[0] + sh.wgs[1] + sh.wgs[2] + sh.wgs[3]), dim3(256), sym_short_lds(), s, p->ctl, sh);
     } else {
       {
@@ -665,12 +669,12 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
         Timer t(h, SPGEMM_K_SYM_HASH);
         if (hist[2])
           hipLaunchKernelGGL((p->alike ? k_sym_wave<true> : k_sym_wave<false>), dim3(record_grid(h, p, hist[2])), dim3(256), 0, s, p->perm_sym, p->ctl, 2, A->rowptr, A->colidx,
-                             B->rowptr, B->colidx, B->nnz, p->cnt, p->records, p->record_rows, p->record_of);
+                             B->rowptr, B->colidx, B->nnz, p->cnt, p->records, p->record_rows, p->record_of, p->shift_of);
         if (hist[3])
           hipLaunchKernelGGL((k_hash<256, 12, T, false>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
                              lds_hash_large, s, p->perm_sym, p->ctl, 0, 3, p->ip, A->rowptr, A->colidx,
                              (const T*)nullptr, B->rowptr, B->colidx, (const T*)nullptr, p->cnt, (const int64_t*)nullptr,
-                             (int32_t*)nullptr, (T*)nullptr, B->cols, (const RecordOf*)nullptr, 0, kOrderNotLooked);
+                             (int32_t*)nullptr, (T*)nullptr, B->cols, (const int*)nullptr, 0, kOrderNotLooked);
       }
     }
     if (rows_dense > 0) {
@@ -755,7 +759,7 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
     sh.pack32 = pack32; sh.pack128 = pack128;
     sh.words32 = words0 ? p->esc_words[0] : nullptr;
     sh.words128 = words1 ? p->esc_words[1] : nullptr;
-    sh.records = p->records; sh.record_of = p->recorded ? p->record_of : nullptr;
+    sh.records = p->records; sh.record_of = p->recorded ? p->record_of : nullptr; sh.shift_of = p->shift_of;
     sh.c_rp = c_rp; sh.c_col = c_col; sh.c_val = c_val;
     sh.tiles = row_tiles ? 1 : 0; sh.most_ip = most_ip; sh.looked = looked3;
     size_t lds = num_short_lds<T>();
@@ -802,10 +806,10 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
         if (inside) {
           const int64_t most = A->nnz > B->nnz ? A->nnz : B->nnz;
           const OrderOperands order{(int)grid_for(most, kOrderInsideTile, kOrderParts), A->nnz, B->nnz, A->colidx, same ? nullptr : B->colidx};
-          hipLaunchKernelGGL((p->alike ? k_num_recorded<T, true, true> : k_num_recorded<T, true, false>), dim3(grid + order.parts), dim3(256), 0, s, p->perm_sym, p->ctl, 2, p->records, p->record_of,
+          hipLaunchKernelGGL((p->alike ? k_num_recorded<T, true, true> : k_num_recorded<T, true, false>), dim3(grid + order.parts), dim3(256), 0, s, p->perm_sym, p->ctl, 2, p->records, p->record_of, p->shift_of,
                              A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val, order);
         } else {
-          hipLaunchKernelGGL((p->alike ? k_num_recorded<T, false, true> : k_num_recorded<T, false, false>), dim3(grid), dim3(256), 0, s, p->perm_sym, p->ctl, 2, p->records, p->record_of,
+          hipLaunchKernelGGL((p->alike ? k_num_recorded<T, false, true> : k_num_recorded<T, false, false>), dim3(grid), dim3(256), 0, s, p->perm_sym, p->ctl, 2, p->records, p->record_of, p->shift_of,
                              A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val, OrderOperands{});
         }
       }
@@ -821,7 +825,7 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
         else
           hipLaunchKernelGGL((k_hash<256, 11, T, true>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
                              lds_hash_large, s, p->perm_num, p->ctl, 1, 3, p->ip, A->rowptr, A->colidx, a_val, B->rowptr,
-                             B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, B->cols, (const RecordOf*)nullptr, most_ip, looked3);
+                             B->colidx, b_val, (int*)nullptr, c_rp, c_col, c_val, B->cols, (const int*)nullptr, most_ip, looked3);
       }
     }
   }

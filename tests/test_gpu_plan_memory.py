@@ -177,3 +177,25 @@ def test_row_blocks_go_on_without_the_optional_memory(case):
     m = Memory(sg, lambda n, used: used + n > least // 2)
     assert m.product(A, B, blocks=4) == -5   # (too little even so: an error, and nothing is left behind)
     m.close()
+
+
+@pytest.mark.parametrize("alike", [False, True])
+def test_records_find_room_in_a_limit(alike):
+    """A limit that holds four bytes for every row of A and the records of the rows that can have one (1792 bytes each), but not eight bytes a
+    row.  Rows that are not alike have no use for more; rows that are do without being taken for it."""
+    from paper_2404_04541_amd import binding as sg
+    rng = np.random.default_rng(5)
+    rows, recorded = 100_000, 40
+    d = np.zeros(rows, np.int64)
+    d[:recorded] = 30
+    rp = np.concatenate([[0], np.cumsum(d)])
+    cols = np.concatenate([np.arange(30) + i if alike else np.sort(rng.choice(500, 30, replace=False)) for i in range(recorded)])
+    A = W.CSR(rows, 500, rp, cols.astype(np.int32), rng.standard_normal(cols.size))
+    B = W.CSR(500, 700, np.arange(501, dtype=np.int64) * 8, ((np.arange(500)[:, None] + np.arange(8)) % 700).ravel().astype(np.int32), rng.standard_normal(4000))
+    map_bytes, record_bytes = -(-rows * 4 // 256) * 256, recorded * 1792
+    for limit, maps in ((map_bytes - 1, 0), (map_bytes + record_bytes, 1), (2 * map_bytes + record_bytes, 1 + alike), (1, 1 + alike)):
+        m = Memory(sg)
+        m.lib.spgemm_set_option(m.h, sg.OPT_COLUMN_LIST, limit)
+        m.phases(A, B)
+        m.close()
+        assert m.asked[1:] == ([maps * map_bytes + record_bytes] if maps else []), limit   # (behind what the plan cannot do without)
