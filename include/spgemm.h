@@ -113,7 +113,10 @@ typedef struct {
 /* Options for spgemm_set_option. */
 enum {
   /* 1: bracket every kernel class with HIP events on the handle's stream; spgemm_get_stats
-   * then waits for the recorded events and reports the times.  Default 0. */
+   * then waits for the recorded events and reports the times.  Default 0.
+   * Every class has launches of its own then.  Without the option the classes of shorter rows
+   * (sorted list, hash) share one launch a phase where they are few (several thousand rows):
+   * such a call is shorter than the sum of these times. */
   SPGEMM_OPT_TIMING = 1,
   /* Route rows through one workspace kind wherever its capacity allows (rows beyond that
    * capacity keep their normal route): 0 = normal binning (default), 1 = sorted-list,

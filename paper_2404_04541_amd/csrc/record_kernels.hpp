@@ -67,16 +67,13 @@ __device__ __forceinline__ int find_quad(const QuadEntry* ent, int q, float per_
   return lo;
 }
 
-
 // The quads of the entries that the wave's lanes hold (len products from bs on each), described in LDS: at most kQuadRounds * 64.
 struct QuadMap {
   int nq;           // quads
   float per_quad;   // entries per quad
 };
 
-// extra(): called by every lane between the barriers, for what else it leaves in LDS.
-template <class F>
-__device__ __forceinline__ QuadMap quad_map(int64_t bs, int len, int nent, QuadEntry* ent, F extra) {
+__device__ __forceinline__ QuadMap quad_map(int64_t bs, int len, int nent, QuadEntry* ent) {
   QuadMap m;
   const int quads = (len + 3) >> 2;
   const int incl = wave_incl_scan(quads);
@@ -84,7 +81,6 @@ __device__ __forceinline__ QuadMap quad_map(int64_t bs, int len, int nent, QuadE
   m.nq = m.nq < kQuadRounds * kWave ? m.nq : kQuadRounds * kWave;
   wave_sync_lds();   // (the entries of the pass before have been read)
   ent[lane_id()] = QuadEntry{incl - quads, len, bs};
-  extra();
   wave_sync_lds();
   m.per_quad = m.nq > 0 ? (float)nent / (float)m.nq : 0.0f;
   return m;
@@ -248,7 +244,7 @@ __device__ __forceinline__ void sym_wave_rows(SymWaveLds* lds, unsigned wg, unsi
           from_here = v.v[0];
           n_here = (int)(v.v[1] - v.v[0]);
         }
-        const QuadMap map = quad_map(from_here, n_here, d - base < kQuadEntries ? d - base : kQuadEntries, ent, [] {});
+        const QuadMap map = quad_map(from_here, n_here, d - base < kQuadEntries ? d - base : kQuadEntries, ent);
         nq = map.nq;
 #pragma unroll
         for (int r = 0; r < kQuadRounds; ++r) {
@@ -453,7 +449,7 @@ __device__ __forceinline__ void num_recorded_rows(NumRecordedLds<T>* lds, unsign
       // (operands of another structure than the plan's read no further than the record)
       if (at != h_rec || n != h_n || d != h_d || __any(len != h_len)) {
         const unsigned* rec = records + (size_t)at * kRecWords;
-        const QuadMap map = quad_map(bs, len, d, ent, [] {});
+        const QuadMap map = quad_map(bs, len, d, ent);
         h_rec = at; h_n = n; h_d = d; h_len = len; h_nq = map.nq;
 #pragma unroll
         for (int r = 0; r < kQuadRounds; ++r) {

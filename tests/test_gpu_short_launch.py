@@ -34,6 +34,20 @@ def test_few_and_many_rows(each, dtype):
     assert_matches_oracle(A, B, gpu_product(A, B), what=f"{each} rows of each class")
 
 
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("sym,num", [(True, True), (True, False), (False, False)])
+def test_sides_of_the_limit(sym, num, dtype):
+    """As many rows as share a launch in both phases, in the symbolic one alone (rows of class 2 come to class 3 in the numeric one) and in neither."""
+    import torch
+    limit = 16 * 4 * torch.cuda.get_device_properties(0).multi_processor_count   # workgroups: 16 times what the chip holds
+    wgs = lambda rows: rows[0] // 16 + rows[1] // 4 + rows[2] // 4 + rows[3]  # noqa: E731
+    each = {(True, True): limit / (1 / 16 + 1 / 4 + 2) - 8, (True, False): limit / (1 / 16 + 1 / 2 + 1) - 8, (False, False): limit / (1 / 16 + 1 / 2 + 1) + 16}[sym, num]
+    A, B = operands((0, 1, 2, 3), int(each), 5000, dtype)
+    got = gpu_product(A, B)
+    assert (wgs(got[3]["sym_bin_rows"]) <= limit, wgs(got[3]["num_bin_rows"]) <= limit) == (sym, num)
+    assert_matches_oracle(A, B, got, what=f"{int(each)} rows of each class")
+
+
 @pytest.mark.parametrize("dense", [False, True])
 def test_kept_plan_and_another_order(dense):
     import torch
