@@ -53,8 +53,9 @@ struct Control {
   int order_later;                // as order_differs, found out beside the recorded rows
   int unlisted;                   // 1: the structure of some row of the dense classes has no place in the plan's list
   int order_differs;              // 1: the entries of the numeric phase's operands come in another order than the plan's
-  unsigned looked, moved;         // rows of A that were looked at, and those that look like the row before them moved to other columns (here, at the end:
-                                  // in front of the counters of the row count, these lie across lines of memory, and it takes 45 us instead of 29 for 394 000 short rows)
+  unsigned looked, moved;         // rows of A that were looked at, and those that look like the row before them moved to other columns
+                                  // (here, at the end: in front of the counters of the row count, these lie across lines of memory, and it
+                                  // takes 45 us instead of 29 for 394 000 short rows)
   int no_lens;                    // 1: the table of RowLens is not to be used
 #ifdef SPG_PHASE_CLOCKS
   unsigned long long clk[2][32];   // [0] dense symbolic, [1] dense numeric: shader clocks per phase, summed over workgroups

@@ -94,9 +94,10 @@ struct EscSymLds {
 };
 
 template <int GROUP, int CAP, bool DESC>
-__device__ __forceinline__ void esc_sym_rows(EscSymLds<GROUP, CAP>* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const int64_t* __restrict__ a_rp,
-                                                 const int32_t* __restrict__ a_col, const int64_t* __restrict__ b_rp, const unsigned long long* __restrict__ desc, const int32_t* __restrict__ b_col,
-                                                 int64_t b_nnz, int pack, int* __restrict__ cnt, unsigned* __restrict__ words) {
+__device__ __forceinline__ void esc_sym_rows(EscSymLds<GROUP, CAP>* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm,
+    const Control* __restrict__ ctl, int bin, const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const int64_t* __restrict__ b_rp,
+    const unsigned long long* __restrict__ desc, const int32_t* __restrict__ b_col, int64_t b_nnz, int pack, int* __restrict__ cnt,
+    unsigned* __restrict__ words) {
   static_assert(CAP == 2 * GROUP && (CAP == 32 || CAP == 128), "each lane owns two list positions");
   constexpr int kGroups = 256 / GROUP;
   constexpr int kLogCap = CAP == 32 ? 5 : 7;
@@ -170,10 +171,10 @@ struct EscNumLds {
 };
 
 template <int GROUP, int CAP, typename T, bool DESC>
-__device__ __forceinline__ void esc_num_rows(EscNumLds<GROUP, CAP>* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const int64_t* __restrict__ a_rp,
-                                                 const int32_t* __restrict__ a_col, const T* __restrict__ a_val, const int64_t* __restrict__ b_rp, const unsigned long long* __restrict__ desc,
-                                                 const T* __restrict__ b_val, int64_t b_nnz, const unsigned* __restrict__ words,
-                                                 const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val) {
+__device__ __forceinline__ void esc_num_rows(EscNumLds<GROUP, CAP>* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm,
+    const Control* __restrict__ ctl, int bin, const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const T* __restrict__ a_val,
+    const int64_t* __restrict__ b_rp, const unsigned long long* __restrict__ desc, const T* __restrict__ b_val, int64_t b_nnz,
+    const unsigned* __restrict__ words, const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val) {
   static_assert(CAP == 2 * GROUP && (CAP == 32 || CAP == 128), "each lane owns two list positions");
   constexpr int kGroups = 256 / GROUP;
   constexpr int kLogCap = CAP == 32 ? 5 : 7;
@@ -257,7 +258,8 @@ __global__ __launch_bounds__(256, GROUP == kWave ? 6 : 5) void k_esc_num(const i
                                                  const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val) {
   __shared__ EscNumLds<GROUP, CAP> lds;
   if (ctl->error || ctl->order_differs) return;
-  esc_num_rows<GROUP, CAP, T, DESC>(&lds, blockIdx.x, gridDim.x, perm, ctl, bin, a_rp, a_col, a_val, b_rp, desc, b_val, b_nnz, words, c_rp, c_col, c_val);
+  esc_num_rows<GROUP, CAP, T, DESC>(&lds, blockIdx.x, gridDim.x, perm, ctl, bin, a_rp, a_col, a_val, b_rp, desc, b_val, b_nnz, words, c_rp, c_col,
+      c_val);
 }
 
 // ---- without them --------------------------------------------------------------------------

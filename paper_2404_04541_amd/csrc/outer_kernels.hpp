@@ -78,17 +78,15 @@ struct OuterKey {
 // Insert stage: products [t0, t0 + n) of the k -> i -> j order fill the accumulation array.  A workgroup takes one range of the
 // sort that follows, kInsertTile products at a time: the columns of A that a tile touches are found once (two bisections of the
 // offsets), a product then only looks among those, in LDS when they are few; the first digit's counts of the range on the way.
-// 16.8 M products over 10^6 columns: 338 us with a bisection of all offsets per product (and 27 for the counts), 162 with the two per tile by a thread each (twenty
-// loads that wait for one another), 144 by a wave each.
+// 16.8 M products over 10^6 columns: 338 us with a bisection of all offsets per product (and 27 for the counts), 162 with the two per tile by a
+// thread each (twenty loads that wait for one another), 144 by a wave each.
 constexpr int kInsertTile = 4096;
 constexpr int kInsertCols = 2048;
 template <typename T>
-__global__ __launch_bounds__(kSortThreads) void k_outer_insert(int64_t t0, int64_t n, int64_t per_range, int shift, int bits, int64_t na, const long long* __restrict__ off,
-                                                      const int32_t* __restrict__ match, const int64_t* __restrict__ a_ptr,
-                                                      const int32_t* __restrict__ a_idx, const T* __restrict__ a_val,
-                                                      const int64_t* __restrict__ b_ptr, const int32_t* __restrict__ b_idx,
-                                                      const T* __restrict__ b_val, int col_bits, unsigned long long* __restrict__ keys,
-                                                      double* __restrict__ vals, unsigned* __restrict__ hist) {
+__global__ __launch_bounds__(kSortThreads) void k_outer_insert(int64_t t0, int64_t n, int64_t per_range, int shift, int bits, int64_t na,
+    const long long* __restrict__ off, const int32_t* __restrict__ match, const int64_t* __restrict__ a_ptr, const int32_t* __restrict__ a_idx,
+    const T* __restrict__ a_val, const int64_t* __restrict__ b_ptr, const int32_t* __restrict__ b_idx, const T* __restrict__ b_val, int col_bits,
+    unsigned long long* __restrict__ keys, double* __restrict__ vals, unsigned* __restrict__ hist) {
   __shared__ unsigned cnt[kHistCopies][kSortBins];
   __shared__ long long s_off[kInsertCols];
   __shared__ long long bound[2];
@@ -224,7 +222,8 @@ __global__ __launch_bounds__(256) void k_run_sum(int64_t n, const unsigned long 
 // Merge stage: the sorted batch (b, unique coordinates) into the all array (a, sorted, unique), equal coordinates added.  The
 // merged order (a's component first where both hold a coordinate) is cut into tiles of kMergeTile; a tile's share of either
 // array comes from a bisection along the diagonal, and so does a thread's share of a tile.  b's component of a coordinate
-// that a holds too is a repeat: a's component takes its value along.  Bound by reading and writing the components (four arrays of 8 bytes in, 20 to 24 bytes out).
+// that a holds too is a repeat: a's component takes its value along.  Bound by reading and writing the components (four arrays of 8 bytes in, 20 to
+// 24 bytes out).
 // Two sorted arrays of 16.7 M components each: bisection of the other array per component, head flags, their scan and a walk
 // over the runs 1.47 ms, tiles with a bisection in LDS per component 0.61 (count 137 us, put 437), here 0.35 (92, 228).
 constexpr int kMergeTile = 2048;
@@ -251,11 +250,11 @@ struct MergeLds {
 constexpr unsigned kFromBits = 12;
 static_assert((1u << kFromBits) > kMergeTile, "places of a tile");
 
-// Loads the tile's keys and merges them, kPer consecutive components of the merged order to a thread: a bisection along its diagonal, then a step each.  Returns how many
-// stay; PUT: lists them in ml->from.
+// Loads the tile's keys and merges them, kPer consecutive components of the merged order to a thread: a bisection along its diagonal, then a step
+// each.  Returns how many stay; PUT: lists them in ml->from.
 template <bool PUT>
-__device__ __forceinline__ int merge_tile(int64_t na, const unsigned long long* __restrict__ ka, int64_t nb, const unsigned long long* __restrict__ kb,
-                                          int64_t a0, int an, int64_t b0, int bn, MergeLds* ml) {
+__device__ __forceinline__ int merge_tile(int64_t na, const unsigned long long* __restrict__ ka, int64_t nb,
+    const unsigned long long* __restrict__ kb, int64_t a0, int an, int64_t b0, int bn, MergeLds* ml) {
   constexpr int kPer = kMergeTile / 256;
   for (int x = threadIdx.x; x < an; x += 256) ml->key[x] = ka[a0 + x];
   for (int x = threadIdx.x; x < bn; x += 256) ml->key[an + x] = kb[b0 + x];

@@ -20,7 +20,9 @@
 // that is the model moved; the numeric one adds 729 products a row in 250 LDS cycles of 500 (without the stores 1.35 of 2.02 ms, without
 // additions 1.95): what it waits for is memory, C's 3.1 GB written and 2.7 GB of A and B read.
 // 27-point stencil of 128^3 rows, fp64 (729 products and 125 entries per row), every row by itself | with models: symbolic 3.08 | 1.12 ms,
-// numeric 2.20 | 2.02 ms; of 61^3 rows 463 | 212 us and 255 | 190 us.  (Hash workspace: 2.39 + 4.80 ms.)
+// numeric 2.20 | 2.02 ms; of 61^3 rows 463 | 212 us and 255 | 190 us.  (Hash workspace: 2.39 + 4.80 ms.)  Of that, rows dealt to all dies in turn |
+// neighbouring ones to one die: symbolic 1.45 | 1.12 ms, numeric 2.14 | 2.02; stores through the caches | past them: numeric 2.32 | 2.02 ms, 61^3
+// 244 | 190 us.
 // Measured and not kept in the numeric kernel: the next row's values asked for before this one's stores, with the loads free of conditions
 // (2.08 ms: 142 registers); two products a load (2.08); 24 or 32 waves on a compute unit (2.36, 2.40).
 #pragma once
@@ -42,7 +44,8 @@ static_assert(kRecWords % 4 == 0 && kRecRankWords % 4 == 0, "records and their c
 constexpr int kRecordGroups = 4;                               // workgroups of these kernels on a compute unit
 constexpr int kSymLogSlots = 10;
 constexpr int kSymSlots = 1 << kSymLogSlots;
-constexpr int kRecSums = 256 + kWave;                          // sums of a row in LDS (a rank is a byte), and a place for every lane's missing products
+// sums of a row in LDS (a rank is a byte), and a place for every lane's missing products
+constexpr int kRecSums = 256 + kWave;
 static_assert(4 * kRecSums * 8 <= 65536, "a sum's place in the workgroup's LDS fits 16 bits");
 
 struct __align__(16) QuadEntry { int first, len; int64_t bs; };   // first quad of an A entry, its products, the start of its B row
@@ -111,11 +114,10 @@ struct SymWaveLds {
 };
 
 template <bool ALIKE>
-__device__ __forceinline__ void sym_wave_rows(SymWaveLds* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, Control* __restrict__ ctl, int bin,
-                                                  const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
-                                                  const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col, int64_t b_nnz,
-                                                  int* __restrict__ cnt, unsigned* __restrict__ records, unsigned record_rows,
-                                                  int* __restrict__ record_of, int* __restrict__ shift_of) {
+__device__ __forceinline__ void sym_wave_rows(SymWaveLds* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, Control* __restrict__ ctl,
+    int bin, const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const int64_t* __restrict__ b_rp,
+    const int32_t* __restrict__ b_col, int64_t b_nnz, int* __restrict__ cnt, unsigned* __restrict__ records, unsigned record_rows,
+    int* __restrict__ record_of, int* __restrict__ shift_of) {
   if (threadIdx.x == 0) { lds->kept = 0; lds->done = 0; }
   __syncthreads();
   const unsigned first = ctl->offset[0][bin];
@@ -138,7 +140,8 @@ __device__ __forceinline__ void sym_wave_rows(SymWaveLds* lds, unsigned wg, unsi
   auto finish = [&] {
     if (lane != 0) return;
     if (kept) atomicAdd(&lds->kept, kept);
-    if (__hip_atomic_fetch_add(&lds->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) != 3) return;   // (the last one sees what all have added)
+    // (the last one sees what all have added)
+    if (__hip_atomic_fetch_add(&lds->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) != 3) return;
     const unsigned all = __hip_atomic_load(&lds->kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (all) atomicAdd(&ctl->recorded, all);
   };
@@ -393,10 +396,11 @@ struct NumRecordedLds {
 
 // ALIKE: neighbouring rows of a wave have the same record; otherwise fewer registers (two quads in flight a lane) and more waves are worth more.
 template <bool ALIKE, typename T>
-__device__ __forceinline__ void num_recorded_rows(NumRecordedLds<T>* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, const Control* __restrict__ ctl, int bin, const unsigned* __restrict__ records, const int* __restrict__ record_of, const int* __restrict__ shift_of,
-                                                      const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const T* __restrict__ a_val,
-                                                      const int64_t* __restrict__ b_rp, const T* __restrict__ b_val, int64_t b_nnz,
-                                                      const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val) {
+__device__ __forceinline__ void num_recorded_rows(NumRecordedLds<T>* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm,
+    const Control* __restrict__ ctl, int bin, const unsigned* __restrict__ records, const int* __restrict__ record_of,
+    const int* __restrict__ shift_of, const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const T* __restrict__ a_val,
+    const int64_t* __restrict__ b_rp, const T* __restrict__ b_val, int64_t b_nnz, const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col,
+    T* __restrict__ c_val) {
   const unsigned first = ctl->offset[0][bin];   // (the order of the symbolic kernel: a wave meets the rows of a record one after the other)
   const unsigned nrows = ctl->offset[0][bin + 1] - first;
   const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
@@ -464,7 +468,10 @@ __device__ __forceinline__ void num_recorded_rows(NumRecordedLds<T>* lds, unsign
           }
           unsigned to[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) to[u] = g * (unsigned)sizeof(lds->acc[0]) + (u < quad_count(h_quad[r]) ? (rank >> (8 * u)) & 255u : 256u + lane) * 8u;
+          for (int u = 0; u < 4; ++u) {
+            const unsigned place = u < quad_count(h_quad[r]) ? (rank >> (8 * u)) & 255u : 256u + lane;
+            to[u] = g * (unsigned)sizeof(lds->acc[0]) + place * 8u;
+          }
           h_sum[r][0] = to[0] | (to[1] << 16);
           h_sum[r][1] = to[2] | (to[3] << 16);
         }
@@ -505,7 +512,8 @@ __device__ __forceinline__ void num_recorded_rows(NumRecordedLds<T>* lds, unsign
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const unsigned to = (h_sum[r][u >> 1] >> (16 * (u & 1))) & 0xffffu;
-            __hip_atomic_fetch_add(static_cast<double*>(__builtin_assume_aligned(reinterpret_cast<unsigned char*>(lds->acc) + to, 8)), a * (double)b[i][u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            double* sum = static_cast<double*>(__builtin_assume_aligned(reinterpret_cast<unsigned char*>(lds->acc) + to, 8));
+            __hip_atomic_fetch_add(sum, a * (double)b[i][u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           }
         }
       }
@@ -531,10 +539,14 @@ __device__ __forceinline__ void num_recorded_rows(NumRecordedLds<T>* lds, unsign
 
 // SUM: the first order.parts workgroups look at the order of the entries (order_later) while the others do the rows.
 template <typename T, bool SUM, bool ALIKE>
-__global__ __launch_bounds__(256, ALIKE ? kRecordGroups : 8) void k_num_recorded(const int* __restrict__ perm, std::conditional_t<SUM, Control, const Control>* __restrict__ ctl, int bin, const unsigned* __restrict__ records, const int* __restrict__ record_of, const int* __restrict__ shift_of,
-                                                      const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const T* __restrict__ a_val,
-                                                      const int64_t* __restrict__ b_rp, const T* __restrict__ b_val, int64_t b_nnz,
-                                                      const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val, const OrderOperands order) {
+__global__ __launch_bounds__(256, ALIKE ? kRecordGroups : 8) void k_num_recorded(const int* __restrict__ perm,
+                                                      std::conditional_t<SUM, Control, const Control>* __restrict__ ctl, int bin,
+                                                          const unsigned* __restrict__ records, const int* __restrict__ record_of,
+                                                          const int* __restrict__ shift_of, const int64_t* __restrict__ a_rp,
+                                                          const int32_t* __restrict__ a_col, const T* __restrict__ a_val,
+                                                          const int64_t* __restrict__ b_rp, const T* __restrict__ b_val, int64_t b_nnz,
+                                                          const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val,
+                                                          const OrderOperands order) {
   __shared__ NumRecordedLds<T> lds;
   if (ctl->error || (!SUM && ctl->order_differs)) return;
   unsigned wg = blockIdx.x, wgs = gridDim.x;
@@ -546,7 +558,8 @@ __global__ __launch_bounds__(256, ALIKE ? kRecordGroups : 8) void k_num_recorded
     wg -= order.parts;
     wgs -= order.parts;
   }
-  num_recorded_rows<ALIKE, T>(&lds, wg, wgs, perm, ctl, bin, records, record_of, shift_of, a_rp, a_col, a_val, b_rp, b_val, b_nnz, c_rp, c_col, c_val);
+  num_recorded_rows<ALIKE, T>(&lds, wg, wgs, perm, ctl, bin, records, record_of, shift_of, a_rp, a_col, a_val, b_rp, b_val, b_nnz, c_rp, c_col,
+      c_val);
 }
 
 }  // namespace spg

@@ -116,7 +116,8 @@ __device__ __forceinline__ void validate_b(int part, int parts, int64_t rows, in
 
 // Are rows mostly the row before moved to other columns (as many entries, the first and the last moved by the same), as those of
 // discretised operators are?  A pair of rows for every thread of one workgroup, spread over all rows.
-__device__ __forceinline__ void sample_rows(int64_t m, int64_t nnz_a, const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, Control* ctl) {
+__device__ __forceinline__ void sample_rows(int64_t m, int64_t nnz_a, const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
+    Control* ctl) {
   const int64_t r = (m - 1) * (int64_t)threadIdx.x / kCountThreads;
   bool looked = false, moved = false;
   if (r + 2 <= m) {
@@ -142,11 +143,12 @@ constexpr unsigned kLensNear = 64;
 constexpr int kLensThreads = 256;
 constexpr int kLensGroup = kLensThreads / 4;   // of a workgroup, a thread writes a word
 
-// Bound by reading the row pointer.  Rows that do not fit (more than 255 entries, a start beyond 32 bits, a row pointer that is not one) are reported, and nobody
-// uses the table then.  Nor where most of 256 rows of A begin close to where the row before begins: their lookups share lines as it is, and taking
-// the lengths out of the table costs more than it saves (27-point stencil of 110^3 rows, both phases, 2532 us without, 2569 with).
-__global__ __launch_bounds__(kLensThreads) void k_row_lens(int64_t b_rows, const int64_t* __restrict__ b_rp, int64_t m, int64_t nnz_a, const int64_t* __restrict__ a_rp,
-                                                           const int32_t* __restrict__ a_col, unsigned* __restrict__ out, Control* ctl) {
+// Bound by reading the row pointer.  Rows that do not fit (more than 255 entries, a start beyond 32 bits, a row pointer that is not one) are
+// reported, and nobody uses the table then.  Nor where most of 256 rows of A begin close to where the row before begins: their lookups share lines
+// as it is, and taking the lengths out of the table costs more than it saves (27-point stencil of 110^3 rows, both phases, 2532 us without, 2569
+// with).
+__global__ __launch_bounds__(kLensThreads) void k_row_lens(int64_t b_rows, const int64_t* __restrict__ b_rp, int64_t m, int64_t nnz_a,
+    const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, unsigned* __restrict__ out, Control* ctl) {
   if (blockIdx.x == 0) {
     const int64_t r = (m - 1) * (int64_t)threadIdx.x / kLensThreads;
     bool looked = false, close = false;
@@ -196,10 +198,12 @@ __device__ __forceinline__ void lens_row(const RowLens& g, unsigned j, int64_t* 
 }
 
 // Bound: the gather of B's row pointer (a line per entry of A where it does not fit the L2 cache), a chain of three loads where there are few rows.
-// COMPACT: out of the table of lens instead, unless it is not to be used (with the table and the descriptions written, 33.5 M entries, 4 M rows of B 0.71 | 0.45 ms,
-// 16 M entries, 1 M rows 0.225 | 0.169; groups of 28 rows in 32 bytes 0.52 and 82 registers).
-// Two workgroups on a compute unit, or nobody works while one waits at its barriers (the compiler took 7 waves a SIMD, one workgroup: 27-point stencil of
-// 128^3 rows 391 | 274 us, 16 M entries in rows of 8 248 | 225; power-law graphs lose a tenth of the count, 2 in 1000 of their calls: R-MAT scale 17 131 | 142 us, scale 20 with 6 edges 337 | 392).
+// COMPACT: out of the table of lens instead, unless it is not to be used (with the table and the descriptions written, 33.5 M entries, 4 M rows of B
+// 0.71 | 0.45 ms, 16 M entries, 1 M rows 0.225 | 0.169; groups of 28 rows in 32 bytes 0.52 and 82 registers).
+// Two workgroups on a compute unit, or nobody works while one waits at its barriers (the compiler took 7 waves a SIMD, one workgroup: 27-point
+// stencil of 128^3 rows 391 | 274 us, 16 M entries in rows of 8 248 | 225; power-law graphs lose a tenth of the count, 2 in 1000 of their calls:
+// R-MAT scale 17 131 | 142 us, scale 20 with 6 edges 337 | 392).  (Between events around all launches of the count; by themselves this kernel and
+// that of the lengths take 228 + 8 us of the 274, and 380 + 13 us of the 0.45 ms.)
 // The first `parts` workgroups check B.  The others count the products of A's rows: a workgroup takes chunks of `chunk_rows`
 // consecutive rows (a chunk of hub rows holds a large share of all entries, hence the widest workgroup): the chunk's A
 // entries are read coalesced, the lengths of their B rows are summed up over the workgroup, and a row takes the difference of the sums
@@ -207,15 +211,14 @@ __device__ __forceinline__ void lens_row(const RowLens& g, unsigned j, int64_t* 
 // stencil of 128^3 rows 494 -> 377 us, 10^7 entries in rows of 2.4 128 -> 95 us, R-MAT scale 14 27 -> 20 us, scale 19 442 -> 400 us).
 // desc (optional): start and length of every A entry's B row, for the kernels of short rows.
 // Writes ip (saturated to int32), the symbolic bin, zero counts for rows without products.
-// lens: of all rows of B, or reported as not to be used.  Both kernels are launched then, and the one that is not meant leaves at once (as two ways inside one kernel,
-// 4 M rows of B take 0.50 instead of 0.45 ms and an R-MAT graph of scale 20, which has no use for the table, 0.42 instead of 0.40; the launch costs 10 us).
+// lens: of all rows of B, or reported as not to be used.  Both kernels are launched then, and the one that is not meant leaves at once (as two ways
+// inside one kernel, 4 M rows of B take 0.50 instead of 0.45 ms and an R-MAT graph of scale 20, which has no use for the table, 0.42 instead of
+// 0.40; the launch costs 10 us).
 template <bool COMPACT>
-__global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int64_t b_cols, int64_t b_nnz, const int32_t* __restrict__ b_col, int64_t m,
-                                                    int64_t nnz_a, int64_t b_rows,
-                                                    const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
-                                                    const int64_t* __restrict__ b_rp, int* __restrict__ ip_out,
-                                                    unsigned char* __restrict__ bin_out, int* __restrict__ cnt_out,
-                                                    Control* ctl, int force, int row_block, unsigned long long* __restrict__ desc, const RowLens* __restrict__ lens) {
+__global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int64_t b_cols, int64_t b_nnz, const int32_t* __restrict__ b_col,
+    int64_t m, int64_t nnz_a, int64_t b_rows, const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const int64_t* __restrict__ b_rp,
+    int* __restrict__ ip_out, unsigned char* __restrict__ bin_out, int* __restrict__ cnt_out, Control* ctl, int force, int row_block,
+    unsigned long long* __restrict__ desc, const RowLens* __restrict__ lens) {
   __shared__ long long rp[kCountMaxRows + 1];
   __shared__ unsigned long long ipl[kCountMaxRows];
   __shared__ __align__(16) unsigned pre[kCountThreads * 4 + 1];   // products before every entry of a round
@@ -435,7 +438,8 @@ struct ScatterLds {
   unsigned count[kNumBins][kScanWaves], base[kNumBins], offset[kNumBins + 1];
 };
 // hist: rows of every bin, of all tiles.
-__device__ __forceinline__ void scatter_bins(const int (&bin)[kScanItems], const unsigned* hist, int* __restrict__ perm, Control* ctl, int phase, ScatterLds* sl) {
+__device__ __forceinline__ void scatter_bins(const int (&bin)[kScanItems], const unsigned* hist, int* __restrict__ perm, Control* ctl, int phase,
+    ScatterLds* sl) {
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
   if (tid == 0) {
     unsigned run = 0;
@@ -501,8 +505,8 @@ __global__ __launch_bounds__(kScanThreads) void k_bin_scatter(int64_t m, const u
   }
 }
 
-// Numeric classes of a tile's rows from ip and the symbolic counts; their numbers, products and entries are added to the workgroup's (all threads together; the
-// barrier after it is the caller's).
+// Numeric classes of a tile's rows from ip and the symbolic counts; their numbers, products and entries are added to the workgroup's (all threads
+// together; the barrier after it is the caller's).
 struct ClassLds {
   unsigned hist[kNumBins];
   unsigned long long ip[kNumBins], nnz[kNumBins];
@@ -597,12 +601,13 @@ __global__ __launch_bounds__(kScanBlockThreads) void k_scan_blocks(int64_t nbloc
 // 700 000; the two of now 14 and 25 us, and the control block reaches the host without a copy (two copies of 10 to 15 us each).
 // The row pointer and the lists of the numeric bins.  direct: partial holds the sums of the tiles (at most kScanDirect), of
 // which every workgroup adds up its own share; otherwise their exclusive prefix (k_scan_blocks).
-// ONE: a single tile.  Its workgroup needs nobody else's numbers and classifies its rows itself: one launch instead of two (whole calls, us: 1000 rows of
-// 10 x 10 88.6 | 87.0, 4096 rows 90.9 | 88.1, R-MAT scale 12 197 | 195, 27-point stencil of 12^3 rows 109 | 106).
+// ONE: a single tile.  Its workgroup needs nobody else's numbers and classifies its rows itself: one launch instead of two (whole calls, us: 1000
+// rows of 10 x 10 88.6 | 87.0, 4096 rows 90.9 | 88.1, R-MAT scale 12 197 | 195, 27-point stencil of 12^3 rows 109 | 106).
 template <bool ONE>
 __global__ __launch_bounds__(kScanThreads) void k_scan_final(int64_t m, int64_t tiles, int direct, const int* __restrict__ cnt, const long long* __restrict__ partial,
-                                                             const int* __restrict__ ip, int force, int staged_cap, unsigned char* __restrict__ bin_of,
-                                                             int* __restrict__ perm, int64_t* __restrict__ rowptr, Control* ctl, Control* host) {
+                                                             const int* __restrict__ ip, int force, int staged_cap,
+                                                                 unsigned char* __restrict__ bin_of, int* __restrict__ perm,
+                                                                 int64_t* __restrict__ rowptr, Control* ctl, Control* host) {
   __shared__ ScatterLds sl;
   __shared__ ClassLds cl;
   __shared__ unsigned long long before, all;
@@ -689,12 +694,12 @@ __global__ __launch_bounds__(kScanThreads) void k_weight_sums(int64_t m, const i
   }
 }
 
-// first[t] = rows of the blocks before block t (t = 1 .. blocks - 1): the first boundary that has t / blocks of the whole weight in front of it; first[blocks + 1] = the
-// whole weight.  sums: of the tiles, exclusive afterwards.  One workgroup; a wave a boundary.
-// Bound by the chain of dependent loads.  (All rows' products copied to the host and added up there: an R-MAT graph of scale 17 in four blocks 6.30 ms | with
-// these kernels 6.16; scale 16 in eight, fp64, 3.79 | 3.72; scale 12 in two 0.544 | 0.535.)
-__global__ __launch_bounds__(kScanThreads) void k_block_rows(int64_t m, int64_t tiles, int blocks, const int* __restrict__ ip, unsigned long long* __restrict__ sums,
-                                                             long long* __restrict__ first) {
+// first[t] = rows of the blocks before block t (t = 1 .. blocks - 1): the first boundary that has t / blocks of the whole weight in front of it;
+// first[blocks + 1] = the whole weight.  sums: of the tiles, exclusive afterwards.  One workgroup; a wave a boundary.
+// Bound by the chain of dependent loads.  (All rows' products copied to the host and added up there: an R-MAT graph of scale 17 in four blocks 6.30
+// ms | with these kernels 6.16; scale 16 in eight, fp64, 3.79 | 3.72; scale 12 in two 0.544 | 0.535.)
+__global__ __launch_bounds__(kScanThreads) void k_block_rows(int64_t m, int64_t tiles, int blocks, const int* __restrict__ ip,
+    unsigned long long* __restrict__ sums, long long* __restrict__ first) {
   __shared__ unsigned long long all;
   const int lane = lane_id(), wave = threadIdx.x >> 6;
   if (wave == 0) {

@@ -228,12 +228,12 @@ __device__ __forceinline__ int64_t wave_first_not(int64_t n, F before) {
 }
 
 // Keys that the passes have sorted by their upper bits (key >> low) are sorted by all, with their payloads: a wave takes a bucket of at most
-// kBucketWave entries with the same upper bits, the workgroup one of at most kBucketGroup.  An entry's lower bits and its place in the bucket make one
-// word, so that a sort of distinct words (registers, lane_sort; sort_shares) is a stable one of the entries; the words then say
+// kBucketWave entries with the same upper bits, the workgroup one of at most kBucketGroup.  An entry's lower bits and its place in the bucket make
+// one word, so that a sort of distinct words (registers, lane_sort; sort_shares) is a stable one of the entries; the words then say
 // where payloads come from.  *too_long is set where a bucket has more entries, and its entries are left out: the caller sorts again by passes alone.
-// Bound: the loads that find a bucket (three to five that wait for each other), then the network and memory.  16.8 M components of 36 bits: three passes
-// of 188 us each with their counts | one of these kernels 135 to 150 us (166 to 210 with a search of all keys, 64 probes a round, for either end); 10^7
-// tensor entries of 33 bits 345 | 118 us.
+// Bound: the loads that find a bucket (three to five that wait for each other), then the network and memory.  16.8 M components of 36 bits: three
+// passes of 188 us each with their counts | one of these kernels 135 to 150 us (166 to 210 with a search of all keys, 64 probes a round, for either
+// end); 10^7 tensor entries of 33 bits 345 | 118 us.
 constexpr int kBucketWave = 512;
 static_assert(kBucketWave * 4 == kBucketGroup, "the waves' buckets and the workgroup's share LDS");
 template <typename P>
@@ -244,14 +244,14 @@ struct BucketLds {
 };
 
 template <typename K, typename P>
-__global__ __launch_bounds__(256) void k_sort_buckets(int64_t n, int64_t buckets, int low, const K* __restrict__ keys, const P* __restrict__ pay, K* __restrict__ keys_out,
-                                                      P* __restrict__ pay_out, int32_t* __restrict__ col_out, K col_mask, int* __restrict__ too_long) {
+__global__ __launch_bounds__(256) void k_sort_buckets(int64_t n, int64_t buckets, int low, const K* __restrict__ keys, const P* __restrict__ pay,
+    K* __restrict__ keys_out, P* __restrict__ pay_out, int32_t* __restrict__ col_out, K col_mask, int* __restrict__ too_long) {
   __shared__ BucketLds<P> lds;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
   const int64_t b0 = (int64_t)blockIdx.x * 4;
   {
-    // Where the wave's bucket begins and where it ends: half of the lanes look for either, 32 probes a round.  First around the place where it is if the
-    // keys are spread evenly up to the largest (a round of loads less, mostly two), otherwise everywhere.
+    // Where the wave's bucket begins and where it ends: half of the lanes look for either, 32 probes a round.  First around the place where it is if
+    // the keys are spread evenly up to the largest (a round of loads less, mostly two), otherwise everywhere.
     const int64_t b = b0 + wave + (lane >> 5);
     const int probe = lane & 31;
     auto before = [&](int64_t p) { return (int64_t)(keys[p] >> low) < b; };
@@ -261,7 +261,8 @@ __global__ __launch_bounds__(256) void k_sort_buckets(int64_t n, int64_t buckets
     const int64_t near = guess < 0 ? 0 : (guess < n ? guess : n - 1);
     const int held = held_of(before(near));
     const int src = (lane & 32) + (held > 0 ? held - 1 : 0), dst = (lane & 32) + (held < 32 ? held : 31);
-    int64_t lo = __shfl((long long)near, src, kWave) + 1, hi = __shfl((long long)near, dst, kWave);   // the first position that is not before is in [lo, hi]
+    // the first position that is not before is in [lo, hi]
+    int64_t lo = __shfl((long long)near, src, kWave) + 1, hi = __shfl((long long)near, dst, kWave);
     if (held == 0) lo = 0;
     if (held == 32) hi = n;
     if (lo > hi) lo = hi;
@@ -347,10 +348,12 @@ __global__ __launch_bounds__(256) void k_sort_buckets(int64_t n, int64_t buckets
   }
 }
 
-// Counts a sample of the keys (key_at(p): the key of entry p) by their upper bits in counts[buckets + 1], which are cleared; *crowded (in host memory, cleared) is
-// set where one is met kSampleCrowded times (once: what goes to the host is slow; the last of the counts says that it is on its way).  Of every kSampleStride consecutive entries one at a changing place: one in order, or with a period,
-// is seen as it is.  A workgroup's entries are counted in LDS first: atomics on one counter in memory take 12 ns each.
-// Bound by its chain of loads, LDS and atomics: 10^7 tensor entries 14 us, 27 where they crowd (one of 64 entries 24 and 47), 16 M products of an outer product 29.
+// Counts a sample of the keys (key_at(p): the key of entry p) by their upper bits in counts[buckets + 1], which are cleared; *crowded (in host
+// memory, cleared) is set where one is met kSampleCrowded times (once: what goes to the host is slow; the last of the counts says that it is on its
+// way).  Of every kSampleStride consecutive entries one at a changing place: one in order, or with a period, is seen as it is.  A workgroup's
+// entries are counted in LDS first: atomics on one counter in memory take 12 ns each.
+// Bound by its chain of loads, LDS and atomics: 10^7 tensor entries 14 us, 27 where they crowd (one of 64 entries 24 and 47), 16 M products of an
+// outer product 29.
 constexpr int kSampleThreads = 256;
 constexpr int kSamplePer = 2;
 __global__ __launch_bounds__(kSampleThreads) void k_sample_clear(unsigned buckets, unsigned* __restrict__ counts) {
@@ -358,7 +361,8 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_clear(unsigned bucket
   if (b <= buckets) counts[b] = 0;
 }
 template <class KeyAt>
-__global__ __launch_bounds__(kSampleThreads) void k_sort_sample(int64_t n, const KeyAt key_at, int low, unsigned buckets, unsigned* __restrict__ counts, int* __restrict__ crowded) {
+__global__ __launch_bounds__(kSampleThreads) void k_sort_sample(int64_t n, const KeyAt key_at, int low, unsigned buckets,
+    unsigned* __restrict__ counts, int* __restrict__ crowded) {
   constexpr unsigned kSlots = 2 * kSampleThreads * kSamplePer, kFree = ~0u;
   __shared__ unsigned bucket[kSlots], met[kSlots];
   for (unsigned t = threadIdx.x; t < kSlots; t += kSampleThreads) { bucket[t] = kFree; met[t] = 0; }

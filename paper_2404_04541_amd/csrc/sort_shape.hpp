@@ -42,15 +42,17 @@ inline SortShape sort_shape(int64_t n, int nbits, int first_bit = 0) {
 constexpr int kBucketMean = 192;
 constexpr int kBucketBits = 20;     // lower bits at most: with an entry's place (11 bits) they make a word that is not the largest
 constexpr int kBucketGroup = 2048;  // entries of a bucket at most: one that has more makes the sort begin again, by passes alone
-// So that this hardly ever happens, an entry of every kSampleStride is counted in its bucket beforehand, and where one of them is met kSampleCrowded times (an
-// estimate of 1800 entries) the passes sort by all bits from the start.  A bucket of 3000 entries is met so often in 98 of 100 sorts, one of 2100 in 7 of 10;
-// where keys are spread evenly (288 a bucket at most) one sort in 100 takes a bucket for crowded.
+// So that this hardly ever happens, an entry of every kSampleStride is counted in its bucket beforehand, and where one of them is met kSampleCrowded
+// times (an estimate of 1800 entries) the passes sort by all bits from the start.  A bucket of 3000 entries is met so often in 98 of 100 sorts, one
+// of 2100 in 7 of 10; where keys are spread evenly (288 a bucket at most) one sort in 100 takes a bucket for crowded.
 constexpr int64_t kSampleStride = 128;
 constexpr unsigned kSampleCrowded = 14;
-// Buckets only where they gain more than the sample costs where it finds them crowded: from a million entries of more than 32 bits on (passes of 64-bit keys).
-// Unfolding, us passes alone | buckets with the sample, keys spread evenly and crowded (coordinates drawn as cubes): 33 bits, 1 M entries 220 | 175 and 256 | 278, 3 M
-// 275 | 218 and 297 | 322, 10 M 725 | 540 and 743 | 792 (sorted twice, without the sample: 1416), 20 M 1294 | 1089 and 1317 | 1390; but 29 bits, 200 000 entries 115 | 111 and
-// 128 | 152, 3 M 186 | 173 and 217 | 255, 20 M 679 | 685.  Outer product of 32 M products 3300 | 2260, with a row of 80 000 of them 3300 | 3050 (sorted twice: 3800).
+// Buckets only where they gain more than the sample costs where it finds them crowded: from a million entries of more than 32 bits on (passes of
+// 64-bit keys).
+// Unfolding, us passes alone | buckets with the sample, keys spread evenly and crowded (coordinates drawn as cubes): 33 bits, 1 M entries 220 | 175
+// and 256 | 278, 3 M 275 | 218 and 297 | 322, 10 M 725 | 540 and 743 | 792 (sorted twice, without the sample: 1416), 20 M 1294 | 1089 and 1317 |
+// 1390; but 29 bits, 200 000 entries 115 | 111 and 128 | 152, 3 M 186 | 173 and 217 | 255, 20 M 679 | 685.  Outer product of 32 M products 3300 |
+// 2260, with a row of 80 000 of them 3300 | 3050 (sorted twice: 3800).
 constexpr int64_t kBucketMinEntries = (1 << 20) + 1;
 static_assert(kBucketMinEntries / 16 + 1025 <= kBucketMinEntries, "the sample's counts fit a buffer of keys");
 inline bool buckets_pay(int64_t n, int nbits) { return n >= kBucketMinEntries && nbits > 32; }

@@ -337,8 +337,9 @@ void drop_desc(spgemm_context* h, spgemm_plan_s* p) {   // (no kernel that uses 
 int count_chunk(spgemm_context* h, int64_t m) { return m >= (int64_t)256 * 2 * h->num_cus ? 256 : 64; }
 
 // Lengths of B's rows in a byte each for the row count: where the row pointer is half as large again as a die's 4 MB of L2 cache (600 000 rows,
-// 3 M lookups: no gain, and two launches of 10 us; 10^6 rows, 16 M lookups 225 | 169 us) and looked up more often than it has entries, and the table finds room where the lists of
-// rows come to lie afterwards.  (Rows that do not fit a byte are found on the way: the row count looks into the row pointer then.)
+// 3 M lookups: no gain, and two launches of 10 us; 10^6 rows, 16 M lookups 225 | 169 us) and looked up more often than it has entries, and the table
+// finds room where the lists of rows come to lie afterwards.  (Rows that do not fit a byte are found on the way: the row count looks into the row
+// pointer then.)
 bool row_lens_ok(const spgemm_csr* A, const spgemm_csr* B) {
   return B->rows * 8 > ((int64_t)6 << 20) && A->nnz >= 2 * B->rows && ceil_div(B->rows, kLensRows) * (int64_t)sizeof(RowLens) <= A->rows * 4;
 }
@@ -353,14 +354,16 @@ int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const sp
     const int chunk = count_chunk(h, m);
     hipLaunchKernelGGL(k_init_control, dim3(1), dim3(kCountThreads), 0, s, p->ctl, m, A->rowptr, chunk, h->num_cus);
     const unsigned parts = grid_for(B->nnz > B->rows ? B->nnz : B->rows, kCountThreads * 8, (int64_t)h->num_cus * 4);
-    const unsigned groups = m > 0 ? grid_for(m, chunk, (int64_t)h->num_cus * 2) : 0;   // (as many as run at a time; chunks are drawn: four times as many 500 000 rows 62 | 58 us)
+    // (as many as run at a time; chunks are drawn: four times as many 500 000 rows 62 | 58 us)
+    const unsigned groups = m > 0 ? grid_for(m, chunk, (int64_t)h->num_cus * 2) : 0;
     RowLens* lens = row_lens_ok(A, B) ? reinterpret_cast<RowLens*>(p->perm_sym) : nullptr;   // (perm_sym is written afterwards)
     if (lens)
-      hipLaunchKernelGGL(k_row_lens, dim3((unsigned)ceil_div(B->rows, kLensGroup * kLensRows)), dim3(kLensThreads), 0, s, B->rows, B->rowptr, m, A->nnz, A->rowptr, A->colidx,
-                         reinterpret_cast<unsigned*>(lens), p->ctl);
+      hipLaunchKernelGGL(k_row_lens, dim3((unsigned)ceil_div(B->rows, kLensGroup * kLensRows)), dim3(kLensThreads), 0, s, B->rows, B->rowptr, m,
+                         A->nnz, A->rowptr, A->colidx, reinterpret_cast<unsigned*>(lens), p->ctl);
     for (int with = lens ? 1 : 0; with >= 0; --with)
-      hipLaunchKernelGGL((with ? k_count_rows<true> : k_count_rows<false>), dim3(parts + groups), dim3(kCountThreads), 0, s, (int)parts, B->cols, B->nnz, B->colidx, m, A->nnz, B->rows,
-                         A->rowptr, A->colidx, B->rowptr, p->ip, p->bin, p->cnt, p->ctl, h->force, h->row_block, p->desc, lens);
+      hipLaunchKernelGGL((with ? k_count_rows<true> : k_count_rows<false>), dim3(parts + groups), dim3(kCountThreads), 0, s, (int)parts, B->cols,
+                         B->nnz, B->colidx, m, A->nnz, B->rows, A->rowptr, A->colidx, B->rowptr, p->ip, p->bin, p->cnt, p->ctl, h->force,
+                         h->row_block, p->desc, lens);
   }
   {
     Timer t(h, SPGEMM_K_BIN);
@@ -642,9 +645,11 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
   }
   if (m > 0) {
     if (!p->flag_rows && !p->desc && short_rows_ok(h, hist)) {
-      const SymShort sh{{short_grid(hist[3], 1), hist[2] ? record_grid(h, p, hist[2]) : 0u, short_grid(hist[1], 4), short_grid(hist[0], 16)}, p->perm_sym, p->ip, A->rowptr, B->rowptr,
-                        A->colidx, B->colidx, B->nnz, B->cols, pack32, pack128, p->cnt, p->esc_words[0], p->esc_words[1], p->records, p->record_rows, p->record_of, p->shift_of};
-      hipLaunchKernelGGL((p->alike ? k_sym_short<true> : k_sym_short<false>), dim3(sh.wgs[0] + sh.wgs[1] + sh.wgs[2] + sh.wgs[3]), dim3(256), sym_short_lds(), s, p->ctl, sh);
+      const SymShort sh{{short_grid(hist[3], 1), hist[2] ? record_grid(h, p, hist[2]) : 0u, short_grid(hist[1], 4), short_grid(hist[0], 16)},
+          p->perm_sym, p->ip, A->rowptr, B->rowptr, A->colidx, B->colidx, B->nnz, B->cols, pack32, pack128, p->cnt, p->esc_words[0], p->esc_words[1],
+          p->records, p->record_rows, p->record_of, p->shift_of};
+      hipLaunchKernelGGL((p->alike ? k_sym_short<true> : k_sym_short<false>), dim3(sh.wgs[0] + sh.wgs[1] + sh.wgs[2] + sh.wgs[3]), dim3(256),
+                         sym_short_lds(), s, p->ctl, sh);
     } else {
       {
         Timer t(h, SPGEMM_K_SYM_ESC);
@@ -652,24 +657,28 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
           auto rows = [&](auto wpl) {
             constexpr int W = decltype(wpl)::value;
             if (hist[0])
-              hipLaunchKernelGGL((k_flag_sym<32, W>), dim3(grid_for(hist[0], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0, A->rowptr, A->colidx, B->rowptr, B->colidx, B->nnz, p->cnt);
+              hipLaunchKernelGGL((k_flag_sym<32, W>), dim3(grid_for(hist[0], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0,
+                                 A->rowptr, A->colidx, B->rowptr, B->colidx, B->nnz, p->cnt);
             if (hist[1])
-              hipLaunchKernelGGL((k_flag_sym<128, W>), dim3(grid_for(hist[1], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx, B->rowptr, B->colidx, B->nnz, p->cnt);
+              hipLaunchKernelGGL((k_flag_sym<128, W>), dim3(grid_for(hist[1], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1,
+                                 A->rowptr, A->colidx, B->rowptr, B->colidx, B->nnz, p->cnt);
           };
           with_flag_words(B->cols, rows);
         }
         if (hist[0] && !p->flag_rows)
-          hipLaunchKernelGGL((p->desc ? k_esc_sym<16, 32, true> : k_esc_sym<16, 32, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0, A->rowptr, A->colidx,
-                             B->rowptr, p->desc, B->colidx, B->nnz, pack32, p->cnt, p->esc_words[0]);
+          hipLaunchKernelGGL((p->desc ? k_esc_sym<16, 32, true> : k_esc_sym<16, 32, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s,
+                             p->perm_sym, p->ctl, 0, A->rowptr, A->colidx, B->rowptr, p->desc, B->colidx, B->nnz, pack32, p->cnt, p->esc_words[0]);
         if (hist[1] && !p->flag_rows)
-          hipLaunchKernelGGL((p->desc ? k_esc_sym<64, 128, true> : k_esc_sym<64, 128, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx,
-                             B->rowptr, p->desc, B->colidx, B->nnz, pack128, p->cnt, p->esc_words[1]);
+          hipLaunchKernelGGL((p->desc ? k_esc_sym<64, 128, true> : k_esc_sym<64, 128, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0,
+                             s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx, B->rowptr, p->desc, B->colidx, B->nnz, pack128, p->cnt,
+                             p->esc_words[1]);
       }
       {
         Timer t(h, SPGEMM_K_SYM_HASH);
         if (hist[2])
-          hipLaunchKernelGGL((p->alike ? k_sym_wave<true> : k_sym_wave<false>), dim3(record_grid(h, p, hist[2])), dim3(256), 0, s, p->perm_sym, p->ctl, 2, A->rowptr, A->colidx,
-                             B->rowptr, B->colidx, B->nnz, p->cnt, p->records, p->record_rows, p->record_of, p->shift_of);
+          hipLaunchKernelGGL((p->alike ? k_sym_wave<true> : k_sym_wave<false>), dim3(record_grid(h, p, hist[2])), dim3(256), 0, s, p->perm_sym,
+                             p->ctl, 2, A->rowptr, A->colidx, B->rowptr, B->colidx, B->nnz, p->cnt, p->records, p->record_rows, p->record_of,
+                             p->shift_of);
         if (hist[3])
           hipLaunchKernelGGL((k_hash<256, 12, T, false>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
                              lds_hash_large, s, p->perm_sym, p->ctl, 0, 3, p->ip, A->rowptr, A->colidx,
@@ -693,8 +702,9 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     Timer t(h, SPGEMM_K_SCAN);
     const int direct = p->scan_blocks <= kScanDirect ? 1 : 0;
     if (!direct) hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanBlockThreads), 0, s, p->scan_blocks, p->partial, m, c_rowptr, p->ctl);
-    hipLaunchKernelGGL((p->scan_blocks == 1 ? k_scan_final<true> : k_scan_final<false>), dim3(p->scan_blocks > 0 ? (unsigned)p->scan_blocks : 1u), dim3(kScanThreads), 0, s, m,
-                       p->scan_blocks, direct, p->cnt, p->partial, p->ip, h->force, staged, p->bin, p->perm_num, c_rowptr, p->ctl, pinned);
+    hipLaunchKernelGGL((p->scan_blocks == 1 ? k_scan_final<true> : k_scan_final<false>), dim3(p->scan_blocks > 0 ? (unsigned)p->scan_blocks : 1u),
+                       dim3(kScanThreads), 0, s, m, p->scan_blocks, direct, p->cnt, p->partial, p->ip, h->force, staged, p->bin, p->perm_num,
+                       c_rowptr, p->ctl, pinned);
   }
   HIP_TRY(h, hipGetLastError());
   return SPGEMM_OK;
@@ -741,9 +751,11 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
   const int most_ip = tiles3 ? kSymHashLarge : 0x7fffffff;
   const bool row_tiles = tiles3 && B->cols <= kRowTileMaxCols;
   auto other_order_rows = [&] {
-    const unsigned w0 = words0 ? grid_for(hist[0], 16, cap_small) : 0, w1 = words1 ? grid_for(hist[1], 4, cap_small) : 0, w2 = p->recorded ? grid_for(hist[2], 4, cap_small) : 0;
-    hipLaunchKernelGGL(k_other_order<T>, dim3(w0 + w1 + w2), dim3(256), other_order_lds_bytes<T>(), s, w0, w1, w2, p->perm_num, p->ctl, p->ip, A->rowptr,
-                       A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, pack128, B->nnz, B->cols, inside ? 1 : 0);
+    const unsigned w0 = words0 ? grid_for(hist[0], 16, cap_small) : 0, w1 = words1 ? grid_for(hist[1], 4, cap_small) : 0,
+        w2 = p->recorded ? grid_for(hist[2], 4, cap_small) : 0;
+    hipLaunchKernelGGL(k_other_order<T>, dim3(w0 + w1 + w2), dim3(256), other_order_lds_bytes<T>(), s, w0, w1, w2, p->perm_num, p->ctl, p->ip,
+                       A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, pack128, B->nnz, B->cols, inside ? 1
+                       : 0);
   };
   if (!p->flag_rows && !p->desc && !inside && !check3 && short_rows_ok(h, hist)) {
     if (check) sum_order(h, p, A, B, 0);
@@ -776,23 +788,25 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
         auto rows = [&](auto wpl) {
           constexpr int W = decltype(wpl)::value;
           if (hist[0])
-            hipLaunchKernelGGL((k_flag_num<32, W, T>), dim3(grid_for(hist[0], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 0, A->rowptr, A->colidx, a_val,
-                               B->rowptr, B->colidx, b_val, B->nnz, c_rp, c_col, c_val);
+            hipLaunchKernelGGL((k_flag_num<32, W, T>), dim3(grid_for(hist[0], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 0,
+                               A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, B->nnz, c_rp, c_col, c_val);
           if (hist[1])
-            hipLaunchKernelGGL((k_flag_num<128, W, T>), dim3(grid_for(hist[1], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, A->rowptr, A->colidx, a_val,
-                               B->rowptr, B->colidx, b_val, B->nnz, c_rp, c_col, c_val);
+            hipLaunchKernelGGL((k_flag_num<128, W, T>), dim3(grid_for(hist[1], kFlagRows, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1,
+                               A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, B->nnz, c_rp, c_col, c_val);
         };
         with_flag_words(B->cols, rows);
       } else if (words0)
-        hipLaunchKernelGGL((p->desc ? k_esc_num<16, 32, T, true> : k_esc_num<16, 32, T, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 0,
-                           A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[0], c_rp, c_col, c_val);
+        hipLaunchKernelGGL((p->desc ? k_esc_num<16, 32, T, true> : k_esc_num<16, 32, T, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256),
+                           0, s, p->perm_sym, p->ctl, 0, A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[0], c_rp,
+                           c_col, c_val);
       else if (hist[0])
         hipLaunchKernelGGL((k_esc<16, 32, T>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 0,
                            A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, B->nnz);
       if (p->flag_rows) {
       } else if (words1)
-        hipLaunchKernelGGL((p->desc ? k_esc_num<64, 128, T, true> : k_esc_num<64, 128, T, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_sym, p->ctl, 1,
-                           A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[1], c_rp, c_col, c_val);
+        hipLaunchKernelGGL((p->desc ? k_esc_num<64, 128, T, true> : k_esc_num<64, 128, T, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256),
+                           0, s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[1], c_rp,
+                           c_col, c_val);
       else if (hist[1])
         hipLaunchKernelGGL((k_esc<64, 128, T>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 1,
                            A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack128, B->nnz);
@@ -806,11 +820,13 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
         if (inside) {
           const int64_t most = A->nnz > B->nnz ? A->nnz : B->nnz;
           const OrderOperands order{(int)grid_for(most, kOrderInsideTile, kOrderParts), A->nnz, B->nnz, A->colidx, same ? nullptr : B->colidx};
-          hipLaunchKernelGGL((p->alike ? k_num_recorded<T, true, true> : k_num_recorded<T, true, false>), dim3(grid + order.parts), dim3(256), 0, s, p->perm_sym, p->ctl, 2, p->records, p->record_of, p->shift_of,
-                             A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val, order);
+          hipLaunchKernelGGL((p->alike ? k_num_recorded<T, true, true> : k_num_recorded<T, true, false>), dim3(grid + order.parts), dim3(256), 0, s,
+                             p->perm_sym, p->ctl, 2, p->records, p->record_of, p->shift_of, A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz,
+                             c_rp, c_col, c_val, order);
         } else {
-          hipLaunchKernelGGL((p->alike ? k_num_recorded<T, false, true> : k_num_recorded<T, false, false>), dim3(grid), dim3(256), 0, s, p->perm_sym, p->ctl, 2, p->records, p->record_of, p->shift_of,
-                             A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col, c_val, OrderOperands{});
+          hipLaunchKernelGGL((p->alike ? k_num_recorded<T, false, true> : k_num_recorded<T, false, false>), dim3(grid), dim3(256), 0, s, p->perm_sym,
+                             p->ctl, 2, p->records, p->record_of, p->shift_of, A->rowptr, A->colidx, a_val, B->rowptr, b_val, B->nnz, c_rp, c_col,
+                             c_val, OrderOperands{});
         }
       }
       if (hist[2] > p->recorded)
@@ -820,8 +836,9 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
       if (check) other_order_rows();
       if (rows3) {
         if (row_tiles)
-          hipLaunchKernelGGL(k_row_tiles<T>, dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(kRowTileWaves * kWave), row_tile_lds<T>(B->cols), s,
-                             p->perm_num, p->ctl, p->ip, most_ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, B->nnz, B->cols, c_rp, c_col, c_val, looked3);
+          hipLaunchKernelGGL(k_row_tiles<T>, dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(kRowTileWaves * kWave),
+                             row_tile_lds<T>(B->cols), s, p->perm_num, p->ctl, p->ip, most_ip, A->rowptr, A->colidx, a_val, B->rowptr, B->colidx,
+                             b_val, B->nnz, B->cols, c_rp, c_col, c_val, looked3);
         else
           hipLaunchKernelGGL((k_hash<256, 11, T, true>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
                              lds_hash_large, s, p->perm_num, p->ctl, 1, 3, p->ip, A->rowptr, A->colidx, a_val, B->rowptr,
@@ -1201,8 +1218,8 @@ int sort_pairs(spgemm_context* h, int64_t n, const SortShape& sh, K* const keys[
   if constexpr (sizeof(K) == 8) {   // (narrow keys have no buckets: buckets_pay)
     if (low > 0) {
       const int64_t buckets = (int64_t)1 << (sh.passes * sh.bits);   // (the passes may have sorted by a bit or two above the keys')
-      hipLaunchKernelGGL((k_sort_buckets<K, P>), dim3((unsigned)ceil_div(buckets, 4)), dim3(256), 0, s, n, buckets, low, keys[cur], pay_in, keys[1 - cur], pay_a, col_out,
-                         col_mask, too_long);
+      hipLaunchKernelGGL((k_sort_buckets<K, P>), dim3((unsigned)ceil_div(buckets, 4)), dim3(256), 0, s, n, buckets, low, keys[cur], pay_in,
+                         keys[1 - cur], pay_a, col_out, col_mask, too_long);
       cur = 1 - cur;
     }
   }
@@ -1221,9 +1238,10 @@ class BucketSample {
     flag_ = reinterpret_cast<int*>(block_.p);
     *flag_ = 0;
     const unsigned buckets = 1u << (nbits - plan.low);
-    hipLaunchKernelGGL(k_sample_clear, dim3((unsigned)ceil_div(buckets + 1, kSampleThreads)), dim3(kSampleThreads), 0, h->stream, buckets, static_cast<unsigned*>(counts));
-    hipLaunchKernelGGL(k_sort_sample<KeyAt>, dim3((unsigned)ceil_div(ceil_div(n, kSampleStride), kSampleThreads * kSamplePer)), dim3(kSampleThreads), 0, h->stream, n, key_at, plan.low,
-                       buckets, static_cast<unsigned*>(counts), flag_);
+    hipLaunchKernelGGL(k_sample_clear, dim3((unsigned)ceil_div(buckets + 1, kSampleThreads)), dim3(kSampleThreads), 0, h->stream, buckets,
+                       static_cast<unsigned*>(counts));
+    hipLaunchKernelGGL(k_sort_sample<KeyAt>, dim3((unsigned)ceil_div(ceil_div(n, kSampleStride), kSampleThreads * kSamplePer)), dim3(kSampleThreads),
+                       0, h->stream, n, key_at, plan.low, buckets, static_cast<unsigned*>(counts), flag_);
     done_ = take_event(h);
     if (done_ && hipEventRecord(done_, h->stream) != hipSuccess) {
       (void)hipGetLastError();
@@ -1283,11 +1301,12 @@ void unfold_launch(spgemm_context* h, const ModeView& v, int64_t nnz, const T* x
     SortPlan plan = sort_plan(nnz, col_bits + row_bits, plain || !buckets_pay(nnz, col_bits + row_bits));
     int* flags = reinterpret_cast<int*>(tmp + lay.o_bad);
     BucketSample sample(h, nnz, col_bits + row_bits, true, plan, TensorKey<unsigned long long>{v.A, v.B, v.C, col_bits, v.xa, v.xb, v.xc}, keys[1]);
-    hipLaunchKernelGGL(k_tensor_keys<K>, dim3(plan.sh.ranges), dim3(kSortThreads), 0, s, nnz, plan.sh.per_range, v.A, v.B, v.C, col_bits, plan.sh.first_bit, plan.sh.bits, v.xa, v.xb,
-                       v.xc, keys[0], counters + kSortBins, flags);
+    hipLaunchKernelGGL(k_tensor_keys<K>, dim3(plan.sh.ranges), dim3(kSortThreads), 0, s, nnz, plan.sh.per_range, v.A, v.B, v.C, col_bits,
+                       plan.sh.first_bit, plan.sh.bits, v.xa, v.xb, v.xc, keys[0], counters + kSortBins, flags);
     const bool crowded = sample.crowded();
     if (crowded) plan = sort_plan(nnz, col_bits + row_bits, true);
-    cur = sort_pairs<K, T>(h, nnz, plan.sh, keys, xval, val, reinterpret_cast<T*>(tmp + lay.o_v), counters, !crowded, col, (K)(((K)1 << col_bits) - 1), plan.low, flags + 1);
+    cur = sort_pairs<K, T>(h, nnz, plan.sh, keys, xval, val, reinterpret_cast<T*>(tmp + lay.o_v), counters, !crowded, col,
+        (K)(((K)1 << col_bits) - 1), plan.low, flags + 1);
   }
   hipLaunchKernelGGL(k_key_ptr<K>, dim3((unsigned)ceil_div(rows + 1, kPtrRows)), dim3(256), 0, s, nnz, rows, col_bits, keys[cur], rp);
 }
@@ -1304,11 +1323,15 @@ int unfold_run(spgemm_context* h, const ModeView& v, int64_t nnz, const void* xv
   for (int plain = 0; plain < 2; ++plain) {
     hipLaunchKernelGGL(k_clear_ints, dim3(1), dim3(64), 0, s, bad);
     if (dtype == SPGEMM_F32) {
-      if (narrow) unfold_launch<uint32_t>(h, v, nnz, static_cast<const float*>(xval), tmp, lay, col_bits, row_bits, plain != 0, rp, col, static_cast<float*>(val));
-      else unfold_launch<unsigned long long>(h, v, nnz, static_cast<const float*>(xval), tmp, lay, col_bits, row_bits, plain != 0, rp, col, static_cast<float*>(val));
+      if (narrow) unfold_launch<uint32_t>(h, v, nnz, static_cast<const float*>(xval), tmp, lay, col_bits, row_bits, plain != 0, rp, col,
+          static_cast<float*>(val));
+      else unfold_launch<unsigned long long>(h, v, nnz, static_cast<const float*>(xval), tmp, lay, col_bits, row_bits, plain != 0, rp, col,
+          static_cast<float*>(val));
     } else {
-      if (narrow) unfold_launch<uint32_t>(h, v, nnz, static_cast<const double*>(xval), tmp, lay, col_bits, row_bits, plain != 0, rp, col, static_cast<double*>(val));
-      else unfold_launch<unsigned long long>(h, v, nnz, static_cast<const double*>(xval), tmp, lay, col_bits, row_bits, plain != 0, rp, col, static_cast<double*>(val));
+      if (narrow) unfold_launch<uint32_t>(h, v, nnz, static_cast<const double*>(xval), tmp, lay, col_bits, row_bits, plain != 0, rp, col,
+          static_cast<double*>(val));
+      else unfold_launch<unsigned long long>(h, v, nnz, static_cast<const double*>(xval), tmp, lay, col_bits, row_bits, plain != 0, rp, col,
+          static_cast<double*>(val));
     }
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(flags, bad, 8, hipMemcpyDeviceToHost, s);
@@ -1480,10 +1503,12 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
     std::vector<long long> first((size_t)nblocks + 2);
     const int chunk = count_chunk(h, m);
     hipLaunchKernelGGL(k_init_control, dim3(1), dim3(kCountThreads), 0, h->stream, ctl, m, A->rowptr, chunk, h->num_cus);
-    hipLaunchKernelGGL(k_count_rows<false>, dim3(grid_for(m, chunk, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, h->stream, 0, B->cols, B->nnz, B->colidx, m,
-                       A->nnz, B->rows, A->rowptr, A->colidx, B->rowptr, ip, tmp + o_bin, reinterpret_cast<int*>(tmp + o_cnt), ctl, 0, 0, (unsigned long long*)nullptr, (const RowLens*)nullptr);
+    hipLaunchKernelGGL(k_count_rows<false>, dim3(grid_for(m, chunk, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, h->stream, 0, B->cols, B->nnz,
+                       B->colidx, m, A->nnz, B->rows, A->rowptr, A->colidx, B->rowptr, ip, tmp + o_bin, reinterpret_cast<int*>(tmp + o_cnt), ctl, 0,
+                       0, (unsigned long long*)nullptr, (const RowLens*)nullptr);
     hipLaunchKernelGGL(k_weight_sums, dim3((unsigned)tiles), dim3(kScanThreads), 0, h->stream, m, ip, sums);
-    hipLaunchKernelGGL(k_block_rows, dim3(1), dim3(kScanThreads), 0, h->stream, m, tiles, nblocks, ip, sums, reinterpret_cast<long long*>(tmp + o_first));
+    hipLaunchKernelGGL(k_block_rows, dim3(1), dim3(kScanThreads), 0, h->stream, m, tiles, nblocks, ip, sums,
+                       reinterpret_cast<long long*>(tmp + o_first));
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(first.data(), tmp + o_first, first.size() * 8, hipMemcpyDeviceToHost, h->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(&host, ctl, sizeof(Control), hipMemcpyDeviceToHost, h->stream);
@@ -1678,7 +1703,8 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
   double* vals[2] = {bufs.get<double>((size_t)cap), bufs.get<double>((size_t)cap)};
   unsigned* counters = bufs.get<unsigned>(sort_counter_bytes(cap) / 4);   // (the last batch is shorter and may take more ranges)
   int* too_long = bufs.get<int>(2);
-  if (!keys[0] || !keys[1] || !vals[0] || !vals[1] || !counters || !too_long) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the accumulation array failed");
+  if (!keys[0] || !keys[1] || !vals[0] || !vals[1] || !counters || !too_long)
+    return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the accumulation array failed");
   // all array: sorted, unique coordinates with their sums
   unsigned long long* all_k = nullptr;
   double* all_v = nullptr;
@@ -1715,10 +1741,12 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
       const SortShape& sh = plan.sh;
       hipLaunchKernelGGL(k_clear_ints, dim3(1), dim3(64), 0, s, too_long);
       // (the batches after the first are taken to be like it; one that is not is sorted again)
-      BucketSample sample(h, cnt, col_bits + bits_of(m), t0 == 0, plan, OuterKey{(int64_t)t0, na, col_bits, off, match, A->ptr, B->ptr, A->idx, B->idx}, keys[1]);
+      const OuterKey key_at{(int64_t)t0, na, col_bits, off, match, A->ptr, B->ptr, A->idx, B->idx};
+      BucketSample sample(h, cnt, col_bits + bits_of(m), t0 == 0, plan, key_at, keys[1]);
       // insert
-      hipLaunchKernelGGL(k_outer_insert<T>, dim3(sh.ranges), dim3(kSortThreads), 0, s, (int64_t)t0, cnt, sh.per_range, sh.first_bit, sh.bits, na, off, match, A->ptr, A->idx,
-                         static_cast<const T*>(A->values), B->ptr, B->idx, static_cast<const T*>(B->values), col_bits, keys[0], vals[0], counters + kSortBins);
+      hipLaunchKernelGGL(k_outer_insert<T>, dim3(sh.ranges), dim3(kSortThreads), 0, s, (int64_t)t0, cnt, sh.per_range, sh.first_bit, sh.bits, na,
+                         off, match, A->ptr, A->idx, static_cast<const T*>(A->values), B->ptr, B->idx, static_cast<const T*>(B->values), col_bits,
+                         keys[0], vals[0], counters + kSortBins);
       // sort
       const bool crowded = sample.crowded();
       if (crowded) {
@@ -1727,7 +1755,8 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
       }
       const int steps = sh.passes + (plan.low > 0 ? 1 : 0);
       sorted = vals[steps & 1];
-      cur = sort_pairs<unsigned long long, double>(h, cnt, sh, keys, vals[0], sorted, vals[1 - (steps & 1)], counters, !crowded, nullptr, 0ULL, plan.low, too_long);
+      cur = sort_pairs<unsigned long long, double>(h, cnt, sh, keys, vals[0], sorted, vals[1 - (steps & 1)], counters, !crowded, nullptr, 0ULL,
+          plan.low, too_long);
       return plan.low > 0;
     };
     const bool buckets = insert_and_sort(plain_sorts);

@@ -34,10 +34,9 @@ struct TensorKey {   // of entry p
 
 // A workgroup takes one range of entries of the sort: keys and the range's counts of the first digit.
 template <typename Key>
-__global__ __launch_bounds__(kSortThreads) void k_tensor_keys(int64_t nnz, int64_t per_range, int64_t I, int64_t J, int64_t K, int col_bits, int shift, int bits,
-                                                              const int32_t* __restrict__ xi, const int32_t* __restrict__ xj,
-                                                              const int32_t* __restrict__ xk, Key* __restrict__ keys, unsigned* __restrict__ hist,
-                                                              int* __restrict__ bad) {
+__global__ __launch_bounds__(kSortThreads) void k_tensor_keys(int64_t nnz, int64_t per_range, int64_t I, int64_t J, int64_t K, int col_bits,
+    int shift, int bits, const int32_t* __restrict__ xi, const int32_t* __restrict__ xj, const int32_t* __restrict__ xk, Key* __restrict__ keys,
+    unsigned* __restrict__ hist, int* __restrict__ bad) {
   __shared__ unsigned cnt[kHistCopies][kSortBins];
   for (int d = threadIdx.x; d < kHistCopies * kSortBins; d += kSortThreads) (&cnt[0][0])[d] = 0;
   __syncthreads();

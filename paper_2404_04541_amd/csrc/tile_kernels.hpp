@@ -502,11 +502,11 @@ template <typename T>
 constexpr size_t row_tile_lds(int64_t n_cols) { return row_tile_bytes<T>(n_cols) + sizeof(TileScratch<T, true, kRowTileWaves>); }
 
 template <typename T>
-__device__ __forceinline__ void row_tiles_rows(unsigned char* smem, unsigned wg, unsigned wgs, const int* __restrict__ perm, const Control* __restrict__ ctl, const int* __restrict__ ip_row, int most_ip,
-                                                                        const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
-                                                                        const T* __restrict__ a_val, const int64_t* __restrict__ b_rp,
-                                                                        const int32_t* __restrict__ b_col, const T* __restrict__ b_val, int64_t b_nnz, int64_t n_cols,
-                                                                        const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val, int looked) {
+__device__ __forceinline__ void row_tiles_rows(unsigned char* smem, unsigned wg, unsigned wgs, const int* __restrict__ perm,
+    const Control* __restrict__ ctl, const int* __restrict__ ip_row, int most_ip, const int64_t* __restrict__ a_rp,
+    const int32_t* __restrict__ a_col, const T* __restrict__ a_val, const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col,
+    const T* __restrict__ b_val, int64_t b_nnz, int64_t n_cols, const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val,
+    int looked) {
   TileScratch<T, true, kRowTileWaves>* ts = reinterpret_cast<TileScratch<T, true, kRowTileWaves>*>(smem + row_tile_bytes<T>(n_cols));
   if (other_order(ctl, looked)) most_ip = 0x7fffffff;
   const unsigned first = ctl->offset[1][3], nrows = ctl->offset[1][4] - first;
@@ -537,7 +537,8 @@ __global__ __launch_bounds__(kRowTileWaves * kWave, 4) void k_row_tiles(const in
                                                                         const int64_t* __restrict__ c_rp, int32_t* __restrict__ c_col, T* __restrict__ c_val, int looked) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (ctl->error) return;
-  row_tiles_rows<T>(smem, blockIdx.x, gridDim.x, perm, ctl, ip_row, most_ip, a_rp, a_col, a_val, b_rp, b_col, b_val, b_nnz, n_cols, c_rp, c_col, c_val, looked);
+  row_tiles_rows<T>(smem, blockIdx.x, gridDim.x, perm, ctl, ip_row, most_ip, a_rp, a_col, a_val, b_rp, b_col, b_val, b_nnz, n_cols, c_rp, c_col,
+      c_val, looked);
 }
 
 template <typename T>
