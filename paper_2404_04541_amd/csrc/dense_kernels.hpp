@@ -32,6 +32,7 @@
 //   per-row block offsets (ascending B rows), so a pass touches only its own products.
 #pragma once
 #include "common.hpp"
+#include "piece_pass.hpp"
 
 namespace spg {
 
@@ -112,9 +113,8 @@ struct __align__(16) RowScratch {   // (the tile planner's arrays, written 16 by
   static constexpr int kPieces = WAVES * kWave;   // A entries described in LDS at a time: one per thread
   long long start[kPieces];   // first B entry of each A entry's piece
   int plen[kPieces];          // piece length
-  int cpre[kPieces + 1];      // exclusive prefix of quad counts
-  int more[kPieces + 1];      // (the column decode stages kListStage entries per wave from `start` to here)
-  int red[2 * WAVES];
+  int cpre[kPieces + 1];      // exclusive prefix of chunk counts
+  int red[kPieces + 1];       // (the column decode stages kListStage entries per wave from `start` to here)
   int s_row;
   int pad;
   unsigned long long span_ip;       // products streamed since the owner last cleared it
@@ -142,32 +142,6 @@ __device__ __forceinline__ void block_excl_scan2(int a, int b, int& ea, int& eb,
   eb = pb + ib - b;
 }
 
-// The non-empty pieces that a pass walks, in LDS: first B entry, exclusive prefix of the quad counts (np + 1
-// values), length and (numeric) a_ik of every piece.
-template <typename T>
-struct PieceList {
-  const long long* s;
-  const int* cpre;
-  const int* len;
-  const T* av;
-};
-
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ long long uni64(long long v) {
-  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(unsigned long long)v);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)((unsigned long long)v >> 32));
-  return (long long)(((unsigned long long)hi << 32) | lo);
-}
-
-// Up to four consecutive elements of a piece.
-template <typename T>
-struct Quad {
-  int n = 0;   // elements that are left in the piece from the quad's first on (0: none)
-  T a{};       // a_ik of the piece
-  Run<int32_t, 4> col{};
-  Run<T, 4> b{};
-};
-
 // Visits every element of the pieces once.  A piece is cut into quads; the quads of all pieces are dealt to the waves in
 // contiguous shares of whole batches of 64, a lane takes a quad: one load of four columns and one of four values.  Which piece a lane's quad belongs to: lane i looks at where the i-th piece behind the one in hand begins and pushes
 // i + 1 to the lane whose quad that is; a running maximum spreads it to the lanes behind.
@@ -180,7 +154,7 @@ struct Quad {
 // next batch is prefetched (15.8 ms at scale 19 against 16.5).  At scale 20 the symbolic kernel lost a little against the chunks
 // (42.2 -> 43.7 ms), the numeric one gained 6 ms.
 template <int WAVES, bool WITH_VALUES, typename T, class G>
-__device__ __forceinline__ void quad_pass(int np, int nq, const PieceList<T> pl, const int32_t* __restrict__ b_col,
+__device__ __forceinline__ void quad_pass(int np, int nq, const PieceList<T, long long> pl, const int32_t* __restrict__ b_col,
                                           const T* __restrict__ b_val, int64_t b_nnz, G g) {
   const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
   np = uni(np);
@@ -273,17 +247,17 @@ __device__ __forceinline__ void stream_columns(int64_t a0, int d, const int32_t*
       for (int sh = 1; sh < kWave; sh <<= 1) wl += __shfl_xor(wl, sh, kWave);
       if (lane == 0 && wl) atomicAdd(&rs->span_ip, wl);
     }
-    int at, eq, np, tq;
-    block_excl_scan2<WAVES>(len > 0 ? 1 : 0, (len + 3) >> 2, at, eq, np, tq, rs->red);
+    const PieceCut cut = piece_chunks<WAVES>(len, rs->red);
     if (len > 0) {
-      rs->start[at] = s;
-      rs->plen[at] = len;
-      rs->cpre[at] = eq;
+      rs->start[cut.idx] = s;
+      rs->plen[cut.idx] = len;
+      rs->cpre[cut.idx] = cut.first;
     }
     __syncthreads();
-    SPG_CLK(clk_mark(&rs->clk, 2); clk_add(&rs->clk, 18, 1); clk_add(&rs->clk, 19, (unsigned long long)tq);)
-    if (tq > 0)
-      quad_pass<WAVES, false, int>(np, tq, PieceList<int>{rs->start, rs->cpre, rs->plen, nullptr}, b_col, static_cast<const int*>(nullptr), b_nnz, f);
+    SPG_CLK(clk_mark(&rs->clk, 2); clk_add(&rs->clk, 18, 1); clk_add(&rs->clk, 19, (unsigned long long)cut.chunks << cut.lanes);)
+    if (cut.chunks > 0)
+      piece_pass<WAVES, false, int, long long>(cut.pieces, cut.chunks, cut.lanes, PieceList<int, long long>{rs->start, rs->cpre, rs->plen, nullptr}, b_col,
+                                               static_cast<const int*>(nullptr), b_nnz, f);
     SPG_CLK(clk_mark(&rs->clk, 3);)
     __syncthreads();
     SPG_CLK(clk_mark(&rs->clk, 4);)
@@ -510,6 +484,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
                                                              int32_t* __restrict__ col_list, int direct_min, int no_tiles_ip,
                                                              int search_ratio, const int* __restrict__ bp, int nb1, int64_t b_nnz, int run_tiles, int wide) {
   constexpr int kThreads = WAVES * kWave;
+  constexpr bool kLook = WAVES == 16 && !ALONE;
   extern __shared__ __align__(16) unsigned char smem[];
   const int flag_words = sym_flag_words(n_cols);
   unsigned* flags = reinterpret_cast<unsigned*>(smem);                               // flag_words
@@ -518,6 +493,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
   if (ctl->error) return;
   const bool sorted = ctl->b_sorted != 0;
   const int64_t span = (int64_t)kSymFlagWords * 32;
+  const bool one = !ALONE || n_cols <= span;   // every column is in the span
   const int tid = threadIdx.x;
   const unsigned row_lo = ctl->offset[0][4], row_hi = ctl->offset[0][7];   // the dense bins, heaviest class last
   const unsigned tile_cap = ctl->tile_cap, run_cap = ctl->run_cap;
@@ -555,14 +531,29 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
       SPG_CLK(clk_mark(&rs->clk, 1); clk_add(&rs->clk, 17, 1);)
       const int lo = (int)c0;
       const int64_t hi = c1;
-      // the flag words are read first (reads of one address are broadcast), and only bits that are not set yet go
-      // through the atomic (hub columns are set early and hit by most pieces)
-      auto mark = [&](const Quad<int>& q) {
+      auto mark = [&](const Quad<int>& q, auto full) {
+        constexpr bool kFull = decltype(full)::value;
+        if (kFull && one) {
+          // (looking at the flag words first, so that only bits that are not set yet go through the atomic, gains where hub columns are hit by
+          // most pieces or columns many times - us without | with: R-MAT scale 17 1515 | 1450, dedup sweep of 30000 4390 | 4270, of 10000 2035 |
+          // 2060 - and loses where the kernel has fewer waves: scale 19 36.0 | 36.4 ms)
+          unsigned w[4];
+          if (kLook) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = flags[(unsigned)q.col.v[i] >> 5];
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const unsigned bit = 1u << (q.col.v[i] & 31);
+            if (!kLook || !(w[i] & bit)) atomicOr(&flags[(unsigned)q.col.v[i] >> 5], bit);
+          }
+          return;
+        }
         unsigned w[4];
         bool ok[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          ok[i] = i < q.n && q.col.v[i] >= lo && (int64_t)q.col.v[i] < hi;
+          ok[i] = i < q.n && (one || (q.col.v[i] >= lo && (int64_t)q.col.v[i] < hi));
           w[i] = flags[ok[i] ? (q.col.v[i] - lo) >> 5 : 0];
         }
 #pragma unroll
@@ -571,9 +562,9 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
           if (ok[i] && !(w[i] & bit)) atomicOr(&flags[(q.col.v[i] - lo) >> 5], bit);
         }
       };
-      if (n_cols > span && sorted && bp)
+      if (!one && sorted && bp)
         stream_columns(a0, d, a_col, b_rp, b_col, b_nnz, rs, TableRange{bp, nb1, (int)(c0 >> kBlkShift), (int)((c1 + kBlkCols - 1) >> kBlkShift)}, mark);
-      else if (n_cols > span && sorted)
+      else if (!one && sorted)
         stream_columns(a0, d, a_col, b_rp, b_col, b_nnz, rs, SearchRange{b_col, lo, hi}, mark);
       else
         stream_columns(a0, d, a_col, b_rp, b_col, b_nnz, rs, NoRange{}, mark);
@@ -826,7 +817,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
   SPG_CLK(clk_mark(&rs->clk, 9); clk_flush(&rs->clk, ctl->clk[0]);)
 }
 
-static_assert(sizeof(RowScratch<8>) % 16 == 0 && sizeof(RowScratch<16>) % 16 == 0 && alignof(TilePlan) == 16, "the planner's arrays start on 16 bytes");
+static_assert(4 * 8 <= RowScratch<8>::kPieces && sizeof(RowScratch<8>) % 16 == 0 && sizeof(RowScratch<16>) % 16 == 0 && alignof(TilePlan) == 16, "the planner's arrays start on 16 bytes");
 template <int WAVES>
 constexpr size_t sym_dense_lds(int64_t flag_words) { return (size_t)flag_words * 4 + sizeof(RowScratch<WAVES>) + sizeof(TilePlan); }
 // Half a span of flag words (64 KB): up to that many columns two workgroups of 8 waves share a compute unit.

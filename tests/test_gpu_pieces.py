@@ -1,0 +1,69 @@
+"""The walk over the pieces of B's rows in the dense workspaces: pieces around the sizes of quads and chunks, rows of
+one length and of many, the ends of B's arrays, more pieces than are described at a time, and enough rows that their
+runs are taken from both ends of the list."""
+import numpy as np
+import pytest
+
+from paper_2404_04541_amd import workloads as W
+from helpers import gpu_product, assert_matches_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def rows_of(lens, cols, rng, dtype, ordered=True):
+    """A matrix whose rows have these many distinct columns."""
+    col = [rng.choice(cols, n, replace=False, shuffle=not ordered) for n in lens]
+    col = [np.sort(c) if ordered else c for c in col]
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    c = np.concatenate(col).astype(np.int32)
+    return W.CSR(len(lens), cols, rp, c, rng.uniform(-1, 1, c.size).astype(dtype))
+
+
+def operands(lens, cols, products, dtype, rows=12, ordered=True, seed=5):
+    """A's rows ask for rows of B of these lengths, in turn and the last row of B among them, until so many products are made."""
+    rng = np.random.default_rng(seed)
+    b_lens = np.asarray(list(lens) * (1200 // len(lens) + 1))[:1200]
+    d = int(np.ceil(products / b_lens.mean()))
+    a = [np.sort(np.append(rng.choice(1199, min(d, 1200) - 1, replace=False), 1199)) for _ in range(rows)]
+    rp = np.arange(rows + 1, dtype=np.int64) * a[0].size
+    c = np.concatenate(a).astype(np.int32)
+    return W.CSR(rows, 1200, rp, c, rng.uniform(-1, 1, c.size).astype(dtype)), rows_of(b_lens, cols, rng, dtype, ordered)
+
+
+@pytest.mark.parametrize("lens", [(2,), (3, 5), (4,), (15, 17), (16,), (31, 32, 33), (63, 64, 65), (64,), (127, 129), (255, 256, 257), (1, 1000), (1, 2, 3, 4, 60, 61, 700)])
+@pytest.mark.parametrize("cols,dtype", [(3000, np.float32), (3000, np.float64), (300_000, np.float64), (600_000, np.float32)])
+def test_pieces_around_the_sizes_of_chunks(lens, cols, dtype):
+    A, B = operands(lens, cols, max(2100, 6 * max(lens)), dtype)
+    got = gpu_product(A, B)
+    assert_matches_oracle(A, B, got, what=f"pieces of {lens}")
+
+
+@pytest.mark.parametrize("lens", [(2, 3), (7, 64, 65), (300,)])
+@pytest.mark.parametrize("cols", [3000, 400_000, 1_200_000])
+def test_pieces_of_unordered_rows(lens, cols):
+    A, B = operands(lens, cols, 4000, np.float32, ordered=False)
+    got = gpu_product(A, B)
+    assert_matches_oracle(A, B, got, what=f"unordered pieces of {lens}")
+
+
+@pytest.mark.parametrize("d", [1023, 1024, 1025, 3000])
+def test_more_pieces_than_are_described_at_a_time(d):
+    rng = np.random.default_rng(7)
+    B = rows_of(rng.integers(1, 9, 4000), 20_000, rng, np.float64)
+    a = [np.sort(rng.choice(4000, d, replace=False)) for _ in range(5)]
+    A = W.CSR(5, 4000, np.arange(6, dtype=np.int64) * d, np.concatenate(a).astype(np.int32), rng.uniform(-1, 1, 5 * d))
+    got = gpu_product(A, B)
+    assert_matches_oracle(A, B, got, what=f"{d} pieces")
+
+
+@pytest.mark.parametrize("rows", [32_767, 32_768, 32_771])
+def test_runs_from_both_ends(rows):
+    """64 runs for each of 512 workgroups; a hundredth of the rows is ten times as heavy."""
+    rng = np.random.default_rng(9)
+    B = rows_of(np.full(400, 200), 2500, rng, np.float32)
+    d = np.where(np.arange(rows) % 100 == 7, 90, 9)
+    c = np.concatenate([np.sort(rng.choice(400, n, replace=False)) for n in d]).astype(np.int32)
+    A = W.CSR(rows, 400, np.concatenate([[0], np.cumsum(d)]).astype(np.int64), c, rng.uniform(-1, 1, c.size).astype(np.float32))
+    got = gpu_product(A, B)
+    assert_matches_oracle(A, B, got, what=f"{rows} rows")
+    assert got[3]["sym_bin_rows"][4] == rows
