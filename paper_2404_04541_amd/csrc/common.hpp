@@ -22,6 +22,8 @@ constexpr int kNumHashSmall = 192;   // bin 2: hash table with 256 slots, one wa
 constexpr int kNumHashLarge = 1536;  // bin 3: hash table with 2048 slots, 256 threads per row
 constexpr int64_t kDenseMid = 65536;     // bins 4/5/6: dense workspace, split by ip so that
 constexpr int64_t kDenseBig = 1048576;   // the heaviest rows are scheduled first
+constexpr int64_t kDenseLight = 12288;   // rows of bin 4 of at most so many products are scheduled behind its others
+constexpr int kLightBin = kNumBins;      // how the row count marks them
 // A row is in a dense numeric bin only if it was in a dense symbolic bin (cnt <= ip), so the
 // tile list that the dense symbolic kernel plans exists for every row the dense numeric kernel sees.
 static_assert(kSymHashLarge <= kNumHashLarge, "dense numeric rows need a dense symbolic pass");

@@ -46,9 +46,8 @@ constexpr int kRankBlkBytes = kBlkCols / 32 * 8;   // flag word + rank per 32 co
 constexpr int kRankEntryBytes = 8;                // sum per entry of a ranked tile (its column goes straight to C)
 constexpr int kDirectMinDefault = 6144; // a block with at least this many entries becomes a direct tile
 constexpr int kRunTiles = 16;           // tiles handed to a workgroup at a time
-constexpr int kListSlab = 1 << 20;      // list entries, tile and run records that a symbolic workgroup draws at a time
+constexpr int kListSlab = 1 << 20;      // list entries and tile records that a symbolic workgroup draws at a time
 constexpr int kTileSlab = 2048;
-constexpr int kRunSlab = 256;           // (run records: at most; see run_slab)
 constexpr int kDirectBit = 1 << 30;     // in TileRec::cnt
 constexpr int kSearchBit = 1 << 29;     // in TileRec::cnt: a searched tile (ranks by bisection of the column list)
 constexpr int kCountMask = kSearchBit - 1;
@@ -85,15 +84,6 @@ __device__ __forceinline__ void stream_store(V* p, V v) { __builtin_nontemporal_
 template <typename V>
 __device__ __forceinline__ V stream_load(const V* p) { return __builtin_nontemporal_load(p); }
 
-// Run records that a symbolic workgroup draws at a time.  What a workgroup draws and does not use stays in the list as
-// an empty record that the numeric kernel steps over (two barriers, about 2 us), so the slab follows the rows a workgroup
-// gets: an eighth of them, 256 for the large products (where a draw per row cost 2.9 ms).  With 256 always, a product with
-// four dense rows per workgroup stepped over 252 empty records in every workgroup: 850 rows of 2600 products took
-// 753 us in the numeric kernel, and 52 us with slabs that follow the rows.
-__host__ __device__ __forceinline__ unsigned run_slab(int64_t rows, int64_t workgroups) {
-  const int64_t s = rows / (8 * workgroups);
-  return (unsigned)(s < 1 ? 1 : (s > kRunSlab ? kRunSlab : s));
-}
 // List entries that a symbolic workgroup draws at a time, at most: together a quarter of the list, so that a short list is not
 // spent on slack.
 __host__ __device__ __forceinline__ unsigned long long list_slab_of(unsigned long long list_cap, int64_t workgroups) {
@@ -316,7 +306,7 @@ struct SearchRange {   // binary search in an ascending row
 struct Slabs {
   unsigned long long list_used;         // list entries taken
   unsigned long long sl_pos, sl_left;   // left: list entries,
-  unsigned st_pos, st_left, sr_pos, sr_left;   // tile records, run records
+  unsigned st_pos, st_left;             // tile records
   unsigned used_tiles, used_runs;
 };
 
@@ -329,7 +319,9 @@ struct __align__(16) TilePlan {
   TileRec rec[kSpanBlocks];
   int ntiles, ndirect, nruns;
   int next_block;         // list decode: the next block to hand to a wave
-  unsigned tile_base, run_base;
+  unsigned tile_base;
+  unsigned place;         // of the row among the rows
+  unsigned run_first, run_base;   // where the span's first run goes, and its others
   int row_out;
   int span_out0;          // row_out when the span began
   long long list_base;    // position of the span's first entry (or first flag word) in the plan's list, -1 = none
@@ -436,6 +428,18 @@ __device__ __forceinline__ void plan_tail(TilePlan* tp, int nb, int block0, int 
   }
 }
 
+// The numeric kernels' runs lie in the order of the symbolic kernel's rows, the heaviest first, and workgroups draw them by number.  Where there are few for a workgroup
+// they are taken in that order, so that no workgroup is left with a long row at the end.  Where there are many, every draw of four is from the
+// front and the others are from the back: heavy rows use the memory, light ones wait for it, and both kinds do better beside the other.  Numeric kernel of
+// R-MAT squared, us in order | from both ends: scale 14 146 | 161, scale 16 746 | 768 (53 runs a workgroup), scale 17 2812 | 2774 (97), 18 8886 |
+// 7827, 19 25364 | 23041; 60 000 rows of 3600 products 1443 | 1409.  One of two and one of eight do less for the larger ones (19: 23413, 23494).
+constexpr unsigned kManyRuns = 64;
+__device__ __forceinline__ unsigned run_of(unsigned draw, unsigned nruns) {
+  if (nruns < kManyRuns * gridDim.x || draw >= nruns) return draw;
+  const unsigned q = draw / 4, r = draw % 4;
+  return r == 0 ? q : nruns - 3 * q - r;
+}
+
 // Takes `amount` from a shared cursor if that stays within `cap` (compare and advance: the cursor never
 // passes the capacity, so a request that does not fit costs later, smaller requests nothing).
 __device__ __forceinline__ bool reserve_below(unsigned long long* cursor, unsigned long long amount, unsigned long long cap,
@@ -461,18 +465,6 @@ __device__ __forceinline__ unsigned long long draw_below(unsigned long long* cur
   return base >= cap ? 0 : (cap - base < amount ? cap - base : amount);
 }
 
-// Fetch the next row of the dense symbolic bins (4..6), heaviest class first; -1 when none is left.
-__device__ __forceinline__ int next_dense_row(const int* __restrict__ perm, Control* ctl, int* s_row) {
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const unsigned lo = ctl->offset[0][4], hi = ctl->offset[0][7];
-    const unsigned idx = atomicAdd(&ctl->work[0], 1u);
-    *s_row = idx < hi - lo ? perm[hi - 1 - idx] : -1;
-  }
-  __syncthreads();
-  return *s_row;
-}
-
 // ALONE: LDS leaves room for one workgroup on a compute unit, so it may take the registers it wants (R-MAT scale 20: 45.8 ms in 64
 // registers, with spills, 44.4 in 75).  The narrow form of 16 waves spills seven registers (32 bytes a lane), outside its loops over products.
 template <int WAVES, bool ALONE>
@@ -493,24 +485,27 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
   if (ctl->error) return;
   const bool sorted = ctl->b_sorted != 0;
   const int64_t span = (int64_t)kSymFlagWords * 32;
-  const bool one = !ALONE || n_cols <= span;   // every column is in the span
   const int tid = threadIdx.x;
   const unsigned row_lo = ctl->offset[0][4], row_hi = ctl->offset[0][7];   // the dense bins, heaviest class last
   const unsigned tile_cap = ctl->tile_cap, run_cap = ctl->run_cap;
   const unsigned long long list_cap = ctl->list_cap;
   SPG_CLK(clk_begin(&rs->clk);)
-  int row = next_dense_row(perm, ctl, &rs->s_row);
-  int next_row = -1;   // (thread 0) the row after this one, fetched while this one is in the works
+  // The first row of a workgroup is its own by its number, the others are drawn from a counter.  A row's place among the rows is
+  // the place of its first run too.
+  const unsigned nrows = row_hi - row_lo;
+  const bool one = !ALONE || n_cols <= span;   // every column is in the span
+  int row = blockIdx.x < nrows ? perm[row_hi - 1 - blockIdx.x] : -1;
+  if (tid == 0) tp->place = blockIdx.x;
   // Thread 0's slabs of the plan's lists are in LDS (its registers would be everybody's), but where there are registers to spare (R-MAT
   // scale 20: 44.6 | 43.0 ms, scale 19, 8 waves, 12.27 | 12.10).  The first slab of
   // every workgroup is its own by its number (the cursors start behind these: k_set_caps); when all workgroups drew their
   // first slab from the shared cursors at the same moment, the compare-and-swaps of 256 of them took 0.2 ms (1071 rows: 366 -> 73 us).
   const unsigned long long list_slab = list_slab_of(list_cap, gridDim.x);
-  const unsigned rslab = run_slab(row_hi - row_lo, gridDim.x);
   Slabs own{};
   Slabs& sl = WAVES == 8 || ALONE ? own : tp->slabs;
   if (tid == 0)
-    sl = Slabs{0, blockIdx.x * list_slab, list_slab, blockIdx.x * (unsigned)kTileSlab, (unsigned)kTileSlab, blockIdx.x * rslab, rslab, 0, 0};
+    sl = Slabs{0, blockIdx.x * list_slab, list_slab, blockIdx.x * (unsigned)kTileSlab, (unsigned)kTileSlab, 0, 0};
+  int next_row = -1;   // (thread 0) the row after this one
   while (row >= 0) {
     unsigned nx = 0;   // (thread 0) the draw for the row after this one: on its way while this row is in the works
     if (tid == 0) nx = atomicAdd(&ctl->work[0], 1u);
@@ -568,6 +563,8 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
         stream_columns(a0, d, a_col, b_rp, b_col, b_nnz, rs, SearchRange{b_col, lo, hi}, mark);
       else
         stream_columns(a0, d, a_col, b_rp, b_col, b_nnz, rs, NoRange{}, mark);
+      const bool last_span = c1 >= n_cols;
+      const int ip_row = tid < kWave ? ip[row] : 0;   // (on its way while the entries are counted)
       // entries per block and per group: a wave takes a block, a lane four words of it, a group is a row of 16 lanes
       {
         static_assert(kBlkWords == 4 * kWave && kGrpWords == 64, "four words per lane, sixteen lanes per group");
@@ -585,14 +582,13 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
       }
       __syncthreads();
       SPG_CLK(clk_mark(&rs->clk, 5);)
-      const bool count_only = ip[row] <= no_tiles_ip;
-      const bool last_span = c1 >= n_cols;
+      const bool count_only = ip_row <= no_tiles_ip;
       const int block0 = (int)(c0 >> kBlkShift);
       if (tid < kWave) {
         plan_head(tp, nb, count_only);
         if (!count_only) plan_tail(tp, nb, block0, direct_min, wide ? kWideTileBudget : kTileBudget);
+        wave_sync_lds();
       }
-      __syncthreads();
       SPG_CLK(clk_mark(&rs->clk, 6);)
       if (tid == 0) {
         // Everything this span needs from the plan's shared lists, and the next row, in one round trip:
@@ -604,13 +600,12 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
         // Wide tiles: one of at most kSearchRow entries wherever a tile is saved.
         const int total = tp->cum[kSpanBlocks];
         const int nt = tp->ntiles;
-        const int nr = (nt + run_tiles - 1) / run_tiles;
         const bool want_list = !count_only && total > 0 && list_cap > 0;
         // a short row with little deduplication becomes one searched tile and needs its columns; every
         // other row keeps its flag words as they are (no decoding here, and far less memory for rows
         // with many entries) unless they would take much more room than the columns
         // (products of the span: counted by the walk when it covered a part of the row)
-        const long long span_products = (n_cols > span && sorted) ? (long long)rs->span_ip : (long long)ip[row];
+        const long long span_products = (n_cols > span && sorted) ? (long long)rs->span_ip : (long long)ip_row;
         // (a searched tile takes every product of its pieces: with unordered B rows the pieces are whole rows,
         // so the tile must be the whole row)
         bool search_row = (sorted || n_cols <= span) && total <= kSearchRow && nt > (wide ? 1 : total <= kSearchCap ? 2 : 4) && span_products <= (long long)search_ratio * total;
@@ -651,23 +646,25 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
             }
           }
         }
+        // (a searched tile pays a bisection per product: only for rows with little deduplication, and
+        // only where it saves tiles - a row that is one ranked or direct tile anyway stays that)
+        const bool as_searched = listed && search_row;
+        const int ntiles = as_searched ? (cut < nb ? 2 : 1) : nt;
+        const int nr = (ntiles + run_tiles - 1) / run_tiles;
+        const int placed = c0 == 0 ? 1 : 0;   // a row's first run has its place, so that the numeric kernel takes the rows in the same order
         bool room = true;
-        if (nt > 0) {
-          if ((unsigned)nt > sl.st_left) {
+        if (ntiles > 0) {
+          if ((unsigned)ntiles > sl.st_left) {
             sl.st_pos = atomicAdd(&ctl->tile_cursor, (unsigned)kTileSlab);
             room = sl.st_pos + (unsigned)kTileSlab <= tile_cap;
             sl.st_left = room ? (unsigned)kTileSlab : 0u;
           }
-          if (room && (unsigned)nr > sl.sr_left) {
-            for (unsigned i = 0; i < sl.sr_left; ++i) runs[sl.sr_pos + i].count = 0;   // (slots left behind: empty records)
-            const unsigned grab = (unsigned)nr > rslab ? (unsigned)nr : rslab;
-            sl.sr_pos = atomicAdd(&ctl->run_cursor, grab);
-            room = sl.sr_pos + grab <= run_cap;
-            sl.sr_left = room ? grab : 0u;
-          }
           if (room) {
-            tb = sl.st_pos; sl.st_pos += (unsigned)nt; sl.st_left -= (unsigned)nt;
-            rb = sl.sr_pos; sl.sr_pos += (unsigned)nr; sl.sr_left -= (unsigned)nr;
+            tb = sl.st_pos; sl.st_pos += (unsigned)ntiles; sl.st_left -= (unsigned)ntiles;
+            if (nr > placed) {
+              rb = atomicAdd(&ctl->run_cursor, (unsigned)(nr - placed));
+              room = rb + (unsigned)(nr - placed) <= run_cap;
+            }
           }
         }
         if (listed) sl.list_used += need;
@@ -675,27 +672,29 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
         tp->list_base = listed ? (long long)at : -1;
         tp->list_words = listed && as_words ? fwords : 0;
         tp->tile_base = tb;
-        tp->run_base = rb;
+        tp->run_base = rb - (unsigned)placed;
+        tp->run_first = placed ? tp->place : rb;
         tp->next_block = 0;
-        tp->nruns = nr;
-        if (nt > 0 && !room) {
+        tp->nruns = nr > placed ? nr : placed;   // (a row without tiles leaves an empty record)
+        tp->ntiles = ntiles;
+        if (!room) {
           ctl->error = 3;   // cannot happen when the host sized the lists from the bound
           tp->ntiles = 0;
-          tp->nruns = 0;
-        } else if (listed && search_row) {
-          // (a searched tile pays a bisection per product: only for rows with little deduplication, and
-          // only where it saves tiles - a row that is one ranked or direct tile anyway stays that)
+          tp->nruns = placed;
+        } else if (as_searched) {
           const int c0 = cut < nb ? tp->cum[cut] : total;
           tp->rec[0] = TileRec{block0, block0 + cut, c0 | kSearchBit, tp->span_out0};
           if (cut < nb) tp->rec[1] = TileRec{block0 + cut, block0 + nb, (total - c0) | kSearchBit, tp->span_out0 + c0};
-          tp->ntiles = cut < nb ? 2 : 1;
           atomicAdd(&ctl->search_tiles, 1u);
         } else if (tp->ndirect > 0) {
           atomicAdd(&ctl->direct_tiles, (unsigned)tp->ndirect);
         }
         sl.used_tiles += (unsigned)tp->ntiles;
-        sl.used_runs += (unsigned)tp->nruns;
-        if (last_span) next_row = nx < row_hi - row_lo ? perm[row_hi - 1 - nx] : -1;
+        sl.used_runs += (unsigned)(room ? nr : 0);
+        if (last_span) {
+          tp->place = gridDim.x + nx;
+          next_row = gridDim.x + nx < nrows ? perm[row_hi - 1 - (gridDim.x + nx)] : -1;
+        }
       }
       __syncthreads();
       SPG_CLK(clk_mark(&rs->clk, 7);)
@@ -703,11 +702,11 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
       const int nt = tp->ntiles;
       if (nt > 0 || tp->nruns > 0) {
         if (tid < nt) tiles[tp->tile_base + tid] = tp->rec[tid];
-        if (tid < tp->nruns) {   // (runs behind the tiles in use stay empty: count 0)
+        if (tid < tp->nruns) {
           const int left = nt - tid * run_tiles;
           // (flag words: the position of the word of column 0, which may lie before the span's words)
           const long long lpos = lb < 0 ? -1LL : (tp->list_words ? (lb + kListBias) | kListFlagWords : lb - tp->span_out0 + kListBias);
-          runs[tp->run_base + tid] = RunRec{row, tp->tile_base + (unsigned)(tid * run_tiles), left < 0 ? 0 : (left < run_tiles ? left : run_tiles), d, a0, lpos};
+          runs[tid == 0 ? tp->run_first : tp->run_base + tid] = RunRec{row, tp->tile_base + (unsigned)(tid * run_tiles), left < 0 ? 0 : (left < run_tiles ? left : run_tiles), d, a0, lpos};
         }
       }
       if (lb >= 0 && tp->list_words) {
@@ -798,18 +797,16 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
           }
         }
       }
+      if (tid == 0 && last_span) {
+        cnt[row] = tp->row_out;
+        rs->s_row = next_row;
+      }
       __syncthreads();
       SPG_CLK(clk_mark(&rs->clk, 8);)
     }
-    if (tid == 0) {
-      cnt[row] = tp->row_out;
-      rs->s_row = next_row;
-    }
-    __syncthreads();
     row = rs->s_row;
   }
   if (tid == 0) {
-    for (unsigned i = 0; i < sl.sr_left; ++i) runs[sl.sr_pos + i].count = 0;
     if (sl.used_tiles) atomicAdd(&ctl->tiles_used, sl.used_tiles);
     if (sl.used_runs) atomicAdd(&ctl->runs_used, sl.used_runs);
     if (sl.list_used) atomicAdd(&ctl->list_used, sl.list_used);

@@ -394,7 +394,7 @@ __global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int6
       const int bin = tid < nr ? classify_symbolic((long long)mine, force) : -1;
       if (tid < nr) {
         ip_out[r0 + tid] = mine > 0x7fffffffULL ? 0x7fffffff : (int)mine;
-        bin_out[r0 + tid] = (unsigned char)bin;
+        bin_out[r0 + tid] = (unsigned char)(bin == 4 && mine <= (unsigned long long)kDenseLight ? kLightBin : bin);
         if (bin == kEmptyBin) cnt_out[r0 + tid] = 0;
       }
       const int bins[1] = {bin};
@@ -435,9 +435,11 @@ __device__ __forceinline__ int64_t tile_row(int u) {
 }
 
 struct ScatterLds {
-  unsigned count[kNumBins][kScanWaves], base[kNumBins], offset[kNumBins + 1];
+  unsigned count[kNumBins + 1][kScanWaves], base[kNumBins + 1], offset[kNumBins + 1];
 };
-// hist: rows of every bin, of all tiles.
+// hist: rows of every bin, of all tiles.  LIGHT: bin 4 is filled from both ends, its lighter rows (kLightBin) from the first place on, the others
+// from the last one down (cursor[phase][kEmptyBin] counts these): k_sym_dense takes its rows from the end.
+template <bool LIGHT>
 __device__ __forceinline__ void scatter_bins(const int (&bin)[kScanItems], const unsigned* hist, int* __restrict__ perm, Control* ctl, int phase,
     ScatterLds* sl) {
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
@@ -449,7 +451,8 @@ __device__ __forceinline__ void scatter_bins(const int (&bin)[kScanItems], const
   int rank[kScanItems];
 #pragma unroll
   for (int u = 0; u < kScanItems; ++u) rank[u] = 0;
-  for (int v = 0; v < kNumBins - 1; ++v) {   // bin 7 holds rows with no work: not listed
+  for (int v = 0; v <= kLightBin; ++v) {
+    if (v == kEmptyBin || (v == kLightBin && !LIGHT)) continue;   // (rows with no work are not listed)
     unsigned before = 0;
 #pragma unroll
     for (int u = 0; u < kScanItems; ++u) {
@@ -460,16 +463,21 @@ __device__ __forceinline__ void scatter_bins(const int (&bin)[kScanItems], const
     if (lane == 0) sl->count[v][wave] = before;
   }
   __syncthreads();
-  if (tid < kNumBins - 1) {
+  if (tid < kNumBins - 1 || (LIGHT && tid == kLightBin)) {
     unsigned run = 0;
     for (int w = 0; w < kScanWaves; ++w) { const unsigned c = sl->count[tid][w]; sl->count[tid][w] = run; run += c; }
-    sl->base[tid] = run ? sl->offset[tid] + atomicAdd(&ctl->cursor[phase][tid], run) : 0u;
+    unsigned base = 0;
+    if (run) {
+      if (LIGHT && tid == 4) base = sl->offset[5] - run - atomicAdd(&ctl->cursor[phase][kEmptyBin], run);
+      else base = sl->offset[tid == kLightBin ? 4 : tid] + atomicAdd(&ctl->cursor[phase][tid == kLightBin ? 4 : tid], run);
+    }
+    sl->base[tid] = base;
   }
   if (blockIdx.x == 0 && tid <= kNumBins) ctl->offset[phase][tid] = sl->offset[tid];
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < kScanItems; ++u)
-    if (bin[u] >= 0 && bin[u] < kNumBins - 1) perm[sl->base[bin[u]] + sl->count[bin[u]][wave] + rank[u]] = (int)tile_row(u);
+    if (bin[u] >= 0 && bin[u] != kEmptyBin) perm[sl->base[bin[u]] + sl->count[bin[u]][wave] + rank[u]] = (int)tile_row(u);
 }
 
 // The control block to the host's copy (pinned memory), by one workgroup whose writes to it are done.
@@ -492,7 +500,7 @@ __global__ __launch_bounds__(kScanThreads) void k_bin_scatter(int64_t m, const u
     bin[u] = i < m ? bin_of[i] : -1;
   }
   // (an error of the count leaves rows without a bin; the one that is set below does not matter here, whoever sees it)
-  if (ctl->error != 1) scatter_bins(bin, ctl->hist[0], perm, ctl, 0, &sl);
+  if (ctl->error != 1) scatter_bins<true>(bin, ctl->hist[0], perm, ctl, 0, &sl);
   if (blockIdx.x == 0) {
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -667,7 +675,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_final(int64_t m, int64_t 
     const int64_t i = tile_row(u);
     if (i < m) rowptr[i] = run + excl[u];
   }
-  scatter_bins(bin, ONE ? cl.hist : ctl->hist[1], perm, ctl, 1, &sl);
+  scatter_bins<false>(bin, ONE ? cl.hist : ctl->hist[1], perm, ctl, 1, &sl);
   if (ONE && tid == kScanThreads - 1) { rowptr[m] = run + s; ctl->nnz_c = run + s; }
   if (blockIdx.x == 0) {
     if (!ONE && direct && tid == 0) { rowptr[m] = (int64_t)all; ctl->nnz_c = (long long)all; }

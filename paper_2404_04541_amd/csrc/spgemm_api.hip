@@ -453,15 +453,14 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
   if (ip_d / h->direct_min < direct) direct = ip_d / h->direct_min;
   const double entries = ip_d < rows_d * n ? ip_d : rows_d * n;
   const double weight = rows_d * blocks * kRankBlkBytes + (double)kRankEntryBytes * entries;
-  // (+ a slab per workgroup of the symbolic kernel: what a workgroup has drawn and not used; a row whose runs do not fit
-  // what is left of a run slab leaves fewer records behind than it takes, hence twice the runs)
+  // (+ a slab per workgroup of the symbolic kernel: what a workgroup has drawn and not used)
   p->blk_ptr_cols = (int)blocks + 1;
   const size_t bp_bytes = (size_t)B->rows * (size_t)p->blk_ptr_cols * 4;
   const bool with_bp = h->block_table && host.b_sorted && B->nnz > 0 && bp_bytes <= ((size_t)1 << 30);
   p->wide_tiles = wide_tiles_from(h, p, B, with_bp, rows_d, ip_d, h->row_block ? h->whole_ip : (double)host.ip_total);
   const double wgs = (double)sym_dense_shape(h, (int64_t)rows_d, B->cols).groups + 1.0;
   const double tiles = 2.0 * direct + 2.0 * weight / (p->wide_tiles ? kWideTileBudget : kTileBudget) + 4.0 * rows_d * spans + 16.0 + wgs * kTileSlab;
-  const double runs = 2.0 * ((tiles - wgs * kTileSlab) / run_tiles_of(h, (int64_t)rows_d) + rows_d * spans + 16.0) + wgs * kRunSlab;
+  const double runs = rows_d + (tiles - wgs * kTileSlab) / run_tiles_of(h, (int64_t)rows_d) + rows_d * spans + 16.0;
   if (tiles > 4.0e9) return fail(h, SPGEMM_UNSUPPORTED, "tile list of the dense workspace would exceed 2^32 records");
   *tile_cap = (unsigned)tiles;
   *run_cap = (unsigned)runs;
@@ -567,12 +566,13 @@ void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, co
   }
 }
 
-// Capacities of the dense workspace's lists, and their cursors behind the first slab of every workgroup of k_sym_dense.
+// Capacities of the dense workspace's lists, and their cursors behind the first slab of every workgroup of k_sym_dense (runs: behind a place
+// for every row).
 __global__ void k_set_caps(Control* ctl, unsigned tile_cap, unsigned run_cap, unsigned long long list_cap, int64_t rows, unsigned workgroups) {
   if (threadIdx.x == 0) {
     ctl->tile_cap = tile_cap; ctl->run_cap = run_cap; ctl->list_cap = list_cap;
     ctl->tile_cursor = workgroups * kTileSlab;
-    ctl->run_cursor = workgroups * run_slab(rows, workgroups);
+    ctl->run_cursor = (unsigned)rows;   // (a place for the first run of every row)
     ctl->list_cursor = workgroups * list_slab_of(list_cap, workgroups);
   }
 }

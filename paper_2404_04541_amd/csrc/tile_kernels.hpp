@@ -442,24 +442,19 @@ __global__ __launch_bounds__(kTileThreads, 8) void k_num_tiles(Control* ctl, con
   bool have_coming = false;
   SPG_CLK(clk_begin(&ts->clk);)
   if (tid < kRunWords) {
-    unsigned first = 0;
-    if (tid == 0) {
-      first = atomicAdd(&ctl->work[1], 1u);
-      drawn = atomicAdd(&ctl->work[1], 1u);
-    }
-    first = (unsigned)uni((int)first);
-    have_coming = first < nruns;
-    if (have_coming) coming = run_words[(size_t)first * kRunWords + tid];
+    if (tid == 0) drawn = atomicAdd(&ctl->work[1], 1u);
+    have_coming = blockIdx.x < nruns;   // (the first draw is the workgroup's own)
+    if (have_coming) coming = run_words[(size_t)run_of(blockIdx.x, nruns) * kRunWords + tid];
   }
   while (true) {
     __syncthreads();
     if (tid < kRunWords) {
       if (tid == 0) ts->s_run = have_coming ? 1 : -1;
       if (have_coming) reinterpret_cast<int*>(&ts->rr)[tid] = coming;
-      const unsigned next = (unsigned)uni((int)drawn);
+      const unsigned next = gridDim.x + (unsigned)uni((int)drawn);
       have_coming = next < nruns;
       if (have_coming) {
-        coming = run_words[(size_t)next * kRunWords + tid];
+        coming = run_words[(size_t)run_of(next, nruns) * kRunWords + tid];
         if (tid == 0) drawn = atomicAdd(&ctl->work[1], 1u);
       }
     }

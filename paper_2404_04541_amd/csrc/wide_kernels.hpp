@@ -494,19 +494,19 @@ __global__ __launch_bounds__(kWideThreads) void k_num_wide(Control* ctl, const u
   bool have_coming = false;
   SPG_CLK(clk_begin(&ns->clk);)
   if (tid == 0) {
-    const unsigned first = atomicAdd(&ctl->work[1], 1u);
     drawn = atomicAdd(&ctl->work[1], 1u);
-    have_coming = first < nruns;
-    if (have_coming) coming = runs[first];
+    have_coming = blockIdx.x < nruns;   // (the first draw is the workgroup's own)
+    if (have_coming) coming = runs[run_of(blockIdx.x, nruns)];
   }
   while (true) {
     __syncthreads();
     if (tid == 0) {
       ns->s_run = have_coming ? 1 : -1;
       if (have_coming) ns->rr = coming;
-      have_coming = drawn < nruns;
+      const unsigned next = gridDim.x + drawn;
+      have_coming = next < nruns;
       if (have_coming) {
-        coming = runs[drawn];
+        coming = runs[run_of(next, nruns)];
         drawn = atomicAdd(&ctl->work[1], 1u);
       }
     }
