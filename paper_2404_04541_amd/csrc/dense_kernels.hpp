@@ -8,15 +8,15 @@
 //   at multiples of kBlkCols columns into tiles, each small enough for the numeric workspace,
 //   and the row's column structure goes to the plan (decoded columns, or the flag words of
 //   direct blocks), so that the numeric phase need not find it again.
-//   The flag list takes the LDS that the matrix's width needs (sym_dense_shape): up to 2^18 columns two workgroups of 16 waves
-//   share a compute unit, up to 2^19 two of 8 waves, beyond that one of 16 waves has it to itself.  What a row costs beside its
-//   products (clearing and counting the flags, the round trips for its entries and its shares of the lists, decoding) was more
-//   than half of the kernel with one workgroup.  The flags are counted with a lane on every fourth word, a block per wave (32
-//   consecutive words per thread collided on the banks: 21 % of the kernel at scale 14).
-//   R-MAT squared, fp32, us with one workgroup | two or three of 8 waves | two of 16 waves: scale 14 210 | 155 | 145, scale 17
-//   2750 | 1300 | -, four row blocks of it - | 2210 | 1750, scale 19 15.8 | 12.0 ms | -; the heaviest rows are what 8 waves take too
-//   long for (1500 rows of a block of scale 15: 73 us a block with 16 waves, 123 with 8).  Deduplication sweep, 10000 columns: 1134 |
-//   695 (four of 8 waves) | 760.
+//   The flag list takes the LDS that the matrix's width needs, and the workgroups are as many as hold 32 waves a compute unit in 64 registers
+//   each (sym_dense_shape): what a row costs beside its products (clearing and counting the flags, planning, the round trips for its entries and
+//   its shares of the lists, decoding) is waiting for the most part, which other workgroups fill.  The flags are counted with a lane on every
+//   fourth word, a block per wave (32 consecutive words per thread collided on the banks).
+//   Up to 2^18 columns, workgroups of 8 waves, four on a compute unit (three at 2^18), where there are 32 rows or more for a compute unit, otherwise two of 16:
+//   us with 16 | 8: R-MAT squared scale 12 34 | 48, scale 14 (5277 rows) 111 | 120, 15 (16 500) 244 | 206, 17 1391 | 990, 18 3435 | 2990; deduplication sweep
+//   of 10 000 columns 533 | 487; 1071 rows of 4400 products 35 | 46; 60 000 of 3600 837 | 671.  With 4 waves 15 and 16 lose (362, 508).
+//   Up to 2^19 two of 16 with 512 A entries described at a time: scale 19 9.3 ms, with two of 8 waves in 84 registers 10.2.
+//   Beyond that one of 16 waves has a compute unit to itself.
 // Numeric (k_num_tiles, or k_num_wide), one tile at a time, one pass over the tile's products:
 //   direct tile (one block of kBlkCols columns in which the row is dense): sums live in a
 //     dense array indexed by column; the flags say which exist; flags and sums are compressed
@@ -47,14 +47,13 @@ constexpr int kRankEntryBytes = 8;                // sum per entry of a ranked t
 constexpr int kDirectMinDefault = 6144; // a block with at least this many entries becomes a direct tile
 constexpr int kRunTiles = 16;           // tiles handed to a workgroup at a time
 constexpr int kListSlab = 1 << 20;      // list entries and tile records that a symbolic workgroup draws at a time
-constexpr int kTileSlab = 2048;
+constexpr int kTileSlab = 512;
 constexpr int kDirectBit = 1 << 30;     // in TileRec::cnt
 constexpr int kSearchBit = 1 << 29;     // in TileRec::cnt: a searched tile (ranks by bisection of the column list)
 constexpr int kCountMask = kSearchBit - 1;
 constexpr int kSearchCap = 5632;      // entries of a searched tile (column 4 B + sum 8 B each)
 constexpr int kSearchRow = 2 * kSearchCap;   // entries of a row that becomes searched tiles: one, or two (one wide one)
 constexpr int kBlkWords = kBlkCols / 32;
-constexpr int kListStage = 5 * kWave;   // entries that a wave gathers in LDS (the piece walker's, free by then) before writing them to the column list
 // every tile kind must fit the tile area of the numeric kernel
 static_assert((long long)kSearchCap * 12 <= kTileBudget && (long long)kSearchRow * 12 <= kWideTileBudget, "searched tile: 4 B column + 8 B sum per entry");
 static_assert((long long)kBlkCols * 8 + kBlkCols / 8 <= kTileBudget, "direct tile: sums, flag words");
@@ -98,9 +97,10 @@ struct TileRec { int b0, b1, cnt, out; };     // blocks [b0, b1), entries (| kDi
 struct RunRec { int row; unsigned first; int count, d; long long a0, list; };
 
 // Per-workgroup bookkeeping of the piece walker below.
-template <int WAVES>
+template <int WAVES, int PIECES>
 struct __align__(16) RowScratch {   // (the tile planner's arrays, written 16 bytes at a time, lie behind it)
-  static constexpr int kPieces = WAVES * kWave;   // A entries described in LDS at a time: one per thread
+  static constexpr int kPieces = PIECES;              // A entries described in LDS at a time, at most one per thread
+  static constexpr int kListStage = 5 * PIECES / WAVES;   // entries that a wave gathers here, when the pieces are done with, before writing them to the column list
   long long start[kPieces];   // first B entry of each A entry's piece
   int plen[kPieces];          // piece length
   int cpre[kPieces + 1];      // exclusive prefix of chunk counts
@@ -213,14 +213,13 @@ __device__ __forceinline__ void quad_pass(int np, int nq, const PieceList<T, lon
 // Walks every pair (A entry p of the row, B entry q of row a_col[p]) and hands the columns to f, a quad per lane at a time.
 // range(k, s, en) may narrow the piece [s, en) of B row k first.  As many A entries as the workgroup has threads are described
 // at once.  Contains barriers: every thread of the workgroup must call it.
-template <int WAVES, class Range, class F>
+template <int WAVES, int PIECES, class Range, class F>
 __device__ __forceinline__ void stream_columns(int64_t a0, int d, const int32_t* __restrict__ a_col,
                                                const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col, int64_t b_nnz,
-                                               RowScratch<WAVES>* rs, Range range, F f) {
+                                               RowScratch<WAVES, PIECES>* rs, Range range, F f) {
   const int tid = threadIdx.x, lane = tid & 63;
-  constexpr int kPieces = RowScratch<WAVES>::kPieces;
-  for (int base = 0; base < d; base += kPieces) {
-    const int e = base + tid;
+  for (int base = 0; base < d; base += PIECES) {
+    const int e = PIECES >= WAVES * kWave || tid < PIECES ? base + tid : d;
     int64_t s = 0;
     int len = 0;
     if (e < d) {
@@ -465,10 +464,10 @@ __device__ __forceinline__ unsigned long long draw_below(unsigned long long* cur
   return base >= cap ? 0 : (cap - base < amount ? cap - base : amount);
 }
 
-// ALONE: LDS leaves room for one workgroup on a compute unit, so it may take the registers it wants (R-MAT scale 20: 45.8 ms in 64
-// registers, with spills, 44.4 in 75).  The narrow form of 16 waves spills seven registers (32 bytes a lane), outside its loops over products.
-template <int WAVES, bool ALONE>
-__global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_sym_dense(const int* __restrict__ perm, Control* ctl,
+// PER_SIMD 4: LDS leaves room for one workgroup on a compute unit, so it may take the registers it wants (R-MAT scale 20: 45.8 ms in 64
+// registers, with spills, 44.4 in 75).  The other forms spill nine registers (40 bytes a lane), outside their loops over products.
+template <int WAVES, int PER_SIMD, int PIECES>
+__global__ __launch_bounds__(WAVES * kWave, PER_SIMD) void k_sym_dense(const int* __restrict__ perm, Control* ctl,
                                                              const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                              const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col,
                                                              int64_t n_cols, const int* __restrict__ ip, int* __restrict__ cnt,
@@ -476,12 +475,15 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
                                                              int32_t* __restrict__ col_list, int direct_min, int no_tiles_ip,
                                                              int search_ratio, const int* __restrict__ bp, int nb1, int64_t b_nnz, int run_tiles, int wide) {
   constexpr int kThreads = WAVES * kWave;
-  constexpr bool kLook = WAVES == 16 && !ALONE;
+  constexpr bool ALONE = PER_SIMD == 4;
+  constexpr bool kLook = !ALONE;
   extern __shared__ __align__(16) unsigned char smem[];
   const int flag_words = sym_flag_words(n_cols);
   unsigned* flags = reinterpret_cast<unsigned*>(smem);                               // flag_words
-  RowScratch<WAVES>* rs = reinterpret_cast<RowScratch<WAVES>*>(smem + (size_t)flag_words * 4);
-  TilePlan* tp = reinterpret_cast<TilePlan*>(smem + (size_t)flag_words * 4 + sizeof(RowScratch<WAVES>));
+  using Scratch = RowScratch<WAVES, PIECES>;
+  constexpr int kListStage = Scratch::kListStage;
+  Scratch* rs = reinterpret_cast<Scratch*>(smem + (size_t)flag_words * 4);
+  TilePlan* tp = reinterpret_cast<TilePlan*>(smem + (size_t)flag_words * 4 + sizeof(Scratch));
   if (ctl->error) return;
   const bool sorted = ctl->b_sorted != 0;
   const int64_t span = (int64_t)kSymFlagWords * 32;
@@ -497,12 +499,12 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
   int row = blockIdx.x < nrows ? perm[row_hi - 1 - blockIdx.x] : -1;
   if (tid == 0) tp->place = blockIdx.x;
   // Thread 0's slabs of the plan's lists are in LDS (its registers would be everybody's), but where there are registers to spare (R-MAT
-  // scale 20: 44.6 | 43.0 ms, scale 19, 8 waves, 12.27 | 12.10).  The first slab of
+  // scale 20: 44.6 | 43.0 ms).  The first slab of
   // every workgroup is its own by its number (the cursors start behind these: k_set_caps); when all workgroups drew their
   // first slab from the shared cursors at the same moment, the compare-and-swaps of 256 of them took 0.2 ms (1071 rows: 366 -> 73 us).
   const unsigned long long list_slab = list_slab_of(list_cap, gridDim.x);
   Slabs own{};
-  Slabs& sl = WAVES == 8 || ALONE ? own : tp->slabs;
+  Slabs& sl = ALONE ? own : tp->slabs;
   if (tid == 0)
     sl = Slabs{0, blockIdx.x * list_slab, list_slab, blockIdx.x * (unsigned)kTileSlab, (unsigned)kTileSlab, 0, 0};
   int next_row = -1;   // (thread 0) the row after this one
@@ -531,7 +533,7 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
         if (kFull && one) {
           // (looking at the flag words first, so that only bits that are not set yet go through the atomic, gains where hub columns are hit by
           // most pieces or columns many times - us without | with: R-MAT scale 17 1515 | 1450, dedup sweep of 30000 4390 | 4270, of 10000 2035 |
-          // 2060 - and loses where the kernel has fewer waves: scale 19 36.0 | 36.4 ms)
+          // 2060 - and loses where there are 16 waves on a compute unit: scale 19 36.0 | 36.4 ms)
           unsigned w[4];
           if (kLook) {
 #pragma unroll
@@ -814,9 +816,9 @@ __global__ __launch_bounds__(WAVES * kWave, WAVES == 8 || ALONE ? 4 : 8) void k_
   SPG_CLK(clk_mark(&rs->clk, 9); clk_flush(&rs->clk, ctl->clk[0]);)
 }
 
-static_assert(4 * 8 <= RowScratch<8>::kPieces && sizeof(RowScratch<8>) % 16 == 0 && sizeof(RowScratch<16>) % 16 == 0 && alignof(TilePlan) == 16, "the planner's arrays start on 16 bytes");
-template <int WAVES>
-constexpr size_t sym_dense_lds(int64_t flag_words) { return (size_t)flag_words * 4 + sizeof(RowScratch<WAVES>) + sizeof(TilePlan); }
+static_assert(sizeof(RowScratch<8, 512>) % 16 == 0 && sizeof(RowScratch<16, 1024>) % 16 == 0 && alignof(TilePlan) == 16, "the planner's arrays start on 16 bytes");
+template <int WAVES, int PIECES>
+constexpr size_t sym_dense_lds(int64_t flag_words) { return (size_t)flag_words * 4 + sizeof(RowScratch<WAVES, PIECES>) + sizeof(TilePlan); }
 // Half a span of flag words (64 KB): up to that many columns two workgroups of 8 waves share a compute unit.
 constexpr int64_t kSymNarrowCols = (int64_t)kSymFlagWords * 16;
 constexpr int64_t kSymShortCols = (int64_t)kSymFlagWords * 8;

@@ -34,8 +34,8 @@ using namespace spg;
 
 // the LDS of a compute unit (160 KB) belongs to one workgroup of the big kernels, or to two
 static_assert(num_wide_lds<double>() <= 160 * 1024, "numeric dense kernel exceeds LDS");
-static_assert(sym_dense_lds<16>(kSymFlagWords) <= 160 * 1024, "symbolic dense kernel exceeds LDS");
-static_assert(sym_dense_lds<8>(kSymNarrowCols / 32) <= 80 * 1024 && sym_dense_lds<16>(kSymShortCols / 32) <= 80 * 1024 && num_tiles_lds<double>() <= 80 * 1024, "two workgroups on a compute unit");
+static_assert(sym_dense_lds<16, 1024>(kSymFlagWords) <= 160 * 1024, "symbolic dense kernel exceeds LDS");
+static_assert(sym_dense_lds<16, 512>(kSymNarrowCols / 32) <= 80 * 1024 && sym_dense_lds<16, 1024>(kSymShortCols / 32) <= 80 * 1024 && num_tiles_lds<double>() <= 80 * 1024, "two workgroups on a compute unit");
 static_assert(staged_lds<double>() <= 160 * 1024 && staged_lds<float>() <= 160 * 1024, "staged kernel exceeds LDS");
 
 // Pinned host memory where the symbolic kernels leave the control block for the host.  Allocating and releasing it costs 50 to
@@ -220,9 +220,10 @@ int ensure_device(spgemm_context* h) {
 int ensure_big_lds(spgemm_context* h) {
   if (h->big_lds_ready) return SPGEMM_OK;
   int rc;
-  if ((rc = allow_lds(h, k_sym_dense<16, false>, sym_dense_lds<16>(kSymFlagWords)))) return rc;
-  if ((rc = allow_lds(h, k_sym_dense<16, true>, sym_dense_lds<16>(kSymFlagWords)))) return rc;
-  if ((rc = allow_lds(h, k_sym_dense<8, false>, sym_dense_lds<8>(kSymNarrowCols / 32)))) return rc;
+  if ((rc = allow_lds(h, k_sym_dense<16, 8, 1024>, sym_dense_lds<16, 1024>(kSymShortCols / 32)))) return rc;
+  if ((rc = allow_lds(h, k_sym_dense<16, 4, 1024>, sym_dense_lds<16, 1024>(kSymFlagWords)))) return rc;
+  if ((rc = allow_lds(h, k_sym_dense<16, 8, 512>, sym_dense_lds<16, 512>(kSymNarrowCols / 32)))) return rc;
+  if ((rc = allow_lds(h, k_sym_dense<8, 8, 512>, sym_dense_lds<8, 512>(kSymShortCols / 32)))) return rc;
   if ((rc = allow_lds(h, k_num_tiles<float>, num_tiles_lds<float>()))) return rc;
   if ((rc = allow_lds(h, k_num_tiles<double>, num_tiles_lds<double>()))) return rc;
   if ((rc = allow_lds(h, k_num_wide<float>, num_wide_lds<float>()))) return rc;
@@ -396,15 +397,19 @@ bool short_rows_ok(spgemm_context* h, const N* hist) {
 }
 unsigned short_grid(int64_t rows, int64_t per_block) { return rows > 0 ? (unsigned)(ceil_div(ceil_div(rows, per_block), kDies) * kDies) : 0; }
 
-// The dense symbolic kernel's workgroups: waves of one, and how many are resident on the card.
-struct SymDense { int waves; size_t lds; unsigned groups; };
+// The dense symbolic kernel's workgroups: waves of one, of a SIMD, and how many are resident on the card.
+struct SymDense { int waves, per_simd, pieces; size_t lds; unsigned groups; };
 SymDense sym_dense_shape(spgemm_context* h, int64_t rows, int64_t cols) {
   const int64_t words = sym_flag_words(cols);
-  const int waves = cols <= kSymShortCols || cols > kSymNarrowCols ? 16 : 8;
-  const size_t lds = waves == 16 ? sym_dense_lds<16>(words) : sym_dense_lds<8>(words);
-  int64_t per_cu = (int64_t)(160 * 1024 / lds);
-  per_cu = per_cu < 32 / waves ? per_cu : 32 / waves;
-  return SymDense{waves, lds, grid_for(rows, 1, (int64_t)h->num_cus * per_cu)};
+  SymDense d{16, 8, 1024, 0, 0};
+  if (cols > kSymNarrowCols) d.per_simd = 4;
+  else if (cols > kSymShortCols) d.pieces = 512;
+  else if (rows >= (int64_t)h->num_cus * 32) { d.waves = 8; d.pieces = 512; }
+  d.lds = d.waves == 8 ? sym_dense_lds<8, 512>(words) : d.pieces == 512 ? sym_dense_lds<16, 512>(words) : sym_dense_lds<16, 1024>(words);
+  int64_t per_cu = (int64_t)(160 * 1024 / d.lds);
+  per_cu = per_cu < d.per_simd * 4 / d.waves ? per_cu : d.per_simd * 4 / d.waves;
+  d.groups = grid_for(rows, 1, (int64_t)h->num_cus * per_cu);
+  return d;
 }
 
 // Tiles of a row that a workgroup of the numeric kernel takes together: they share the set-up of the row's entries, but where
@@ -459,8 +464,10 @@ int alloc_dense_lists(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, 
   const bool with_bp = h->block_table && host.b_sorted && B->nnz > 0 && bp_bytes <= ((size_t)1 << 30);
   p->wide_tiles = wide_tiles_from(h, p, B, with_bp, rows_d, ip_d, h->row_block ? h->whole_ip : (double)host.ip_total);
   const double wgs = (double)sym_dense_shape(h, (int64_t)rows_d, B->cols).groups + 1.0;
-  const double tiles = 2.0 * direct + 2.0 * weight / (p->wide_tiles ? kWideTileBudget : kTileBudget) + 4.0 * rows_d * spans + 16.0 + wgs * kTileSlab;
-  const double runs = rows_d + (tiles - wgs * kTileSlab) / run_tiles_of(h, (int64_t)rows_d) + rows_d * spans + 16.0;
+  // (a row's tiles, at most kSpanBlocks a span, lie together: a slab may end with so many less one that its next row does not fit)
+  const double planned = 2.0 * direct + 2.0 * weight / (p->wide_tiles ? kWideTileBudget : kTileBudget) + 4.0 * rows_d * spans + 16.0;
+  const double tiles = planned * kTileSlab / (kTileSlab - kSpanBlocks + 1) + wgs * kTileSlab;
+  const double runs = rows_d + planned / run_tiles_of(h, (int64_t)rows_d) + rows_d * spans + 16.0;
   if (tiles > 4.0e9) return fail(h, SPGEMM_UNSUPPORTED, "tile list of the dense workspace would exceed 2^32 records");
   *tile_cap = (unsigned)tiles;
   *run_cap = (unsigned)runs;
@@ -689,7 +696,7 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
     if (rows_dense > 0) {
       Timer t(h, SPGEMM_K_SYM_DENSE);
       const SymDense d = sym_dense_shape(h, rows_dense, B->cols);
-      hipLaunchKernelGGL((d.waves == 8 ? k_sym_dense<8, false> : B->cols > kSymNarrowCols ? k_sym_dense<16, true> : k_sym_dense<16, false>), dim3(d.groups), dim3(d.waves * kWave), d.lds, s, p->perm_sym, p->ctl, A->rowptr, A->colidx, B->rowptr, B->colidx, B->cols, p->ip, p->cnt, p->tiles, p->runs, p->col_list, h->direct_min,
+      hipLaunchKernelGGL((d.waves == 8 ? k_sym_dense<8, 8, 512> : d.per_simd == 4 ? k_sym_dense<16, 4, 1024> : d.pieces == 512 ? k_sym_dense<16, 8, 512> : k_sym_dense<16, 8, 1024>), dim3(d.groups), dim3(d.waves * kWave), d.lds, s, p->perm_sym, p->ctl, A->rowptr, A->colidx, B->rowptr, B->colidx, B->cols, p->ip, p->cnt, p->tiles, p->runs, p->col_list, h->direct_min,
                          staged, h->search_ratio, p->blk_ptr, p->blk_ptr_cols, B->nnz, run_tiles_of(h, rows_dense), p->wide_tiles ? 1 : 0);
     }
     if (p->scan_blocks > 1) {

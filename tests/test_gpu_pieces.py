@@ -67,3 +67,33 @@ def test_runs_from_both_ends(rows):
     got = gpu_product(A, B)
     assert_matches_oracle(A, B, got, what=f"{rows} rows")
     assert got[3]["sym_bin_rows"][4] == rows
+
+
+@pytest.mark.parametrize("rows", [8191, 8192])
+@pytest.mark.parametrize("cols", [2500, 262_144, 262_145])
+def test_rows_for_smaller_workgroups(rows, cols):
+    """Both sides of 32 rows for each of 256 compute units, and of 2^18 columns."""
+    rng = np.random.default_rng(11)
+    B = rows_of(rng.integers(100, 300, 300), cols, rng, np.float64)
+    c = np.concatenate([np.sort(rng.choice(300, 17, replace=False)) for _ in range(rows)]).astype(np.int32)
+    A = W.CSR(rows, 300, np.arange(rows + 1, dtype=np.int64) * 17, c, rng.uniform(-1, 1, c.size))
+    got = gpu_product(A, B)
+    assert_matches_oracle(A, B, got, what=f"{rows} rows of {cols} columns")
+    assert got[3]["sym_bin_rows"][4] == rows
+
+
+def test_tiles_of_changing_size():
+    """Every other block of 8192 columns is nearly a tile by itself and the ones between hold an entry: as many tiles as the plan's bound allows for."""
+    rng = np.random.default_rng(13)
+    n = 400_000
+    full = [np.sort(rng.choice(8192, 6100, replace=False)) + 16384 * b for b in range(n // 16384)]
+    one = [np.array([16384 * b + 8192 + 5]) for b in range(n // 16384)]
+    cols = np.sort(np.concatenate(full + one)).astype(np.int32)
+    B = W.CSR(8, n, np.arange(9, dtype=np.int64) * cols.size, np.tile(cols, 8), rng.uniform(-1, 1, 8 * cols.size))
+    rows = 700
+    A = W.CSR(rows, 8, np.arange(rows + 1, dtype=np.int64), rng.integers(0, 8, rows).astype(np.int32), rng.uniform(-1, 1, rows))
+    got = gpu_product(A, B)
+    assert np.array_equal(got[0], np.arange(rows + 1, dtype=np.int64) * cols.size)
+    assert np.array_equal(got[1], np.tile(cols, rows))
+    want = A.values[:, None] * B.values.reshape(8, -1)[A.colidx]
+    assert np.allclose(got[2].reshape(rows, -1), want, rtol=1e-15, atol=0)   # (one product an entry)
