@@ -6,19 +6,35 @@ namespace spg {
 
 constexpr int kCountThreads = 1024;
 constexpr int kCountMaxRows = 1024;   // rows of A in a chunk: at most
+constexpr int kFineRows = 32, kFineProbe = 256, kHeavyChunk = 4;
+constexpr int64_t kFineFrom = 65536;
+inline bool fine_rows(int64_t m, int64_t nnz_a, int64_t b_rows, int64_t nnz_b) { return m >= kFineFrom && nnz_a >= 6 * m && nnz_b >= 6 * b_rows; }
 
 // Clears the control block and says how many rows of A a workgroup of the row count takes at a time: chunk, or kCountMaxRows where
 // there are enough rows for all workgroups, rows are short (a chunk of 256 rows of a few entries leaves most of the 1024 threads idle
 // and costs six barriers) and no stretch of them is much heavier than what a workgroup gets anyway (two are resident on each of `cus`
 // compute units; one that holds the hub rows of a graph keeps the whole count waiting).
+// Where a stretch of 256 rows (of a thousandth of them) holds kHeavyChunk times what a workgroup gets on average, chunks are of kFineRows rows, or
+// twice as many: the one with the hub rows of a graph took as long as the whole count (R-MAT scale 17 squared 4436 | 4385 us, scale 19 34.8 | 34.6
+// ms).  fine: this is looked at, which takes 2 us, where rows are many and of some length (400 000 rows of 8 x 4 239 | 241 us if they were).
 // us with chunks of 256 | 1024 rows: 4.2 M rows of 2 entries 329 | 241, of 16 entries 1368 | 1322, of 27 entries 2131 | 2200; 2 M rows of 2
 // entries 121 | 67, of 16 entries 253 | 240, of 27 entries 385 | 383; R-MAT of 2^20 vertices, 4 edges each 248 | 398, of 2^21, 7 edges
 // each 637 | 1061.
-__global__ __launch_bounds__(kCountThreads) void k_init_control(Control* ctl, int64_t m, const int64_t* __restrict__ a_rp, int chunk, int cus) {
+__global__ __launch_bounds__(kCountThreads) void k_init_control(Control* ctl, int64_t m, const int64_t* __restrict__ a_rp, int chunk, int cus, int fine) {
   __shared__ unsigned long long heaviest;
+  __shared__ int heavy;
+  // (a stretch of rows a thread, asked for before the block is cleared)
+  const int64_t probe = m > (int64_t)kFineProbe * kCountThreads ? (m + kCountThreads - 1) / kCountThreads : kFineProbe, r0 = threadIdx.x * probe;
+  int mine = 0;
+  int64_t all = 0;
+  if (fine) {
+    const int64_t n = r0 < m ? a_rp[r0 + probe < m ? r0 + probe : m] - a_rp[r0] : 0;   // (nobody has checked these yet)
+    mine = n < 0 ? 0 : (n < 0x7fffffff ? (int)n : 0x7fffffff);
+    all = a_rp[m] - a_rp[0];
+  }
   unsigned* w = reinterpret_cast<unsigned*>(ctl);
   for (int i = threadIdx.x; i < (int)(sizeof(Control) / sizeof(unsigned)); i += blockDim.x) w[i] = 0;
-  if (threadIdx.x == 0) heaviest = 0;
+  if (threadIdx.x == 0) { heaviest = 0; heavy = 0; }
   __syncthreads();
   if (m >= (int64_t)kCountMaxRows * 2 * cus) {
     const int64_t nnz = a_rp[m] - a_rp[0];
@@ -34,6 +50,12 @@ __global__ __launch_bounds__(kCountThreads) void k_init_control(Control* ctl, in
     __syncthreads();
     // (a row pointer that descends gives a huge one)
     if (nnz <= 16 * m && heaviest <= (unsigned long long)nnz / (unsigned)cus) chunk = kCountMaxRows;
+  }
+  if (fine && chunk < kCountMaxRows) {
+    const int most = group_max_scan<kWave>(mine);
+    if (lane_id() == kWave - 1) atomicMax(&heavy, most);
+    __syncthreads();
+    if ((int64_t)(heavy - kCountThreads * 4) * (2 * cus) > kHeavyChunk * all) chunk = m <= (int64_t)kFineRows * 64 * cus ? kFineRows : 2 * kFineRows;
   }
   if (threadIdx.x == 0) ctl->chunk_rows = chunk;
 }

@@ -353,10 +353,11 @@ int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const sp
   {
     Timer t(h, SPGEMM_K_COUNT);
     const int chunk = count_chunk(h, m);
-    hipLaunchKernelGGL(k_init_control, dim3(1), dim3(kCountThreads), 0, s, p->ctl, m, A->rowptr, chunk, h->num_cus);
+    const bool fine = fine_rows(m, A->nnz, B->rows, B->nnz);
+    hipLaunchKernelGGL(k_init_control, dim3(1), dim3(kCountThreads), 0, s, p->ctl, m, A->rowptr, chunk, h->num_cus, fine ? 1 : 0);
     const unsigned parts = grid_for(B->nnz > B->rows ? B->nnz : B->rows, kCountThreads * 8, (int64_t)h->num_cus * 4);
     // (as many as run at a time; chunks are drawn: four times as many 500 000 rows 62 | 58 us)
-    const unsigned groups = m > 0 ? grid_for(m, chunk, (int64_t)h->num_cus * 2) : 0;
+    const unsigned groups = m > 0 ? grid_for(m, fine ? kFineRows : chunk, (int64_t)h->num_cus * 2) : 0;
     RowLens* lens = row_lens_ok(A, B) ? reinterpret_cast<RowLens*>(p->perm_sym) : nullptr;   // (perm_sym is written afterwards)
     if (lens)
       hipLaunchKernelGGL(k_row_lens, dim3((unsigned)ceil_div(B->rows, kLensGroup * kLensRows)), dim3(kLensThreads), 0, s, B->rows, B->rowptr, m,
@@ -1509,8 +1510,9 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
     Control host{};
     std::vector<long long> first((size_t)nblocks + 2);
     const int chunk = count_chunk(h, m);
-    hipLaunchKernelGGL(k_init_control, dim3(1), dim3(kCountThreads), 0, h->stream, ctl, m, A->rowptr, chunk, h->num_cus);
-    hipLaunchKernelGGL(k_count_rows<false>, dim3(grid_for(m, chunk, (int64_t)h->num_cus * 8)), dim3(kCountThreads), 0, h->stream, 0, B->cols, B->nnz,
+    const bool fine = fine_rows(m, A->nnz, B->rows, B->nnz);
+    hipLaunchKernelGGL(k_init_control, dim3(1), dim3(kCountThreads), 0, h->stream, ctl, m, A->rowptr, chunk, h->num_cus, fine ? 1 : 0);
+    hipLaunchKernelGGL(k_count_rows<false>, dim3(grid_for(m, fine ? kFineRows : chunk, (int64_t)h->num_cus * 2)), dim3(kCountThreads), 0, h->stream, 0, B->cols, B->nnz,
                        B->colidx, m, A->nnz, B->rows, A->rowptr, A->colidx, B->rowptr, ip, tmp + o_bin, reinterpret_cast<int*>(tmp + o_cnt), ctl, 0,
                        0, (unsigned long long*)nullptr, (const RowLens*)nullptr);
     hipLaunchKernelGGL(k_weight_sums, dim3((unsigned)tiles), dim3(kScanThreads), 0, h->stream, m, ip, sums);

@@ -50,3 +50,11 @@ def test_chunks_of_about_as_many_entries_as_threads(a_lens):
 def test_a_huge_row_of_b_among_short_ones(longest, entries):
     """(the first, the only and a later round of a row hold it)"""
     count([entries, 5], [longest] + [1] * 3000, 6)
+
+
+@pytest.mark.parametrize("rows", [65_535, 65_536, 70_001])
+def test_count_where_a_stretch_of_rows_is_heavy(rows):
+    """Rows of 6 entries, and 300 of 700 in a row: finer chunks from 65536 rows on."""
+    a_lens = np.full(rows, 6)
+    a_lens[31_000:31_300] = 700
+    count(a_lens, [7] * 900, 8)
