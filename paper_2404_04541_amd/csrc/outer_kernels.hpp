@@ -150,19 +150,25 @@ __global__ __launch_bounds__(kSortThreads) void k_outer_insert(int64_t t0, int64
   sort_hist_out(cnt, 1 << bits, blockIdx.x, gridDim.x, hist);
 }
 
-// Where components go: coordinate and sum of the all array or, with the last stage, the coordinate (the row pointer comes from
-// it), the column and the value of C.
+// Where components go: coordinate and sum of the all array or, with the last stage, the row (the row pointer comes from
+// it: four bytes written and read in place of the coordinate's eight), the column and the value of C.
 template <typename T>
 struct OuterOut {
   unsigned long long* keys;
-  double* vals;     // null with the last stage
-  int32_t* col;     // null before it
+  double* vals;     // keys, vals: null with the last stage
+  uint32_t* row;
+  int32_t* col;     // row, col, val: null before it
   T* val;
-  unsigned long long col_mask;
+  int col_bits;
   __device__ __forceinline__ void put(int64_t at, unsigned long long key, double v) const {
-    keys[at] = key;
-    if (vals) vals[at] = v;
-    else { col[at] = (int32_t)(key & col_mask); val[at] = (T)v; }
+    if (vals) {
+      keys[at] = key;
+      vals[at] = v;
+    } else {
+      row[at] = (uint32_t)(key >> col_bits);
+      col[at] = (int32_t)(key & ((1ULL << col_bits) - 1));
+      val[at] = (T)v;
+    }
   }
 };
 
@@ -219,11 +225,12 @@ __global__ __launch_bounds__(256) void k_run_sum(int64_t n, const unsigned long 
   }
 }
 
-// Merge stage: the sorted batch (b, unique coordinates) into the all array (a, sorted, unique), equal coordinates added.  The
-// merged order (a's component first where both hold a coordinate) is cut into tiles of kMergeTile; a tile's share of either
-// array comes from a bisection along the diagonal, and so does a thread's share of a tile.  b's component of a coordinate
-// that a holds too is a repeat: a's component takes its value along.  Bound by reading and writing the components (four arrays of 8 bytes in, 20 to
-// 24 bytes out).
+// Merge stage: the sorted batch (b) into the all array (a), equal coordinates added.  The
+// merged order (a's components first where both hold a coordinate) is cut into tiles of kMergeTile; a tile's share of either
+// array comes from a bisection along the diagonal, and so does a thread's share of a tile.  Either array may hold a coordinate
+// several times: the first component of the merged order that has it stays and takes the others' values along, a's in their order, then b's.
+// (So the batches need not be added up by themselves first, which took a pass over their keys, one over all, and a wait of the host each: 16.8 M
+// components 145 us and the wait.)  Bound by reading and writing the components (four arrays of 8 bytes in, 20 to 24 bytes out).
 // Two sorted arrays of 16.7 M components each: bisection of the other array per component, head flags, their scan and a walk
 // over the runs 1.47 ms, tiles with a bisection in LDS per component 0.61 (count 137 us, put 437), here 0.35 (92, 228).
 constexpr int kMergeTile = 2048;
@@ -244,10 +251,11 @@ __global__ __launch_bounds__(256) void k_merge_split(int64_t na, const unsigned 
 
 struct MergeLds {
   unsigned long long key[kMergeTile];   // a's components of the tile, then b's
-  unsigned from[kMergeTile];            // of every component that stays: its place in key, and 1 + the place in b of the value to be added to it
+  unsigned from[kMergeTile];            // of every component that stays: how many of a's and of b's lie before it, and whether it is a's
   int part[4];
 };
 constexpr unsigned kFromBits = 12;
+constexpr unsigned kFromA = 1u << (2 * kFromBits);
 static_assert((1u << kFromBits) > kMergeTile, "places of a tile");
 
 // Loads the tile's keys and merges them, kPer consecutive components of the merged order to a thread: a bisection along its diagonal, then a step
@@ -258,11 +266,8 @@ __device__ __forceinline__ int merge_tile(int64_t na, const unsigned long long* 
   constexpr int kPer = kMergeTile / 256;
   for (int x = threadIdx.x; x < an; x += 256) ml->key[x] = ka[a0 + x];
   for (int x = threadIdx.x; x < bn; x += 256) ml->key[an + x] = kb[b0 + x];
-  // the neighbours in the tiles around: a's component before the first, b's after the last
-  bool have = a0 > 0;
-  unsigned long long before = have ? ka[a0 - 1] : 0ULL;
-  const bool more = b0 + bn < nb;
-  const unsigned long long after = more ? kb[b0 + bn] : 0ULL;
+  // the components in front of the tile
+  const unsigned long long a_front = a0 > 0 ? ka[a0 - 1] : 0ULL, b_front = b0 > 0 ? kb[b0 - 1] : 0ULL;
   __syncthreads();
   const int n = an + bn, d = (int)threadIdx.x * kPer < n ? (int)threadIdx.x * kPer : n;
   int i = d > bn ? d - bn : 0, hi = d < an ? d : an;
@@ -271,23 +276,25 @@ __device__ __forceinline__ int merge_tile(int64_t na, const unsigned long long* 
     if (ml->key[mid] <= ml->key[an + d - 1 - mid]) i = mid + 1; else hi = mid;
   }
   int j = d - i;
-  if (i > 0) { have = true; before = ml->key[i - 1]; }
+  // the component before the thread's first: the larger one of both arrays
+  bool have = a0 + i > 0 || b0 + j > 0;
+  const unsigned long long a_last = i > 0 ? ml->key[i - 1] : a_front, b_last = j > 0 ? ml->key[an + j - 1] : b_front;
+  unsigned long long before = a_last > b_last ? a_last : b_last;
   unsigned long long x = i < an ? ml->key[i] : 0ULL, y = j < bn ? ml->key[an + j] : 0ULL;
   unsigned from[kPer], stay = 0;
 #pragma unroll
   for (int t = 0; t < kPer; ++t) {
     from[t] = 0;
     if (d + t >= n) continue;
-    if (i < an && (j >= bn || x <= y)) {
-      const bool both = j < bn ? x == y : more && x == after;
-      from[t] = (unsigned)i | (both ? (unsigned)(j + 1) << kFromBits : 0u);
-      stay |= 1u << t;
-      have = true;
-      before = x;
+    const bool of_a = i < an && (j >= bn || x <= y);
+    const unsigned long long key = of_a ? x : y;
+    from[t] = (unsigned)i | ((unsigned)j << kFromBits) | (of_a ? kFromA : 0u);
+    if (!(have && before == key)) stay |= 1u << t;
+    have = true;
+    before = key;
+    if (of_a) {
       if (++i < an) x = ml->key[i];
-    } else {   // (all of a's components up to this one have been taken)
-      from[t] = (unsigned)(an + j);
-      if (!(have && before == y)) stay |= 1u << t;
+    } else {
       if (++j < bn) y = ml->key[an + j];
     }
   }
@@ -329,11 +336,17 @@ __global__ __launch_bounds__(256) void k_merge_put(int64_t na, const unsigned lo
   const int stay = merge_tile<true>(na, ka, nb, kb, a0, an, b0, bn, &ml);
   const int64_t at = sums[blockIdx.x];
   for (int x = threadIdx.x; x < stay; x += 256) {
-    const unsigned w = ml.from[x], add = w >> kFromBits;
-    const int p = (int)(w & ((1u << kFromBits) - 1));
-    double v = p < an ? va[a0 + p] : vb[b0 + (p - an)];
-    if (add) v += vb[b0 + add - 1];
-    out.put(at + x, ml.key[p], v);
+    const unsigned w = ml.from[x];
+    int i = (int)(w & ((1u << kFromBits) - 1)), j = (int)((w >> kFromBits) & ((1u << kFromBits) - 1));
+    const bool of_a = (w & kFromA) != 0;
+    const unsigned long long key = ml.key[of_a ? i : an + j];
+    double v = of_a ? va[a0 + i] : vb[b0 + j];
+    if (of_a) ++i; else ++j;
+    // the others: a's (none where the first is b's), then b's, in the tile or behind it
+    if (of_a)
+      for (; a0 + i < na && (i < an ? ml.key[i] : ka[a0 + i]) == key; ++i) v += va[a0 + i];
+    for (; b0 + j < nb && (j < bn ? ml.key[an + j] : kb[b0 + j]) == key; ++j) v += vb[b0 + j];
+    out.put(at + x, key, v);
   }
 }
 

@@ -328,7 +328,7 @@ __global__ __launch_bounds__(256) void k_sort_buckets(int64_t n, int64_t buckets
     const int64_t from = lds.begin[w], count = lds.begin[w + 1] - from;   // (the same for the workgroup)
     if (count <= kBucketWave) continue;
     if (count > kBucketGroup) {
-      if (threadIdx.x == 0) *too_long = 1;
+      if (threadIdx.x == 0) __hip_atomic_store(too_long, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       continue;
     }
     constexpr int kPlaceBits = 11;
@@ -518,8 +518,9 @@ __global__ __launch_bounds__(256) void k_scan_sums(int64_t n, const T* __restric
   if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
+// total (optional, in host memory): the sum of all.
 template <typename T>
-__global__ __launch_bounds__(256) void k_scan_top(int64_t n, T* __restrict__ sums) {
+__global__ __launch_bounds__(256) void k_scan_top(int64_t n, T* __restrict__ sums, T* __restrict__ total_out) {
   __shared__ T ws[4];
   T carry = 0;
   for (int64_t b = 0; b < n; b += kScanTileN) {
@@ -533,7 +534,10 @@ __global__ __launch_bounds__(256) void k_scan_top(int64_t n, T* __restrict__ sum
     for (int t = 0; t < kScanV; ++t) { if (base + t < n) sums[base + t] = run; run += x[t]; }
     carry += total;
   }
-  if (threadIdx.x == 0) sums[n] = carry;
+  if (threadIdx.x == 0) {
+    sums[n] = carry;
+    if (total_out) __hip_atomic_store(total_out, carry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 template <typename T>

@@ -1649,11 +1649,12 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
 namespace {
 
 // In-place exclusive scan of n values, v[n] = their sum; sums: ceil(n / kScanTileN) + 1 slots of scratch.
+// total: the sum in host memory too.
 template <typename T>
-void scan_values(spgemm_context* h, int64_t n, T* v, T* sums) {
+void scan_values(spgemm_context* h, int64_t n, T* v, T* sums, T* total) {
   const int64_t tiles = ceil_div(n > 0 ? n : 1, kScanTileN);
   hipLaunchKernelGGL(k_scan_sums<T>, dim3((unsigned)tiles), dim3(256), 0, h->stream, n, v, sums);
-  hipLaunchKernelGGL(k_scan_top<T>, dim3(1), dim3(256), 0, h->stream, tiles, sums);
+  hipLaunchKernelGGL(k_scan_top<T>, dim3(1), dim3(256), 0, h->stream, tiles, sums, total);
   hipLaunchKernelGGL(k_scan_tiles<T>, dim3((unsigned)tiles), dim3(256), 0, h->stream, n, v, sums);
 }
 
@@ -1685,10 +1686,12 @@ int dcs_compress(spgemm_context* h, int64_t n, int64_t nnz, const int64_t* ptr, 
   hipLaunchKernelGGL(k_dcs_flags, dim3(g), dim3(256), 0, s, n, ptr, pos);
   unsigned* sums = bufs.get<unsigned>((size_t)ceil_div(n > 0 ? n : 1, kScanTileN) + 1);
   if (!sums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the doubly compressed format failed");
-  scan_values(h, n, pos, sums);
-  unsigned total = 0;
-  HIP_TRY(h, hipMemcpyAsync(&total, pos + n, 4, hipMemcpyDeviceToHost, s));
+  PinnedLease pinned;
+  if (!pinned.p) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of pinned host memory failed");
+  unsigned* host = reinterpret_cast<unsigned*>(pinned.p);
+  scan_values(h, n, pos, sums, host);
   HIP_TRY(h, hipStreamSynchronize(s));
+  const unsigned total = *static_cast<volatile unsigned*>(host);
   *nvec = total;
   *vec = bufs.get<int32_t>((size_t)total + 1);
   *out_ptr = bufs.get<int64_t>((size_t)total + 1);
@@ -1698,11 +1701,19 @@ int dcs_compress(spgemm_context* h, int64_t n, int64_t nnz, const int64_t* ptr, 
   return SPGEMM_OK;
 }
 
+constexpr int64_t kOuterKeepCap = (int64_t)1 << 26;   // accumulation arrays up to this long become the all array (1 GB, however many of its coordinates are equal)
+
 template <typename T>
 int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64_t cap, spgemm_csr* C) {
   hipStream_t s = h->stream;
   const int64_t m = A->minor_dim, n = B->minor_dim, na = A->nvec, nb = B->nvec;
   DevBufs bufs(h);
+  // numbers that come to the host: the products, components that stay, whether a bucket of a sort was too long
+  PinnedLease pinned;
+  if (!pinned.p) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of pinned host memory failed");
+  long long* host_total = reinterpret_cast<long long*>(pinned.p);
+  unsigned* host_stay = reinterpret_cast<unsigned*>(host_total + 1);
+  int* too_long = reinterpret_cast<int*>(host_total + 2);
   int64_t* rp = bufs.get<int64_t>((size_t)m + 1);
   long long* off = bufs.get<long long>((size_t)na + 1);
   int32_t* match = bufs.get<int32_t>((size_t)na + 1);
@@ -1713,48 +1724,51 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
                        off, match);
     long long* sums = bufs.get<long long>((size_t)ceil_div(na, kScanTileN) + 1);
     if (!sums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the outer product failed");
-    scan_values(h, na, off, sums);
-    HIP_TRY(h, hipMemcpyAsync(&total, off + na, 8, hipMemcpyDeviceToHost, s));
+    scan_values(h, na, off, sums, host_total);
     HIP_TRY(h, hipStreamSynchronize(s));
+    total = *static_cast<volatile long long*>(host_total);
   }
   if (cap <= 0) cap = (int64_t)1 << 24;
   if (cap > ((int64_t)1 << 30)) cap = (int64_t)1 << 30;
   if (cap > total) cap = total > 0 ? total : 1;
   // accumulation array: coordinates (row above the column's bits) and values, twice (the sort's two buffers)
   const int col_bits = bits_of(n);
-  const unsigned long long col_mask = (1ULL << col_bits) - 1;
   unsigned long long* keys[2] = {bufs.get<unsigned long long>((size_t)cap), bufs.get<unsigned long long>((size_t)cap)};
   double* vals[2] = {bufs.get<double>((size_t)cap), bufs.get<double>((size_t)cap)};
   unsigned* counters = bufs.get<unsigned>(sort_counter_bytes(cap) / 4);   // (the last batch is shorter and may take more ranges)
-  int* too_long = bufs.get<int>(2);
-  if (!keys[0] || !keys[1] || !vals[0] || !vals[1] || !counters || !too_long)
+  if (!keys[0] || !keys[1] || !vals[0] || !vals[1] || !counters)
     return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the accumulation array failed");
   // all array: sorted, unique coordinates with their sums
   unsigned long long* all_k = nullptr;
   double* all_v = nullptr;
   int64_t all_n = 0;
+  uint32_t* all_row = nullptr;   // of C's entries
   int32_t* col = nullptr;
   T* val = nullptr;
   // Room for `uniq` components of the next all array; the last stage writes columns and values of C in place of sums.
   auto room = [&](unsigned uniq, bool last, OuterOut<T>* out) -> int {
-    *out = OuterOut<T>{bufs.get<unsigned long long>((size_t)uniq), nullptr, nullptr, nullptr, col_mask};
+    *out = OuterOut<T>{nullptr, nullptr, nullptr, nullptr, nullptr, col_bits};
     if (last) {
+      out->row = all_row = bufs.get<uint32_t>((size_t)uniq);
       out->col = col = bufs.get<int32_t>((size_t)uniq);
       out->val = val = bufs.get<T>((size_t)uniq);
     } else {
+      out->keys = bufs.get<unsigned long long>((size_t)uniq);
       out->vals = bufs.get<double>((size_t)uniq);
     }
-    if (!out->keys || (last ? !out->col || !out->val : !out->vals)) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the all array failed");
+    if (last ? !out->row || !out->col || !out->val : !out->keys || !out->vals) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the all array failed");
     return SPGEMM_OK;
   };
   // Scan of the tiles' counts; their sum comes to the host.
   auto total_of = [&](int64_t tiles, unsigned* sums, unsigned* uniq) -> int {
-    hipLaunchKernelGGL(k_scan_top<unsigned>, dim3(1), dim3(256), 0, s, tiles, sums);
-    HIP_TRY(h, hipMemcpyAsync(uniq, sums + tiles, 4, hipMemcpyDeviceToHost, s));
+    hipLaunchKernelGGL(k_scan_top<unsigned>, dim3(1), dim3(256), 0, s, tiles, sums, host_stay);
     HIP_TRY(h, hipStreamSynchronize(s));
+    *uniq = *static_cast<volatile unsigned*>(host_stay);
     return SPGEMM_OK;
   };
-  bool plain_sorts = false;
+  bool plain_sorts = false, all_raw = false;   // all_raw: the all array is the first batch as its sort has left it, which nobody has waited for
+  auto was_too_long = [&] { return *static_cast<volatile int*>(too_long) != 0; };
+  *too_long = 0;
   for (long long t0 = 0; t0 < total; t0 += cap) {
     const int64_t cnt = total - t0 < cap ? total - t0 : cap;
     const bool last = t0 + cap >= total;
@@ -1763,7 +1777,6 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
     auto insert_and_sort = [&](bool plain) {
       SortPlan plan = sort_plan(cnt, col_bits + bits_of(m), plain || !buckets_pay(cnt, col_bits + bits_of(m)));
       const SortShape& sh = plan.sh;
-      hipLaunchKernelGGL(k_clear_ints, dim3(1), dim3(64), 0, s, too_long);
       // (the batches after the first are taken to be like it; one that is not is sorted again)
       const OuterKey key_at{(int64_t)t0, na, col_bits, off, match, A->ptr, B->ptr, A->idx, B->idx};
       BucketSample sample(h, cnt, col_bits + bits_of(m), t0 == 0, plan, key_at, keys[1]);
@@ -1784,49 +1797,99 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
       return plan.low > 0;
     };
     const bool buckets = insert_and_sort(plain_sorts);
-    // merge: equal coordinates of the batch, then the batch into the all array
-    const int64_t tiles = ceil_div(cnt, kRunTile);
-    unsigned* sums = bufs.get<unsigned>((size_t)tiles + 1);
-    if (!sums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the merge stage failed");
-    hipLaunchKernelGGL(k_run_count, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sums);
-    unsigned uniq = 0;
-    int rc = SPGEMM_OK, long_bucket = 0;
-    if (buckets) HIP_TRY(h, hipMemcpyAsync(&long_bucket, too_long, 4, hipMemcpyDeviceToHost, s));
-    rc = total_of(tiles, sums, &uniq);   // (waits)
-    if (rc) return rc;
-    if (long_bucket) {   // (again, and the batches after this one too, by passes alone)
+    int rc = SPGEMM_OK;
+    auto sort_again = [&] {   // (and the batches after this one too, by passes alone)
       plain_sorts = true;
+      *too_long = 0;
       (void)insert_and_sort(true);
-      hipLaunchKernelGGL(k_run_count, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sums);
-      if ((rc = total_of(tiles, sums, &uniq))) return rc;
-    }
+    };
     OuterOut<T> batch{};
-    if ((rc = room(uniq, last && all_n == 0, &batch))) return rc;
-    hipLaunchKernelGGL(k_run_sum<T>, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sorted, sums, batch);
-    bufs.release(sums);
-    if (all_n == 0) {
-      all_k = batch.keys; all_v = batch.vals; all_n = uniq;
+    unsigned uniq = 0;
+    // Equal coordinates of the batch are added up; with to_c that gives C.
+    auto add_up = [&](bool to_c) -> int {
+      const int64_t tiles = ceil_div(cnt, kRunTile);
+      unsigned* sums = bufs.get<unsigned>((size_t)tiles + 1);
+      if (!sums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the merge stage failed");
+      hipLaunchKernelGGL(k_run_count, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sums);
+      int r = total_of(tiles, sums, &uniq);   // (waits)
+      if (r) return r;
+      if (buckets && was_too_long()) {
+        sort_again();
+        hipLaunchKernelGGL(k_run_count, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sums);
+        if ((r = total_of(tiles, sums, &uniq))) return r;
+      }
+      if ((r = room(uniq, to_c, &batch))) return r;
+      hipLaunchKernelGGL(k_run_sum<T>, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sorted, sums, batch);
+      bufs.release(sums);
+      return SPGEMM_OK;
+    };
+    if (last && all_n == 0) {
+      if ((rc = add_up(true))) return rc;
+      all_n = uniq;
       continue;
     }
-    const int64_t both = all_n + (int64_t)uniq;
+    // Of several batches none has to be added up by itself: the merge takes components that are there more than once.
+    if (all_n == 0) {
+      // the first one: its buffers become the all array, and the accumulation array gets others, where these are not large
+      unsigned long long* next_keys = cap <= kOuterKeepCap ? bufs.get<unsigned long long>((size_t)cap) : nullptr;
+      double* next_vals = next_keys ? bufs.get<double>((size_t)cap) : nullptr;
+      if (next_vals) {
+        all_k = keys[cur]; all_v = sorted; all_n = cnt;
+        all_raw = buckets;
+        keys[cur] = next_keys;
+        vals[sorted == vals[0] ? 0 : 1] = next_vals;
+      } else {
+        bufs.release(next_keys);
+        if ((rc = add_up(false))) return rc;
+        all_k = batch.keys; all_v = batch.vals; all_n = uniq;
+      }
+      continue;
+    }
+    if (buckets || all_raw) {
+      HIP_TRY(h, hipStreamSynchronize(s));
+      if (was_too_long()) {
+        if (all_raw) {   // (this batch or the first one: from the start, by passes alone)
+          plain_sorts = true;
+          all_raw = false;
+          *too_long = 0;
+          bufs.release(all_k); bufs.release(all_v);
+          all_k = nullptr; all_v = nullptr; all_n = 0;
+          t0 = -cap;
+          continue;
+        }
+        sort_again();
+      }
+      all_raw = false;
+    }
+    int64_t batch_n = cnt;
+    const bool compact = all_n + cnt >= 0xffffffffLL;   // (too many, but perhaps not so many different ones)
+    if (compact) {
+      if ((rc = add_up(false))) return rc;
+      batch_n = uniq;
+    } else {
+      batch.keys = keys[cur];
+      batch.vals = sorted;
+    }
+    const int64_t both = all_n + batch_n;
     if (both >= 0xffffffffLL) return fail(h, SPGEMM_UNSUPPORTED, "the all array of the outer product would exceed 2^32 - 1 components");
     const int64_t mtiles = ceil_div(both, kMergeTile);
     int64_t* split = bufs.get<int64_t>((size_t)mtiles + 1);
     unsigned* msums = bufs.get<unsigned>((size_t)mtiles + 1);
     if (!split || !msums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the merge stage failed");
-    hipLaunchKernelGGL(k_merge_split, dim3((unsigned)ceil_div(mtiles + 1, 256)), dim3(256), 0, s, all_n, all_k, (int64_t)uniq, batch.keys, mtiles, split);
-    hipLaunchKernelGGL(k_merge_count, dim3((unsigned)mtiles), dim3(256), 0, s, all_n, all_k, (int64_t)uniq, batch.keys, split, msums);
+    hipLaunchKernelGGL(k_merge_split, dim3((unsigned)ceil_div(mtiles + 1, 256)), dim3(256), 0, s, all_n, all_k, batch_n, batch.keys, mtiles, split);
+    hipLaunchKernelGGL(k_merge_count, dim3((unsigned)mtiles), dim3(256), 0, s, all_n, all_k, batch_n, batch.keys, split, msums);
     unsigned merged = 0;
     if ((rc = total_of(mtiles, msums, &merged))) return rc;
     OuterOut<T> next{};
     if ((rc = room(merged, last, &next))) return rc;
-    hipLaunchKernelGGL(k_merge_put<T>, dim3((unsigned)mtiles), dim3(256), 0, s, all_n, all_k, all_v, (int64_t)uniq, batch.keys, batch.vals, split, msums, next);
+    hipLaunchKernelGGL(k_merge_put<T>, dim3((unsigned)mtiles), dim3(256), 0, s, all_n, all_k, all_v, batch_n, batch.keys, batch.vals, split, msums, next);
     HIP_TRY(h, hipGetLastError());
-    bufs.release(all_k); bufs.release(all_v); bufs.release(batch.keys); bufs.release(batch.vals); bufs.release(split); bufs.release(msums);
+    bufs.release(all_k); bufs.release(all_v); bufs.release(split); bufs.release(msums);
+    if (compact) { bufs.release(batch.keys); bufs.release(batch.vals); }
     all_k = next.keys; all_v = next.vals; all_n = merged;
   }
   // compress: columns and values are there, the row pointer comes from the coordinates
-  hipLaunchKernelGGL(k_key_ptr<unsigned long long>, dim3((unsigned)ceil_div(m + 1, kPtrRows)), dim3(256), 0, s, all_n, m, col_bits, all_k ? all_k : keys[0], rp);
+  hipLaunchKernelGGL(k_key_ptr<uint32_t>, dim3((unsigned)ceil_div(m + 1, kPtrRows)), dim3(256), 0, s, all_n, m, 0, all_row, rp);
   HIP_TRY(h, hipGetLastError());
   HIP_TRY(h, hipStreamSynchronize(s));
   bufs.keep(rp); bufs.keep(col); bufs.keep(val);

@@ -114,3 +114,31 @@ def test_a_last_batch_that_is_cut_into_more_ranges_than_a_full_one():
     assert products // (1025 * tile) == 1 and 513 * tile < last <= 1024 * tile
     _, _, C = run_outer(A, B, 1025 * tile)
     check_against_oracles(A, B, C, "long last batch")
+
+
+@pytest.mark.parametrize("batches_before", [1, 2])
+def test_a_later_batch_that_no_bucket_holds(batches_before):
+    """Batches of evenly spread products, then one that is all in one row: found out when the first batch has only been sorted (everything
+    again, by passes alone), and when it has been merged (that batch again)."""
+    rng = np.random.default_rng(61)
+    m, n, per, batch = 200_000, 65_536, 40, 1_200_000
+    spread = batches_before * batch // (per * 4)           # columns of A with four entries each
+    late = batch // per                                    # columns with one entry, of row 7
+    k = spread + late
+    rows = np.concatenate([rng.integers(0, m, 4 * spread), np.full(late, 7)])
+    cols = np.concatenate([np.repeat(np.arange(spread), 4), np.arange(spread, k)])
+    key = np.unique(rows.astype(np.int64) * k + cols)
+    rp = np.concatenate([[0], np.cumsum(np.bincount(key // k, minlength=m))]).astype(np.int64)
+    A = W.CSR(m, k, rp, (key % k).astype(np.int32), rng.uniform(-1, 1, key.size))
+    B = W.uniform_rows(k, n, per, 63, 3, np.float64)
+    _, _, C = run_outer(A, B, batch)
+    check_against_oracles(A, B, C, f"after {batches_before} batches")
+
+
+@pytest.mark.parametrize("capacity", [50_000, 100_000, 1 << 20])
+def test_batches_with_hardly_a_coordinate_of_their_own(capacity):
+    """Every coordinate comes hundreds of times in every batch, and across their ends."""
+    A = W.uniform_rows(40, 2000, 1000, 65, 1, np.float32)
+    B = W.uniform_rows(2000, 30, 10, 65, 3, np.float32)
+    _, _, C = run_outer(A, B, capacity)
+    check_against_oracles(A, B, C, f"capacity {capacity}")
