@@ -473,8 +473,12 @@ __device__ __forceinline__ void scatter_bins(const int (&bin)[kScanItems], const
   int rank[kScanItems];
 #pragma unroll
   for (int u = 0; u < kScanItems; ++u) rank[u] = 0;
-  for (int v = 0; v <= kLightBin; ++v) {
-    if (v == kEmptyBin || (v == kLightBin && !LIGHT)) continue;   // (rows with no work are not listed)
+  unsigned present = 0;   // bins that have rows
+#pragma unroll
+  for (int b = 0; b < kNumBins - 1; ++b) present |= hist[b] ? 1u << b : 0u;
+  if (LIGHT && (present >> 4 & 1u)) present |= 1u << kLightBin;
+  for (int v = 0; v <= kLightBin; ++v) {   // (rows with no work are not listed)
+    if (!(present >> v & 1u)) continue;
     unsigned before = 0;
 #pragma unroll
     for (int u = 0; u < kScanItems; ++u) {
@@ -485,7 +489,7 @@ __device__ __forceinline__ void scatter_bins(const int (&bin)[kScanItems], const
     if (lane == 0) sl->count[v][wave] = before;
   }
   __syncthreads();
-  if (tid < kNumBins - 1 || (LIGHT && tid == kLightBin)) {
+  if (tid <= kLightBin && (present >> tid & 1u)) {
     unsigned run = 0;
     for (int w = 0; w < kScanWaves; ++w) { const unsigned c = sl->count[tid][w]; sl->count[tid][w] = run; run += c; }
     unsigned base = 0;
