@@ -296,7 +296,9 @@ __device__ __forceinline__ void tile_run(const RunRec rr, TileScratch<T, WHOLE, 
         const int32_t* words = col_list + list_at + span_rank_slots(span_flag_words(n_cols, span_c0)) + rel;
         const int ngrp = nw / kGrpWords;
         const int nw_kept = (int)((t_hi - t_lo + 31) >> 5);   // (the last block of the matrix may be cut short)
-        constexpr int kGrpBatch = 4;
+        // (loads of two groups in flight: R-MAT squared, whole calls, us with one | two | four | eight: scale 14 456 | 455 | 457 | 473, scale 17
+        // 4364 | 4312 | 4390 | 4609, scale 16 (fp64) 1425 | 1409 | 1418 | -)
+        constexpr int kGrpBatch = 2;
         for (int g0 = wave; g0 < ngrp; g0 += WAVES * kGrpBatch) {
           int wd[kGrpBatch], rk[kGrpBatch];
 #pragma unroll
