@@ -401,6 +401,15 @@ unsigned record_grid(spgemm_context* h, const spgemm_plan_s* p, int64_t rows) {
   return (unsigned)(ceil_div(grid_for(rows, 4, most), kDies) * kDies);
 }
 
+// Workgroups of the sorted-list kernels, per_block rows at a time: each keeps the loads of several rows in flight and pays for their first ones, so
+// it should have some twenty times as many; beyond 32 for a compute unit (what is resident, a few times over) they only even out the end.  Whole calls,
+// us with 32 | 48 | 96 | 128 a compute unit: 4.2 M rows of 8 x 4 2460 | 2431 | 2434 | 2443, 3 M of 10 x 9 3645 | 3598 | 3555 | 3537, 2 M of 5 x 4 871 | 862 |
+// 904 | 912, 400 000 of 8 x 8 461 | 467 | 488 | 504.
+unsigned sorted_grid(spgemm_context* h, int64_t rows, int64_t per_block) {
+  const int64_t least = (int64_t)h->num_cus * 32, most = (int64_t)h->num_cus * 128, twenty = ceil_div(rows, per_block) / 20;
+  return grid_for(rows, per_block, twenty < least ? least : (twenty < most ? twenty : most));
+}
+
 // Whether the classes of shorter rows share a launch (short_kernels.hpp): where there are rows of two of them, and no more than fill the chip
 // kShortRounds times (each class counted in the workgroups it would like).
 constexpr int64_t kShortRounds = 16;
@@ -689,10 +698,10 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
           with_flag_words(B->cols, rows);
         }
         if (hist[0] && !p->flag_rows)
-          hipLaunchKernelGGL((p->desc ? k_esc_sym<16, 32, true> : k_esc_sym<16, 32, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s,
+          hipLaunchKernelGGL((p->desc ? k_esc_sym<16, 32, true> : k_esc_sym<16, 32, false>), dim3(sorted_grid(h, hist[0], 16)), dim3(256), 0, s,
                              p->perm_sym, p->ctl, 0, A->rowptr, A->colidx, B->rowptr, p->desc, B->colidx, B->nnz, pack32, p->cnt, p->esc_words[0]);
         if (hist[1] && !p->flag_rows)
-          hipLaunchKernelGGL((p->desc ? k_esc_sym<64, 128, true> : k_esc_sym<64, 128, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0,
+          hipLaunchKernelGGL((p->desc ? k_esc_sym<64, 128, true> : k_esc_sym<64, 128, false>), dim3(sorted_grid(h, hist[1], 4)), dim3(256), 0,
                              s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx, B->rowptr, p->desc, B->colidx, B->nnz, pack128, p->cnt,
                              p->esc_words[1]);
       }
@@ -819,19 +828,19 @@ int run_numeric(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const 
         };
         with_flag_words(B->cols, rows);
       } else if (words0)
-        hipLaunchKernelGGL((p->desc ? k_esc_num<16, 32, T, true> : k_esc_num<16, 32, T, false>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256),
+        hipLaunchKernelGGL((p->desc ? k_esc_num<16, 32, T, true> : k_esc_num<16, 32, T, false>), dim3(sorted_grid(h, hist[0], 16)), dim3(256),
                            0, s, p->perm_sym, p->ctl, 0, A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[0], c_rp,
                            c_col, c_val);
       else if (hist[0])
-        hipLaunchKernelGGL((k_esc<16, 32, T>), dim3(grid_for(hist[0], 16, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 0,
+        hipLaunchKernelGGL((k_esc<16, 32, T>), dim3(sorted_grid(h, hist[0], 16)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 0,
                            A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack32, B->nnz);
       if (p->flag_rows) {
       } else if (words1)
-        hipLaunchKernelGGL((p->desc ? k_esc_num<64, 128, T, true> : k_esc_num<64, 128, T, false>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256),
+        hipLaunchKernelGGL((p->desc ? k_esc_num<64, 128, T, true> : k_esc_num<64, 128, T, false>), dim3(sorted_grid(h, hist[1], 4)), dim3(256),
                            0, s, p->perm_sym, p->ctl, 1, A->rowptr, A->colidx, a_val, B->rowptr, p->desc, b_val, B->nnz, p->esc_words[1], c_rp,
                            c_col, c_val);
       else if (hist[1])
-        hipLaunchKernelGGL((k_esc<64, 128, T>), dim3(grid_for(hist[1], 4, cap_small)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 1,
+        hipLaunchKernelGGL((k_esc<64, 128, T>), dim3(sorted_grid(h, hist[1], 4)), dim3(256), 0, s, p->perm_num, p->ctl, 1, 1,
                            A->rowptr, A->colidx, a_val, B->rowptr, B->colidx, b_val, c_rp, c_col, c_val, pack128, B->nnz);
     }
     {
