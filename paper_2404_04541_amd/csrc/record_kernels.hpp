@@ -42,7 +42,10 @@ constexpr int kRecColBits = 23;                                // a column and i
 static_assert(kNumHashSmall <= 256, "a rank fits a byte");
 static_assert(kRecWords % 4 == 0 && kRecRankWords % 4 == 0, "records and their column lists start on 16 bytes");
 constexpr int kRecordGroups = 4;                               // workgroups of these kernels on a compute unit
-constexpr int kSymLogSlots = 10;
+// Slots of the set: 2.7 times the most products.  With 1024 the slowest lane of an insertion walked over twenty taken ones and more, and a row of 768
+// products took 35 us: whole calls, us with 1024 | 2048: ragged 5003 rows 240 | 219, R-MAT squared scale 12 214 | 206, 14 455 | 439, 30 000 ragged rows
+// of 20 x 20 573 | 532, 60 000 of 16 x 16 550 | 547.
+constexpr int kSymLogSlots = 11;
 constexpr int kSymSlots = 1 << kSymLogSlots;
 // sums of a row in LDS (a rank is a byte), and a place for every lane's missing products
 constexpr int kRecSums = 256 + kWave;
