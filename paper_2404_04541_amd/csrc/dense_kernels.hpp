@@ -132,17 +132,15 @@ __device__ __forceinline__ void block_excl_scan2(int a, int b, int& ea, int& eb,
   eb = pb + ib - b;
 }
 
-// Visits every element of the pieces once.  A piece is cut into quads; the quads of all pieces are dealt to the waves in
-// contiguous shares of whole batches of 64, a lane takes a quad: one load of four columns and one of four values.  Which piece a lane's quad belongs to: lane i looks at where the i-th piece behind the one in hand begins and pushes
-// i + 1 to the lane whose quad that is; a running maximum spreads it to the lanes behind.
-// g(quad) is called per lane and batch (a, b only meaningful when WITH_VALUES).
-// What bounds the pass is not traffic but what a wave does between loads: chunks of 64 elements with wave-uniform descriptors
-// took about 35 scalar and 10 vector instructions a chunk and were 70 % full with pieces of 122 entries; quads are 98 % full
-// and take about 45 per 256 elements.  R-MAT scale 19 squared (fp32), k_num_wide 27.9 -> 25.9 ms; scale 14: numeric 218 ->
-// 190 us, symbolic 229 -> 208 us; deduplication sweep (fp64) 1.64 -> 1.59 ms.  With values one batch at a time is best (two in
-// flight 26.5 ms, three 29.7, four 31.8: registers; the next one prefetched 25.9, but 1.69 for the sweep); without them the
-// next batch is prefetched (15.8 ms at scale 19 against 16.5).  At scale 20 the symbolic kernel lost a little against the chunks
-// (42.2 -> 43.7 ms), the numeric one gained 6 ms.
+// Visits every element of the pieces once (k_num_wide; cpre counts quads here).  A piece is cut into quads; the quads of all pieces are dealt to the waves
+// in contiguous shares of whole batches of 64, a lane takes a quad: one load of four columns and one of four values.  Which piece a lane's quad belongs to:
+// lane i looks at where the i-th piece behind the one in hand begins and pushes i + 1 to the lane whose quad that is; a running maximum spreads it to the
+// lanes behind.  g(quad) is called per lane and batch (a, b only meaningful when WITH_VALUES).
+// What bounds the numeric pass is neither traffic nor its instructions (a search for every 64 chunks, as in piece_pass, is slower here: rows in any order 577 |
+// 634 us) but the chain of loads and LDS steps of a batch.  Chunks of 64 elements with wave-uniform descriptors took about 35 scalar and 10 vector
+// instructions a chunk and were 70 % full with pieces of 122 entries; quads are 98 % full and take about 45 per 256 elements.  R-MAT scale 19 squared
+// (fp32), k_num_wide 27.9 -> 25.9 ms; scale 14: numeric 218 -> 190 us; deduplication sweep (fp64) 1.64 -> 1.59 ms.  With values one batch at a time is best
+// (two in flight 26.5 ms, three 29.7, four 31.8: registers; the next one prefetched 25.9, but 1.69 for the sweep).
 template <int WAVES, bool WITH_VALUES, typename T, class G>
 __device__ __forceinline__ void quad_pass(int np, int nq, const PieceList<T, long long> pl, const int32_t* __restrict__ b_col,
                                           const T* __restrict__ b_val, int64_t b_nnz, G g) {
@@ -427,11 +425,12 @@ __device__ __forceinline__ void plan_tail(TilePlan* tp, int nb, int block0, int 
   }
 }
 
-// The numeric kernels' runs lie in the order of the symbolic kernel's rows, the heaviest first, and workgroups draw them by number.  Where there are few for a workgroup
-// they are taken in that order, so that no workgroup is left with a long row at the end.  Where there are many, every draw of four is from the
+// The numeric kernels' runs lie in the order of the symbolic kernel's rows, the heaviest first, and workgroups draw them by number.  Where there are few
+// for a workgroup they are taken in that order, so that no workgroup is left with a long row at the end.  Where there are many, every draw of four is from the
 // front and the others are from the back: heavy rows use the memory, light ones wait for it, and both kinds do better beside the other.  Numeric kernel of
 // R-MAT squared, us in order | from both ends: scale 14 146 | 161, scale 16 746 | 768 (53 runs a workgroup), scale 17 2812 | 2774 (97), 18 8886 |
-// 7827, 19 25364 | 23041; 60 000 rows of 3600 products 1443 | 1409.  One of two and one of eight do less for the larger ones (19: 23413, 23494).
+// 7827, 19 25364 | 23041 (before: in the order in which the symbolic workgroups drew records, 165, 784, 2840, 8096, 23636; k_num_wide, scale 20,
+// 70.0 ms before and 72.0); 60 000 rows of 3600 products 1443 | 1409.  One of two and one of eight do less for the larger ones (19: 23413, 23494).
 constexpr unsigned kManyRuns = 64;
 __device__ __forceinline__ unsigned run_of(unsigned draw, unsigned nruns) {
   if (nruns < kManyRuns * gridDim.x || draw >= nruns) return draw;

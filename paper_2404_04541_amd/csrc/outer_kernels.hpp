@@ -5,8 +5,9 @@
 // they pass through a workspace of whole components:
 //   insert   a batch of products fills the accumulation array: coordinate (i above the bits of j, one 64-bit key) and a_ik * b_kj
 //   sort     the accumulation array goes into result order (stable radix sort by coordinate, values along)
-//   merge    equal coordinates of the batch are added up (the first component of a run walks it, in order), and the sorted batch
-//            is merged into the all array (sorted, unique), where the all array's component takes the batch's along
+//   merge    the first batch's array becomes the all array; every other sorted batch is merged into it, and the first component of a
+//            coordinate takes the values of all others along, whichever array holds them (a single batch is added up instead: the first
+//            component of a run walks it, in order)
 //   compress the last of these stages writes columns and values of C, the row pointer comes from the coordinates
 // On the GPU a batch is inserted by one launch, a workgroup taking a range of the sort and finding the columns of A of a tile of
 // products once, and the merge is cut into tiles along the diagonals of the two arrays; the stages and the two arrays are the

@@ -1,5 +1,5 @@
 // The classes of shorter rows (0 to 3) in one launch, a stretch of workgroups for each, where they are few: the kernel of a class takes as long as
-// its slowest row (a chain of dependent loads and LDS steps: 5 us for 128 products, 35 us for 768 of more than 64 entries), whether it has ten rows
+// its slowest row (a chain of dependent loads and LDS steps: 5 us for 128 products, 25 us for 768, 35 before their set had 2048 slots), whether it has ten rows
 // or a thousand, and so do four of them one after the other, with a launch each.
 // Bound: the slowest row.  Registers and LDS are those of the hungriest class, 16 waves on a compute unit, so where the rows fill the
 // chip several times over the kernels of the classes follow each other as before (short_rows_ok).
