@@ -243,8 +243,7 @@ __device__ __forceinline__ void stream_columns(int64_t a0, int d, const int32_t*
     __syncthreads();
     SPG_CLK(clk_mark(&rs->clk, 2); clk_add(&rs->clk, 18, 1); clk_add(&rs->clk, 19, (unsigned long long)cut.chunks << cut.lanes);)
     if (cut.chunks > 0)
-      piece_pass<WAVES, false, int, long long>(cut.pieces, cut.chunks, cut.lanes, PieceList<int, long long>{rs->start, rs->cpre, rs->plen, nullptr}, b_col,
-                                               static_cast<const int*>(nullptr), b_nnz, f);
+      piece_pass<WAVES>(cut.pieces, cut.chunks, cut.lanes, PieceList<int, long long>{rs->start, rs->cpre, rs->plen, nullptr}, b_col, b_nnz, f);
     SPG_CLK(clk_mark(&rs->clk, 3);)
     __syncthreads();
     SPG_CLK(clk_mark(&rs->clk, 4);)

@@ -1,5 +1,5 @@
-// The walk over the products of a row that the dense kernels share: the pieces of B's rows that the row's entries of A ask for,
-// four consecutive elements (a quad) to a lane.
+// The dense symbolic kernel's walk over the products of a row: the pieces of B's rows that the row's entries of A ask for,
+// four consecutive elements (a quad) to a lane.  (Quads and lists of pieces are the numeric kernels' too.)
 //
 // A piece is cut into chunks of L = 1, 4 or 16 quads (the last one may be short); the chunks of all pieces are dealt to the waves in
 // contiguous shares.  A wave finds where its next 64 chunks lie at once, a chunk to a lane: lane i looks at where the i-th
@@ -85,10 +85,10 @@ __device__ __forceinline__ PieceCut piece_chunks(int len, int* red) {
 }
 
 // Visits every element of np pieces (nch chunks of 2^lanes quads) once: g(quad, full) per lane and batch, full (a type) where all lanes' quads
-// are (a, b only meaningful when WITH_VALUES).
-template <int WAVES, bool WITH_VALUES, typename T, typename Start, class G>
-__device__ __forceinline__ void piece_pass(int np, int nch, int lanes, const PieceList<T, Start> pl, const int32_t* __restrict__ b_col,
-                                           const T* __restrict__ b_val, int64_t b_nnz, G g) {
+// are; columns only.
+template <int WAVES, class G>
+__device__ __forceinline__ void piece_pass(int np, int nch, int lanes, const PieceList<int, long long> pl, const int32_t* __restrict__ b_col, int64_t b_nnz,
+                                           G g) {
   const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int cpb = kWave >> lanes;   // chunks of a batch
   const int nb = (nch + cpb - 1) >> (6 - lanes);
@@ -105,10 +105,9 @@ __device__ __forceinline__ void piece_pass(int np, int nch, int lanes, const Pie
     p = hi * 16 + __popcll(__ballot(lane < 16 && i1 < np && pl.cpre[i1 < np ? i1 : 0] <= c)) - 1;
   }
   const int in = (lane & ((1 << lanes) - 1)) * 4;   // where the lane's quad lies in its chunk
-  constexpr bool kLong = sizeof(Start) == 8;
-  Quad<T> now;
+  Quad<int> now;
   bool have = false;
-  auto visit = [&](const Quad<T>& q) {
+  auto visit = [&](const Quad<int>& q) {
     if (__all(q.n >= 4)) g(q, std::true_type{});
     else g(q, std::false_type{});
   };
@@ -120,62 +119,33 @@ __device__ __forceinline__ void piece_pass(int np, int nch, int lanes, const Pie
     m = group_max_scan<kWave>(lane == 0 ? 0 : m);
     const int piece = p + m;
     const int off = (c + lane - pl.cpre[piece]) << (lanes + 2);
-    const Start at0 = pl.s[piece] + (Start)off;
+    const long long at0 = pl.s[piece] + off;
     const int left0 = c + lane < cend ? pl.len[piece] - off : 0;
-    T a0{};
-    if (WITH_VALUES) a0 = pl.av[piece];
     p += __popcll(__ballot(begins <= kWave));
     const int left_chunks = cend - c < kWave ? cend - c : kWave;
     const int batches = (left_chunks + cpb - 1) >> (6 - lanes);
     int src = (lane >> lanes) * 4;
     for (int b = 0; b < batches; ++b, src += cpb * 4) {
-      Quad<T> q;
-      Start at;
-      if constexpr (kLong) {
-        const unsigned lo = (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)(unsigned)(unsigned long long)at0);
-        const unsigned hi = (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)(unsigned)((unsigned long long)at0 >> 32));
-        at = (Start)(((unsigned long long)hi << 32) | lo);
-      } else {
-        at = (Start)__builtin_amdgcn_ds_bpermute(src, (int)at0);
-      }
+      Quad<int> q;
+      const unsigned lo = (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)(unsigned)(unsigned long long)at0);
+      const unsigned hi = (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)(unsigned)((unsigned long long)at0 >> 32));
+      const long long at = (long long)(((unsigned long long)hi << 32) | lo) + in;
       q.n = __builtin_amdgcn_ds_bpermute(src, left0) - in;
-      at += (Start)in;
-      if (WITH_VALUES) {
-        if constexpr (sizeof(T) == 8) {
-          const unsigned long long w = (unsigned long long)__double_as_longlong((double)a0);
-          const unsigned lo = (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)(unsigned)w);
-          const unsigned hi = (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)(unsigned)(w >> 32));
-          q.a = (T)__longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-        } else {
-          q.a = (T)__int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int((float)a0)));
-        }
-      }
       if (__all(q.n >= 4)) {
         q.col = load_run<int32_t, 4>(b_col + at);
-        if (WITH_VALUES) q.b = load_run<T, 4>(b_val + at);
-      } else if (!__any(q.n > 0 && at + 4 > (Start)b_nnz)) {
-        if (q.n > 0) {
-          q.col = load_run<int32_t, 4>(b_col + at);
-          if (WITH_VALUES) q.b = load_run<T, 4>(b_val + at);
-        }
+      } else if (!__any(q.n > 0 && at + 4 > b_nnz)) {
+        if (q.n > 0) q.col = load_run<int32_t, 4>(b_col + at);
       } else {   // (fewer than four elements behind some lane's position)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (i < q.n) {
-            q.col.v[i] = b_col[at + i];
-            if (WITH_VALUES) q.b.v[i] = b_val[at + i];
-          }
+          if (i < q.n) q.col.v[i] = b_col[at + i];
       }
-      if constexpr (WITH_VALUES) {
-        visit(q);
-      } else {   // (the next batch is on its way while g works on this one)
-        if (have) visit(now);
-        now = q;
-        have = true;
-      }
+      if (have) visit(now);   // (the next batch is on its way while g works on this one)
+      now = q;
+      have = true;
     }
   }
-  if constexpr (!WITH_VALUES) visit(now);
+  visit(now);
 }
 
 }  // namespace spg
