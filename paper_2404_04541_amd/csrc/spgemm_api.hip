@@ -38,9 +38,10 @@ static_assert(sym_dense_lds<16, 1024>(kSymFlagWords) <= 160 * 1024, "symbolic de
 static_assert(sym_dense_lds<16, 512>(kSymNarrowCols / 32) <= 80 * 1024 && sym_dense_lds<16, 1024>(kSymShortCols / 32) <= 80 * 1024 && num_tiles_lds<double>() <= 80 * 1024, "two workgroups on a compute unit");
 static_assert(staged_lds<double>() <= 160 * 1024 && staged_lds<float>() <= 160 * 1024, "staged kernel exceeds LDS");
 
-// Pinned host memory where the symbolic kernels leave the control block for the host.  Allocating and releasing it costs 50 to
+// Pinned host memory where kernels leave numbers for the host (the symbolic ones the control block).  Allocating and releasing it costs 50 to
 // 300 us, so a few blocks wait for the next calls; a call holds its own from before its first kernel until its stream has been
-// waited for, whatever handle, stream or thread it comes from.
+// waited for, whatever handle, stream or thread it comes from: the lease itself waits where the call returns before it has (an
+// allocation that is refused while kernels are on their way).
 namespace {
 
 class PinnedBlocks {
@@ -71,10 +72,20 @@ PinnedBlocks g_pinned;
 
 struct PinnedLease {
   Control* p;
-  PinnedLease() : p(g_pinned.take()) {}
-  ~PinnedLease() { if (p) g_pinned.give(p); }
+  explicit PinnedLease(hipStream_t stream) : p(g_pinned.take()), stream_(stream) {}
+  ~PinnedLease() {
+    if (!p) return;
+    if (written_) (void)hipStreamSynchronize(stream_);
+    g_pinned.give(p);
+  }
+  void written() { written_ = true; }   // kernels that write to the block are about to be launched
+  void waited() { written_ = false; }   // and all of them are done
   PinnedLease(const PinnedLease&) = delete;
   PinnedLease& operator=(const PinnedLease&) = delete;
+
+ private:
+  hipStream_t stream_;
+  bool written_ = false;
 };
 
 }  // namespace
@@ -904,7 +915,7 @@ int symbolic(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B, int64_
   *plan = nullptr;
   if ((rc = ensure_device(h))) return rc;
   drop_timed(h);   // (timed launches of an earlier plan that nobody asked about)
-  PinnedLease pinned;
+  PinnedLease pinned(h->stream);
   if (!pinned.p) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of pinned host memory failed");
 
   spgemm_plan_s* p = new (std::nothrow) spgemm_plan_s();
@@ -943,6 +954,7 @@ int symbolic(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B, int64_
   p->partial = reinterpret_cast<long long*>(base + o_part);
 
   Control host{};
+  pinned.written();
   rc = run_setup(h, p, A, B, pinned.p, &host);
   if (rc == SPGEMM_OK && !host.error)
     rc = (A->dtype == SPGEMM_F32) ? run_symbolic<float>(h, p, A, B, c_rowptr, host, pinned.p, plan_leaves)
@@ -952,8 +964,9 @@ int symbolic(spgemm_context* h, const spgemm_csr* A, const spgemm_csr* B, int64_
     if (e != hipSuccess) rc = fail(h, SPGEMM_HIP_ERROR, std::string("symbolic phase: ") + hipGetErrorString(e));
     else std::memcpy(&host, pinned.p, sizeof(Control));
   }
+  if (rc != SPGEMM_OK) (void)hipStreamSynchronize(h->stream);
+  pinned.waited();
   if (rc != SPGEMM_OK) {
-    (void)hipStreamSynchronize(h->stream);
     drop_timed(h);
     spgemm_plan_destroy(p);
     return rc;
@@ -1264,12 +1277,13 @@ int sort_pairs(spgemm_context* h, int64_t n, const SortShape& sh, K* const keys[
 class BucketSample {
  public:
   template <class KeyAt>
-  BucketSample(spgemm_context* h, int64_t n, int nbits, bool wanted, const SortPlan& plan, const KeyAt& key_at, void* counts) : h_(h) {
+  BucketSample(spgemm_context* h, int64_t n, int nbits, bool wanted, const SortPlan& plan, const KeyAt& key_at, void* counts) : h_(h), block_(h->stream) {
     if (!wanted || plan.low == 0) return;
     asked_ = true;
     if (!block_.p) return;
     flag_ = reinterpret_cast<int*>(block_.p);
     *flag_ = 0;
+    block_.written();
     const unsigned buckets = 1u << (nbits - plan.low);
     hipLaunchKernelGGL(k_sample_clear, dim3((unsigned)ceil_div(buckets + 1, kSampleThreads)), dim3(kSampleThreads), 0, h->stream, buckets,
                        static_cast<unsigned*>(counts));
@@ -1289,6 +1303,7 @@ class BucketSample {
     if (flag_) {
       const hipError_t e = done_ ? hipEventSynchronize(done_) : hipStreamSynchronize(h_->stream);
       crowded_ = e != hipSuccess || *static_cast<volatile int*>(flag_) != 0;
+      if (e == hipSuccess) block_.waited();
       flag_ = nullptr;
       if (done_) h_->event_pool.push_back(done_);
     } else if (asked_ && !block_.p) {
@@ -1695,11 +1710,13 @@ int dcs_compress(spgemm_context* h, int64_t n, int64_t nnz, const int64_t* ptr, 
   hipLaunchKernelGGL(k_dcs_flags, dim3(g), dim3(256), 0, s, n, ptr, pos);
   unsigned* sums = bufs.get<unsigned>((size_t)ceil_div(n > 0 ? n : 1, kScanTileN) + 1);
   if (!sums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the doubly compressed format failed");
-  PinnedLease pinned;
+  PinnedLease pinned(s);
   if (!pinned.p) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of pinned host memory failed");
   unsigned* host = reinterpret_cast<unsigned*>(pinned.p);
+  pinned.written();
   scan_values(h, n, pos, sums, host);
   HIP_TRY(h, hipStreamSynchronize(s));
+  pinned.waited();
   const unsigned total = *static_cast<volatile unsigned*>(host);
   *nvec = total;
   *vec = bufs.get<int32_t>((size_t)total + 1);
@@ -1717,9 +1734,11 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
   hipStream_t s = h->stream;
   const int64_t m = A->minor_dim, n = B->minor_dim, na = A->nvec, nb = B->nvec;
   DevBufs bufs(h);
-  // numbers that come to the host: the products, components that stay, whether a bucket of a sort was too long
-  PinnedLease pinned;
+  // numbers that come to the host: the products, components that stay, whether a bucket of a sort was too long.  (Sorts that may write the
+  // last one are on their way whenever memory is refused.)
+  PinnedLease pinned(s);
   if (!pinned.p) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of pinned host memory failed");
+  pinned.written();
   long long* host_total = reinterpret_cast<long long*>(pinned.p);
   unsigned* host_stay = reinterpret_cast<unsigned*>(host_total + 1);
   int* too_long = reinterpret_cast<int*>(host_total + 2);
@@ -1901,6 +1920,7 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
   hipLaunchKernelGGL(k_key_ptr<uint32_t>, dim3((unsigned)ceil_div(m + 1, kPtrRows)), dim3(256), 0, s, all_n, m, 0, all_row, rp);
   HIP_TRY(h, hipGetLastError());
   HIP_TRY(h, hipStreamSynchronize(s));
+  pinned.waited();
   bufs.keep(rp); bufs.keep(col); bufs.keep(val);
   C->rows = m; C->cols = n; C->nnz = all_n; C->dtype = A->dtype;
   C->rowptr = rp; C->colidx = col; C->values = val;

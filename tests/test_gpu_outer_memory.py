@@ -1,0 +1,85 @@
+"""Outer products whose allocator refuses memory: what is on its way then, and that the optional memory is optional."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2404_04541_amd import workloads as W
+from helpers import RTOL, assert_matches_oracle
+from test_gpu_plan_memory import Memory
+
+pytestmark = pytest.mark.gpu
+
+
+class Outer:
+    """Operands, the product from the oracle, and calls of spgemm_outer with an allocator's memory."""
+
+    def __init__(self, A, B, capacity):
+        from paper_2404_04541_amd import binding as sg
+        self.sg, self.capacity, self.dtype = sg, capacity, A.values.dtype
+        h = sg.Handle()
+        self.a, self.b = sg.dcsc_from_csr(h, sg.to_device(A)), sg.dcsr_from_csr(h, sg.to_device(B))
+        self.ref = oracle.spgemm(A, B)
+        self.products = int(self.ref.ip.sum())
+
+    def call(self, m, check=True):
+        """-> the call's status, and whether the stream was idle when it returned."""
+        import torch
+        sa, sb, sc = self.a.struct(), self.b.struct(), self.sg.CsrStruct()
+        torch.cuda.synchronize()
+        rc = m.lib.spgemm_outer(m.h, C.byref(sa), C.byref(sb), self.capacity, C.byref(sc))
+        idle = torch.cuda.current_stream().query()
+        torch.cuda.synchronize()
+        if rc == 0:
+            if check:
+                ref, dtype = self.ref, torch.from_numpy(np.zeros(1, self.dtype)).dtype
+                get = lambda ptr, n, t: m.live[ptr][:n * t.itemsize].view(t).cpu().numpy()  # noqa: E731
+                assert np.array_equal(get(sc.rowptr, sc.rows + 1, torch.int64), ref.rowptr)
+                assert np.array_equal(get(sc.colidx, sc.nnz, torch.int32), ref.colidx)
+                err = np.abs(get(sc.values, sc.nnz, dtype).astype(np.float64) - ref.values.astype(self.dtype).astype(np.float64))
+                assert np.all(err <= RTOL[np.dtype(self.dtype)] * ref.absum)
+            for ptr in (sc.rowptr, sc.colidx, sc.values):
+                m.lib.spgemm_free_device(m.h, ptr)
+        return rc, idle
+
+
+def refuse_request(number):
+    count = [0]
+
+    def refuse(_n, _used):
+        count[0] += 1
+        return count[0] - 1 == number
+    return refuse
+
+
+@pytest.mark.parametrize("batches", [1, 2])
+def test_nothing_is_on_its_way_when_a_request_is_refused(batches):
+    """Every request in turn: the call goes on without it, or returns when its kernels are done (they write to memory of the host that the next
+    call takes, here a product of another handle on another stream)."""
+    import torch
+    from paper_2404_04541_amd import binding as sg
+    A = W.uniform_rows(150_000, 50_000, 8, 81, 1, np.float64)
+    B = W.uniform_rows(50_000, 65_536, 5, 81, 3, np.float64)
+    o = Outer(A, B, 6_000_000 // batches)
+    assert o.products == 6_000_000
+    X, Y = W.config3(scale=10)
+    want = oracle.spgemm(X, Y)
+    side = torch.cuda.Stream()
+    other = sg.Handle(stream=side)
+    dX, dY = sg.to_device(X), sg.to_device(Y)
+    m = Memory(sg)
+    assert o.call(m)[0] == 0
+    m.close()
+    refused = 0
+    for number in range(len(m.asked)):
+        m = Memory(sg, refuse_request(number))
+        rc, idle = o.call(m)
+        assert rc in (0, -5) and idle, number
+        refused += rc != 0
+        m.close()
+        with torch.cuda.stream(side):
+            got = sg.spgemm(other, dX, dY)
+            side.synchronize()
+        assert_matches_oracle(X, Y, [t.cpu().numpy() for t in (got.rowptr, got.colidx, got.values)], want)
+    assert refused >= 8
