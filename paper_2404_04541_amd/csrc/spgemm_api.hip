@@ -1727,7 +1727,9 @@ int dcs_compress(spgemm_context* h, int64_t n, int64_t nnz, const int64_t* ptr, 
   return SPGEMM_OK;
 }
 
-constexpr int64_t kOuterKeepCap = (int64_t)1 << 26;   // accumulation arrays up to this long become the all array (1 GB, however many of its coordinates are equal)
+// Accumulation arrays up to this long become the all array (1 GB, however many of its coordinates are equal).  Where memory is refused before the
+// first merge is through, the call begins again without that.
+constexpr int64_t kOuterKeepCap = (int64_t)1 << 26;
 
 template <typename T>
 int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64_t cap, spgemm_csr* C) {
@@ -1784,8 +1786,10 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
       out->keys = bufs.get<unsigned long long>((size_t)uniq);
       out->vals = bufs.get<double>((size_t)uniq);
     }
-    if (last ? !out->row || !out->col || !out->val : !out->keys || !out->vals) return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the all array failed");
-    return SPGEMM_OK;
+    if (last ? out->row && out->col && out->val : out->keys && out->vals) return SPGEMM_OK;
+    bufs.release(out->row); bufs.release(out->col); bufs.release(out->val); bufs.release(out->keys); bufs.release(out->vals);
+    *out = OuterOut<T>{};
+    return fail(h, SPGEMM_ALLOC_FAILED, "allocation of the all array failed");
   };
   // Scan of the tiles' counts; their sum comes to the host.
   auto total_of = [&](int64_t tiles, unsigned* sums, unsigned* uniq) -> int {
@@ -1794,7 +1798,8 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
     *uniq = *static_cast<volatile unsigned*>(host_stay);
     return SPGEMM_OK;
   };
-  bool plain_sorts = false, all_raw = false;   // all_raw: the all array is the first batch as its sort has left it, which nobody has waited for
+  // kept: the all array is the first batch as its sort has left it; all_raw: and nobody has waited for that
+  bool plain_sorts = false, keep_first = cap <= kOuterKeepCap, kept = false, all_raw = false;
   auto was_too_long = [&] { return *static_cast<volatile int*>(too_long) != 0; };
   *too_long = 0;
   for (long long t0 = 0; t0 < total; t0 += cap) {
@@ -1840,16 +1845,46 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
       if (!sums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the merge stage failed");
       hipLaunchKernelGGL(k_run_count, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sums);
       int r = total_of(tiles, sums, &uniq);   // (waits)
-      if (r) return r;
-      if (buckets && was_too_long()) {
+      if (!r && buckets && was_too_long()) {
         sort_again();
         hipLaunchKernelGGL(k_run_count, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sums);
-        if ((r = total_of(tiles, sums, &uniq))) return r;
+        r = total_of(tiles, sums, &uniq);
       }
-      if ((r = room(uniq, to_c, &batch))) return r;
-      hipLaunchKernelGGL(k_run_sum<T>, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sorted, sums, batch);
+      if (!r) r = room(uniq, to_c, &batch);
+      if (!r) hipLaunchKernelGGL(k_run_sum<T>, dim3((unsigned)tiles), dim3(256), 0, s, cnt, keys[cur], sorted, sums, batch);
       bufs.release(sums);
-      return SPGEMM_OK;
+      return r;
+    };
+    // The batch into the all array.
+    auto merge = [&](int64_t batch_n) -> int {
+      const int64_t both = all_n + batch_n;
+      if (both >= 0xffffffffLL) return fail(h, SPGEMM_UNSUPPORTED, "the all array of the outer product would exceed 2^32 - 1 components");
+      const int64_t tiles = ceil_div(both, kMergeTile);
+      int64_t* split = bufs.get<int64_t>((size_t)tiles + 1);
+      unsigned* sums = bufs.get<unsigned>((size_t)tiles + 1);
+      unsigned merged = 0;
+      OuterOut<T> next{};
+      int r = split && sums ? SPGEMM_OK : fail(h, SPGEMM_ALLOC_FAILED, "allocation for the merge stage failed");
+      if (!r) {
+        hipLaunchKernelGGL(k_merge_split, dim3((unsigned)ceil_div(tiles + 1, 256)), dim3(256), 0, s, all_n, all_k, batch_n, batch.keys, tiles, split);
+        hipLaunchKernelGGL(k_merge_count, dim3((unsigned)tiles), dim3(256), 0, s, all_n, all_k, batch_n, batch.keys, split, sums);
+        r = total_of(tiles, sums, &merged);
+      }
+      if (!r) r = room(merged, last, &next);
+      if (!r) {
+        hipLaunchKernelGGL(k_merge_put<T>, dim3((unsigned)tiles), dim3(256), 0, s, all_n, all_k, all_v, batch_n, batch.keys, batch.vals, split, sums, next);
+        bufs.release(all_k); bufs.release(all_v);
+        all_k = next.keys; all_v = next.vals; all_n = merged;
+      }
+      bufs.release(split); bufs.release(sums);
+      return r;
+    };
+    auto from_start = [&] {   // the batches once more, from the first one on
+      bufs.release(all_k); bufs.release(all_v);
+      all_k = nullptr; all_v = nullptr; all_n = 0;
+      kept = all_raw = false;
+      *too_long = 0;
+      t0 = -cap;
     };
     if (last && all_n == 0) {
       if ((rc = add_up(true))) return rc;
@@ -1859,10 +1894,11 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
     // Of several batches none has to be added up by itself: the merge takes components that are there more than once.
     if (all_n == 0) {
       // the first one: its buffers become the all array, and the accumulation array gets others, where these are not large
-      unsigned long long* next_keys = cap <= kOuterKeepCap ? bufs.get<unsigned long long>((size_t)cap) : nullptr;
+      unsigned long long* next_keys = keep_first ? bufs.get<unsigned long long>((size_t)cap) : nullptr;
       double* next_vals = next_keys ? bufs.get<double>((size_t)cap) : nullptr;
       if (next_vals) {
         all_k = keys[cur]; all_v = sorted; all_n = cnt;
+        kept = true;
         all_raw = buckets;
         keys[cur] = next_keys;
         vals[sorted == vals[0] ? 0 : 1] = next_vals;
@@ -1878,43 +1914,31 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
       if (was_too_long()) {
         if (all_raw) {   // (this batch or the first one: from the start, by passes alone)
           plain_sorts = true;
-          all_raw = false;
-          *too_long = 0;
-          bufs.release(all_k); bufs.release(all_v);
-          all_k = nullptr; all_v = nullptr; all_n = 0;
-          t0 = -cap;
+          from_start();
           continue;
         }
         sort_again();
       }
       all_raw = false;
     }
-    int64_t batch_n = cnt;
     const bool compact = all_n + cnt >= 0xffffffffLL;   // (too many, but perhaps not so many different ones)
     if (compact) {
-      if ((rc = add_up(false))) return rc;
-      batch_n = uniq;
+      rc = add_up(false);
     } else {
       batch.keys = keys[cur];
       batch.vals = sorted;
     }
-    const int64_t both = all_n + batch_n;
-    if (both >= 0xffffffffLL) return fail(h, SPGEMM_UNSUPPORTED, "the all array of the outer product would exceed 2^32 - 1 components");
-    const int64_t mtiles = ceil_div(both, kMergeTile);
-    int64_t* split = bufs.get<int64_t>((size_t)mtiles + 1);
-    unsigned* msums = bufs.get<unsigned>((size_t)mtiles + 1);
-    if (!split || !msums) return fail(h, SPGEMM_ALLOC_FAILED, "allocation for the merge stage failed");
-    hipLaunchKernelGGL(k_merge_split, dim3((unsigned)ceil_div(mtiles + 1, 256)), dim3(256), 0, s, all_n, all_k, batch_n, batch.keys, mtiles, split);
-    hipLaunchKernelGGL(k_merge_count, dim3((unsigned)mtiles), dim3(256), 0, s, all_n, all_k, batch_n, batch.keys, split, msums);
-    unsigned merged = 0;
-    if ((rc = total_of(mtiles, msums, &merged))) return rc;
-    OuterOut<T> next{};
-    if ((rc = room(merged, last, &next))) return rc;
-    hipLaunchKernelGGL(k_merge_put<T>, dim3((unsigned)mtiles), dim3(256), 0, s, all_n, all_k, all_v, batch_n, batch.keys, batch.vals, split, msums, next);
-    HIP_TRY(h, hipGetLastError());
-    bufs.release(all_k); bufs.release(all_v); bufs.release(split); bufs.release(msums);
+    if (!rc) rc = merge(compact ? uniq : cnt);
     if (compact) { bufs.release(batch.keys); bufs.release(batch.vals); }
-    all_k = next.keys; all_v = next.vals; all_n = merged;
+    if (rc == SPGEMM_ALLOC_FAILED && kept) {
+      // (the first batch, added up, may take less)
+      keep_first = false;
+      from_start();
+      continue;
+    }
+    if (rc) return rc;
+    HIP_TRY(h, hipGetLastError());
+    kept = false;
   }
   // compress: columns and values are there, the row pointer comes from the coordinates
   hipLaunchKernelGGL(k_key_ptr<uint32_t>, dim3((unsigned)ceil_div(m + 1, kPtrRows)), dim3(256), 0, s, all_n, m, 0, all_row, rp);

@@ -83,3 +83,34 @@ def test_nothing_is_on_its_way_when_a_request_is_refused(batches):
             side.synchronize()
         assert_matches_oracle(X, Y, [t.cpu().numpy() for t in (got.rowptr, got.colidx, got.values)], want)
     assert refused >= 8
+
+
+def test_a_first_batch_that_is_kept_does_not_take_the_room_of_the_rest():
+    """A coordinate comes hundreds of times in every batch.  Every limit at which some request just finds room or does not, down to what the call
+    takes when the first batch is added up by itself."""
+    from paper_2404_04541_amd import binding as sg
+    A, B = W.uniform_rows(40, 2000, 1000, 65, 1, np.float32), W.uniform_rows(2000, 30, 10, 65, 3, np.float32)
+    batch = 100_000
+    o = Outer(A, B, batch)
+    assert o.products == 4 * batch
+    seen, of_that_size = [], [0]
+    m = Memory(sg, lambda n, used: seen.append(used + n))
+    assert o.call(m)[0] == 0
+    m.close()
+
+    def no_other_buffers(n, _used):   # (keys and values of the accumulation array, twice, then the others)
+        of_that_size[0] += n == 8 * batch
+        return n == 8 * batch and of_that_size[0] > 4
+    m = Memory(sg, no_other_buffers)
+    assert o.call(m)[0] == 0 and of_that_size[0] > 4
+    least = m.most
+    m.close()
+    limits = {least} | {v - short for v in seen for short in (0, 1) if v - short >= least}
+    assert len(limits) > 4
+    for limit in sorted(limits):
+        m = Memory(sg, lambda n, used: used + n > limit)
+        assert o.call(m)[0] == 0, limit
+        m.close()
+    m = Memory(sg, lambda n, used: used + n > 32 * batch)
+    assert o.call(m)[0] == -5   # (not even the accumulation array)
+    m.close()
