@@ -52,7 +52,9 @@ class PinnedBlocks {
       if (n_ > 0) return free_[--n_];
     }
     void* p = nullptr;
-    return hipHostMalloc(&p, sizeof(Control), hipHostMallocPortable) == hipSuccess ? static_cast<Control*>(p) : nullptr;
+    if (hipHostMalloc(&p, sizeof(Control), hipHostMallocPortable) == hipSuccess) return static_cast<Control*>(p);
+    (void)hipGetLastError();
+    return nullptr;
   }
   void give(Control* p) {
     {
@@ -200,8 +202,9 @@ void* dev_alloc(spgemm_context* h, size_t bytes) {
   if (bytes == 0) bytes = 256;
   if (h->has_alloc) return h->alloc.alloc(h->alloc.ctx, bytes);
   void* p = nullptr;
-  if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
-  return p;
+  if (hipMalloc(&p, bytes) == hipSuccess) return p;
+  (void)hipGetLastError();   // (the thread's last error stays until it is asked for: a call that goes on without would find it behind its kernels)
+  return nullptr;
 }
 
 void dev_free(spgemm_context* h, void* p) {
@@ -558,7 +561,10 @@ void alloc_optional(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* B, co
   size_t limit = asked - (double)p->desc_bytes < (double)want ? (size_t)(asked - (double)p->desc_bytes) : want;
   if ((double)(want + p->desc_bytes) + list_want > (double)kAskFreeAbove) {
     size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
     double entries = 0;   // of C, at most
     for (int b = 0; b < kNumBins; ++b) {
       const double ip = (double)host.bin_ip[0][b], full = (double)host.hist[0][b] * (double)B->cols;

@@ -114,3 +114,36 @@ def test_a_first_batch_that_is_kept_does_not_take_the_room_of_the_rest():
     m = Memory(sg, lambda n, used: used + n > 32 * batch)
     assert o.call(m)[0] == -5   # (not even the accumulation array)
     m.close()
+
+
+def test_a_refusal_by_the_device_leaves_no_error_behind():
+    """Without an allocator of the caller's: the card has room for the accumulation array and the result, not for a second accumulation array,
+    which the call then does without."""
+    import torch
+    from paper_2404_04541_amd import binding as sg
+    A, B = W.uniform_rows(4096, 2048, 64, 83, 1, np.float32), W.uniform_rows(2048, 500, 128, 83, 3, np.float32)
+    h = sg.Handle()
+    a, b = sg.dcsc_from_csr(h, sg.to_device(A)), sg.dcsr_from_csr(h, sg.to_device(B))
+    want = sg.spgemm(h, sg.to_device(A), sg.to_device(B))
+    batch = 1 << 24
+    bare = sg.Handle(torch_allocator=False)
+
+    def call():
+        sa, sb, sc = a.struct(), b.struct(), sg.CsrStruct()
+        rc = bare.lib.spgemm_outer(bare.ptr, C.byref(sa), C.byref(sb), batch, C.byref(sc))
+        text = bare.lib.spgemm_last_error(bare.ptr)
+        nnz = int(sc.nnz)
+        for ptr in (sc.rowptr, sc.colidx, sc.values):
+            bare.lib.spgemm_free_device(bare.ptr, ptr)
+        return rc, nnz, text
+    assert call()[:2] == (0, want.nnz)   # (and what the kernels need of the device themselves is there)
+    torch.cuda.empty_cache()
+    room = 32 * batch + 8 * batch + (100 << 20)   # (keys of the second array find room, values do not)
+    free = torch.cuda.mem_get_info()[0]
+    ballast = torch.empty(free - room, dtype=torch.uint8, device="cuda")
+    try:
+        rc, nnz, text = call()
+    finally:
+        del ballast
+        torch.cuda.empty_cache()
+    assert (rc, nnz) == (0, want.nnz), text
