@@ -42,11 +42,15 @@ constexpr int kRecColBits = 23;                                // a column and i
 static_assert(kNumHashSmall <= 256, "a rank fits a byte");
 static_assert(kRecWords % 4 == 0 && kRecRankWords % 4 == 0, "records and their column lists start on 16 bytes");
 constexpr int kRecordGroups = 4;                               // workgroups of these kernels on a compute unit
-// Slots of the set: 2.7 times the most products.  With 1024 the slowest lane of an insertion walked over twenty taken ones and more, and a row of 768
-// products took 35 us: whole calls, us with 1024 | 2048: ragged 5003 rows 240 | 219, R-MAT squared scale 12 214 | 206, 14 455 | 439, 30 000 ragged rows
-// of 20 x 20 573 | 532, 60 000 of 16 x 16 550 | 547.
-constexpr int kSymLogSlots = 11;
-constexpr int kSymSlots = 1 << kSymLogSlots;
+// Slots of the set: 2048, 2.7 times the most products (with 1024 the slowest lane of an insertion walked over twenty taken ones and more, and a row of
+// 768 products took 35 us: whole calls, us with 1024 | 2048: ragged 5003 rows 236 | 216, R-MAT squared scale 12 210 | 201, 14 444 | 432).  That is
+// 38 KB a workgroup, four of which fit a compute unit.  Where rows differ and the class's have kFewProducts or fewer on average, 1024: a row with more
+// is still right, five workgroups fit (22 KB), and half as many slots are cleared, which is what short rows pay for.  300 000 rows, this kernel, us
+// with 1024 | 2048: 144 products a row 354 | 390, 196 265 | 272, 240 288 | 282, 256 293 | 285, 324 554 | 476, 400 648 | 512, 576 1412 | 831, 756
+// 2362 | 986; 2 M rows of 130 products 1831 | 2130.  Where the classes of shorter rows share a launch (few rows: the slowest one decides) it is always 2048.
+constexpr int kSymLogSlots = 11, kFewLogSlots = 10;
+constexpr int kFewGroups = 5;
+constexpr int64_t kFewProducts = 208;
 // sums of a row in LDS (a rank is a byte), and a place for every lane's missing products
 constexpr int kRecSums = 256 + kWave;
 static_assert(4 * kRecSums * 8 <= 65536, "a sum's place in the workgroup's LDS fits 16 bits");
@@ -93,8 +97,9 @@ __device__ __forceinline__ QuadMap quad_map(int64_t bs, int len, int nent, QuadE
 }
 
 // Home slot of a column (24-bit multiplication: a 32-bit one takes four issue slots).
+template <int LOG_SLOTS>
 __device__ __forceinline__ unsigned set_home(int col) {
-  return (__umul24((unsigned)col ^ ((unsigned)col >> 20), 0x9E3779u) >> (32 - kSymLogSlots)) & (kSymSlots - 1);
+  return (__umul24((unsigned)col ^ ((unsigned)col >> 20), 0x9E3779u) >> (32 - LOG_SLOTS)) & ((1 << LOG_SLOTS) - 1);
 }
 
 struct NumRow {   // record (-1: no row, -2: none), how far its columns are from the row's, entries of A, entries of C
@@ -109,18 +114,21 @@ struct SymRow {   // a row, its entries of A (none: row < 0)
 };
 constexpr int kAlikeTries = 8;   // rows that only look alike a wave compares in vain before it stops
 
+template <int LOG_SLOTS>
 struct SymWaveLds {
-  __align__(16) int table[4][kSymSlots];
+  __align__(16) int table[4][1 << LOG_SLOTS];
   QuadEntry ent[4][kQuadEntries];
   unsigned short slot[4][kNumHashSmall];   // slot of the column with a number
   unsigned kept, done;                     // rows with a record, waves that have no more rows
 };
+static_assert(kRecordGroups * sizeof(SymWaveLds<kSymLogSlots>) <= 160 * 1024 && kFewGroups * sizeof(SymWaveLds<kFewLogSlots>) <= 160 * 1024, "workgroups on a compute unit");
 
-template <bool ALIKE>
-__device__ __forceinline__ void sym_wave_rows(SymWaveLds* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, Control* __restrict__ ctl,
+template <bool ALIKE, int LOG_SLOTS>
+__device__ __forceinline__ void sym_wave_rows(SymWaveLds<LOG_SLOTS>* lds, unsigned wg, unsigned wgs, const int* __restrict__ perm, Control* __restrict__ ctl,
     int bin, const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const int64_t* __restrict__ b_rp,
     const int32_t* __restrict__ b_col, int64_t b_nnz, int* __restrict__ cnt, unsigned* __restrict__ records, unsigned record_rows,
     int* __restrict__ record_of, int* __restrict__ shift_of) {
+  constexpr int kSlots = 1 << LOG_SLOTS;
   if (threadIdx.x == 0) { lds->kept = 0; lds->done = 0; }
   __syncthreads();
   const unsigned first = ctl->offset[0][bin];
@@ -275,7 +283,7 @@ __device__ __forceinline__ void sym_wave_rows(SymWaveLds* lds, unsigned wg, unsi
       if (base == 0) {
         int4* t4 = reinterpret_cast<int4*>(table);
 #pragma unroll
-        for (int t = 0; t < kSymSlots / 4 / kWave; ++t) t4[t * kWave + lane] = make_int4(kEmptyKey, kEmptyKey, kEmptyKey, kEmptyKey);
+        for (int t = 0; t < kSlots / 4 / kWave; ++t) t4[t * kWave + lane] = make_int4(kEmptyKey, kEmptyKey, kEmptyKey, kEmptyKey);
         wave_sync_lds();
         if (ALIKE && d <= kQuadEntries && (m_hits == 0 || ++m_missed > 1)) {   // (one row at an edge leaves the model what it is)
           m_d = d; m_len = len; m_nq = nq; m_hits = 0; m_missed = 0;
@@ -294,14 +302,14 @@ __device__ __forceinline__ void sym_wave_rows(SymWaveLds* lds, unsigned wg, unsi
         unsigned slot[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          slot[u] = set_home(col[r][u]);
+          slot[u] = set_home<LOG_SLOTS>(col[r][u]);
           bool is_new = false;
           if (u < quad_count(quad[r])) {
             while (true) {
               const int old = atomicCAS(&table[slot[u]], kEmptyKey, col[r][u]);
               if (old == kEmptyKey) { is_new = true; break; }
               if (old == col[r][u]) break;
-              slot[u] = (slot[u] + 1) & (kSymSlots - 1);
+              slot[u] = (slot[u] + 1) & (kSlots - 1);
             }
           }
           const unsigned long long fresh = __ballot(is_new);
@@ -377,16 +385,16 @@ __device__ __forceinline__ void sym_wave_rows(SymWaveLds* lds, unsigned wg, unsi
   finish();
 }
 
-// ALIKE: rows are compared with a model.
-template <bool ALIKE>
-__global__ __launch_bounds__(256, ALIKE ? kRecordGroups : 5) void k_sym_wave(const int* __restrict__ perm, Control* __restrict__ ctl, int bin,
+// ALIKE: rows are compared with a model.  (Bounds: as many workgroups as LDS holds.)
+template <bool ALIKE, int LOG_SLOTS>
+__global__ __launch_bounds__(256, LOG_SLOTS == kSymLogSlots ? kRecordGroups : kFewGroups) void k_sym_wave(const int* __restrict__ perm, Control* __restrict__ ctl, int bin,
                                                   const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col,
                                                   const int64_t* __restrict__ b_rp, const int32_t* __restrict__ b_col, int64_t b_nnz,
                                                   int* __restrict__ cnt, unsigned* __restrict__ records, unsigned record_rows,
                                                   int* __restrict__ record_of, int* __restrict__ shift_of) {
-  __shared__ SymWaveLds lds;
+  __shared__ SymWaveLds<LOG_SLOTS> lds;
   if (ctl->error) return;
-  sym_wave_rows<ALIKE>(&lds, blockIdx.x, gridDim.x, perm, ctl, bin, a_rp, a_col, b_rp, b_col, b_nnz, cnt, records, record_rows, record_of, shift_of);
+  sym_wave_rows<ALIKE, LOG_SLOTS>(&lds, blockIdx.x, gridDim.x, perm, ctl, bin, a_rp, a_col, b_rp, b_col, b_nnz, cnt, records, record_rows, record_of, shift_of);
 }
 
 // Numeric pass over the recorded rows of a bin, a wave per row; rows without a record are left to the hash workspace.

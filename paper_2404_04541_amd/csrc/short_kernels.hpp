@@ -33,7 +33,7 @@ struct SymShort {
 
 constexpr size_t sym_short_lds() {
   size_t n = hash_lds_bytes<256, 12, false>();
-  if (n < sizeof(SymWaveLds)) n = sizeof(SymWaveLds);
+  if (n < sizeof(SymWaveLds<kSymLogSlots>)) n = sizeof(SymWaveLds<kSymLogSlots>);
   if (n < sizeof(EscSymLds<64, 128>)) n = sizeof(EscSymLds<64, 128>);
   if (n < sizeof(EscSymLds<16, 32>)) n = sizeof(EscSymLds<16, 32>);
   return n;
@@ -51,7 +51,7 @@ __global__ __launch_bounds__(256, kShortGroups) void k_sym_short(Control* __rest
   }
   wg -= s.wgs[0];
   if (wg < s.wgs[1]) {
-    sym_wave_rows<ALIKE>(reinterpret_cast<SymWaveLds*>(smem), wg, s.wgs[1], s.perm, ctl, 2, s.a_rp, s.a_col, s.b_rp, s.b_col, s.b_nnz, s.cnt,
+    sym_wave_rows<ALIKE, kSymLogSlots>(reinterpret_cast<SymWaveLds<kSymLogSlots>*>(smem), wg, s.wgs[1], s.perm, ctl, 2, s.a_rp, s.a_col, s.b_rp, s.b_col, s.b_nnz, s.cnt,
         s.records, s.record_rows, s.record_of, s.shift_of);
     return;
   }

@@ -407,9 +407,10 @@ int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const sp
 }
 
 // Workgroups of the kernels of recorded rows.  Where rows are alike, as many as are resident together, the same number in both phases, so that a
-// wave of the numeric one meets the rows that a wave of the symbolic one has given the same record; otherwise twice as many, which evens out rows
-// that differ (symbolic us with 32 | 10 | 5 on a compute unit: 30 000 rows of 256 products 99 | 53 | 46, 300 000 336 | 331 | 358, 32 000 ragged
-// ones 193 | 197 | 208).
+// wave of the numeric one meets the rows that a wave of the symbolic one has given the same record; otherwise ten a compute unit, two or two and a half
+// times as many as are resident in the symbolic phase, which evens out rows that differ (300 000 rows, symbolic us with 8 | 10 | 16 on a compute
+// unit: 144 products 394 | 354 | 370, 256 294 | 282 | 287, 400 540 | 511 | 521, 756 1047 | 988 | 1006; 60 000 of 256 67 | 65 | 68; 100 000 ragged ones 247 |
+// 254 | 263).
 unsigned record_grid(spgemm_context* h, const spgemm_plan_s* p, int64_t rows) {
   const unsigned most = (unsigned)(ceil_div((int64_t)h->num_cus * (p->alike ? kRecordGroups : 10), kDies) * kDies);
   return (unsigned)(ceil_div(grid_for(rows, 4, most), kDies) * kDies);
@@ -724,10 +725,12 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
       }
       {
         Timer t(h, SPGEMM_K_SYM_HASH);
-        if (hist[2])
-          hipLaunchKernelGGL((p->alike ? k_sym_wave<true> : k_sym_wave<false>), dim3(record_grid(h, p, hist[2])), dim3(256), 0, s, p->perm_sym,
-                             p->ctl, 2, A->rowptr, A->colidx, B->rowptr, B->colidx, B->nnz, p->cnt, p->records, p->record_rows, p->record_of,
-                             p->shift_of);
+        if (hist[2]) {
+          const bool few = host.bin_ip[0][2] <= (unsigned long long)kFewProducts * hist[2];
+          hipLaunchKernelGGL((p->alike ? k_sym_wave<true, kSymLogSlots> : few ? k_sym_wave<false, kFewLogSlots> : k_sym_wave<false, kSymLogSlots>),
+                             dim3(record_grid(h, p, hist[2])), dim3(256), 0, s, p->perm_sym, p->ctl, 2, A->rowptr, A->colidx,
+                             B->rowptr, B->colidx, B->nnz, p->cnt, p->records, p->record_rows, p->record_of, p->shift_of);
+        }
         if (hist[3])
           hipLaunchKernelGGL((k_hash<256, 12, T, false>), dim3(grid_for(hist[3], 1, (int64_t)h->num_cus * 8)), dim3(256),
                              lds_hash_large, s, p->perm_sym, p->ctl, 0, 3, p->ip, A->rowptr, A->colidx,

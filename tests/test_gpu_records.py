@@ -67,6 +67,21 @@ def test_new_values_on_a_kept_plan(force):
     plan.destroy()
 
 
+@pytest.mark.parametrize("entries", [(16,), (16,) * 9 + (17,), (10,) * 9 + (59,), (10,) * 4 + (59,)])
+@pytest.mark.parametrize("timing", [0, 1])
+def test_slots_by_the_average_row(entries, timing):
+    """Rows of 13 products an entry: 208 on average and a little more, and few and many with rows of 767 among them.  With the timing option the class
+    has a launch of its own, whose set has slots by the average."""
+    from paper_2404_04541_amd import binding as sg
+    rng = np.random.default_rng(41)
+    B = csr([np.sort(rng.choice(1500, 13, replace=False)) for _ in range(200)], 1500, np.float64, 42)
+    rows = [rng.choice(200, entries[i % len(entries)], replace=False) for i in range(1000)]
+    A = csr(rows, 200, np.float64, 43)
+    got = gpu_product(A, B, options={sg.OPT_TIMING: timing})
+    assert_matches_oracle(A, B, got, what=f"{entries}")
+    assert got[3]["sym_bin_rows"][2] == 1000
+
+
 def short_operands(b_rows, cols, dtype, sort_b, seed=31):
     """Rows of 0 to 128 products: one long B row, many short ones, more entries than lanes (most of them with empty B rows),
     columns hit several times; with more than 2^19 rows of B the row count describes the entries."""
