@@ -424,17 +424,24 @@ __device__ __forceinline__ void plan_tail(TilePlan* tp, int nb, int block0, int 
   }
 }
 
-// The numeric kernels' runs lie in the order of the symbolic kernel's rows, the heaviest first, and workgroups draw them by number.  Where there are few
-// for a workgroup they are taken in that order, so that no workgroup is left with a long row at the end.  Where there are many, every draw of four is from the
-// front and the others are from the back: heavy rows use the memory, light ones wait for it, and both kinds do better beside the other.  Numeric kernel of
-// R-MAT squared, us in order | from both ends: scale 14 146 | 161, scale 16 746 | 768 (53 runs a workgroup), scale 17 2812 | 2774 (97), 18 8886 |
-// 7827, 19 25364 | 23041 (before: in the order in which the symbolic workgroups drew records, 165, 784, 2840, 8096, 23636; k_num_wide, scale 20,
-// 70.0 ms before and 72.0); 60 000 rows of 3600 products 1443 | 1409.  One of two and one of eight do less for the larger ones (19: 23413, 23494).
+// The numeric kernels' runs lie in the order of the symbolic kernel's rows, the first of every row, the heaviest first, and behind them the further runs of
+// rows that have several; workgroups draw them by number.  Where there are few for a workgroup they are taken in that order, so that no workgroup is left with
+// a long row at the end.  Where there are many, every draw of four is from the front and the others are from the back: heavy rows use the memory, light ones
+// wait for it, and both kinds do better beside the other.  k_num_tiles of R-MAT squared, us in order | from both ends: scale 14 146 | 161, scale 16 746 | 768
+// (53 runs a workgroup), scale 17 2812 | 2774 (97), 18 8886 | 7827, 19 25364 | 23041; 60 000 rows of 3600 products 1443 | 1409.  One of two and one
+// of eight do less for the larger ones (19: 23413, 23494).
+// k_num_wide takes the further runs before all others (`rows` first runs; they belong to the heaviest rows, and in k_num_tiles it makes no difference).
+// k_num_wide, ms in order | from both ends | so: R-MAT squared scale 20 (fp32) 74.4 | 71.9 | 71.5, fp64 90.9 | 85.4 | 85.8, 8 edges 29.3 | 27.1 | 27.0,
+// scale 21 with 6 edges 78.5 | 78.9 | 78.5; 20 000 unordered rows of 120 x 120 products 2.57 | 2.55 | 2.56.  (In the order in which the symbolic
+// workgroups drew records, 256 at a time: 70.0, 86.4, 27.0, 79.2, 2.57.  That order over the rows as they lie now 71.0, 86.2, 27.3, 79.7, 2.59; halves from
+// either end 71.3, 86.1, 26.9, 83.6, 2.57; 4, 16 or 64 stretches side by side 74 and more, -, 29.)
 constexpr unsigned kManyRuns = 64;
-__device__ __forceinline__ unsigned run_of(unsigned draw, unsigned nruns) {
+__device__ __forceinline__ unsigned run_of(unsigned draw, unsigned nruns, unsigned rows) {
   if (nruns < kManyRuns * gridDim.x || draw >= nruns) return draw;
-  const unsigned q = draw / 4, r = draw % 4;
-  return r == 0 ? q : nruns - 3 * q - r;
+  const unsigned more = nruns - rows;
+  if (draw < more) return rows + draw;
+  const unsigned q = (draw - more) / 4, r = (draw - more) % 4;
+  return r == 0 ? q : rows - 3 * q - r;
 }
 
 // Takes `amount` from a shared cursor if that stays within `cap` (compare and advance: the cursor never

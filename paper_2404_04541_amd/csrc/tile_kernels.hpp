@@ -446,7 +446,7 @@ __global__ __launch_bounds__(kTileThreads, 8) void k_num_tiles(Control* ctl, con
   if (tid < kRunWords) {
     if (tid == 0) drawn = atomicAdd(&ctl->work[1], 1u);
     have_coming = blockIdx.x < nruns;   // (the first draw is the workgroup's own)
-    if (have_coming) coming = run_words[(size_t)run_of(blockIdx.x, nruns) * kRunWords + tid];
+    if (have_coming) coming = run_words[(size_t)run_of(blockIdx.x, nruns, nruns) * kRunWords + tid];
   }
   while (true) {
     __syncthreads();
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(kTileThreads, 8) void k_num_tiles(Control* ctl, con
       const unsigned next = gridDim.x + (unsigned)uni((int)drawn);
       have_coming = next < nruns;
       if (have_coming) {
-        coming = run_words[(size_t)run_of(next, nruns) * kRunWords + tid];
+        coming = run_words[(size_t)run_of(next, nruns, nruns) * kRunWords + tid];
         if (tid == 0) drawn = atomicAdd(&ctl->work[1], 1u);
       }
     }

@@ -486,7 +486,7 @@ __global__ __launch_bounds__(kWideThreads) void k_num_wide(Control* ctl, const u
   const bool sorted = ctl->b_sorted != 0;
   const bool class3 = tiles3 != 0 && !other_order(ctl, looked);   // (as in k_num_tiles)
   const int tid = threadIdx.x;
-  const unsigned nruns = ctl->run_cursor;
+  const unsigned nruns = ctl->run_cursor, nrows = ctl->offset[0][7] - ctl->offset[0][4];   // (and as many first runs)
   // Thread 0 draws runs ahead of their use: the counter value for the run after next and the record
   // of the next run are on their way while the current run is in the works.
   unsigned drawn = 0;
@@ -496,7 +496,7 @@ __global__ __launch_bounds__(kWideThreads) void k_num_wide(Control* ctl, const u
   if (tid == 0) {
     drawn = atomicAdd(&ctl->work[1], 1u);
     have_coming = blockIdx.x < nruns;   // (the first draw is the workgroup's own)
-    if (have_coming) coming = runs[run_of(blockIdx.x, nruns)];
+    if (have_coming) coming = runs[run_of(blockIdx.x, nruns, nrows)];
   }
   while (true) {
     __syncthreads();
@@ -506,7 +506,7 @@ __global__ __launch_bounds__(kWideThreads) void k_num_wide(Control* ctl, const u
       const unsigned next = gridDim.x + drawn;
       have_coming = next < nruns;
       if (have_coming) {
-        coming = runs[run_of(next, nruns)];
+        coming = runs[run_of(next, nruns, nrows)];
         drawn = atomicAdd(&ctl->work[1], 1u);
       }
     }

@@ -97,3 +97,33 @@ def test_tiles_of_changing_size():
     assert np.array_equal(got[1], np.tile(cols, rows))
     want = A.values[:, None] * B.values.reshape(8, -1)[A.colidx]
     assert np.allclose(got[2].reshape(rows, -1), want, rtol=1e-15, atol=0)   # (one product an entry)
+
+
+@pytest.mark.parametrize("rows,cols", [(16_383, 2500), (16_384, 2500), (8191, 1_200_000), (8195, 1_200_000)])
+def test_wide_runs_from_both_ends(rows, cols):
+    """64 runs for each of 256 workgroups: B's rows are unordered, which leaves the wide kernel; beyond 2^20 columns a row has a run for each span."""
+    rng = np.random.default_rng(15)
+    B = rows_of(np.full(300, 200), cols, rng, np.float32, ordered=False)
+    d = np.where(np.arange(rows) % 100 == 7, 90, 9)
+    c = np.concatenate([rng.choice(300, n, replace=False) for n in d]).astype(np.int32)
+    A = W.CSR(rows, 300, np.concatenate([[0], np.cumsum(d)]).astype(np.int64), c, rng.uniform(-1, 1, c.size).astype(np.float32))
+    got = gpu_product(A, B)
+    assert_matches_oracle(A, B, got, what=f"{rows} rows of {cols} columns")
+    assert got[3]["sym_bin_rows"][4] == rows and got[3]["dense_runs"] == rows * (2 if cols > 1 << 20 else 1)
+
+
+def test_light_rows_have_a_place_in_a_short_list():
+    """Many rows of a wide matrix, every fourth of which takes 73 KB of flag words; a list with room for two thirds of those alone."""
+    from paper_2404_04541_amd import binding as sg
+    rng = np.random.default_rng(17)
+    rows, cols = 16_400, 600_000
+    B = rows_of(np.full(400, 100), cols, rng, np.float32)
+    d = np.where(np.arange(rows) % 4 == 1, 130, 30)
+    c = np.concatenate([np.sort(rng.choice(400, n, replace=False)) for n in d]).astype(np.int32)
+    A = W.CSR(rows, 400, np.concatenate([[0], np.cumsum(d)]).astype(np.int64), c, rng.uniform(-1, 1, c.size).astype(np.float32))
+    want = gpu_product(A, B)
+    assert want[3]["dense_search_tiles"] == int((d == 30).sum())
+    got = gpu_product(A, B, options={sg.OPT_COLUMN_LIST: 200_000_000})
+    assert got[3]["dense_search_tiles"] > rows // 8
+    assert all(np.array_equal(got[i], want[i]) for i in (0, 1))
+    assert np.allclose(got[2], want[2], rtol=1e-5, atol=1e-5)
