@@ -145,7 +145,11 @@ enum {
    * not exceed this value is accumulated in one "searched" tile, or two, where that saves more than half of
    * its tiles: a product finds its sum by bisection of the row's column list, whatever the width of the row.
    * 0: never.  Default 4. */
-  SPGEMM_OPT_SEARCH_RATIO = 6
+  SPGEMM_OPT_SEARCH_RATIO = 6,
+  /* Outer product: the all array and a batch that is merged into it have fewer components together than
+   * this (SPGEMM_UNSUPPORTED otherwise).  A batch that does not fit so is first added up by itself.
+   * 2 to 2^32 - 1, the default and the most that the kernels count; less bounds the memory of a result. */
+  SPGEMM_OPT_MERGE_LIMIT = 7
 };
 
 /* Create a handle bound to a HIP stream (hipStream_t passed as void*, null = default
@@ -307,7 +311,7 @@ int spgemm_dcs_free(spgemm_handle h, spgemm_dcs* M);
  * acc_capacity: components the accumulation array holds before it is sorted and merged (0: 2^24).
  * C's buffers come from the handle's allocator (release with its free or spgemm_free_device).
  * Synchronises (once per batch of acc_capacity products).  Sums are accumulated in double.
- * SPGEMM_UNSUPPORTED: the result would have 2^32 - 1 or more entries. */
+ * SPGEMM_UNSUPPORTED: the result would have 2^32 - 1 or more entries, or SPGEMM_OPT_MERGE_LIMIT is reached. */
 int spgemm_outer(spgemm_handle h, const spgemm_dcs* A, const spgemm_dcs* B, int64_t acc_capacity, spgemm_csr* C);
 
 /* Library version: major*10000 + minor*100 + patch. */

@@ -106,6 +106,7 @@ struct spgemm_context {
   int direct_min = kDirectMinDefault;
   int64_t col_list = 1;   // 0 off, 1 automatic size, larger: byte limit
   int block_table = 1;    // 0: never build the block-offset table of B (pieces are bisected)
+  int64_t merge_limit = 0xffffffffLL;   // components of the outer product's all array and a batch together: fewer
   int search_ratio = 4;   // searched tiles for rows with at most this many products per entry (0: never)
   int row_block = 0;      // 1: A is a block of rows of a larger matrix (row pointer values are that matrix's positions)
   double whole_ip = 0;    // ... and the products of all its rows
@@ -1073,6 +1074,10 @@ int spgemm_set_option(spgemm_handle h, int option, int64_t value) {
       if (value < 0 || value > 1000000) return fail(h, SPGEMM_INVALID_ARG, "search-ratio option takes 0..1000000");
       h->search_ratio = (int)value;
       return SPGEMM_OK;
+    case SPGEMM_OPT_MERGE_LIMIT:
+      if (value < 2 || value > 0xffffffffLL) return fail(h, SPGEMM_INVALID_ARG, "merge-limit option takes 2..2^32-1");
+      h->merge_limit = value;
+      return SPGEMM_OK;
     case SPGEMM_OPT_BLOCK_TABLE:
       if (value != 0 && value != 1) return fail(h, SPGEMM_INVALID_ARG, "block-table option takes 0 or 1");
       h->block_table = (int)value;
@@ -1817,7 +1822,7 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
     return SPGEMM_OK;
   };
   // kept: the all array is the first batch as its sort has left it; all_raw: and nobody has waited for that
-  bool plain_sorts = false, keep_first = cap <= kOuterKeepCap, kept = false, all_raw = false;
+  bool plain_sorts = false, keep_first = cap <= kOuterKeepCap && 2 * cap < h->merge_limit, kept = false, all_raw = false;
   auto was_too_long = [&] { return *static_cast<volatile int*>(too_long) != 0; };
   *too_long = 0;
   for (long long t0 = 0; t0 < total; t0 += cap) {
@@ -1876,7 +1881,8 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
     // The batch into the all array.
     auto merge = [&](int64_t batch_n) -> int {
       const int64_t both = all_n + batch_n;
-      if (both >= 0xffffffffLL) return fail(h, SPGEMM_UNSUPPORTED, "the all array of the outer product would exceed 2^32 - 1 components");
+      if (both >= h->merge_limit)
+        return fail(h, SPGEMM_UNSUPPORTED, "the all array of the outer product and a batch would reach " + std::to_string(h->merge_limit) + " components");
       const int64_t tiles = ceil_div(both, kMergeTile);
       int64_t* split = bufs.get<int64_t>((size_t)tiles + 1);
       unsigned* sums = bufs.get<unsigned>((size_t)tiles + 1);
@@ -1939,7 +1945,7 @@ int outer_run(spgemm_context* h, const spgemm_dcs* A, const spgemm_dcs* B, int64
       }
       all_raw = false;
     }
-    const bool compact = all_n + cnt >= 0xffffffffLL;   // (too many, but perhaps not so many different ones)
+    const bool compact = all_n + cnt >= h->merge_limit;   // (too many, but perhaps not so many different ones)
     if (compact) {
       rc = add_up(false);
     } else {

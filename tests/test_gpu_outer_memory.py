@@ -147,3 +147,26 @@ def test_a_refusal_by_the_device_leaves_no_error_behind():
         del ballast
         torch.cuda.empty_cache()
     assert (rc, nnz) == (0, want.nnz), text
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_a_batch_that_does_not_fit_the_limit_is_added_up_first(dtype):
+    """Six batches with a coordinate some four times in each: the all array (at most 3000 components) and a batch of 12 000 reach any limit up to 15 000,
+    but not the all array and the batch's different coordinates."""
+    from paper_2404_04541_amd import binding as sg
+    A, B = W.uniform_rows(40, 300, 180, 91, 1, dtype), W.uniform_rows(300, 75, 10, 91, 3, dtype)
+    ref = oracle.spgemm(A, B)
+    assert int(ref.ip.sum()) == 72_000 and ref.colidx.size == 3000
+    h = sg.Handle()
+    a, b = sg.dcsc_from_csr(h, sg.to_device(A)), sg.dcsr_from_csr(h, sg.to_device(B))
+    for limit in (6001, 12_000, 14_999, 15_000, 15_001, 24_000, 24_001, (1 << 32) - 1):
+        h.set_option(sg.OPT_MERGE_LIMIT, limit)
+        c = sg.spgemm_outer(h, a, b, 12_000)
+        assert np.array_equal(c.rowptr.cpu().numpy(), ref.rowptr) and np.array_equal(c.colidx.cpu().numpy(), ref.colidx), limit
+        err = np.abs(c.values.cpu().numpy().astype(np.float64) - ref.values.astype(dtype).astype(np.float64))
+        assert np.all(err <= RTOL[np.dtype(dtype)] * ref.absum), limit
+    for limit in (2, 3000):
+        h.set_option(sg.OPT_MERGE_LIMIT, limit)
+        with pytest.raises(sg.SpgemmError) as e:
+            sg.spgemm_outer(h, a, b, 12_000)
+        assert e.value.status == -4
