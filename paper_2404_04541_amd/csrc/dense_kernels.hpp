@@ -111,25 +111,14 @@ struct __align__(16) RowScratch {   // (the tile planner's arrays, written 16 by
   SPG_CLK(ClkLds clk;)
 };
 
-// Exclusive scans of two ints over the workgroup, with totals.  Contains barriers.
-// The 16 wave totals are scanned by every wave itself: lane w reads the total of wave w, a DPP row
-// scan adds them up, and the wave takes its own prefix and the grand total with readlane.
+// block_excl_scan of two ints, by name.
 template <int WAVES>
 __device__ __forceinline__ void block_excl_scan2(int a, int b, int& ea, int& eb, int& ta, int& tb, int* red) {
-  static_assert(WAVES == 4 || WAVES == 8 || WAVES == 16, "one DPP row of wave totals, or the first lanes of one");
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ia = wave_incl_scan(a), ib = wave_incl_scan(b);
-  __syncthreads();
-  if (lane_id() == kWave - 1) { red[wave] = ia; red[WAVES + wave] = ib; }
-  __syncthreads();
-  const int l = lane_id() & (WAVES - 1);   // (the lanes behind WAVES repeat the totals: only the first ones are looked at)
-  const int sa = group_incl_scan<16>(red[l]), sb = group_incl_scan<16>(red[WAVES + l]);
-  ta = __builtin_amdgcn_readlane(sa, WAVES - 1);
-  tb = __builtin_amdgcn_readlane(sb, WAVES - 1);
-  const int pa = wave ? __builtin_amdgcn_readlane(sa, wave - 1) : 0;
-  const int pb = wave ? __builtin_amdgcn_readlane(sb, wave - 1) : 0;
-  ea = pa + ia - a;
-  eb = pb + ib - b;
+  const int v[2] = {a, b};
+  int e[2], t[2];
+  block_excl_scan<WAVES>(v, e, t, red);
+  ea = e[0]; eb = e[1];
+  ta = t[0]; tb = t[1];
 }
 
 // Visits every element of the pieces once (k_num_wide; cpre counts quads here).  A piece is cut into quads; the quads of all pieces are dealt to the waves
@@ -142,7 +131,7 @@ __device__ __forceinline__ void block_excl_scan2(int a, int b, int& ea, int& eb,
 // (fp32), k_num_wide 27.9 -> 25.9 ms; scale 14: numeric 218 -> 190 us; deduplication sweep (fp64) 1.64 -> 1.59 ms.  With values one batch at a time is best
 // (two in flight 26.5 ms, three 29.7, four 31.8: registers; the next one prefetched 25.9, but 1.69 for the sweep).
 template <int WAVES, bool WITH_VALUES, typename T, class G>
-__device__ __forceinline__ void quad_pass(int np, int nq, const PieceList<T, long long> pl, const int32_t* __restrict__ b_col,
+__device__ __forceinline__ void quad_pass(int np, int nq, const PieceList<T> pl, const int32_t* __restrict__ b_col,
                                           const T* __restrict__ b_val, int64_t b_nnz, G g) {
   const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
   np = uni(np);
@@ -243,7 +232,7 @@ __device__ __forceinline__ void stream_columns(int64_t a0, int d, const int32_t*
     __syncthreads();
     SPG_CLK(clk_mark(&rs->clk, 2); clk_add(&rs->clk, 18, 1); clk_add(&rs->clk, 19, (unsigned long long)cut.chunks << cut.lanes);)
     if (cut.chunks > 0)
-      piece_pass<WAVES>(cut.pieces, cut.chunks, cut.lanes, PieceList<int, long long>{rs->start, rs->cpre, rs->plen, nullptr}, b_col, b_nnz, f);
+      piece_pass<WAVES>(cut.pieces, cut.chunks, cut.lanes, PieceList<int>{rs->start, rs->cpre, rs->plen, nullptr}, b_col, b_nnz, f);
     SPG_CLK(clk_mark(&rs->clk, 3);)
     __syncthreads();
     SPG_CLK(clk_mark(&rs->clk, 4);)
@@ -824,8 +813,9 @@ __global__ __launch_bounds__(WAVES * kWave, PER_SIMD) void k_sym_dense(const int
 static_assert(sizeof(RowScratch<8, 512>) % 16 == 0 && sizeof(RowScratch<16, 1024>) % 16 == 0 && alignof(TilePlan) == 16, "the planner's arrays start on 16 bytes");
 template <int WAVES, int PIECES>
 constexpr size_t sym_dense_lds(int64_t flag_words) { return (size_t)flag_words * 4 + sizeof(RowScratch<WAVES, PIECES>) + sizeof(TilePlan); }
-// Half a span of flag words (64 KB): up to that many columns two workgroups of 8 waves share a compute unit.
+// Half a span of flag words (64 KB): up to that many columns two workgroups of 16 waves share a compute unit, with 512 pieces described at a time.
 constexpr int64_t kSymNarrowCols = (int64_t)kSymFlagWords * 16;
+// A quarter: two of 16 waves with 1024 pieces or, where rows are many, four of 8 waves.
 constexpr int64_t kSymShortCols = (int64_t)kSymFlagWords * 8;
 
 }  // namespace spg

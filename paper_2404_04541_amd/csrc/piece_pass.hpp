@@ -47,11 +47,11 @@ __device__ __forceinline__ void block_excl_scan(const int (&v)[N], int (&excl)[N
   }
 }
 
-// The non-empty pieces that a pass walks, in LDS: first B entry, exclusive prefix of the chunk counts (one more than there are pieces:
-// their number), length and (numeric) a_ik of every piece.
-template <typename T, typename Start>
+// The non-empty pieces that a pass walks, in LDS: first B entry, exclusive prefix of the chunk counts (of the quad counts in quad_pass),
+// length and (numeric) a_ik of every piece.
+template <typename T>
 struct PieceList {
-  const Start* s;
+  const long long* s;
   const int* cpre;
   const int* len;
   const T* av;
@@ -61,9 +61,9 @@ struct PieceList {
 template <typename T>
 struct Quad {
   int n = 0;   // elements that are left in the piece from the quad's first on (0 or less: none; four or more: the quad is full)
-  T a{};       // a_ik of the piece
+  T a{};       // a_ik of the piece (numeric walks)
   Run<int32_t, 4> col{};
-  Run<T, 4> b{};
+  Run<T, 4> b{};   // (numeric walks)
 };
 
 // How a workgroup's pieces are cut, a piece of len elements (0: none) a thread.  Contains barriers.  red: 4 * WAVES ints.
@@ -87,7 +87,7 @@ __device__ __forceinline__ PieceCut piece_chunks(int len, int* red) {
 // Visits every element of np pieces (nch chunks of 2^lanes quads) once: g(quad, full) per lane and batch, full (a type) where all lanes' quads
 // are; columns only.
 template <int WAVES, class G>
-__device__ __forceinline__ void piece_pass(int np, int nch, int lanes, const PieceList<int, long long> pl, const int32_t* __restrict__ b_col, int64_t b_nnz,
+__device__ __forceinline__ void piece_pass(int np, int nch, int lanes, const PieceList<int> pl, const int32_t* __restrict__ b_col, int64_t b_nnz,
                                            G g) {
   const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int cpb = kWave >> lanes;   // chunks of a batch

@@ -15,8 +15,10 @@ inline bool fine_rows(int64_t m, int64_t nnz_a, int64_t b_rows, int64_t nnz_b) {
 // and costs six barriers) and no stretch of them is much heavier than what a workgroup gets anyway (two are resident on each of `cus`
 // compute units; one that holds the hub rows of a graph keeps the whole count waiting).
 // Where a stretch of 256 rows (of a thousandth of them) holds kHeavyChunk times what a workgroup gets on average, chunks are of kFineRows rows, or
-// twice as many: the one with the hub rows of a graph took as long as the whole count (R-MAT scale 17 squared 4436 | 4385 us, scale 19 34.8 | 34.6
-// ms).  fine: this is looked at, which takes 2 us, where rows are many and of some length (400 000 rows of 8 x 4 239 | 241 us if they were).
+// twice as many: the one with the hub rows of a graph took as long as the whole count.  fine: this is looked at, which takes 2 us, where rows are
+// many and of some length.  Whole calls, us without | with, R-MAT squared: scale 16 1670 | 1681 (f64, 8 edges 1004 | 996), 17 4318 | 4262, 18 11 813 | 11 730, 19
+// 34 178 | 34 034; 400 000 rows of 8 x 8 470 | 471; stencils no difference.  From 32 768 rows scale 15 gains nothing (790 | 790), from 131 072 scale 16 loses what
+// it gains; with 3 entries a row in place of 6 scale 18 of 4 edges 2689 | 2709, scale 19 of 5 8744 | 8796; a kHeavyChunk of 2 or 8 makes no difference.
 // us with chunks of 256 | 1024 rows: 4.2 M rows of 2 entries 329 | 241, of 16 entries 1368 | 1322, of 27 entries 2131 | 2200; 2 M rows of 2
 // entries 121 | 67, of 16 entries 253 | 240, of 27 entries 385 | 383; R-MAT of 2^20 vertices, 4 edges each 248 | 398, of 2^21, 7 edges
 // each 637 | 1061.

@@ -200,7 +200,7 @@ __device__ __forceinline__ void wide_run(const RunRec rr, WideScratch<T>* ns, un
         if (nseg > 1) seg_piece(sg, s, len, av);
         int np, nquads;
         tile_pieces(ns, s, len, av, np, nquads);   // (its barriers also publish cols and the cleared sums)
-        quad_pass<kWideWaves, true, T>(np, nquads, PieceList<T, long long>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
+        quad_pass<kWideWaves, true, T>(np, nquads, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
                                [&](const Quad<T>& q) {
           // last position whose column is <= c (the column is in the list); the four bisections of a quad
           // advance in lockstep so that their LDS reads overlap
@@ -242,7 +242,7 @@ __device__ __forceinline__ void wide_run(const RunRec rr, WideScratch<T>* ns, un
         int np, nquads;
         tile_pieces(ns, s, len, av, np, nquads);
         SPG_CLK(clk_mark(&ns->clk, 7);)
-        quad_pass<kWideWaves, true, T>(np, nquads, PieceList<T, long long>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
+        quad_pass<kWideWaves, true, T>(np, nquads, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
                                [&](const Quad<T>& q) {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -382,7 +382,7 @@ __device__ __forceinline__ void wide_run(const RunRec rr, WideScratch<T>* ns, un
         T av = my_av;
         if (nseg > 1) seg_piece(sg, s, len, av);
         tile_pieces(ns, s, len, av, np, nquads);
-        quad_pass<kWideWaves, false, T>(np, nquads, PieceList<T, long long>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
+        quad_pass<kWideWaves, false, T>(np, nquads, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
                                 [&](const Quad<T>& q) {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -441,7 +441,7 @@ __device__ __forceinline__ void wide_run(const RunRec rr, WideScratch<T>* ns, un
           seg_piece(sg, s, len, av);
           tile_pieces(ns, s, len, av, np, nquads);
         }
-        quad_pass<kWideWaves, true, T>(np, nquads, PieceList<T, long long>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
+        quad_pass<kWideWaves, true, T>(np, nquads, PieceList<T>{ns->c_s, ns->c_cpre, ns->c_len, ns->c_av}, b_col, b_val, b_nnz,
                                [&](const Quad<T>& q) {
           // the four flag words of a quad first, so that their reads overlap
           uint2 w[4];

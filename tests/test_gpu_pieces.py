@@ -72,14 +72,16 @@ def test_runs_from_both_ends(rows):
 @pytest.mark.parametrize("rows", [8191, 8192])
 @pytest.mark.parametrize("cols", [2500, 262_144, 262_145])
 def test_rows_for_smaller_workgroups(rows, cols):
-    """Both sides of 32 rows for each of 256 compute units, and of 2^18 columns."""
+    """Both sides of 32 rows for each of 256 compute units, and of 2^18 columns; rows of more A entries than 8 waves (512) and 16 (1024) describe at a time."""
     rng = np.random.default_rng(11)
     B = rows_of(rng.integers(100, 300, 300), cols, rng, np.float64)
-    c = np.concatenate([np.sort(rng.choice(300, 17, replace=False)) for _ in range(rows)]).astype(np.int32)
-    A = W.CSR(rows, 300, np.arange(rows + 1, dtype=np.int64) * 17, c, rng.uniform(-1, 1, c.size))
+    d = np.full(rows, 17)
+    d[:10] = (511, 512, 513, 600, 1023, 1024, 1025, 1100, 1537, 2100)
+    c = np.concatenate([np.sort(rng.choice(300, n, replace=n > 300)) for n in d]).astype(np.int32)   # (the long ones with repeats)
+    A = W.CSR(rows, 300, np.concatenate([[0], np.cumsum(d)]).astype(np.int64), c, rng.uniform(-1, 1, c.size))
     got = gpu_product(A, B)
     assert_matches_oracle(A, B, got, what=f"{rows} rows of {cols} columns")
-    assert got[3]["sym_bin_rows"][4] == rows
+    assert sum(got[3]["sym_bin_rows"][4:7]) == rows
 
 
 def test_tiles_of_changing_size():
