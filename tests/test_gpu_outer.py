@@ -142,3 +142,28 @@ def test_batches_with_hardly_a_coordinate_of_their_own(capacity):
     B = W.uniform_rows(2000, 30, 10, 65, 3, np.float32)
     _, _, C = run_outer(A, B, capacity)
     check_against_oracles(A, B, C, f"capacity {capacity}")
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_coordinates_repeated_in_either_array(dtype):
+    """Two batches: every coordinate some times in the first and some times in the second, none among them, around the steps in which equal
+    components are added up; the last coordinate's lie at the ends of both."""
+    from paper_2404_04541_amd import binding as sg
+    counts = [0, 1, 2, 3, 4, 5, 7, 8, 9, 11, 12, 13, 19, 20, 21, 600]
+    pairs = [(x, y) for x in counts for y in counts][1:]
+    first, second = np.array(pairs).T
+    assert first.sum() == second.sum()
+    K, most = 1200, 600
+    cols = [np.concatenate([np.arange(x), most + np.arange(y)]) for x, y in pairs]
+    rp = np.concatenate([[0], np.cumsum([c.size for c in cols])]).astype(np.int64)
+    rng = np.random.default_rng(19)
+    A = W.CSR(len(pairs), K, rp, np.concatenate(cols).astype(np.int32), rng.uniform(-1, 1, rp[-1]).astype(dtype))
+    B = W.CSR(K, 1, np.arange(K + 1, dtype=np.int64), np.zeros(K, np.int32), rng.uniform(-1, 1, K).astype(dtype))
+    _, _, C = run_outer(A, B, int(first.sum()))
+    check_against_oracles(A, B, C, "repeats")
+    got = C.values.cpu().numpy()
+    for i, c in enumerate(cols):   # (added up in the order of the products, in double)
+        s = np.float64(0)
+        for v in A.values[rp[i]:rp[i + 1]].astype(np.float64) * B.values[c].astype(np.float64):
+            s = s + v
+        assert got[i] == dtype(s), pairs[i]
