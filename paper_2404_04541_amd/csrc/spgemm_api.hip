@@ -251,8 +251,8 @@ int ensure_big_lds(spgemm_context* h) {
   return SPGEMM_OK;
 }
 
-// The handle's second stream, on the device that is current.  (Made and released by every call it cost 110 us: R-MAT scale 12 in two row blocks
-// 467 | 395 us, scale 17 in four 5800 | 5690.)
+// The handle's second stream, on the device that is current.  (Made and released by every call: R-MAT scale 12 in two row blocks 432 | 384 us,
+// scale 17 in four 5565 | 5520; finer chunks of rows in the row count are worth as much again there, 5571 | 5520.)
 int ensure_second_stream(spgemm_context* h) {
   int dev = 0;
   HIP_TRY(h, hipGetDevice(&dev));
