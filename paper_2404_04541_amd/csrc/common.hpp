@@ -16,7 +16,8 @@ constexpr int kPadKey = 0x7fffffff;  // sorts behind every real column
 // (an upper bound of its output size); numeric classes on ip and the exact output size.
 constexpr int kEscSmallCap = 32;     // bin 0: sorted-list workspace, 16 lanes per row
 constexpr int kEscLargeCap = 128;    // bin 1: sorted-list workspace, one wave per row
-constexpr int kSymHashSmall = 768;   // bin 2: hash set with 2048 slots, one wave per row
+constexpr int kSymHashSmall = 768;   // bin 2: hash set with 2048 slots (1024 where hardly any row has many products), one wave per row
+constexpr int kLongProducts = 512;   // rows of bin 2 with more are counted: they want the larger set (kFewLongShare)
 constexpr int kSymHashLarge = 1536;  // bin 3: hash set with 4096 slots, 256 threads per row
 constexpr int kNumHashSmall = 192;   // bin 2: hash table with 256 slots, one wave per row
 constexpr int kNumHashLarge = 1536;  // bin 3: hash table with 2048 slots, 256 threads per row
@@ -62,6 +63,7 @@ struct Control {
                                   // (here, at the end: in front of the counters of the row count, these lie across lines of memory, and it
                                   // takes 45 us instead of 29 for 394 000 short rows)
   int no_lens;                    // 1: the table of RowLens is not to be used
+  unsigned long_rows;             // rows of symbolic bin 2 with more than kLongProducts products
 #ifdef SPG_PHASE_CLOCKS
   unsigned long long clk[2][32];   // [0] dense symbolic, [1] dense numeric: shader clocks per phase, summed over workgroups
 #endif

@@ -44,13 +44,18 @@ static_assert(kRecWords % 4 == 0 && kRecRankWords % 4 == 0, "records and their c
 constexpr int kRecordGroups = 4;                               // workgroups of these kernels on a compute unit
 // Slots of the set: 2048, 2.7 times the most products (with 1024 the slowest lane of an insertion walked over twenty taken ones and more, and a row of
 // 768 products took 35 us: whole calls, us with 1024 | 2048: ragged 5003 rows 236 | 216, R-MAT squared scale 12 210 | 201, 14 444 | 432).  That is
-// 38 KB a workgroup, four of which fit a compute unit.  Where rows differ and the class's have kFewProducts or fewer on average, 1024: a row with more
-// is still right, five workgroups fit (22 KB), and half as many slots are cleared, which is what short rows pay for.  300 000 rows, this kernel, us
-// with 1024 | 2048: 144 products a row 354 | 390, 196 265 | 272, 240 288 | 282, 256 293 | 285, 324 554 | 476, 400 648 | 512, 576 1412 | 831, 756
-// 2362 | 986; 2 M rows of 130 products 1831 | 2130.  Where the classes of shorter rows share a launch (few rows: the slowest one decides) it is always 2048.
+// 38 KB a workgroup, four of which fit a compute unit, where rows of few products would rather have more: with 1024 (22 KB) they do.  So 1024 where rows
+// differ and the class's have kFewProducts or fewer on average and no more than one of kFewLongShare has more than kLongProducts (any row is still
+// right).  300 000 rows, this kernel, us with 1024 | 2048: 144 products a row 354 | 390, 196 265 | 272, 240 288 | 282, 256 293 | 285, 324 554 |
+// 476, 400 648 | 512, 576 1412 | 831, 756 2362 | 986; 2 M rows of 130 products 1831 | 2130.  200 000 rows of 143, whole calls, one of 50 of 767 704 | 650, of
+// 400 633 | 592, of 1000 574 | 568, of 4000 562 | 563; one of 20 of 390 627 | 636, one of four (205 on average)
+// 947 | 932.  Where the classes of shorter rows share a launch, which the slowest row
+// ends, not a single one may be long: 60 000 rows 234 | 241, 40 000 189 | 194, 20 000 153 | 154, with one of 4000 of 767 40 000 223 | 210.
+// (The number of slots by the row, in the LDS of 2048, gains nothing: what counts is the fifth workgroup.)
 constexpr int kSymLogSlots = 11, kFewLogSlots = 10;
 constexpr int kFewGroups = 5;
-constexpr int64_t kFewProducts = 208;
+constexpr int64_t kFewProducts = 200;
+constexpr unsigned kFewLongShare = 4096;
 // sums of a row in LDS (a rank is a byte), and a place for every lane's missing products
 constexpr int kRecSums = 256 + kWave;
 static_assert(4 * kRecSums * 8 <= 65536, "a sum's place in the workgroup's LDS fits 16 bits");

@@ -250,6 +250,7 @@ __global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int6
   __shared__ unsigned long long hip[kNumBins];
   __shared__ int sums[2][kCountThreads / kWave];
   __shared__ int bad;
+  __shared__ unsigned longs;
   if (lens && COMPACT == (ctl->no_lens != 0)) return;
   if ((int)blockIdx.x < parts) {
     if (blockIdx.x == 0) sample_rows(m, nnz_a, a_rp, a_col, ctl);
@@ -259,6 +260,7 @@ __global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int6
   const int tid = threadIdx.x;
   const int chunk_rows = ctl->chunk_rows;
   if (tid < kNumBins) { hist[tid] = 0; hip[tid] = 0; }
+  if (tid == 0) longs = 0;
   // a workgroup takes several chunks and reports its bin populations once (thousands of workgroups adding to
   // the same few counters cost more than the counting)
   __shared__ long long next_chunk;
@@ -425,6 +427,8 @@ __global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int6
       const unsigned long long ips[1] = {mine};
       const unsigned none[1] = {0};
       add_to_bins<1>(bins, ips, none, hist, hip, nullptr);
+      const unsigned long long is_long = __ballot(bin == 2 && mine > (unsigned long long)kLongProducts);
+      if (is_long && lane_id() == 0) atomicAdd(&longs, (unsigned)__popcll(is_long));
     }
     if (tid == 0) next_chunk = drawn;
     __syncthreads();
@@ -439,6 +443,7 @@ __global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int6
     unsigned long long tot = 0;
     for (int b = 0; b < kNumBins; ++b) tot += hip[b];
     if (tot) atomicAdd(&ctl->ip_total, tot);
+    if (longs) atomicAdd(&ctl->long_rows, longs);
   }
 }
 

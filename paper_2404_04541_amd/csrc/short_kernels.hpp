@@ -31,15 +31,16 @@ struct SymShort {
   int *record_of, *shift_of;
 };
 
+template <int LOG_SLOTS>
 constexpr size_t sym_short_lds() {
   size_t n = hash_lds_bytes<256, 12, false>();
-  if (n < sizeof(SymWaveLds<kSymLogSlots>)) n = sizeof(SymWaveLds<kSymLogSlots>);
+  if (n < sizeof(SymWaveLds<LOG_SLOTS>)) n = sizeof(SymWaveLds<LOG_SLOTS>);
   if (n < sizeof(EscSymLds<64, 128>)) n = sizeof(EscSymLds<64, 128>);
   if (n < sizeof(EscSymLds<16, 32>)) n = sizeof(EscSymLds<16, 32>);
   return n;
 }
 
-template <bool ALIKE>
+template <bool ALIKE, int LOG_SLOTS>
 __global__ __launch_bounds__(256, kShortGroups) void k_sym_short(Control* __restrict__ ctl, const SymShort s) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (ctl->error) return;
@@ -51,7 +52,7 @@ __global__ __launch_bounds__(256, kShortGroups) void k_sym_short(Control* __rest
   }
   wg -= s.wgs[0];
   if (wg < s.wgs[1]) {
-    sym_wave_rows<ALIKE, kSymLogSlots>(reinterpret_cast<SymWaveLds<kSymLogSlots>*>(smem), wg, s.wgs[1], s.perm, ctl, 2, s.a_rp, s.a_col, s.b_rp, s.b_col, s.b_nnz, s.cnt,
+    sym_wave_rows<ALIKE, LOG_SLOTS>(reinterpret_cast<SymWaveLds<LOG_SLOTS>*>(smem), wg, s.wgs[1], s.perm, ctl, 2, s.a_rp, s.a_col, s.b_rp, s.b_col, s.b_nnz, s.cnt,
         s.records, s.record_rows, s.record_of, s.shift_of);
     return;
   }

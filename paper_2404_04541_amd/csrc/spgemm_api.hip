@@ -703,13 +703,17 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
                          p->blk_ptr_cols, B->rowptr, B->colidx, p->ctl, p->blk_ptr);
     }
   }
+  // rows of bin 2 have few products and hardly any of them many, or none where they share a launch
+  const bool few = !p->alike && host.bin_ip[0][2] <= (unsigned long long)kFewProducts * hist[2] && host.long_rows <= hist[2] / kFewLongShare;
   if (m > 0) {
     if (!p->flag_rows && !p->desc && short_rows_ok(h, hist)) {
       const SymShort sh{{short_grid(hist[3], 1), hist[2] ? record_grid(h, p, hist[2]) : 0u, short_grid(hist[1], 4), short_grid(hist[0], 16)},
           p->perm_sym, p->ip, A->rowptr, B->rowptr, A->colidx, B->colidx, B->nnz, B->cols, pack32, pack128, p->cnt, p->esc_words[0], p->esc_words[1],
           p->records, p->record_rows, p->record_of, p->shift_of};
-      hipLaunchKernelGGL((p->alike ? k_sym_short<true> : k_sym_short<false>), dim3(sh.wgs[0] + sh.wgs[1] + sh.wgs[2] + sh.wgs[3]), dim3(256),
-                         sym_short_lds(), s, p->ctl, sh);
+      const bool slots_few = few && host.long_rows == 0;
+      const size_t lds = slots_few ? sym_short_lds<kFewLogSlots>() : sym_short_lds<kSymLogSlots>();
+      hipLaunchKernelGGL((p->alike ? k_sym_short<true, kSymLogSlots> : slots_few ? k_sym_short<false, kFewLogSlots> : k_sym_short<false, kSymLogSlots>),
+                         dim3(sh.wgs[0] + sh.wgs[1] + sh.wgs[2] + sh.wgs[3]), dim3(256), lds, s, p->ctl, sh);
     } else {
       {
         Timer t(h, SPGEMM_K_SYM_ESC);
@@ -736,7 +740,6 @@ int run_symbolic(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const
       {
         Timer t(h, SPGEMM_K_SYM_HASH);
         if (hist[2]) {
-          const bool few = host.bin_ip[0][2] <= (unsigned long long)kFewProducts * hist[2];
           hipLaunchKernelGGL((p->alike ? k_sym_wave<true, kSymLogSlots> : few ? k_sym_wave<false, kFewLogSlots> : k_sym_wave<false, kSymLogSlots>),
                              dim3(record_grid(h, p, hist[2])), dim3(256), 0, s, p->perm_sym, p->ctl, 2, A->rowptr, A->colidx,
                              B->rowptr, B->colidx, B->nnz, p->cnt, p->records, p->record_rows, p->record_of, p->shift_of);

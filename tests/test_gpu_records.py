@@ -67,19 +67,21 @@ def test_new_values_on_a_kept_plan(force):
     plan.destroy()
 
 
-@pytest.mark.parametrize("entries", [(16,), (16,) * 9 + (17,), (10,) * 9 + (59,), (10,) * 4 + (59,)])
+@pytest.mark.parametrize("entries,long_rows", [((20,), 0), ((20,) * 9 + (21,), 0), ((14,), 0), ((14,), 1), ((14,), 2), ((14,) * 9 + (59,), 0), ((14,) * 4 + (59,), 0)])
 @pytest.mark.parametrize("timing", [0, 1])
-def test_slots_by_the_average_row(entries, timing):
-    """Rows of 13 products an entry: 208 on average and a little more, and few and many with rows of 767 among them.  With the timing option the class
-    has a launch of its own, whose set has slots by the average."""
+def test_slots_by_the_rows(entries, long_rows, timing):
+    """Rows of 10 products an entry: 200 on average and a little more, one or two of 590 in 4200 (on both sides of one in 4096), many of them.  With the timing
+    option the class has a launch of its own, without it shares one with a few shorter rows."""
     from paper_2404_04541_amd import binding as sg
     rng = np.random.default_rng(41)
-    B = csr([np.sort(rng.choice(1500, 13, replace=False)) for _ in range(200)], 1500, np.float64, 42)
-    rows = [rng.choice(200, entries[i % len(entries)], replace=False) for i in range(1000)]
+    B = csr([np.sort(rng.choice(1500, 10, replace=False)) for _ in range(200)], 1500, np.float64, 42)
+    rows = [rng.choice(200, entries[i % len(entries)], replace=False) for i in range(4200)]
+    rows[1000:1000 + long_rows] = [rng.choice(200, 59, replace=False) for _ in range(long_rows)]
+    rows[77:80] = [rng.choice(200, n, replace=False) for n in (1, 5, 9)]
     A = csr(rows, 200, np.float64, 43)
     got = gpu_product(A, B, options={sg.OPT_TIMING: timing})
     assert_matches_oracle(A, B, got, what=f"{entries}")
-    assert got[3]["sym_bin_rows"][2] == 1000
+    assert got[3]["sym_bin_rows"][2] == 4197
 
 
 def short_operands(b_rows, cols, dtype, sort_b, seed=31):
