@@ -23,7 +23,7 @@ constexpr int kNumHashSmall = 192;   // bin 2: hash table with 256 slots, one wa
 constexpr int kNumHashLarge = 1536;  // bin 3: hash table with 2048 slots, 256 threads per row
 constexpr int64_t kDenseMid = 65536;     // bins 4/5/6: dense workspace, split by ip so that
 constexpr int64_t kDenseBig = 1048576;   // the heaviest rows are scheduled first
-// Rows of bin 4 of at most so many products are scheduled behind its others (see dense_light).  Whole calls, us with 0 (as they come) | 6144 | 12 288 |
+// Rows of bin 4 of at most so many products are scheduled behind its others (see light_last).  Whole calls, us with 0 (as they come) | 6144 | 12 288 |
 // 24 576: R-MAT squared scale 13 430 | 410 | 403 | 409, 14 570 | 545 | 546 | 552, 15 926 | 892 | 897 | 904, 16 1801 | 1762 | 1774 | 1774, 17 4376 | 4380 |
 // 4380 | 4359, 19 34 137 | 34 414 | 34 289 | 34 262; 20 000 ragged rows of 100 x 100 products 1146 | 1129 | 1151 | 1164, 8000 of 80 x 80 727 | 713 | 710 | 739.
 constexpr int64_t kDenseLight = 12288;

@@ -234,15 +234,18 @@ __device__ __forceinline__ void lens_row(const RowLens& g, unsigned j, int64_t* 
 // at its ends (an addition to the row's counter per entry, after a bisection for its row, was bound by LDS: 27-point
 // stencil of 128^3 rows 494 -> 377 us, 10^7 entries in rows of 2.4 128 -> 95 us, R-MAT scale 14 27 -> 20 us, scale 19 442 -> 400 us).
 // desc (optional): start and length of every A entry's B row, for the kernels of short rows.
-// Writes ip (saturated to int32), the symbolic bin (kLightBin for rows of bin 4 with at most `light` products), zero counts for rows without products.
+// Writes ip (saturated to int32), the symbolic bin (with kCountLight kLightBin for rows of bin 4 of at most kDenseLight products), zero counts for rows without products.
 // lens: of all rows of B, or reported as not to be used.  Both kernels are launched then, and the one that is not meant leaves at once (as two ways
 // inside one kernel, 4 M rows of B take 0.50 instead of 0.45 ms and an R-MAT graph of scale 20, which has no use for the table, 0.42 instead of
 // 0.40; the launch costs 10 us).
+// modes: kCountBlock, A is a block of rows; kCountLight.  (One argument: with another one the scalar registers no longer suffice and the kernel takes scratch memory,
+// 0.4 us a launch.)
+constexpr int kCountBlock = 1, kCountLight = 2;
 template <bool COMPACT>
 __global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int64_t b_cols, int64_t b_nnz, const int32_t* __restrict__ b_col,
     int64_t m, int64_t nnz_a, int64_t b_rows, const int64_t* __restrict__ a_rp, const int32_t* __restrict__ a_col, const int64_t* __restrict__ b_rp,
-    int* __restrict__ ip_out, unsigned char* __restrict__ bin_out, int* __restrict__ cnt_out, Control* ctl, int force, int row_block,
-    unsigned long long light, unsigned long long* __restrict__ desc, const RowLens* __restrict__ lens) {
+    int* __restrict__ ip_out, unsigned char* __restrict__ bin_out, int* __restrict__ cnt_out, Control* ctl, int force, int modes,
+    unsigned long long* __restrict__ desc, const RowLens* __restrict__ lens) {
   __shared__ long long rp[kCountMaxRows + 1];
   __shared__ unsigned long long ipl[kCountMaxRows];
   __shared__ __align__(16) unsigned pre[kCountThreads * 4 + 1];   // products before every entry of a round
@@ -281,8 +284,8 @@ __global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int6
     if (tid == 0) {
       if (rp[0] < 0 || rp[nr] > nnz_a) bad = 1;
       // (a block of rows of a larger matrix keeps that matrix's positions: it neither starts at 0 nor ends at nnz)
-      if (!row_block && r0 == 0 && rp[0] != 0) bad = 1;
-      if (!row_block && r0 + nr == m && rp[nr] != nnz_a) bad = 1;
+      if (!(modes & kCountBlock) && r0 == 0 && rp[0] != 0) bad = 1;
+      if (!(modes & kCountBlock) && r0 + nr == m && rp[nr] != nnz_a) bad = 1;
     }
     __syncthreads();
     if (bad) {
@@ -420,7 +423,7 @@ __global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int6
       const int bin = tid < nr ? classify_symbolic((long long)mine, force) : -1;
       if (tid < nr) {
         ip_out[r0 + tid] = mine > 0x7fffffffULL ? 0x7fffffff : (int)mine;
-        bin_out[r0 + tid] = (unsigned char)(bin == 4 && mine <= light ? kLightBin : bin);
+        bin_out[r0 + tid] = (unsigned char)(bin == 4 && (modes & kCountLight) && mine <= (unsigned long long)kDenseLight ? kLightBin : bin);
         if (bin == kEmptyBin) cnt_out[r0 + tid] = 0;
       }
       const int bins[1] = {bin};

@@ -367,14 +367,12 @@ void drop_desc(spgemm_context* h, spgemm_plan_s* p) {   // (no kernel that uses 
 // where there are too few rows to fill the card.  16384 rows of a power-law graph: 256 rows 57 us, 64 rows 27 us.
 int count_chunk(spgemm_context* h, int64_t m) { return m >= (int64_t)256 * 2 * h->num_cus ? 256 : 64; }
 
-// Up to how many products rows of bin 4 are scheduled behind the others of their bin (0: all lie as they come).  Where matrices are wide and rows many they
-// are not: the column list may be too short there, and with the rows that want flag words first the light ones, whose few columns save most of their
+// Whether rows of bin 4 of at most kDenseLight products are scheduled behind the others of their bin.  Where matrices are wide and rows many they
+// lie as they come: the column list may be too short there, and with the rows that want flag words first the light ones, whose few columns save most of their
 // tiles, found no room in it (R-MAT scale 20 squared, fp64, a list of three quarters of what all rows take: 3357 instead of 105 000 searched rows,
 // k_num_wide 90.6 | 85.4 ms, the whole call 129.3 | 124.9; a shorter list 132.9 | 132.4), and light rows among heavy ones are what run_of is after anyway (fp32 113.2 | 113.0 ms, scale 21 with 6 edges 156.5 | 156.3).  With few rows the
 // light ones fill the end (6000 rows of 60 x 400 products, 900 000 columns, 1503 | 1472 us).
-unsigned long long dense_light(spgemm_context* h, int64_t m, int64_t b_cols) {
-  return b_cols <= kSymNarrowCols || m < (int64_t)kManyRuns * h->num_cus ? (unsigned long long)kDenseLight : 0ULL;
-}
+bool light_last(spgemm_context* h, int64_t m, int64_t b_cols) { return b_cols <= kSymNarrowCols || m < (int64_t)kManyRuns * h->num_cus; }
 
 // Lengths of B's rows in a byte each for the row count: where the row pointer is half as large again as a die's 4 MB of L2 cache (600 000 rows,
 // 3 M lookups: no gain, and two launches of 10 us; 10^6 rows, 16 M lookups 225 | 169 us) and looked up more often than it has entries, and the table
@@ -404,7 +402,7 @@ int run_setup(spgemm_context* h, spgemm_plan_s* p, const spgemm_csr* A, const sp
     for (int with = lens ? 1 : 0; with >= 0; --with)
       hipLaunchKernelGGL((with ? k_count_rows<true> : k_count_rows<false>), dim3(parts + groups), dim3(kCountThreads), 0, s, (int)parts, B->cols,
                          B->nnz, B->colidx, m, A->nnz, B->rows, A->rowptr, A->colidx, B->rowptr, p->ip, p->bin, p->cnt, p->ctl, h->force,
-                         h->row_block, dense_light(h, m, B->cols), p->desc, lens);
+                         (h->row_block ? kCountBlock : 0) | (light_last(h, m, B->cols) ? kCountLight : 0), p->desc, lens);
   }
   {
     Timer t(h, SPGEMM_K_BIN);
@@ -1580,7 +1578,7 @@ int spgemm_pipelined(spgemm_handle h, const spgemm_csr* A, const spgemm_csr* B, 
     hipLaunchKernelGGL(k_init_control, dim3(1), dim3(kCountThreads), 0, h->stream, ctl, m, A->rowptr, chunk, h->num_cus, fine ? 1 : 0);
     hipLaunchKernelGGL(k_count_rows<false>, dim3(grid_for(m, fine ? kFineRows : chunk, (int64_t)h->num_cus * 2)), dim3(kCountThreads), 0, h->stream, 0, B->cols, B->nnz,
                        B->colidx, m, A->nnz, B->rows, A->rowptr, A->colidx, B->rowptr, ip, tmp + o_bin, reinterpret_cast<int*>(tmp + o_cnt), ctl, 0,
-                       0, 0ULL, (unsigned long long*)nullptr, (const RowLens*)nullptr);
+                       0, (unsigned long long*)nullptr, (const RowLens*)nullptr);
     hipLaunchKernelGGL(k_weight_sums, dim3((unsigned)tiles), dim3(kScanThreads), 0, h->stream, m, ip, sums);
     hipLaunchKernelGGL(k_block_rows, dim3(1), dim3(kScanThreads), 0, h->stream, m, tiles, nblocks, ip, sums,
                        reinterpret_cast<long long*>(tmp + o_first));
