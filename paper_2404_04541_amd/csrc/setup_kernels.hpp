@@ -234,12 +234,13 @@ __device__ __forceinline__ void lens_row(const RowLens& g, unsigned j, int64_t* 
 // at its ends (an addition to the row's counter per entry, after a bisection for its row, was bound by LDS: 27-point
 // stencil of 128^3 rows 494 -> 377 us, 10^7 entries in rows of 2.4 128 -> 95 us, R-MAT scale 14 27 -> 20 us, scale 19 442 -> 400 us).
 // desc (optional): start and length of every A entry's B row, for the kernels of short rows.
-// Writes ip (saturated to int32), the symbolic bin (with kCountLight kLightBin for rows of bin 4 of at most kDenseLight products), zero counts for rows without products.
+// Writes ip (saturated to int32), the symbolic bin (with kCountLight kLightBin for rows of bin 4 of at most kDenseLight products), zero counts for
+// rows without products.
 // lens: of all rows of B, or reported as not to be used.  Both kernels are launched then, and the one that is not meant leaves at once (as two ways
 // inside one kernel, 4 M rows of B take 0.50 instead of 0.45 ms and an R-MAT graph of scale 20, which has no use for the table, 0.42 instead of
 // 0.40; the launch costs 10 us).
-// modes: kCountBlock, A is a block of rows; kCountLight.  (One argument: with another one the scalar registers no longer suffice and the kernel takes scratch memory,
-// 0.4 us a launch.)
+// modes: kCountBlock, A is a block of rows; kCountLight.  (One argument: with another one the scalar registers no longer suffice and the kernel takes
+// scratch memory, 0.4 us a launch.)
 constexpr int kCountBlock = 1, kCountLight = 2;
 template <bool COMPACT>
 __global__ __launch_bounds__(kCountThreads, 8) void k_count_rows(int parts, int64_t b_cols, int64_t b_nnz, const int32_t* __restrict__ b_col,

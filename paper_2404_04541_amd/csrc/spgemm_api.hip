@@ -370,8 +370,9 @@ int count_chunk(spgemm_context* h, int64_t m) { return m >= (int64_t)256 * 2 * h
 // Whether rows of bin 4 of at most kDenseLight products are scheduled behind the others of their bin.  Where matrices are wide and rows many they
 // lie as they come: the column list may be too short there, and with the rows that want flag words first the light ones, whose few columns save most of their
 // tiles, found no room in it (R-MAT scale 20 squared, fp64, a list of three quarters of what all rows take: 3357 instead of 105 000 searched rows,
-// k_num_wide 90.6 | 85.4 ms, the whole call 129.3 | 124.9; a shorter list 132.9 | 132.4), and light rows among heavy ones are what run_of is after anyway (fp32 113.2 | 113.0 ms, scale 21 with 6 edges 156.5 | 156.3).  With few rows the
-// light ones fill the end (6000 rows of 60 x 400 products, 900 000 columns, 1503 | 1472 us).
+// k_num_wide 90.6 | 85.4 ms, the whole call 129.3 | 124.9; a shorter list 132.9 | 132.4), and light rows among heavy ones are
+// what run_of is after anyway (fp32 113.2 | 113.0 ms, scale 21 with 6 edges 156.5 | 156.3).  With few rows the light ones fill the end (6000 rows of
+// 60 x 400 products, 900 000 columns, 1503 | 1472 us).
 bool light_last(spgemm_context* h, int64_t m, int64_t b_cols) { return b_cols <= kSymNarrowCols || m < (int64_t)kManyRuns * h->num_cus; }
 
 // Lengths of B's rows in a byte each for the row count: where the row pointer is half as large again as a die's 4 MB of L2 cache (600 000 rows,
